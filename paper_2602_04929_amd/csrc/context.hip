@@ -40,6 +40,7 @@ extern "C" int tboa_create(tboa_ctx** out, int hip_device, void* hip_stream) {
     c->ws = nullptr; c->ws_bytes = 0;
     c->d_status = nullptr; c->h_status = nullptr; c->prof_on = 0;
     c->aux = nullptr; c->ev_fork = nullptr; c->ev_join = nullptr;
+    c->splitk[0] = c->splitk[1] = nullptr;
     for (auto& v : c->counters) v = 0;
     if (hipMalloc(&c->d_status, 256 * sizeof(int)) != hipSuccess ||
         hipHostMalloc(&c->h_status, 256 * sizeof(int)) != hipSuccess) {
@@ -47,6 +48,12 @@ extern "C" int tboa_create(tboa_ctx** out, int hip_device, void* hip_stream) {
         delete c;
         return TBOA_ENOMEM;
     }
+    if (hipMalloc(&c->splitk[0], 2 * TB_SPLITK_ELEMS * sizeof(double)) != hipSuccess) {
+        (void)hipGetLastError();
+        tboa_destroy(c);
+        return TBOA_ENOMEM;
+    }
+    c->splitk[1] = c->splitk[0] + TB_SPLITK_ELEMS;
     if (hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming) != hipSuccess) {
@@ -122,6 +129,7 @@ extern "C" void tboa_destroy(tboa_ctx* ctx) {
     for (auto& t : ctx->tile_orders) (void)hipFree(t.dev);
     for (auto& t : ctx->tile_schedules) (void)hipFree(t.dev);
     if (ctx->ws) (void)hipFree(ctx->ws);
+    if (ctx->splitk[0]) (void)hipFree(ctx->splitk[0]);
     if (ctx->d_status) (void)hipFree(ctx->d_status);
     if (ctx->h_status) (void)hipHostFree(ctx->h_status);
     delete ctx;

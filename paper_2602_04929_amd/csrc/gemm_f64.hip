@@ -3,23 +3,25 @@
 // C[b] = alpha * A[b] B[b] + beta * C[b].  A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn] with one unit
 // stride per operand, so the four transpose cases share one kernel body; the layout of an operand's LDS tile
 // follows its contiguous axis so that global loads are coalesced and LDS reads by 16-lane groups are
-// conflict-free.  Workgroup: 256 threads = 4 wavefronts (2 x 2), tile 128 x 128 x 16, each wavefront owns a
-// 64 x 64 sub-tile as 4 x 4 MFMA tiles (64 fp64 accumulators per lane).  Global -> register -> LDS software
-// pipeline with two LDS buffers, one barrier per k-step.
-// Products with at most 32 rows per batch entry (the compensation terms of a block of out-channels against a d x d
-// factor per head) run a 32 x 128 tile instead (wavefronts 1 x 4, each 32 x 32): with the 128-row tile three quarters
-// of the MFMAs would multiply padding, and those products are bound by reading B once from HBM.
+// (nearly) conflict-free.  Workgroup: 256 threads = 4 wavefronts; global -> register -> LDS software pipeline with two LDS
+// buffers, one barrier per k-step.
+//
+// One v_mfma_f64_16x16x4 occupies its SIMD for 64 cycles, so a 128 x 128 x 16 step takes a workgroup 1.9 us however little
+// else it does: a product of few tiles and a long contraction (K_g^T K_g of a head: one tile, k = 8192) ran at the speed of
+// a handful of CUs, 1.4 ms for 8 heads.  Four tile shapes and a split of the contraction spread such products over the
+// chip; the choice is a cost model over (tiles, k-steps), see choose():
+//   128 x 128 x 16  wavefronts 2 x 2, each 64 x 64 (64 fp64 accumulators per lane): the best rate when there are >= 256 tiles
+//    64 x  64 x 32  wavefronts 2 x 2, each 32 x 32
+//    32 x  32 x 64  wavefronts 2 x 2, each 16 x 16: the shortest step, for the small updates between latency-bound kernels
+//    32 x 128 x 16  wavefronts 1 x 4, each 32 x 32: at most 32 rows per batch entry, bound by reading B once from HBM
+// With a split every workgroup leaves its part of the sum in a buffer of the context and splitk_sum_kernel adds the parts in
+// a fixed order (the results do not depend on timing).
 #include "internal.h"
 #include <algorithm>
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 namespace {
-
-constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int PKC = BK + 1;   // pitch of a [row][k] tile (k-contiguous operand); odd -> conflict-free 16-lane reads
-constexpr int PMC = BM + 16;  // pitch of a [k][row] tile (row-contiguous operand): k and k+1 land 32 of the 64 LDS banks apart
-constexpr int TILE = (BM * PKC > BK * PMC) ? BM * PKC : BK * PMC;
 
 struct Args {
     int M, N, K;
@@ -32,77 +34,96 @@ struct Args {
     int klo_m, klo_n, khi_m, khi_n, skip_lower, skip_upper, skip_col0, diag_order;
     const int* m_limit;
     const double* A2; const double* B2;
+    double* part; int splits;     // splits > 1 or part given: part[(blockIdx.z)][M, N] receives the raw sum of this split
 };
 
-// Loads the BMxBK tile of an operand whose element (r, k) lives at base[r*s_r + k*s_k].
-// KC: s_k == 1 (k-contiguous), else s_r == 1.  Out-of-range elements read as zero.
-template <bool KC, int ROWS>
+constexpr int tile_pitch_kc(int bk) { return bk + 1; }          // [row][k] tile (k-contiguous operand); odd
+constexpr int tile_pitch_mc(int rows) { return rows + 16; }     // [k][row] tile (row-contiguous operand): k and k+1 land 32 of the 64 LDS banks apart
+constexpr int tile_elems(bool kc, int rows, int bk) { return kc ? rows * tile_pitch_kc(bk) : bk * tile_pitch_mc(rows); }
+
+// Loads the ROWS x BK tile of an operand whose element (r, k) lives at base[r*s_r + k*s_k].
+// KC: s_k == 1 (k-contiguous), else s_r == 1.  Indexes beyond the operand are clamped into it: what a row beyond r_lim adds
+// only reaches results that are not stored, and store_tile replaces what lies beyond k_lim by zeros (on the way to LDS, so
+// that nothing waits for the loads where they are issued).
+template <bool KC, int ROWS, int BK>
 __device__ __forceinline__ void load_tile(const double* __restrict__ base, long long s_r, long long s_k,
-                                          int r0, int k0, int r_lim, int k_lim, bool vec, double (&reg)[ROWS / 16]) {
+                                          int r0, int k0, int r_lim, int k_lim, double (&reg)[ROWS * BK / 256]) {
     const int t = threadIdx.x;
 #pragma unroll
-    for (int p = 0; p < ROWS / 32; ++p) {
+    for (int p = 0; p < ROWS * BK / 512; ++p) {
         const int idx = t + 256 * p;
-        int r, k;
-        if (KC) { r = idx >> 3; k = (idx & 7) * 2; } else { k = idx / (ROWS / 2); r = (idx % (ROWS / 2)) * 2; }
-        const int gr = r0 + r, gk = k0 + k;
-        double v0 = 0.0, v1 = 0.0;
-        if (KC) {
-            if (gr < r_lim) {
-                const double* p0 = base + (long long)gr * s_r + gk;
-                if (vec && gk + 1 < k_lim) { double2 v = *(const double2*)p0; v0 = v.x; v1 = v.y; }
-                else { if (gk < k_lim) v0 = p0[0]; if (gk + 1 < k_lim) v1 = p0[1]; }
-            }
-        } else {
-            if (gk < k_lim) {
-                const double* p0 = base + (long long)gk * s_k + gr;
-                if (vec && gr + 1 < r_lim) { double2 v = *(const double2*)p0; v0 = v.x; v1 = v.y; }
-                else { if (gr < r_lim) v0 = p0[0]; if (gr + 1 < r_lim) v1 = p0[1]; }
-            }
-        }
-        reg[2 * p] = v0; reg[2 * p + 1] = v1;
+        const int r = r0 + (KC ? idx / (BK / 2) : (idx % (ROWS / 2)) * 2), k = k0 + (KC ? (idx % (BK / 2)) * 2 : idx / (ROWS / 2));
+        const int ra = min(r, r_lim - 1), ka = min(k, k_lim - 1), rb = KC ? ra : min(r + 1, r_lim - 1), kb = KC ? min(k + 1, k_lim - 1) : ka;
+        reg[2 * p] = base[(long long)ra * s_r + (long long)ka * s_k];
+        reg[2 * p + 1] = base[(long long)rb * s_r + (long long)kb * s_k];
     }
 }
 
-template <bool KC, int ROWS>
-__device__ __forceinline__ void store_tile(double* __restrict__ lds, const double (&reg)[ROWS / 16]) {
+// The same for a tile that lies inside the operand, rows 16-byte aligned: no predicates; p0 as tile_origin gives it for the tile
+template <bool KC, int ROWS, int BK>
+__device__ __forceinline__ const double* tile_origin(const double* __restrict__ base, long long s_r, long long s_k, int r0, int k0) {
     const int t = threadIdx.x;
+    return KC ? base + (long long)(r0 + t / (BK / 2)) * s_r + k0 + (t % (BK / 2)) * 2 : base + (long long)(k0 + t / (ROWS / 2)) * s_k + r0 + (t % (ROWS / 2)) * 2;
+}
+template <bool KC, int ROWS, int BK>
+__device__ __forceinline__ void load_tile_inside(const double* __restrict__ p0, long long s_r, long long s_k, double (&reg)[ROWS * BK / 256]) {
+    const long long step = KC ? (256 / (BK / 2)) * s_r : (256 / (ROWS / 2)) * s_k;
 #pragma unroll
-    for (int p = 0; p < ROWS / 32; ++p) {
+    for (int p = 0; p < ROWS * BK / 512; ++p) {
+        const double2 v = *(const double2*)(p0 + p * step);
+        reg[2 * p] = v.x; reg[2 * p + 1] = v.y;
+    }
+}
+
+template <bool KC, int ROWS, int BK>
+__device__ __forceinline__ void store_tile(double* __restrict__ lds, const double (&in)[ROWS * BK / 256], int kvalid = BK) {
+    const int t = threadIdx.x;
+    double reg[ROWS * BK / 256];
+#pragma unroll
+    for (int i = 0; i < ROWS * BK / 256; ++i) reg[i] = in[i];
+    if (kvalid < BK) {      // contraction indices kvalid .. BK - 1 of the tile do not exist
+#pragma unroll
+        for (int p = 0; p < ROWS * BK / 512; ++p) {
+            const int idx = t + 256 * p, k = KC ? (idx % (BK / 2)) * 2 : idx / (ROWS / 2);
+            if (k >= kvalid) reg[2 * p] = 0.0;
+            if (k + (KC ? 1 : 0) >= kvalid) reg[2 * p + 1] = 0.0;
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < ROWS * BK / 512; ++p) {
         const int idx = t + 256 * p;
         if (KC) {
-            const int r = idx >> 3, k = (idx & 7) * 2;
-            lds[r * PKC + k] = reg[2 * p]; lds[r * PKC + k + 1] = reg[2 * p + 1];
+            const int r = idx / (BK / 2), k = (idx % (BK / 2)) * 2;
+            lds[r * tile_pitch_kc(BK) + k] = reg[2 * p]; lds[r * tile_pitch_kc(BK) + k + 1] = reg[2 * p + 1];
         } else {
             const int k = idx / (ROWS / 2), r = (idx % (ROWS / 2)) * 2;
-            *(double2*)(lds + k * (ROWS + 16) + r) = make_double2(reg[2 * p], reg[2 * p + 1]);
+            *(double2*)(lds + k * tile_pitch_mc(ROWS) + r) = make_double2(reg[2 * p], reg[2 * p + 1]);
         }
     }
 }
 
-// pitch of a [k][row] tile: ROWS + 16 doubles, so that k and k + 1 land 32 of the 64 LDS banks apart (ROWS = 128 or 32)
-template <bool KC, int ROWS>
+template <bool KC, int ROWS, int BK>
 __device__ __forceinline__ double lds_at(const double* __restrict__ lds, int r, int k) {
-    return KC ? lds[r * PKC + k] : lds[k * (ROWS + 16) + r];
+    return KC ? lds[r * tile_pitch_kc(BK) + k] : lds[k * tile_pitch_mc(ROWS) + r];
 }
 
-// TM: rows of the output tile, 128 (wavefronts 2 x 2, 64 x 64 each) or 32 (wavefronts 1 x 4, 32 x 32 each)
-template <bool AKC, bool BKC, int TM>
+template <bool AKC, bool BKC, int TM, int TN, int BK>
 __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool vecB) {
-    constexpr int TI = TM == 128 ? 4 : 2, TJ = TM == 128 ? 4 : 2;     // 16 x 16 MFMA tiles per wavefront
-    constexpr int ATILE = TM == 128 ? TILE : 32 * (BK + 16);          // covers [32][PKC] and [BK][32 + 16]
-    __shared__ __attribute__((aligned(16))) double As[2][ATILE];
-    __shared__ __attribute__((aligned(16))) double Bs[2][TILE];
+    constexpr int WM = TM == 32 && TN == 128 ? 1 : 2, WN = 4 / WM;      // wavefronts along the rows / columns of the tile
+    constexpr int TI = TM / WM / 16, TJ = TN / WN / 16;                 // 16 x 16 MFMA tiles per wavefront
+    __shared__ __attribute__((aligned(16))) double As[2][tile_elems(AKC, TM, BK)];
+    __shared__ __attribute__((aligned(16))) double Bs[2][tile_elems(BKC, TN, BK)];
 
     // Workgroups go to the eight XCDs round-robin by linear number, so with a column count that is a multiple of 8 an XCD
     // always gets the same tile columns; where the contraction length grows with the column (diag_order), the columns of
     // each tile row are rotated by the row number so that every XCD sees all lengths.
     const int tx = g.diag_order ? (int)((blockIdx.x + blockIdx.y) % gridDim.x) : (int)blockIdx.x;
-    const int m0 = blockIdx.y * TM, n0 = tx * BN;
-    if (g.m_limit && m0 >= g.m_limit[blockIdx.z]) return;
-    if (g.skip_lower && g.skip_col0 + n0 + BN <= m0) return;
+    const int m0 = blockIdx.y * TM, n0 = tx * TN;
+    const int bz = blockIdx.z / g.splits, sp = blockIdx.z % g.splits;
+    if (g.m_limit && m0 >= g.m_limit[bz]) return;
+    if (g.skip_lower && g.skip_col0 + n0 + TN <= m0) return;
     if (g.skip_upper && m0 + TM <= g.skip_col0 + n0) return;
-    const long long b = blockIdx.z / g.batch_inner, b2 = blockIdx.z % g.batch_inner;
+    const long long b = bz / g.batch_inner, b2 = bz % g.batch_inner;
     const double* A = g.A + b * g.strideA + b2 * g.strideA2;
     const double* B = g.B + b * g.strideB + b2 * g.strideB2;
     const double* A2 = g.A2 ? g.A2 + b * g.strideA + b2 * g.strideA2 : nullptr;
@@ -113,13 +134,18 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
     if (g.klo_m) klo = max(klo, m0);
     if (g.klo_n) klo = max(klo, n0);
     if (g.khi_m) khi = min(khi, m0 + TM);
-    if (g.khi_n) khi = min(khi, n0 + BN);
+    if (g.khi_n) khi = min(khi, n0 + TN);
     klo = (klo / BK) * BK;
+    if (g.splits > 1) {      // this workgroup's run of k-steps
+        const int steps = khi > klo ? (khi - klo + BK - 1) / BK : 0, per = (steps + g.splits - 1) / g.splits;
+        const int lo = klo + sp * per * BK;
+        khi = min(khi, lo + per * BK); klo = lo;
+    }
     const int nk1 = khi > klo ? (khi - klo + BK - 1) / BK : 0;      // k-steps of one pair of operands
     const int nk = A2 ? 2 * nk1 : nk1;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int wm = TM == 128 ? (wave >> 1) * 64 : 0, wn = TM == 128 ? (wave & 1) * 64 : wave * 32;
+    const int wm = (wave / WN) * (TM / WM), wn = (wave % WN) * (TN / WN);
     const int l16 = lane & 15, lk = lane >> 4;
 
     v4d acc[TI][TJ];
@@ -128,44 +154,75 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
 #pragma unroll
         for (int j = 0; j < TJ; ++j) acc[i][j] = (v4d){0.0, 0.0, 0.0, 0.0};
 
-    double ra[TM / 16], rb[8];
-    if (nk > 0) {
-        load_tile<AKC, TM>(A, g.sa_r, g.sa_k, m0, klo, g.M, khi, vecA, ra);
-        load_tile<BKC, BN>(B, g.sb_r, g.sb_k, n0, klo, g.N, khi, vecB, rb);
-        store_tile<AKC, TM>(As[0], ra);
-        store_tile<BKC, BN>(Bs[0], rb);
-    }
-    __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        if (kt + 1 < nk) {
-            const bool second = kt + 1 >= nk1;
-            const int k0 = klo + (kt + 1 - (second ? nk1 : 0)) * BK;
-            load_tile<AKC, TM>(second ? A2 : A, g.sa_r, g.sa_k, m0, k0, g.M, khi, vecA, ra);
-            load_tile<BKC, BN>(second ? B2 : B, g.sb_r, g.sb_k, n0, k0, g.N, khi, vecB, rb);
-        }
+    double ra[TM * BK / 256], rb[TN * BK / 256];
+    auto multiply = [&](int cur) {
 #pragma unroll
         for (int k4 = 0; k4 < BK / 4; ++k4) {
             double a[TI], bb[TJ];
 #pragma unroll
-            for (int i = 0; i < TI; ++i) a[i] = lds_at<AKC, TM>(As[cur], wm + 16 * i + l16, 4 * k4 + lk);
+            for (int i = 0; i < TI; ++i) a[i] = lds_at<AKC, TM, BK>(As[cur], wm + 16 * i + l16, 4 * k4 + lk);
 #pragma unroll
-            for (int j = 0; j < TJ; ++j) bb[j] = lds_at<BKC, BN>(Bs[cur], wn + 16 * j + l16, 4 * k4 + lk);
+            for (int j = 0; j < TJ; ++j) bb[j] = lds_at<BKC, TN, BK>(Bs[cur], wn + 16 * j + l16, 4 * k4 + lk);
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
                 for (int j = 0; j < TJ; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], bb[j], acc[i][j], 0, 0, 0);
         }
-        if (kt + 1 < nk) {
-            store_tile<AKC, TM>(As[cur ^ 1], ra);
-            store_tile<BKC, BN>(Bs[cur ^ 1], rb);
-        }
+    };
+    auto stage = [&](int buf, int kvalid = BK) { store_tile<AKC, TM, BK>(As[buf], ra, kvalid); store_tile<BKC, TN, BK>(Bs[buf], rb, kvalid); };
+    const int tail = khi > klo ? (khi - klo) % BK : 0, nfull = tail ? nk - 1 : nk;
+    if (vecA && vecB && m0 + TM <= g.M && n0 + TN <= g.N && nfull > 0 && !(tail && A2)) {
+        // every whole k-step of this workgroup lies inside the operands: 16-byte loads, one address per load.  (With the edge
+        // loads in the same loop the compiler waits for each of them before the next: 58.6 instead of 66.3 TFLOP/s on 8192^3.)
+        const double* pa = tile_origin<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo);
+        const double* pb = tile_origin<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo);
+        const long long da = AKC ? BK : BK * g.sa_k, db = BKC ? BK : BK * g.sb_k;
+        load_tile_inside<AKC, TM, BK>(pa, g.sa_r, g.sa_k, ra);
+        load_tile_inside<BKC, TN, BK>(pb, g.sb_r, g.sb_k, rb);
+        stage(0);
         __syncthreads();
+        for (int kt = 0; kt < nfull - 1; ++kt) {
+            pa += da; pb += db;
+            if (kt + 1 == nk1) {
+                pa = tile_origin<AKC, TM, BK>(A2, g.sa_r, g.sa_k, m0, klo);
+                pb = tile_origin<BKC, TN, BK>(B2, g.sb_r, g.sb_k, n0, klo);
+            }
+            load_tile_inside<AKC, TM, BK>(pa, g.sa_r, g.sa_k, ra);
+            load_tile_inside<BKC, TN, BK>(pb, g.sb_r, g.sb_k, rb);
+            multiply(kt & 1);
+            stage((kt & 1) ^ 1);
+            __syncthreads();
+        }
+        if (tail) {
+            load_tile<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo + nfull * BK, g.M, khi, ra);
+            load_tile<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo + nfull * BK, g.N, khi, rb);
+        }
+        multiply((nfull - 1) & 1);
+        if (tail) {
+            stage(nfull & 1, tail);
+            __syncthreads();
+            multiply(nfull & 1);
+        }
+    } else if (nk > 0) {
+        load_tile<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo, g.M, khi, ra);
+        load_tile<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo, g.N, khi, rb);
+        stage(0, min(BK, khi - klo));
+        __syncthreads();
+        for (int kt = 0; kt < nk - 1; ++kt) {
+            const bool second = kt + 1 >= nk1;
+            const int k0 = klo + (kt + 1 - (second ? nk1 : 0)) * BK;
+            load_tile<AKC, TM, BK>(second ? A2 : A, g.sa_r, g.sa_k, m0, k0, g.M, khi, ra);
+            load_tile<BKC, TN, BK>(second ? B2 : B, g.sb_r, g.sb_k, n0, k0, g.N, khi, rb);
+            multiply(kt & 1);
+            stage((kt & 1) ^ 1, min(BK, khi - k0));
+            __syncthreads();
+        }
+        multiply((nk - 1) & 1);
     }
 
     // accumulator element v of tile (i, j): row 16 i + lane / 16 + 4 v, column 16 j + lane % 16
+    double* P = g.part ? g.part + (long long)blockIdx.z * g.M * g.N : nullptr;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -176,12 +233,68 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
             for (int j = 0; j < TJ; ++j) {
                 const int col = n0 + wn + 16 * j + l16;
                 if (col >= g.N) continue;
+                if (P) { P[(long long)row * g.N + col] = acc[i][j][v]; continue; }
                 double* c = C + (long long)row * g.ldc + col;
                 double r = g.alpha * acc[i][j][v];
                 if (g.beta != 0.0) r += g.beta * (*c);
                 *c = r;
             }
         }
+}
+
+// C[b][m, n] = alpha * sum_p part[b P + p][m, n] + beta * C[b][m, n], the parts added in increasing p.  `inner` consecutive results
+// (b = outer * inner + i) lie at C + outer * sC1 + i * sC2.
+__global__ __launch_bounds__(256) void splitk_sum_kernel(const double* __restrict__ part, int P, int M, int N, int nres, int inner, double alpha, double beta,
+                                                         double* __restrict__ C, long long ldc, long long sC1, long long sC2) {
+    const long long mn = (long long)M * N, total = mn * nres;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
+        const long long b = i / mn, e = i - b * mn;
+        const double* p = part + b * P * mn + e;
+        double s = 0.0;
+        for (int k = 0; k < P; ++k) s += p[k * mn];
+        double* c = C + (b / inner) * sC1 + (b % inner) * sC2 + (e / N) * ldc + e % N;
+        double r = alpha * s;
+        if (beta != 0.0) r += beta * (*c);
+        *c = r;
+    }
+}
+
+enum Shape { S128, S64, S32, SKINNY };
+struct Choice { Shape shape; int splits; };
+constexpr int TILE_M[4] = {128, 64, 32, 32}, TILE_N[4] = {128, 64, 32, 128}, TILE_K[4] = {16, 32, 64, 16};
+// microseconds a workgroup takes for 16 contraction indices, measured on contractions of 2048 and more with 256 - 512 tiles in flight:
+// the MFMAs bind the large tile (64 of them per SIMD take 1.8 us), loads, LDS and the barrier have a growing part in the small ones
+constexpr double STEP_US[4] = {2.1, 0.78, 0.32, 0.8};
+
+// Tile shape and number of splits of least modelled time: rounds of 256 workgroups, each of the contraction's steps, plus the
+// second kernel and the traffic of the parts when there is a split.
+Choice choose(const GemmF64& q, bool akc, size_t part_elems, int sum) {
+    const double k16 = std::max(1.0, q.K / 16.0 * (q.A2 ? 2.0 : 1.0));
+    const bool in_place = q.C == q.A || q.C == q.B;               // needs whole rows per workgroup: one column of tiles, no other order
+    const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.A2 || in_place;
+    Choice best{S128, 1}; double best_us = 1e30;
+    for (int s = 0; s < 4; ++s) {
+        if (s == SKINNY && !(q.M <= 32 && akc)) continue;
+        if (in_place && cdiv64(q.N, TILE_N[s]) > 1 && s != S128) continue;
+        const double tiles = (double)cdiv64(q.M, TILE_M[s]) * cdiv64(q.N, TILE_N[s]) * q.batch;
+        for (int sp = 1; sp <= (no_split ? 1 : 64); sp *= 2) {
+            if (sp > 1 && (q.K / TILE_K[s] < 2 * sp || tiles * sp > 1024)) break;
+            const bool parts = sp > 1 || sum > 1;
+            if (parts && (double)q.M * q.N * q.batch * sp > (double)part_elems) break;
+            double us = ceil(tiles * sp / 256.0) * (k16 / sp * STEP_US[s] + 2.0);
+            if (parts) us += 5.0 + (double)q.M * q.N * q.batch * sp * 16.0 / 3e6;
+            if (us < best_us) { best_us = us; best = Choice{(Shape)s, sp}; }
+        }
+    }
+    return best;
+}
+
+template <int TM, int TN, int BK>
+void launch(tboa_ctx* ctx, dim3 grid, bool akc, bool bkc, const Args& a, bool vecA, bool vecB) {
+    if (akc && bkc) hipLaunchKernelGGL((gemm_f64_kernel<true, true, TM, TN, BK>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
+    else if (akc) hipLaunchKernelGGL((gemm_f64_kernel<true, false, TM, TN, BK>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
+    else if (bkc) hipLaunchKernelGGL((gemm_f64_kernel<false, true, TM, TN, BK>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
+    else hipLaunchKernelGGL((gemm_f64_kernel<false, false, TM, TN, BK>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
 }
 
 }  // namespace
@@ -204,38 +317,62 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
     a.A2 = q.A2; a.B2 = q.A2 ? q.B2 : nullptr;
     if (q.A2 && (!q.B2 || q.klo_m || q.klo_n || q.khi_m || q.khi_n)) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: a second operand pair needs both operands and an unrestricted contraction");
     a.skip_lower = q.skip_lower; a.skip_upper = q.skip_upper; a.skip_col0 = q.skip_col0; a.m_limit = q.m_limit; a.diag_order = q.diag_order;
+    // sum_inner: the inner batch entries are terms of one result
+    const int sum = q.sum_inner ? a.batch_inner : 1;
+    if (q.sum_inner && (q.batch % a.batch_inner || q.skip_lower || q.skip_upper || q.m_limit)) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: summed batch entries need whole groups and whole results");
     // 16-byte vector loads need every row start and the tile offsets (even) to stay 16-byte aligned
     const bool vecA = ((uintptr_t)q.A % 16 == 0) && ((uintptr_t)q.A2 % 16 == 0) && (q.strideA % 2 == 0) && (q.strideA2 % 2 == 0) && ((akc ? q.sam : q.sak) % 2 == 0);
     const bool vecB = ((uintptr_t)q.B % 16 == 0) && ((uintptr_t)q.B2 % 16 == 0) && (q.strideB % 2 == 0) && (q.strideB2 % 2 == 0) && ((bkc ? q.sbn : q.sbk) % 2 == 0);
+    double* part = ctx->splitk[ctx->stream == ctx->aux ? 1 : 0];
+    if (sum > 1 && (!part || (size_t)q.M * q.N * q.batch > TB_SPLITK_ELEMS)) {      // the terms one after the other
+        GemmF64 one = q;
+        one.sum_inner = 0; one.batch = q.batch / a.batch_inner; one.batch_inner = 1;
+        for (int r = 0; r < a.batch_inner; ++r) {
+            one.A = q.A + r * q.strideA2; one.B = q.B + r * q.strideB2; one.beta = r ? 1.0 : q.beta;
+            TB_TRY(gemm_f64(ctx, one));
+        }
+        return 0;
+    }
+    const Choice ch = choose(q, akc, part ? TB_SPLITK_ELEMS : 0, sum);
+    const int tm = TILE_M[ch.shape], tn = TILE_N[ch.shape];
     // algorithmic flops of a tagged launch: 2 M N K per batch entry over the contraction range each output tile really has;
     // a launch whose row count comes from device memory (m_limit) is timed but not counted
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on && q.tag >= 0) {
         double macs = 0.0;
         if (!q.m_limit)
-            for (int m0 = 0; m0 < q.M; m0 += BM)
-                for (int n0 = 0; n0 < q.N; n0 += BN) {
-                    if (q.skip_lower && q.skip_col0 + n0 + BN <= m0) continue;
-                    if (q.skip_upper && m0 + BM <= q.skip_col0 + n0) continue;
+            for (int m0 = 0; m0 < q.M; m0 += tm)
+                for (int n0 = 0; n0 < q.N; n0 += tn) {
+                    if (q.skip_lower && q.skip_col0 + n0 + tn <= m0) continue;
+                    if (q.skip_upper && m0 + tm <= q.skip_col0 + n0) continue;
                     int klo = 0, khi = q.K;
                     if (q.klo_m) klo = std::max(klo, m0);
                     if (q.klo_n) klo = std::max(klo, n0);
-                    if (q.khi_m) khi = std::min(khi, m0 + BM);
-                    if (q.khi_n) khi = std::min(khi, n0 + BN);
-                    if (khi > klo) macs += (double)std::min(BM, q.M - m0) * std::min(BN, q.N - n0) * (khi - klo) * (q.A2 ? 2.0 : 1.0);
+                    if (q.khi_m) khi = std::min(khi, m0 + tm);
+                    if (q.khi_n) khi = std::min(khi, n0 + tn);
+                    if (khi > klo) macs += (double)std::min(tm, q.M - m0) * std::min(tn, q.N - n0) * (khi - klo) * (q.A2 ? 2.0 : 1.0);
                 }
         TB_TRY(prof_begin(ctx, q.tag, 2.0 * macs * q.batch, rec, timed));
     }
-    const bool skinny = q.M <= 32 && akc;
-    dim3 grid((unsigned)cdiv64(q.N, BN), (unsigned)cdiv64(q.M, skinny ? 32 : BM), (unsigned)q.batch);
-    if (grid.y > 65535 || grid.z > 65535) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: grid too large");
-    if (skinny && bkc) hipLaunchKernelGGL((gemm_f64_kernel<true, true, 32>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
-    else if (skinny) hipLaunchKernelGGL((gemm_f64_kernel<true, false, 32>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
-    else if (akc && bkc) hipLaunchKernelGGL((gemm_f64_kernel<true, true, BM>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
-    else if (akc && !bkc) hipLaunchKernelGGL((gemm_f64_kernel<true, false, BM>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
-    else if (!akc && bkc) hipLaunchKernelGGL((gemm_f64_kernel<false, true, BM>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
-    else hipLaunchKernelGGL((gemm_f64_kernel<false, false, BM>), grid, dim3(256), 0, ctx->stream, a, vecA, vecB);
+    a.splits = ch.splits;
+    a.part = (ch.splits > 1 || sum > 1) ? part : nullptr;
+    dim3 grid((unsigned)cdiv64(q.N, tn), (unsigned)cdiv64(q.M, tm), (unsigned)(q.batch * ch.splits));
+    if (grid.y > 65535 || cdiv64(q.batch, 1) * ch.splits > 65535) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: grid too large");
+    switch (ch.shape) {
+        case S128: launch<128, 128, 16>(ctx, grid, akc, bkc, a, vecA, vecB); break;
+        case S64: launch<64, 64, 32>(ctx, grid, akc, bkc, a, vecA, vecB); break;
+        case S32: launch<32, 32, 64>(ctx, grid, akc, bkc, a, vecA, vecB); break;
+        default: launch<32, 128, 16>(ctx, grid, true, bkc, a, vecA, vecB);
+    }
     TB_KERNEL_CHECK(ctx);
+    if (a.part) {
+        const int nres = q.batch / sum, inner = sum > 1 ? 1 : a.batch_inner;
+        const long long total = (long long)q.M * q.N * nres;
+        const long long gb = std::min<long long>((total + 255) / 256, 16384);
+        hipLaunchKernelGGL(splitk_sum_kernel, dim3((unsigned)gb), dim3(256), 0, ctx->stream, part, sum * ch.splits, q.M, q.N, nres, inner, q.alpha, q.beta,
+                           q.C, (long long)q.ldc, (long long)q.strideC, (long long)q.strideC2);
+        TB_KERNEL_CHECK(ctx);
+    }
     TB_TRY(prof_end(ctx, rec, timed));
     return 0;
 }

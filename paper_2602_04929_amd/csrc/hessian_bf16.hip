@@ -698,10 +698,23 @@ __global__ __launch_bounds__(256) void splitk_reduce_lower_kernel(const float* _
     }
 }
 
-__global__ void bcast_heads_kernel(const double* __restrict__ src, float* __restrict__ dst, int rep, long long per, long long total) {
+// dst[h] = src[h / rep] for matrices of dh x dh, or (sym) src[h / rep] + its transpose
+__global__ void bcast_heads_kernel(const double* __restrict__ src, float* __restrict__ dst, int rep, int dh, long long total, int sym) {
+    const long long per = (long long)dh * dh;
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
         const long long h = i / per, e = i % per;
-        dst[i] = (float)src[(h / rep) * per + e];
+        const double* m = src + (h / rep) * per;
+        dst[i] = (float)(sym ? m[e] + m[(e % dh) * dh + e / dh] : m[e]);
+    }
+}
+
+// T = the lower triangle of the symmetric H with half its diagonal, zeros above: H = T + T^T, so that W H W^T = W T W^T + its
+// transpose needs only the contraction indices k >= column of the wide product W T
+__global__ void lower_half_f64_kernel(const float* __restrict__ H, double* __restrict__ T, int n) {
+    const long long nn = (long long)n * n;
+    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < nn; i += (long long)gridDim.x * blockDim.x) {
+        const int r = (int)(i / n), c = (int)(i % n);
+        T[i] = c < r ? (double)H[i] : c == r ? 0.5 * (double)H[i] : 0.0;
     }
 }
 
@@ -992,13 +1005,16 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, T, 1.0, 1, part, Hin_qk));
     if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, T, d->alpha, 0, part, R_qk));
     // ---- H_out: K_g^T K_g = W_K,g H_in W_K,g^T ; sum_h Q_h^T Q_h ; sum_h W_out,h^T W_out,h   (fp64)
-    TB_TRY(launch_cvt_f32_to_f64(ctx, Hin_qk, Hin64, dd));
+    // (the wide product W_Q H_in, d_q x d x d, is taken with the triangular half of H_in; the d_h x d_h products of a group's heads
+    // are one launch whose terms are summed in fp64: as one launch per head of the group they ran on n_kv_heads workgroups)
+    hipLaunchKernelGGL(lower_half_f64_kernel, dim3(g1(dd)), dim3(256), 0, st, Hin_qk, Hin64, dm);
+    TB_KERNEL_CHECK(ctx);
     TB_TRY(launch_cvt_to_f64(ctx, Wq, TBOA_BF16, Wq64, (int64_t)dq * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wk, TBOA_BF16, Wk64, (int64_t)dkv * dm));
     {
         GemmF64 a{};
         a.M = dq; a.N = dm; a.K = dm; a.alpha = 1.0; a.beta = 0.0; a.A = Wq64; a.sam = dm; a.sak = 1; a.B = Hin64; a.sbk = dm; a.sbn = 1;
-        a.C = Tq; a.ldc = dm; a.batch = 1;
+        a.C = Tq; a.ldc = dm; a.batch = 1; a.klo_n = 1; a.diag_order = 1;
         TB_TRY(gemm_f64(ctx, a));
         a.M = dkv; a.A = Wk64; a.C = Tk;
         TB_TRY(gemm_f64(ctx, a));
@@ -1006,26 +1022,22 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
         b.M = dh; b.N = dh; b.K = dm; b.alpha = 1.0; b.beta = 0.0; b.A = Tk; b.sam = dm; b.sak = 1; b.B = Wk64; b.sbk = 1; b.sbn = dm;
         b.C = Ho; b.ldc = dh; b.batch = Hkv; b.strideA = (long long)dh * dm; b.strideB = b.strideA; b.strideC = hh;
         TB_TRY(gemm_f64(ctx, b));
-        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hq * hh)), dim3(256), 0, st, Ho, Hout_q, rep, hh, Hq * hh);
-        for (int r = 0; r < rep; ++r) {   // sum over the query heads of a group
-            b.A = Tq + (long long)r * dh * dm; b.B = Wq64 + (long long)r * dh * dm; b.beta = r ? 1.0 : 0.0;
-            b.strideA = (long long)rep * dh * dm; b.strideB = b.strideA;
-            TB_TRY(gemm_f64(ctx, b));
-        }
-        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hkv * hh)), dim3(256), 0, st, Ho, Hout_k, 1, hh, Hkv * hh);
+        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hq * hh)), dim3(256), 0, st, Ho, Hout_q, rep, dh, Hq * hh, 1);
+        b.A = Tq; b.B = Wq64; b.batch = Hkv * rep; b.batch_inner = rep; b.sum_inner = 1;      // sum over the query heads of a group
+        b.strideA2 = (long long)dh * dm; b.strideB2 = b.strideA2; b.strideA = rep * b.strideA2; b.strideB = b.strideA;
+        TB_TRY(gemm_f64(ctx, b));
+        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hkv * hh)), dim3(256), 0, st, Ho, Hout_k, 1, dh, Hkv * hh, 1);
         TB_KERNEL_CHECK(ctx);
     }
     }
     if (Hout_v) {
         TB_TRY(launch_cvt_to_f64(ctx, Wo, TBOA_BF16, Wo64, (int64_t)dm * dq));
-        GemmF64 c{};   // W_out,h^T W_out,h, W_out,h = Wo[:, h dh : (h+1) dh]
-        c.M = dh; c.N = dh; c.K = dm; c.alpha = 1.0; c.sam = 1; c.sak = dq; c.sbk = dq; c.sbn = 1; c.C = Ho; c.ldc = dh;
-        c.batch = Hkv; c.strideA = (long long)rep * dh; c.strideB = c.strideA; c.strideC = hh;
-        for (int r = 0; r < rep; ++r) {
-            c.A = Wo64 + (long long)r * dh; c.B = c.A; c.beta = r ? 1.0 : 0.0;
-            TB_TRY(gemm_f64(ctx, c));
-        }
-        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hkv * hh)), dim3(256), 0, st, Ho, Hout_v, 1, hh, Hkv * hh);
+        GemmF64 c{};   // sum over the group's heads of W_out,h^T W_out,h, W_out,h = Wo[:, h dh : (h+1) dh]
+        c.M = dh; c.N = dh; c.K = dm; c.alpha = 1.0; c.beta = 0.0; c.sam = 1; c.sak = dq; c.sbk = dq; c.sbn = 1; c.C = Ho; c.ldc = dh;
+        c.A = Wo64; c.B = Wo64; c.batch = Hkv * rep; c.batch_inner = rep; c.sum_inner = 1;
+        c.strideA2 = dh; c.strideB2 = dh; c.strideA = (long long)rep * dh; c.strideB = c.strideA; c.strideC = hh;
+        TB_TRY(gemm_f64(ctx, c));
+        hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hkv * hh)), dim3(256), 0, st, Ho, Hout_v, 1, dh, Hkv * hh, 0);
         TB_KERNEL_CHECK(ctx);
     }
     // ---- H_in (and R) of W_V
@@ -1654,10 +1666,9 @@ extern "C" int tboa_build_hout(tboa_ctx* ctx, int d_in, int n_heads, int rep, in
     GemmF64 b{};      // per head of the result: sum over its rep row blocks of TW_h W_h^T
     b.M = head_dim; b.N = head_dim; b.K = d_in; b.alpha = 1.0; b.sam = d_in; b.sak = 1; b.sbk = 1; b.sbn = d_in;
     b.C = Ho; b.ldc = head_dim; b.batch = n_heads; b.strideA = (long long)rep * head_dim * d_in; b.strideB = b.strideA; b.strideC = hh;
-    for (int r = 0; r < rep; ++r) {
-        b.A = TW + (long long)r * head_dim * d_in; b.B = W64 + (long long)r * head_dim * d_in; b.beta = r ? 1.0 : 0.0;
-        TB_TRY(gemm_f64(ctx, b));
-    }
+    b.A = TW; b.B = W64; b.beta = 0.0; b.batch = n_heads * rep; b.batch_inner = rep; b.sum_inner = 1;
+    b.strideA2 = (long long)head_dim * d_in; b.strideB2 = b.strideA2;
+    TB_TRY(gemm_f64(ctx, b));
     return launch_cvt_f64_to_f32(ctx, Ho, H_out, (int64_t)n_heads * hh);
 }
 
@@ -1701,7 +1712,7 @@ extern "C" int tboa_build_hout_q_kv_cache(tboa_ctx* ctx, const tboa_attn_desc* d
         c.C = Ho; c.ldc = dh; c.batch = Hkv; c.strideA = dh; c.strideB = dh; c.strideC = hh;
         TB_TRY(gemm_f64(ctx, c));
     }
-    hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hq * hh)), dim3(256), 0, ctx->stream, Ho, Hout_q, rep, hh, Hq * hh);
+    hipLaunchKernelGGL(bcast_heads_kernel, dim3(g1(Hq * hh)), dim3(256), 0, ctx->stream, Ho, Hout_q, rep, dh, Hq * hh, 0);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }

@@ -26,6 +26,7 @@ struct tboa_ctx {
     int* h_status;       // pinned host mirror
     hipStream_t aux;     // second stream (default priority) for work of one call that is independent of what `stream` does
     hipEvent_t ev_fork, ev_join;
+    double* splitk[2];   // partial sums of split fp64 contractions, TB_SPLITK_ELEMS each: launches on `stream`, launches on `aux`
     int prof_on;         // record HIP events around tagged GEMM launches
     std::vector<ProfRec> prof;
     long long counters[8];   // tboa_counter_id
@@ -36,6 +37,7 @@ struct tboa_ctx {
 };
 
 #define TB_GSTAT_WORD 8
+#define TB_SPLITK_ELEMS ((size_t)1 << 22)     // 32 MiB
 int tboa_fail(tboa_ctx* ctx, int code, const char* fmt, ...);
 
 #define TB_HIP(ctx, call)                                                                          \
@@ -96,6 +98,7 @@ struct GemmF64 {
     // optional second pair of operands with the shapes, strides and batch strides of the first:
     // C = alpha (A B + A2 B2) + beta C in one pass (not combined with the contraction-range restrictions)
     const double* A2 = nullptr; const double* B2 = nullptr;
+    int sum_inner = 0;   // C[outer] = alpha * sum over the batch_inner entries of A B + beta * C[outer] (strideC2 unused)
     int tag = -1;   // tboa_prof_tag of this launch (timed with HIP events when profiling is on)
 };
 int gemm_f64(tboa_ctx* ctx, const GemmF64& g);

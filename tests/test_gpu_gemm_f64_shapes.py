@@ -1,0 +1,51 @@
+"""fp64 GEMM over the tile shapes and contraction splits its dispatch chooses from, against numpy in fp64.
+
+Tolerance: a dot product of K terms of N(0, 1) factors accumulated in any order stays within K * 2^-53 * sum |a b| <= K^2 2^-53 of the
+exact value; 1e-13 relative to the result's norm covers K <= 4100 with a wide margin (observed 3e-15)."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+# (batch, M, N, K): one tile and long contractions (split), tile edges +- 1, a row count of the skinny shape, many tiles, an odd
+# pitch (no 16-byte loads), a contraction that is no whole step, an empty one
+CASES = [(1, 128, 128, 4096), (8, 128, 128, 1024), (1, 129, 127, 515), (2, 64, 64, 32), (1, 65, 63, 33), (3, 32, 256, 96), (2, 31, 130, 1000),
+         (1, 33, 33, 2050), (1, 1, 1, 1), (1, 7, 300, 64), (1, 1000, 1000, 250), (1, 500, 501, 77), (40, 128, 128, 128), (1, 600, 1300, 256), (1, 20, 20, 0)]
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_gemm_f64_shapes(lib, case, ta, tb):
+    b, M, N, K = case
+    rng = np.random.default_rng(b * 7919 + M * 31 + N * 17 + K)
+    A = rng.standard_normal((b, K, M) if ta else (b, M, K)); B = rng.standard_normal((b, N, K) if tb else (b, K, N))
+    C0 = rng.standard_normal((b, M, N))
+    ctx = lib.Context()
+    dev = lambda x: torch.from_numpy(x).cuda()
+    if K == 0:      # the binding derives the strides from the shapes: an empty operand still needs an address
+        A = np.zeros((b, 1, M) if ta else (b, M, 1)); B = np.zeros((b, N, 1) if tb else (b, 1, N))
+    ref = (np.swapaxes(A, 1, 2) if ta else A) @ (np.swapaxes(B, 1, 2) if tb else B)
+    got = ctx.gemm_f64(dev(A), dev(B), transA=bool(ta), transB=bool(tb)).cpu().numpy()
+    tol = 1e-13 * max(np.linalg.norm(ref), 1.0)
+    assert np.linalg.norm(got - ref) <= tol
+    acc = dev(C0)
+    ctx.gemm_f64(dev(A), dev(B), acc, alpha=-0.5, beta=2.0, transA=bool(ta), transB=bool(tb))
+    want = 2.0 * C0 - 0.5 * ref
+    assert np.linalg.norm(acc.cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want) + tol
+    ctx.close()
+
+
+@pytest.mark.parametrize("rep,dh,d", [(8, 128, 1024), (3, 100, 520), (1, 64, 4096), (5, 33, 65)])
+def test_hout_sums_the_heads_of_a_group(lib, rep, dh, d):
+    """build_hout adds the d_h x d_h products of a group's heads in one launch (or, where the parts do not fit the buffer, one by one)."""
+    rng = np.random.default_rng(rep * 100 + dh)
+    X = rng.standard_normal((2 * d, d)); H = (X.T @ X).astype(np.float32)
+    nh = 3
+    W = (0.02 * rng.standard_normal((nh * rep * dh, d))).astype(np.float32)
+    ctx = lib.Context()
+    got = ctx.build_hout(torch.from_numpy(H).cuda(), torch.from_numpy(W).cuda(), nh, rep, dh).cpu().numpy().astype(np.float64)
+    W64 = W.astype(np.float64).reshape(nh, rep, dh, d)
+    want = np.stack([sum(W64[g, r] @ H.astype(np.float64) @ W64[g, r].T for r in range(rep)) for g in range(nh)])
+    assert np.abs(got - want).max() <= 2.0 ** -23 * np.abs(want).max()      # the rounding of the fp32 result
+    ctx.close()
