@@ -57,7 +57,7 @@ void tboa_destroy(tboa_ctx* ctx);
 const char* tboa_last_error(const tboa_ctx* ctx);
 /* Event counters of this context since its creation (host values).
  * TBOA_CTR_GRID_PASSES: grid-search passes that used the two-phase search (approximate costs of all candidates on the
- * bf16 matrix cores, exact fp64 costs of the near-minimal ones); TBOA_CTR_GRID_FALLBACKS: tboa_quantize_layer calls whose
+ * 16-bit matrix cores, exact fp64 costs of the near-minimal ones); TBOA_CTR_GRID_FALLBACKS: tboa_quantize_layer calls whose
  * two-phase search did not trust itself (see tboa_layer_desc.grid_guard) and that were therefore run again with every
  * candidate of every row evaluated in fp64; TBOA_CTR_GRID_EXACT_ROWS: unused, always 0;
  * TBOA_CTR_GRID_SURVIVORS: near-minimal candidates that were evaluated exactly (rows with a single near-minimal
@@ -211,10 +211,10 @@ typedef struct {
     double max_shrink;  /* candidates k = 0 .. ceil(max_shrink*grid_points)-1, range scaled by 1-k/grid_points */
     double damp;        /* every Hessian gets damp * mean(diag) added to its diagonal at entry        */
     double grid_guard;  /* the grid search of wide per-row layers (d_in >= 256, group = 0) finds its candidates' costs
-                           approximately on the bf16 matrix cores and re-evaluates the near-minimal ones (within tau = 2e-3
+                           approximately on the 16-bit matrix cores and re-evaluates the near-minimal ones (within tau = 2e-3
                            of the minimum) in fp64; every re-evaluation is compared with its approximation, and a call in
                            which one differs by more than grid_guard * tau (relative) is run again with fp64 costs for every
-                           candidate.  0: the default, 0.25.  Negative: fp64 costs for every candidate from the start. */
+                           candidate (where H_in went in as one half term: with two terms first).  0: the default, 0.25.  Negative: fp64 costs for every candidate from the start. */
 } tboa_layer_desc;
 
 /* Workspace that tboa_quantize_layer needs for this descriptor, called with (with_H_out != 0) or without H_out and with

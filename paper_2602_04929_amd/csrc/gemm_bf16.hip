@@ -60,6 +60,9 @@ struct Args {
     // term_dB bytes (the distance to the next pair's buffer less the columns just read); term_segs = 0: one pair
     int term_segs;
     long long term_dA[3], term_dB[3];
+    // dispatched LDS-direct kernel, repeated left operand: every segment reads the same columns of A, segment t of B lies t * rep_dB bytes
+    // on, and segs[batch entry] (device memory) says how many segments there are; rep_dB = 0: ordinary segments
+    long long rep_dB; const int* segs;
 };
 
 // Work item of this workgroup.  Workgroups are dealt to the eight XCDs round-robin by their linear number, so workgroup
@@ -382,7 +385,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     const __hip_bfloat16* B = g.B + z1 * g.sB1 + z2 * g.sB2;
 
     const int seg_len = g.kseg > 0 ? g.kseg : g.K;
-    const int nseg = g.kseg > 0 ? g.K / g.kseg : 1;
+    const int nseg = g.segs ? __builtin_amdgcn_readfirstlane(g.segs[z]) : g.kseg > 0 ? g.K / g.kseg : 1;
     int kend = seg_len;
     if (causal) kend = min(kend, n0 + BN);
     const int kbeg = (g.flags & TBOA_GEMM_KLO) ? min(kend, max(m0, n0)) : 0;      // a multiple of the tile size
@@ -424,18 +427,25 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     // byte offset along k of the next stage to be issued (stages are issued strictly in order), kept incrementally;
     // in a blocked operand 32 k are one block of 1 KB, not 64 bytes of a row
     long long koff_next = 2LL * kbeg; int kin_next = kbeg;
-    auto advance = [&]() { kin_next += FK; koff_next += 2 * FK; if (kin_next == kend) { kin_next = kbeg; koff_next += 2LL * (seg_len - kend + kbeg); } };
+    auto advance = [&]() {
+        kin_next += FK; koff_next += 2 * FK;
+        if (kin_next == kend) {
+            kin_next = kbeg;
+            if (g.rep_dB) { koff_next = 2LL * kbeg; Brow += g.rep_dB; }
+            else koff_next += 2LL * (seg_len - kend + kbeg);
+        }
+    };
     const unsigned ring_lds = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)ring);
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     auto issue = [&](int slot) {
-        const long long kb = koff_next;
+        const char* pa = Arow + (koff_next << shA); const char* pb = Brow + (koff_next << shB);
         advance();
         const unsigned st = ring_lds + (unsigned)(slot * STAGE_ELEMS * 2);
 #pragma unroll
         for (int i = 0; i < LPW; ++i) {
             const unsigned blk = (unsigned)(wave_s * LPW + i) * 1024u;
-            lds_direct_16(offA[i], Arow + (kb << shA), st + blk);
-            lds_direct_16(offB[i], Brow + (kb << shB), st + (unsigned)(BM * FK * 2) + blk);
+            lds_direct_16(offA[i], pa, st + blk);
+            lds_direct_16(offB[i], pb, st + (unsigned)(BM * FK * 2) + blk);
         }
     };
     // Fragments are double-buffered in registers at k-step granularity: while the MFMAs of one k-step run, the
@@ -874,6 +884,9 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     }
     const bool f16 = (q.flags & TBOA_GEMM_F16) != 0;
     a.term_segs = 0;
+    a.rep_dB = 2 * q.rep_strideB; a.segs = q.segs;
+    if ((q.segs != nullptr) != (q.rep_strideB != 0) || (q.segs && (!fast || q.kseg > 0 || (q.flags & TBOA_GEMM_PERSISTENT) || q.rep_strideB % 8)))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: a repeated left operand needs the dispatched LDS-direct kernel");
     if (q.nterms > 1) {
         const bool pers = fast && (q.kseg > 0 ? q.kseg : q.K) % (FK * 4) == 0 && (q.flags & TBOA_GEMM_PERSISTENT) != 0;
         const int seg = q.kseg > 0 ? q.kseg : q.K;

@@ -124,6 +124,9 @@ struct GemmBf16 {
     // t-th pair read from termA[t], termB[t] (laid out and strided as A and B; A = termA[0], B = termB[0]):
     // C = sum_t termA[t] termB[t]^T in one pass over the accumulators
     int nterms = 1; const __hip_bfloat16* termA[4] = {}; const __hip_bfloat16* termB[4] = {};
+    // segs (device, one int >= 1 per batch entry; dispatched LDS-direct kernel): C = A (B_0 + B_1 + .. + B_(segs - 1))^T with B_t at
+    // B + t rep_strideB; K is the length of ONE segment and the flops counted are those of one
+    const int* segs = nullptr; int64_t rep_strideB = 0;
 };
 // internal flag: a 16-bit result leaves as an exact-to-16-bit pair of bf16 values (hi into C, lo into C2), whatever the operands
 #define TBOA_GEMM_C_HILO 0x10000

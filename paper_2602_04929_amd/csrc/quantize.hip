@@ -2,8 +2,8 @@
 //
 // Heads are independent and run side by side: the N rows of the current step of every head form one
 // "block" of n_heads*N rows (block row R = h*nbr + r  <->  layer row h*d_h + i0 + r).  Per step:
-//   grid search   (Alg. 1 line 9)  candidates -> approximate costs of all of them on the bf16 matrix cores (delta and H_in as
-//                                  (hi, lo) bf16 pairs) -> exact fp64 costs of the near-minimal ones -> argmin
+//   grid search   (Alg. 1 line 9)  candidates -> approximate costs of all of them on the 16-bit matrix cores (integer codes against
+//                                  H_in as one or two half terms) -> exact fp64 costs of the near-minimal ones -> argmin
 //                                  (narrow layers and group-wise grids: every candidate exactly, one fp64 GEMM)
 //   in-channel sweep (Algorithm 3) panels of 64 columns: a wavefront owns a row, lane k holds column k, the 64
 //                                  sequential column steps run inside the kernel with U/P panel rows in LDS;
@@ -13,6 +13,8 @@
 // and after the last step the coordinate descent of Algorithm 2 on precomputed Gram matrices (d_h x d_h per head; per
 // pair of groups when the grids are group-wise), then the outputs and the loss.
 #include "internal.h"
+#include <hip/hip_fp16.h>
+#include <algorithm>
 #include <string.h>
 #include <stdlib.h>
 #include <math.h>
@@ -116,121 +118,257 @@ __global__ void grid_argmin_kernel(const double* __restrict__ cost, const double
     z_out[lr * ng + gi] = cand_z[(long long)row * ncand + best];
 }
 
-// ---- two-phase search: approximate costs of all candidates on the bf16 matrix cores, exact fp64 costs of the few
-// candidates within GRID_TAU of the approximate minimum.  delta and H_in are each split into an exact-to-16-bits (hi, lo)
-// bf16 pair and  delta H  ~  hi.hi + lo.hi + hi.lo  is one GEMM over three concatenated segments.  Both need their second
-// term: the cost is a difference of large terms when the input channels are correlated (cost / (|delta| |H| |delta|^T)
-// of 2e-3 is ordinary), so an operand carried to 8 bits leaves errors of 1e-2 of the cost, five times GRID_TAU, and the
-// true minimum can fall outside the survivors; with 16 bits on both sides the error is some 1e-5 of the cost.  As a guard,
-// every exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of
-// GRID_TAU is repeated with exact costs for every candidate (counted by tboa_counter).
-constexpr int GRID_PAD = 256;        // extra elements per row of the concatenated operands (memory-channel spread)
+// ---- two-phase search: approximate costs of all candidates on the 16-bit matrix cores, exact fp64 costs of the few
+// candidates within GRID_TAU of the approximate minimum.
+//
+// delta_k = s_k qbar_k - w with qbar = code - zero, small integers that IEEE half holds exactly, so that
+//     delta_k H delta_k^T = 2 sum_c delta_c (s_k G_k[c] - G_w[c]),   G_k = qbar_k T^T,  G_w = w T^T,
+// T = the lower triangle of H with half its diagonal (H is symmetric; the GEMM then needs, for output column r, only the
+// contraction indices c <= r: its causal limit).  The left operand is exact and w enters as 22 bits in two extra rows per weight
+// row, so that only T has to be split, into one or two half terms, where (hi, lo) pairs of delta and of H took three products.
+// With one term what is left is the rounding of H, 2^-12 per entry and the same for every candidate (the diagonal is exempt: its
+// rounding is known and added back).  Relative to the cost that is 2^-12 |H off the diagonal|_F / tr H times a factor of up to 40 over the
+// rows (the cost of the best candidate is below the mean): channels that are nearly uncorrelated need one term, strongly correlated
+// ones two (22 bits).  The device decides per matrix (grid_terms_kernel, GRID_ONE_TERM).
+// The channels are equilibrated by powers of two, T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, and
+// qbar'_c = qbar_c 2^(e_c - e_max) (exact), so that the entries of T' are at most 2^12 whatever the spread of the channels.
+// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates; one term): the products take 42 instead of 125 ms.  As a guard, every
+// exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of GRID_TAU is
+// repeated: with two terms if a matrix had one, else with exact costs for every candidate (counted by tboa_counter).
+// Deviations seen: 1e-5 on uncorrelated channels with one term, 5e-6 - 5e-5 on correlated ones with two (one term: 6e-3); the three
+// products of bf16 pairs had 1e-5 and 4e-5 - 2e-4.
+constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
+constexpr double GRID_ONE_TERM = 0.03;      // |H off the diagonal|_F <= this times tr H: one half term of T is enough
+constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
-typedef __hip_bfloat16 bf16;
+inline int grid_width(int n) { return (n + 31) / 32 * 32; }      // columns of the operands: zeros beyond n
+inline long long grid_mat_rows(long long rows, int ncand) { return (rows * (ncand + 2) + 15) / 16 * 16; }
 
-constexpr int GRID_TERMS = 3;        // segments of the concatenated contraction axis: [hi | lo | hi] of delta against [hi | hi | lo] of T
-
-// H_in is symmetric, so delta H delta^T = 2 delta T delta^T with T = the lower triangle of H and half its diagonal: the GEMM
-// then needs, for output column r, only the contraction indices c <= r (its causal limit), half the products.
-// Hcat[b, r, :] = [hi(T[r,:]) | hi(T[r,:]) | lo(T[r,:])]; blocked: every [n, 3n + pad] matrix in the 16 x 32 blocks of the bf16 GEMM
-__global__ void hcat_kernel(const double* __restrict__ H, bf16* __restrict__ out, int n, long long total, int blocked) {
-    const long long pitch = GRID_TERMS * n + GRID_PAD;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
-        const long long row = i / n; const int c = (int)(i % n);
-        const int rr = (int)(row % n);
-        const float v = c < rr ? (float)H[i] : c == rr ? (float)(0.5 * H[i]) : 0.f;
-        const bf16 hi = __float2bfloat16(v), lo = __float2bfloat16(v - __bfloat162float(hi));
-        if (blocked) {
-            bf16* o = out + (row / n) * n * pitch; const long long r = row % n;
-            o[tboa_blocked_offset(r, c, pitch >> 5)] = hi; o[tboa_blocked_offset(r, n + c, pitch >> 5)] = hi;
-            o[tboa_blocked_offset(r, 2 * n + c, pitch >> 5)] = lo;
-        } else {
-            bf16* o = out + row * pitch + c;
-            o[0] = hi; o[n] = hi; o[2 * n] = lo;
-        }
+// What a matrix's equilibration leaves behind, [n_hin][np] each: up[c] = 2^(e_c - e_max) (0 beyond n), down[c] = 2^-e_c, dcorr[c] = H'_cc less
+// twice what the half terms hold of T'_cc, off2[c] = sum of the squares of row c left of the diagonal; per matrix scale = 2^(2 e_max) and
+// terms = number of half terms of T'.
+struct GridScale { float* up; double* down; float* dcorr; double* off2; double* scale; int* terms; };
+__global__ __launch_bounds__(256) void grid_scale_kernel(const double* __restrict__ H, int n, int np, GridScale g) {
+    __shared__ int red[256];
+    const double* Hm = H + (long long)blockIdx.x * n * n;
+    const long long o = (long long)blockIdx.x * np;
+    auto half_exponent = [&](int c) {
+        const double v = Hm[(long long)c * n + c];
+        return (v > 0.0 && v < 1.7976931348623157e308) ? (ilogb(v) >> 1) : -600;
+    };
+    int m = -600;
+    for (int c = threadIdx.x; c < n; c += 256) m = max(m, half_exponent(c));
+    red[threadIdx.x] = m;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) { if ((int)threadIdx.x < w) red[threadIdx.x] = max(red[threadIdx.x], red[threadIdx.x + w]); __syncthreads(); }
+    const int emax = red[0];
+    for (int c = threadIdx.x; c < np; c += 256) {
+        if (c >= n) { g.up[o + c] = 0.f; g.down[o + c] = 0.0; continue; }
+        const int e = max(half_exponent(c), emax - GRID_SPREAD);
+        g.up[o + c] = ldexpf(1.f, e - emax); g.down[o + c] = ldexp(1.0, -e);
     }
+    if (threadIdx.x == 0) g.scale[blockIdx.x] = ldexp(1.0, 2 * emax);
 }
 
-// Acat[(row, k), :] = [hi(delta) | lo(delta) | hi(delta)], delta as in grid_delta_kernel; mat_rows > 0: Acat is a sequence of matrices
-// of mat_rows rows each (the rows that share one H_in), every one kept in the 16 x 32 blocks of the bf16 GEMM
-__global__ __launch_bounds__(256) void grid_delta_split_kernel(const double* __restrict__ Wk, long long ldw, int n, int ncand, double maxq,
-                                                               const double* __restrict__ cand_s, const double* __restrict__ cand_z,
-                                                               bf16* __restrict__ Acat, long long mat_rows) {
-    // four consecutive columns per thread (they share a 16-byte chunk of a block): 8-byte stores
-    const int row = blockIdx.y;
-    const int c = 4 * (blockIdx.x * blockDim.x + threadIdx.x);
-    if (c >= n) return;
-    const int nv = n - c < 4 ? n - c : 4;
-    const bool vec = nv == 4 && n % 4 == 0;
-    double w[4];
+// T' as two half terms in the GEMM's 16 x 32 blocks, one [np, np + pad] matrix per H and term (all first terms, then all second ones); only
+// what the causal limit reads (columns up to the end of the row's 256-tile) is written.  One workgroup per row, eight consecutive columns per thread.
+__global__ __launch_bounds__(256) void grid_factor_kernel(const double* __restrict__ H, int n, int np, GridScale g, __half* __restrict__ out, long long term_stride) {
+    __shared__ double red[4];
+    const int r = blockIdx.x;
+    const long long o = (long long)blockIdx.y * np, pitch = np + GRID_PAD;
+    const double* h = H + (long long)blockIdx.y * n * n + (long long)r * n;
+    _Float16* dst = (_Float16*)out + (long long)blockIdx.y * np * pitch;
+    const double dr = 1024.0 * g.down[o + r];
+    const int cend = min(np, (r / 256 + 1) * 256);
+    double sq = 0.0;
+    for (int c = 8 * threadIdx.x; c < cend; c += 2048) {
+        union { _Float16 b[8]; uint4 u; } hi, lo;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) w[j] = j < nv ? Wk[(long long)row * ldw + c + j] : 0.0;
-    const double* cs = cand_s + (long long)row * ncand;
-    const double* cz = cand_z + (long long)row * ncand;
-    const long long pitch = (long long)GRID_TERMS * n + GRID_PAD;
-    for (int k = 0; k < ncand; ++k) {
-        const double s = cs[k], z = cz[k];
-        union { bf16 b[4]; uint2 u; } hi, lo;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const float dl = (float)(s * (quant_code(w[j], s, z, maxq) - z) - w[j]);
-            hi.b[j] = __float2bfloat16(dl); lo.b[j] = __float2bfloat16(dl - __bfloat162float(hi.b[j]));
-        }
-        const long long R = (long long)row * ncand + k;
-        bf16* o; long long o0, o1, o2;
-        if (mat_rows > 0) {
-            o = Acat + (R / mat_rows) * mat_rows * pitch; const long long r = R % mat_rows;
-            o0 = tboa_blocked_offset(r, c, pitch >> 5); o1 = tboa_blocked_offset(r, n + c, pitch >> 5); o2 = tboa_blocked_offset(r, 2 * n + c, pitch >> 5);
-        } else { o = Acat + R * pitch; o0 = c; o1 = n + c; o2 = 2 * n + c; }
-        if (vec) { *(uint2*)(o + o0) = hi.u; *(uint2*)(o + o1) = lo.u; *(uint2*)(o + o2) = hi.u; }
-        else
-            for (int j = 0; j < nv; ++j) {     // (a blocked Acat has n % 32 == 0 and never comes here)
-                o[o0 + j] = hi.b[j]; o[o1 + j] = lo.b[j]; o[o2 + j] = hi.b[j];
+        for (int j = 0; j < 8; ++j) {
+            const int k = c + j;
+            double t = 0.0;
+            if (r < n && k <= r) {
+                const double v = h[k];
+                t = v * dr * g.down[o + k];
+                if (k == r) t *= 0.5; else sq += v * v;
             }
+            hi.b[j] = (_Float16)(float)t;
+            lo.b[j] = (_Float16)(float)(t - (double)hi.b[j]);
+        }
+        const long long a = tboa_blocked_offset(r, c, pitch >> 5);
+        *(uint4*)(dst + a) = hi.u; *(uint4*)(dst + term_stride + a) = lo.u;
+    }
+    sq = wave_sum(sq);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) g.off2[o + r] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// number of half terms of each matrix (`at_least` 2: never one), and what they leave out of the diagonal
+__global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restrict__ H, int n, int np, GridScale g, int at_least, int* __restrict__ gstat) {
+    __shared__ double red[2][256];
+    const double* Hm = H + (long long)blockIdx.x * n * n;
+    const long long o = (long long)blockIdx.x * np;
+    double tr = 0.0, off = 0.0;
+    for (int c = threadIdx.x; c < n; c += 256) { tr += Hm[(long long)c * n + c]; off += g.off2[o + c]; }
+    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = off;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) { red[0][threadIdx.x] += red[0][threadIdx.x + w]; red[1][threadIdx.x] += red[1][threadIdx.x + w]; }
+        __syncthreads();
+    }
+    const double lim = GRID_ONE_TERM * red[0][0];
+    const int terms = (at_least < 2 && 2.0 * red[1][0] <= lim * lim) ? 1 : 2;
+    if (threadIdx.x == 0) { g.terms[blockIdx.x] = terms; if (terms == 1) atomicOr(gstat, 1); }
+    for (int c = threadIdx.x; c < np; c += 256) {
+        double d = 0.0;
+        if (c < n) {
+            const double t = 0.5 * Hm[(long long)c * n + c] * (1024.0 * g.down[o + c]) * g.down[o + c];
+            const _Float16 hi = (_Float16)(float)t, lo = (_Float16)(float)(t - (double)hi);
+            d = 2.0 * (t - (double)hi - (terms > 1 ? (double)lo : 0.0)) / 1024.0;
+        }
+        g.dcorr[o + c] = (float)d;
     }
 }
 
-// cost[i] = 2 sum_c G[i, c] (hi + lo)[i, c], one wavefront per row (G = delta T^T, see hcat_kernel)
-__global__ __launch_bounds__(256) void rowdot_split_kernel(const float* __restrict__ G, const bf16* __restrict__ Acat, long long rows, int n,
-                                                           double* __restrict__ out, long long mat_rows) {
-    const int lane = threadIdx.x & 63;
-    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+// Rows of a pass, in one array of matrices (the rows that share one H): matrix row of (weight row rl of the matrix, candidate k) is
+// rl ncand + k; the high and low parts of the weights follow at per ncand + rl and per ncand + per + rl.
+struct GridRows { int per, ncand; long long mat_rows; int np; };
+
+// per weight row (one wavefront): range, candidates (s_k, z_k) and 1 / s_k in fp32 (0 where that is no normal number), the row in fp32, and the
+// row's two operand rows: w up 2^t as a (hi, lo) pair of halves, 2^t bringing the row's largest magnitude into [2^13, 2^14)
+__global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict__ Wk, long long ldw, int n, int rows, int grid_points, double maxq,
+                                                        GridRows m, GridScale g, double* __restrict__ cand_s, double* __restrict__ cand_z,
+                                                        float* __restrict__ cand_r, float* __restrict__ Wf, float* __restrict__ wdown, __half* __restrict__ Acat) {
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
-    const long long pitch = (long long)GRID_TERMS * n + GRID_PAD;
-    const float* g = G + row * n; const bf16* a = Acat + row * pitch;
-    double s = 0.0;
-    if (n % 4 == 0) {     // four consecutive columns per lane (they share a 16-byte chunk of a block): 16- and 8-byte streaming loads
-        typedef float f4 __attribute__((ext_vector_type(4)));
-        const bf16* base = mat_rows > 0 ? Acat + (row / mat_rows) * mat_rows * pitch : a;
-        const long long r = mat_rows > 0 ? row % mat_rows : 0;
-        for (int c = 4 * lane; c < n; c += 256) {
-            const f4 gv = __builtin_nontemporal_load((const f4*)(g + c));
-            union { uint2 u; bf16 b[4]; } hi, lo;
-            if (mat_rows > 0) {
-                hi.u = *(const uint2*)(base + tboa_blocked_offset(r, c, pitch >> 5));
-                lo.u = *(const uint2*)(base + tboa_blocked_offset(r, n + c, pitch >> 5));
-            } else { hi.u = *(const uint2*)(a + c); lo.u = *(const uint2*)(a + n + c); }
+    const double* w = Wk + (long long)row * ldw;
+    double lo = 0.0, hi = 0.0;
+    for (int c = lane; c < n; c += 64) { const double v = w[c]; lo = fmin(lo, v); hi = fmax(hi, v); }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) s += (double)gv[j] * ((double)__bfloat162float(hi.b[j]) + (double)__bfloat162float(lo.b[j]));
+    for (int o = 32; o > 0; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o, 64)); hi = fmax(hi, __shfl_xor(hi, o, 64)); }
+    const double big = fmax(-lo, hi);
+    const int t = (big > 0.0 && big < 1e300) ? 13 - ilogb(big) : 0;
+    if (lo == hi) { lo = -1.0; hi = 1.0; }
+    for (int k = lane; k < m.ncand; k += 64) {
+        const double p = 1.0 - (double)k / (double)grid_points;
+        const double s = (p * hi - p * lo) / maxq;
+        cand_s[(long long)row * m.ncand + k] = s;
+        cand_z[(long long)row * m.ncand + k] = rint(-(p * lo) / s);
+        const double r = 1.0 / s;
+        cand_r[(long long)row * m.ncand + k] = (r >= 1.17549435e-38 && r <= 3.4e38) ? (float)r : 0.f;
+    }
+    if (lane == 0) wdown[row] = ldexpf(1.f, -t);
+    const int mat = row / m.per, rl = row % m.per;
+    const long long pitch = m.np + GRID_PAD, R = (long long)m.per * m.ncand + rl;
+    const float* up = g.up + (long long)mat * m.np;
+    _Float16* A = (_Float16*)Acat + (long long)mat * m.mat_rows * pitch;
+    for (int c = lane; c < m.np; c += 64) {
+        const double v = c < n ? w[c] : 0.0;
+        Wf[(long long)row * m.np + c] = (float)v;
+        const double x = ldexp(v, t) * (double)up[c];
+        const _Float16 h = (_Float16)(float)x;
+        A[tboa_blocked_offset(R, c, pitch >> 5)] = h;
+        A[tboa_blocked_offset(R + m.per, c, pitch >> 5)] = (_Float16)(float)(x - (double)h);
+    }
+}
+
+// qbar'[(row, k), c] = (clamp(round(w_c / s_k) + z_k) - z_k) up[c].  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so
+// wherever it is further than 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
+// A wavefront makes whole 16 x 32 blocks: lane = (row of the block lane / 4, eight columns of lane % 4).
+// DELTA (8-bit grids): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
+// elements further on.  With 256 levels s qbar and w agree to 1e-2 and their products with T, formed in fp32, would be subtracted:
+// deviations of 5e-4 on correlated channels, against 3e-6 this way; for 16 levels and less the subtraction leaves 5e-5 and the
+// exact operand saves the second product.
+template <bool DELTA>
+__global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, int rows, float maxq,
+                                                         GridRows m, GridScale g, const double* __restrict__ cand_s, const double* __restrict__ cand_z,
+                                                         const float* __restrict__ cand_r, const float* __restrict__ wdown, __half* __restrict__ Acat, long long lo_off) {
+    const int lane = threadIdx.x & 63;
+    const int mat = blockIdx.z;
+    const long long R = 16LL * (blockIdx.y * 4 + (threadIdx.x >> 6)) + (lane >> 2);
+    if (R >= (long long)m.per * m.ncand) return;
+    const int rl = (int)(R / m.ncand), k = (int)(R % m.ncand), row = mat * m.per + rl;
+    const double s = cand_s[(long long)row * m.ncand + k], zd = cand_z[(long long)row * m.ncand + k], up2 = DELTA ? 1.0 / (double)wdown[row] : 0.0;
+    const float inv = cand_r[(long long)row * m.ncand + k], z = (float)zd;
+    const float* wf = Wf + (long long)row * m.np; const float* up = g.up + (long long)mat * m.np;
+    const long long pitch = m.np + GRID_PAD;
+    _Float16* A = (_Float16*)Acat + (long long)mat * m.mat_rows * pitch;
+    const int nblk = m.np / 32, per = (nblk + gridDim.x - 1) / gridDim.x, b1 = min(nblk, ((int)blockIdx.x + 1) * per);
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    for (int cb = blockIdx.x * per; cb < b1; ++cb) {
+        const int c = 32 * cb + 8 * (lane & 3);
+        f4 wv[2] = {*(const f4*)(wf + c), *(const f4*)(wf + c + 4)}, uv[2] = {*(const f4*)(up + c), *(const f4*)(up + c + 4)};
+        union { _Float16 b[8]; uint4 u; } o, l;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float t = wv[j >> 2][j & 3] * inv, uj = uv[j >> 2][j & 3];
+            float r = rintf(t);
+            const bool safe = inv != 0.f && fabsf(t - r) < 0.5f - (fabsf(t) * 9.5367431640625e-7f + 9.5367431640625e-7f);
+            if (!safe && c + j < n) r = (float)fmin(fmax(rint(Wk[(long long)row * ldw + c + j] / s), -1024.0), 1024.0);
+            const float q = fminf(fmaxf(r + z, 0.f), maxq);
+            if constexpr (DELTA) {
+                const double w = c + j < n ? Wk[(long long)row * ldw + c + j] : 0.0;
+                const double d = (s * ((double)q - zd) - w) * (double)uj * up2;
+                o.b[j] = (_Float16)(float)d; l.b[j] = (_Float16)(float)(d - (double)o.b[j]);
+            } else o.b[j] = (_Float16)((q - z) * uj);
         }
-    } else if (mat_rows > 0) {
-        a = Acat + (row / mat_rows) * mat_rows * pitch; const long long r = row % mat_rows;
-        for (int c = lane; c < n; c += 64)
-            s += (double)g[c] * ((double)__bfloat162float(a[tboa_blocked_offset(r, c, pitch >> 5)]) +
-                                 (double)__bfloat162float(a[tboa_blocked_offset(r, n + c, pitch >> 5)]));
-    } else
-    for (int c = lane; c < n; c += 64) s += (double)g[c] * ((double)__bfloat162float(a[c]) + (double)__bfloat162float(a[n + c]));
-    s = wave_sum(s);
-    if (lane == 0) out[row] = 2.0 * s;
+        const long long a = tboa_blocked_offset(R, c, pitch >> 5);
+        *(uint4*)(A + a) = o.u;
+        if constexpr (DELTA) *(uint4*)(A + lo_off + a) = l.u;
+    }
+}
+
+// cost[(row, k)] = 2^(2 e_max) sum_c delta'_c (2 (s G[c] - Gw[c]) 2^-10 + dcorr_c delta'_c), delta' = s qbar' - w'; one wavefront per (row, k).
+// DELTA: delta' = the pair, G its product.
+template <bool DELTA>
+__global__ __launch_bounds__(256) void grid_cost_kernel(const float* __restrict__ G, const __half* __restrict__ Acat, int rows, GridRows m, GridScale g,
+                                                        const double* __restrict__ cand_s, const float* __restrict__ wdown, double* __restrict__ out, long long lo_off) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63;
+    const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= (long long)rows * m.ncand) return;
+    const int row = (int)(i / m.ncand), k = (int)(i % m.ncand), mat = row / m.per, rl = row % m.per;
+    const long long pitch = m.np + GRID_PAD, kb = pitch >> 5, R = (long long)rl * m.ncand + k, Rw = (long long)m.per * m.ncand + rl;
+    const _Float16* A = (const _Float16*)Acat + (long long)mat * m.mat_rows * pitch;
+    const float* Gm = G + (long long)mat * m.mat_rows * m.np;
+    const float *g0 = Gm + R * m.np, *g1 = Gm + Rw * m.np, *g2 = Gm + (Rw + m.per) * m.np, *dc = g.dcorr + (long long)mat * m.np;
+    const double s = cand_s[i], wd = wdown[row];
+    double acc = 0.0;
+    for (int c = 4 * lane; c < m.np; c += 256) {
+        const f4 a = __builtin_nontemporal_load((const f4*)(g0 + c)), d = *(const f4*)(dc + c);
+        const h4 q = *(const h4*)(A + tboa_blocked_offset(R, c, kb));
+        if constexpr (DELTA) {
+            const h4 ql = *(const h4*)(A + lo_off + tboa_blocked_offset(R, c, kb));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double delta = wd * ((double)(float)q[j] + (double)(float)ql[j]);
+                acc += delta * ((2.0 / 1024.0) * wd * (double)a[j] + (double)d[j] * delta);
+            }
+        } else {
+            const f4 wh = *(const f4*)(g1 + c), wl = *(const f4*)(g2 + c);
+            const h4 vh = *(const h4*)(A + tboa_blocked_offset(Rw, c, kb)), vl = *(const h4*)(A + tboa_blocked_offset(Rw + m.per, c, kb));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double delta = s * (double)(float)q[j] - wd * ((double)(float)vh[j] + (double)(float)vl[j]);
+                const double gd = s * (double)a[j] - wd * ((double)wh[j] + (double)wl[j]);
+                acc += delta * ((2.0 / 1024.0) * gd + (double)d[j] * delta);
+            }
+        }
+    }
+    acc = wave_sum(acc);
+    if (lane == 0) out[i] = g.scale[mat] * acc;
 }
 
 // Device-side bookkeeping of the two-phase search, accumulated over every pass of a quantize_layer call and read once at
 // its end: [0] set when a pass could not be trusted as it stands (non-finite approximate cost, more near-minimal
 // candidates in a group of rows than the exact re-evaluation has room for), [1] near-minimal candidates evaluated exactly,
-// [2] the largest |approximate - exact| / |exact| seen, as the bits of a non-negative float.
-enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_WORDS = 3 };
+// [2] the largest |approximate - exact| / |exact| seen, as the bits of a non-negative float, [3] set when a matrix of the call has one half
+// term (see grid_terms_kernel).
+enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_ONE_TERM = 3, GS_WORDS = 4 };
 
 // per row: the limit below which a candidate's approximate cost makes it a survivor, and the number of survivors that the
 // exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
@@ -643,10 +781,11 @@ struct Layer {
     double *Q64, *s64, *z64;
     double *Wb, *Wk, *Epan, *Wsnap, *E, *S1, *S2, *T;
     double *cand_s, *cand_z, *Delta, *G, *cost, *DeltaS, *GS, *costS, *lim;
-    __hip_bfloat16* Hcat; int* sel; int fast_grid, grid_blocked;
+    __half* Hcat; int* sel; int fast_grid, grid_terms;          // two-phase search: T' of every H_in, survivor bookkeeping
+    GridScale gscale; float *cand_r, *Wf, *wdown;
     double *Wbar, *Abar, *Z, *WR, *Cm, *Fm, *dvec, *lossbuf;
     double *Cg, *Fg;    // group-wise refinement: Gram blocks per (group, group) pair
-    int grid_chunk;     // block rows (shared H_in) or heads (per-head H_in) per grid-search pass
+    int grid_chunk, fast_chunk;     // block rows (shared H_in) or heads (per-head H_in) per grid-search pass: exact, two-phase
     int* gstat;         // device words of the two-phase search (GS_*), cleared at the start of a run
     long long nn;
 };
@@ -660,32 +799,50 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
     const int total_rows = nh * rows_per_head;
     const int units = ph ? nh : total_rows;                 // chunk unit: a head or a row
     const int rows_per_unit = ph ? rows_per_head : 1;
-    for (int u0 = 0; u0 < units; u0 += L.grid_chunk) {
-        const int nu = (units - u0 < L.grid_chunk) ? units - u0 : L.grid_chunk;
+    const bool fast = L.fast_grid && c0 == 0 && ncols == L.n;
+    const int chunk = fast ? L.fast_chunk : L.grid_chunk;
+    for (int u0 = 0; u0 < units; u0 += chunk) {
+        const int nu = (units - u0 < chunk) ? units - u0 : chunk;
         const int r0 = u0 * rows_per_unit, rows = nu * rows_per_unit;
         const double* Wc = Wrows + (long long)r0 * ldw;
-        hipLaunchKernelGGL(grid_candidates_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, c0, ncols, rows,
-                           ncand, L.d->grid_points, L.maxq, L.cand_s, L.cand_z);
-        TB_KERNEL_CHECK(ctx);
-        if (L.fast_grid && c0 == 0 && ncols == L.n) {
-            const int n = L.n;
-            __hip_bfloat16* Acat = (__hip_bfloat16*)L.Delta; float* G32 = (float*)L.G;
-            // both operands in the GEMM's 16 x 32 blocks when the shapes allow it (L.grid_blocked, decided with Hcat)
-            long long mat_rows = L.grid_blocked ? (long long)(ph ? rows_per_head : rows) * ncand : 0;
-            if (mat_rows % 16) mat_rows = 0;
-            hipLaunchKernelGGL(grid_delta_split_kernel, dim3((n + 1023) / 1024, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
-                               L.cand_s, L.cand_z, Acat, mat_rows);
+        if (fast) {
+            const int n = L.n, np = grid_width(n);
+            __half* Acat = (__half*)L.Delta; float* G32 = (float*)L.G;
+            const int mats = ph ? nu : 1;
+            const GridRows m{ph ? rows_per_head : rows, ncand, grid_mat_rows(ph ? rows_per_head : rows, ncand), np};
+            GridScale gs = L.gscale;      // of the first matrix of this pass
+            if (ph) { gs.up += (long long)u0 * np; gs.down += (long long)u0 * np; gs.dcorr += (long long)u0 * np; gs.scale += u0; gs.terms += u0; }
+            hipLaunchKernelGGL(grid_rows_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, n, rows, L.d->grid_points, L.maxq, m, gs,
+                               L.cand_s, L.cand_z, L.cand_r, L.Wf, L.wdown, Acat);
+            const unsigned rb = (unsigned)(((long long)m.per * ncand + 63) / 64);
+            // (columns in up to 8 parts where there are few rows)
+            const unsigned cparts = (long long)rb * mats >= 2048 ? 1u : (unsigned)std::min<long long>(8, 2048 / ((long long)rb * mats) + 1);
+            const bool delta = L.d->bits == 8;
+            const long long lo_off = (long long)mats * m.mat_rows * (np + GRID_PAD);
+            if (delta)
+                hipLaunchKernelGGL(grid_codes_kernel<true>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
+                                   L.cand_s, L.cand_z, L.cand_r, L.wdown, Acat, lo_off);
+            else
+                hipLaunchKernelGGL(grid_codes_kernel<false>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
+                                   L.cand_s, L.cand_z, L.cand_r, L.wdown, Acat, lo_off);
             TB_KERNEL_CHECK(ctx);
             GemmBf16 a{};
-            a.N = n; a.K = GRID_TERMS * n; a.alpha = 1.f; a.A = Acat; a.lda = (long long)GRID_TERMS * n + GRID_PAD; a.ldb = a.lda; a.C = G32; a.ldc = n;
-            a.c_dtype = TBOA_F32; a.accumulate = 0; a.flags = (mat_rows > 0 ? TBOA_GEMM_A_TILED : 0) | (L.grid_blocked ? TBOA_GEMM_B_TILED : 0); a.tag = TBOA_PROF_GRID;
-            a.flags |= TBOA_GEMM_CAUSAL_K; a.kseg = n;   // Hcat holds the lower triangle: contraction index <= output column, in every segment
-            if (ph) { a.M = rows_per_head * ncand; a.batch = nu; a.B = L.Hcat + (long long)u0 * n * a.lda;
-                      a.strideA = (long long)a.M * a.lda; a.strideB = (long long)n * a.lda; a.strideC = (long long)a.M * n; }
-            else { a.M = rows * ncand; a.batch = 1; a.B = L.Hcat; }
+            a.M = (int)m.mat_rows; a.N = np; a.K = np; a.alpha = 1.f; a.lda = np + GRID_PAD; a.ldb = a.lda; a.C = G32; a.ldc = np;
+            a.A = (const __hip_bfloat16*)Acat; a.B = (const __hip_bfloat16*)L.Hcat + (ph ? (long long)u0 * np * a.ldb : 0);
+            a.batch = mats; a.strideA = m.mat_rows * a.lda; a.strideB = (long long)np * a.ldb; a.strideC = m.mat_rows * np;
+            a.c_dtype = TBOA_F32; a.accumulate = 0; a.tag = TBOA_PROF_GRID;
+            a.segs = gs.terms; a.rep_strideB = (long long)L.nhin * np * a.ldb;
+            a.flags = TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED | TBOA_GEMM_CAUSAL_K;     // T' is lower triangular
             TB_TRY(gemm_bf16_nt(ctx, a));
+            if (delta) {      // the low parts of delta against the first term of T'
+                a.A += lo_off; a.segs = nullptr; a.rep_strideB = 0; a.accumulate = 1;
+                TB_TRY(gemm_bf16_nt(ctx, a));
+            }
             const long long crow = (long long)rows * ncand;
-            hipLaunchKernelGGL(rowdot_split_kernel, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, G32, Acat, crow, n, L.cost, mat_rows);
+            if (delta)
+                hipLaunchKernelGGL(grid_cost_kernel<true>, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, G32, Acat, rows, m, gs, L.cand_s, L.wdown, L.cost, lo_off);
+            else
+                hipLaunchKernelGGL(grid_cost_kernel<false>, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, G32, Acat, rows, m, gs, L.cand_s, L.wdown, L.cost, lo_off);
             const int per = ph ? rows_per_head : rows, ngrp = rows / per;    // rows that share one H_in
             const int cap = per * GRID_KS;                                    // exact re-evaluations a group has room for
             int* cntv = L.sel; int* offv = cntv + rows; int* totv = offv + rows;
@@ -709,6 +866,8 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             ++ctx->counters[TBOA_CTR_GRID_PASSES];
             continue;
         }
+        hipLaunchKernelGGL(grid_candidates_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, c0, ncols, rows,
+                           ncand, L.d->grid_points, L.maxq, L.cand_s, L.cand_z);
         hipLaunchKernelGGL(grid_delta_kernel, dim3((ncols + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, c0, ncols, ncand,
                            L.maxq, L.cand_s, L.cand_z, L.Delta);
         TB_KERNEL_CHECK(ctx);
@@ -750,9 +909,9 @@ int block_gemm(Layer& L, int nbr, int N, int K, double alpha, const double* A, l
     return gemm_f64(L.ctx, g);
 }
 
-// return value of run_layer: the approximate costs of the two-phase grid search could not be trusted somewhere in this
-// run (see grid_search): the caller runs the layer again with exact costs for every candidate
-constexpr int RUN_AGAIN_EXACT = 1;
+// return values of run_layer: the approximate costs of the two-phase grid search could not be trusted somewhere in this
+// run (see grid_search): the caller runs the layer again with exact costs for every candidate, or (one half term of H was not enough) with two
+constexpr int RUN_AGAIN_EXACT = 1, RUN_AGAIN_TWO_TERMS = 2;
 
 int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, const float* R, uint8_t* codes, float* scales,
               float* zeros, float* W_deq, double* loss, double* loss_per_head) {
@@ -770,8 +929,10 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     TB_TRY(launch_f32_to_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hi));
     TB_HIP(ctx, hipMemcpyAsync(L.Hfac, L.Hi, nhin * nn * sizeof(double), hipMemcpyDeviceToDevice, st));
     if (L.fast_grid) {
-        long long tot = nhin * nn, gb = (tot + 255) / 256; if (gb > 32768) gb = 32768;
-        hipLaunchKernelGGL(hcat_kernel, dim3((unsigned)gb), dim3(256), 0, st, L.Hi, L.Hcat, n, tot, L.grid_blocked);
+        const int np = grid_width(n);
+        hipLaunchKernelGGL(grid_scale_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale);
+        hipLaunchKernelGGL(grid_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.Hcat, (long long)nhin * np * (np + GRID_PAD));
+        hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, L.gstat + GS_ONE_TERM);
         TB_KERNEL_CHECK(ctx);
     }
     // U_in, P and U_out are first needed by the first in-channel sweep; the grid search before it needs only W and H_in.
@@ -1032,7 +1193,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         float dev; memcpy(&dev, &gs[GS_MAXDEV], sizeof(float));
         ctx->counters[TBOA_CTR_GRID_SURVIVORS] += gs[GS_SURVIVORS];
         const double guard = d->grid_guard > 0.0 ? d->grid_guard : 0.25;
-        if (gs[GS_TRIPPED] || dev > guard * GRID_TAU) { free(host); return RUN_AGAIN_EXACT; }
+        if (gs[GS_TRIPPED]) { free(host); return RUN_AGAIN_EXACT; }
+        if (dev > guard * GRID_TAU) { free(host); return gs[GS_ONE_TERM] ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT; }
     }
     if (want_loss) {
         double q = 0.0, c = 0.0;
@@ -1053,7 +1215,13 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     const int n = L.n, nh = L.nh, dh = L.dh;
     const int blk = d->block < dh ? d->block : dh;
     const size_t wn = (size_t)d->d_out * n, brows = (size_t)nh * blk;
-    const size_t grows = (size_t)L.grid_chunk * (L.nhin > 1 ? (d->adaptive_grid ? blk : dh) : 1);
+    const int unit_rows = L.nhin > 1 ? (d->adaptive_grid ? blk : dh) : 1;
+    const size_t grows = (size_t)(L.fast_grid ? L.fast_chunk : L.grid_chunk) * unit_rows;
+    size_t delta_bytes = (size_t)L.grid_chunk * unit_rows * L.ncand * L.gsz * sizeof(double), g_bytes = delta_bytes;
+    if (L.fast_grid) {
+        const size_t np = grid_width(n), mrows = (L.nhin > 1 ? (size_t)L.fast_chunk : 1) * grid_mat_rows(L.nhin > 1 ? unit_rows : (long long)grows, L.ncand);
+        delta_bytes = std::max(delta_bytes, (d->bits == 8 ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
+    }
     const int fmax = n > dh ? n : dh;
     const int fb = (L.nhin > nh) ? L.nhin : nh;
     const int nblk_f = (fmax + TB_FACT_NB - 1) / TB_FACT_NB;
@@ -1072,12 +1240,16 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.S1 = (H_out && R) ? ar.get<double>(brows * n) : nullptr; L.S2 = (H_out && R) ? ar.get<double>(brows * n) : nullptr;
     L.T = H_out ? ar.get<double>((size_t)nh * dh * d->block) : nullptr;
     L.cand_s = ar.get<double>(grows * L.ncand); L.cand_z = ar.get<double>(grows * L.ncand); L.cost = ar.get<double>(grows * L.ncand);
-    L.Delta = ar.get<double>(grows * L.ncand * L.gsz); L.G = ar.get<double>(grows * L.ncand * L.gsz);
+    L.Delta = ar.get<double>(delta_bytes / sizeof(double) + 1); L.G = ar.get<double>(g_bytes / sizeof(double) + 1);
     L.DeltaS = L.GS = L.costS = L.lim = nullptr; L.sel = nullptr; L.Hcat = nullptr;
     if (L.fast_grid) {
         L.DeltaS = ar.get<double>(grows * GRID_KS * n); L.GS = ar.get<double>(grows * GRID_KS * n);
         L.costS = ar.get<double>(grows * GRID_KS); L.lim = ar.get<double>(grows); L.sel = ar.get<int>(grows * 3);
-        L.Hcat = ar.get<__hip_bfloat16>((size_t)L.nhin * n * (GRID_TERMS * (size_t)n + GRID_PAD));
+        const size_t np = grid_width(n);
+        L.Hcat = ar.get<__half>((size_t)2 * L.nhin * np * (np + GRID_PAD));
+        L.gscale.up = ar.get<float>(L.nhin * np); L.gscale.down = ar.get<double>(L.nhin * np); L.gscale.dcorr = ar.get<float>(L.nhin * np);
+        L.gscale.off2 = ar.get<double>(L.nhin * np); L.gscale.scale = ar.get<double>(L.nhin); L.gscale.terms = ar.get<int>(L.nhin);
+        L.cand_r = ar.get<float>(grows * L.ncand); L.Wf = ar.get<float>(grows * np); L.wdown = ar.get<float>(grows);
     }
     L.Wbar = ar.get<double>(wn); L.Abar = ar.get<double>(wn); L.Z = ar.get<double>(wn);
     L.WR = R ? ar.get<double>(wn) : nullptr;
@@ -1120,12 +1292,14 @@ void init_layer(Layer& L, tboa_ctx* ctx, const tboa_layer_desc* d) {
     const double cap = 2147483648.0;
     const double per_row = (double)L.ncand * L.gsz * 8.0;
     const int max_rows_block = d->adaptive_grid ? blk : L.dh;
-    if (L.nhin > 1) { int c = (int)(cap / (per_row * max_rows_block)); L.grid_chunk = c < 1 ? 1 : (c > L.nh ? L.nh : c); }
-    else { int c = (int)(cap / per_row); const int tot = L.nh * max_rows_block; L.grid_chunk = c < 1 ? 1 : (c > tot ? tot : c); }
-    // per-row grids of wide layers: two-phase search (a negative grid_guard asks for exact costs throughout); its GEMM
-    // operands in 16 x 32 blocks when the width allows
-    L.fast_grid = (!d->group && L.n % 8 == 0 && L.n >= 256 && !(d->grid_guard < 0.0)) ? 1 : 0;
-    L.grid_blocked = (L.fast_grid && L.n % 32 == 0) ? 1 : 0;
+    const int units = L.nhin > 1 ? L.nh : L.nh * max_rows_block;
+    const double c = cap / (L.nhin > 1 ? per_row * max_rows_block : per_row);
+    L.grid_chunk = c < 1.0 ? 1 : (c > units ? units : (int)c);
+    // the two-phase search holds 2 + 4 bytes per entry where the exact one holds 8 + 8: twice the rows in the same buffers
+    L.fast_chunk = c < 0.5 ? 1 : (2.0 * c > units ? units : (int)(2.0 * c));
+    // per-row grids of wide layers: two-phase search (a negative grid_guard asks for exact costs throughout).  Narrow layers
+    // (d_in < 256) keep the exact search: one launch over all candidates, nothing to re-evaluate
+    L.fast_grid = (!d->group && L.n >= 256 && !(d->grid_guard < 0.0)) ? 1 : 0;
     L.gstat = ctx ? ctx->d_status + TB_GSTAT_WORD : nullptr;
 }
 
@@ -1156,6 +1330,10 @@ extern "C" int tboa_quantize_layer(tboa_ctx* ctx, const tboa_layer_desc* d, cons
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }
     int rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
+    if (rc == RUN_AGAIN_TWO_TERMS) {
+        L.grid_terms = 2;
+        rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
+    }
     if (rc == RUN_AGAIN_EXACT) {
         // the guard of the two-phase grid search: exact costs for every candidate, same workspace
         ++ctx->counters[TBOA_CTR_GRID_FALLBACKS];

@@ -1,0 +1,65 @@
+"""The two-phase grid search against the same layer with fp64 costs for every candidate (grid_guard < 0): same codes, scales and zeros,
+and no call that had to be repeated.  The search returns the fp64 argmin either way, so nothing may differ; the widths sit at the
+edges of the operands' 32-column padding and of the 256-tiles, the Hessians need one half term (independent channels) or two."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(n, heads, dh, seed, corr, per_head):
+    g = torch.Generator(device="cuda"); g.manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float64)
+
+    def hessian():
+        x = rnd(4 * n, n)
+        x[:, torch.randperm(n, generator=g, device="cuda")[:4]] *= 20
+        if corr:
+            x = x + 0.3 * (x @ rnd(n, 4)) @ rnd(4, n)
+        return (x.T @ x).float()
+    H = torch.stack([hessian() for _ in range(heads)]) if per_head else hessian()
+    k = rnd(heads, 3 * dh, dh)
+    Ho = torch.stack([a.T @ a for a in k]).float().contiguous()
+    return (rnd(heads * dh, n) * 0.02).float(), H, Ho
+
+
+def same(a, b):
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("corr", [0, 1])
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("n,heads,dh,per_head", [(256, 3, 20, 0), (257, 1, 33, 0), (288, 2, 16, 1), (300, 5, 30, 0), (511, 2, 24, 1), (544, 2, 24, 0), (1001, 1, 40, 0)])
+def test_two_phase_search_equals_exact(lib, n, heads, dh, per_head, bits, corr):
+    W, H, Ho = layer(n, heads, dh, n + bits, corr, per_head)
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, Ho, None, heads, bits, 16)
+    passes, again = ctx.counter(0), ctx.counter(1)
+    assert passes > 0 and again == 0
+    same(fast, ctx.quantize_layer(W, H, Ho, None, heads, bits, 16, grid_guard=-1.0))
+    assert ctx.counter(0) == passes
+    ctx.close()
+
+
+@pytest.mark.parametrize("corr", [0, 1])
+def test_a_guard_that_cannot_be_met_ends_in_exact_costs(lib, corr):
+    """A guard below what any rounding gives: the call is run again (independent channels: with two half terms first, twice the passes) and at
+    last exactly, once by the counter."""
+    W, H, Ho = layer(320, 2, 32, 5, corr, 0)
+    ctx = lib.Context()
+    got = ctx.quantize_layer(W, H, Ho, None, 2, 2, 32, grid_guard=1e-12)
+    assert ctx.counter(1) == 1 and ctx.counter(0) == (2 if not corr else 1)
+    same(got, ctx.quantize_layer(W, H, Ho, None, 2, 2, 32, grid_guard=-1.0))
+    ctx.close()
+
+
+def test_channels_of_very_different_variance(lib):
+    """Variances over 2^40: beyond the spread of the half exponents the small channels share one (their part of the cost is nothing)."""
+    W, H, Ho = layer(320, 2, 32, 6, 0, 0)
+    d = torch.logspace(-6, 6, 320, device="cuda", dtype=torch.float64)
+    H = (H.double() * d[:, None] * d[None, :]).float()
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, Ho, None, 2, 3, 32)
+    same(fast, ctx.quantize_layer(W, H, Ho, None, 2, 3, 32, grid_guard=-1.0))
+    ctx.close()
