@@ -43,6 +43,15 @@ __device__ __forceinline__ double quant_code(double w, double s, double z, doubl
     return fmin(fmax(rint(w / s) + z, 0.0), maxq);
 }
 
+// the same code without the division: w (1 / s) is within 4 ulp of w / s, so that wherever it is further than that from a
+// half-integer both round to the same integer; only the others are divided
+__device__ __forceinline__ double quant_code_fast(double w, double s, double si, double z, double maxq) {
+    const double t = w * si;
+    double r = rint(t);
+    if (!(0.5 - fabs(t - r) > fabs(t) * 1e-15)) r = rint(w / s);
+    return fmin(fmax(r + z, 0.0), maxq);
+}
+
 // ------------------------------------------------------------------------------------------------ rows
 __global__ void gather_rows_kernel(const double* __restrict__ src, double* __restrict__ dst, BlockMap m, int n) {
     const int R = blockIdx.y;
@@ -502,22 +511,38 @@ struct SweepArgs {
     int epitch;
 };
 
+// Bound by the chain of the 64 column steps: what a step needs from the one before goes through one broadcast and a dozen dependent
+// fp64 operations, two rows per wavefront side by side.  Both divisions of a step are products with reciprocals taken once per panel
+// (quant_code_fast decides the code as the quotient would; the other one gets a Newton correction), and the loads of the panel's pieces of U
+// and P are all in flight together (they were taken one row after the other: half of the time): 33 -> 21 us per panel.
 template <int RPW>
 __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
     __shared__ double Us[64][64];
     __shared__ double Ps[64][64];
+    __shared__ double Ui[64];
     const int h = blockIdx.y, n = a.n, c0 = a.c0, pw = a.pw;
     const double* U = a.U + (a.per_head ? (long long)h * n * n : 0);
     const double* P = a.P ? a.P + (a.per_head ? (long long)h * n * n : 0) : nullptr;
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int j = i >> 6, k = i & 63;
-        const bool in = (j < pw && k < pw);
-        Us[j][k] = in ? U[(long long)(c0 + j) * n + c0 + k] : 0.0;
-        Ps[j][k] = (in && P) ? P[(long long)(c0 + j) * n + c0 + k] : 0.0;
-    }
-    __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double w[RPW], s[RPW], z[RPW], qv[RPW], Qv[RPW], ev[RPW], wsv[RPW];
+    {      // all loads of the two 64 x 64 pieces in flight together (clamped indices; what lies beyond the panel becomes zero on the way to LDS)
+        double u[16], p[16];
+        const int k = min(lane, pw - 1);
+#pragma unroll
+        for (int q = 0; q < 16; ++q) u[q] = U[(long long)(c0 + min(wave + 4 * q, pw - 1)) * n + c0 + k];
+        if (P) {
+#pragma unroll
+            for (int q = 0; q < 16; ++q) p[q] = P[(long long)(c0 + min(wave + 4 * q, pw - 1)) * n + c0 + k];
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int j = wave + 4 * q;
+            const bool in = j < pw && lane < pw;
+            Us[j][lane] = in ? u[q] : 0.0;
+            Ps[j][lane] = in && P ? p[q] : 0.0;
+            if (j == lane) Ui[lane] = in ? 1.0 / u[q] : 1.0;
+        }
+    }
+    double w[RPW], s[RPW], si[RPW], z[RPW], qv[RPW], Qv[RPW], ev[RPW], wsv[RPW];
     int R[RPW]; bool valid[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -526,21 +551,23 @@ __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
         R[i] = h * a.nbr + (valid[i] ? r : 0);
         const long long lr = layer_row(a.map, R[i]);
         w[i] = (valid[i] && lane < pw) ? a.Wk[(long long)R[i] * n + c0 + lane] : 0.0;
-        s[i] = a.s[lr * a.ng + a.gi]; z[i] = a.z[lr * a.ng + a.gi];
+        s[i] = a.s[lr * a.ng + a.gi]; z[i] = a.z[lr * a.ng + a.gi]; si[i] = 1.0 / s[i];
         qv[i] = Qv[i] = ev[i] = wsv[i] = 0.0;
     }
+    __syncthreads();
     const bool hasP = (P != nullptr);
     for (int j = 0; j < pw; ++j) {
-        const double urow = Us[j][lane], prow = Ps[j][lane], ujj = Us[j][j];
+        const double urow = Us[j][lane], prow = Ps[j][lane], ujj = Us[j][j], uinv = Ui[j];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
             const double wj = readlane_f64(w[i], j);
-            const double q = quant_code(wj, s[i], z[i], a.maxq);
+            const double q = quant_code_fast(wj, s[i], si[i], z[i], a.maxq);
             const double Qj = s[i] * (q - z[i]);
-            const double e = (wj - Qj) / ujj;
+            const double d = wj - Qj, e0 = d * uinv;
+            const double e = __builtin_fma(__builtin_fma(-e0, ujj, d), uinv, e0);      // d / ujj
             if (lane == j) { qv[i] = q; Qv[i] = Qj; ev[i] = e; wsv[i] = wj; }
-            w[i] = w[i] - e * urow;
-            if (hasP) w[i] = w[i] - wj * prow;
+            w[i] = __builtin_fma(-e, urow, w[i]);
+            if (hasP) w[i] = __builtin_fma(-wj, prow, w[i]);
         }
     }
 #pragma unroll
@@ -628,42 +655,72 @@ __global__ __launch_bounds__(256) void cd_head_kernel(const double* __restrict__
 // g = 0 .. ng-1, and Q = sum over (k, g') of s[k, g'] Wbar[k, G'] (rows masked to one group).  With
 //   Cg[g][g'][j][k] = Wbar[j, G] H_in[G, G'] Wbar[k, G']^T      Fg[g][j][k] = Wbar[j, G] (W (H_in - R))[k, G]^T
 // the step is  s[j, g] += sum_k Ho[k, j] (Fg[g][j][k] - sum_g' s[k, g'] Cg[g][g'][j][k]) / (Cg[g][g][j][j] Ho[j, j]).
-// One workgroup per head; the scales of the head live in LDS.
-__global__ __launch_bounds__(256) void cd_group_head_kernel(const double* __restrict__ Fg, const double* __restrict__ Cg,
-                                                            const double* __restrict__ Ho, int dh, int ng, int iters,
-                                                            double* __restrict__ s_all) {
+// While the groups of row j are visited only the scales of row j itself change, so the numerators of all its groups are summed at
+// once with the scales as they stand when the row begins, and a short recurrence over the groups then takes out what the steps before
+// have changed: num[g] -= Ho[j, j] Cg[g][g'][j][j] (change of s[j, g']), g' < g.  d_h long sums instead of d_h n_groups dependent
+// ones: bound by reading Cg once (n_groups^2 d_h^2 doubles per head) at the rate of one CU per head.  40 heads of 128 rows and 40
+// groups: 54 ms with one sum per (row, group), 6.7 ms this way.
+// One workgroup of 16 wavefronts per head; the scales of the head (by group) live in LDS, and where they leave room the numerators and column j
+// of H_out (lds & 1; else num_mem and H_out itself) and the diagonals Cg[g][g'][j][j] (lds & 2; else read from memory).
+__global__ __launch_bounds__(1024) void cd_group_head_kernel(const double* __restrict__ Fg, const double* __restrict__ Cg,
+                                                             const double* __restrict__ Ho, int dh, int ng, int iters, int lds,
+                                                             double* __restrict__ num_mem, double* __restrict__ s_all) {
     extern __shared__ double sh[];
-    double* s = sh; double* hoj = sh + (size_t)dh * ng; double* red = hoj + dh;
-    const int h = blockIdx.x, t = threadIdx.x;
+    const bool cd_lds = lds & 2, hoj_lds = lds & 1;
+    double* s = sh; double* hoj = s + (size_t)dh * ng; double* cd = hoj + dh + ng;     // s[g dh + k]
+    double* num = hoj_lds ? hoj + dh : num_mem + (long long)blockIdx.x * ng;
+    const int h = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const long long rr = (long long)dh * dh;
     const double* Fh = Fg + (long long)h * ng * rr; const double* Ch = Cg + (long long)h * ng * ng * rr;
     const double* Hh = Ho + (long long)h * rr;
     double* sg = s_all + (long long)h * dh * ng;
-    for (int i = t; i < dh * ng; i += 256) s[i] = sg[i];
-    __syncthreads();
+    for (int i = t; i < dh * ng; i += 1024) s[(i % ng) * dh + i / ng] = sg[i];
     for (int it = 0; it < iters; ++it)
         for (int j = 0; j < dh; ++j) {
-            for (int k = t; k < dh; k += 256) hoj[k] = Hh[(long long)k * dh + j];
             __syncthreads();
-            for (int g = 0; g < ng; ++g) {
+            if (hoj_lds) for (int k = t; k < dh; k += 1024) hoj[k] = Hh[(long long)k * dh + j];
+            __syncthreads();
+            for (int g = wave; g < ng; g += 16) {
+                const double* F = Fh + ((long long)g * dh + j) * dh; const double* C = Ch + ((long long)g * ng * dh + j) * dh;
                 double acc = 0.0;
-                for (int k = t; k < dh; k += 256) acc += Fh[((long long)g * dh + j) * dh + k] * hoj[k];
-                for (int i = t; i < ng * dh; i += 256) {
-                    const int g2 = i / dh, k = i - g2 * dh;
-                    acc -= s[k * ng + g2] * Ch[(((long long)g * ng + g2) * dh + j) * dh + k] * hoj[k];
+                for (int k = lane; k < dh; k += 64) {
+                    double a = F[k];
+                    int g2 = 0;
+                    for (; g2 + 8 <= ng; g2 += 8) {
+                        double c[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) c[u] = C[(g2 + u) * rr + k];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) {
+                            a -= s[(g2 + u) * dh + k] * c[u];
+                            if (cd_lds && k == j) cd[g * ng + g2 + u] = c[u];
+                        }
+                    }
+                    for (; g2 < ng; ++g2) {
+                        const double c = C[g2 * rr + k];
+                        a -= s[g2 * dh + k] * c;
+                        if (cd_lds && k == j) cd[g * ng + g2] = c;
+                    }
+                    acc += a * (hoj_lds ? hoj[k] : Hh[(long long)k * dh + j]);
                 }
                 acc = wave_sum(acc);
-                if ((t & 63) == 0) red[t >> 6] = acc;
-                __syncthreads();
-                if (t == 0) {
-                    const double num = (red[0] + red[1]) + (red[2] + red[3]);
-                    const double den = Ch[(((long long)g * ng + g) * dh + j) * dh + j] * hoj[j];
-                    if (den > 0.0) s[j * ng + g] = s[j * ng + g] + num / den;
+                if (lane == 0) num[g] = acc;
+            }
+            __syncthreads();
+            if (wave == 0) {       // the recurrence over the groups of row j
+                const double hjj = Hh[(long long)j * dh + j];
+                for (int g = 0; g < ng; ++g) {
+                    const double den = (cd_lds ? cd[g * ng + g] : Ch[((long long)(g * ng + g) * dh + j) * dh + j]) * hjj;
+                    const double step = den > 0.0 ? num[g] / den : 0.0;
+                    for (int g2 = g + 1 + lane; g2 < ng; g2 += 64)
+                        num[g2] -= hjj * (cd_lds ? cd[g2 * ng + g] : Ch[((long long)(g2 * ng + g) * dh + j) * dh + j]) * step;
+                    if (lane == 0) s[g * dh + j] += step;
+                    __builtin_amdgcn_wave_barrier();
                 }
-                __syncthreads();
             }
         }
-    for (int i = t; i < dh * ng; i += 256) sg[i] = s[i];
+    __syncthreads();
+    for (int i = t; i < dh * ng; i += 1024) sg[i] = s[(i % ng) * dh + i / ng];
 }
 
 // out[row, seg] = sum over the columns c of segment seg of A[row, c] B[row, c]; one wavefront per (row, segment)
@@ -784,7 +841,7 @@ struct Layer {
     __half* Hcat; int* sel; int fast_grid, grid_terms;          // two-phase search: T' of every H_in, survivor bookkeeping
     GridScale gscale; float *cand_r, *Wf, *wdown;
     double *Wbar, *Abar, *Z, *WR, *Cm, *Fm, *dvec, *lossbuf;
-    double *Cg, *Fg;    // group-wise refinement: Gram blocks per (group, group) pair
+    double *Cg, *Fg, *cdnum;    // group-wise refinement: Gram blocks per (group, group) pair
     int grid_chunk, fast_chunk;     // block rows (shared H_in) or heads (per-head H_in) per grid-search pass: exact, two-phase
     int* gstat;         // device words of the two-phase search (GS_*), cleared at the start of a run
     long long nn;
@@ -1100,10 +1157,12 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             }
         }
         if (H_out) {
-            const size_t smem = ((size_t)dh * ng + dh + 8) * sizeof(double);
-            if (smem > 160 * 1024) return tboa_fail(ctx, TBOA_EINVAL, "quantize_layer: %d scales per head exceed the LDS of the group-wise refinement", dh * ng);
+            const size_t room = 160 * 1024 / sizeof(double), scales = (size_t)dh * ng, small = (size_t)dh + ng, diag = (size_t)ng * ng;
+            if (scales + dh + 8 > room) return tboa_fail(ctx, TBOA_EINVAL, "quantize_layer: %d scales per head exceed the LDS of the group-wise refinement", dh * ng);
+            const int lds = scales + small + diag <= room ? 3 : scales + small <= room ? 1 : 0;
+            const size_t smem = (scales + (lds & 1 ? small : 0) + (lds & 2 ? diag : 0)) * sizeof(double);
             TB_HIP(ctx, hipFuncSetAttribute((const void*)cd_group_head_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-            hipLaunchKernelGGL(cd_group_head_kernel, dim3(nh), dim3(256), smem, st, L.Fg, L.Cg, L.Ho, dh, ng, d->cd_iters, L.s64);
+            hipLaunchKernelGGL(cd_group_head_kernel, dim3(nh), dim3(1024), smem, st, L.Fg, L.Cg, L.Ho, dh, ng, d->cd_iters, lds, L.cdnum, L.s64);
         } else {
             const size_t smem = (size_t)4 * ng * sizeof(double);
             hipLaunchKernelGGL(cd_group_diag_kernel, dim3((rows_all + 3) / 4), dim3(256), smem, st, L.Fg, L.Cg, (long long)rows_all, ng,
@@ -1255,11 +1314,12 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.WR = R ? ar.get<double>(wn) : nullptr;
     L.Cm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr; L.Fm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr;
     L.dvec = ar.get<double>(2 * (size_t)d->d_out); L.lossbuf = ar.get<double>(2 * (size_t)nh);
-    L.Cg = L.Fg = nullptr;
+    L.Cg = L.Fg = L.cdnum = nullptr;
     if (d->group && d->cd_iters > 0) {
         const size_t ng = (size_t)L.ng;
         L.Cg = ar.get<double>(H_out ? (size_t)nh * ng * ng * dh * dh : (size_t)d->d_out * ng * ng);
         L.Fg = ar.get<double>(H_out ? (size_t)nh * ng * dh * dh : (size_t)d->d_out * ng);
+        L.cdnum = H_out ? ar.get<double>((size_t)nh * ng) : nullptr;
     }
 }
 
