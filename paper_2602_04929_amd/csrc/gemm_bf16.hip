@@ -60,9 +60,9 @@ struct Args {
     // term_dB bytes (the distance to the next pair's buffer less the columns just read); term_segs = 0: one pair
     int term_segs;
     long long term_dA[3], term_dB[3];
-    // dispatched LDS-direct kernel, repeated left operand: every segment reads the same columns of A, segment t of B lies t * rep_dB bytes
-    // on, and segs[batch entry] (device memory) says how many segments there are; rep_dB = 0: ordinary segments
-    long long rep_dB; const int* segs;
+    // dispatched LDS-direct kernel: term_dA / term_dB are the distances in bytes from one pair's buffer to the next; segs (or null) says per
+    // batch entry how many pairs are taken; last_scale: see GemmBf16
+    const int* segs; float last_scale;
 };
 
 // Work item of this workgroup.  Workgroups are dealt to the eight XCDs round-robin by their linear number, so workgroup
@@ -385,7 +385,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     const __hip_bfloat16* B = g.B + z1 * g.sB1 + z2 * g.sB2;
 
     const int seg_len = g.kseg > 0 ? g.kseg : g.K;
-    const int nseg = g.segs ? __builtin_amdgcn_readfirstlane(g.segs[z]) : g.kseg > 0 ? g.K / g.kseg : 1;
+    int nseg = g.kseg > 0 ? g.K / g.kseg : 1;
+    if (g.segs) nseg = min(nseg, __builtin_amdgcn_readfirstlane(g.segs[z]));
     int kend = seg_len;
     if (causal) kend = min(kend, n0 + BN);
     const int kbeg = (g.flags & TBOA_GEMM_KLO) ? min(kend, max(m0, n0)) : 0;      // a multiple of the tile size
@@ -426,12 +427,12 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     const char* Brow = (const char*)(B + (long long)n0 * g.ldb);
     // byte offset along k of the next stage to be issued (stages are issued strictly in order), kept incrementally;
     // in a blocked operand 32 k are one block of 1 KB, not 64 bytes of a row
-    long long koff_next = 2LL * kbeg; int kin_next = kbeg;
+    long long koff_next = 2LL * kbeg; int kin_next = kbeg, term = 0;
     auto advance = [&]() {
         kin_next += FK; koff_next += 2 * FK;
         if (kin_next == kend) {
             kin_next = kbeg;
-            if (g.rep_dB) { koff_next = 2LL * kbeg; Brow += g.rep_dB; }
+            if (g.term_segs) { koff_next = 2LL * kbeg; Arow += g.term_dA[term]; Brow += g.term_dB[term]; if (term < 2) ++term; }
             else koff_next += 2LL * (seg_len - kend + kbeg);
         }
     };
@@ -520,13 +521,26 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
         __syncthreads();
         TB_LOAD_FRAGS(0, 0, 0)
         int kt = 0;
+        const int kscale = (g.last_scale != 1.f && nseg > 1) ? nk - nk_seg : -1;      // the stage at which the last term begins
+        auto rescale = [&]() {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] *= g.last_scale;
+        };
         // steady state, unrolled over the ring so that slot numbers are constants: the loads of stages kt+2 and kt+3 may
         // stay in flight while stage kt+1 is awaited
         for (; kt + 2 * NS - 1 < nk; kt += NS) {
+            if (kt == kscale) rescale();               // (a term is a whole number of turns of the ring then)
 #pragma unroll
             for (int u = 0; u < NS; ++u) TB_STAGE_STEADY(kt + u, u, (u + 1) % NS)
         }
-        for (; kt < nk; ++kt) TB_STAGE_TAIL(kt, kt % NS, (kt + 1) % NS)
+        for (; kt < nk; ++kt) {
+            if (kt == kscale) rescale();
+            TB_STAGE_TAIL(kt, kt % NS, (kt + 1) % NS)
+        }
     }
 #undef TB_STAGE_STEADY
 #undef TB_STAGE_TAIL
@@ -884,26 +898,27 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     }
     const bool f16 = (q.flags & TBOA_GEMM_F16) != 0;
     a.term_segs = 0;
-    a.rep_dB = 2 * q.rep_strideB; a.segs = q.segs;
-    if ((q.segs != nullptr) != (q.rep_strideB != 0) || (q.segs && (!fast || q.kseg > 0 || (q.flags & TBOA_GEMM_PERSISTENT) || q.rep_strideB % 8)))
-        return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: a repeated left operand needs the dispatched LDS-direct kernel");
+    a.segs = q.segs; a.last_scale = q.last_scale;
     if (q.nterms > 1) {
-        const bool pers = fast && (q.kseg > 0 ? q.kseg : q.K) % (FK * 4) == 0 && (q.flags & TBOA_GEMM_PERSISTENT) != 0;
-        const int seg = q.kseg > 0 ? q.kseg : q.K;
-        if (!pers || q.nterms > 4 || q.K % q.nterms || (q.K / q.nterms) % seg)
-            return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: several operand pairs need the persistent kernel, at most 4 pairs, whole segments per pair");
-        const long long term_cols = q.K / q.nterms;
-        const long long bytesA = (term_cols * 2) << ((q.flags & TBOA_GEMM_A_TILED) ? 4 : 0), bytesB = (term_cols * 2) << ((q.flags & TBOA_GEMM_B_TILED) ? 4 : 0);
+        const bool pers = (q.flags & TBOA_GEMM_PERSISTENT) != 0;
+        const long long term_cols = q.segs ? q.K : q.K / q.nterms;
+        const int seg = (pers && q.kseg > 0) ? q.kseg : pers ? q.K : (int)term_cols;
+        if (!fast || q.nterms > 4 || (!q.segs && q.K % q.nterms) || term_cols % seg || (pers && seg % (FK * 4)) || (!pers && (q.kseg > 0 || term_cols % FK)) ||
+            (pers && (q.segs || q.last_scale != 1.f)) || (q.last_scale != 1.f && term_cols % (FK * 4)))
+            return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: several operand pairs need an LDS-direct kernel, at most 4 pairs, whole segments per pair");
+        // (the persistent kernel goes on from the end of a pair's columns, the dispatched one from their beginning)
+        const long long bytesA = pers ? (term_cols * 2) << ((q.flags & TBOA_GEMM_A_TILED) ? 4 : 0) : 0, bytesB = pers ? (term_cols * 2) << ((q.flags & TBOA_GEMM_B_TILED) ? 4 : 0) : 0;
         for (int t = 0; t < q.nterms; ++t)
             if (!q.termA[t] || !q.termB[t] || ((uintptr_t)q.termA[t] & 15) || ((uintptr_t)q.termB[t] & 15))
                 return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: operand pair %d missing or not 16-byte aligned", t);
         if (q.termA[0] != q.A || q.termB[0] != q.B) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: the first operand pair must be (A, B)");
-        a.term_segs = (int)(term_cols / seg);
+        a.term_segs = pers ? (int)(term_cols / seg) : 1;
+        if (!pers) { a.kseg = (int)term_cols; a.K = (int)term_cols * q.nterms; }
         for (int t = 0; t + 1 < q.nterms; ++t) {
             a.term_dA[t] = ((const char*)q.termA[t + 1] - (const char*)q.termA[t]) - bytesA;
             a.term_dB[t] = ((const char*)q.termB[t + 1] - (const char*)q.termB[t]) - bytesB;
         }
-    }
+    } else if (q.segs || q.last_scale != 1.f) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: terms to choose from or to scale need several operand pairs");
     const bool persistent = fast && (q.kseg > 0 ? q.kseg : q.K) % (FK * 4) == 0 && (q.flags & TBOA_GEMM_PERSISTENT) != 0;
     if (persistent) {
         int wgs = 0;

@@ -294,12 +294,12 @@ __global__ __launch_bounds__(256) void int_form_kernel(const float* __restrict__
     if (threadIdx.x == 0) { step[blockIdx.x] = st; if (!all_ok || !(st > 0.f)) atomicOr(fail, 1); }
 }
 
-// V^T fp32 [rows, G*L] (times row_scale, if given) -> per-sequence segments of length L: (hi, hi, lo) of V^T in segments
+// V^T fp32 [rows, G*L] (times row_scale, if given) -> per-sequence segments of L columns, Lp apart (the caller has cleared what lies between): (hi, hi, lo) of V^T in segments
 // 0, 1, 2 and, when the full-precision V~^T is given, (hi, hi, lo) of V~^T in segments 3, 4, 5
 __global__ void vt_segments_kernel(const float* __restrict__ in, const float* __restrict__ row_scale, const float* __restrict__ in_fp,
-                                   bf16* __restrict__ out, int rows, int G, int L, int nseg, long long ld, int f16) {
+                                   bf16* __restrict__ out, int rows, int G, int L, int Lp, int nseg, long long ld, int f16) {
     const long long tot = (long long)rows * G * L;
-    if (L % 4 == 0 && ld % 4 == 0 && ((uintptr_t)out & 7) == 0) {     // four consecutive tokens per thread: 16-byte streaming loads, 8-byte stores
+    if (L % 4 == 0 && Lp % 4 == 0 && ld % 4 == 0 && ((uintptr_t)out & 7) == 0) {     // four consecutive tokens per thread: 16-byte streaming loads, 8-byte stores
         typedef float f4 __attribute__((ext_vector_type(4)));
         for (long long i4 = blockIdx.x * (long long)blockDim.x + threadIdx.x; i4 < tot / 4; i4 += (long long)gridDim.x * blockDim.x) {
             const long long i = 4 * i4, row = i / ((long long)G * L); const int s = (int)((i / L) % G), t = (int)(i % L);
@@ -313,9 +313,9 @@ __global__ void vt_segments_kernel(const float* __restrict__ in, const float* __
                 h.b[j] = enc16(v[j], f16); l.b[j] = enc16(v[j] - dec16(h.b[j], f16), f16);
                 wh.b[j] = enc16(w[j], f16); wl.b[j] = enc16(w[j] - dec16(wh.b[j], f16), f16);
             }
-            bf16* o = out + row * ld + ((long long)s * nseg) * L + t;
-            *(uint2*)o = h.u; *(uint2*)(o + L) = h.u; *(uint2*)(o + 2 * L) = l.u;
-            if (in_fp) { *(uint2*)(o + 3 * L) = wh.u; *(uint2*)(o + 4 * L) = wh.u; *(uint2*)(o + 5 * L) = wl.u; }
+            bf16* o = out + row * ld + ((long long)s * nseg) * Lp + t;
+            *(uint2*)o = h.u; *(uint2*)(o + Lp) = h.u; *(uint2*)(o + 2 * Lp) = l.u;
+            if (in_fp) { *(uint2*)(o + 3 * Lp) = wh.u; *(uint2*)(o + 4 * Lp) = wh.u; *(uint2*)(o + 5 * Lp) = wl.u; }
         }
         return;
     }
@@ -323,27 +323,28 @@ __global__ void vt_segments_kernel(const float* __restrict__ in, const float* __
         const long long row = i / ((long long)G * L); const int s = (int)((i / L) % G), t = (int)(i % L);
         const float v = row_scale ? in[i] * row_scale[row] : in[i];
         const bf16 h = enc16(v, f16);
-        bf16* o = out + row * ld + ((long long)s * nseg) * L + t;
-        o[0] = h; o[L] = h; o[2 * L] = enc16(v - dec16(h, f16), f16);
-        if (in_fp) { const float w = in_fp[i]; const bf16 wh = enc16(w, f16); o[3 * L] = wh; o[4 * L] = wh; o[5 * L] = enc16(w - dec16(wh, f16), f16); }
+        bf16* o = out + row * ld + ((long long)s * nseg) * Lp + t;
+        o[0] = h; o[Lp] = h; o[2 * Lp] = enc16(v - dec16(h, f16), f16);
+        if (in_fp) { const float w = in_fp[i]; const bf16 wh = enc16(w, f16); o[3 * Lp] = wh; o[4 * Lp] = wh; o[5 * Lp] = enc16(w - dec16(wh, f16), f16); }
     }
 }
 
 // P[t, k] = A[t, k] (and once more at column hi2col + k, and its low part A - P[t, k] at locol + k, when those are not
 // negative), A = softmax over the first t+1 (causal) or L entries of the score row; with a
 // second score matrix S2 also P[t, dcol + k] = A[t, k] - A2[t, k], the difference taken in fp32 before rounding, or
-// (pair2) A2 itself as (hi, lo, hi) in the three segments of L columns from dcol.
-// Zero up to the next multiple of 256 (the k-loop of the consumer stops there).  One wavefront per row, y = head.
-__global__ __launch_bounds__(256) void softmax_bf16_kernel(const float* __restrict__ S, const float* __restrict__ S2, int L, int causal,
+// (pair2) A2 itself as (hi, lo, hi) in the three segments of Lp columns from dcol.
+// Zero up to the next multiple of 256 (the k-loop of the consumer stops there).  One wavefront per row, y = head.  Rows and columns
+// L .. Lp - 1 (Lp: L rounded up to whole 32s, so that the products take whole k-steps) are written as zeros.
+__global__ __launch_bounds__(256) void softmax_bf16_kernel(const float* __restrict__ S, const float* __restrict__ S2, int L, int Lp, int causal,
                                                            bf16* __restrict__ P, long long ldp, long long head_stride, int hi2col, int locol, int dcol, int f16,
                                                            int pair2) {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= L) return;
-    const long long so = ((long long)blockIdx.y * L + t) * L;
+    if (t >= Lp) return;
+    const long long so = ((long long)blockIdx.y * L + min(t, L - 1)) * L;
     const float* s = S + so; const float* s2 = S2 ? S2 + so : nullptr;
     bf16* p = P + blockIdx.y * head_stride + (long long)t * ldp;
-    const int kend = causal ? t + 1 : L;
-    int kz = ((kend + 255) / 256) * 256; if (kz > L) kz = L;
+    const int kend = t >= L ? 0 : causal ? t + 1 : L;
+    int kz = causal ? (t / 256 + 1) * 256 : Lp; if (kz > Lp) kz = Lp;
     float m = -INFINITY, m2 = -INFINITY;
     for (int k = lane; k < kend; k += 64) { m = fmaxf(m, s[k]); if (s2) m2 = fmaxf(m2, s2[k]); }
 #pragma unroll
@@ -361,7 +362,7 @@ __global__ __launch_bounds__(256) void softmax_bf16_kernel(const float* __restri
         if (locol >= 0) p[locol + k] = enc16(a - dec16(v, f16), f16);
         if (s2) {
             const float a2 = k < kend ? __expf(s2[k] - m2) * inv2 : 0.f;
-            if (pair2) { const bf16 v2 = enc16(a2, f16); p[dcol + k] = v2; p[dcol + L + k] = enc16(a2 - dec16(v2, f16), f16); p[dcol + 2 * L + k] = v2; }
+            if (pair2) { const bf16 v2 = enc16(a2, f16); p[dcol + k] = v2; p[dcol + Lp + k] = enc16(a2 - dec16(v2, f16), f16); p[dcol + 2 * Lp + k] = v2; }
             else p[dcol + k] = enc16(a - a2, f16);
         }
     }
@@ -371,26 +372,26 @@ __global__ __launch_bounds__(256) void softmax_bf16_kernel(const float* __restri
 // once with 16-byte loads and kept in registers (lane l holds scores 256 c + 4 l .. + 3 of chunk c), each exponential
 // is taken once, and the probabilities leave as 8-byte stores.
 template <int NCH>
-__global__ __launch_bounds__(256) void softmax_bf16_regs_kernel(const float* __restrict__ S, const float* __restrict__ S2, int L, int causal,
+__global__ __launch_bounds__(256) void softmax_bf16_regs_kernel(const float* __restrict__ S, const float* __restrict__ S2, int L, int Lp, int causal,
                                                                 bf16* __restrict__ P, long long ldp, long long head_stride, int hi2col, int locol, int dcol,
                                                                 int blocked, int f16, int pair2) {
     const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= L) return;
+    if (t >= Lp) return;
     // heads from the last to the first: the score product wrote them in ascending order, so the last ones are the part of the
     // scores the memory-side cache still holds (measured: 175 -> 169 us on 32 heads x 2048^2)
     const int hy = gridDim.y - 1 - blockIdx.y;
-    const long long so = ((long long)hy * L + t) * L;
+    const long long so = ((long long)hy * L + min(t, L - 1)) * L;
     const float* s = S + so; const float* s2 = S2 ? S2 + so : nullptr;
     bf16* p = P + hy * head_stride + (blocked ? 0 : (long long)t * ldp);
-    const int kend = causal ? t + 1 : L;
-    int kz = ((kend + 255) / 256) * 256; if (kz > L) kz = L;
+    const int kend = t >= L ? 0 : causal ? t + 1 : L;
+    int kz = causal ? (t / 256 + 1) * 256 : Lp; if (kz > Lp) kz = Lp;
     float v[NCH][4], w[NCH][4];
     float m = -INFINITY, m2 = -INFINITY;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const int k = c * 256 + lane * 4;
         float4 a = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY), b = a;
-        if (k < kz) {     // the scores are read this once: streaming loads leave the L2 to the probabilities being written
+        if (k < kend) {     // (L % 4 == 0: four scores at a time stay in the row) the scores are read this once: streaming loads leave the L2 to the probabilities being written
             typedef float f4 __attribute__((ext_vector_type(4)));
             const f4 ta = __builtin_nontemporal_load((const f4*)(s + k)); a = make_float4(ta.x, ta.y, ta.z, ta.w);
             if (s2) { const f4 tb = __builtin_nontemporal_load((const f4*)(s2 + k)); b = make_float4(tb.x, tb.y, tb.z, tb.w); }
@@ -410,12 +411,12 @@ __global__ __launch_bounds__(256) void softmax_bf16_regs_kernel(const float* __r
     for (int c = 0; c < NCH; ++c)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            v[c][i] = __expf(v[c][i] - m); sum += v[c][i];
-            if (s2) { w[c][i] = __expf(w[c][i] - m2); sum2 += w[c][i]; }
+            v[c][i] = kend ? __expf(v[c][i] - m) : 0.f; sum += v[c][i];
+            if (s2) { w[c][i] = kend ? __expf(w[c][i] - m2) : 0.f; sum2 += w[c][i]; }
         }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { sum += __shfl_xor(sum, o, 64); sum2 += __shfl_xor(sum2, o, 64); }
-    const float inv = 1.f / sum, inv2 = s2 ? 1.f / sum2 : 0.f;
+    const float inv = kend ? 1.f / sum : 0.f, inv2 = (s2 && kend) ? 1.f / sum2 : 0.f;
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
         const int k = c * 256 + lane * 4;
@@ -435,15 +436,15 @@ __global__ __launch_bounds__(256) void softmax_bf16_regs_kernel(const float* __r
             if (locol >= 0) *(uint2*)(p + tboa_blocked_offset(t, (long long)locol + k, ldp >> 5)) = pl.u;
             if (s2) *(uint2*)(p + tboa_blocked_offset(t, dcol + k, ldp >> 5)) = pd.u;
             if (s2 && pair2) {
-                *(uint2*)(p + tboa_blocked_offset(t, (long long)dcol + L + k, ldp >> 5)) = pe.u;
-                *(uint2*)(p + tboa_blocked_offset(t, (long long)dcol + 2 * L + k, ldp >> 5)) = pd.u;
+                *(uint2*)(p + tboa_blocked_offset(t, (long long)dcol + Lp + k, ldp >> 5)) = pe.u;
+                *(uint2*)(p + tboa_blocked_offset(t, (long long)dcol + 2 * Lp + k, ldp >> 5)) = pd.u;
             }
         } else {
             *(uint2*)(p + k) = pa.u;
             if (hi2col >= 0) *(uint2*)(p + hi2col + k) = pa.u;
             if (locol >= 0) *(uint2*)(p + locol + k) = pl.u;
             if (s2) *(uint2*)(p + dcol + k) = pd.u;
-            if (s2 && pair2) { *(uint2*)(p + dcol + L + k) = pe.u; *(uint2*)(p + dcol + 2 * L + k) = pd.u; }
+            if (s2 && pair2) { *(uint2*)(p + dcol + Lp + k) = pe.u; *(uint2*)(p + dcol + 2 * Lp + k) = pd.u; }
         }
     }
 }
@@ -811,11 +812,17 @@ int gram_splitk(tboa_ctx* ctx, int splits, int n, int npairs, const GramPair* pa
     GemmBf16 g = nt(n, n, Kc, 1.f, pairs[0].A, ld, pairs[0].B, ld, part, n, TBOA_F32, 0, (lower ? TBOA_GEMM_LOWER : 0) | (f16 ? TBOA_GEMM_F16 : 0));
     g.tag = TBOA_PROF_GRAM; g.flags &= ~TBOA_GEMM_PERSISTENT;
     g.batch = splits; g.strideA = Kc; g.strideB = Kc; g.strideC = (long long)n * n;
-    if (lower) TB_TRY(launch_fill_f32(ctx, part, (int64_t)splits * n * n, 0.f));
-    for (int p = 0; p < npairs; ++p) {
-        g.A = pairs[p].A; g.B = pairs[p].B; g.accumulate = p ? 1 : 0;
+    // all pairs in one pass over the accumulators (one launch per pair read and wrote the partial sums again each time; the pairs come with
+    // the small products first, so that the sum rounds where the large ones do); K a multiple of 32 does it, else pair by pair
+    if (npairs > 1 && Kc % 32 == 0) {
+        g.nterms = npairs; g.K = Kc * npairs;
+        for (int p = 0; p < npairs; ++p) { g.termA[p] = pairs[p].A; g.termB[p] = pairs[p].B; }
         TB_TRY(gemm_bf16_nt(ctx, g));
-    }
+    } else
+        for (int p = 0; p < npairs; ++p) {
+            g.A = pairs[p].A; g.B = pairs[p].B; g.accumulate = p ? 1 : 0;
+            TB_TRY(gemm_bf16_nt(ctx, g));
+        }
     const bool aligned16 = (((uintptr_t)part | (uintptr_t)out) & 15) == 0;
     const int vec = (!lower && aligned16 && ((long long)n * n) % 4 == 0) ? 1 : 0;
     if (lower) {
@@ -829,7 +836,7 @@ int gram_splitk(tboa_ctx* ctx, int splits, int n, int npairs, const GramPair* pa
 }
 int gram_splitk(tboa_ctx* ctx, int splits, int n, const bf16* A, const bf16* A_lo, const bf16* B, long long ld, int K, double scale, int lower,
                 float* part, float* out) {
-    const GramPair pairs[2] = {{A, B}, {A_lo, B}};
+    const GramPair pairs[2] = {{A_lo ? A_lo : A, B}, {A, B}};
     return gram_splitk(ctx, splits, n, A_lo ? 2 : 1, pairs, ld, K, scale, lower, part, out);
 }
 
@@ -899,22 +906,31 @@ int scores_pair(const Dims& D, const bf16* Qh, const bf16* Kh, const bf16* Qhf, 
 }
 
 // probabilities in 16 x 32 blocks (per head) when `blocked`: see blocked_inputs
-int softmax(const Dims& D, const float* Sc, const float* Sc2, bf16* P, long long ldp, int hi2col, int locol, int dcol, int blocked = 0, int pair2 = 0) {
+int softmax(const Dims& D, const float* Sc, const float* Sc2, bf16* P, int Lp, long long ldp, int hi2col, int locol, int dcol, int blocked = 0, int pair2 = 0) {
     if (D.L % 4 == 0 && D.L <= 2048 && ldp % 4 == 0 && dcol % 4 == 0)
-        hipLaunchKernelGGL(softmax_bf16_regs_kernel<8>, dim3((D.L + 3) / 4, D.Hq), dim3(256), 0, D.ctx->stream, Sc, Sc2, D.L, D.d->causal, P,
-                           ldp, (long long)D.L * ldp, hi2col, locol, dcol, blocked, D.f16, pair2);
+        hipLaunchKernelGGL(softmax_bf16_regs_kernel<8>, dim3((Lp + 3) / 4, D.Hq), dim3(256), 0, D.ctx->stream, Sc, Sc2, D.L, Lp, D.d->causal, P,
+                           ldp, (long long)Lp * ldp, hi2col, locol, dcol, blocked, D.f16, pair2);
     else if (blocked) return tboa_fail(D.ctx, TBOA_EINVAL, "softmax: blocked probabilities need the in-register kernel");
     else
-        hipLaunchKernelGGL(softmax_bf16_kernel, dim3((D.L + 3) / 4, D.Hq), dim3(256), 0, D.ctx->stream, Sc, Sc2, D.L, D.d->causal, P, ldp,
-                           (long long)D.L * ldp, hi2col, locol, dcol, D.f16, pair2);
+        hipLaunchKernelGGL(softmax_bf16_kernel, dim3((Lp + 3) / 4, D.Hq), dim3(256), 0, D.ctx->stream, Sc, Sc2, D.L, Lp, D.d->causal, P, ldp,
+                           (long long)Lp * ldp, hi2col, locol, dcol, D.f16, pair2);
     TB_HIP(D.ctx, hipGetLastError());
     return 0;
 }
 
+// Sequence length as the products over a sequence see it: whole 32s, the k-step of the LDS-direct GEMM kernels.  (With the true length 1000
+// they ran on the register-staged kernel: 8.3 of 10.5 ms of the Hessians of 5 x 1000 tokens, d = 1536.)  What lies beyond the
+// sequence is zero in both operands.
+int padded_len(int L) { return (L + 31) / 32 * 32; }
+// the same for a contraction over all tokens in `splits` parts (the parts need not end where sequences do)
+long long padded_tokens(long long T, int splits) { return (T + 32LL * splits - 1) / (32LL * splits) * (32LL * splits); }
+// clears a 16-bit buffer of n elements whose columns beyond the data take part in a product
+int clear16(tboa_ctx* ctx, bf16* p, long long n) { return launch_fill_f32(ctx, (float*)p, n / 2, 0.f); }
+
 // The transposed activations and the probabilities are operands of the A X products only: they are kept in the GEMM's
 // 16 x 32 blocks when the shapes allow (whole blocks, the in-register softmax)
 bool blocked_inputs(const Dims& D) {
-    return D.L % 32 == 0 && D.L <= 2048 && D.dm % 16 == 0;
+    return D.L % 4 == 0 && D.L <= 2048 && D.dm % 16 == 0;
 }
 
 // The form of the W_V Hessian that works on L x L Gram matrices of the probabilities (see build_hessians_bf16): needs
@@ -956,7 +972,9 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     int G = d->seq_chunk > 0 ? d->seq_chunk : 8; if (G > D.S) G = D.S;
     // segments of P / of the transposed chunk ([X | dX | X~]; summed form: every one twice, for the (hi, lo) operands it meets)
     const int nsg = rv ? 2 : 1, nsx = (grouped ? 2 : 1) * (rv ? 3 : 1), splits = pick_splits(D.S);
-    const long long dd = (long long)dm * dm, hh = (long long)dh * dh, TP = (long long)T + PADE;
+    const int Lp = padded_len(L);       // (the summed form has whole 256-tiles: Lp = L there)
+    const long long Tp = padded_tokens(T, splits);
+    const long long dd = (long long)dm * dm, hh = (long long)dh * dh, TP = Tp + PADE;
     // summed form: pitches of the transposed probabilities, of [B1_hi | B1_lo | B2^T_hi | B2^T_lo], of the chunk buffers
     const long long ldpt = (long long)rep * L + PADE, ldbc = (rv ? 4LL : 2LL) * L + PADE, ldg = (long long)G * L + PADE;
     // summed form: the L x L Gram matrices of a group are built as `parts` partial sums over subsets of its heads (added up
@@ -979,7 +997,7 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
         Qhf = rv ? ar.get<bf16>((size_t)G * L * dq * 3) : nullptr; Khf = rv ? ar.get<bf16>((size_t)G * L * dkv * 3) : nullptr;
         Sc = fused ? nullptr : ar.get<float>((size_t)Hq * L * L); Scf = (rv && !fused) ? ar.get<float>((size_t)Hq * L * L) : nullptr;
         amx = ar.get<int>((size_t)4 * G);
-        XcT = ar.get<bf16>((size_t)dm * (G * nsx * L + PADE));
+        XcT = ar.get<bf16>((size_t)dm * (G * nsx * Lp + PADE));
         if (grouped) {
             P = nullptr;
             pt.hi = ar.get<bf16>((size_t)Hkv * L * ldpt); pt.lo = ar.get<bf16>((size_t)Hkv * L * ldpt);
@@ -990,8 +1008,8 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             YT = ar.get<bf16>((size_t)Hkv * dm * ldg); YTl = ar.get<bf16>((size_t)Hkv * dm * ldg);
             dYT = rv ? ar.get<bf16>((size_t)Hkv * dm * ldg) : nullptr; dYTl = rv ? ar.get<bf16>((size_t)Hkv * dm * ldg) : nullptr;
         } else {
-            P = ar.get<bf16>((size_t)Hq * L * (nsg * L + PADE));
-            YT = ar.get<bf16>((size_t)Hkv * dm * (rep * G * L + PADE)); dYT = rv ? ar.get<bf16>((size_t)Hkv * dm * (rep * G * L + PADE)) : nullptr;
+            P = ar.get<bf16>((size_t)Hq * Lp * (nsg * Lp + PADE));
+            YT = ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)); dYT = rv ? ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)) : nullptr;
         }
         Hin64 = ar.get<double>((size_t)dd); Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm);
         Wo64 = ar.get<double>((size_t)dm * dq); Tq = ar.get<double>((size_t)dq * dm); Tk = ar.get<double>((size_t)dkv * dm);
@@ -1001,9 +1019,11 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     hipStream_t st = ctx->stream;
     // ---- H_in and R for W_Q / W_K
     if (Hin_qk) {
+    if (Tp != T)
+        for (bf16* p : {XT, dXh, dXl}) if (p) TB_TRY(clear16(ctx, p, dm * TP));
     TB_TRY(transpose(D, X, fp ? X_fp : nullptr, dm, T, dm, XT, fp ? dXh : nullptr, dXl, TP));
-    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, T, 1.0, 1, part, Hin_qk));
-    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, T, d->alpha, 0, part, R_qk));
+    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk));
+    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk));
     // ---- H_out: K_g^T K_g = W_K,g H_in W_K,g^T ; sum_h Q_h^T Q_h ; sum_h W_out,h^T W_out,h   (fp64)
     // (the wide product W_Q H_in, d_q x d x d, is taken with the triangular half of H_in; the d_h x d_h products of a group's heads
     // are one launch whose terms are summed in fp64: as one launch per head of the group they ran on n_kv_heads workgroups)
@@ -1064,12 +1084,12 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     TB_TRY(launch_fill_f32(ctx, Hin_v, (int64_t)Hkv * dd, 0.f));
     if (rv) TB_TRY(launch_fill_f32(ctx, R_v, (int64_t)Hkv * dd, 0.f));
     const int cflag = d->causal ? TBOA_GEMM_CAUSAL_K : 0;
-    const bool blocked = dm % 256 == 0 && L % 256 == 0;
+    const bool blocked = dm % 256 == 0 && Lp % 256 == 0;
     const int bin = grouped ? 1 : blocked_inputs(D);      // (the grouped form has whole blocks by its own conditions)
     for (int s0 = 0; s0 < D.S; s0 += G) {
         const int Gc = (D.S - s0 < G) ? D.S - s0 : G;
         const long long t0 = (long long)s0 * L;
-        const long long ldx = (long long)Gc * nsx * L + PADE, ky = (long long)rep * Gc * L, ldy = ky + PADE, ldp = (long long)nsg * L + PADE;
+        const long long ldx = (long long)Gc * nsx * Lp + PADE, ky = (long long)rep * Gc * Lp, ldy = ky + PADE, ldp = (long long)nsg * Lp + PADE;
         // the fused kernel takes scaled half operands (22 significant bits in the scores instead of 16); the GEMM path bf16 pairs
         int *aq = fused ? amx : nullptr, *ak = fused ? amx + G : nullptr, *aqf = fused ? amx + 2 * G : nullptr, *akf = fused ? amx + 3 * G : nullptr;
         TB_TRY(project_qk(D, X + t0 * dm, Gc * L, Wq, nullptr, Wk, nullptr, Qf, Kf, Qh, Kh, nullptr, nullptr, aq, ak));
@@ -1081,9 +1101,10 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
         }
         if (rv) TB_TRY(project_qk(D, X_fp + t0 * dm, Gc * L, Wq, nullptr, Wk, nullptr, Qf, Kf, Qhf, Khf, nullptr, nullptr, aqf, akf));
         const long long is = bin ? 16 : 1;      // a column offset c into a blocked matrix is the pointer offset 16 c
+        if (Lp != L) TB_TRY(clear16(ctx, XcT, dm * ldx));
         for (int sl = 0; sl < Gc; ++sl) {   // XcT[:, sl, :, :] = X_s^T | (X_s - X~_s)^T | X~_s^T
             const bf16* xs = X + (t0 + (long long)sl * L) * dm;
-            bf16* o = XcT + is * sl * nsx * L;
+            bf16* o = XcT + is * sl * nsx * Lp;
             if (grouped) {      // [X | X | dX | dX | X~ | X~], and X_s^T once more as bf16 (the exact input), the chunk's sequences side by side
                 const bf16* xf = rv ? X_fp + (t0 + (long long)sl * L) * dm : nullptr;
                 for (int c = 0; c < 2; ++c) {
@@ -1095,8 +1116,8 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             } else if (!rv) TB_TRY(transpose(D, xs, nullptr, dm, L, dm, o, nullptr, nullptr, ldx, bin, D.f16));
             else {
                 const bf16* xf = X_fp + (t0 + (long long)sl * L) * dm;
-                TB_TRY(transpose(D, xs, xf, dm, L, dm, o, o + is * L, nullptr, ldx, bin, D.f16));
-                TB_TRY(transpose(D, xf, nullptr, dm, L, dm, o + is * 2 * L, nullptr, nullptr, ldx, bin, D.f16));
+                TB_TRY(transpose(D, xs, xf, dm, L, dm, o, o + is * Lp, nullptr, ldx, bin, D.f16));
+                TB_TRY(transpose(D, xf, nullptr, dm, L, dm, o + is * 2 * Lp, nullptr, nullptr, ldx, bin, D.f16));
             }
         }
         if (grouped) {
@@ -1152,13 +1173,14 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             GemmBf16 h = nt(dm, dm, Gc * L, (float)ldexp(1.0, ey), YT, ldg, half_y ? XgTh : XgT, ldg, Hin_v, dm, TBOA_F32, 1, TBOA_GEMM_LOWER | tiled | hy);
             h.batch = Hkv; h.strideA = (long long)dm * ldg; h.strideB = 0; h.strideC = dd; h.tag = TBOA_PROF_HV_SYRK;
             h.flags &= ~TBOA_GEMM_PERSISTENT;
-            TB_TRY(gemm_bf16_nt(ctx, h));
-            h.A = YTl; if (half_y) h.alpha = (float)ldexp(1.0, ey - 11);
+            // both parts in one pass over the accumulators, the low one first and scaled back when the high one begins: one read and write of
+            // the result instead of two
+            h.nterms = 2; h.K = 2 * Gc * L; h.last_scale = half_y ? 1.f / 2048.f : 1.f;
+            h.A = YTl; h.termA[0] = YTl; h.termA[1] = YT; h.termB[0] = h.termB[1] = h.B;
             TB_TRY(gemm_bf16_nt(ctx, h));
             if (rv) {
                 h.tag = TBOA_PROF_RV; h.C = R_v; h.flags = tiled | hy; h.alpha = (float)ldexp(d->alpha, ez);
-                h.A = dYT; TB_TRY(gemm_bf16_nt(ctx, h));
-                h.A = dYTl; if (half_y) h.alpha = (float)ldexp(d->alpha, ez - 11);
+                h.A = dYTl; h.termA[0] = dYTl; h.termA[1] = dYT;
                 TB_TRY(gemm_bf16_nt(ctx, h));
             }
             continue;
@@ -1167,17 +1189,17 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             // P = [A | A - A~];  Y^T = X_s^T A^T;  (Y - Y~)^T = [dX_s^T | X~_s^T] [A | A - A~]^T  since  A X - A~ X~ = A dX + (A - A~) X~
             if (rv) TB_TRY(scores_pair(D, Qh, Kh, Qhf, Khf, sl, Sc, Scf));
             else TB_TRY(scores(D, Qh, Kh, sl, Sc));
-            TB_TRY(softmax(D, Sc, rv ? Scf : nullptr, P, ldp, -1, -1, L, bin));
+            TB_TRY(softmax(D, Sc, rv ? Scf : nullptr, P, Lp, ldp, -1, -1, Lp, bin));
             // Y^T and (Y - Y~)^T are read only by the two products below: with whole 256 x 256 tiles they are written in the
             // blocked layout of the GEMM (column offset c -> pointer offset 16 c), whose blocks those products load whole
             const long long cs = blocked ? 16 : 1;
-            GemmBf16 y = nt(dm, L, L, 1.f, XcT + is * sl * nsx * L, ldx, P, ldp, YT + cs * sl * L, ldy, TBOA_BF16, 0,
+            GemmBf16 y = nt(dm, Lp, Lp, 1.f, XcT + is * sl * nsx * Lp, ldx, P, ldp, YT + cs * sl * Lp, ldy, TBOA_BF16, 0,
                             cflag | hf | (blocked ? TBOA_GEMM_C_TILED : 0) | (bin ? TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED : 0));
             y.batch = Hq; y.batch_inner = rep; y.tag = TBOA_PROF_AX;
-            y.strideB = (long long)rep * L * ldp; y.strideB2 = (long long)L * ldp;
-            y.strideC = (long long)dm * ldy; y.strideC2 = cs * Gc * L;
+            y.strideB = (long long)rep * Lp * ldp; y.strideB2 = (long long)Lp * ldp;
+            y.strideC = (long long)dm * ldy; y.strideC2 = cs * Gc * Lp;
             TB_TRY(gemm_bf16_nt(ctx, y));
-            if (rv) { y.A = XcT + is * ((long long)sl * nsx + 1) * L; y.K = 2 * L; y.kseg = L; y.C = dYT + cs * sl * L; TB_TRY(gemm_bf16_nt(ctx, y)); }
+            if (rv) { y.A = XcT + is * ((long long)sl * nsx + 1) * Lp; y.K = 2 * Lp; y.kseg = Lp; y.C = dYT + cs * sl * Lp; TB_TRY(gemm_bf16_nt(ctx, y)); }
         }
         const int oflag = (blocked ? (TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED) : 0) | hf;
         GemmBf16 h = nt(dm, dm, (int)ky, 1.f, YT, ldy, YT, ldy, Hin_v, dm, TBOA_F32, 1, TBOA_GEMM_LOWER | oflag);
@@ -1271,7 +1293,8 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
     // segments of V^T ((hi, hi, lo) per path) and of P (the same, or (hi, lo) per path from the fused kernel: its products name
     // their three operand pairs instead of reading a repeated segment)
     const int nsg = fp ? 6 : 3, nsp = fused ? (fp ? 4 : 2) : (fp ? 6 : 3), splits = pick_splits(D.S);
-    const long long TP = (long long)T + PADE, ldp = (long long)nsp * L + PADE;
+    const int Lp = padded_len(L);       // (the fused kernel takes whole 256-tiles: Lp = L there)
+    const long long Tp = padded_tokens(T, splits), TP = Tp + PADE, ldp = (long long)nsp * Lp + PADE;
     bf16 *Wqh, *Wql, *Wkh, *Wkl, *Wvh, *Wvl, *Wq3, *Wk3, *Wv3, *Qh, *Kh, *Qhf, *Khf, *P, *VTc, *OT, *OTl, *dOT, *dOTl;
     float *Qf, *Kf, *VT32, *VT32f, *Sc, *Scf, *part, *steps;
     int* amx;      // [q | k | q~ | k~] x G (see QkScale)
@@ -1285,8 +1308,8 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
         VT32f = fp ? ar.get<float>((size_t)dkv * G * L) : nullptr; Scf = (fp && !fused) ? ar.get<float>((size_t)Hq * L * L) : nullptr;
         Qh = ar.get<bf16>((size_t)G * L * dq * 3); Kh = ar.get<bf16>((size_t)G * L * dkv * 3);
         Qhf = fp ? ar.get<bf16>((size_t)G * L * dq * 3) : nullptr; Khf = fp ? ar.get<bf16>((size_t)G * L * dkv * 3) : nullptr;
-        Sc = fused ? nullptr : ar.get<float>((size_t)Hq * L * L); P = ar.get<bf16>((size_t)Hq * L * ldp);
-        VTc = ar.get<bf16>((size_t)dkv * (G * nsg * L + PADE));
+        Sc = fused ? nullptr : ar.get<float>((size_t)Hq * L * L); P = ar.get<bf16>((size_t)Hq * Lp * ldp);
+        VTc = ar.get<bf16>((size_t)dkv * (G * nsg * Lp + PADE));
         OT = ar.get<bf16>((size_t)dq * TP); OTl = ar.get<bf16>((size_t)dq * TP);
         dOT = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr; dOTl = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr;
         part = ar.get<float>((size_t)splits * dq * dq);
@@ -1309,9 +1332,11 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
     TB_TRY(fits_half(ctx, X, fp ? X_fp : nullptr, (long long)T * dm, &D.f16));
     const int hf = D.f16 ? TBOA_GEMM_F16 : 0;
     const int cflag = (d->causal ? TBOA_GEMM_CAUSAL_K : 0) | hf;
+    if (Tp != T)
+        for (bf16* p : {OT, OTl, dOT, dOTl}) if (p) TB_TRY(clear16(ctx, p, dq * TP));
     for (int s0 = 0; s0 < D.S; s0 += G) {
         const int Gc = (D.S - s0 < G) ? D.S - s0 : G;
-        const long long t0 = (long long)s0 * L, ldv = (long long)Gc * nsg * L + PADE;
+        const long long t0 = (long long)s0 * L, ldv = (long long)Gc * nsg * Lp + PADE;
         const bf16* Xc = X + t0 * dm;
         // V'^T = Wv_deq Xc^T (fp32; the row steps of the integer form are applied by vt_segments_kernel) and the
         // full-precision V~^T = Wv X~c^T
@@ -1332,7 +1357,8 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
             } else TB_TRY(project_qk(D, X_fp + t0 * dm, Gc * L, Wq, nullptr, Wk, nullptr, Qf, Kf, Qhf, Khf, nullptr, nullptr,
                                      fused ? amx + 2 * G : nullptr, fused ? amx + 3 * G : nullptr));
         }
-        hipLaunchKernelGGL(vt_segments_kernel, dim3(g1((long long)dkv * Gc * L)), dim3(256), 0, st, VT32, sv, fp ? VT32f : nullptr, VTc, dkv, Gc, L,
+        if (Lp != L) TB_TRY(clear16(ctx, VTc, dkv * ldv));
+        hipLaunchKernelGGL(vt_segments_kernel, dim3(g1((long long)dkv * Gc * L)), dim3(256), 0, st, VT32, sv, fp ? VT32f : nullptr, VTc, dkv, Gc, L, Lp,
                            nsg, ldv, D.f16);
         TB_KERNEL_CHECK(ctx);
         for (int sl = 0; sl < Gc; ++sl) {
@@ -1347,17 +1373,17 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
             } else {
                 if (fp) TB_TRY(scores_pair(D, Qh, Kh, Qhf, Khf, sl, Sc, Scf));
                 else TB_TRY(scores(D, Qh, Kh, sl, Sc));
-                TB_TRY(softmax(D, Sc, fp ? Scf : nullptr, P, ldp, 2 * L, L, 3 * L, 0, 1));
+                TB_TRY(softmax(D, Sc, fp ? Scf : nullptr, P, Lp, ldp, 2 * Lp, Lp, 3 * Lp, 0, 1));
             }
             const long long co = t0 + (long long)sl * L;
             const float pa = (fused && D.f16) ? 1.f / ATTN_PROBS_HALF_SCALE : 1.f;       // half probabilities from the fused kernel are scaled
             // (an attention output is a convex combination of values: it fits half where they do, and then leaves as a pair of halves)
-            GemmBf16 o = nt(dh, L, 3 * L, pa, VTc + (long long)sl * nsg * L, ldv, P, ldp, OT + co, TP, TBOA_BF16, 0,
+            GemmBf16 o = nt(dh, L, 3 * Lp, pa, VTc + (long long)sl * nsg * Lp, ldv, P, ldp, OT + co, TP, TBOA_BF16, 0,
                             cflag | TBOA_GEMM_C_HILO | (D.f16 ? TBOA_GEMM_C_HILO_HALF : 0));
             o.C2 = OTl + co;
-            o.kseg = L; o.batch = Hq; o.batch_inner = rep; o.tag = TBOA_PROF_PV;
+            o.kseg = Lp; o.batch = Hq; o.batch_inner = rep; o.tag = TBOA_PROF_PV;
             o.strideA = (long long)dh * ldv; o.strideA2 = 0;
-            o.strideB = (long long)rep * L * ldp; o.strideB2 = (long long)L * ldp;
+            o.strideB = (long long)rep * Lp * ldp; o.strideB2 = (long long)Lp * ldp;
             o.strideC = (long long)rep * dh * TP; o.strideC2 = (long long)dh * TP;
             if (fused) {       // (the fused kernel leaves P in 16 x 32 blocks: a column offset c is the pointer offset 16 c)
                 o.flags |= TBOA_GEMM_B_TILED;
@@ -1367,7 +1393,7 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
             }
             TB_TRY(gemm_bf16_nt(ctx, o));
             if (fp) {       // O~^T for now
-                o.A = VTc + ((long long)sl * nsg + 3) * L; o.B = P + (fused ? 16LL * 2 : 3) * L; o.C = dOT + co; o.C2 = dOTl + co;
+                o.A = VTc + ((long long)sl * nsg + 3) * Lp; o.B = P + (fused ? 16LL * 2 : 3) * Lp; o.C = dOT + co; o.C2 = dOTl + co;
                 if (fused) {
                     o.termA[0] = o.A; o.termA[1] = o.A; o.termA[2] = o.A + 2 * L;
                     o.termB[0] = o.B; o.termB[1] = o.B + 16LL * L; o.termB[2] = o.B;
@@ -1386,11 +1412,11 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
         if (!Hin_o) return 0;
     }
     // H_in^O = (O_hi + O_lo)^T (O_hi + O_lo), R_o = alpha (dO_hi + dO_lo)^T (O_hi + O_lo), without the lo.lo terms (half or bf16 pairs)
-    const GramPair ho[3] = {{OT, OT}, {OTl, OT}, {OT, OTl}};
-    TB_TRY(gram_splitk(ctx, splits, dq, 3, ho, TP, T, 1.0, 1, part, Hin_o, D.f16));
+    const GramPair ho[3] = {{OTl, OT}, {OT, OTl}, {OT, OT}};
+    TB_TRY(gram_splitk(ctx, splits, dq, 3, ho, TP, (int)Tp, 1.0, 1, part, Hin_o, D.f16));
     if (fp) {
-        const GramPair ro[3] = {{dOT, OT}, {dOTl, OT}, {dOT, OTl}};
-        TB_TRY(gram_splitk(ctx, splits, dq, 3, ro, TP, T, d->alpha, 0, part, R_o, D.f16));
+        const GramPair ro[3] = {{dOTl, OT}, {dOT, OTl}, {dOT, OT}};
+        TB_TRY(gram_splitk(ctx, splits, dq, 3, ro, TP, (int)Tp, d->alpha, 0, part, R_o, D.f16));
     }
     return 0;
 }
@@ -1410,10 +1436,12 @@ __global__ void swiglu_kernel(const float* __restrict__ G, const float* __restri
 // layer-wise Hessian of a plain linear layer from bf16 activations: H = X^T X, R = alpha (X - X~)^T X
 int build_hessian_linear_bf16(tboa_ctx* ctx, long long T, int n, double alpha, const bf16* X, const bf16* X_fp, float* H_in, float* R) {
     if (T % 8 || n % 8) return tboa_fail(ctx, TBOA_EINVAL, "build_hessian_linear: n_tokens and d_in must be multiples of 8 for bf16 inputs");
+    // partial sums over the tokens, added in fp64: 16 where the tokens allow it.  (At d_in = 11008 and 8192 tokens they are 7.8 GB; 4 instead of 16
+    // take 5.6 instead of 8.9 ms, but their fp32 sums are four times as long: R is then off by 1.9e-7 instead of 8.7e-8.)
     int splits = 1;
     for (int sp = 16; sp > 1; --sp) if (T % ((long long)sp * 256) == 0) { splits = sp; break; }
     const bool fp = X_fp && R;
-    const long long TP = T + PADE;
+    const long long Tp = padded_tokens(T, splits), TP = Tp + PADE;
     bf16 *XT, *dXh, *dXl; float* part;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
@@ -1423,9 +1451,11 @@ int build_hessian_linear_bf16(tboa_ctx* ctx, long long T, int n, double alpha, c
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }
     Dims D{}; D.ctx = ctx;
+    if (Tp != T)
+        for (bf16* p : {XT, dXh, dXl}) if (p) TB_TRY(clear16(ctx, p, n * TP));
     TB_TRY(transpose(D, X, fp ? X_fp : nullptr, n, (int)T, n, XT, fp ? dXh : nullptr, dXl, TP));
-    TB_TRY(gram_splitk(ctx, splits, n, XT, nullptr, XT, TP, (int)T, 1.0, 1, part, H_in));
-    if (fp) TB_TRY(gram_splitk(ctx, splits, n, dXh, dXl, XT, TP, (int)T, alpha, 0, part, R));
+    TB_TRY(gram_splitk(ctx, splits, n, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, H_in));
+    if (fp) TB_TRY(gram_splitk(ctx, splits, n, dXh, dXl, XT, TP, (int)Tp, alpha, 0, part, R));
     return 0;
 }
 

@@ -120,13 +120,16 @@ struct GemmBf16 {
     int batch_inner = 1; int64_t strideA2 = 0, strideB2 = 0, strideC2 = 0;
     int tag = -1;   // tboa_prof_tag of this launch (timed with HIP events when profiling is on)
     int kseg = 0;   // > 0: K is a concatenation of K/kseg segments; TBOA_GEMM_CAUSAL_K then limits each segment
-    // nterms > 1 (persistent kernel only): the contraction runs over nterms operand pairs, K / nterms columns each, the
-    // t-th pair read from termA[t], termB[t] (laid out and strided as A and B; A = termA[0], B = termB[0]):
-    // C = sum_t termA[t] termB[t]^T in one pass over the accumulators
+    // nterms > 1: the contraction runs over nterms operand pairs, K / nterms columns each, the t-th pair read from termA[t], termB[t]
+    // (laid out and strided as A and B; A = termA[0], B = termB[0]): C = sum_t termA[t] termB[t]^T in one pass over the accumulators
+    // (LDS-direct kernels; kseg only with the persistent one).
     int nterms = 1; const __hip_bfloat16* termA[4] = {}; const __hip_bfloat16* termB[4] = {};
-    // segs (device, one int >= 1 per batch entry; dispatched LDS-direct kernel): C = A (B_0 + B_1 + .. + B_(segs - 1))^T with B_t at
-    // B + t rep_strideB; K is the length of ONE segment and the flops counted are those of one
-    const int* segs = nullptr; int64_t rep_strideB = 0;
+    // dispatched kernel: the sum of the terms before the last is multiplied by this power of two when the last term begins (low parts stored with a
+    // factor of their own go first)
+    float last_scale = 1.f;
+    // dispatched kernel: device array, one int per batch entry: only its first min(segs, nterms) terms are taken; K is then the length of
+    // ONE term and the flops counted are those of one
+    const int* segs = nullptr;
 };
 // internal flag: a 16-bit result leaves as an exact-to-16-bit pair of bf16 values (hi into C, lo into C2), whatever the operands
 #define TBOA_GEMM_C_HILO 0x10000

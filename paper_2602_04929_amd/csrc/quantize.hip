@@ -888,11 +888,11 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             a.A = (const __hip_bfloat16*)Acat; a.B = (const __hip_bfloat16*)L.Hcat + (ph ? (long long)u0 * np * a.ldb : 0);
             a.batch = mats; a.strideA = m.mat_rows * a.lda; a.strideB = (long long)np * a.ldb; a.strideC = m.mat_rows * np;
             a.c_dtype = TBOA_F32; a.accumulate = 0; a.tag = TBOA_PROF_GRID;
-            a.segs = gs.terms; a.rep_strideB = (long long)L.nhin * np * a.ldb;
+            a.segs = gs.terms; a.nterms = 2; a.termA[0] = a.termA[1] = a.A; a.termB[0] = a.B; a.termB[1] = a.B + (long long)L.nhin * np * a.ldb;
             a.flags = TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED | TBOA_GEMM_CAUSAL_K;     // T' is lower triangular
             TB_TRY(gemm_bf16_nt(ctx, a));
             if (delta) {      // the low parts of delta against the first term of T'
-                a.A += lo_off; a.segs = nullptr; a.rep_strideB = 0; a.accumulate = 1;
+                a.A += lo_off; a.segs = nullptr; a.nterms = 1; a.accumulate = 1;
                 TB_TRY(gemm_bf16_nt(ctx, a));
             }
             const long long crow = (long long)rows * ncand;
