@@ -34,6 +34,7 @@ struct Args {
     int klo_m, klo_n, khi_m, khi_n, skip_lower, skip_upper, skip_col0, diag_order;
     const int* m_limit;
     const double* A2; const double* B2;
+    int sym;
     double* part; int splits;     // splits > 1 or part given: part[(blockIdx.z)][M, N] receives the raw sum of this split
 };
 
@@ -141,8 +142,11 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
         const int lo = klo + sp * per * BK;
         khi = min(khi, lo + per * BK); klo = lo;
     }
-    const int nk1 = khi > klo ? (khi - klo + BK - 1) / BK : 0;      // k-steps of one pair of operands
-    const int nk = A2 ? 2 * nk1 : nk1;
+    // a second run of k-steps: the other pair of operands over the same range, or (sym) the diagonal tile after what lies below it
+    int klo2 = klo, khi2 = khi;
+    if (g.sym) { klo2 = n0; khi2 = min(khi, n0 + TN); klo = min(khi, n0 + TN); A2 = A; B2 = B; }
+    const int nk1 = khi > klo ? (khi - klo + BK - 1) / BK : 0;
+    const int nk = A2 ? nk1 + (khi2 > klo2 ? (khi2 - klo2 + BK - 1) / BK : 0) : nk1;
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave / WN) * (TM / WM), wn = (wave % WN) * (TN / WN);
@@ -171,12 +175,18 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
         }
     };
     auto stage = [&](int buf, int kvalid = BK) { store_tile<AKC, TM, BK>(As[buf], ra, kvalid); store_tile<BKC, TN, BK>(Bs[buf], rb, kvalid); };
-    const int tail = khi > klo ? (khi - klo) % BK : 0, nfull = tail ? nk - 1 : nk;
-    if (vecA && vecB && m0 + TM <= g.M && n0 + TN <= g.N && nfull > 0 && !(tail && A2)) {
+    auto twice = [&]() {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] *= 2.0;
+    };
+    const int tail = khi > klo ? (khi - klo) % BK : 0, tail2 = A2 && khi2 > klo2 ? (khi2 - klo2) % BK : 0, nfull = tail ? nk - 1 : nk;
+    if (vecA && vecB && m0 + TM <= g.M && n0 + TN <= g.N && nfull > 0 && !(A2 && (tail || tail2))) {
         // every whole k-step of this workgroup lies inside the operands: 16-byte loads, one address per load.  (With the edge
         // loads in the same loop the compiler waits for each of them before the next: 58.6 instead of 66.3 TFLOP/s on 8192^3.)
-        const double* pa = tile_origin<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo);
-        const double* pb = tile_origin<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo);
+        const double* pa = nk1 ? tile_origin<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo) : tile_origin<AKC, TM, BK>(A2, g.sa_r, g.sa_k, m0, klo2);
+        const double* pb = nk1 ? tile_origin<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo) : tile_origin<BKC, TN, BK>(B2, g.sb_r, g.sb_k, n0, klo2);
         const long long da = AKC ? BK : BK * g.sa_k, db = BKC ? BK : BK * g.sb_k;
         load_tile_inside<AKC, TM, BK>(pa, g.sa_r, g.sa_k, ra);
         load_tile_inside<BKC, TN, BK>(pb, g.sb_r, g.sb_k, rb);
@@ -185,11 +195,12 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
         for (int kt = 0; kt < nfull - 1; ++kt) {
             pa += da; pb += db;
             if (kt + 1 == nk1) {
-                pa = tile_origin<AKC, TM, BK>(A2, g.sa_r, g.sa_k, m0, klo);
-                pb = tile_origin<BKC, TN, BK>(B2, g.sb_r, g.sb_k, n0, klo);
+                pa = tile_origin<AKC, TM, BK>(A2, g.sa_r, g.sa_k, m0, klo2);
+                pb = tile_origin<BKC, TN, BK>(B2, g.sb_r, g.sb_k, n0, klo2);
             }
             load_tile_inside<AKC, TM, BK>(pa, g.sa_r, g.sa_k, ra);
             load_tile_inside<BKC, TN, BK>(pb, g.sb_r, g.sb_k, rb);
+            if (g.sym && kt == nk1) twice();
             multiply(kt & 1);
             stage((kt & 1) ^ 1);
             __syncthreads();
@@ -198,6 +209,7 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
             load_tile<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo + nfull * BK, g.M, khi, ra);
             load_tile<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo + nfull * BK, g.N, khi, rb);
         }
+        if (g.sym && nfull - 1 == nk1) twice();
         multiply((nfull - 1) & 1);
         if (tail) {
             stage(nfull & 1, tail);
@@ -205,20 +217,25 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
             multiply(nfull & 1);
         }
     } else if (nk > 0) {
-        load_tile<AKC, TM, BK>(A, g.sa_r, g.sa_k, m0, klo, g.M, khi, ra);
-        load_tile<BKC, TN, BK>(B, g.sb_r, g.sb_k, n0, klo, g.N, khi, rb);
-        stage(0, min(BK, khi - klo));
+        int lim = khi;
+        auto fetch = [&](int kt) {
+            const bool second = kt >= nk1;
+            const int k0 = second ? klo2 + (kt - nk1) * BK : klo + kt * BK;
+            lim = second ? khi2 : khi;
+            load_tile<AKC, TM, BK>(second ? A2 : A, g.sa_r, g.sa_k, m0, k0, g.M, lim, ra);
+            load_tile<BKC, TN, BK>(second ? B2 : B, g.sb_r, g.sb_k, n0, k0, g.N, lim, rb);
+            lim -= k0;
+        };
+        fetch(0);
+        stage(0, min(BK, lim));
         __syncthreads();
-        for (int kt = 0; kt < nk - 1; ++kt) {
-            const bool second = kt + 1 >= nk1;
-            const int k0 = klo + (kt + 1 - (second ? nk1 : 0)) * BK;
-            load_tile<AKC, TM, BK>(second ? A2 : A, g.sa_r, g.sa_k, m0, k0, g.M, khi, ra);
-            load_tile<BKC, TN, BK>(second ? B2 : B, g.sb_r, g.sb_k, n0, k0, g.N, khi, rb);
+        for (int kt = 0; kt < nk; ++kt) {
+            if (kt + 1 < nk) fetch(kt + 1);
+            if (g.sym && kt == nk1) twice();
             multiply(kt & 1);
-            stage((kt & 1) ^ 1, min(BK, khi - k0));
+            if (kt + 1 < nk) stage((kt & 1) ^ 1, min(BK, lim));
             __syncthreads();
         }
-        multiply((nk - 1) & 1);
     }
 
     // accumulator element v of tile (i, j): row 16 i + lane / 16 + 4 v, column 16 j + lane % 16
@@ -269,9 +286,9 @@ constexpr double STEP_US[4] = {2.1, 0.78, 0.32, 0.8};
 // Tile shape and number of splits of least modelled time: rounds of 256 workgroups, each of the contraction's steps, plus the
 // second kernel and the traffic of the parts when there is a split.
 Choice choose(const GemmF64& q, bool akc, size_t part_elems, int sum) {
-    const double k16 = std::max(1.0, q.K / 16.0 * (q.A2 ? 2.0 : 1.0));
+    const double k16 = std::max(1.0, q.K / 16.0 * (q.A2 ? 2.0 : q.sym ? 0.5 : 1.0));
     const bool in_place = q.C == q.A || q.C == q.B;               // needs whole rows per workgroup: one column of tiles, no other order
-    const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.A2 || in_place;
+    const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.sym || in_place;
     Choice best{S128, 1}; double best_us = 1e30;
     for (int s = 0; s < 4; ++s) {
         if (s == SKINNY && !(q.M <= 32 && akc)) continue;
@@ -316,7 +333,10 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
     a.klo_m = q.klo_m; a.klo_n = q.klo_n; a.khi_m = q.khi_m; a.khi_n = q.khi_n;
     a.A2 = q.A2; a.B2 = q.A2 ? q.B2 : nullptr;
     if (q.A2 && (!q.B2 || q.klo_m || q.klo_n || q.khi_m || q.khi_n)) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: a second operand pair needs both operands and an unrestricted contraction");
-    a.skip_lower = q.skip_lower; a.skip_upper = q.skip_upper; a.skip_col0 = q.skip_col0; a.m_limit = q.m_limit; a.diag_order = q.diag_order;
+    if (q.sym && (q.N != q.K || q.A2 || q.klo_m || q.klo_n || q.khi_m || q.khi_n || q.skip_lower || q.skip_upper || q.sum_inner))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: a symmetric right operand is square and goes with no other restriction");
+    a.sym = q.sym;
+    a.skip_lower = q.skip_lower; a.skip_upper = q.skip_upper; a.skip_col0 = q.skip_col0; a.m_limit = q.m_limit; a.diag_order = q.diag_order || q.sym;
     // sum_inner: the inner batch entries are terms of one result
     const int sum = q.sum_inner ? a.batch_inner : 1;
     if (q.sum_inner && (q.batch % a.batch_inner || q.skip_lower || q.skip_upper || q.m_limit)) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: summed batch entries need whole groups and whole results");
@@ -347,7 +367,7 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
                     if (q.skip_upper && m0 + tm <= q.skip_col0 + n0) continue;
                     int klo = 0, khi = q.K;
                     if (q.klo_m) klo = std::max(klo, m0);
-                    if (q.klo_n) klo = std::max(klo, n0);
+                    if (q.klo_n || q.sym) klo = std::max(klo, n0);
                     if (q.khi_m) khi = std::min(khi, m0 + tm);
                     if (q.khi_n) khi = std::min(khi, n0 + tn);
                     if (khi > klo) macs += (double)std::min(tm, q.M - m0) * std::min(tn, q.N - n0) * (khi - klo) * (q.A2 ? 2.0 : 1.0);

@@ -98,6 +98,10 @@ struct GemmF64 {
     // optional second pair of operands with the shapes, strides and batch strides of the first:
     // C = alpha (A B + A2 B2) + beta C in one pass (not combined with the contraction-range restrictions)
     const double* A2 = nullptr; const double* B2 = nullptr;
+    // B symmetric (K == N): C = A T with T = twice the part of B below the diagonal tiles, the diagonal tiles once and nothing above
+    // (T + T^T = 2 B): half the work where C only goes into symmetric forms, A B A'^T = (C A'^T + A C'^T) / 2 with C' = A' T.  The tile
+    // width is the launch's own: two launches of the same shape (M, N, batch) have the same T.
+    int sym = 0;
     int sum_inner = 0;   // C[outer] = alpha * sum over the batch_inner entries of A B + beta * C[outer] (strideC2 unused)
     int tag = -1;   // tboa_prof_tag of this launch (timed with HIP events when profiling is on)
 };

@@ -53,11 +53,11 @@ __device__ __forceinline__ double quant_code_fast(double w, double s, double si,
 }
 
 // ------------------------------------------------------------------------------------------------ rows
-__global__ void gather_rows_kernel(const double* __restrict__ src, double* __restrict__ dst, BlockMap m, int n) {
+__global__ void gather_rows_kernel(const double* __restrict__ src, double* __restrict__ dst, double* __restrict__ work, BlockMap m, int n) {
     const int R = blockIdx.y;
     const double* s = src + layer_row(m, R) * n;
-    double* d = dst + (long long)R * n;
-    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) d[c] = s[c];
+    const long long o = (long long)R * n;
+    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) { const double v = s[c]; dst[o + c] = v; work[o + c] = v; }
 }
 
 // ------------------------------------------------------------------------------------------------ grid search
@@ -113,15 +113,28 @@ __global__ __launch_bounds__(256) void rowdot_kernel(const double* __restrict__ 
     if (lane == 0) out[row] = s;
 }
 
-// lowest k among the minima of cost[row, :] -> (s, z) of that candidate
-__global__ void grid_argmin_kernel(const double* __restrict__ cost, const double* __restrict__ cand_s,
+// lowest (value, index) over the wavefront; an index of INT_MAX loses to every other one
+__device__ __forceinline__ void wave_argmin(double& v, int& k) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double v2 = __shfl_xor(v, o, 64); const int k2 = __shfl_xor(k, o, 64);
+        if (k2 != 0x7fffffff && (k == 0x7fffffff || v2 < v || (v2 == v && k2 < k))) { v = v2; k = k2; }
+    }
+}
+
+// lowest k among the minima of cost[row, :] -> (s, z) of that candidate; one wavefront per row (one thread per row took 16 us for
+// 80 dependent loads).  A NaN at k = 0 stays the minimum, as it does in a loop over k that replaces what is larger.
+__global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restrict__ cost, const double* __restrict__ cand_s,
                                    const double* __restrict__ cand_z, int rows, int ncand, BlockMap m, int r_off,
                                    double* __restrict__ s_out, double* __restrict__ z_out, int ng, int gi) {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const double* c = cost + (long long)row * ncand;
-    int best = 0; double bc = c[0];
-    for (int k = 1; k < ncand; ++k) if (c[k] < bc) { bc = c[k]; best = k; }
+    double bc = 0.0; int best = 0x7fffffff;
+    for (int k = lane; k < ncand; k += 64) { const double v = c[k]; if (v == v && (best == 0x7fffffff || v < bc)) { bc = v; best = k; } }
+    wave_argmin(bc, best);
+    if (lane != 0) return;
+    if (best == 0x7fffffff || !(c[0] == c[0])) best = 0;
     const long long lr = layer_row(m, r_off + row);
     s_out[lr * ng + gi] = cand_s[(long long)row * ncand + best];
     z_out[lr * ng + gi] = cand_z[(long long)row * ncand + best];
@@ -379,22 +392,30 @@ __global__ __launch_bounds__(256) void grid_cost_kernel(const float* __restrict_
 // term (see grid_terms_kernel).
 enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_ONE_TERM = 3, GS_WORDS = 4 };
 
-// per row: the limit below which a candidate's approximate cost makes it a survivor, and the number of survivors that the
-// exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
+// per row (one wavefront): the candidates whose approximate cost makes them survivors (in increasing k, list[row][0 ..]), and the number that
+// the exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
 // exact cost is what the deviation guard of the pass measures.
-__global__ void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, double* __restrict__ lim_out,
+__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, int* __restrict__ list,
                                   int* __restrict__ cnt_out, int* __restrict__ gstat) {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
-    const double* c = cost + (long long)row * ncand;
-    double m = c[0];
-    bool bad = !(c[0] == c[0]);
-    for (int k = 1; k < ncand; ++k) { m = fmin(m, c[k]); bad |= !(c[k] == c[k]); }
+    const double* c = cost + (long long)row * ncand; int* out = list + (long long)row * ncand;
+    double m = INFINITY; int bad = 0;
+    for (int k = lane; k < ncand; k += 64) { const double v = c[k]; m = fmin(m, v); bad |= !(v == v); }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { m = fmin(m, __shfl_xor(m, o, 64)); bad |= __shfl_xor(bad, o, 64); }
     const double lim = m + tau * fabs(m);
     int cnt = 0;
-    for (int k = 0; k < ncand; ++k) cnt += (c[k] <= lim) ? 1 : 0;
-    if (bad || !(m == m) || cnt == 0) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
-    lim_out[row] = lim;
+    for (int k0 = 0; k0 < ncand; k0 += 64) {
+        const int k = k0 + lane;
+        const bool in = k < ncand && c[k] <= lim;
+        const unsigned long long mask = __ballot(in);
+        if (in) out[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = k;
+        cnt += __popcll(mask);
+    }
+    if (lane != 0) return;
+    if (cnt == 0) out[0] = 0;
+    if (bad || cnt == 0) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
     const int ev = (cnt > 1 || row % 8 == 0) ? cnt : 0;
     cnt_out[row] = ev;
     if (ev) atomicAdd(gstat + GS_SURVIVORS, ev);
@@ -427,22 +448,19 @@ __global__ __launch_bounds__(256) void grid_scan_kernel(const int* __restrict__ 
 // the row (increasing k); slots at or beyond cap do not exist
 __global__ __launch_bounds__(256) void grid_delta_sel_kernel(const double* __restrict__ Wk, long long ldw, int n, int ncand, double maxq,
                                                              const double* __restrict__ cand_s, const double* __restrict__ cand_z,
-                                                             const double* __restrict__ cost, const double* __restrict__ lim,
-                                                             const int* __restrict__ cnt, const int* __restrict__ off,
+                                                             const int* __restrict__ list, const int* __restrict__ cnt, const int* __restrict__ off,
                                                              int per, int cap, double* __restrict__ DeltaS) {
     const int row = blockIdx.y;
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n || cnt[row] == 0) return;
+    const int nc = cnt[row];
+    if (c >= n || nc == 0) return;
     const double w = Wk[(long long)row * ldw + c];
-    const double l = lim[row];
-    const double* cr = cost + (long long)row * ncand;
+    const int* l = list + (long long)row * ncand;
     double* out = DeltaS + ((long long)(row / per) * cap) * n + c;
-    int slot = off[row];
-    for (int k = 0; k < ncand && slot < cap; ++k) {
-        if (!(cr[k] <= l)) continue;
-        const double s = cand_s[(long long)row * ncand + k], z = cand_z[(long long)row * ncand + k];
-        out[(long long)slot * n] = s * (quant_code(w, s, z, maxq) - z) - w;
-        ++slot;
+    const int slot0 = off[row];
+    for (int j = 0; j < nc && slot0 + j < cap; ++j) {
+        const double s = cand_s[(long long)row * ncand + l[j]], z = cand_z[(long long)row * ncand + l[j]];
+        out[(long long)(slot0 + j) * n] = s * (quant_code(w, s, z, maxq) - z) - w;
     }
 }
 
@@ -460,38 +478,32 @@ __global__ __launch_bounds__(256) void rowdot_limited_kernel(const double* __res
     if (lane == 0) out[row] = s;
 }
 
-// lowest exact cost among the survivors of a row (lowest k among equals: they are visited in increasing k); a row whose
-// survivors were not evaluated takes its first one (it has a single one, or the pass is void anyway).  Every exact
-// re-evaluation is compared with its approximation for the guard.
-__global__ void grid_argmin_sel_kernel(const double* __restrict__ costS, const double* __restrict__ cost, const double* __restrict__ lim,
+// lowest exact cost among the survivors of a row (lowest k among equals); a row whose survivors were not evaluated takes its
+// first one (it has a single one, or the pass is void anyway).  Every exact re-evaluation is compared with its approximation for
+// the guard.  One wavefront per row, one survivor per lane.
+__global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __restrict__ costS, const double* __restrict__ cost, const int* __restrict__ list,
                                        const int* __restrict__ cnt, const int* __restrict__ off, int per, int cap,
                                        const double* __restrict__ cand_s, const double* __restrict__ cand_z, int rows, int ncand,
                                        BlockMap m, int r_off, double* __restrict__ s_out, double* __restrict__ z_out, int ng, int gi,
                                        int* __restrict__ gstat) {
-    const int row = blockIdx.x * blockDim.x + threadIdx.x;
+    const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
-    const double* cr = cost + (long long)row * ncand;
-    const double l = lim[row];
-    const int nc = cnt[row];
-    int best = -1;
-    if (nc > 0) {
-        const double* ce = costS + (long long)(row / per) * cap;
-        int slot = off[row];
-        double bc = 0.0, dev = 0.0;
-        for (int k = 0; k < ncand && slot < cap; ++k) {
-            if (!(cr[k] <= l)) continue;
-            const double e = ce[slot];
-            if (best < 0 || e < bc) { bc = e; best = k; }
-            const double d = fabs(cr[k] - e) / fabs(e);
-            dev = (d == d) ? fmax(dev, d) : 1.0;
-            ++slot;
-        }
-        atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
+    const double* cr = cost + (long long)row * ncand; const int* l = list + (long long)row * ncand;
+    const double* ce = costS + (long long)(row / per) * cap;
+    const int nc = cnt[row], slot0 = off[row];
+    double bc = 0.0, dev = 0.0; int best = 0x7fffffff;
+    for (int j = lane; j < nc && slot0 + j < cap; j += 64) {
+        const int k = l[j];
+        const double e = ce[slot0 + j], d = fabs(cr[k] - e) / fabs(e);
+        if (best == 0x7fffffff || e < bc) { bc = e; best = k; }
+        dev = fmax(dev, (d == d) ? d : 1.0);
     }
-    if (best < 0) {
-        best = 0;
-        for (int k = 0; k < ncand; ++k) if (cr[k] <= l) { best = k; break; }
-    }
+    wave_argmin(bc, best);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) dev = fmax(dev, __shfl_xor(dev, o, 64));
+    if (lane != 0) return;
+    if (nc > 0) atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
+    if (best == 0x7fffffff) best = l[0];
     const long long lr = layer_row(m, r_off + row);
     s_out[lr * ng + gi] = cand_s[(long long)row * ncand + best];
     z_out[lr * ng + gi] = cand_z[(long long)row * ncand + best];
@@ -597,19 +609,25 @@ __global__ void comp_error_kernel(const double* __restrict__ Wb, const double* _
     }
 }
 
-// T[h, a, :] = Lo[a, B] Lo[B, B]^-1 for a = i1 .. dh-1, Lo = U_out[h]^T (lower): right-hand triangular solve,
-// one thread per remaining row, columns from the last to the first.
-__global__ void comp_T_kernel(const double* __restrict__ Uout, int dh, int i0, int i1, double* __restrict__ T, int TP) {
-    const int h = blockIdx.y;
-    const int a = i1 + blockIdx.x * blockDim.x + threadIdx.x;
+// T[h, a, :] = Lo[a, B] Lo[B, B]^-1 for a = i1 .. dh-1, Lo = U_out[h]^T (lower): right-hand triangular solve, columns from the last to
+// the first.  One wavefront per remaining row: lane k holds the right-hand side of the columns k, k + 64, .. in LDS, and a finished column
+// is taken out of all the earlier ones at once (one thread per row, summing over the later columns, took 125 us for 48 columns; 10 us).
+__global__ __launch_bounds__(256) void comp_T_kernel(const double* __restrict__ Uout, int dh, int i0, int i1, double* T, int TP, int lds) {
+    extern __shared__ double rhs[];      // [4][nb]; without lds (blocks of thousands of rows) the right-hand side stands in T itself
+    const int h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int a = i1 + blockIdx.x * 4 + wave, nb = i1 - i0;
     if (a >= dh) return;
-    const double* U = Uout + (long long)h * dh * dh;
+    const double* U = Uout + (long long)h * dh * dh + (long long)i0 * dh;      // row c: Lo[., i0 + c]
     double* t = T + ((long long)h * dh + a) * TP;
-    const int nb = i1 - i0;
+    double* x = lds ? rhs + (size_t)wave * nb : t;
+    auto settle = [&]() { if (lds) __builtin_amdgcn_wave_barrier(); else __threadfence_block(); };
+    for (int k = lane; k < nb; k += 64) x[k] = U[(long long)k * dh + a];
+    settle();
     for (int c = nb - 1; c >= 0; --c) {
-        double acc = U[(long long)(i0 + c) * dh + a];                 // Lo[a, i0+c]
-        for (int k = c + 1; k < nb; ++k) acc -= t[k] * U[(long long)(i0 + c) * dh + i0 + k];   // Lo[i0+k, i0+c]
-        t[c] = acc / U[(long long)(i0 + c) * dh + i0 + c];
+        const double tc = x[c] / U[(long long)c * dh + i0 + c];
+        for (int k = lane; k < c; k += 64) x[k] = __builtin_fma(-tc, U[(long long)k * dh + i0 + c], x[k]);      // Lo[i0 + c, i0 + k]
+        settle();
+        if (lane == 0) t[c] = tc;
     }
 }
 
@@ -623,7 +641,7 @@ __global__ void wbar_kernel(const uint8_t* __restrict__ codes, const double* __r
 }
 
 // Per head: s_j += sum_k (F[j,k] - s_k C[j,k]) Ho[k,j] / (C[j,j] Ho[j,j]) in order j = 0..dh-1,
-// F = Wbar (W (H_in - R))^T, C = Wbar H_in Wbar^T   (Prop. 3.3 with Q = diag(s) Wbar)
+// F = Wbar (W (H_in - R))^T, C = Wbar H_in Wbar^T = (Cm + Cm^T) / 2   (Prop. 3.3 with Q = diag(s) Wbar; Cm from the half product, GemmF64::sym)
 __global__ __launch_bounds__(256) void cd_head_kernel(const double* __restrict__ F, const double* __restrict__ Cm,
                                                       const double* __restrict__ Ho, int dh, int iters, double* __restrict__ s_all) {
     extern __shared__ double sh[];
@@ -637,7 +655,7 @@ __global__ __launch_bounds__(256) void cd_head_kernel(const double* __restrict__
     for (int it = 0; it < iters; ++it)
         for (int j = 0; j < dh; ++j) {
             double acc = 0.0;
-            for (int k = t; k < dh; k += 256) acc += (Fh[(long long)j * dh + k] - s[k] * Ch[(long long)j * dh + k]) * Hh[(long long)k * dh + j];
+            for (int k = t; k < dh; k += 256) acc += (Fh[(long long)j * dh + k] - s[k] * 0.5 * (Ch[(long long)j * dh + k] + Ch[(long long)k * dh + j])) * Hh[(long long)k * dh + j];
             acc = wave_sum(acc);
             if ((t & 63) == 0) red[t >> 6] = acc;
             __syncthreads();
@@ -788,27 +806,44 @@ __global__ void finalize_kernel(const double* __restrict__ Wbar, const double* _
         }
 }
 
-// (Q - W) H_in from products that the scale refinement already formed, for one scale per row (Q = diag(s) Wbar):
-// DH = diag(s) (Wbar H_in) - W H_in, with W H_in = Z + W R where Z = W (H_in - R).  Overwrites AH = Wbar H_in.
-__global__ void dh_from_products_kernel(double* __restrict__ AH, const double* __restrict__ s, const double* __restrict__ Z,
-                                        const double* __restrict__ WR, int n) {
+// identity H_out, one wavefront per row: C = Wbar H_in Wbar^T and F = Wbar (W (H_in - R))^T of the row alone, from the half products
+// A = Wbar T, Gw = W T (T + T^T = 2 H_in) and WR = W R (or NULL)
+__global__ __launch_bounds__(256) void cd_row_products_kernel(const double* __restrict__ A, const double* __restrict__ Wbar, const double* __restrict__ W,
+                                                              const double* __restrict__ Gw, const double* __restrict__ WR, long long rows, int n,
+                                                              double* __restrict__ Cd, double* __restrict__ Fd) {
+    const int lane = threadIdx.x & 63;
+    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rows) return;
+    const long long o = row * n;
+    double c = 0.0, f = 0.0;
+    for (int k = lane; k < n; k += 64) {
+        const double a = A[o + k], wb = Wbar[o + k];
+        c += a * wb;
+        f += 0.5 * (a * W[o + k] + wb * Gw[o + k]) - (WR ? wb * WR[o + k] : 0.0);
+    }
+    c = wave_sum(c); f = wave_sum(f);
+    if (lane == 0) { Cd[row] = c; Fd[row] = f; }
+}
+
+// (Q - W) T from products that the scale refinement already formed, for one scale per row (Q = diag(s) Wbar):
+// DH = diag(s) (Wbar T) - W T.  Overwrites AH = Wbar T.
+__global__ void dh_from_products_kernel(double* __restrict__ AH, const double* __restrict__ s, const double* __restrict__ Gw, int n) {
     const int r = blockIdx.y;
     const double sr = s[r];
     for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < n; c += gridDim.x * blockDim.x) {
         const long long i = (long long)r * n + c;
-        const double wh = WR ? Z[i] + WR[i] : Z[i];
-        AH[i] = sr * AH[i] - wh;
+        AH[i] = sr * AH[i] - Gw[i];
     }
 }
 
-// out[h] = scale * sum_{j,k} Ho[h][j,k] M[h][k,j]
+// out[h] = scale * sum_{j,k} Ho[h][j,k] M[h][k,j]; sym: of the symmetric part of M (a half product)
 __global__ __launch_bounds__(256) void head_trace_kernel(const double* __restrict__ Ho, const double* __restrict__ M, int dh,
-                                                         double scale, double* __restrict__ out) {
+                                                         double scale, int sym, double* __restrict__ out) {
     __shared__ double red[4];
     const int h = blockIdx.x, t = threadIdx.x;
     const double* Hh = Ho + (long long)h * dh * dh; const double* Mh = M + (long long)h * dh * dh;
     double acc = 0.0;
-    for (int i = t; i < dh * dh; i += 256) { const int j = i / dh, k = i % dh; acc += Hh[i] * Mh[(long long)k * dh + j]; }
+    for (int i = t; i < dh * dh; i += 256) { const int j = i / dh, k = i % dh; acc += Hh[i] * (sym ? 0.5 * (Mh[(long long)k * dh + j] + Mh[i]) : Mh[(long long)k * dh + j]); }
     acc = wave_sum(acc);
     if ((t & 63) == 0) red[t >> 6] = acc;
     __syncthreads();
@@ -837,8 +872,8 @@ struct Layer {
     double *W64, *Wt, *Hi, *Hfac, *Uin, *Rd, *P, *Ho, *Hofac, *Uout, *ftmp, *fdinv;
     double *Q64, *s64, *z64;
     double *Wb, *Wk, *Epan, *Wsnap, *E, *S1, *S2, *T;
-    double *cand_s, *cand_z, *Delta, *G, *cost, *DeltaS, *GS, *costS, *lim;
-    __half* Hcat; int* sel; int fast_grid, grid_terms;          // two-phase search: T' of every H_in, survivor bookkeeping
+    double *cand_s, *cand_z, *Delta, *G, *cost, *DeltaS, *GS, *costS;
+    __half* Hcat; int *sel, *list; int fast_grid, grid_terms;          // two-phase search: T' of every H_in, survivor bookkeeping
     GridScale gscale; float *cand_r, *Wf, *wdown;
     double *Wbar, *Abar, *Z, *WR, *Cm, *Fm, *dvec, *lossbuf;
     double *Cg, *Fg, *cdnum;    // group-wise refinement: Gram blocks per (group, group) pair
@@ -903,21 +938,21 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             const int per = ph ? rows_per_head : rows, ngrp = rows / per;    // rows that share one H_in
             const int cap = per * GRID_KS;                                    // exact re-evaluations a group has room for
             int* cntv = L.sel; int* offv = cntv + rows; int* totv = offv + rows;
-            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 255) / 256), dim3(256), 0, ctx->stream, L.cost, rows, ncand, GRID_TAU, L.lim, cntv, L.gstat);
+            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, GRID_TAU, L.list, cntv, L.gstat);
             hipLaunchKernelGGL(grid_scan_kernel, dim3(ngrp), dim3(256), 0, ctx->stream, cntv, per, cap, offv, totv, L.gstat);
             hipLaunchKernelGGL(grid_delta_sel_kernel, dim3((n + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
-                               L.cand_s, L.cand_z, L.cost, L.lim, cntv, offv, per, cap, L.DeltaS);
+                               L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
             TB_KERNEL_CHECK(ctx);
             GemmF64 g{};
             g.M = cap; g.N = n; g.K = n; g.alpha = 1.0; g.beta = 0.0; g.A = L.DeltaS; g.sam = n; g.sak = 1; g.sbk = n; g.sbn = 1;
             g.C = L.GS; g.ldc = n; g.batch = ngrp; g.strideA = (long long)g.M * n; g.strideC = g.strideA; g.m_limit = totv;
             g.B = L.Hi + (ph ? (long long)u0 * L.nn : 0); g.strideB = ph ? L.nn : 0;
-            g.tag = TBOA_PROF_F64_GRID;
+            g.tag = TBOA_PROF_F64_GRID; g.sym = 1;      // delta H delta^T: half of H is enough
             TB_TRY(gemm_f64(ctx, g));
             const long long srow = (long long)ngrp * cap;
             hipLaunchKernelGGL(rowdot_limited_kernel, dim3((unsigned)((srow + 3) / 4)), dim3(256), 0, ctx->stream, L.GS, L.DeltaS, n, cap,
                                srow, totv, L.costS);
-            hipLaunchKernelGGL(grid_argmin_sel_kernel, dim3((rows + 255) / 256), dim3(256), 0, ctx->stream, L.costS, L.cost, L.lim, cntv, offv, per, cap,
+            hipLaunchKernelGGL(grid_argmin_sel_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.costS, L.cost, L.list, cntv, offv, per, cap,
                                L.cand_s, L.cand_z, rows, ncand, map, r0, L.s64, L.z64, L.ng, gi, L.gstat);
             TB_KERNEL_CHECK(ctx);
             ++ctx->counters[TBOA_CTR_GRID_PASSES];
@@ -932,7 +967,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
         g.N = ncols; g.K = ncols; g.alpha = 1.0; g.beta = 0.0;
         g.A = L.Delta; g.sam = ncols; g.sak = 1;
         g.sbk = L.n; g.sbn = 1; g.C = L.G; g.ldc = ncols;
-        g.tag = TBOA_PROF_F64_GRID;
+        g.tag = TBOA_PROF_F64_GRID; g.sym = 1;
         if (ph) {
             g.M = rows_per_head * ncand; g.batch = nu;
             g.B = L.Hi + (long long)u0 * L.nn + (long long)c0 * L.n + c0;
@@ -945,7 +980,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
         const long long crow = (long long)rows * ncand;
         hipLaunchKernelGGL(rowdot_kernel, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, L.G, (long long)ncols, L.Delta,
                            (long long)ncols, crow, ncols, L.cost);
-        hipLaunchKernelGGL(grid_argmin_kernel, dim3((rows + 255) / 256), dim3(256), 0, ctx->stream, L.cost, L.cand_s, L.cand_z, rows,
+        hipLaunchKernelGGL(grid_argmin_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, L.cand_s, L.cand_z, rows,
                            ncand, map, r0, L.s64, L.z64, L.ng, gi);
         TB_KERNEL_CHECK(ctx);
     }
@@ -1057,9 +1092,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         const int i1 = (i0 + d->block < dh) ? i0 + d->block : dh;
         const int nbr = i1 - i0, rows = nh * nbr;
         BlockMap map{nbr, dh, i0};
-        hipLaunchKernelGGL(gather_rows_kernel, dim3(gx(n), rows), dim3(256), 0, st, L.Wt, L.Wb, map, n);
+        hipLaunchKernelGGL(gather_rows_kernel, dim3(gx(n), rows), dim3(256), 0, st, L.Wt, L.Wb, L.Wk, map, n);
         TB_KERNEL_CHECK(ctx);
-        TB_HIP(ctx, hipMemcpyAsync(L.Wk, L.Wb, (size_t)rows * n * sizeof(double), hipMemcpyDeviceToDevice, st));
         if (d->adaptive_grid && !d->group) TB_TRY(grid_search(L, L.Wk, n, nbr, map, 0, n, 0));
         // Algorithm 3 in panels on two levels: inside a group of up to SWEEP_SP columns every 64-column panel updates the rest of
         // the group at once; the columns right of the group get the group's whole update in one product (a contraction SWEEP_SP
@@ -1103,7 +1137,9 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             }
             hipLaunchKernelGGL(comp_error_kernel, dim3(gx(n), rows), dim3(256), 0, st, L.Wb, L.Q64, S3, L.E, map, n);
             const int rem = dh - i1;
-            hipLaunchKernelGGL(comp_T_kernel, dim3((rem + 63) / 64, nh), dim3(64), 0, st, L.Uout, dh, i0, i1, L.T, d->block);
+            const int t_lds = nbr <= 2048;
+            hipLaunchKernelGGL(comp_T_kernel, dim3((rem + 3) / 4, nh), dim3(256), t_lds ? (size_t)4 * nbr * sizeof(double) : 0, st, L.Uout, dh, i0, i1, L.T, d->block,
+                               t_lds);
             TB_KERNEL_CHECK(ctx);
             GemmF64 u{};   // W~[i1:, :] -= T E per head
             u.M = rem; u.N = n; u.K = nbr; u.alpha = -1.0; u.beta = 1.0;
@@ -1118,6 +1154,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
 
     // Algorithm 2 + outputs + loss
     const int rows_all = d->d_out;
+    GemmF64 half{}; half.sym = 1;
     hipLaunchKernelGGL(wbar_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, codes, L.z64, ng, L.gsz, n, L.Wbar);
     TB_KERNEL_CHECK(ctx);
     if (R) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Rd, 0, n, 1, 0.0, L.WR, n, TBOA_PROF_F64_CD));
@@ -1170,23 +1207,23 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         }
         TB_KERNEL_CHECK(ctx);
     } else if (d->cd_iters > 0) {
-        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD));
-        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD));
-        if (R) TB_TRY(launch_sub_f64(ctx, L.Z, L.WR, L.Z, wn));
+        // H_in is symmetric and its products only go into symmetric forms: half products A = Wbar T and Z = W T, T + T^T = 2 H_in
+        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
+        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD, &half));
         if (H_out) {
             GemmF64 c{};
             c.M = dh; c.N = dh; c.K = n; c.alpha = 1.0; c.beta = 0.0;
             c.A = L.Abar; c.sam = n; c.sak = 1; c.B = L.Wbar; c.sbk = 1; c.sbn = n; c.C = L.Cm; c.ldc = dh;
             c.batch = nh; c.strideA = (long long)dh * n; c.strideB = c.strideA; c.strideC = (long long)dh * dh;
             TB_TRY(gemm_f64(ctx, c));
-            c.A = L.Wbar; c.B = L.Z; c.C = L.Fm;
+            // F = Wbar H_in W^T - Wbar (W R)^T = (A W^T + Wbar Z^T) / 2 - Wbar (W R)^T
+            c.alpha = 0.5; c.B = L.W64; c.A2 = L.Wbar; c.B2 = L.Z; c.C = L.Fm;
             TB_TRY(gemm_f64(ctx, c));
+            if (R) { c.alpha = -1.0; c.beta = 1.0; c.A = L.Wbar; c.B = L.WR; c.A2 = nullptr; c.B2 = nullptr; TB_TRY(gemm_f64(ctx, c)); }
             hipLaunchKernelGGL(cd_head_kernel, dim3(nh), dim3(256), (dh + 8) * sizeof(double), st, L.Fm, L.Cm, L.Ho, dh, d->cd_iters, L.s64);
         } else {
-            hipLaunchKernelGGL(rowdot_kernel, dim3((rows_all + 3) / 4), dim3(256), 0, st, L.Abar, (long long)n, L.Wbar, (long long)n,
-                               (long long)rows_all, n, L.dvec);
-            hipLaunchKernelGGL(rowdot_kernel, dim3((rows_all + 3) / 4), dim3(256), 0, st, L.Wbar, (long long)n, L.Z, (long long)n,
-                               (long long)rows_all, n, L.dvec + rows_all);
+            hipLaunchKernelGGL(cd_row_products_kernel, dim3((rows_all + 3) / 4), dim3(256), 0, st, L.Abar, L.Wbar, L.W64, L.Z, R ? L.WR : nullptr,
+                               (long long)rows_all, n, L.dvec, L.dvec + rows_all);
             hipLaunchKernelGGL(cd_diag_kernel, dim3((rows_all + 255) / 256), dim3(256), 0, st, L.dvec + rows_all, L.dvec, rows_all,
                                d->cd_iters, L.s64);
         }
@@ -1197,12 +1234,12 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     TB_KERNEL_CHECK(ctx);
     const bool want_loss = loss || loss_per_head;
     if (want_loss) {
-        // D = Q - W (into Wbar), D H_in (into Abar)
+        // D = Q - W (into Wbar), D T (into Abar): tr(H_out D H_in D^T) takes the symmetric part of D T D^T
         TB_TRY(launch_sub_f64(ctx, L.Q64, L.W64, L.Wbar, wn));
-        if (d->cd_iters > 0 && !d->group) {   // Abar = Wbar H_in and Z are still those of the scale refinement
-            hipLaunchKernelGGL(dh_from_products_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, L.Abar, L.s64, L.Z, R ? L.WR : nullptr, n);
+        if (d->cd_iters > 0 && !d->group) {   // Abar = Wbar T and Z = W T are still those of the scale refinement
+            hipLaunchKernelGGL(dh_from_products_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, L.Abar, L.s64, L.Z, n);
             TB_KERNEL_CHECK(ctx);
-        } else TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD));
+        } else TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
         double* lq = L.lossbuf; double* lc = L.lossbuf + nh;
         TB_TRY(launch_fill_f64(ctx, L.lossbuf, 2 * nh, 0.0));
         if (H_out) {
@@ -1212,11 +1249,11 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             c.batch = nh; c.strideA = (long long)dh * n; c.strideB = c.strideA; c.strideC = (long long)dh * dh;
             c.tag = TBOA_PROF_F64_CD;
             TB_TRY(gemm_f64(ctx, c));
-            hipLaunchKernelGGL(head_trace_kernel, dim3(nh), dim3(256), 0, st, L.Ho, L.Cm, dh, 1.0, lq);
+            hipLaunchKernelGGL(head_trace_kernel, dim3(nh), dim3(256), 0, st, L.Ho, L.Cm, dh, 1.0, 1, lq);
             if (R) {
                 c.A = L.WR; c.B = L.Wbar; c.C = L.Fm;
                 TB_TRY(gemm_f64(ctx, c));
-                hipLaunchKernelGGL(head_trace_kernel, dim3(nh), dim3(256), 0, st, L.Ho, L.Fm, dh, 2.0, lc);
+                hipLaunchKernelGGL(head_trace_kernel, dim3(nh), dim3(256), 0, st, L.Ho, L.Fm, dh, 2.0, 0, lc);
             }
         } else {
             hipLaunchKernelGGL(rowdot_kernel, dim3((rows_all + 3) / 4), dim3(256), 0, st, L.Abar, (long long)n, L.Wbar, (long long)n,
@@ -1300,10 +1337,10 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.T = H_out ? ar.get<double>((size_t)nh * dh * d->block) : nullptr;
     L.cand_s = ar.get<double>(grows * L.ncand); L.cand_z = ar.get<double>(grows * L.ncand); L.cost = ar.get<double>(grows * L.ncand);
     L.Delta = ar.get<double>(delta_bytes / sizeof(double) + 1); L.G = ar.get<double>(g_bytes / sizeof(double) + 1);
-    L.DeltaS = L.GS = L.costS = L.lim = nullptr; L.sel = nullptr; L.Hcat = nullptr;
+    L.DeltaS = L.GS = L.costS = nullptr; L.sel = L.list = nullptr; L.Hcat = nullptr;
     if (L.fast_grid) {
         L.DeltaS = ar.get<double>(grows * GRID_KS * n); L.GS = ar.get<double>(grows * GRID_KS * n);
-        L.costS = ar.get<double>(grows * GRID_KS); L.lim = ar.get<double>(grows); L.sel = ar.get<int>(grows * 3);
+        L.costS = ar.get<double>(grows * GRID_KS); L.sel = ar.get<int>(grows * 3); L.list = ar.get<int>(grows * L.ncand);
         const size_t np = grid_width(n);
         L.Hcat = ar.get<__half>((size_t)2 * L.nhin * np * (np + GRID_PAD));
         L.gscale.up = ar.get<float>(L.nhin * np); L.gscale.down = ar.get<double>(L.nhin * np); L.gscale.dcorr = ar.get<float>(L.nhin * np);
