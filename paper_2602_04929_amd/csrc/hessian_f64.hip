@@ -1,16 +1,21 @@
 // Table 1 Hessians for fp32 inputs: every contraction on the fp64 matrix cores (small problems, reference-grade
 // accuracy).  Literal order of Table 1: projections, A_h = softmax(Q_h K_h^T / sqrt(d_h)) per sequence and head,
-// Y = A_h X_s, sums of outer products over tokens.  The bf16 path for large blocks lives in hessian_bf16.hip.
+// Y = A_h X_s, sums of outer products over tokens.  These calls are bound by launches: the products of a chunk of sequences and KV
+// groups are one launch each (per query head of a group where the operands' layout asks for it), and the sums over the chunk's
+// sequences and heads are one long contraction: the tiny configuration (8 sequences, 4 heads) takes 40 launches instead of 350.  The bf16 path for large blocks lives in hessian_bf16.hip.
 #include "internal.h"
+#include <algorithm>
 #include <math.h>
 
 namespace {
 
-// P[t, :] = softmax(S[t, :k_end]) with k_end = t+1 (causal) or L; zeros elsewhere.  One wavefront per row.
-__global__ __launch_bounds__(256) void softmax_f64_kernel(const double* __restrict__ S, double* __restrict__ P, int L, int causal) {
-    const int lane = threadIdx.x & 63, t = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= L) return;
-    const double* s = S + (long long)t * L; double* p = P + (long long)t * L;
+// in place: every row t of the [L, L] matrices becomes softmax(row[:k_end]) with k_end = t+1 (causal) or L; zeros elsewhere.  One wavefront per row.
+__global__ __launch_bounds__(256) void softmax_f64_kernel(double* __restrict__ S, long long rows, int L, int causal) {
+    const int lane = threadIdx.x & 63;
+    const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (row >= rows) return;
+    const int t = (int)(row % L);
+    double* s = S + row * L;
     const int kend = causal ? t + 1 : L;
     double m = -INFINITY;
     for (int k = lane; k < kend; k += 64) m = fmax(m, s[k]);
@@ -20,7 +25,7 @@ __global__ __launch_bounds__(256) void softmax_f64_kernel(const double* __restri
     for (int k = lane; k < kend; k += 64) sum += exp(s[k] - m);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    for (int k = lane; k < L; k += 64) p[k] = (k < kend) ? exp(s[k] - m) / sum : 0.0;
+    for (int k = lane; k < L; k += 64) s[k] = (k < kend) ? exp(s[k] - m) / sum : 0.0;
 }
 
 struct F64Attn {
@@ -36,12 +41,30 @@ inline GemmF64 mk(int M, int N, int K, double alpha, const double* A, int64_t sa
     return g;
 }
 
-// probabilities of (sequence s, query head h) from the projected activations Qa [T, dq], Ka [T, dkv]
-int attn_probs(const F64Attn& a, const double* Qa, const double* Ka, int s, int h, double* Sbuf, double* Pbuf) {
-    const int g = h / a.rep, L = a.L;
-    TB_TRY(gemm_f64(a.ctx, mk(L, L, a.dh, 1.0 / sqrt((double)a.dh), Qa + (long long)s * L * a.dq + h * a.dh, a.dq, 1,
-                              Ka + (long long)s * L * a.dkv + g * a.dh, 1, a.dkv, 0.0, Sbuf, L)));
-    hipLaunchKernelGGL(softmax_f64_kernel, dim3((L + 3) / 4), dim3(256), 0, a.ctx->stream, Sbuf, Pbuf, L, a.d->causal);
+// Sequences and KV groups taken together: as many as keep the probabilities and `ny` [L, width] results per head within 1 GiB
+struct Chunk { int G, gc; };
+Chunk pick_chunk(const F64Attn& a, int width, int ny) {
+    const double per_group = (double)a.rep * a.L * (a.L + (double)ny * width) * 8.0, room = 1073741824.0;
+    int gc = (int)std::min<double>(a.Hkv, std::max(1.0, floor(room / per_group)));
+    int G = gc < a.Hkv ? 1 : (int)std::min<double>(a.S, std::max(1.0, floor(room / (per_group * a.Hkv))));
+    if ((long long)G * gc > 32768) { G = 32768 / gc; if (G < 1) { G = 1; gc = 32768; } }
+    return Chunk{G, gc};
+}
+
+// probabilities P[g][s][r][L, L] of the sequences s0 .. s0 + Gc - 1 and the KV groups g0 .. g0 + gc - 1 (query head g rep + r) from the projected
+// activations Qa [T, dq], Ka [T, dkv]
+int attn_probs(const F64Attn& a, const double* Qa, const double* Ka, int s0, int Gc, int g0, int gc, double* P) {
+    const long long L = a.L, LL = L * L;
+    for (int r = 0; r < a.rep; ++r) {
+        GemmF64 g = mk(a.L, a.L, a.dh, 1.0 / sqrt((double)a.dh), Qa + s0 * L * a.dq + ((long long)g0 * a.rep + r) * a.dh, a.dq, 1,
+                       Ka + s0 * L * a.dkv + (long long)g0 * a.dh, 1, a.dkv, 0.0, P + r * LL, L);
+        g.batch = gc * Gc; g.batch_inner = Gc;
+        g.strideA = (long long)a.rep * a.dh; g.strideA2 = L * a.dq; g.strideB = a.dh; g.strideB2 = L * a.dkv;
+        g.strideC = (long long)Gc * a.rep * LL; g.strideC2 = a.rep * LL;
+        TB_TRY(gemm_f64(a.ctx, g));
+    }
+    const long long rows = (long long)gc * Gc * a.rep * L;
+    hipLaunchKernelGGL(softmax_f64_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, a.ctx->stream, P, rows, a.L, a.d->causal);
     TB_HIP(a.ctx, hipGetLastError());
     return 0;
 }
@@ -57,15 +80,16 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
     const int T = a.T, dm = a.dm, Hq = a.Hq, Hkv = a.Hkv, dh = a.dh, L = a.L, dq = a.dq, dkv = a.dkv;
     const bool fp = X_fp != nullptr;
     const bool rv = fp && R_v;
-    double *X64, *Xf64, *dX, *Wq64, *Wk64, *Wo64, *Qa, *Ka, *Qf, *Kf, *Sb, *Pb, *Y, *Yf, *Hin, *Rq, *Hoq, *Hok, *Hiv, *Rv, *Hov;
+    const Chunk ck = pick_chunk(a, dm, rv ? 2 : 1);
+    double *X64, *Xf64, *dX, *Wq64, *Wk64, *Wo64, *Qa, *Ka, *Qf, *Kf, *P, *Y, *Yf, *Hin, *Rq, *Hoq, *Hok, *Hiv, *Rv, *Hov;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         X64 = ar.get<double>((size_t)T * dm); Xf64 = fp ? ar.get<double>((size_t)T * dm) : nullptr; dX = fp ? ar.get<double>((size_t)T * dm) : nullptr;
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wo64 = ar.get<double>((size_t)dm * dq);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv);
         Qf = rv ? ar.get<double>((size_t)T * dq) : nullptr; Kf = rv ? ar.get<double>((size_t)T * dkv) : nullptr;
-        Sb = ar.get<double>((size_t)L * L); Pb = ar.get<double>((size_t)L * L);
-        Y = ar.get<double>((size_t)L * dm); Yf = rv ? ar.get<double>((size_t)L * dm) : nullptr;
+        const size_t mats = (size_t)ck.gc * ck.G * a.rep;
+        P = ar.get<double>(mats * L * L); Y = ar.get<double>(mats * L * dm); Yf = rv ? ar.get<double>(mats * L * dm) : nullptr;
         Hin = ar.get<double>((size_t)dm * dm); Rq = fp ? ar.get<double>((size_t)dm * dm) : nullptr;
         Hoq = ar.get<double>((size_t)Hq * dh * dh); Hok = ar.get<double>((size_t)Hkv * dh * dh); Hov = ar.get<double>((size_t)Hkv * dh * dh);
         Hiv = ar.get<double>((size_t)Hkv * dm * dm); Rv = rv ? ar.get<double>((size_t)Hkv * dm * dm) : nullptr;
@@ -90,29 +114,45 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
         TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xf64, dm, 1, Wk64, 1, dm, 0.0, Kf, dkv)));
     }
     // H_out of W_Q,h: K_g^T K_g ; of W_K,g: sum_h Q_h^T Q_h ; of W_V,g: sum_h W_out,h^T W_out,h
-    TB_TRY(launch_fill_f64(ctx, Hok, (int64_t)Hkv * dh * dh, 0.0));
-    TB_TRY(launch_fill_f64(ctx, Hov, (int64_t)Hkv * dh * dh, 0.0));
-    for (int h = 0; h < Hq; ++h) {
-        const int g = h / a.rep;
-        TB_TRY(gemm_f64(ctx, mk(dh, dh, T, 1.0, Ka + g * dh, 1, dkv, Ka + g * dh, dkv, 1, 0.0, Hoq + (long long)h * dh * dh, dh)));
-        TB_TRY(gemm_f64(ctx, mk(dh, dh, T, 1.0, Qa + h * dh, 1, dq, Qa + h * dh, dq, 1, 1.0, Hok + (long long)g * dh * dh, dh)));
-        TB_TRY(gemm_f64(ctx, mk(dh, dh, dm, 1.0, Wo64 + h * dh, 1, dq, Wo64 + h * dh, dq, 1, 1.0, Hov + (long long)g * dh * dh, dh)));
+    {
+        const long long hh = (long long)dh * dh;
+        GemmF64 q = mk(dh, dh, T, 1.0, Ka, 1, dkv, Ka, dkv, 1, 0.0, Hoq, dh);
+        q.batch = Hq; q.batch_inner = a.rep; q.strideA = dh; q.strideB = dh; q.strideC = a.rep * hh; q.strideC2 = hh;
+        TB_TRY(gemm_f64(ctx, q));
+        GemmF64 k = mk(dh, dh, T, 1.0, Qa, 1, dq, Qa, dq, 1, 0.0, Hok, dh);
+        k.batch = Hq; k.batch_inner = a.rep; k.sum_inner = 1; k.strideA = (long long)a.rep * dh; k.strideB = k.strideA; k.strideA2 = dh; k.strideB2 = dh; k.strideC = hh;
+        TB_TRY(gemm_f64(ctx, k));
+        GemmF64 v = mk(dh, dh, dm, 1.0, Wo64, 1, dq, Wo64, dq, 1, 0.0, Hov, dh);
+        v.batch = Hq; v.batch_inner = a.rep; v.sum_inner = 1; v.strideA = k.strideA; v.strideB = k.strideA; v.strideA2 = dh; v.strideB2 = dh; v.strideC = hh;
+        TB_TRY(gemm_f64(ctx, v));
     }
     // H_in of W_V,g: sum over heads of the group and sequences of (A_h X_s)^T (A_h X_s)
-    TB_TRY(launch_fill_f64(ctx, Hiv, (int64_t)Hkv * dm * dm, 0.0));
-    if (rv) TB_TRY(launch_fill_f64(ctx, Rv, (int64_t)Hkv * dm * dm, 0.0));
-    for (int s = 0; s < a.S; ++s)
-        for (int h = 0; h < Hq; ++h) {
-            const int g = h / a.rep;
-            const double* Xs = X64 + (long long)s * L * dm;
-            TB_TRY(attn_probs(a, Qa, Ka, s, h, Sb, Pb));
-            TB_TRY(gemm_f64(ctx, mk(L, dm, L, 1.0, Pb, L, 1, Xs, dm, 1, 0.0, Y, dm)));
-            TB_TRY(gemm_f64(ctx, mk(dm, dm, L, 1.0, Y, 1, dm, Y, dm, 1, 1.0, Hiv + (long long)g * dm * dm, dm)));
+    const long long LL = (long long)L * L, Ld = (long long)L * dm, dd = (long long)dm * dm;
+    for (int s0 = 0; s0 < a.S; s0 += ck.G)
+        for (int g0 = 0; g0 < Hkv; g0 += ck.gc) {
+            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, Hkv - g0);
+            const long long kk = (long long)Gc * a.rep * L;      // rows of Y of one KV group
+            auto outputs = [&](const double* X, double* out) -> int {      // Y[g][s][r] = A X_s
+                for (int r = 0; r < a.rep; ++r) {
+                    GemmF64 y = mk(L, dm, L, 1.0, P + r * LL, L, 1, X + s0 * Ld, dm, 1, 0.0, out + r * Ld, dm);
+                    y.batch = gc * Gc; y.batch_inner = Gc; y.strideA = Gc * a.rep * LL; y.strideA2 = a.rep * LL; y.strideB2 = Ld;
+                    y.strideC = Gc * a.rep * Ld; y.strideC2 = a.rep * Ld;
+                    TB_TRY(gemm_f64(ctx, y));
+                }
+                return 0;
+            };
+            if (kk > 2147483647LL) return tboa_fail(ctx, TBOA_EINVAL, "build_hessians: a KV group's rows exceed the range of int");
+            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, P));
+            TB_TRY(outputs(X64, Y));
+            GemmF64 h = mk(dm, dm, (int)kk, 1.0, Y, 1, dm, Y, dm, 1, s0 ? 1.0 : 0.0, Hiv + g0 * dd, dm);
+            h.batch = gc; h.strideA = kk * dm; h.strideB = h.strideA; h.strideC = dd;
+            TB_TRY(gemm_f64(ctx, h));
             if (rv) {
-                TB_TRY(attn_probs(a, Qf, Kf, s, h, Sb, Pb));
-                TB_TRY(gemm_f64(ctx, mk(L, dm, L, 1.0, Pb, L, 1, Xf64 + (long long)s * L * dm, dm, 1, 0.0, Yf, dm)));
-                TB_TRY(launch_sub_f64(ctx, Y, Yf, Yf, (int64_t)L * dm));
-                TB_TRY(gemm_f64(ctx, mk(dm, dm, L, d->alpha, Yf, 1, dm, Y, dm, 1, 1.0, Rv + (long long)g * dm * dm, dm)));
+                TB_TRY(attn_probs(a, Qf, Kf, s0, Gc, g0, gc, P));
+                TB_TRY(outputs(Xf64, Yf));
+                TB_TRY(launch_sub_f64(ctx, Y, Yf, Yf, gc * kk * dm));
+                h.A = Yf; h.alpha = d->alpha; h.C = Rv + g0 * dd;
+                TB_TRY(gemm_f64(ctx, h));
             }
         }
     if (Hin_qk) TB_TRY(launch_cvt_f64_to_f32(ctx, Hin, Hin_qk, (int64_t)dm * dm));
@@ -126,19 +166,25 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
 }
 
 // attention output concat_h(A_h V_g(h)) [T, dq] for weights Wq/Wk/Wv (fp64) on activations Xa (fp64)
-static int attn_output_f64(const F64Attn& a, const double* Xa, const double* Wq64, const double* Wk64, const double* Wv64,
-                           double* Qa, double* Ka, double* Va, double* Sb, double* Pb, double* O) {
+static int attn_output_f64(const F64Attn& a, Chunk ck, const double* Xa, const double* Wq64, const double* Wk64, const double* Wv64,
+                           double* Qa, double* Ka, double* Va, double* P, double* O) {
     tboa_ctx* ctx = a.ctx;
     const int T = a.T, dm = a.dm, dq = a.dq, dkv = a.dkv, L = a.L, dh = a.dh;
+    const long long LL = (long long)L * L;
     TB_TRY(gemm_f64(ctx, mk(T, dq, dm, 1.0, Xa, dm, 1, Wq64, 1, dm, 0.0, Qa, dq)));
     TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xa, dm, 1, Wk64, 1, dm, 0.0, Ka, dkv)));
     TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xa, dm, 1, Wv64, 1, dm, 0.0, Va, dkv)));
-    for (int s = 0; s < a.S; ++s)
-        for (int h = 0; h < a.Hq; ++h) {
-            const int g = h / a.rep;
-            TB_TRY(attn_probs(a, Qa, Ka, s, h, Sb, Pb));
-            TB_TRY(gemm_f64(ctx, mk(L, dh, L, 1.0, Pb, L, 1, Va + (long long)s * L * dkv + g * dh, dkv, 1, 0.0,
-                                    O + (long long)s * L * dq + h * dh, dq)));
+    for (int s0 = 0; s0 < a.S; s0 += ck.G)
+        for (int g0 = 0; g0 < a.Hkv; g0 += ck.gc) {
+            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, a.Hkv - g0);
+            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, P));
+            for (int r = 0; r < a.rep; ++r) {
+                GemmF64 o = mk(L, dh, L, 1.0, P + r * LL, L, 1, Va + (long long)s0 * L * dkv + (long long)g0 * dh, dkv, 1, 0.0,
+                               O + (long long)s0 * L * dq + ((long long)g0 * a.rep + r) * dh, dq);
+                o.batch = gc * Gc; o.batch_inner = Gc; o.strideA = Gc * a.rep * LL; o.strideA2 = a.rep * LL;
+                o.strideB = dh; o.strideB2 = (long long)L * dkv; o.strideC = (long long)a.rep * dh; o.strideC2 = (long long)L * dq;
+                TB_TRY(gemm_f64(ctx, o));
+            }
         }
     return 0;
 }
@@ -150,13 +196,14 @@ int build_hessian_out_proj_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const voi
               d->n_q_heads / d->n_kv_heads, d->n_q_heads * d->head_dim, d->n_kv_heads * d->head_dim};
     const int T = a.T, dm = a.dm, L = a.L, dq = a.dq, dkv = a.dkv;
     const bool fp = X_fp && R_o;
-    double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *Sb, *Pb, *O, *Of, *H;
+    const Chunk ck = pick_chunk(a, 0, 0);
+    double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *P, *O, *Of, *H;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         X64 = ar.get<double>((size_t)T * dm);
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wv64 = ar.get<double>((size_t)dkv * dm);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv); Va = ar.get<double>((size_t)T * dkv);
-        Sb = ar.get<double>((size_t)L * L); Pb = ar.get<double>((size_t)L * L);
+        P = ar.get<double>((size_t)ck.gc * ck.G * a.rep * L * L);
         O = ar.get<double>((size_t)T * dq); Of = fp ? ar.get<double>((size_t)T * dq) : nullptr;
         H = ar.get<double>((size_t)dq * dq);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
@@ -165,7 +212,7 @@ int build_hessian_out_proj_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const voi
     TB_TRY(launch_cvt_to_f64(ctx, Wq_deq, TBOA_F32, Wq64, (int64_t)dq * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wk_deq, TBOA_F32, Wk64, (int64_t)dkv * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wv_deq, TBOA_F32, Wv64, (int64_t)dkv * dm));
-    TB_TRY(attn_output_f64(a, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, Sb, Pb, O));
+    TB_TRY(attn_output_f64(a, ck, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, P, O));
     TB_TRY(gemm_f64(ctx, mk(dq, dq, T, 1.0, O, 1, dq, O, dq, 1, 0.0, H, dq)));
     TB_TRY(launch_cvt_f64_to_f32(ctx, H, Hin_o, (int64_t)dq * dq));
     if (fp) {
@@ -173,7 +220,7 @@ int build_hessian_out_proj_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const voi
         TB_TRY(launch_cvt_to_f64(ctx, Wq, TBOA_F32, Wq64, (int64_t)dq * dm));
         TB_TRY(launch_cvt_to_f64(ctx, Wk, TBOA_F32, Wk64, (int64_t)dkv * dm));
         TB_TRY(launch_cvt_to_f64(ctx, Wv, TBOA_F32, Wv64, (int64_t)dkv * dm));
-        TB_TRY(attn_output_f64(a, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, Sb, Pb, Of));
+        TB_TRY(attn_output_f64(a, ck, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, P, Of));
         TB_TRY(launch_sub_f64(ctx, O, Of, Of, (int64_t)T * dq));
         TB_TRY(gemm_f64(ctx, mk(dq, dq, T, d->alpha, Of, 1, dq, O, dq, 1, 0.0, H, dq)));
         TB_TRY(launch_cvt_f64_to_f32(ctx, H, R_o, (int64_t)dq * dq));
@@ -186,13 +233,14 @@ int attention_forward_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const float* X
     F64Attn a{ctx, d, d->n_seqs * d->seq_len, d->d_model, d->n_q_heads, d->n_kv_heads, d->head_dim, d->seq_len, d->n_seqs,
               d->n_q_heads / d->n_kv_heads, d->n_q_heads * d->head_dim, d->n_kv_heads * d->head_dim};
     const int T = a.T, dm = a.dm, L = a.L, dq = a.dq, dkv = a.dkv;
-    double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *Sb, *Pb, *O64;
+    const Chunk ck = pick_chunk(a, 0, 0);
+    double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *P, *O64;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         X64 = ar.get<double>((size_t)T * dm);
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wv64 = ar.get<double>((size_t)dkv * dm);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv); Va = ar.get<double>((size_t)T * dkv);
-        Sb = ar.get<double>((size_t)L * L); Pb = ar.get<double>((size_t)L * L);
+        P = ar.get<double>((size_t)ck.gc * ck.G * a.rep * L * L);
         O64 = ar.get<double>((size_t)T * dq);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }
@@ -200,7 +248,7 @@ int attention_forward_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const float* X
     TB_TRY(launch_cvt_to_f64(ctx, Wq, TBOA_F32, Wq64, (int64_t)dq * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wk, TBOA_F32, Wk64, (int64_t)dkv * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wv, TBOA_F32, Wv64, (int64_t)dkv * dm));
-    TB_TRY(attn_output_f64(a, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, Sb, Pb, O64));
+    TB_TRY(attn_output_f64(a, ck, X64, Wq64, Wk64, Wv64, Qa, Ka, Va, P, O64));
     return launch_cvt_f64_to_f32(ctx, O64, O, (int64_t)T * dq);
 }
 
