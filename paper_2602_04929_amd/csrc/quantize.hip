@@ -516,6 +516,7 @@ constexpr int SWEEP_SP = 512;      // columns whose updates of the columns furth
 struct SweepArgs {
     double* Wk; int n; int nbr; BlockMap map;
     const double* U; const double* P; int per_head;   // U, P: [n, n] or [n_heads, n, n]
+    const double* nv;                // null: P is that of Algorithm 3; else block array [rows, n] and P holds S (see run_layer)
     int c0, pw;
     const double* s; const double* z; int ng, gi; double maxq;
     uint8_t* codes; double* Q;       // layer arrays [d_out, n]
@@ -527,7 +528,9 @@ struct SweepArgs {
 // fp64 operations, two rows per wavefront side by side.  Both divisions of a step are products with reciprocals taken once per panel
 // (quant_code_fast decides the code as the quotient would; the other one gets a Newton correction), and the loads of the panel's pieces of U
 // and P are all in flight together (they were taken one row after the other: half of the time): 33 -> 21 us per panel.
-template <int RPW>
+// LAZY: the deviation term through S = R U^T instead of P = (S * M_U) U: with v_m = sum_{j < m} w_j S[j, m] (nv holds -v; what earlier panels
+// contribute is already in it) column j is w_j - v_j U[j, j] when its turn comes, and (e_j + v_j) U[j, :] is taken from the columns to its right.
+template <int RPW, bool LAZY>
 __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
     __shared__ double Us[64][64];
     __shared__ double Ps[64][64];
@@ -550,11 +553,11 @@ __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
             const int j = wave + 4 * q;
             const bool in = j < pw && lane < pw;
             Us[j][lane] = in ? u[q] : 0.0;
-            Ps[j][lane] = in && P ? p[q] : 0.0;
+            Ps[j][lane] = in && P && (!LAZY || lane > j) ? p[q] : 0.0;
             if (j == lane) Ui[lane] = in ? 1.0 / u[q] : 1.0;
         }
     }
-    double w[RPW], s[RPW], si[RPW], z[RPW], qv[RPW], Qv[RPW], ev[RPW], wsv[RPW];
+    double w[RPW], nv[RPW], s[RPW], si[RPW], z[RPW], qv[RPW], Qv[RPW], ev[RPW], wsv[RPW];
     int R[RPW]; bool valid[RPW];
 #pragma unroll
     for (int i = 0; i < RPW; ++i) {
@@ -563,6 +566,7 @@ __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
         R[i] = h * a.nbr + (valid[i] ? r : 0);
         const long long lr = layer_row(a.map, R[i]);
         w[i] = (valid[i] && lane < pw) ? a.Wk[(long long)R[i] * n + c0 + lane] : 0.0;
+        nv[i] = (LAZY && valid[i] && lane < pw) ? a.nv[(long long)R[i] * n + c0 + lane] : 0.0;
         s[i] = a.s[lr * a.ng + a.gi]; z[i] = a.z[lr * a.ng + a.gi]; si[i] = 1.0 / s[i];
         qv[i] = Qv[i] = ev[i] = wsv[i] = 0.0;
     }
@@ -572,14 +576,17 @@ __global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
         const double urow = Us[j][lane], prow = Ps[j][lane], ujj = Us[j][j], uinv = Ui[j];
 #pragma unroll
         for (int i = 0; i < RPW; ++i) {
-            const double wj = readlane_f64(w[i], j);
+            const double nvj = LAZY ? readlane_f64(nv[i], j) : 0.0;
+            const double wj = LAZY ? __builtin_fma(nvj, ujj, readlane_f64(w[i], j)) : readlane_f64(w[i], j);
             const double q = quant_code_fast(wj, s[i], si[i], z[i], a.maxq);
             const double Qj = s[i] * (q - z[i]);
             const double d = wj - Qj, e0 = d * uinv;
-            const double e = __builtin_fma(__builtin_fma(-e0, ujj, d), uinv, e0);      // d / ujj
+            const double eq = __builtin_fma(__builtin_fma(-e0, ujj, d), uinv, e0);     // d / ujj
+            const double e = LAZY ? eq - nvj : eq;
             if (lane == j) { qv[i] = q; Qv[i] = Qj; ev[i] = e; wsv[i] = wj; }
             w[i] = __builtin_fma(-e, urow, w[i]);
-            if (hasP) w[i] = __builtin_fma(-wj, prow, w[i]);
+            if constexpr (LAZY) nv[i] = __builtin_fma(-wj, prow, nv[i]);
+            else if (hasP) w[i] = __builtin_fma(-wj, prow, w[i]);
         }
     }
 #pragma unroll
@@ -878,6 +885,8 @@ struct Layer {
     double *Wbar, *Abar, *Z, *WR, *Cm, *Fm, *dvec, *lossbuf;
     double *Cg, *Fg, *cdnum;    // group-wise refinement: Gram blocks per (group, group) pair
     int grid_chunk, fast_chunk;     // block rows (shared H_in) or heads (per-head H_in) per grid-search pass: exact, two-phase
+    int lazy;           // the deviation term of the sweep goes through S = R U^T (see run_layer); nr, nv: its row arrays
+    double *nr, *nv;
     int* gstat;         // device words of the two-phase search (GS_*), cleared at the start of a run
     long long nn;
 };
@@ -1001,6 +1010,18 @@ int block_gemm(Layer& L, int nbr, int N, int K, double alpha, const double* A, l
     return gemm_f64(L.ctx, g);
 }
 
+// The two updates of a lazily corrected sweep (L.lazy) as one launch: Wk[:, col ..] -= Epan U and acc[:, col ..] -= Wsnap M, for the columns ecol .. of the
+// panel arrays and the N columns at offset boff of U and of M (both d x d, or one per head).
+int pair_gemm(Layer& L, int nbr, int N, int K, int ecol, long long boff, const double* M, int col, double* acc) {
+    GemmF64 g{};
+    g.N = N; g.K = K; g.alpha = -1.0; g.beta = 1.0; g.tag = TBOA_PROF_F64_SWEEP;
+    g.A = L.Epan + ecol; g.sam = SWEEP_SP; g.sak = 1; g.B = L.Uin + boff; g.sbk = L.n; g.sbn = 1; g.C = L.Wk + col; g.ldc = L.n;
+    g.batch_inner = 2; g.strideA2 = L.Wsnap - L.Epan; g.strideB2 = M - L.Uin; g.strideC2 = acc - L.Wk;
+    if (L.nhin > 1) { g.M = nbr; g.batch = 2 * L.nh; g.strideA = (long long)nbr * SWEEP_SP; g.strideB = L.nn; g.strideC = (long long)nbr * L.n; }
+    else { g.M = L.nh * nbr; g.batch = 2; }
+    return gemm_f64(L.ctx, g);
+}
+
 // return values of run_layer: the approximate costs of the two-phase grid search could not be trusted somewhere in this
 // run (see grid_search): the caller runs the layer again with exact costs for every candidate, or (one half term of H was not enough) with two
 constexpr int RUN_AGAIN_EXACT = 1, RUN_AGAIN_TWO_TERMS = 2;
@@ -1046,24 +1067,42 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     StreamSwap swap(ctx);
     TB_HIP(ctx, hipStreamWaitEvent(ctx->aux, ctx->ev_fork, 0));
     TB_TRY(chol_inv_upper_f64(ctx, n, nhin, L.Hfac, L.Uin, L.ftmp, L.fdinv, 0, true));
-    if (R) {   // Algorithm 3 line 2: P = ((R U^T) * M_U) U
+    // Algorithm 3 line 2: P = ((R U^T) * M_U) U.  Two products of d^3 / 3 flops each per H_in, which few rows do not repay (W_V of a grouped-query
+    // block: 128 rows per 8192 x 8192 Hessian, 54 of its 176 ms).  L.lazy: the term that P carries from the columns j to a column k is
+    //     sum_{j < k} w_j P[j, k] = sum_{m <= k} v_m U[m, k],    v_m = sum_{j < m} w_j S[j, m] = sum_{k >= m} U[m, k] sum_{j < m} w_j R[j, k],  S = R U^T
+    // so a group of SWEEP_SP columns starts from v = r U^T with r = sum of w_j R[j, :] over the columns already done (one product per group), inside the
+    // group the block of S on the diagonal takes the place of P, and after it r += w R.  That costs rows d^2 flops more in the sweep and
+    // SWEEP_SP d^2 for the blocks: taken when that is less than the products it saves (rows < d / 2 - SWEEP_SP per H_in).
+    if (R) {
         TB_TRY(launch_cvt_f32_to_f64(ctx, R, L.Rd, nhin * nn));
-        GemmF64 a{};
-        a.M = n; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0;
-        a.A = L.Rd; a.sam = n; a.sak = 1; a.B = L.Uin; a.sbk = 1; a.sbn = n; a.klo_n = 1;   // U[c, k] = 0 for k < c
-        a.skip_lower = 1;   // only the part above the diagonal survives the mask below
-        a.C = L.Hfac; a.ldc = n; a.batch = nhin; a.strideA = nn; a.strideB = nn; a.strideC = nn;
-        a.tag = TBOA_PROF_F64_FACTOR;
-        TB_TRY(gemm_f64(ctx, a));
-        TB_TRY(launch_strict_upper_f64(ctx, L.Hfac, n, nhin));
-        GemmF64 b{};
-        b.M = n; b.N = n; b.K = n; b.alpha = 1.0; b.beta = 0.0;
-        b.A = L.Hfac; b.sam = n; b.sak = 1; b.klo_m = 1;       // (R U^T)_masked[j, m] = 0 for m <= j
-        b.B = L.Uin; b.sbk = n; b.sbn = 1; b.khi_n = 1;        // U[m, k] = 0 for m > k
-        b.diag_order = 1;                                      // contraction range (row start, column end]: grows with the column
-        b.C = L.P; b.ldc = n; b.batch = nhin; b.strideA = nn; b.strideB = nn; b.strideC = nn;
-        b.tag = TBOA_PROF_F64_FACTOR;
-        TB_TRY(gemm_f64(ctx, b));
+        if (L.lazy) {
+            // only the blocks of SWEEP_SP columns on the diagonal of S = R U^T, into L.P
+            for (int s0 = 0; s0 < n; s0 += SWEEP_SP) {
+                const int w = n - s0 < SWEEP_SP ? n - s0 : SWEEP_SP;
+                const long long o = (long long)s0 * n + s0;
+                GemmF64 a{};
+                a.M = w; a.N = w; a.K = n - s0; a.alpha = 1.0; a.beta = 0.0; a.A = L.Rd + o; a.sam = n; a.sak = 1; a.B = L.Uin + o; a.sbk = 1; a.sbn = n;
+                a.C = L.P + o; a.ldc = n; a.batch = nhin; a.strideA = nn; a.strideB = nn; a.strideC = nn; a.tag = TBOA_PROF_F64_FACTOR;
+                TB_TRY(gemm_f64(ctx, a));
+            }
+        } else {
+            GemmF64 a{};
+            a.M = n; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0;
+            a.A = L.Rd; a.sam = n; a.sak = 1; a.B = L.Uin; a.sbk = 1; a.sbn = n; a.klo_n = 1;   // U[c, k] = 0 for k < c
+            a.skip_lower = 1;   // only the part above the diagonal survives the mask below
+            a.C = L.Hfac; a.ldc = n; a.batch = nhin; a.strideA = nn; a.strideB = nn; a.strideC = nn;
+            a.tag = TBOA_PROF_F64_FACTOR;
+            TB_TRY(gemm_f64(ctx, a));
+            TB_TRY(launch_strict_upper_f64(ctx, L.Hfac, n, nhin));
+            GemmF64 b{};
+            b.M = n; b.N = n; b.K = n; b.alpha = 1.0; b.beta = 0.0;
+            b.A = L.Hfac; b.sam = n; b.sak = 1; b.klo_m = 1;       // (R U^T)_masked[j, m] = 0 for m <= j
+            b.B = L.Uin; b.sbk = n; b.sbn = 1; b.khi_n = 1;        // U[m, k] = 0 for m > k
+            b.diag_order = 1;                                      // contraction range (row start, column end]: grows with the column
+            b.C = L.P; b.ldc = n; b.batch = nhin; b.strideA = nn; b.strideB = nn; b.strideC = nn;
+            b.tag = TBOA_PROF_F64_FACTOR;
+            TB_TRY(gemm_f64(ctx, b));
+        }
     }
     if (H_out) {
         TB_TRY(launch_f32_to_f64_damp(ctx, dh, nh, H_out, d->damp, L.Ho));
@@ -1094,12 +1133,15 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         BlockMap map{nbr, dh, i0};
         hipLaunchKernelGGL(gather_rows_kernel, dim3(gx(n), rows), dim3(256), 0, st, L.Wt, L.Wb, L.Wk, map, n);
         TB_KERNEL_CHECK(ctx);
+        if (L.lazy) { TB_TRY(launch_fill_f64(ctx, L.nr, (int64_t)rows * n, 0.0)); TB_TRY(launch_fill_f64(ctx, L.nv, (int64_t)rows * n, 0.0)); }
         if (d->adaptive_grid && !d->group) TB_TRY(grid_search(L, L.Wk, n, nbr, map, 0, n, 0));
         // Algorithm 3 in panels on two levels: inside a group of up to SWEEP_SP columns every 64-column panel updates the rest of
         // the group at once; the columns right of the group get the group's whole update in one product (a contraction SWEEP_SP
         // deep instead of 64: a quarter of the passes over the remaining columns)
         for (int s0 = 0; s0 < n; s0 += sp) {
             const int s1 = (n - s0 < sp) ? n : s0 + sp;
+            if (L.lazy && s0 > 0)      // -v of the group's columns from what the columns before it have left in -r
+                TB_TRY(block_gemm(L, nbr, s1 - s0, n - s0, 1.0, L.nr + s0, n, L.Uin, (long long)s0 * n + s0, 1, n, 0.0, L.nv + s0, n, TBOA_PROF_F64_SWEEP));
             for (int c0 = s0; c0 < s1; c0 += pw_max) {
                 const int pw = (s1 - c0 < pw_max) ? s1 - c0 : pw_max, c1 = c0 + pw;
                 const int gi = c0 / L.gsz;
@@ -1107,18 +1149,27 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                 SweepArgs a;
                 a.Wk = L.Wk; a.n = n; a.nbr = nbr; a.map = map; a.U = L.Uin; a.P = Pp; a.per_head = nhin > 1;
                 a.c0 = c0; a.pw = pw; a.s = L.s64; a.z = L.z64; a.ng = ng; a.gi = gi; a.maxq = L.maxq;
-                a.codes = codes; a.Q = L.Q64; a.Epan = L.Epan + (c0 - s0); a.Wsnap = L.Wsnap + (c0 - s0); a.epitch = SWEEP_SP;
+                a.codes = codes; a.Q = L.Q64; a.Epan = L.Epan + (c0 - s0); a.Wsnap = L.Wsnap + (c0 - s0); a.epitch = SWEEP_SP; a.nv = L.nv;
                 TB_TRY(setup_join());
-                hipLaunchKernelGGL((sweep_panel_kernel<2>), dim3((nbr + 7) / 8, nh), dim3(256), 0, st, a);
+                if (L.lazy) hipLaunchKernelGGL((sweep_panel_kernel<2, true>), dim3((nbr + 7) / 8, nh), dim3(256), 0, st, a);
+                else hipLaunchKernelGGL((sweep_panel_kernel<2, false>), dim3((nbr + 7) / 8, nh), dim3(256), 0, st, a);
                 TB_KERNEL_CHECK(ctx);
                 if (c1 < s1) {   // rest of the group: W[:, c1:s1] -= E U[c0:c1, c1:s1] + Wsnap P[c0:c1, c1:s1]
                     GemmF64 two{};   // both terms in one pass over the output
+                    if (L.lazy) {    // W -= (E + V) U and -V -= Wsnap S: two results, one launch
+                        TB_TRY(pair_gemm(L, nbr, s1 - c1, pw, c0 - s0, (long long)c0 * n + c1, L.P, c1, L.nv));
+                        continue;
+                    }
                     if (Pp) { two.A2 = L.Wsnap + (c0 - s0); two.B2 = L.P + (long long)c0 * n + c1; }
                     TB_TRY(block_gemm(L, nbr, s1 - c1, pw, -1.0, L.Epan + (c0 - s0), SWEEP_SP, L.Uin, (long long)c0 * n + c1, n, 1, 1.0, L.Wk + c1, n,
                                       TBOA_PROF_F64_SWEEP, &two));
                 }
             }
             if (s1 < n) {   // columns right of the group: W[:, s1:] -= E U[s0:s1, s1:] + Wsnap P[s0:s1, s1:]
+                if (L.lazy) {        // W -= (E + V) U and -R -= Wsnap R
+                    TB_TRY(pair_gemm(L, nbr, n - s1, s1 - s0, 0, (long long)s0 * n + s1, L.Rd, s1, L.nr));
+                    continue;
+                }
                 GemmF64 two{};
                 if (Pp) { two.A2 = L.Wsnap; two.B2 = L.P + (long long)s0 * n + s1; }
                 TB_TRY(block_gemm(L, nbr, n - s1, s1 - s0, -1.0, L.Epan, SWEEP_SP, L.Uin, (long long)s0 * n + s1, n, 1, 1.0, L.Wk + s1, n,
@@ -1334,6 +1385,9 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.Epan = ar.get<double>(brows * SWEEP_SP); L.Wsnap = ar.get<double>(brows * SWEEP_SP);
     L.E = H_out ? ar.get<double>(brows * n) : nullptr;
     L.S1 = (H_out && R) ? ar.get<double>(brows * n) : nullptr; L.S2 = (H_out && R) ? ar.get<double>(brows * n) : nullptr;
+    // (a group-wise grid is searched on the current columns, which the lazy form does not hold until their turn comes)
+    L.lazy = R && !d->group && (L.nhin > 1 ? dh : d->d_out) < n / 2 - SWEEP_SP;
+    L.nr = L.lazy ? ar.get<double>(brows * n) : nullptr; L.nv = L.lazy ? ar.get<double>(brows * n) : nullptr;
     L.T = H_out ? ar.get<double>((size_t)nh * dh * d->block) : nullptr;
     L.cand_s = ar.get<double>(grows * L.ncand); L.cand_z = ar.get<double>(grows * L.ncand); L.cost = ar.get<double>(grows * L.ncand);
     L.Delta = ar.get<double>(delta_bytes / sizeof(double) + 1); L.G = ar.get<double>(g_bytes / sizeof(double) + 1);
