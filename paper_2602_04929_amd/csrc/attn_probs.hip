@@ -16,6 +16,9 @@
 // both paths (segments k_hi, k_lo: 64 x d_h each) is copied global -> LDS block by block (a 16 x 32 block is 1 KB contiguous
 // in memory and lands as it is: its XOR-swizzled 16-byte pieces are what conflict-free fragment reads need), the copy of
 // the next tile running under the element-wise work on the current one.
+// With one score matrix only (attention forward, Hessians without the full-precision path) the second path's wavefronts and buffers take the next
+// 64 keys of the same matrix: a tile is 128 keys then, and the two halves' maxima and sums are merged like those of two key halves.  (Left idle
+// they were half of the wavefronts: 32 heads of 2048 tokens 343 -> 278 us.)
 // Pass 1 walks the key tiles up to the diagonal and leaves, per query, maximum and 1 / sum; pass 2 walks them again,
 // turns scores into probabilities, exchanges them through LDS (so that A - A~ can be formed and every thread ends up with
 // 16 consecutive queries of one key row), and writes whole 16-byte pieces of the blocked result; the key tiles between the
@@ -87,9 +90,11 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     // work of one runs under the MFMAs of the other
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = wave >> 2, wi = (wave >> 1) & 1, th = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
-    const bool two = Qb != nullptr, active = (p == 0) || two;
+    const bool two = Qb != nullptr;
     const long long mat = (long long)L * 3 * DH;
-    const bf16* K0 = Ka + g * mat; const bf16* K1 = two ? Kb + g * mat : K0;
+    const bf16* K0 = Ka + g * mat; const bf16* K1 = two ? Kb + g * mat : K0 + 64LL * 3 * DH;     // one path: the next 64 keys (four block rows)
+    const int step = two ? 64 : 128, ko = two ? 0 : 64 * p;      // keys of a tile; first key of this wavefront's half of it
+    const int ps = two ? p : 0;                                  // score matrix of this wavefront
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const unsigned kt_lds = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)kt);
     const int tq = t0 + 64 * th;                 // first query of this wavefront
@@ -97,8 +102,8 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     bool half_ops = false;
     float sc2 = scale2;
     {
-        const int* wq = p ? qs.qb : qs.qa; const int* wk = p ? qs.kb : qs.ka;
-        if (active && wq && wk) {
+        const int* wq = ps ? qs.qb : qs.qa; const int* wk = ps ? qs.kb : qs.ka;
+        if (wq && wk) {
             const int bq = __builtin_amdgcn_readfirstlane(*wq), bk = __builtin_amdgcn_readfirstlane(*wk);
             if (bq >= 0 && bk >= 0) { half_ops = true; sc2 = ldexpf(scale2, -(tboa_half_exp(bq) + tboa_half_exp(bk))); }
         }
@@ -106,8 +111,8 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
 
     // Q^ fragments of this wavefront's path: B operand of the MFMA (lane: query l32 of block tb, 8 contraction elements from 8 lh)
     bf16x8 qh[2][NKS], ql[2][NKS];
-    if (active) {
-        const bf16* Qp = (p ? Qb : Qa) + h * mat;
+    {
+        const bf16* Qp = (ps ? Qb : Qa) + h * mat;
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
@@ -121,18 +126,15 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     // the K^ tile at keys i0: block b = ((path 2 + segment) NCB + cb) 4 + rb of the LDS image comes from block
     // (i0 / 16 + rb, segment's first block + cb) of that path's K^; wavefront w copies the blocks w, w + 8, ...
     auto issue = [&](int i0) {
-        const int nblk = two ? NBLK : NBLK / 2;
 #pragma unroll
         for (int j = 0; j < NBLK / 8; ++j) {
             const int b = wave_s + 8 * j;
-            if (b < nblk) {
-                const int rb = b & 3, cb = (b >> 2) % NCB, ps = (b >> 2) / NCB;     // ps = path 2 + segment (k_hi, k_lo)
-                const bf16* src = ((ps >> 1) ? K1 : K0) + ((long long)((i0 >> 4) + rb) * KB + ((ps & 1) ? 2 * NCB : 0) + cb) * 512;
-                lds_direct_16((unsigned)lane * 16u, (const char*)src, kt_lds + (unsigned)b * 1024u);
-            }
+            const int rb = b & 3, cb = (b >> 2) % NCB, seg = (b >> 2) / NCB;        // seg = path 2 + segment (k_hi, k_lo)
+            const bf16* src = ((seg >> 1) ? K1 : K0) + ((long long)((i0 >> 4) + rb) * KB + ((seg & 1) ? 2 * NCB : 0) + cb) * 512;
+            lds_direct_16((unsigned)lane * 16u, (const char*)src, kt_lds + (unsigned)b * 1024u);
         }
     };
-    // S^T of the tile for this wavefront: acc[tb][4 b + j] = q . k of (key i0 + 32 wi + 8 b + 4 lh + j, query tq + 32 tb + l32)
+    // S^T of the tile for this wavefront: acc[tb][4 b + j] = q . k of (key i0 + ko + 32 wi + 8 b + 4 lh + j, query tq + 32 tb + l32)
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     f32x16 acc[2];
     auto multiply = [&]() {
@@ -165,8 +167,8 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     };
     auto landed = [&]() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); __syncthreads(); };
 
-    const int live = t0 / 64 + 2;                              // key tiles up to and including the two on the diagonal
-    const int tiles = min(L, (t0 / 256 + 1) * 256) / 64;       // ... up to the end of the diagonal's 256-tile
+    const int live = (t0 + 128) / step;                        // key tiles up to and including those on the diagonal
+    const int tiles = min(L, (t0 / 256 + 1) * 256) / step;     // ... up to the end of the diagonal's 256-tile
     // Scores are kept in units of log 2: v = (q . k) sc2 with sc2 = log2(e) / sqrt(d_h) (over the operands' powers of two),
     // probabilities 2^(v - max) / sum.
     // ---- pass 1: maximum and sum per query, over this wavefront's keys
@@ -174,12 +176,12 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     issue(0);
     landed();
     for (int it = 0; it < live; ++it) {
-        if (active) multiply();
+        multiply();
         __syncthreads();                                   // every wavefront has read the tile
-        if (it + 1 < live) issue(64 * (it + 1));           // the next one lands under the element-wise work below
-        if (active) {
-            const int ib = 64 * it + 32 * wi + 4 * lh;
-            const bool masked = 64 * it + 63 > tq;         // a tile that reaches beyond the first query of this wavefront
+        if (it + 1 < live) issue(step * (it + 1));         // the next one lands under the element-wise work below
+        {
+            const int ib = step * it + ko + 32 * wi + 4 * lh;
+            const bool masked = step * it + ko + 63 > tq;         // a tile that reaches beyond the first query of this wavefront
 #pragma unroll
             for (int tb = 0; tb < 2; ++tb) {
                 const int t = tq + 32 * tb + l32;
@@ -199,7 +201,7 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
         }
         landed();
     }
-    if (active) {
+    {
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb) {       // the two lane halves hold different keys of the same query
             const float m2 = __shfl_xor(m[tb], 32, 64), s2 = __shfl_xor(s[tb], 32, 64);
@@ -210,17 +212,23 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
         }
     }
     __syncthreads();
-    if (threadIdx.x < 2 * BT && (threadIdx.x < BT || two)) {
+    if (threadIdx.x < 2 * BT) {                // (one path: both halves of the threads merge all four parts)
         const int pp = threadIdx.x / BT, tl = threadIdx.x % BT;
-        const float ma = stat[((pp * 2 + 0) * 2 + 0) * BT + tl], sa = stat[((pp * 2 + 0) * 2 + 1) * BT + tl];
-        const float mb = stat[((pp * 2 + 1) * 2 + 0) * BT + tl], sb = stat[((pp * 2 + 1) * 2 + 1) * BT + tl];
-        const float M = fmaxf(ma, mb);
-        const float sum = (ma == -INFINITY ? 0.f : sa * ex2(ma - M)) + (mb == -INFINITY ? 0.f : sb * ex2(mb - M));
+        float M = -INFINITY, sum = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int part = two ? 2 * pp + (q & 1) : q;
+            if (two && q > 1) break;
+            const float mq = stat[(part * 2 + 0) * BT + tl], sq = stat[(part * 2 + 1) * BT + tl];
+            const float Mn = fmaxf(M, mq);
+            sum = (M == -INFINITY ? 0.f : sum * ex2(M - Mn)) + (mq == -INFINITY ? 0.f : sq * ex2(mq - Mn));
+            M = Mn;
+        }
         fin[(pp * 2 + 0) * BT + tl] = M; fin[(pp * 2 + 1) * BT + tl] = 1.f / sum;
     }
     __syncthreads();
     float M[2] = {0.f, 0.f}, inv[2] = {0.f, 0.f};
-    if (active) {
+    {
 #pragma unroll
         for (int tb = 0; tb < 2; ++tb) {
             const int tl = 64 * th + 32 * tb + l32;
@@ -231,17 +239,17 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     // (ATTN_PROBS_HALF_SCALE): the lo half of a pair then stays a normal number down to probabilities of 2^-17, where unscaled it
     // would be subnormal below 2^-3 (an absolute error of 3e-8 on every entry); the products that read them take the factor out.
     const float osc = f16 ? ATTN_PROBS_HALF_SCALE : 1.f;
-    bf16* dst[4] = {out.hi + g * group_stride, out.lo ? out.lo + g * group_stride : nullptr, out.dhi ? out.dhi + g * group_stride : nullptr,
-                    out.dlo ? out.dlo + g * group_stride : nullptr};
+    bf16* dst[4] = {out.hi + g * group_stride, out.lo ? out.lo + g * group_stride : nullptr, two ? out.dhi + g * group_stride : out.hi + g * group_stride,
+                    two ? out.dlo + g * group_stride : out.lo + g * group_stride};
     issue(0);
     landed();
     for (int it = 0; it < tiles; ++it) {
-        const int i0 = 64 * it;
+        const int i0 = step * it;
         if (it < live) {
-            if (active) {
+            {
                 multiply();
                 const int il = 32 * wi + 4 * lh;
-                const bool masked = i0 + 63 > tq;
+                const bool masked = i0 + ko + 63 > tq;
 #pragma unroll
                 for (int tb = 0; tb < 2; ++tb) {
                     const int t = tq + 32 * tb + l32;
@@ -249,13 +257,13 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
                     for (int e = 0; e < 16; ++e) {
                         const int row = il + 8 * (e >> 2) + (e & 3);
                         float a = ex2(acc[tb][e] * sc2 - M[tb]) * inv[tb];
-                        if (masked && i0 + row > t) a = 0.f;
+                        if (masked && i0 + ko + row > t) a = 0.f;
                         ex[(p * 64 + row) * EXP + 64 * th + 32 * tb + l32] = a;
                     }
                 }
             }
             __syncthreads();                               // the tile has been read, its probabilities are in LDS
-            if (it + 1 < live) issue(64 * (it + 1));
+            if (it + 1 < live) issue(step * (it + 1));
         }
         if constexpr (ROWS) {
             // per-head result P[h][t][.] = [A_hi | A_lo | A~_hi | A~_lo] (segments of L columns), queries as rows: eight consecutive
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float a = (it < live) ? ex[(8 * i8 + e) * EXP + tq2] * osc : 0.f;
-                    const float a2 = (it < live && two) ? ex[(64 + 8 * i8 + e) * EXP + tq2] * osc : 0.f;
+                    const float a2 = (it < live) ? ex[(64 + 8 * i8 + e) * EXP + tq2] * osc : 0.f;
                     hi.b[e] = enc16(a, f16); lo.b[e] = enc16(a - dec16(hi.b[e], f16), f16);
                     h2.b[e] = enc16(a2, f16); l2.b[e] = enc16(a2 - dec16(h2.b[e], f16), f16);
                 }
@@ -275,7 +283,8 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
                 bf16* ph = out.hi + h * group_stride;
                 const long long kb = ldp >> 5, tq3 = t0 + tq2, col = i0 + 8 * i8;
                 *(uint4*)(ph + tboa_blocked_offset(tq3, col, kb)) = hi.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + col, kb)) = lo.u;
-                if (two) { *(uint4*)(ph + tboa_blocked_offset(tq3, 2LL * L + col, kb)) = h2.u; *(uint4*)(ph + tboa_blocked_offset(tq3, 3LL * L + col, kb)) = l2.u; }
+                const long long c2 = two ? 2LL * L + col : col + 64;      // the other path's segments, or the next 64 keys
+                *(uint4*)(ph + tboa_blocked_offset(tq3, c2, kb)) = h2.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + c2, kb)) = l2.u;
             }
         } else {
             // transposed blocked result: sixteen consecutive lanes take the 128 queries of one key row, 8 each (one 16-byte piece per
@@ -289,18 +298,19 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
                     f4 v = {0.f, 0.f, 0.f, 0.f}, w = {0.f, 0.f, 0.f, 0.f};
                     if (it < live) {
                         v = *(const f4*)(ex + ri * EXP + 8 * t8 + 4 * q);
-                        if (two) w = *(const f4*)(ex + (64 + ri) * EXP + 8 * t8 + 4 * q);
+                        w = *(const f4*)(ex + (64 + ri) * EXP + 8 * t8 + 4 * q);
                     }
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float a = v[e] * osc, d = (v[e] - w[e]) * osc;
+                        const float a = v[e] * osc, d = (two ? v[e] - w[e] : w[e]) * osc;
                         hi.b[4 * q + e] = enc16(a, f16); lo.b[4 * q + e] = enc16(a - dec16(hi.b[4 * q + e], f16), f16);
                         dh.b[4 * q + e] = enc16(d, f16); dl.b[4 * q + e] = enc16(d - dec16(dh.b[4 * q + e], f16), f16);
                     }
                 }
                 const long long o = tboa_blocked_offset(i0 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
                 *(uint4*)(dst[0] + o) = hi.u; *(uint4*)(dst[1] + o) = lo.u;
-                if (two) { *(uint4*)(dst[2] + o) = dh.u; *(uint4*)(dst[3] + o) = dl.u; }
+                const long long o2 = two ? o : tboa_blocked_offset(i0 + 64 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
+                *(uint4*)(dst[2] + o2) = dh.u; *(uint4*)(dst[3] + o2) = dl.u;
             }
         }
         if (it < live) landed();                           // next tile in LDS; the exchange buffer is free again
