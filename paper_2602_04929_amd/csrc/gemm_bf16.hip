@@ -63,6 +63,8 @@ struct Args {
     // dispatched LDS-direct kernel: term_dA / term_dB are the distances in bytes from one pair's buffer to the next; segs (or null) says per
     // batch entry how many pairs are taken; last_scale: see GemmBf16
     const int* segs; float last_scale;
+    const float* col_scale; const __hip_bfloat16* residual;      // epilogue of a single 16-bit result (see GemmBf16)
+    int half_n; const float* up_scale;      // gated product: result columns, else 0
 };
 
 // Work item of this workgroup.  Workgroups are dealt to the eight XCDs round-robin by their linear number, so workgroup
@@ -189,6 +191,64 @@ __device__ __forceinline__ void store_acc_tiled(const Args& g, const f32x16 (&ac
                 *(uint2*)p = pack16x4(g, r);
                 if (g.flags & TBOA_GEMM_C_HILO) *(uint2*)((__hip_bfloat16*)g.C2 + (p - (__hip_bfloat16*)g.C)) = pack_lo4(g, r);
             }
+        }
+}
+
+// the result times a factor per column plus a residual, rounded to bf16 (linear layers); four consecutive columns per lane
+template <int TJ>
+__device__ __forceinline__ void store_acc_linear(const Args& g, const f32x16 (&acc)[4][TJ], int row0, int col0) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+    __hip_bfloat16* C = (__hip_bfloat16*)g.C; const __hip_bfloat16* res = g.residual;
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) {
+        const int col = col0 + 32 * j + 4 * (l32 >> 2);
+        f32x4 sc = {1.f, 1.f, 1.f, 1.f};
+        if (g.col_scale) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) if (col + e < g.N) sc[e] = g.col_scale[col + e];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int b = 0; b < 4; ++b) {
+                const int row = row0 + 32 * i + 8 * b + 4 * lh + (l32 & 3);
+                if (row >= g.M || col >= g.N) continue;
+                f32x4 r = {acc[i][j][4 * b], acc[i][j][4 * b + 1], acc[i][j][4 * b + 2], acc[i][j][4 * b + 3]};
+                r = r * g.alpha * sc;
+                const long long o = (long long)row * g.ldc + col;
+                if (g.vec_c && col + 4 <= g.N) {
+                    if (res) r += __builtin_convertvector(__builtin_bit_cast(bf16x4, *(const uint2*)(res + o)), f32x4);
+                    *(uint2*)(C + o) = __builtin_bit_cast(uint2, __builtin_convertvector(r, bf16x4));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) C[o + e] = __float2bfloat16(r[e] + (res ? __bfloat162float(res[o + e]) : 0.f));
+                }
+            }
+    }
+}
+
+// gated product: the wavefront's first 32 columns are gate values, the second 32 the up values of the same result columns
+__device__ __forceinline__ void store_acc_gate_up(const Args& g, const f32x16 (&acc)[4][2], int row0, int col0) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+    const int col = (col0 >> 1) + 4 * (l32 >> 2);      // col0 = tile column + 64 (wavefront % 4)
+    if (col >= g.half_n) return;                        // (half_n is a multiple of 32)
+    f32x4 gs = {1.f, 1.f, 1.f, 1.f}, us = gs;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { if (g.col_scale) gs[e] = g.col_scale[col + e]; if (g.up_scale) us[e] = g.up_scale[col + e]; }
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int row = row0 + 32 * i + 8 * b + 4 * lh + (l32 & 3);
+            if (row >= g.M) continue;
+            f32x4 r;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float x = acc[i][0][4 * b + e] * gs[e], u = acc[i][1][4 * b + e] * us[e];
+                r[e] = (x / (1.0f + __expf(-x))) * u;
+            }
+            *(uint2*)((__hip_bfloat16*)g.C + (long long)row * g.ldc + col) = __builtin_bit_cast(uint2, __builtin_convertvector(r, bf16x4));
         }
 }
 
@@ -361,6 +421,18 @@ __device__ __forceinline__ bf16x8 read_frag32(const __hip_bfloat16* __restrict__
     return *(const bf16x8*)(t + row * FK + ((chunk ^ ((row >> 2) & 3)) * 8));
 }
 
+// half_n: of every 64 rows of the B tile the first 32 are rows n of B, the second 32 its rows half_n + n, so that a wavefront holds both factors of its
+// results.  Offsets from row n0 / 2; rows beyond the matrix are clamped (never stored).
+template <int LPW>
+__device__ __forceinline__ void gate_up_rows(const Args& g, int wave, int lane, int n0, unsigned (&offB)[LPW]) {
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int lrow = 16 * (wave * LPW + i) + (lane >> 2);              // row of the LDS tile
+        const int row = min(32 * (lrow >> 6) + (lrow & 31), g.half_n - 1 - n0 / 2) + (lrow & 32 ? g.half_n : 0);
+        offB[i] = (unsigned)(((long long)row * g.ldb + ((lane & 3) ^ ((lrow >> 2) & 3)) * 8) * 2);
+    }
+}
+
 // WAVES = 8: 512 threads, two wavefronts per SIMD, each owning 128 x 64 of the tile (128 accumulators, at most 256
 // registers).  With one wavefront per SIMD every cycle it spends issuing an LDS read or an LDS-direct load is a cycle
 // in which no MFMA is issued; with two, one wavefront's issue stalls fall into the shadow of the other's MFMAs.
@@ -425,6 +497,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     // (for a blocked operand m0 * lda is also the element offset of its block row m0 / 16)
     const char* Arow = (const char*)(A + (long long)m0 * g.lda);
     const char* Brow = (const char*)(B + (long long)n0 * g.ldb);
+    if (g.half_n) { Brow = (const char*)(B + (long long)(n0 / 2) * g.ldb); gate_up_rows<LPW>(g, wave, lane, n0, offB); }
     // byte offset along k of the next stage to be issued (stages are issued strictly in order), kept incrementally;
     // in a blocked operand 32 k are one block of 1 KB, not 64 bytes of a row
     long long koff_next = 2LL * kbeg; int kin_next = kbeg, term = 0;
@@ -549,7 +622,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
 #undef TB_INTERLEAVE_DS
 
     transpose_acc<TJ>(acc);
-    store_acc<TJ>(g, acc, m0 + __builtin_amdgcn_readfirstlane(wm), n0 + __builtin_amdgcn_readfirstlane(wn), z1 * g.sC1 + z2 * g.sC2);
+    const int r0 = m0 + __builtin_amdgcn_readfirstlane(wm), c0 = n0 + __builtin_amdgcn_readfirstlane(wn);
+    if (g.half_n) store_acc_gate_up(g, acc, r0, c0);
+    else if (g.col_scale || g.residual) store_acc_linear<TJ>(g, acc, r0, c0);
+    else store_acc<TJ>(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -862,13 +938,20 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
         attr_set = true;
     }
     const bool fast = (q.kseg > 0 ? q.kseg : q.K) % FK == 0 && q.K > 0;
+    if ((q.col_scale || q.residual || q.gate_up) &&
+        (!fast || q.c_dtype != TBOA_BF16 || q.accumulate || q.batch != 1 || q.nterms > 1 || q.kseg || q.alpha != 1.f ||
+         (q.flags & ~(TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) || (q.gate_up && (q.flags || q.residual))))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: a scaled result is the single bf16 result of one product of the dispatched LDS-direct kernel");
+    if (q.gate_up && (q.N % 64 || q.ldc % 4 || ((uintptr_t)q.C & 7) || 2LL * q.N * q.ldb >= (1LL << 32)))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: the gated product needs whole 32s of columns and its weights below 4 GiB");
     if ((q.flags & (TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) && !fast) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: blocked operands are read by the LDS-direct kernel only");
     Args a{};
     a.sched = nullptr; a.rounds = 0;
     a.M = q.M; a.N = q.N; a.K = q.K; a.alpha = q.alpha;
     a.A = q.A; a.lda = q.lda; a.B = q.B; a.ldb = q.ldb; a.C = q.C; a.ldc = q.ldc; a.C2 = q.C2; a.lo_scale = q.lo_scale;
     a.c_bf16 = (q.c_dtype == TBOA_BF16); a.accumulate = q.accumulate; a.flags = q.flags;
-    a.vec_c = q.ldc % 4 == 0 && q.strideC % 4 == 0 && q.strideC2 % 4 == 0 && ((uintptr_t)q.C & 15) == 0;
+    a.col_scale = q.col_scale; a.residual = q.residual; a.up_scale = q.up_scale; a.half_n = q.gate_up ? q.N / 2 : 0;
+    a.vec_c = ((uintptr_t)q.residual & 7) == 0 && q.ldc % 4 == 0 && q.strideC % 4 == 0 && q.strideC2 % 4 == 0 && ((uintptr_t)q.C & 15) == 0;
     a.batch_inner = q.batch_inner > 0 ? q.batch_inner : 1;
     a.kseg = q.kseg;
     if (q.kseg < 0 || (q.kseg > 0 && (q.K % q.kseg || q.kseg % 8))) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: kseg must divide K and be a multiple of 8");

@@ -131,6 +131,11 @@ struct GemmBf16 {
     // dispatched kernel: the sum of the terms before the last is multiplied by this power of two when the last term begins (low parts stored with a
     // factor of their own go first)
     float last_scale = 1.f;
+    // dispatched LDS-direct kernel, a single bf16 result: C = round(A B^T * col_scale[column] + residual) (each or NULL; residual laid out as C)
+    const float* col_scale = nullptr; const __hip_bfloat16* residual = nullptr;
+    // B holds gate rows, then as many up rows (N = 2 N', N' a multiple of 32, all of B below 4 GiB); the result has N' columns:
+    // C = round(silu(A B_gate^T * col_scale) * (A B_up^T * up_scale))
+    bool gate_up = false; const float* up_scale = nullptr;
     // dispatched kernel: device array, one int per batch entry: only its first min(segs, nterms) terms are taken; K is then the length of
     // ONE term and the flops counted are those of one
     const int* segs = nullptr;
