@@ -15,6 +15,7 @@
  *     context: one workspace, grown on demand (a growth frees and reallocates it after synchronising the stream) and
  *     released by tboa_destroy.  tboa_hessian_workspace_bytes / tboa_quantize_workspace_bytes tell what a call will need
  *     and tboa_reserve_workspace obtains it ahead, so that no call allocates afterwards.
+ *     A context also holds 64 MiB from tboa_create on, for the partial sums of fp64 products.
  *   - Matrices are dense row-major.  Activations are token-major: X[t, c] is channel c of token t, so the
  *     paper's X (channels x tokens) is the transpose and H_in = X X^T = sum_t x_t x_t^T.
  *     Weights are [out-channels, in-channels]; head h of a projection owns rows h*d_h .. (h+1)*d_h-1.
