@@ -162,6 +162,7 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
+constexpr int GRID_DELTA_BITS = 4;  // from here on the left operand is delta as a pair, below it the integer codes (see grid_codes_kernel)
 constexpr double GRID_ONE_TERM = 0.03;      // |H off the diagonal|_F <= this times tr H: one half term of T is enough
 constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
@@ -300,10 +301,11 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict
 // qbar'[(row, k), c] = (clamp(round(w_c / s_k) + z_k) - z_k) up[c].  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so
 // wherever it is further than 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
 // A wavefront makes whole 16 x 32 blocks: lane = (row of the block lane / 4, eight columns of lane % 4).
-// DELTA (8-bit grids): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
+// DELTA (grids of 4 bits and more): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
 // elements further on.  With 256 levels s qbar and w agree to 1e-2 and their products with T, formed in fp32, would be subtracted:
-// deviations of 5e-4 on correlated channels, against 3e-6 this way; for 16 levels and less the subtraction leaves 5e-5 and the
-// exact operand saves the second product.
+// deviations of 5e-4 on correlated channels, against 3e-6 this way.  With 16 levels the subtraction left 5e-5 on the correlated
+// inputs of the tests, but 5.4e-4 on the Hessian of a 7B down projection (d_in 11008, rows of silu(gate) up with outlier tokens), and the
+// whole search was repeated with exact costs (0.94 s); with 8 levels and less it leaves 5e-5 at the most and the exact operand saves the second product.
 template <bool DELTA>
 __global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, int rows, float maxq,
                                                          GridRows m, GridScale g, const double* __restrict__ cand_s, const double* __restrict__ cand_z,
@@ -918,7 +920,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             const unsigned rb = (unsigned)(((long long)m.per * ncand + 63) / 64);
             // (columns in up to 8 parts where there are few rows)
             const unsigned cparts = (long long)rb * mats >= 2048 ? 1u : (unsigned)std::min<long long>(8, 2048 / ((long long)rb * mats) + 1);
-            const bool delta = L.d->bits == 8;
+            const bool delta = L.d->bits >= GRID_DELTA_BITS;
             const long long lo_off = (long long)mats * m.mat_rows * (np + GRID_PAD);
             if (delta)
                 hipLaunchKernelGGL(grid_codes_kernel<true>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
@@ -1367,7 +1369,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     size_t delta_bytes = (size_t)L.grid_chunk * unit_rows * L.ncand * L.gsz * sizeof(double), g_bytes = delta_bytes;
     if (L.fast_grid) {
         const size_t np = grid_width(n), mrows = (L.nhin > 1 ? (size_t)L.fast_chunk : 1) * grid_mat_rows(L.nhin > 1 ? unit_rows : (long long)grows, L.ncand);
-        delta_bytes = std::max(delta_bytes, (d->bits == 8 ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
+        delta_bytes = std::max(delta_bytes, (d->bits >= GRID_DELTA_BITS ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
     }
     const int fmax = n > dh ? n : dh;
     const int fb = (L.nhin > nh) ? L.nhin : nh;
