@@ -16,9 +16,10 @@
 // both paths (segments k_hi, k_lo: 64 x d_h each) is copied global -> LDS block by block (a 16 x 32 block is 1 KB contiguous
 // in memory and lands as it is: its XOR-swizzled 16-byte pieces are what conflict-free fragment reads need), the copy of
 // the next tile running under the element-wise work on the current one.
-// With one score matrix only (attention forward, Hessians without the full-precision path) the second path's wavefronts and buffers take the next
-// 64 keys of the same matrix: a tile is 128 keys then, and the two halves' maxima and sums are merged like those of two key halves.  (Left idle
-// they were half of the wavefronts: 32 heads of 2048 tokens 343 -> 278 us.)
+// With one score matrix only (attention forward, Hessians without the full-precision path; TWO false) the second path's buffers take the next 64
+// keys of the same matrix, a tile is 128 keys then, and the wavefronts of both paths share its queries: each walks the two halves of the tile one
+// after the other for 32 queries instead of one half for 64, so that a query's maximum and sum go through the same keys in the same order, and
+// come out the same to the bit, as with two matrices.  (Left idle the second path's were half of the wavefronts.)
 // Pass 1 walks the key tiles up to the diagonal and leaves, per query, maximum and 1 / sum; pass 2 walks them again,
 // turns scores into probabilities, exchanges them through LDS (so that A - A~ can be formed and every thread ends up with
 // 16 consecutive queries of one key row), and writes whole 16-byte pieces of the blocked result; the key tiles between the
@@ -61,7 +62,7 @@ __device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, u
 // 2^x on the transcendental unit
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <int DH, bool ROWS>
+template <int DH, bool ROWS, bool TWO>
 __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restrict__ Qa, const bf16* __restrict__ Ka, const bf16* __restrict__ Qb,
                                                            const bf16* __restrict__ Kb, int L, int nheads, int rep, int xcd_runs, float scale2,
                                                            PtOut out, long long ldp, long long group_stride, int f16, QkScale qs) {
@@ -90,14 +91,14 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     // work of one runs under the MFMAs of the other
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = wave >> 2, wi = (wave >> 1) & 1, th = wave & 1;
     const int l32 = lane & 31, lh = lane >> 5;
-    const bool two = Qb != nullptr;
     const long long mat = (long long)L * 3 * DH;
-    const bf16* K0 = Ka + g * mat; const bf16* K1 = two ? Kb + g * mat : K0 + 64LL * 3 * DH;     // one path: the next 64 keys (four block rows)
-    const int step = two ? 64 : 128, ko = two ? 0 : 64 * p;      // keys of a tile; first key of this wavefront's half of it
-    const int ps = two ? p : 0;                                  // score matrix of this wavefront
+    const bf16* K0 = Ka + g * mat; const bf16* K1 = TWO ? Kb + g * mat : K0 + 64LL * 3 * DH;     // one path: the next 64 keys (four block rows)
+    constexpr int step = TWO ? 64 : 128;                         // keys of a tile
+    constexpr int NQB = TWO ? 2 : 1;                             // 32-query blocks of a wavefront
+    const int ps = TWO ? p : 0;                                  // score matrix of this wavefront
     const int wave_s = __builtin_amdgcn_readfirstlane(wave);
     const unsigned kt_lds = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)kt);
-    const int tq = t0 + 64 * th;                 // first query of this wavefront
+    const int qo = 64 * th + (TWO ? 0 : 32 * p), tq = t0 + qo;   // first query of this wavefront, in the workgroup and in the sequence
     // encoding of this path's operands (uniform over the wavefront) and the scale that takes their powers of two back out
     bool half_ops = false;
     float sc2 = scale2;
@@ -110,11 +111,11 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     }
 
     // Q^ fragments of this wavefront's path: B operand of the MFMA (lane: query l32 of block tb, 8 contraction elements from 8 lh)
-    bf16x8 qh[2][NKS], ql[2][NKS];
+    bf16x8 qh[NQB][NKS], ql[NQB][NKS];
     {
         const bf16* Qp = (ps ? Qb : Qa) + h * mat;
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < NQB; ++tb)
 #pragma unroll
             for (int ks = 0; ks < NKS; ++ks) {
                 const int t = tq + 32 * tb + l32, c = 16 * ks + 8 * lh;
@@ -134,33 +135,38 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
             lds_direct_16((unsigned)lane * 16u, (const char*)src, kt_lds + (unsigned)b * 1024u);
         }
     };
-    // S^T of the tile for this wavefront: acc[tb][4 b + j] = q . k of (key i0 + ko + 32 wi + 8 b + 4 lh + j, query tq + 32 tb + l32)
+    // S^T of the tile for this wavefront, two blocks u of 32 keys x 32 queries: query block u of the one half of the keys, or (one path) the one
+    // query block against key half u.  With tb = TWO ? u : 0 and kb = TWO ? 0 : 64 u
+    //     acc[u][4 b + j] = q . k of (key i0 + kb + 32 wi + 8 b + 4 lh + j, query tq + 32 tb + l32)
     const f32x16 zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     f32x16 acc[2];
     auto multiply = [&]() {
         acc[0] = zero16; acc[1] = zero16;
         const int row = 32 * wi + l32;
-        const unsigned char* kh_img = kt + (p * 2 + 0) * SEGB + row * 64;
+        const unsigned char* kh_img = kt + (TWO ? p * 2 * SEGB : 0) + row * 64;
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             const int c8 = 2 * ks + lh;                                   // 8-element piece of the segment
             const int off = (c8 >> 2) * 4096 + (((c8 & 3) ^ ((row >> 2) & 3)) << 4);
-            const bf16x8 kh = *(const bf16x8*)(kh_img + off), kl = *(const bf16x8*)(kh_img + SEGB + off);
-            if (half_ops) {
-                const f16x8 fkh = __builtin_bit_cast(f16x8, kh), fkl = __builtin_bit_cast(f16x8, kl);
+            bf16x8 kh[3 - NQB], kl[3 - NQB];                              // (one image, or both halves')
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    const f16x8 fqh = __builtin_bit_cast(f16x8, qh[tb][ks]), fql = __builtin_bit_cast(f16x8, ql[tb][ks]);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkh, fqh, acc[tb], 0, 0, 0);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkh, fql, acc[tb], 0, 0, 0);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkl, fqh, acc[tb], 0, 0, 0);
+            for (int v = 0; v < 3 - NQB; ++v) { kh[v] = *(const bf16x8*)(kh_img + 2 * v * SEGB + off); kl[v] = *(const bf16x8*)(kh_img + (2 * v + 1) * SEGB + off); }
+            if (half_ops) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const f16x8 fkh = __builtin_bit_cast(f16x8, kh[TWO ? 0 : u]), fkl = __builtin_bit_cast(f16x8, kl[TWO ? 0 : u]);
+                    const f16x8 fqh = __builtin_bit_cast(f16x8, qh[TWO ? u : 0][ks]), fql = __builtin_bit_cast(f16x8, ql[TWO ? u : 0][ks]);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkh, fqh, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkh, fql, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fkl, fqh, acc[u], 0, 0, 0);
                 }
             } else {
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, qh[tb][ks], acc[tb], 0, 0, 0);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kh, ql[tb][ks], acc[tb], 0, 0, 0);
-                    acc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kl, qh[tb][ks], acc[tb], 0, 0, 0);
+                for (int u = 0; u < 2; ++u) {
+                    const bf16x8 xh = kh[TWO ? 0 : u], xl = kl[TWO ? 0 : u], yh = qh[TWO ? u : 0][ks], yl = ql[TWO ? u : 0][ks];
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, yh, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xh, yl, acc[u], 0, 0, 0);
+                    acc[u] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xl, yh, acc[u], 0, 0, 0);
                 }
             }
         }
@@ -172,94 +178,79 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     // Scores are kept in units of log 2: v = (q . k) sc2 with sc2 = log2(e) / sqrt(d_h) (over the operands' powers of two),
     // probabilities 2^(v - max) / sum.
     // ---- pass 1: maximum and sum per query, over this wavefront's keys
-    float m[2] = {-INFINITY, -INFINITY}, s[2] = {0.f, 0.f};
+    float m[NQB], s[NQB];
+#pragma unroll
+    for (int tb = 0; tb < NQB; ++tb) { m[tb] = -INFINITY; s[tb] = 0.f; }
     issue(0);
     landed();
     for (int it = 0; it < live; ++it) {
         multiply();
         __syncthreads();                                   // every wavefront has read the tile
         if (it + 1 < live) issue(step * (it + 1));         // the next one lands under the element-wise work below
-        {
-            const int ib = step * it + ko + 32 * wi + 4 * lh;
-            const bool masked = step * it + ko + 63 > tq;         // a tile that reaches beyond the first query of this wavefront
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb) {
-                const int t = tq + 32 * tb + l32;
-                float vm = -INFINITY;
+        for (int u = 0; u < 2; ++u) {
+            const int tb = TWO ? u : 0, k0 = step * it + (TWO ? 0 : 64 * u), ib = k0 + 32 * wi + 4 * lh;
+            const bool masked = k0 + 63 > tq;              // keys that reach beyond the first query of this wavefront
+            const int t = tq + 32 * tb + l32;
+            float vm = -INFINITY;
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    acc[tb][e] *= sc2;
-                    if (masked && ib + 8 * (e >> 2) + (e & 3) > t) acc[tb][e] = -INFINITY;
-                    vm = fmaxf(vm, acc[tb][e]);
-                }
-                if (vm > m[tb]) { s[tb] *= ex2(m[tb] - vm); m[tb] = vm; }
-                if (m[tb] != -INFINITY) {
+            for (int e = 0; e < 16; ++e) {
+                acc[u][e] *= sc2;
+                if (masked && ib + 8 * (e >> 2) + (e & 3) > t) acc[u][e] = -INFINITY;
+                vm = fmaxf(vm, acc[u][e]);
+            }
+            if (vm > m[tb]) { s[tb] *= ex2(m[tb] - vm); m[tb] = vm; }
+            if (m[tb] != -INFINITY) {
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) s[tb] += ex2(acc[tb][e] - m[tb]);
-                }
+                for (int e = 0; e < 16; ++e) s[tb] += ex2(acc[u][e] - m[tb]);
             }
         }
         landed();
     }
-    {
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {       // the two lane halves hold different keys of the same query
-            const float m2 = __shfl_xor(m[tb], 32, 64), s2 = __shfl_xor(s[tb], 32, 64);
-            const float M = fmaxf(m[tb], m2);
-            const float sum = (m[tb] == -INFINITY ? 0.f : s[tb] * ex2(m[tb] - M)) + (m2 == -INFINITY ? 0.f : s2 * ex2(m2 - M));
-            const int tl = 64 * th + 32 * tb + l32;
-            if (lh == 0) { stat[((p * 2 + wi) * 2 + 0) * BT + tl] = M; stat[((p * 2 + wi) * 2 + 1) * BT + tl] = sum; }
-        }
+    for (int tb = 0; tb < NQB; ++tb) {         // the two lane halves hold different keys of the same query
+        const float m2 = __shfl_xor(m[tb], 32, 64), s2 = __shfl_xor(s[tb], 32, 64);
+        const float M = fmaxf(m[tb], m2);
+        const float sum = (m[tb] == -INFINITY ? 0.f : s[tb] * ex2(m[tb] - M)) + (m2 == -INFINITY ? 0.f : s2 * ex2(m2 - M));
+        const int tl = qo + 32 * tb + l32;
+        if (lh == 0) { stat[((ps * 2 + wi) * 2 + 0) * BT + tl] = M; stat[((ps * 2 + wi) * 2 + 1) * BT + tl] = sum; }
     }
     __syncthreads();
-    if (threadIdx.x < 2 * BT) {                // (one path: both halves of the threads merge all four parts)
+    if (threadIdx.x < (TWO ? 2 * BT : BT)) {
         const int pp = threadIdx.x / BT, tl = threadIdx.x % BT;
-        float M = -INFINITY, sum = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int part = two ? 2 * pp + (q & 1) : q;
-            if (two && q > 1) break;
-            const float mq = stat[(part * 2 + 0) * BT + tl], sq = stat[(part * 2 + 1) * BT + tl];
-            const float Mn = fmaxf(M, mq);
-            sum = (M == -INFINITY ? 0.f : sum * ex2(M - Mn)) + (mq == -INFINITY ? 0.f : sq * ex2(mq - Mn));
-            M = Mn;
-        }
+        const float ma = stat[((pp * 2 + 0) * 2 + 0) * BT + tl], sa = stat[((pp * 2 + 0) * 2 + 1) * BT + tl];
+        const float mb = stat[((pp * 2 + 1) * 2 + 0) * BT + tl], sb = stat[((pp * 2 + 1) * 2 + 1) * BT + tl];
+        const float M = fmaxf(ma, mb);
+        const float sum = (ma == -INFINITY ? 0.f : sa * ex2(ma - M)) + (mb == -INFINITY ? 0.f : sb * ex2(mb - M));
         fin[(pp * 2 + 0) * BT + tl] = M; fin[(pp * 2 + 1) * BT + tl] = 1.f / sum;
     }
     __syncthreads();
-    float M[2] = {0.f, 0.f}, inv[2] = {0.f, 0.f};
-    {
+    float M[NQB], inv[NQB];
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
-            const int tl = 64 * th + 32 * tb + l32;
-            M[tb] = fin[(p * 2 + 0) * BT + tl]; inv[tb] = fin[(p * 2 + 1) * BT + tl];
-        }
-    }
+    for (int tb = 0; tb < NQB; ++tb) { M[tb] = fin[(ps * 2 + 0) * BT + qo + 32 * tb + l32]; inv[tb] = fin[(ps * 2 + 1) * BT + qo + 32 * tb + l32]; }
     // ---- pass 2: probabilities, exchanged through LDS, written transposed.  As IEEE half they are written times 2^14
     // (ATTN_PROBS_HALF_SCALE): the lo half of a pair then stays a normal number down to probabilities of 2^-17, where unscaled it
     // would be subnormal below 2^-3 (an absolute error of 3e-8 on every entry); the products that read them take the factor out.
     const float osc = f16 ? ATTN_PROBS_HALF_SCALE : 1.f;
-    bf16* dst[4] = {out.hi + g * group_stride, out.lo ? out.lo + g * group_stride : nullptr, two ? out.dhi + g * group_stride : out.hi + g * group_stride,
-                    two ? out.dlo + g * group_stride : out.lo + g * group_stride};
+    bf16* dst[4] = {out.hi + g * group_stride, out.lo ? out.lo + g * group_stride : nullptr, TWO ? out.dhi + g * group_stride : out.hi + g * group_stride,
+                    TWO ? out.dlo + g * group_stride : out.lo + g * group_stride};
     issue(0);
     landed();
     for (int it = 0; it < tiles; ++it) {
         const int i0 = step * it;
         if (it < live) {
-            {
-                multiply();
-                const int il = 32 * wi + 4 * lh;
-                const bool masked = i0 + ko + 63 > tq;
+            multiply();
+            const int il = 32 * wi + 4 * lh;
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb) {
-                    const int t = tq + 32 * tb + l32;
+            for (int u = 0; u < 2; ++u) {
+                const int tb = TWO ? u : 0, kb = TWO ? 0 : 64 * u, t = tq + 32 * tb + l32;
+                const bool masked = i0 + kb + 63 > tq;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        const int row = il + 8 * (e >> 2) + (e & 3);
-                        float a = ex2(acc[tb][e] * sc2 - M[tb]) * inv[tb];
-                        if (masked && i0 + ko + row > t) a = 0.f;
-                        ex[(p * 64 + row) * EXP + 64 * th + 32 * tb + l32] = a;
-                    }
+                for (int e = 0; e < 16; ++e) {
+                    const int row = il + 8 * (e >> 2) + (e & 3);
+                    float a = ex2(acc[u][e] * sc2 - M[tb]) * inv[tb];
+                    if (masked && i0 + kb + row > t) a = 0.f;
+                    ex[((TWO ? p : u) * 64 + row) * EXP + qo + 32 * tb + l32] = a;
                 }
             }
             __syncthreads();                               // the tile has been read, its probabilities are in LDS
@@ -283,7 +274,7 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
                 bf16* ph = out.hi + h * group_stride;
                 const long long kb = ldp >> 5, tq3 = t0 + tq2, col = i0 + 8 * i8;
                 *(uint4*)(ph + tboa_blocked_offset(tq3, col, kb)) = hi.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + col, kb)) = lo.u;
-                const long long c2 = two ? 2LL * L + col : col + 64;      // the other path's segments, or the next 64 keys
+                const long long c2 = TWO ? 2LL * L + col : col + 64;      // the other path's segments, or the next 64 keys
                 *(uint4*)(ph + tboa_blocked_offset(tq3, c2, kb)) = h2.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + c2, kb)) = l2.u;
             }
         } else {
@@ -302,14 +293,14 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
                     }
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
-                        const float a = v[e] * osc, d = (two ? v[e] - w[e] : w[e]) * osc;
+                        const float a = v[e] * osc, d = (TWO ? v[e] - w[e] : w[e]) * osc;
                         hi.b[4 * q + e] = enc16(a, f16); lo.b[4 * q + e] = enc16(a - dec16(hi.b[4 * q + e], f16), f16);
                         dh.b[4 * q + e] = enc16(d, f16); dl.b[4 * q + e] = enc16(d - dec16(dh.b[4 * q + e], f16), f16);
                     }
                 }
                 const long long o = tboa_blocked_offset(i0 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
                 *(uint4*)(dst[0] + o) = hi.u; *(uint4*)(dst[1] + o) = lo.u;
-                const long long o2 = two ? o : tboa_blocked_offset(i0 + 64 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
+                const long long o2 = TWO ? o : tboa_blocked_offset(i0 + 64 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
                 *(uint4*)(dst[2] + o2) = dh.u; *(uint4*)(dst[3] + o2) = dl.u;
             }
         }
@@ -317,30 +308,30 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     }
 }
 
-template <int DH, bool ROWS>
+template <int DH, bool ROWS, bool TWO>
 int launch(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, PtOut out, long long ldp,
            long long group_stride, int f16, QkScale qs) {
     static bool attr_set = false;
     constexpr int smem = attn_lds_bytes<DH>();
     if (!attr_set) {
-        TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_probs_t_kernel<DH, ROWS>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_probs_t_kernel<DH, ROWS, TWO>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
     }
     const int total = Hq * (L / BT), xcd_runs = ((Hq / rep) % 8 == 0 && total % 8 == 0) ? 1 : 0;
-    hipLaunchKernelGGL((attn_probs_t_kernel<DH, ROWS>), dim3(total), dim3(512), smem, ctx->stream, Qa, Ka, Qb, Kb, L, Hq, rep, xcd_runs,
+    hipLaunchKernelGGL((attn_probs_t_kernel<DH, ROWS, TWO>), dim3(total), dim3(512), smem, ctx->stream, Qa, Ka, Qb, Kb, L, Hq, rep, xcd_runs,
                        (float)(1.4426950408889634 / sqrt((double)DH)), out, ldp, group_stride, f16, qs);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
 
-template <bool ROWS>
+template <bool ROWS, bool TWO>
 int dispatch(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, int dh, PtOut out,
              long long ldp, long long group_stride, int f16, QkScale qs) {
     switch (dh) {
-        case 32: return launch<32, ROWS>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        case 64: return launch<64, ROWS>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        case 96: return launch<96, ROWS>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        default: return launch<128, ROWS>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 32: return launch<32, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 64: return launch<64, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 96: return launch<96, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        default: return launch<128, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
     }
 }
 
@@ -354,7 +345,7 @@ int attn_probs_t(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, 
                  long long ldp, long long group_stride, int f16, QkScale qs) {
     if (!attn_probs_t_supported(L, dh) || Hq % rep || !Qa || !Ka || (Qb && !Kb) || !out.hi || !out.lo || (Qb && (!out.dhi || !out.dlo)) || ldp % 32)
         return tboa_fail(ctx, TBOA_EINVAL, "attn_probs_t: unsupported shape or missing buffer");
-    return dispatch<false>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, group_stride, f16, qs);
+    return (Qb ? dispatch<false, true> : dispatch<false, false>)(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, group_stride, f16, qs);
 }
 
 int attn_probs_rows(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, int dh, bf16* P,
@@ -362,5 +353,5 @@ int attn_probs_rows(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Q
     if (!attn_probs_t_supported(L, dh) || Hq % rep || !Qa || !Ka || (Qb && !Kb) || !P || ldp % 32 || ldp < (Qb ? 4LL : 2LL) * L || ((uintptr_t)P & 15))
         return tboa_fail(ctx, TBOA_EINVAL, "attn_probs_rows: unsupported shape or missing buffer");
     PtOut out{P, nullptr, nullptr, nullptr};
-    return dispatch<true>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, (long long)L * ldp, f16, qs);
+    return (Qb ? dispatch<true, true> : dispatch<true, false>)(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, (long long)L * ldp, f16, qs);
 }
