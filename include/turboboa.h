@@ -278,7 +278,9 @@ size_t tboa_chol_inv_upper_static_max_elems(void);
 int tboa_chol_inv_upper_static(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* U);
 
 /* C[b] = alpha * A[b] B[b] + beta * C[b] in fp64 on the fp64 matrix cores.
- * A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn]; in each pair one stride must be 1. C row-major, ldc. */
+ * A(m,k) = A[m*sam + k*sak], B(k,n) = B[k*sbk + n*sbn]; in each pair one stride must be 1. C row-major, ldc.
+ * C may share memory with A or B (the operands count as they were before the call) while batch * M * N <= 2^22; a larger C only
+ * as A itself in the same layout with N <= 128. */
 int tboa_gemm_f64(tboa_ctx* ctx, int M, int N, int K, double alpha,
                   const double* A, int64_t sam, int64_t sak, const double* B, int64_t sbk, int64_t sbn,
                   double beta, double* C, int64_t ldc,

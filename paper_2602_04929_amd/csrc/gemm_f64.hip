@@ -285,18 +285,19 @@ constexpr double STEP_US[4] = {2.1, 0.78, 0.32, 0.8};
 
 // Tile shape and number of splits of least modelled time: rounds of 256 workgroups, each of the contraction's steps, plus the
 // second kernel and the traffic of the parts when there is a split.
-Choice choose(const GemmF64& q, bool akc, size_t part_elems, int sum) {
+// own_rows: C takes A's place, row for row: a workgroup reads all of the rows that it writes and no others, with one column of tiles.
+// always_parts: the result goes through the parts whatever the split.
+Choice choose(const GemmF64& q, bool akc, size_t part_elems, bool always_parts, bool own_rows) {
     const double k16 = std::max(1.0, q.K / 16.0 * (q.A2 ? 2.0 : q.sym ? 0.5 : 1.0));
-    const bool in_place = q.C == q.A || q.C == q.B;               // needs whole rows per workgroup: one column of tiles, no other order
-    const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.sym || in_place;
+    const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.sym || own_rows;
     Choice best{S128, 1}; double best_us = 1e30;
     for (int s = 0; s < 4; ++s) {
         if (s == SKINNY && !(q.M <= 32 && akc)) continue;
-        if (in_place && cdiv64(q.N, TILE_N[s]) > 1 && s != S128) continue;
+        if (own_rows && q.N > TILE_N[s]) continue;
         const double tiles = (double)cdiv64(q.M, TILE_M[s]) * cdiv64(q.N, TILE_N[s]) * q.batch;
         for (int sp = 1; sp <= (no_split ? 1 : 64); sp *= 2) {
             if (sp > 1 && (q.K / TILE_K[s] < 2 * sp || tiles * sp > 1024)) break;
-            const bool parts = sp > 1 || sum > 1;
+            const bool parts = sp > 1 || always_parts;
             if (parts && (double)q.M * q.N * q.batch * sp > (double)part_elems) break;
             double us = ceil(tiles * sp / 256.0) * (k16 / sp * STEP_US[s] + 2.0);
             if (parts) us += 5.0 + (double)q.M * q.N * q.batch * sp * 16.0 / 3e6;
@@ -305,6 +306,15 @@ Choice choose(const GemmF64& q, bool akc, size_t part_elems, int sum) {
     }
     return best;
 }
+
+// [first, last] element of an operand of n1 x n2 elements, strides s1 and s2, in b1 x b2 batch entries, strides t1 and t2
+struct Span { const double *lo, *hi; };
+Span span_of(const double* p, long long n1, long long s1, long long n2, long long s2, long long b1, long long t1, long long b2, long long t2) {
+    Span e{p, p};
+    for (long long d : {(n1 - 1) * s1, (n2 - 1) * s2, (b1 - 1) * t1, (b2 - 1) * t2}) (d < 0 ? e.lo : e.hi) += d;
+    return e;
+}
+bool meet(Span a, Span b) { return a.lo <= b.hi && b.lo <= a.hi; }
 
 template <int TM, int TN, int BK>
 void launch(tboa_ctx* ctx, dim3 grid, bool akc, bool bkc, const Args& a, bool vecA, bool vecB) {
@@ -353,7 +363,13 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
         }
         return 0;
     }
-    const Choice ch = choose(q, akc, part ? TB_SPLITK_ELEMS : 0, sum);
+    // C over an operand: row for row over A with at most 128 columns any shape of one column of tiles does; otherwise workgroups would overwrite
+    // what others have yet to read, and the result goes through the parts; where it does not fit them, as one tile does it (128 x 128, no split)
+    const bool over_a = q.over_a || q.C == q.A, over_b = q.over_b || q.C == q.B;
+    const bool own_rows = !over_b && q.C == q.A && akc && q.sam == q.ldc && q.K <= q.ldc && q.N <= TILE_N[S128] && q.strideA == q.strideC && q.strideA2 == q.strideC2;
+    const bool shared = over_b || (over_a && !own_rows), detour = shared && part && (size_t)q.M * q.N * q.batch <= TB_SPLITK_ELEMS &&
+                                                                  !(q.skip_lower || q.skip_upper || q.m_limit);
+    const Choice ch = shared && !detour ? Choice{S128, 1} : choose(q, akc, part ? TB_SPLITK_ELEMS : 0, sum > 1 || detour, own_rows);
     const int tm = TILE_M[ch.shape], tn = TILE_N[ch.shape];
     // algorithmic flops of a tagged launch: 2 M N K per batch entry over the contraction range each output tile really has;
     // a launch whose row count comes from device memory (m_limit) is timed but not counted
@@ -375,7 +391,7 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
         TB_TRY(prof_begin(ctx, q.tag, 2.0 * macs * q.batch, rec, timed));
     }
     a.splits = ch.splits;
-    a.part = (ch.splits > 1 || sum > 1) ? part : nullptr;
+    a.part = (ch.splits > 1 || sum > 1 || detour) ? part : nullptr;
     dim3 grid((unsigned)cdiv64(q.N, tn), (unsigned)cdiv64(q.M, tm), (unsigned)(q.batch * ch.splits));
     if (grid.y > 65535 || cdiv64(q.batch, 1) * ch.splits > 65535) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: grid too large");
     switch (ch.shape) {
@@ -406,5 +422,10 @@ extern "C" int tboa_gemm_f64(tboa_ctx* ctx, int M, int N, int K, double alpha,
     g.M = M; g.N = N; g.K = K; g.alpha = alpha; g.beta = beta;
     g.A = A; g.sam = sam; g.sak = sak; g.B = B; g.sbk = sbk; g.sbn = sbn;
     g.C = C; g.ldc = ldc; g.batch = batch; g.strideA = strideA; g.strideB = strideB; g.strideC = strideC;
+    if (A && B && C && M > 0 && N > 0 && K > 0 && batch > 0) {
+        const Span c = span_of(C, M, ldc, N, 1, batch, strideC, 1, 0);
+        g.over_a = meet(c, span_of(A, M, sam, K, sak, batch, strideA, 1, 0));
+        g.over_b = meet(c, span_of(B, K, sbk, N, sbn, batch, strideB, 1, 0));
+    }
     return gemm_f64(ctx, g);
 }

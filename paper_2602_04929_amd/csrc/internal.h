@@ -102,6 +102,7 @@ struct GemmF64 {
     // (T + T^T = 2 B): half the work where C only goes into symmetric forms, A B A'^T = (C A'^T + A C'^T) / 2 with C' = A' T.  The tile
     // width is the launch's own: two launches of the same shape (M, N, batch) have the same T.
     int sym = 0;
+    int over_a = 0, over_b = 0;      // C may share memory with A / with B (C == A and C == B are seen without)
     int sum_inner = 0;   // C[outer] = alpha * sum over the batch_inner entries of A B + beta * C[outer] (strideC2 unused)
     int tag = -1;   // tboa_prof_tag of this launch (timed with HIP events when profiling is on)
 };

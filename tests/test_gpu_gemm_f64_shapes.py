@@ -49,3 +49,56 @@ def test_hout_sums_the_heads_of_a_group(lib, rep, dh, d):
     want = np.stack([sum(W64[g, r] @ H.astype(np.float64) @ W64[g, r].T for r in range(rep)) for g in range(nh)])
     assert np.abs(got - want).max() <= 2.0 ** -23 * np.abs(want).max()      # the rounding of the fp32 result
     ctx.close()
+
+
+# (M, N, K): one 128 x 128 tile that smaller shapes would cut into several rows or columns, and several such tiles
+@pytest.mark.parametrize("M,N,K", [(64, 20, 64), (128, 64, 128), (128, 128, 128), (200, 200, 200), (300, 20, 300), (20, 300, 20), (1, 1, 1), (33, 65, 40)])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_result_over_an_operand(lib, M, N, K, ta, tb):
+    """C in the place of A, of B, of both, and in a buffer that begins inside an operand: the product of the operands as they were."""
+    rng = np.random.default_rng(M * 31 + N * 17 + K)
+    a, b = rng.standard_normal((K, M) if ta else (M, K)), rng.standard_normal((N, K) if tb else (K, N))
+    want = (a.T if ta else a) @ (b.T if tb else b)
+    tol = 1e-13 * np.linalg.norm(want)
+    ctx = lib.Context()
+    buf = torch.empty(max(M * K, K * N) + M * N, dtype=torch.float64, device="cuda")
+
+    def run(over, at):
+        A, B = torch.from_numpy(a).cuda(), torch.from_numpy(b).cuda()
+        op = A if over == "A" else B
+        o = buf[:op.numel()].view(op.shape); o.copy_(op)
+        C = buf[at:at + M * N].view(M, N)
+        ctx.gemm_f64(o if over == "A" else A, o if over == "B" else B, C, transA=bool(ta), transB=bool(tb))
+        assert np.linalg.norm(C.cpu().numpy() - want) <= tol, (over, at)
+    for over, size in (("A", M * K), ("B", K * N)):
+        run(over, 0)
+        run(over, size // 3)
+    ctx.close()
+
+
+@pytest.mark.parametrize("bs,n", [(3, 40), (2, 150)])
+def test_batched_result_over_an_operand(lib, bs, n):
+    rng = np.random.default_rng(n)
+    a, b = rng.standard_normal((bs, n, n)), rng.standard_normal((bs, n, n))
+    ctx = lib.Context()
+    for over in (0, 1):
+        for beta in (0.0, 0.5):
+            ops = [torch.from_numpy(x).cuda() for x in (a, b)]
+            ctx.gemm_f64(ops[0], ops[1], ops[over], alpha=2.0, beta=beta)
+            want = 2.0 * a @ b + beta * (a, b)[over]
+            assert np.linalg.norm(ops[over].cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
+    sq = torch.from_numpy(a).cuda()
+    ctx.gemm_f64(sq, sq, sq)
+    assert np.linalg.norm(sq.cpu().numpy() - a @ a) <= 1e-13 * np.linalg.norm(a @ a)
+    ctx.close()
+
+
+def test_tall_result_in_the_place_of_A(lib):
+    """More elements than the parts hold, row for row over A: the rows' own workgroups, bits as in a buffer of its own."""
+    g = torch.Generator(device="cuda"); g.manual_seed(1)
+    A = torch.randn(40000, 128, dtype=torch.float64, device="cuda", generator=g); B = torch.randn(128, 128, dtype=torch.float64, device="cuda", generator=g)
+    ctx = lib.Context()
+    want = ctx.gemm_f64(A, B)
+    ctx.gemm_f64(A, B, A)
+    assert torch.equal(A, want)
+    ctx.close()
