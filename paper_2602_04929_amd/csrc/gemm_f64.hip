@@ -294,6 +294,7 @@ Choice choose(const GemmF64& q, bool akc, size_t part_elems, bool always_parts, 
     for (int s = 0; s < 4; ++s) {
         if (s == SKINNY && !(q.M <= 32 && akc)) continue;
         if (own_rows && q.N > TILE_N[s]) continue;
+        if (s != S128 && cdiv64(q.M, TILE_M[s]) > 65535) continue;      // rows of tiles that a launch can have
         const double tiles = (double)cdiv64(q.M, TILE_M[s]) * cdiv64(q.N, TILE_N[s]) * q.batch;
         for (int sp = 1; sp <= (no_split ? 1 : 64); sp *= 2) {
             if (sp > 1 && (q.K / TILE_K[s] < 2 * sp || tiles * sp > 1024)) break;

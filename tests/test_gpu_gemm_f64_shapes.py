@@ -102,3 +102,16 @@ def test_tall_result_in_the_place_of_A(lib):
     ctx.gemm_f64(A, B, A)
     assert torch.equal(A, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(65535 * 32 + 1, 3, 256), (65535 * 64 + 5, 40, 80)])
+def test_more_rows_than_small_tiles_can_have(lib, M, N, K):
+    """A launch has at most 65535 rows of tiles: from there on the tile must be the one of 128 rows."""
+    g = torch.Generator(device="cuda"); g.manual_seed(N)
+    A = torch.randn(M, K, dtype=torch.float64, device="cuda", generator=g); B = torch.randn(K, N, dtype=torch.float64, device="cuda", generator=g)
+    ctx = lib.Context()
+    got = ctx.gemm_f64(A, B)
+    for rows in (slice(0, 1000), slice(M // 2, M // 2 + 1000), slice(M - 1000, M)):
+        want = A[rows].cpu().numpy() @ B.cpu().numpy()
+        assert np.linalg.norm(got[rows].cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
+    ctx.close()
