@@ -355,7 +355,7 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
     const bool vecA = ((uintptr_t)q.A % 16 == 0) && ((uintptr_t)q.A2 % 16 == 0) && (q.strideA % 2 == 0) && (q.strideA2 % 2 == 0) && ((akc ? q.sam : q.sak) % 2 == 0);
     const bool vecB = ((uintptr_t)q.B % 16 == 0) && ((uintptr_t)q.B2 % 16 == 0) && (q.strideB % 2 == 0) && (q.strideB2 % 2 == 0) && ((bkc ? q.sbn : q.sbk) % 2 == 0);
     double* part = ctx->splitk[ctx->stream == ctx->aux ? 1 : 0];
-    if (sum > 1 && (!part || (size_t)q.M * q.N * q.batch > TB_SPLITK_ELEMS)) {      // the terms one after the other
+    if (sum > 1 && (!part || (size_t)q.M * q.N * q.batch > TB_SPLITK_ELEMS || q.batch > 65535)) {      // the terms one after the other
         GemmF64 one = q;
         one.sum_inner = 0; one.batch = q.batch / a.batch_inner; one.batch_inner = 1;
         for (int r = 0; r < a.batch_inner; ++r) {

@@ -114,17 +114,22 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
         TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xf64, dm, 1, Wk64, 1, dm, 0.0, Kf, dkv)));
     }
     // H_out of W_Q,h: K_g^T K_g ; of W_K,g: sum_h Q_h^T Q_h ; of W_V,g: sum_h W_out,h^T W_out,h
-    {
-        const long long hh = (long long)dh * dh;
-        GemmF64 q = mk(dh, dh, T, 1.0, Ka, 1, dkv, Ka, dkv, 1, 0.0, Hoq, dh);
-        q.batch = Hq; q.batch_inner = a.rep; q.strideA = dh; q.strideB = dh; q.strideC = a.rep * hh; q.strideC2 = hh;
-        TB_TRY(gemm_f64(ctx, q));
-        GemmF64 k = mk(dh, dh, T, 1.0, Qa, 1, dq, Qa, dq, 1, 0.0, Hok, dh);
-        k.batch = Hq; k.batch_inner = a.rep; k.sum_inner = 1; k.strideA = (long long)a.rep * dh; k.strideB = k.strideA; k.strideA2 = dh; k.strideB2 = dh; k.strideC = hh;
+    // (a launch has at most 65535 batch entries: as many KV groups at a time as that allows)
+    const int per = std::max(1, std::min(Hkv, 65535 / a.rep)), rc = std::min(a.rep, 65535);
+    for (int g0 = 0; g0 < Hkv; g0 += per) {
+        const long long hh = (long long)dh * dh, h0 = (long long)g0 * a.rep;
+        const int gc = std::min(per, Hkv - g0);
+        GemmF64 q = mk(dh, dh, T, 1.0, Ka + (long long)g0 * dh, 1, dkv, Ka + (long long)g0 * dh, dkv, 1, 0.0, nullptr, dh);
+        q.strideA = dh; q.strideB = dh; q.strideC = a.rep * hh; q.strideC2 = hh;
+        for (int r0 = 0; r0 < a.rep; r0 += rc) {
+            q.batch_inner = std::min(rc, a.rep - r0); q.batch = gc * q.batch_inner; q.C = Hoq + (h0 + r0) * hh;
+            TB_TRY(gemm_f64(ctx, q));
+        }
+        GemmF64 k = mk(dh, dh, T, 1.0, Qa + h0 * dh, 1, dq, Qa + h0 * dh, dq, 1, 0.0, Hok + g0 * hh, dh);
+        k.batch = gc * a.rep; k.batch_inner = a.rep; k.sum_inner = 1; k.strideA = (long long)a.rep * dh; k.strideB = k.strideA; k.strideA2 = dh; k.strideB2 = dh; k.strideC = hh;
         TB_TRY(gemm_f64(ctx, k));
-        GemmF64 v = mk(dh, dh, dm, 1.0, Wo64, 1, dq, Wo64, dq, 1, 0.0, Hov, dh);
-        v.batch = Hq; v.batch_inner = a.rep; v.sum_inner = 1; v.strideA = k.strideA; v.strideB = k.strideA; v.strideA2 = dh; v.strideB2 = dh; v.strideC = hh;
-        TB_TRY(gemm_f64(ctx, v));
+        k.K = dm; k.A = Wo64 + h0 * dh; k.B = k.A; k.C = Hov + g0 * hh;
+        TB_TRY(gemm_f64(ctx, k));
     }
     // H_in of W_V,g: sum over heads of the group and sequences of (A_h X_s)^T (A_h X_s)
     const long long LL = (long long)L * L, Ld = (long long)L * dm, dd = (long long)dm * dm;

@@ -68,3 +68,21 @@ def test_compensation_after_a_block(lib, dh, block):
     ref = O.quantize_layer(W.astype(np.float64), H.astype(np.float64), Ho.astype(np.float64), None, 1, bits=3, block=block, cd_iters=0)
     compare_layer(got, ref, rtol=1e-6)
     ctx.close()
+
+
+def test_more_heads_than_a_launch_has_batch_entries(lib):
+    hq, hkv, L, d = 65600, 16400, 2, 4
+    g = torch.Generator(device="cuda"); g.manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    X, Wq, Wk, Wv, Wo = rnd(1, L, d), rnd(hq, d), rnd(hkv, d), rnd(hkv, d), rnd(d, hq)
+    ctx = lib.Context()
+    got = ctx.build_hessians(X, None, Wq, Wk, Wv, Wo, hq, hkv, 1, causal=False)
+    x, wq, wk, wo = (t.to(F64) for t in (X[0], Wq, Wk, Wo))
+    k, q = x @ wk.T, x @ wq.T
+    A = torch.softmax(q.view(L, hkv, 4).permute(1, 2, 0)[..., None] * k.T[:, None, None, :], -1)      # [group, head, query, key]
+    Y = (A @ x).reshape(hkv, 4 * L, d)
+    want = dict(Hout_q=(k * k).sum(0).repeat_interleave(4), Hout_k=(q * q).sum(0).view(hkv, 4).sum(1), Hout_v=(wo * wo).sum(0).view(hkv, 4).sum(1),
+                Hin_v=(Y[..., :, None] * Y[..., None, :]).sum(1))
+    for name, w in want.items():
+        assert float((got[name].to(F64).view(w.shape) - w).abs().max() / w.abs().max()) <= 2.0 ** -23, name
+    ctx.close()

@@ -115,3 +115,18 @@ def test_more_rows_than_small_tiles_can_have(lib, M, N, K):
         want = A[rows].cpu().numpy() @ B.cpu().numpy()
         assert np.linalg.norm(got[rows].cpu().numpy() - want) <= 1e-13 * np.linalg.norm(want)
     ctx.close()
+
+
+def test_hout_sums_that_fit_no_launch_or_no_buffer(lib):
+    """More terms than a launch has batch entries, and partial products that do not fit their buffer (15 of 530 x 530): the terms one after the other."""
+    ctx = lib.Context()
+    for nh, rep, dh, d in ((16384, 8, 1, 4), (3, 5, 530, 40)):
+        g = torch.Generator(device="cuda"); g.manual_seed(rep)
+        X = torch.randn(2 * d, d, dtype=torch.float64, device="cuda", generator=g); H = (X.T @ X).float()
+        W = 0.02 * torch.randn(nh * rep * dh, d, device="cuda", generator=g)
+        got = ctx.build_hout(H, W, nh, rep, dh).double()
+        w = W.double().view(nh, rep * dh, d)
+        y = (w @ H.double()).view(nh, rep, dh, d)
+        want = torch.stack([y[:, r] @ w.view(nh, rep, dh, d)[:, r].transpose(1, 2).contiguous() for r in range(rep)]).sum(0)
+        assert float((got - want).abs().max()) <= 2.0 ** -23 * float(want.abs().max())      # the rounding of the fp32 result
+    ctx.close()
