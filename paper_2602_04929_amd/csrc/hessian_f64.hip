@@ -41,10 +41,11 @@ inline GemmF64 mk(int M, int N, int K, double alpha, const double* A, int64_t sa
     return g;
 }
 
-// Sequences and KV groups taken together: as many as keep the probabilities and `ny` [L, width] results per head within 1 GiB
+// Sequences and KV groups taken together: as many as keep the probabilities and two [L, width] results per head within 1 GiB.  The same for every
+// set of outputs (a build without the full-precision path needs one result only), so that no call needs more than the one that asks for everything.
 struct Chunk { int G, gc; };
-Chunk pick_chunk(const F64Attn& a, int width, int ny) {
-    const double per_group = (double)a.rep * a.L * (a.L + (double)ny * width) * 8.0, room = 1073741824.0;
+Chunk pick_chunk(const F64Attn& a, int width) {
+    const double per_group = (double)a.rep * a.L * (a.L + 2.0 * width) * 8.0, room = 1073741824.0;
     int gc = (int)std::min<double>(a.Hkv, std::max(1.0, floor(room / per_group)));
     int G = gc < a.Hkv ? 1 : (int)std::min<double>(a.S, std::max(1.0, floor(room / (per_group * a.Hkv))));
     if ((long long)G * gc > 32768) { G = 32768 / gc; if (G < 1) { G = 1; gc = 32768; } }
@@ -80,7 +81,7 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
     const int T = a.T, dm = a.dm, Hq = a.Hq, Hkv = a.Hkv, dh = a.dh, L = a.L, dq = a.dq, dkv = a.dkv;
     const bool fp = X_fp != nullptr;
     const bool rv = fp && R_v;
-    const Chunk ck = pick_chunk(a, dm, rv ? 2 : 1);
+    const Chunk ck = pick_chunk(a, dm);
     double *X64, *Xf64, *dX, *Wq64, *Wk64, *Wo64, *Qa, *Ka, *Qf, *Kf, *P, *Y, *Yf, *Hin, *Rq, *Hoq, *Hok, *Hiv, *Rv, *Hov;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
@@ -201,7 +202,7 @@ int build_hessian_out_proj_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const voi
               d->n_q_heads / d->n_kv_heads, d->n_q_heads * d->head_dim, d->n_kv_heads * d->head_dim};
     const int T = a.T, dm = a.dm, L = a.L, dq = a.dq, dkv = a.dkv;
     const bool fp = X_fp && R_o;
-    const Chunk ck = pick_chunk(a, 0, 0);
+    const Chunk ck = pick_chunk(a, 0);
     double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *P, *O, *Of, *H;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
@@ -238,7 +239,7 @@ int attention_forward_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const float* X
     F64Attn a{ctx, d, d->n_seqs * d->seq_len, d->d_model, d->n_q_heads, d->n_kv_heads, d->head_dim, d->seq_len, d->n_seqs,
               d->n_q_heads / d->n_kv_heads, d->n_q_heads * d->head_dim, d->n_kv_heads * d->head_dim};
     const int T = a.T, dm = a.dm, L = a.L, dq = a.dq, dkv = a.dkv;
-    const Chunk ck = pick_chunk(a, 0, 0);
+    const Chunk ck = pick_chunk(a, 0);
     double *X64, *Wq64, *Wk64, *Wv64, *Qa, *Ka, *Va, *P, *O64;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);

@@ -86,3 +86,20 @@ def test_more_heads_than_a_launch_has_batch_entries(lib):
     for name, w in want.items():
         assert float((got[name].to(F64).view(w.shape) - w).abs().max() / w.abs().max()) <= 2.0 ** -23, name
     ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("S,L,d,hq,hkv,dh", [(1, 2048, 1032, 16, 2, 64), (3, 40, 64, 4, 2, 32), (2, 256, 256, 4, 2, 32)])
+def test_reserved_workspace_is_enough_for_every_set_of_outputs(lib, S, L, d, hq, hkv, dh, dtype):
+    g = torch.Generator(device="cuda"); g.manual_seed(L)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dtype)
+    X, Xf, Wq, Wk, Wv, Wo = rnd(S, L, d), rnd(S, L, d), rnd(hq * dh, d), rnd(hkv * dh, d), rnd(hkv * dh, d), rnd(d, hq * dh)
+    ctx = lib.Context()
+    need = lib.Context.hessian_workspace_bytes(d, hq, hkv, dh, S, L, dtype)
+    ctx.reserve_workspace(need)
+    f = [w.float() for w in (Wq, Wk, Wv)]
+    for xf in (Xf, None):
+        ctx.build_hessians(X, xf, Wq, Wk, Wv, Wo, hq, hkv, dh, alpha=0.25)
+        ctx.build_hessian_out_proj(X, xf, *f, Wq, Wk, Wv, hq, hkv, dh, alpha=0.25)
+        assert ctx.workspace_bytes() == need
+    ctx.close()
