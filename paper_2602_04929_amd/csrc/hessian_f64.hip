@@ -41,30 +41,32 @@ inline GemmF64 mk(int M, int N, int K, double alpha, const double* A, int64_t sa
     return g;
 }
 
-// Sequences and KV groups taken together: as many as keep the probabilities and two [L, width] results per head within 1 GiB.  The same for every
-// set of outputs (a build without the full-precision path needs one result only), so that no call needs more than the one that asks for everything.
-struct Chunk { int G, gc; };
+// Sequences, KV groups and query heads of a group taken together: as many as keep the probabilities and two [L, width] results per head within
+// 1 GiB, but one head at least.  The same for every set of outputs (a build without the full-precision path needs one result only), so that no
+// call needs more than the one that asks for everything.
+struct Chunk { int G, gc, rc; };
 Chunk pick_chunk(const F64Attn& a, int width) {
-    const double per_group = (double)a.rep * a.L * (a.L + 2.0 * width) * 8.0, room = 1073741824.0;
-    int gc = (int)std::min<double>(a.Hkv, std::max(1.0, floor(room / per_group)));
+    const double per_head = (double)a.L * (a.L + 2.0 * width) * 8.0, per_group = a.rep * per_head, room = 1073741824.0;
+    if (per_group > room) return Chunk{1, 1, (int)std::min<double>(a.rep, std::max(1.0, floor(room / per_head)))};
+    int gc = (int)std::min<double>(a.Hkv, floor(room / per_group));
     int G = gc < a.Hkv ? 1 : (int)std::min<double>(a.S, std::max(1.0, floor(room / (per_group * a.Hkv))));
     if ((long long)G * gc > 32768) { G = 32768 / gc; if (G < 1) { G = 1; gc = 32768; } }
-    return Chunk{G, gc};
+    return Chunk{G, gc, a.rep};
 }
 
-// probabilities P[g][s][r][L, L] of the sequences s0 .. s0 + Gc - 1 and the KV groups g0 .. g0 + gc - 1 (query head g rep + r) from the projected
-// activations Qa [T, dq], Ka [T, dkv]
-int attn_probs(const F64Attn& a, const double* Qa, const double* Ka, int s0, int Gc, int g0, int gc, double* P) {
+// probabilities P[g][s][r][L, L] of the sequences s0 .. s0 + Gc - 1, the KV groups g0 .. g0 + gc - 1 and rc of their query heads (g rep + r0 + r)
+// from the projected activations Qa [T, dq], Ka [T, dkv]
+int attn_probs(const F64Attn& a, const double* Qa, const double* Ka, int s0, int Gc, int g0, int gc, int r0, int rc, double* P) {
     const long long L = a.L, LL = L * L;
-    for (int r = 0; r < a.rep; ++r) {
-        GemmF64 g = mk(a.L, a.L, a.dh, 1.0 / sqrt((double)a.dh), Qa + s0 * L * a.dq + ((long long)g0 * a.rep + r) * a.dh, a.dq, 1,
+    for (int r = 0; r < rc; ++r) {
+        GemmF64 g = mk(a.L, a.L, a.dh, 1.0 / sqrt((double)a.dh), Qa + s0 * L * a.dq + ((long long)g0 * a.rep + r0 + r) * a.dh, a.dq, 1,
                        Ka + s0 * L * a.dkv + (long long)g0 * a.dh, 1, a.dkv, 0.0, P + r * LL, L);
         g.batch = gc * Gc; g.batch_inner = Gc;
         g.strideA = (long long)a.rep * a.dh; g.strideA2 = L * a.dq; g.strideB = a.dh; g.strideB2 = L * a.dkv;
-        g.strideC = (long long)Gc * a.rep * LL; g.strideC2 = a.rep * LL;
+        g.strideC = (long long)Gc * rc * LL; g.strideC2 = rc * LL;
         TB_TRY(gemm_f64(a.ctx, g));
     }
-    const long long rows = (long long)gc * Gc * a.rep * L;
+    const long long rows = (long long)gc * Gc * rc * L;
     hipLaunchKernelGGL(softmax_f64_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, a.ctx->stream, P, rows, a.L, a.d->causal);
     TB_HIP(a.ctx, hipGetLastError());
     return 0;
@@ -89,7 +91,7 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wo64 = ar.get<double>((size_t)dm * dq);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv);
         Qf = rv ? ar.get<double>((size_t)T * dq) : nullptr; Kf = rv ? ar.get<double>((size_t)T * dkv) : nullptr;
-        const size_t mats = (size_t)ck.gc * ck.G * a.rep;
+        const size_t mats = (size_t)ck.gc * ck.G * ck.rc;
         P = ar.get<double>(mats * L * L); Y = ar.get<double>(mats * L * dm); Yf = rv ? ar.get<double>(mats * L * dm) : nullptr;
         Hin = ar.get<double>((size_t)dm * dm); Rq = fp ? ar.get<double>((size_t)dm * dm) : nullptr;
         Hoq = ar.get<double>((size_t)Hq * dh * dh); Hok = ar.get<double>((size_t)Hkv * dh * dh); Hov = ar.get<double>((size_t)Hkv * dh * dh);
@@ -135,26 +137,27 @@ int build_hessians_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const void* X, co
     // H_in of W_V,g: sum over heads of the group and sequences of (A_h X_s)^T (A_h X_s)
     const long long LL = (long long)L * L, Ld = (long long)L * dm, dd = (long long)dm * dm;
     for (int s0 = 0; s0 < a.S; s0 += ck.G)
-        for (int g0 = 0; g0 < Hkv; g0 += ck.gc) {
-            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, Hkv - g0);
-            const long long kk = (long long)Gc * a.rep * L;      // rows of Y of one KV group
+        for (int g0 = 0; g0 < Hkv; g0 += ck.gc)
+        for (int r0 = 0; r0 < a.rep; r0 += ck.rc) {
+            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, Hkv - g0), rc = std::min(ck.rc, a.rep - r0);
+            const long long kk = (long long)Gc * rc * L;         // rows of Y of one KV group
             auto outputs = [&](const double* X, double* out) -> int {      // Y[g][s][r] = A X_s
-                for (int r = 0; r < a.rep; ++r) {
+                for (int r = 0; r < rc; ++r) {
                     GemmF64 y = mk(L, dm, L, 1.0, P + r * LL, L, 1, X + s0 * Ld, dm, 1, 0.0, out + r * Ld, dm);
-                    y.batch = gc * Gc; y.batch_inner = Gc; y.strideA = Gc * a.rep * LL; y.strideA2 = a.rep * LL; y.strideB2 = Ld;
-                    y.strideC = Gc * a.rep * Ld; y.strideC2 = a.rep * Ld;
+                    y.batch = gc * Gc; y.batch_inner = Gc; y.strideA = Gc * rc * LL; y.strideA2 = rc * LL; y.strideB2 = Ld;
+                    y.strideC = Gc * rc * Ld; y.strideC2 = rc * Ld;
                     TB_TRY(gemm_f64(ctx, y));
                 }
                 return 0;
             };
             if (kk > 2147483647LL) return tboa_fail(ctx, TBOA_EINVAL, "build_hessians: a KV group's rows exceed the range of int");
-            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, P));
+            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, r0, rc, P));
             TB_TRY(outputs(X64, Y));
-            GemmF64 h = mk(dm, dm, (int)kk, 1.0, Y, 1, dm, Y, dm, 1, s0 ? 1.0 : 0.0, Hiv + g0 * dd, dm);
+            GemmF64 h = mk(dm, dm, (int)kk, 1.0, Y, 1, dm, Y, dm, 1, s0 || r0 ? 1.0 : 0.0, Hiv + g0 * dd, dm);
             h.batch = gc; h.strideA = kk * dm; h.strideB = h.strideA; h.strideC = dd;
             TB_TRY(gemm_f64(ctx, h));
             if (rv) {
-                TB_TRY(attn_probs(a, Qf, Kf, s0, Gc, g0, gc, P));
+                TB_TRY(attn_probs(a, Qf, Kf, s0, Gc, g0, gc, r0, rc, P));
                 TB_TRY(outputs(Xf64, Yf));
                 TB_TRY(launch_sub_f64(ctx, Y, Yf, Yf, gc * kk * dm));
                 h.A = Yf; h.alpha = d->alpha; h.C = Rv + g0 * dd;
@@ -181,13 +184,14 @@ static int attn_output_f64(const F64Attn& a, Chunk ck, const double* Xa, const d
     TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xa, dm, 1, Wk64, 1, dm, 0.0, Ka, dkv)));
     TB_TRY(gemm_f64(ctx, mk(T, dkv, dm, 1.0, Xa, dm, 1, Wv64, 1, dm, 0.0, Va, dkv)));
     for (int s0 = 0; s0 < a.S; s0 += ck.G)
-        for (int g0 = 0; g0 < a.Hkv; g0 += ck.gc) {
-            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, a.Hkv - g0);
-            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, P));
-            for (int r = 0; r < a.rep; ++r) {
+        for (int g0 = 0; g0 < a.Hkv; g0 += ck.gc)
+        for (int r0 = 0; r0 < a.rep; r0 += ck.rc) {
+            const int Gc = std::min(ck.G, a.S - s0), gc = std::min(ck.gc, a.Hkv - g0), rc = std::min(ck.rc, a.rep - r0);
+            TB_TRY(attn_probs(a, Qa, Ka, s0, Gc, g0, gc, r0, rc, P));
+            for (int r = 0; r < rc; ++r) {
                 GemmF64 o = mk(L, dh, L, 1.0, P + r * LL, L, 1, Va + (long long)s0 * L * dkv + (long long)g0 * dh, dkv, 1, 0.0,
-                               O + (long long)s0 * L * dq + ((long long)g0 * a.rep + r) * dh, dq);
-                o.batch = gc * Gc; o.batch_inner = Gc; o.strideA = Gc * a.rep * LL; o.strideA2 = a.rep * LL;
+                               O + (long long)s0 * L * dq + ((long long)g0 * a.rep + r0 + r) * dh, dq);
+                o.batch = gc * Gc; o.batch_inner = Gc; o.strideA = Gc * rc * LL; o.strideA2 = rc * LL;
                 o.strideB = dh; o.strideB2 = (long long)L * dkv; o.strideC = (long long)a.rep * dh; o.strideC2 = (long long)L * dq;
                 TB_TRY(gemm_f64(ctx, o));
             }
@@ -209,7 +213,7 @@ int build_hessian_out_proj_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const voi
         X64 = ar.get<double>((size_t)T * dm);
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wv64 = ar.get<double>((size_t)dkv * dm);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv); Va = ar.get<double>((size_t)T * dkv);
-        P = ar.get<double>((size_t)ck.gc * ck.G * a.rep * L * L);
+        P = ar.get<double>((size_t)ck.gc * ck.G * ck.rc * L * L);
         O = ar.get<double>((size_t)T * dq); Of = fp ? ar.get<double>((size_t)T * dq) : nullptr;
         H = ar.get<double>((size_t)dq * dq);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
@@ -246,7 +250,7 @@ int attention_forward_f64(tboa_ctx* ctx, const tboa_attn_desc* d, const float* X
         X64 = ar.get<double>((size_t)T * dm);
         Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm); Wv64 = ar.get<double>((size_t)dkv * dm);
         Qa = ar.get<double>((size_t)T * dq); Ka = ar.get<double>((size_t)T * dkv); Va = ar.get<double>((size_t)T * dkv);
-        P = ar.get<double>((size_t)ck.gc * ck.G * a.rep * L * L);
+        P = ar.get<double>((size_t)ck.gc * ck.G * ck.rc * L * L);
         O64 = ar.get<double>((size_t)T * dq);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }

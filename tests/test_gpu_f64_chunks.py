@@ -88,6 +88,16 @@ def test_more_heads_than_a_launch_has_batch_entries(lib):
     ctx.close()
 
 
+def test_f64_build_in_parts_of_a_group(lib):
+    """A KV group that 1 GiB does not hold (30 of its 40 heads at a time), and a workspace that does not grow with the heads of a group."""
+    test_f64_build_in_chunks(lib, 2, 2048, 64, 40, 1, 8, 1)
+    need = lib.Context.hessian_workspace_bytes(64, 40, 1, 8, 2, 2048, torch.float32)
+    assert need < 2 ** 30 + 2 ** 27
+    # heads too long for 1 GiB: one at a time, however many there are in a group (only the projections grow)
+    one, two = (lib.Context.hessian_workspace_bytes(64, hq, 1, 8, 1, 32768, torch.float32) for hq in (1, 2))
+    assert two - one < 2 ** 27
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("S,L,d,hq,hkv,dh", [(1, 2048, 1032, 16, 2, 64), (3, 40, 64, 4, 2, 32), (2, 256, 256, 4, 2, 32)])
 def test_reserved_workspace_is_enough_for_every_set_of_outputs(lib, S, L, d, hq, hkv, dh, dtype):
