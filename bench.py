@@ -288,7 +288,8 @@ def main():
         "losses": {k: out[k]["loss"] for k in ("q", "k", "v", "o")},
         "workspace_gib": sum(c.workspace_bytes() for c in ctxs) / 2 ** 30,
         "workspace_reserved_gib": sum(reserved) / 2 ** 30,
-        "grid_search": {"two_phase_passes": sum(c.counter(0) for c in ctxs), "layers_rerun_exact": sum(c.counter(1) for c in ctxs)},
+        "grid_search": {"two_phase_passes": sum(c.counter(0) for c in ctxs), "layers_rerun_exact": sum(c.counter(1) for c in ctxs),
+                        "layers_rerun_two_terms": sum(c.counter(6) for c in ctxs)},
         "roofline": roofline,
         "roofline_f64": roofline_f64,
     }

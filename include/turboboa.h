@@ -62,12 +62,13 @@ const char* tboa_last_error(const tboa_ctx* ctx);
  * two-phase search did not trust itself (see tboa_layer_desc.grid_guard) and that were therefore run again with every
  * candidate of every row evaluated in fp64; TBOA_CTR_GRID_EXACT_ROWS: unused, always 0;
  * TBOA_CTR_GRID_SURVIVORS: near-minimal candidates that were evaluated exactly (rows with a single near-minimal
- * candidate need none).
+ * candidate need none); TBOA_CTR_GRID_TWO_TERM_RUNS: tboa_quantize_layer calls that were run again with H_in as two half terms in the
+ * approximate costs where one had been taken.
  * TBOA_CTR_WEIGHTS_INT_FORM / TBOA_CTR_WEIGHTS_HILO: dequantized fp32 weight matrices handed to
  * tboa_build_hessian_out_proj or tboa_swiglu_forward that were found to be integer multiples of one step per row (one
  * bf16 GEMM with exact operands per product) / that were not and were split into bf16 terms (two or three). */
 enum tboa_counter_id { TBOA_CTR_GRID_PASSES = 0, TBOA_CTR_GRID_FALLBACKS = 1, TBOA_CTR_GRID_EXACT_ROWS = 2, TBOA_CTR_GRID_SURVIVORS = 3,
-                       TBOA_CTR_WEIGHTS_INT_FORM = 4, TBOA_CTR_WEIGHTS_HILO = 5 };
+                       TBOA_CTR_WEIGHTS_INT_FORM = 4, TBOA_CTR_WEIGHTS_HILO = 5, TBOA_CTR_GRID_TWO_TERM_RUNS = 6 };
 int64_t tboa_counter(const tboa_ctx* ctx, int which);
 /* Bytes of context-owned workspace currently allocated (host value). */
 size_t tboa_workspace_bytes(const tboa_ctx* ctx);

@@ -1484,6 +1484,7 @@ extern "C" int tboa_quantize_layer(tboa_ctx* ctx, const tboa_layer_desc* d, cons
     }
     int rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
     if (rc == RUN_AGAIN_TWO_TERMS) {
+        ++ctx->counters[TBOA_CTR_GRID_TWO_TERM_RUNS];
         L.grid_terms = 2;
         rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
     }

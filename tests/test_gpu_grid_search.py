@@ -7,12 +7,12 @@ import torch
 pytestmark = pytest.mark.gpu
 
 
-def layer(n, heads, dh, seed, corr, per_head):
+def layer(n, heads, dh, seed, corr, per_head, tokens=0):
     g = torch.Generator(device="cuda"); g.manual_seed(seed)
     rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float64)
 
     def hessian():
-        x = rnd(4 * n, n)
+        x = rnd(tokens or 4 * n, n)
         x[:, torch.randperm(n, generator=g, device="cuda")[:4]] *= 20
         if corr:
             x = x + 0.3 * (x @ rnd(n, 4)) @ rnd(4, n)
@@ -62,4 +62,12 @@ def test_channels_of_very_different_variance(lib):
     ctx = lib.Context()
     fast = ctx.quantize_layer(W, H, Ho, None, 2, 3, 32)
     same(fast, ctx.quantize_layer(W, H, Ho, None, 2, 3, 32, grid_guard=-1.0))
+    ctx.close()
+
+
+def test_runs_with_two_terms_are_counted(lib):
+    W, H, Ho = layer(320, 2, 32, 5, 0, 0, tokens=160 * 320)
+    ctx = lib.Context()
+    ctx.quantize_layer(W, H, Ho, None, 2, 2, 32, grid_guard=1e-12)
+    assert ctx.counter(0) == 2 and ctx.counter(1) == 1 and ctx.counter(6) == 1
     ctx.close()
