@@ -496,7 +496,7 @@ __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __re
     double bc = 0.0, dev = 0.0; int best = 0x7fffffff;
     for (int j = lane; j < nc && slot0 + j < cap; j += 64) {
         const int k = l[j];
-        const double e = ce[slot0 + j], d = fabs(cr[k] - e) / fabs(e);
+        const double e = ce[slot0 + j], d = cr[k] == e ? 0.0 : fabs(cr[k] - e) / fabs(e);      // (equal: a row of zeros costs 0 both ways)
         if (best == 0x7fffffff || e < bc) { bc = e; best = k; }
         dev = fmax(dev, (d == d) ? d : 1.0);
     }
@@ -1343,7 +1343,9 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         ctx->counters[TBOA_CTR_GRID_SURVIVORS] += gs[GS_SURVIVORS];
         const double guard = d->grid_guard > 0.0 ? d->grid_guard : 0.25;
         if (gs[GS_TRIPPED]) { free(host); return RUN_AGAIN_EXACT; }
-        if (dev > guard * GRID_TAU) { free(host); return gs[GS_ONE_TERM] ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT; }
+        // a cost that its approximation misses by as much as itself (weights that lie on the candidate's grid but for the last bits) is no
+        // matter of the bits of H
+        if (dev > guard * GRID_TAU) { free(host); return gs[GS_ONE_TERM] && dev < 1.f ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT; }
     }
     if (want_loss) {
         double q = 0.0, c = 0.0;

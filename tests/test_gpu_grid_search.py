@@ -65,6 +65,30 @@ def test_channels_of_very_different_variance(lib):
     ctx.close()
 
 
+def test_rows_of_zeros(lib):
+    """Every candidate of a row of zeros costs 0, approximately and exactly: no deviation, no run again; the first candidate wins as in the exact search."""
+    W, H, _ = layer(320, 2, 32, 8, 0, 0, tokens=160 * 320)
+    W[3] = 0; W[40] = 0
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, None, None, 2, 2, 32)
+    assert ctx.counter(1) == 0 and ctx.counter(6) == 0
+    same(fast, ctx.quantize_layer(W, H, None, None, 2, 2, 32, grid_guard=-1.0))
+    ctx.close()
+
+
+def test_weights_on_a_grid_go_to_exact_costs_at_once(lib):
+    """Weights that one candidate meets up to fp32 rounding: its cost is nothing but that rounding, which no number of terms of H brings out; one
+    approximate run, then the exact one."""
+    W, H, _ = layer(320, 2, 32, 9, 0, 0, tokens=160 * 320)
+    q = torch.randint(0, 4, W.shape, device="cuda"); q[:, 0] = 0; q[:, 1] = 3
+    W = (q - 1) * (0.01 + W.abs().amax(1, keepdim=True))
+    ctx = lib.Context()
+    got = ctx.quantize_layer(W, H, None, None, 2, 2, 32)
+    assert ctx.counter(0) == 1 and ctx.counter(1) == 1 and ctx.counter(6) == 0
+    same(got, ctx.quantize_layer(W, H, None, None, 2, 2, 32, grid_guard=-1.0))
+    ctx.close()
+
+
 def test_runs_with_two_terms_are_counted(lib):
     W, H, Ho = layer(320, 2, 32, 5, 0, 0, tokens=160 * 320)
     ctx = lib.Context()
