@@ -148,22 +148,24 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
 // T = the lower triangle of H with half its diagonal (H is symmetric; the GEMM then needs, for output column r, only the
 // contraction indices c <= r: its causal limit).  The left operand is exact and w enters as 22 bits in two extra rows per weight
 // row, so that only T has to be split, into one or two half terms, where (hi, lo) pairs of delta and of H took three products.
-// With one term what is left is the rounding of H, 2^-12 per entry and the same for every candidate (the diagonal is exempt: its
-// rounding is known and added back).  Relative to the cost that is 2^-12 |H off the diagonal|_F / tr H times a factor of up to 40 over the
-// rows (the cost of the best candidate is below the mean): channels that are nearly uncorrelated need one term, strongly correlated
-// ones two (22 bits).  The device decides per matrix (grid_terms_kernel, GRID_ONE_TERM).
+// With one term what is left is the rounding of H, at most 2^-11 of an entry and the same for every candidate (the diagonal is exempt: its
+// rounding is known and added back).  Its effect on a cost goes by rho = |H off the diagonal|_F / tr H: measured 2.9e-4 rho (root mean square over the
+// near-minimal candidates) and up to 1.2e-3 rho, for every width, token count and number of bits alike.  The three products of bf16 pairs were off
+// by 1.4e-6 - 2.3e-6 with 2 bits, 1e-6 - 2e-6 with 3 and 4, 0.6e-6 - 2.3e-6 with 8 (root mean square, widths 1024 - 8192, 16 - 131 thousand tokens): one
+// term is taken where it is off by no more than that, which is where channels are uncorrelated and the tokens many (grid_one_term), and two (22 bits)
+// elsewhere: 1e-7 - 3e-7.  The device decides per matrix (grid_terms_kernel).
 // The channels are equilibrated by powers of two, T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, and
 // qbar'_c = qbar_c 2^(e_c - e_max) (exact), so that the entries of T' are at most 2^12 whatever the spread of the channels.
-// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates; one term): the products take 42 instead of 125 ms.  As a guard, every
+// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates): the products take 42 ms with one term and 80 with two, where three took 125.  As a guard, every
 // exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of GRID_TAU is
 // repeated: with two terms if a matrix had one, else with exact costs for every candidate (counted by tboa_counter).
-// Deviations seen: 1e-5 on uncorrelated channels with one term, 5e-6 - 5e-5 on correlated ones with two (one term: 6e-3); the three
-// products of bf16 pairs had 1e-5 and 4e-5 - 2e-4.
+// Largest deviations seen: 7e-6 with one term; with two 2e-6 on uncorrelated channels and 2e-5 on strongly correlated ones (one term there: 6e-3); the
+// three products of bf16 pairs had 1.5e-5 and 9e-5.
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
 constexpr int GRID_DELTA_BITS = 4;  // from here on the left operand is delta as a pair, below it the integer codes (see grid_codes_kernel)
-constexpr double GRID_ONE_TERM = 0.03;      // |H off the diagonal|_F <= this times tr H: one half term of T is enough
+constexpr double grid_one_term(int bits) { return bits == 2 ? 0.005 : bits <= 4 ? 0.003 : 0.0; }      // one half term of T is enough for |H off the diagonal|_F up to this times tr H
 constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
 inline int grid_width(int n) { return (n + 31) / 32 * 32; }      // columns of the operands: zeros beyond n
@@ -229,8 +231,8 @@ __global__ __launch_bounds__(256) void grid_factor_kernel(const double* __restri
     if (threadIdx.x == 0) g.off2[o + r] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// number of half terms of each matrix (`at_least` 2: never one), and what they leave out of the diagonal
-__global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restrict__ H, int n, int np, GridScale g, int at_least, int* __restrict__ gstat) {
+// number of half terms of each matrix (one up to |H off the diagonal|_F = one_term tr H; `at_least` 2: never one), and what they leave out of the diagonal
+__global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restrict__ H, int n, int np, GridScale g, int at_least, double one_term, int* __restrict__ gstat) {
     __shared__ double red[2][256];
     const double* Hm = H + (long long)blockIdx.x * n * n;
     const long long o = (long long)blockIdx.x * np;
@@ -242,7 +244,7 @@ __global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restric
         if ((int)threadIdx.x < w) { red[0][threadIdx.x] += red[0][threadIdx.x + w]; red[1][threadIdx.x] += red[1][threadIdx.x + w]; }
         __syncthreads();
     }
-    const double lim = GRID_ONE_TERM * red[0][0];
+    const double lim = one_term * red[0][0];
     const int terms = (at_least < 2 && 2.0 * red[1][0] <= lim * lim) ? 1 : 2;
     if (threadIdx.x == 0) { g.terms[blockIdx.x] = terms; if (terms == 1) atomicOr(gstat, 1); }
     for (int c = threadIdx.x; c < np; c += 256) {
@@ -1047,7 +1049,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         const int np = grid_width(n);
         hipLaunchKernelGGL(grid_scale_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale);
         hipLaunchKernelGGL(grid_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.Hcat, (long long)nhin * np * (np + GRID_PAD));
-        hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, L.gstat + GS_ONE_TERM);
+        hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, grid_one_term(d->bits), L.gstat + GS_ONE_TERM);
         TB_KERNEL_CHECK(ctx);
     }
     // U_in, P and U_out are first needed by the first in-channel sweep; the grid search before it needs only W and H_in.

@@ -46,7 +46,7 @@ def test_two_phase_search_equals_exact(lib, n, heads, dh, per_head, bits, corr):
 def test_a_guard_that_cannot_be_met_ends_in_exact_costs(lib, corr):
     """A guard below what any rounding gives: the call is run again (independent channels: with two half terms first, twice the passes) and at
     last exactly, once by the counter."""
-    W, H, Ho = layer(320, 2, 32, 5, corr, 0)
+    W, H, Ho = layer(320, 2, 32, 5, corr, 0, tokens=0 if corr else 160 * 320)      # (one term: independent channels over so many tokens)
     ctx = lib.Context()
     got = ctx.quantize_layer(W, H, Ho, None, 2, 2, 32, grid_guard=1e-12)
     assert ctx.counter(1) == 1 and ctx.counter(0) == (2 if not corr else 1)
@@ -94,4 +94,30 @@ def test_runs_with_two_terms_are_counted(lib):
     ctx = lib.Context()
     ctx.quantize_layer(W, H, Ho, None, 2, 2, 32, grid_guard=1e-12)
     assert ctx.counter(0) == 2 and ctx.counter(1) == 1 and ctx.counter(6) == 1
+    ctx.close()
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("n,tokens", [(320, 1280), (1000, 2000), (1024, 32768)])
+def test_approximate_costs_of_independent_channels(lib, bits, n, tokens):
+    """Few tokens correlate independent channels by chance, and a cost takes up the rounding of H by that much.  Costs from (hi, lo) pairs of H are within 5e-6
+    of the exact ones here; a guard at 1.5e-5 holds however many terms are taken."""
+    W, H, _ = layer(n, 2, 32, n, 0, 0, tokens=tokens)
+    ctx = lib.Context()
+    ctx.quantize_layer(W, H, None, None, 2, bits, 32, grid_guard=1.5e-5 / 2e-3)
+    assert ctx.counter(0) > 0 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4, 8])
+@pytest.mark.parametrize("n,heads,dh,per_head", [(257, 1, 33, 0), (288, 2, 16, 1), (544, 2, 24, 0)])
+def test_one_term_search_equals_exact(lib, n, heads, dh, per_head, bits):
+    """Independent channels over many tokens: H_in as one half term (except with 8 bits)."""
+    W, H, Ho = layer(n, heads, dh, n + bits, 0, per_head, tokens=200000)
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, Ho, None, heads, bits, 16)
+    assert ctx.counter(0) > 0 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    same(fast, ctx.quantize_layer(W, H, Ho, None, heads, bits, 16, grid_guard=-1.0))
+    ctx.quantize_layer(W, H, Ho, None, heads, bits, 16, grid_guard=1e-12)      # what cannot be met tells whether there was one term
+    assert ctx.counter(6) == (bits != 8)
     ctx.close()
