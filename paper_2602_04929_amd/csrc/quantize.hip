@@ -164,7 +164,7 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
-constexpr int GRID_DELTA_BITS = 4;  // from here on the left operand is delta as a pair, below it the integer codes (see grid_codes_kernel)
+constexpr bool grid_delta(int bits, int n) { return bits > 3 || (bits == 3 && n > 2048); }      // the left operand is delta as a pair, else the integer codes (see grid_codes_kernel)
 constexpr double grid_one_term(int bits) { return bits == 2 ? 0.005 : bits <= 4 ? 0.003 : 0.0; }      // one half term of T is enough for |H off the diagonal|_F up to this times tr H
 constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
@@ -303,11 +303,13 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict
 // qbar'[(row, k), c] = (clamp(round(w_c / s_k) + z_k) - z_k) up[c].  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so
 // wherever it is further than 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
 // A wavefront makes whole 16 x 32 blocks: lane = (row of the block lane / 4, eight columns of lane % 4).
-// DELTA (grids of 4 bits and more): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
-// elements further on.  With 256 levels s qbar and w agree to 1e-2 and their products with T, formed in fp32, would be subtracted:
-// deviations of 5e-4 on correlated channels, against 3e-6 this way.  With 16 levels the subtraction left 5e-5 on the correlated
-// inputs of the tests, but 5.4e-4 on the Hessian of a 7B down projection (d_in 11008, rows of silu(gate) up with outlier tokens), and the
-// whole search was repeated with exact costs (0.94 s); with 8 levels and less it leaves 5e-5 at the most and the exact operand saves the second product.
+// DELTA (grid_delta): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
+// elements further on.  The finer the grid, the closer s qbar and w, whose products with T, formed in fp32, the integer form subtracts: it loses bits by
+// the number of levels, the width and the correlation of H.  Deviations (largest, root mean square) on the Hessian of a 7B down projection (d_in 11008, rows of
+// silu(gate) up over 131072 fake-quantized tokens): integer form 4.0e-4, 8.1e-5 with 16 levels, 2.4e-4, 4.2e-5 with 8, 1.2e-4, 2.1e-5 with 4; three products
+// of bf16 pairs of delta and H 1.4e-4, 2.7e-5 and this form 2.9e-5, 5.8e-6 for any of them.  On channels correlated by eight common factors (8192 wide): integer
+// form 9.9e-6 with 8 levels and 5.9e-6 with 4 (root mean square), bf16 pairs 9e-6, this form 1.5e-6.  The integer form, which saves a product, is kept where it is
+// at least as close as the bf16 pairs were on every H tried: 4 levels at any width, 8 levels up to 3072 columns (at 4096 2.0e-5 against 1.7e-5 on a down projection).
 template <bool DELTA>
 __global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, int rows, float maxq,
                                                          GridRows m, GridScale g, const double* __restrict__ cand_s, const double* __restrict__ cand_z,
@@ -922,7 +924,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             const unsigned rb = (unsigned)(((long long)m.per * ncand + 63) / 64);
             // (columns in up to 8 parts where there are few rows)
             const unsigned cparts = (long long)rb * mats >= 2048 ? 1u : (unsigned)std::min<long long>(8, 2048 / ((long long)rb * mats) + 1);
-            const bool delta = L.d->bits >= GRID_DELTA_BITS;
+            const bool delta = grid_delta(L.d->bits, n);
             const long long lo_off = (long long)mats * m.mat_rows * (np + GRID_PAD);
             if (delta)
                 hipLaunchKernelGGL(grid_codes_kernel<true>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
@@ -1373,7 +1375,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     size_t delta_bytes = (size_t)L.grid_chunk * unit_rows * L.ncand * L.gsz * sizeof(double), g_bytes = delta_bytes;
     if (L.fast_grid) {
         const size_t np = grid_width(n), mrows = (L.nhin > 1 ? (size_t)L.fast_chunk : 1) * grid_mat_rows(L.nhin > 1 ? unit_rows : (long long)grows, L.ncand);
-        delta_bytes = std::max(delta_bytes, (d->bits >= GRID_DELTA_BITS ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
+        delta_bytes = std::max(delta_bytes, (grid_delta(d->bits, n) ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
     }
     const int fmax = n > dh ? n : dh;
     const int fb = (L.nhin > nh) ? L.nhin : nh;

@@ -121,3 +121,26 @@ def test_one_term_search_equals_exact(lib, n, heads, dh, per_head, bits):
     ctx.quantize_layer(W, H, Ho, None, heads, bits, 16, grid_guard=1e-12)      # what cannot be met tells whether there was one term
     assert ctx.counter(6) == (bits != 8)
     ctx.close()
+
+
+@pytest.mark.parametrize("bits", [3, 4, 8])
+@pytest.mark.parametrize("seed", [1, 2])
+def test_approximate_costs_of_fine_grids(lib, bits, seed):
+    """Strongly correlated wide channels: costs from pairs of delta are within 1.5e-5 of the exact ones (22 bits on both sides, fp32 sums), those from codes
+    and weights that are subtracted are off by 7e-5 and more; a guard at 4e-5 tells which it was."""
+    W, H, _ = layer(2304, 4, 64, seed, 1, 0)
+    ctx = lib.Context()
+    ctx.quantize_layer(W, H, None, None, 4, bits, 64, grid_guard=4e-5 / 2e-3)
+    assert ctx.counter(0) > 0 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [2048, 2049])
+def test_both_operands_of_3_bits_equal_exact(lib, n):
+    """The widths on either side of the rule that chooses codes or pairs of delta."""
+    W, H, Ho = layer(n, 2, 16, n, 0, 0)
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, Ho, None, 2, 3, 16)
+    assert ctx.counter(0) > 0 and ctx.counter(1) == 0
+    same(fast, ctx.quantize_layer(W, H, Ho, None, 2, 3, 16, grid_guard=-1.0))
+    ctx.close()
