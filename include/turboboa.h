@@ -225,7 +225,8 @@ typedef struct {
 size_t tboa_quantize_workspace_bytes(const tboa_layer_desc* desc, int with_H_out, int with_R);
 
 /*   W      [d_out, d_in]            (w_dtype)
- *   H_in   fp32, shape per hin_per_head
+ *   H_in   fp32, shape per hin_per_head; symmetric.  Where it is so up to rounding only, the factorisation reads the upper
+ *          triangle and everything else (H_in + H_in^T) / 2
  *   H_out  [n_heads, d_h, d_h] fp32, or NULL = identity (output projection / GPTQ: rows decouple,
  *          no compensation between out-channels)
  *   R      fp32, same shape as H_in, already scaled by alpha, or NULL = 0 (first block / BoA)

@@ -133,12 +133,42 @@ __global__ void cvt_offdiag_kernel(const float* __restrict__ H, double* __restri
     }
 }
 
+// out = (H + H^T) / 2 off the diagonal, exactly H where H is symmetric; grid.x runs over the pairs of 64 x 64 tiles (tr, tc), tr >= tc, that are each
+// other's mirror image, grid.z over the matrices
+__global__ __launch_bounds__(256) void cvt_symmetric_kernel(const float* __restrict__ H, double* __restrict__ out, int n) {
+    __shared__ float lo[64][65], up[64][65];
+    const long long base = (long long)blockIdx.z * n * n;
+    int tr = (int)((sqrtf(8.f * (float)blockIdx.x + 1.f) - 1.f) * 0.5f);
+    while ((long long)(tr + 1) * (tr + 2) / 2 <= (long long)blockIdx.x) ++tr;
+    while ((long long)tr * (tr + 1) / 2 > (long long)blockIdx.x) --tr;
+    const int r0 = tr * 64, c0 = (int)(blockIdx.x - (long long)tr * (tr + 1) / 2) * 64;
+    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
+        const int r = i >> 6, c = i & 63;
+        lo[r][c] = (r0 + r < n && c0 + c < n) ? H[base + (long long)(r0 + r) * n + c0 + c] : 0.f;
+        up[r][c] = (c0 + r < n && r0 + c < n) ? H[base + (long long)(c0 + r) * n + r0 + c] : 0.f;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
+        const int r = i >> 6, c = i & 63;
+        if (r0 + r < n && c0 + c < n) out[base + (long long)(r0 + r) * n + c0 + c] = 0.5 * ((double)lo[r][c] + (double)up[c][r]);
+        if (c0 + r < n && r0 + c < n) out[base + (long long)(c0 + r) * n + r0 + c] = 0.5 * ((double)up[r][c] + (double)lo[c][r]);
+    }
+}
+
 }  // namespace
 
 int launch_f32_to_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out) {
     const long long total = (long long)batch * n * n;
     long long g = (total + 255) / 256; if (g > 16384) g = 16384;
     hipLaunchKernelGGL(cvt_offdiag_kernel, dim3((unsigned)g), dim3(256), 0, ctx->stream, H, out, n, total);
+    hipLaunchKernelGGL(cvt_damp_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, out, n, damp);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
+
+int launch_symmetric_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out) {
+    const long long nt = (n + 63) / 64;
+    hipLaunchKernelGGL(cvt_symmetric_kernel, dim3((unsigned)(nt * (nt + 1) / 2), 1, batch), dim3(256), 0, ctx->stream, H, out, n);
     hipLaunchKernelGGL(cvt_damp_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, out, n, damp);
     TB_KERNEL_CHECK(ctx);
     return 0;

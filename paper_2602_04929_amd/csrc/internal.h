@@ -195,6 +195,7 @@ int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H64, double* U, 
 int chol_status_f64(tboa_ctx* ctx, int status_slot);
 int chol_static_init(int device);   // looks up the device address of the static scratch of tboa_chol_inv_upper_static (device current)
 int launch_f32_to_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out);
+int launch_symmetric_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out);      // of (H + H^T) / 2
 
 // ---------------------------------------------------------------- misc elementwise (elementwise.hip)
 int launch_fill_f64(tboa_ctx* ctx, double* p, int64_t n, double v);

@@ -1044,9 +1044,10 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
 
     TB_TRY(launch_cvt_to_f64(ctx, W, d->w_dtype, L.W64, wn));
     TB_HIP(ctx, hipMemcpyAsync(L.Wt, L.W64, wn * sizeof(double), hipMemcpyDeviceToDevice, st));
-    // eq. 3 for H_in (and H_out)
-    TB_TRY(launch_f32_to_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hi));
-    TB_HIP(ctx, hipMemcpyAsync(L.Hfac, L.Hi, nhin * nn * sizeof(double), hipMemcpyDeviceToDevice, st));
+    // eq. 3 for H_in (and H_out).  The factorisation reads the upper triangle; the half products below read whatever triangle their tiles say, so
+    // that an H_in that is symmetric up to rounding only must be made so first
+    TB_TRY(launch_symmetric_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hi));
+    TB_TRY(launch_f32_to_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hfac));
     if (L.fast_grid) {
         const int np = grid_width(n);
         hipLaunchKernelGGL(grid_scale_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale);

@@ -205,3 +205,31 @@ def test_workspace_queries(ctx, lib):
         assert c2.quantize_workspace_bytes(bad) == 0
     finally:
         c2.close()
+
+
+@pytest.mark.parametrize("n,group,coupled", [(64, 0, 1), (300, 0, 1), (300, 0, 0), (320, 64, 1), (1000, 0, 0)])
+def test_h_in_that_is_not_exactly_symmetric(lib, n, group, coupled):
+    """Costs, refinement and loss are quadratic forms: they see (H + H^T) / 2 however a product walks the matrix."""
+    rng = np.random.default_rng(n)
+    X = rng.standard_normal((3 * n, n)); H = X.T @ X
+    K = rng.standard_normal((n, n)); H = (H + 0.05 * n ** 0.5 * (K - K.T)).astype(np.float32)
+    heads, dh = 2, 40
+    W = (0.02 * rng.standard_normal((heads * dh, n))).astype(np.float32)
+    G = rng.standard_normal((heads, 3 * dh, dh)); Ho = np.stack([g.T @ g for g in G]).astype(np.float32) if coupled else None
+    ctx = lib.Context()
+    d = lambda a: None if a is None else torch.from_numpy(a).cuda()
+    got = ctx.quantize_layer(d(W), d(H), d(Ho), None, heads, 3, 8, group=group, damp=0.0)
+    D = (got["W_deq"].cpu().numpy().astype(np.float64) - W).reshape(heads, dh, n)
+    want = [np.trace((Ho[h].astype(np.float64) if coupled else np.eye(dh)) @ D[h] @ H.astype(np.float64) @ D[h].T) for h in range(heads)]
+    assert np.abs(np.array(got["loss_per_head_terms"])[:, 0] - want).max() <= 1e-5 * max(want)      # W_deq is rounded to fp32
+    if not group:
+        exact = ctx.quantize_layer(d(W), d(H), d(Ho), None, heads, 3, 8, damp=0.0, grid_guard=-1.0)
+        for k in ("codes", "scales", "zeros"):
+            assert torch.equal(got[k], exact[k]), k
+    # least squares of the scales on the final codes: without H_out a row's scale minimises its own quadratic form of (H + H^T) / 2
+    if not coupled:
+        wbar = got["codes"].cpu().numpy().astype(np.float64) - got["zeros"].cpu().numpy().astype(np.float64)
+        Hs = 0.5 * (H.astype(np.float64) + H.astype(np.float64).T)
+        s = np.einsum("rc,rc->r", wbar @ Hs, W.astype(np.float64)) / np.einsum("rc,rc->r", wbar @ Hs, wbar)
+        assert np.abs(got["scales"].cpu().numpy()[:, 0] - s).max() <= 1e-6 * s.max()
+    ctx.close()
