@@ -38,7 +38,7 @@ def test_gemm_f64_shapes(lib, case, ta, tb):
 
 @pytest.mark.parametrize("rep,dh,d", [(8, 128, 1024), (3, 100, 520), (1, 64, 4096), (5, 33, 65)])
 def test_hout_sums_the_heads_of_a_group(lib, rep, dh, d):
-    """build_hout adds the d_h x d_h products of a group's heads in one launch (or, where the parts do not fit the buffer, one by one)."""
+    """build_hout adds the d_h x d_h products of a group's heads in one launch."""
     rng = np.random.default_rng(rep * 100 + dh)
     X = rng.standard_normal((2 * d, d)); H = (X.T @ X).astype(np.float32)
     nh = 3
