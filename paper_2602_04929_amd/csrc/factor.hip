@@ -25,7 +25,7 @@ __device__ __forceinline__ double reciprocal(double p) {
 // Latency-bound (one workgroup per matrix, between the updates of the factorisation).  Thread (tx, ty) keeps the rows ty, ty + 4, ..
 // of column tx in registers; a step exchanges one column (one row, in the inverse) through LDS and has one barrier.  The
 // factorisation works on unscaled columns, V[r][r2] -= c[r] c[r2] / pivot, so that no step waits for a square root, and the columns
-// are scaled at the end.  100 -> 54 us per 64 x 64 block, against the version with everything in LDS, three barriers and a
+// are scaled at the end.  100 -> 55 us per 64 x 64 block (the kernel alone on the GPU), against the version with everything in LDS, three barriers and a
 // division per element.
 __global__ __launch_bounds__(256) void diag_factor_kernel(double* __restrict__ H, int n, int j0, int bs,
                                                           double* __restrict__ dinv, int blk, int nblk, int* status) {

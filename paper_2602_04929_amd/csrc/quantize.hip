@@ -533,7 +533,7 @@ struct SweepArgs {
 // Bound by the chain of the 64 column steps: what a step needs from the one before goes through one broadcast and a dozen dependent
 // fp64 operations, two rows per wavefront side by side.  Both divisions of a step are products with reciprocals taken once per panel
 // (quant_code_fast decides the code as the quotient would; the other one gets a Newton correction), and the loads of the panel's pieces of U
-// and P are all in flight together (they were taken one row after the other: half of the time): 33 -> 21 us per panel.
+// and P are all in flight together (they were taken one row after the other: half of the time): 34 -> 21 us per panel of 16 or 32 rows a head (alone on the GPU).
 // LAZY: the deviation term through S = R U^T instead of P = (S * M_U) U: with v_m = sum_{j < m} w_j S[j, m] (nv holds -v; what earlier panels
 // contribute is already in it) column j is w_j - v_j U[j, j] when its turn comes, and (e_j + v_j) U[j, :] is taken from the columns to its right.
 template <int RPW, bool LAZY>
