@@ -150,17 +150,17 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
 // row, so that only T has to be split, into one or two half terms, where (hi, lo) pairs of delta and of H took three products.
 // With one term what is left is the rounding of H, at most 2^-11 of an entry and the same for every candidate (the diagonal is exempt: its
 // rounding is known and added back).  Its effect on a cost goes by rho = |H off the diagonal|_F / tr H: measured 2.9e-4 rho (root mean square over the
-// near-minimal candidates) and up to 1.2e-3 rho, for every width, token count and number of bits alike.  The three products of bf16 pairs were off
+// near-minimal candidates) and up to 1.4e-3 rho below rho = 0.01, at every width and number of bits, and more of it above (up to 8e-3 rho at 0.4).  The three products of bf16 pairs were off
 // by 1.4e-6 - 2.3e-6 with 2 bits, 1e-6 - 2e-6 with 3 and 4, 0.6e-6 - 2.3e-6 with 8 (root mean square, widths 1024 - 8192, 16 - 131 thousand tokens): one
 // term is taken where it is off by no more than that, which is where channels are uncorrelated and the tokens many (grid_one_term), and two (22 bits)
 // elsewhere: 1e-7 - 3e-7.  The device decides per matrix (grid_terms_kernel).
 // The channels are equilibrated by powers of two, T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, and
 // qbar'_c = qbar_c 2^(e_c - e_max) (exact), so that the entries of T' are at most 2^12 whatever the spread of the channels.
-// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates): the products take 42 ms with one term and 80 with two, where three took 125.  As a guard, every
+// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates): the products take 44 ms with one term and 82 with two, where three took 120.  As a guard, every
 // exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of GRID_TAU is
 // repeated: with two terms if a matrix had one, else with exact costs for every candidate (counted by tboa_counter).
-// Largest deviations seen: 7e-6 with one term; with two 2e-6 on uncorrelated channels and 2e-5 on strongly correlated ones (one term there: 6e-3); the
-// three products of bf16 pairs had 1.5e-5 and 9e-5.
+// Largest deviations seen: 7e-6 with one term; with two 2e-6 on uncorrelated channels, 4e-5 on strongly correlated ones (one term there: 6e-3) and
+// 1.2e-4 on the Hessian of a down projection; the three products of bf16 pairs had 1.5e-5, 8e-5 and 1.4e-4.
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
