@@ -197,6 +197,25 @@ int chol_static_init(int device);   // looks up the device address of the static
 int launch_f32_to_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out);
 int launch_symmetric_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out);      // of (H + H^T) / 2
 
+// ---------------------------------------------------------------- sweep.hip
+// the rows of a step: block row R = h nbr + r is layer row h dh + i0 + r
+struct BlockMap { int nbr, dh, i0; };
+__device__ __forceinline__ long long layer_row(const BlockMap& m, int R) {
+    return (long long)(R / m.nbr) * m.dh + m.i0 + (R % m.nbr);
+}
+constexpr int SWEEP_SP = 512;      // columns whose updates of the columns further right are applied in one product: the widest sweep launch
+struct SweepArgs {
+    const double* Wk; int n; int nbr; BlockMap map;
+    const double* U; const double* P; int per_head;   // U, P: [n, n] or [n_heads, n, n]; P null: no deviation term
+    const double* nv;                // lazy: block array [rows, n], P holds S (see run_layer)
+    int c0, width;                   // columns c0 .. c0 + width - 1, width <= SWEEP_SP; more than 16 only where the grid groups are whole 16s
+    const double* s; const double* z; int ng, gsz; double maxq;      // grids per layer row and group of gsz columns
+    uint8_t* codes; double* Q;       // layer arrays [d_out, n]
+    double* Epan; double* Wsnap;     // block arrays [rows, epitch], already offset to the first column
+    int epitch;
+};
+int launch_sweep(tboa_ctx* ctx, const SweepArgs& a, int nh, bool lazy);
+
 // ---------------------------------------------------------------- misc elementwise (elementwise.hip)
 int launch_fill_f64(tboa_ctx* ctx, double* p, int64_t n, double v);
 int launch_fill_f32(tboa_ctx* ctx, float* p, int64_t n, float v);

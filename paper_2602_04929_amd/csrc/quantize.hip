@@ -5,9 +5,7 @@
 //   grid search   (Alg. 1 line 9)  candidates -> approximate costs of all of them on the 16-bit matrix cores (integer codes against
 //                                  H_in as one or two half terms) -> exact fp64 costs of the near-minimal ones -> argmin
 //                                  (narrow layers and group-wise grids: every candidate exactly, one fp64 GEMM)
-//   in-channel sweep (Algorithm 3) panels of 64 columns: a wavefront owns a row, lane k holds column k, the 64
-//                                  sequential column steps run inside the kernel with U/P panel rows in LDS;
-//                                  columns right of the panel get one rank-64 GEMM update per term
+//   in-channel sweep (Algorithm 3) groups of 512 columns (sweep.hip); the columns right of a group get one rank-512 GEMM update per term
 //   compensation  (Prop. 3.1/3.2)  T = [U_out^T]_{i1:,B} [U_out^T]_{B,B}^-1 per head, then W~[i1:] -= T E as a
 //                                  batched GEMM, E = (W_B - Q_B) - ((W_B R) U_in^T) U_in
 // and after the last step the coordinate descent of Algorithm 2 on precomputed Gram matrices (d_h x d_h per head; per
@@ -21,18 +19,6 @@
 
 namespace {
 
-struct BlockMap { int nbr, dh, i0; };
-__device__ __forceinline__ long long layer_row(const BlockMap& m, int R) {
-    return (long long)(R / m.nbr) * m.dh + m.i0 + (R % m.nbr);
-}
-
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_readlane(lo, l);
-    hi = __builtin_amdgcn_readlane(hi, l);
-    return __hiloint2double(hi, lo);
-}
-
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -41,15 +27,6 @@ __device__ __forceinline__ double wave_sum(double v) {
 
 __device__ __forceinline__ double quant_code(double w, double s, double z, double maxq) {
     return fmin(fmax(rint(w / s) + z, 0.0), maxq);
-}
-
-// the same code without the division: w (1 / s) is within 4 ulp of w / s, so that wherever it is further than that from a
-// half-integer both round to the same integer; only the others are divided
-__device__ __forceinline__ double quant_code_fast(double w, double s, double si, double z, double maxq) {
-    const double t = w * si;
-    double r = rint(t);
-    if (!(0.5 - fabs(t - r) > fabs(t) * 1e-15)) r = rint(w / s);
-    return fmin(fmax(r + z, 0.0), maxq);
 }
 
 // ------------------------------------------------------------------------------------------------ rows
@@ -516,97 +493,6 @@ __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __re
 }
 
 __global__ void clear_words_kernel(int* p, int n) { if ((int)threadIdx.x < n) p[threadIdx.x] = 0; }
-
-// ------------------------------------------------------------------------------------------------ Algorithm 3
-constexpr int SWEEP_SP = 512;      // columns whose updates of the columns further right are applied in one product
-struct SweepArgs {
-    double* Wk; int n; int nbr; BlockMap map;
-    const double* U; const double* P; int per_head;   // U, P: [n, n] or [n_heads, n, n]
-    const double* nv;                // null: P is that of Algorithm 3; else block array [rows, n] and P holds S (see run_layer)
-    int c0, pw;
-    const double* s; const double* z; int ng, gi; double maxq;
-    uint8_t* codes; double* Q;       // layer arrays [d_out, n]
-    double* Epan; double* Wsnap;     // block arrays [rows, epitch], already offset to this panel's first column
-    int epitch;
-};
-
-// Bound by the chain of the 64 column steps: what a step needs from the one before goes through one broadcast and a dozen dependent
-// fp64 operations, two rows per wavefront side by side.  Both divisions of a step are products with reciprocals taken once per panel
-// (quant_code_fast decides the code as the quotient would; the other one gets a Newton correction), and the loads of the panel's pieces of U
-// and P are all in flight together (they were taken one row after the other: half of the time): 34 -> 21 us per panel of 16 or 32 rows a head (alone on the GPU).
-// LAZY: the deviation term through S = R U^T instead of P = (S * M_U) U: with v_m = sum_{j < m} w_j S[j, m] (nv holds -v; what earlier panels
-// contribute is already in it) column j is w_j - v_j U[j, j] when its turn comes, and (e_j + v_j) U[j, :] is taken from the columns to its right.
-template <int RPW, bool LAZY>
-__global__ __launch_bounds__(256) void sweep_panel_kernel(SweepArgs a) {
-    __shared__ double Us[64][64];
-    __shared__ double Ps[64][64];
-    __shared__ double Ui[64];
-    const int h = blockIdx.y, n = a.n, c0 = a.c0, pw = a.pw;
-    const double* U = a.U + (a.per_head ? (long long)h * n * n : 0);
-    const double* P = a.P ? a.P + (a.per_head ? (long long)h * n * n : 0) : nullptr;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    {      // all loads of the two 64 x 64 pieces in flight together (clamped indices; what lies beyond the panel becomes zero on the way to LDS)
-        double u[16], p[16];
-        const int k = min(lane, pw - 1);
-#pragma unroll
-        for (int q = 0; q < 16; ++q) u[q] = U[(long long)(c0 + min(wave + 4 * q, pw - 1)) * n + c0 + k];
-        if (P) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) p[q] = P[(long long)(c0 + min(wave + 4 * q, pw - 1)) * n + c0 + k];
-        }
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int j = wave + 4 * q;
-            const bool in = j < pw && lane < pw;
-            Us[j][lane] = in ? u[q] : 0.0;
-            Ps[j][lane] = in && P && (!LAZY || lane > j) ? p[q] : 0.0;
-            if (j == lane) Ui[lane] = in ? 1.0 / u[q] : 1.0;
-        }
-    }
-    double w[RPW], nv[RPW], s[RPW], si[RPW], z[RPW], qv[RPW], Qv[RPW], ev[RPW], wsv[RPW];
-    int R[RPW]; bool valid[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int r = (blockIdx.x * 4 + wave) * RPW + i;
-        valid[i] = r < a.nbr;
-        R[i] = h * a.nbr + (valid[i] ? r : 0);
-        const long long lr = layer_row(a.map, R[i]);
-        w[i] = (valid[i] && lane < pw) ? a.Wk[(long long)R[i] * n + c0 + lane] : 0.0;
-        nv[i] = (LAZY && valid[i] && lane < pw) ? a.nv[(long long)R[i] * n + c0 + lane] : 0.0;
-        s[i] = a.s[lr * a.ng + a.gi]; z[i] = a.z[lr * a.ng + a.gi]; si[i] = 1.0 / s[i];
-        qv[i] = Qv[i] = ev[i] = wsv[i] = 0.0;
-    }
-    __syncthreads();
-    const bool hasP = (P != nullptr);
-    for (int j = 0; j < pw; ++j) {
-        const double urow = Us[j][lane], prow = Ps[j][lane], ujj = Us[j][j], uinv = Ui[j];
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const double nvj = LAZY ? readlane_f64(nv[i], j) : 0.0;
-            const double wj = LAZY ? __builtin_fma(nvj, ujj, readlane_f64(w[i], j)) : readlane_f64(w[i], j);
-            const double q = quant_code_fast(wj, s[i], si[i], z[i], a.maxq);
-            const double Qj = s[i] * (q - z[i]);
-            const double d = wj - Qj, e0 = d * uinv;
-            const double eq = __builtin_fma(__builtin_fma(-e0, ujj, d), uinv, e0);     // d / ujj
-            const double e = LAZY ? eq - nvj : eq;
-            if (lane == j) { qv[i] = q; Qv[i] = Qj; ev[i] = e; wsv[i] = wj; }
-            w[i] = __builtin_fma(-e, urow, w[i]);
-            if constexpr (LAZY) nv[i] = __builtin_fma(-wj, prow, nv[i]);
-            else if (hasP) w[i] = __builtin_fma(-wj, prow, w[i]);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        if (!valid[i]) continue;
-        if (lane < pw) {
-            a.Epan[(long long)R[i] * a.epitch + lane] = ev[i];
-            a.Wsnap[(long long)R[i] * a.epitch + lane] = wsv[i];
-            const long long lr = layer_row(a.map, R[i]);
-            a.codes[lr * n + c0 + lane] = (uint8_t)qv[i];
-            a.Q[lr * n + c0 + lane] = Qv[i];
-        }
-    }
-}
 
 // ------------------------------------------------------------------------------------------------ Prop. 3.1 / 3.2
 // E[R, c] = Wb[R, c] - Q[layer_row(R), c] (- S3[R, c])
@@ -1125,10 +1011,11 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         return 0;
     };
     const double* Pp = R ? L.P : nullptr;
-    const int pw_max = L.gsz < 64 ? L.gsz : 64;
     // columns per group of panels: a group-wise grid is searched on the current columns of its group when the sweep enters
     // it, so a group of panels must not straddle a grid group that starts inside it unaligned
-    const int sp = (!d->group || SWEEP_SP % L.gsz == 0 || L.gsz % SWEEP_SP == 0) ? SWEEP_SP : pw_max;
+    const int sp = (!d->group || SWEEP_SP % L.gsz == 0 || L.gsz % SWEEP_SP == 0) ? SWEEP_SP : L.gsz < 64 ? L.gsz : 64;
+    // columns per launch of the sweep: up to where the next grid is searched (and one grid per launch if it has fewer columns than a sub-panel)
+    const int pw_max = d->group && (d->adaptive_grid || L.gsz < 16) ? std::min(L.gsz, sp) : sp;
 
     if (!d->adaptive_grid) {   // BoA: one grid from the original weights
         BlockMap id{dh, dh, 0};
@@ -1142,31 +1029,23 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         TB_KERNEL_CHECK(ctx);
         if (L.lazy) { TB_TRY(launch_fill_f64(ctx, L.nr, (int64_t)rows * n, 0.0)); TB_TRY(launch_fill_f64(ctx, L.nv, (int64_t)rows * n, 0.0)); }
         if (d->adaptive_grid && !d->group) TB_TRY(grid_search(L, L.Wk, n, nbr, map, 0, n, 0));
-        // Algorithm 3 in panels on two levels: inside a group of up to SWEEP_SP columns every 64-column panel updates the rest of
-        // the group at once; the columns right of the group get the group's whole update in one product (a contraction SWEEP_SP
-        // deep instead of 64: a quarter of the passes over the remaining columns)
+        // Algorithm 3 in groups of up to SWEEP_SP columns: one launch takes the rows through a group (group-wise grids: through a panel of it, after
+        // which the rest of the group follows), and the columns right of the group get the whole update in one product
         for (int s0 = 0; s0 < n; s0 += sp) {
             const int s1 = (n - s0 < sp) ? n : s0 + sp;
             if (L.lazy && s0 > 0)      // -v of the group's columns from what the columns before it have left in -r
                 TB_TRY(block_gemm(L, nbr, s1 - s0, n - s0, 1.0, L.nr + s0, n, L.Uin, (long long)s0 * n + s0, 1, n, 0.0, L.nv + s0, n, TBOA_PROF_F64_SWEEP));
             for (int c0 = s0; c0 < s1; c0 += pw_max) {
                 const int pw = (s1 - c0 < pw_max) ? s1 - c0 : pw_max, c1 = c0 + pw;
-                const int gi = c0 / L.gsz;
-                if (d->group && d->adaptive_grid && c0 % L.gsz == 0) TB_TRY(grid_search(L, L.Wk, n, nbr, map, c0, L.gsz, gi));
+                if (d->group && d->adaptive_grid && c0 % L.gsz == 0) TB_TRY(grid_search(L, L.Wk, n, nbr, map, c0, L.gsz, c0 / L.gsz));
                 SweepArgs a;
                 a.Wk = L.Wk; a.n = n; a.nbr = nbr; a.map = map; a.U = L.Uin; a.P = Pp; a.per_head = nhin > 1;
-                a.c0 = c0; a.pw = pw; a.s = L.s64; a.z = L.z64; a.ng = ng; a.gi = gi; a.maxq = L.maxq;
+                a.c0 = c0; a.width = pw; a.s = L.s64; a.z = L.z64; a.ng = ng; a.gsz = L.gsz; a.maxq = L.maxq;
                 a.codes = codes; a.Q = L.Q64; a.Epan = L.Epan + (c0 - s0); a.Wsnap = L.Wsnap + (c0 - s0); a.epitch = SWEEP_SP; a.nv = L.nv;
                 TB_TRY(setup_join());
-                if (L.lazy) hipLaunchKernelGGL((sweep_panel_kernel<2, true>), dim3((nbr + 7) / 8, nh), dim3(256), 0, st, a);
-                else hipLaunchKernelGGL((sweep_panel_kernel<2, false>), dim3((nbr + 7) / 8, nh), dim3(256), 0, st, a);
-                TB_KERNEL_CHECK(ctx);
-                if (c1 < s1) {   // rest of the group: W[:, c1:s1] -= E U[c0:c1, c1:s1] + Wsnap P[c0:c1, c1:s1]
-                    GemmF64 two{};   // both terms in one pass over the output
-                    if (L.lazy) {    // W -= (E + V) U and -V -= Wsnap S: two results, one launch
-                        TB_TRY(pair_gemm(L, nbr, s1 - c1, pw, c0 - s0, (long long)c0 * n + c1, L.P, c1, L.nv));
-                        continue;
-                    }
+                TB_TRY(launch_sweep(ctx, a, nh, L.lazy));
+                if (c1 < s1) {   // group-wise grids: rest of the group of panels, W[:, c1:s1] -= E U[c0:c1, c1:s1] + Wsnap P[c0:c1, c1:s1], both terms in one pass
+                    GemmF64 two{};
                     if (Pp) { two.A2 = L.Wsnap + (c0 - s0); two.B2 = L.P + (long long)c0 * n + c1; }
                     TB_TRY(block_gemm(L, nbr, s1 - c1, pw, -1.0, L.Epan + (c0 - s0), SWEEP_SP, L.Uin, (long long)c0 * n + c1, n, 1, 1.0, L.Wk + c1, n,
                                       TBOA_PROF_F64_SWEEP, &two));
