@@ -98,11 +98,11 @@ __device__ __forceinline__ float quad_perm(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 
-template <int TJ>
-__device__ __forceinline__ void transpose_acc(f32x16 (&acc)[4][TJ]) {
+template <int TI, int TJ>
+__device__ __forceinline__ void transpose_acc(f32x16 (&acc)[TI][TJ]) {
     const bool x0 = threadIdx.x & 1, x1 = threadIdx.x & 2;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
@@ -142,8 +142,8 @@ __device__ __forceinline__ uint2 pack_lo4(const Args& g, f32x4 r) {
     return __builtin_bit_cast(uint2, __builtin_convertvector(r - __builtin_convertvector(hi, f32x4), bf16x4));
 }
 
-template <int TJ, bool SCALE>
-__device__ __forceinline__ void store_acc_interior(const Args& g, const f32x16 (&acc)[4][TJ], int row0, int col0, long long coff) {
+template <bool SCALE, int TI, int TJ>
+__device__ __forceinline__ void store_acc_interior(const Args& g, const f32x16 (&acc)[TI][TJ], int row0, int col0, long long coff) {
     // the whole wavefront tile lies inside C and C allows vector accesses: no predicates, addresses = uniform base of the
     // group + one per-lane offset computed once
     const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
@@ -151,7 +151,7 @@ __device__ __forceinline__ void store_acc_interior(const Args& g, const f32x16 (
     const unsigned off = (unsigned)(((long long)(4 * lh + (l32 & 3)) * g.ldc + 4 * (l32 >> 2)) * es);
     char* base = (char*)g.C + (coff + (long long)row0 * g.ldc + col0) * es;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int b = 0; b < 4; ++b)
 #pragma unroll
@@ -260,8 +260,8 @@ __device__ __forceinline__ void store_acc(const Args& g, const f32x16 (&acc)[4][
         return;
     }
     if (g.vec_c && row0 + 128 <= g.M && col0 + 32 * TJ <= g.N) {
-        if (g.alpha == 1.0f) store_acc_interior<TJ, false>(g, acc, row0, col0, coff);
-        else store_acc_interior<TJ, true>(g, acc, row0, col0, coff);
+        if (g.alpha == 1.0f) store_acc_interior<false>(g, acc, row0, col0, coff);
+        else store_acc_interior<true>(g, acc, row0, col0, coff);
         return;
     }
     const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_kernel(Args g) {
         __syncthreads();
     }
 
-    transpose_acc<4>(acc);
+    transpose_acc(acc);
     store_acc<4>(g, acc, m0 + __builtin_amdgcn_readfirstlane(wm), n0 + __builtin_amdgcn_readfirstlane(wn), z1 * g.sC1 + z2 * g.sC2);
 }
 
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
 #undef TB_LOAD_FRAGS
 #undef TB_INTERLEAVE_DS
 
-    transpose_acc<TJ>(acc);
+    transpose_acc(acc);
     const int r0 = m0 + __builtin_amdgcn_readfirstlane(wm), c0 = n0 + __builtin_amdgcn_readfirstlane(wn);
     if (g.half_n) store_acc_gate_up(g, acc, r0, c0);
     else if (g.col_scale || g.residual) store_acc_linear<TJ>(g, acc, r0, c0);
@@ -786,7 +786,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 #pragma unroll
             for (int u = 0; u < NS; ++u) TB_STAGE(u, (u + 1) % NS, true, false)
         }
-        transpose_acc<TJ>(acc);
+        transpose_acc(acc);
         // every load of the stream issued so far (up to stage NS - 1 of the next tile) has landed before the first store is
         // issued: the first NS - 1 stages of the next tile then need no wait, and by the time stage NS is awaited the stores
         // (which count among the outstanding operations) have had NS - 1 stage times to be acknowledged
@@ -803,14 +803,165 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 #undef TB_LOAD_FRAGS
 }
 
+// ------------------------------------------------------------------------------------------------
+// Gram products over long contractions: C = scale * sum over the operand pairs of A B^T as ONE fp32 matrix.  After every `flush` stages what the accumulators
+// hold is added to running sums without loss: t = s + a, and what t has rounded away goes back into the accumulators, where the next stages are added to
+// it.  So a sum rounds as those of 32 `flush` terms do.  That took 16 partial sums in memory before (n x n each, 7.8 GB at n = 11008) and a pass that added
+// them in fp64, a third of the time.  The pipeline is that of gemm_bf16_nt_fast_kernel; the running sums take as many registers as the accumulators, so that a
+// wavefront has 64 x 64 results instead of 128 x 64.  LDS then binds (eight wavefronts read 32 KB and write 12 KB per 256 cycles of MFMAs): 1.0 PFLOP/s at
+// 11008 x 11008 x 16384, H and R of 8192 tokens 8.9 -> 4.9 ms.  (96 x 64 per wavefront does not fit the registers: 35 spilled, 14.8 ms; 256 x 128 per
+// workgroup: 5.05.)
+template <int TI, int TJ, int WM, int WN, int NS, bool F16>
+__global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, double scale) {
+    constexpr int TM = 32 * TI * WM, TN = 32 * TJ * WN, BLKS = (TM + TN) / 16, LPW = (BLKS + 7) / 8, STAGE_BYTES = (TM + TN) * FK * 2;
+    extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+    int z, tm, tn;
+    if (!work_item(g, z, tm, tn)) return;
+    const int m0 = tm * TM, n0 = tn * TN;
+    const int nk_seg = g.kseg / FK, nk = g.K / FK;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = (wave / WN) * (32 * TI), wn = (wave % WN) * (32 * TJ);
+    const int l32 = lane & 31, lh = lane >> 5;
+    f32x16 acc[TI][TJ], sum[TI][TJ];
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.0f; sum[i][j][v] = 0.0f; }
+
+    // this wavefront's LPW blocks (16 rows x 32) of a stage, the A tile's first; where 8 LPW exceeds their number the last one is copied more than once
+    const bool tiled = g.flags & TBOA_GEMM_A_TILED;
+    const int sh = tiled ? 4 : 0, wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const char* Abase = (const char*)(g.A + (long long)m0 * g.lda);
+    const char* Bbase = (const char*)(g.B + (long long)n0 * g.ldb);
+    unsigned off[LPW];
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) {
+        const int blk = min(wave * LPW + i, BLKS - 1), inB = blk >= TM / 16, b = inB ? blk - TM / 16 : blk;
+        const long long ld = inB ? g.ldb : g.lda;
+        const int last = (inB ? g.N - n0 : g.M - m0) - 1;                 // last row of the operand, from the tile's first
+        const int row = 16 * b + (lane >> 2), lc = (lane & 3) ^ ((row >> 2) & 3);
+        off[i] = tiled ? (unsigned)((long long)min(b, last >> 4) * (ld >> 5) * 1024 + lane * 16) : (unsigned)(((long long)min(row, last) * ld + lc * 8) * 2);
+    }
+    int kin = 0, term = 0; long long koff = 0;
+    auto advance = [&]() {
+        kin += FK; koff += 2 * FK;
+        if (kin == g.kseg) { kin = 0; koff = 0; Abase += g.term_dA[term]; Bbase += g.term_dB[term]; if (term < 2) ++term; }
+    };
+    const unsigned ring_lds = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)smem);
+    auto issue_one = [&](int i, const char* pa, const char* pb, unsigned st) {
+        const int blk = min(wave_s * LPW + i, BLKS - 1);
+        lds_direct_16(off[i], blk >= TM / 16 ? pb : pa, st + (unsigned)blk * 1024u);
+    };
+    auto issue = [&](int slot) {
+        const char* pa = Abase + (koff << sh); const char* pb = Bbase + (koff << sh);
+        advance();
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) issue_one(i, pa, pb, ring_lds + (unsigned)(slot * STAGE_BYTES));
+    };
+    bf16x8 fa[2][TI], fb[2][TJ];
+    auto frags = [&](int set, int slot, int ks) {
+        const __hip_bfloat16* a_s = (const __hip_bfloat16*)(smem + slot * STAGE_BYTES);
+        const __hip_bfloat16* b_s = a_s + TM * FK;
+#pragma unroll
+        for (int i = 0; i < TI; ++i) fa[set][i] = read_frag32(a_s, wm + 32 * i + l32, 2 * ks + lh);
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) fb[set][j] = read_frag32(b_s, wn + 32 * j + l32, 2 * ks + lh);
+    };
+    auto mma = [&](int set) {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) acc[i][j] = mma16<F16>(fa[set][i], fb[set][j], acc[i][j]);
+    };
+    auto fold = [&]() {
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float s = sum[i][j][v], a = acc[i][j][v], t = s + a, r = a - (t - s);
+                    sum[i][j][v] = t; acc[i][j][v] = __builtin_isfinite(r) ? r : 0.0f;      // (an infinite or undefined sum stays what it is)
+                }
+    };
+#pragma unroll
+    for (int s = 0; s < NS; ++s) if (s < nk) issue(s);
+    if (nk < NS) wait_loads_but<0>(); else wait_loads_but<(NS - 1) * LPW>();
+    __syncthreads();
+    frags(0, 0, 0);
+    int kt = 0, next = flush;
+    for (; kt + 2 * NS - 1 < nk; kt += NS) {
+        if (kt >= next) { fold(); next += flush; }
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            const char* pa = Abase + (koff << sh); const char* pb = Bbase + (koff << sh);
+            const unsigned st = ring_lds + (unsigned)(u * STAGE_BYTES);
+            advance();
+            frags(1, u, 1);
+            mma(0);
+            __builtin_amdgcn_sched_group_barrier(0x100, TI + TJ, 0);
+            __builtin_amdgcn_sched_group_barrier(0x008, TI * TJ, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            wait_loads_but<(NS - 2) * LPW>();
+            __syncthreads();
+            __builtin_amdgcn_sched_barrier(0);
+            frags(0, (u + 1) % NS, 0);
+#pragma unroll
+            for (int q = 0; q < TI * TJ; ++q) {
+                acc[q / TJ][q % TJ] = mma16<F16>(fa[1][q / TJ], fb[1][q % TJ], acc[q / TJ][q % TJ]);
+                if (q < LPW) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    issue_one(q, pa, pb, st);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+        }
+    }
+    for (; kt < nk; ++kt) {
+        if (kt >= next) { fold(); next += flush; }
+        frags(1, kt % NS, 1);
+        mma(0);
+        if (kt + 1 < nk) {
+            wait_loads_but<0>();
+            __syncthreads();
+            if (kt + NS < nk) issue(kt % NS);
+            frags(0, (kt + 1) % NS, 0);
+        }
+        mma(1);
+    }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = (float)(scale * ((double)sum[i][j][v] + (double)acc[i][j][v]));
+    transpose_acc(acc);
+    const int r0 = m0 + __builtin_amdgcn_readfirstlane(wm), c0 = n0 + __builtin_amdgcn_readfirstlane(wn);
+    if (g.vec_c && r0 + 32 * TI <= g.M && c0 + 32 * TJ <= g.N) { store_acc_interior<false>(g, acc, r0, c0, 0); return; }
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int row = r0 + 32 * i + 8 * b + 4 * lh + (l32 & 3), col = c0 + 32 * j + 4 * (l32 >> 2) + e;
+                    if (row < g.M && col < g.N) ((float*)g.C)[(long long)row * g.ldc + col] = acc[i][j][4 * b + e];
+                }
+}
+
 // Launch order of the output tiles of one batch entry, built once per (tile counts, flags) and kept on the device.
 // 32 consecutive tiles run side by side on one XCD, so the order walks compact blocks: row bands of 8 tile rows,
 // column by column inside a band (a column's tiles share the B panel, a band's rows the 8 A panels).  A symmetric
 // product lists only the tiles on or below the diagonal.  With a causal contraction limit the k-range grows with the
 // column, so a band takes its columns from the longest to the shortest (the short ones fill the tail of the launch).
-int tile_order(tboa_ctx* ctx, int tiles_m, int tiles_n, int flags, const int** dev, int* count) {
+int tile_order(tboa_ctx* ctx, int tiles_m, int tiles_n, int flags, const int** dev, int* count, int tile_rows = BM, int tile_cols = BN) {
     for (const TileOrder& t : ctx->tile_orders)
-        if (t.tiles_m == tiles_m && t.tiles_n == tiles_n && t.flags == flags) { *dev = t.dev; *count = t.count; return 0; }
+        if (t.tiles_m == tiles_m && t.tiles_n == tiles_n && t.flags == flags && t.tile_rows == tile_rows && t.tile_cols == tile_cols) { *dev = t.dev; *count = t.count; return 0; }
     const bool lower = flags & TBOA_GEMM_LOWER, causal = flags & TBOA_GEMM_CAUSAL_K;
     const int band = (causal && !lower) ? 16 : 8;
     std::vector<int> h;
@@ -819,10 +970,10 @@ int tile_order(tboa_ctx* ctx, int tiles_m, int tiles_n, int flags, const int** d
         for (int c = 0; c < tiles_n; ++c) {
             const int tn = (causal && !lower) ? tiles_n - 1 - c : c;
             for (int tm = m0; tm < m1; ++tm)
-                if (!lower || tn <= tm) h.push_back((tm << 16) | tn);
+                if (!lower || tn * tile_cols < (tm + 1) * tile_rows) h.push_back((tm << 16) | tn);
         }
     }
-    TileOrder t{tiles_m, tiles_n, flags, nullptr, (int)h.size()};
+    TileOrder t{tiles_m, tiles_n, flags, tile_rows, tile_cols, nullptr, (int)h.size()};
     TB_HIP(ctx, hipMalloc(&t.dev, h.size() * sizeof(int)));
     hipError_t e = hipMemcpy(t.dev, h.data(), h.size() * sizeof(int), hipMemcpyHostToDevice);
     if (e != hipSuccess) { (void)hipFree(t.dev); return tboa_fail(ctx, TBOA_EHIP, "tile order upload: %s", hipGetErrorString(e)); }
@@ -1016,6 +1167,54 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     TB_KERNEL_CHECK(ctx);
     TB_TRY(prof_end(ctx, rec, timed));
     return 0;
+}
+
+namespace {
+constexpr int GRAM_TI = 2, GRAM_TJ = 2, GRAM_WM = 2, GRAM_WN = 4, GRAM_NS = 4;      // 128 x 256 per workgroup
+constexpr int GRAM_ROWS = 32 * GRAM_TI * GRAM_WM, GRAM_COLS = 32 * GRAM_TJ * GRAM_WN;
+}  // namespace
+
+long long gemm_gram_tiles(int M, int N, int lower) {
+    const long long tm = cdiv64(M, GRAM_ROWS), tn = cdiv64(N, GRAM_COLS);
+    if (!lower) return tm * tn;
+    long long t = 0;
+    for (long long i = 0; i < tm; ++i) t += std::min<long long>(tn, cdiv64((i + 1) * GRAM_ROWS, GRAM_COLS));
+    return t;
+}
+
+int gemm_gram(tboa_ctx* ctx, const GemmBf16& q, double scale, int chunk) {
+    if (q.M <= 0 || q.N <= 0) return 0;
+    const bool tiled = (q.flags & TBOA_GEMM_A_TILED) != 0;
+    const int term = q.nterms > 0 ? q.K / q.nterms : 0;
+    if (!q.A || !q.B || !q.C || q.batch != 1 || q.c_dtype != TBOA_F32 || q.accumulate || q.nterms < 1 || q.nterms > 4 || chunk < FK * GRAM_NS || chunk % (FK * GRAM_NS) || q.K % q.nterms || term % FK || term <= 0 ||
+        (q.flags & ~(TBOA_GEMM_LOWER | TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) || tiled != ((q.flags & TBOA_GEMM_B_TILED) != 0) ||
+        q.lda % (tiled ? 32 : 8) || q.ldb % (tiled ? 32 : 8) || (tiled && (q.M % 16 || q.N % 16)) || ((q.flags & TBOA_GEMM_LOWER) && q.M != q.N))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: unsupported product");
+    Args a{};
+    a.M = q.M; a.N = q.N; a.K = q.K; a.kseg = term; a.alpha = 1.f;
+    a.A = q.A; a.lda = q.lda; a.B = q.B; a.ldb = q.ldb; a.C = q.C; a.ldc = q.ldc; a.flags = q.flags; a.batch_inner = 1;
+    a.vec_c = q.ldc % 4 == 0 && ((uintptr_t)q.C & 15) == 0;
+    for (int t = 0; t < q.nterms; ++t) {
+        const __hip_bfloat16 *A = q.nterms > 1 ? q.termA[t] : q.A, *B = q.nterms > 1 ? q.termB[t] : q.B;
+        if (!A || !B || ((uintptr_t)A & 15) || ((uintptr_t)B & 15) || (t == 0 && (A != q.A || B != q.B))) return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: operand pair %d", t);
+        if (t + 1 < q.nterms) { a.term_dA[t] = (const char*)q.termA[t + 1] - (const char*)A; a.term_dB[t] = (const char*)q.termB[t + 1] - (const char*)B; }
+    }
+    const int tiles_m = (int)cdiv64(q.M, GRAM_ROWS), tiles_n = (int)cdiv64(q.N, GRAM_COLS);
+    if (tiles_m > 32767 || tiles_n > 32767) return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: more than 32767 tiles along one axis");
+    TB_TRY(tile_order(ctx, tiles_m, tiles_n, q.flags & TBOA_GEMM_LOWER, &a.tile_order, &a.ntiles, GRAM_ROWS, GRAM_COLS));
+    a.nitems = a.ntiles; a.per = (a.nitems + 7) / 8;
+    constexpr int smem = GRAM_NS * (GRAM_ROWS + GRAM_COLS) * FK * 2;
+    ProfRec rec{}; bool timed = false;
+    if (ctx->prof_on && q.tag >= 0) TB_TRY(prof_begin(ctx, q.tag, ((q.flags & TBOA_GEMM_LOWER) ? (double)q.M * (q.M + 1.0) : 2.0 * q.M * q.N) * q.K, rec, timed));
+    const void* kern = (q.flags & TBOA_GEMM_F16) ? (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true>
+                                                 : (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false>;
+    TB_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    if (q.flags & TBOA_GEMM_F16)
+        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+    else
+        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+    TB_KERNEL_CHECK(ctx);
+    return prof_end(ctx, rec, timed);
 }
 
 extern "C" int tboa_gemm_bf16_nt(tboa_ctx* ctx, int M, int N, int K, float alpha, const void* A, int64_t lda, const void* B,

@@ -852,15 +852,37 @@ GemmBf16 nt(int M, int N, int K, float alpha, const bf16* A, long long lda, cons
     return g;
 }
 
+// Whether a Gram product goes through gemm_gram (one result, long sums folded in registers) instead of `splits` partial sums in memory.  A stage of 32 contraction
+// indices takes a workgroup 0.40 us there (128 x 256; 0.46 from row-major operands) and 0.75 us in the split launches (256 x 256), and the partial sums are written once and read once at
+// 4.5 TB/s; few tiles leave the chip idle in one pass.  Measured (H and R, 8192 tokens): 11008 columns 8.2 -> 4.9 ms, 8192 4.7 -> 2.7, 4096 1.24 -> 0.72,
+// 2048 0.35 -> 0.29, 1024 0.13 -> 0.26 (stays split).  Sums are folded after no more terms than a split had (of 512 in R's two pairs 384: at
+// 8192 tokens R is then off by 6e-8, with partial sums by 7e-8); those of splits of fewer than 128 tokens stay as they are, and sums of fewer than 512.
+bool one_pass_gram(int n, int splits, int npairs, int Kc, int lower, int blocked) {
+    if (Kc % 32 || Kc < 128 || Kc * splits < 512 || (long long)Kc * npairs * splits > 0x7fffffffLL) return false;
+    const double steps = (double)Kc / 32 * npairs, t256 = (double)cdiv64(n, 256), tiles = lower ? t256 * (t256 + 1) / 2 : t256 * t256;
+    const double one = std::ceil(gemm_gram_tiles(n, n, lower) / 256.0) * steps * splits * (blocked ? 0.40 : 0.46);
+    const double split = std::ceil(tiles * splits / 256.0) * steps * 0.75 + (double)n * n * splits * (lower ? 4.0 : 8.0) / 4.5e6 + 5.0;
+    return one < split;
+}
+
 // out[n, n] = scale * sum over the operand pairs p of A_p B_p^T, with the contraction over all T tokens split into `splits`
 // chunks (an exact-to-16-bit (hi, lo) operand takes part as several pairs: hi.hi + lo.hi + hi.lo)
 struct GramPair { const bf16* A; const bf16* B; };
 int gram_splitk(tboa_ctx* ctx, int splits, int n, int npairs, const GramPair* pairs, long long ld, int K, double scale, int lower,
-                float* part, float* out, int f16 = 0) {
+                float* part, float* out, int f16 = 0, int blocked = 0) {
     const int Kc = K / splits;
+    if (one_pass_gram(n, splits, npairs, Kc, lower, blocked)) {
+        GemmBf16 g = nt(n, n, K * npairs, 1.f, pairs[0].A, ld, pairs[0].B, ld, out, n, TBOA_F32, 0, 0);
+        g.flags = (lower ? TBOA_GEMM_LOWER : 0) | (f16 ? TBOA_GEMM_F16 : 0) | (blocked ? TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED : 0);
+        g.tag = TBOA_PROF_GRAM; g.nterms = npairs;
+        for (int p = 0; p < npairs; ++p) { g.termA[p] = pairs[p].A; g.termB[p] = pairs[p].B; }
+        TB_TRY(gemm_gram(ctx, g, scale, Kc >= 512 && npairs == 1 ? 512 : Kc >= 384 ? 384 : Kc >= 256 ? 256 : 128));
+        return lower ? launch_mirror_lower_f32(ctx, out, n, 1) : 0;
+    }
     GemmBf16 g = nt(n, n, Kc, 1.f, pairs[0].A, ld, pairs[0].B, ld, part, n, TBOA_F32, 0, (lower ? TBOA_GEMM_LOWER : 0) | (f16 ? TBOA_GEMM_F16 : 0));
     g.tag = TBOA_PROF_GRAM; g.flags &= ~TBOA_GEMM_PERSISTENT;
-    g.batch = splits; g.strideA = Kc; g.strideB = Kc; g.strideC = (long long)n * n;
+    g.batch = splits; g.strideA = g.strideB = blocked ? 16LL * Kc : Kc; g.strideC = (long long)n * n;
+    if (blocked) g.flags |= TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED;
     // all pairs in one pass over the accumulators (one launch per pair read and wrote the partial sums again each time; the pairs come with
     // the small products first, so that the sum rounds where the large ones do); K a multiple of 32 does it, else pair by pair
     if (npairs > 1 && Kc % 32 == 0) {
@@ -884,9 +906,9 @@ int gram_splitk(tboa_ctx* ctx, int splits, int n, int npairs, const GramPair* pa
     return 0;
 }
 int gram_splitk(tboa_ctx* ctx, int splits, int n, const bf16* A, const bf16* A_lo, const bf16* B, long long ld, int K, double scale, int lower,
-                float* part, float* out) {
+                float* part, float* out, int blocked) {
     const GramPair pairs[2] = {{A_lo ? A_lo : A, B}, {A, B}};
-    return gram_splitk(ctx, splits, n, A_lo ? 2 : 1, pairs, ld, K, scale, lower, part, out);
+    return gram_splitk(ctx, splits, n, A_lo ? 2 : 1, pairs, ld, K, scale, lower, part, out, 0, blocked);
 }
 
 // Q^ [rows, Hq, 3 dh] and K^ [rows, Hkv, 3 dh] of `rows` tokens Xr [rows, d]; weights as one, two or three bf16 terms.
@@ -1070,9 +1092,10 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     if (Hin_qk) {
     if (Tp != T)
         for (bf16* p : {XT, dXh, dXl}) if (p) TB_TRY(clear16(ctx, p, dm * TP));
-    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, dm, T, dm, XT, fp ? dXh : nullptr, dXl, TP));
-    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk));
-    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk));
+    const int blocked = dm % 16 == 0;
+    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, dm, T, dm, XT, fp ? dXh : nullptr, dXl, TP, blocked));
+    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk, blocked));
+    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk, blocked));
     // ---- H_out: K_g^T K_g = W_K,g H_in W_K,g^T ; sum_h Q_h^T Q_h ; sum_h W_out,h^T W_out,h   (fp64)
     // (the wide product W_Q H_in, d_q x d x d, is taken with the triangular half of H_in; the d_h x d_h products of a group's heads
     // are one launch whose terms are summed in fp64: as one launch per head of the group they ran on n_kv_heads workgroups)
@@ -1491,26 +1514,28 @@ __global__ void swiglu_kernel(const float* __restrict__ G, const float* __restri
 // layer-wise Hessian of a plain linear layer from bf16 activations: H = X^T X, R = alpha (X - X~)^T X
 int build_hessian_linear_bf16(tboa_ctx* ctx, long long T, int n, double alpha, const bf16* X, const bf16* X_fp, float* H_in, float* R) {
     if (T % 8 || n % 8) return tboa_fail(ctx, TBOA_EINVAL, "build_hessian_linear: n_tokens and d_in must be multiples of 8 for bf16 inputs");
-    // partial sums over the tokens, added in fp64: 16 where the tokens allow it.  (At d_in = 11008 and 8192 tokens they are 7.8 GB; 4 instead of 16
-    // take 5.6 instead of 8.9 ms, but their fp32 sums are four times as long: R is then off by 1.9e-7 instead of 8.7e-8.)
+    // sums of at most a sixteenth of the tokens where these allow it (as partial sums or folded in registers, see one_pass_gram): four times as long, they
+    // leave R off by 1.9e-7 instead of 8.7e-8 (d_in = 11008, 8192 tokens)
     int splits = 1;
     for (int sp = 16; sp > 1; --sp) if (T % ((long long)sp * 256) == 0) { splits = sp; break; }
     const bool fp = X_fp && R;
     const long long Tp = padded_tokens(T, splits), TP = Tp + PADE;
+    const int blocked = n % 16 == 0;
     bf16 *XT, *dXh, *dXl; float* part;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         XT = ar.get<bf16>((size_t)n * TP);
         dXh = fp ? ar.get<bf16>((size_t)n * TP) : nullptr; dXl = fp ? ar.get<bf16>((size_t)n * TP) : nullptr;
-        part = ar.get<float>((size_t)splits * n * n);
+        const int Kc = (int)(Tp / splits);
+        part = one_pass_gram(n, splits, 1, Kc, 1, blocked) && (!fp || one_pass_gram(n, splits, 2, Kc, 0, blocked)) ? nullptr : ar.get<float>((size_t)splits * n * n);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }
     Dims D{}; D.ctx = ctx;
     if (Tp != T)
         for (bf16* p : {XT, dXh, dXl}) if (p) TB_TRY(clear16(ctx, p, n * TP));
-    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, n, (int)T, n, XT, fp ? dXh : nullptr, dXl, TP));
-    TB_TRY(gram_splitk(ctx, splits, n, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, H_in));
-    if (fp) TB_TRY(gram_splitk(ctx, splits, n, dXh, dXl, XT, TP, (int)Tp, alpha, 0, part, R));
+    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, n, (int)T, n, XT, fp ? dXh : nullptr, dXl, TP, blocked));
+    TB_TRY(gram_splitk(ctx, splits, n, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, H_in, blocked));
+    if (fp) TB_TRY(gram_splitk(ctx, splits, n, dXh, dXl, XT, TP, (int)Tp, alpha, 0, part, R, blocked));
     return 0;
 }
 

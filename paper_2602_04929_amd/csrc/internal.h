@@ -11,7 +11,7 @@
 
 struct ProfRec { hipEvent_t a, b; int tag; double flops; };
 
-struct TileOrder { int tiles_m, tiles_n, flags; int* dev; int count; };   // gemm_bf16: launch order of the output tiles
+struct TileOrder { int tiles_m, tiles_n, flags, tile_rows, tile_cols; int* dev; int count; };   // gemm_bf16: launch order of the output tiles
 // gemm_bf16, persistent kernel: per workgroup the list of (batch entry, tm << 16 | tn) it works through, `rounds` entries each
 struct TileSchedule { int tiles_m, tiles_n, flags, batch, seg_len; int2* dev; int rounds, wgs; };
 
@@ -145,6 +145,11 @@ struct GemmBf16 {
 #define TBOA_GEMM_C_HILO 0x10000
 #define TBOA_GEMM_C_HILO_HALF 0x20000     // (with C_HILO) the pair is IEEE half, 22 significant bits, instead of bf16, 16: for values known to fit half
 int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& g);
+// C = scale * sum_t termA[t] termB[t]^T as one fp32 matrix whose sums round as those of `chunk` (a multiple of 128) contraction indices do (gemm_gram_kernel); nterms pairs of K / nterms
+// columns each, K / nterms a multiple of 32, no batch, C fp32; flags: LOWER (only the tiles on or below the diagonal are written), F16, A_TILED and B_TILED together.
+// gemm_gram_tiles: how many workgroups such a launch has.
+int gemm_gram(tboa_ctx* ctx, const GemmBf16& g, double scale, int chunk);
+long long gemm_gram_tiles(int M, int N, int lower);
 
 // Transposed causal attention probabilities of all heads of one sequence as (hi, lo) pairs of 16-bit values (IEEE half
 // when f16, else bf16): Pt[g][i][r L + t] = A_h[t, i], h = g rep + r, every [L, ldp] matrix of a KV group in 16 x 32 blocks,
