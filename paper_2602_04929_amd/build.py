@@ -20,7 +20,8 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=o
 
 # Per-file flags.  gemm_f64: keep the 128 fp64 accumulators in ordinary VGPRs (the kernel fits in 256 registers); with the
 # default AGPR form the compiler copies all of them between the two register files on every k-step.
-EXTRA = {"gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+EXTRA = {"gemm_f64.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"], "sweep.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "factor.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def _compile(src):

@@ -11,89 +11,118 @@ namespace {
 
 constexpr int NB = TB_FACT_NB;
 
-// 1 / p to an ulp for a normal p away from the ends of the exponent range (others are divided), without the scaling steps of a division
-__device__ __forceinline__ double reciprocal(double p) {
-    if (!(p > 1e-290 && p < 1e290)) return 1.0 / p;
-    double r = __builtin_amdgcn_rcp(p);
+// v / p for positive p, the quotient to an ulp or two, without the scaling steps and branches of a division
+__device__ __forceinline__ double over_pivot(double v, double p) {
+    const double m = __builtin_amdgcn_frexp_mant(p);
+    double r = __builtin_amdgcn_rcp(m);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) r = __builtin_fma(__builtin_fma(-p, r, 1.0), r, r);
-    return r;
+    for (int i = 0; i < 3; ++i) r = __builtin_fma(__builtin_fma(-m, r, 1.0), r, r);
+    return ldexp(v, -__builtin_amdgcn_frexp_exp(p)) * (p < INFINITY ? r : 0.0);
+}
+
+__device__ __forceinline__ double lane_value(double v, int lane) {      // of a lane that is the same for the wavefront
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane), hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+    return __hiloint2double(hi, lo);
 }
 
 // status[0] = 1 + column of the first non-positive pivot (0 = fine), status[1] = batch index
 //
-// Latency-bound (one workgroup per matrix, between the updates of the factorisation).  Thread (tx, ty) keeps the rows ty, ty + 4, ..
-// of column tx in registers; a step exchanges one column (one row, in the inverse) through LDS and has one barrier.  The
-// factorisation works on unscaled columns, V[r][r2] -= c[r] c[r2] / pivot, so that no step waits for a square root, and the columns
-// are scaled at the end.  100 -> 55 us per 64 x 64 block (the kernel alone on the GPU), against the version with everything in LDS, three barriers and a
-// division per element.
+// Latency-bound (one workgroup per matrix, between the updates of the factorisation): 64 columns that wait for each other.  The block is taken as 4 x 4 tiles of
+// 16 x 16.  A tile on the diagonal is factored by one wavefront in registers, lane = column: a column reaches the other lanes by v_readlane, with
+// no LDS and no barrier between two steps, on unscaled columns (V[r][r2] -= c[r] c[r2] / pivot), so that no step waits for a square root.  Then one wavefront
+// solves for the tiles above it (lane = row), a second for the 16 rows of the inverse (lane = column), both by substitution, and fp64 MFMAs take what
+// they found from the tiles left of and above it.
+// 55 -> 28 us per 64 x 64 block (the kernel alone on the GPU) against a step with one barrier for every column of the factorisation and of the inverse.
 __global__ __launch_bounds__(256) void diag_factor_kernel(double* __restrict__ H, int n, int j0, int bs,
                                                           double* __restrict__ dinv, int blk, int nblk, int* status) {
-    __shared__ __attribute__((aligned(16))) double col[2][4][NB / 4];      // the column (row) of a step, by (row % 4, row / 4)
-    __shared__ double VT[NB][4][NB / 4 + 1];                                // column c of V, rows as in col
-    __shared__ double piv[NB], dinvs[NB];
-    __shared__ double row[2][NB];
-    const int b = blockIdx.x, t = threadIdx.x, tx = t & 63, ty = t >> 6;
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    constexpr int TP = NB + 1;                                             // odd pitch: 16 rows fall into different banks
+    __shared__ double S[NB][TP], W[NB][TP];                                // the block, then V; the right-hand side I, then W = V^-1
+    __shared__ __attribute__((aligned(16))) double Q[16][16], dq[16];      // columns of the tile on the diagonal, 1 / its diagonal
+    const int b = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, l16 = lane & 15, lk = lane >> 4;
     double* Hb = H + (long long)b * n * n;
-    double v[NB / 4];
-#pragma unroll
-    for (int i = 0; i < NB / 4; ++i) {
-        const int r = ty + 4 * i;
-        v[i] = (tx < bs && r <= tx) ? Hb[(long long)(j0 + r) * n + j0 + tx] : 0.0;
+    // the upper triangle, mirrored; beyond bs the identity
+    for (int i = t; i < NB * NB; i += 256) {
+        const int r = i >> 6, c = i & 63;
+        W[r][c] = r == c ? 1.0 : 0.0;
+        if (r > c) continue;
+        const double v = c < bs ? Hb[(long long)(j0 + r) * n + j0 + c] : (r == c ? 1.0 : 0.0);
+        S[r][c] = v; if (r < c) S[c][r] = v;
     }
-    // H_jj = V V^T, V upper: columns from the last to the first
-    for (int c = bs - 1; c >= 0; --c) {
-        const int buf = c & 1;
-        if (tx == c) {
+    __syncthreads();
+    const int nt = (bs + 15) / 16;
+    // H_jj = V V^T, V upper, and V W = I: 16 columns (rows of W) at a time from the last to the first
+    for (int q = nt - 1; q >= 0; --q) {
+        if (wave == 0) {
+            double v[16], piv = 1.0; int bad = -1;
 #pragma unroll
-            for (int i = 0; i < NB / 4; ++i) col[buf][ty][i] = v[i];
+            for (int r = 0; r < 16; ++r) v[r] = S[16 * q + r][16 * q + l16];
+#pragma unroll
+            for (int c = 15; c >= 0; --c) {
+                double p = lane_value(v[c], c);
+                bad = p > 0.0 || bad >= 0 ? bad : c;
+                p = p > 0.0 ? p : 1.0;
+                piv = l16 == c ? p : piv;
+                const double f = l16 < c ? over_pivot(v[c], p) : 0.0;      // (the tile is symmetric: V[l16][c] = v[c])
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (r < c) v[r] = __builtin_fma(-lane_value(v[r], c), f, v[r]);
+            }
+            if (bad >= 0 && t == 0) { if (atomicCAS(&status[0], 0, 1 + j0 + 16 * q + bad) == 0) status[1] = b; }
+            const double dv = sqrt(piv), di = 1.0 / dv;
+            if (lk == 0) {
+                dq[l16] = di;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    v[r] = r < l16 ? v[r] * di : (r == l16 ? dv : 0.0);    // a non-positive pivot leaves 1 on the diagonal
+                    S[16 * q + r][16 * q + l16] = v[r]; Q[l16][r] = v[r];
+                }
+            }
         }
         __syncthreads();
-        double p = col[buf][c & 3][c >> 2];
-        if (!(p > 0.0)) {
-            if (t == 0) { if (atomicCAS(&status[0], 0, 1 + j0 + c) == 0) status[1] = b; }
-            p = 1.0;
-        }
-        if (t == 0) piv[c] = p;
-        if (tx < c) {
-            const double f = col[buf][tx & 3][tx >> 2] * reciprocal(p);
+        // x V_qq^T = h for the rows above (first wavefront), V_qq w = e for the columns from this tile's on (second)
+        if (wave < 2) {
+            const bool in = wave == 0 ? lane < 16 * q : lane >= 16 * q;
+            double x[16];
 #pragma unroll
-            for (int i = 0; i < NB / 4; ++i) v[i] = __builtin_fma(-col[buf][ty][i], f, v[i]);
+            for (int r = 0; r < 16; ++r) x[r] = wave == 0 ? S[lane][16 * q + r] : W[16 * q + r][lane];
+#pragma unroll
+            for (int c = 15; c >= 0; --c) {
+                x[c] *= dq[c];
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    if (r < c) x[r] = __builtin_fma(-Q[c][r], x[c], x[r]);
+            }
+            if (in) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) if (wave == 0) S[lane][16 * q + r] = x[r]; else W[16 * q + r][lane] = x[r];
+            }
         }
+        __syncthreads();
+        // H[i, j] -= V[i, q] V[j, q]^T, i <= j < q, and I[i, j] -= V[i, q] W[q, j], i < q <= j
+        const int nh = q * (q + 1) / 2, nw = q * (nt - q);
+        for (int e = wave; e < nh + nw; e += 4) {
+            const bool sym = e < nh;
+            int j = 0, i = sym ? e : (e - nh) % q;
+            if (sym) { while (i > j) { i -= j + 1; ++j; } } else j = q + (e - nh) / q;
+            v4d x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int k = 16 * q + 4 * s + lk;
+                x = __builtin_amdgcn_mfma_f64_16x16x4f64(S[16 * i + l16][k], sym ? S[16 * j + l16][k] : W[k][16 * j + l16], x, 0, 0, 0);
+            }
+            double (&T)[NB][TP] = sym ? S : W;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) T[16 * i + lk + 4 * k][16 * j + l16] -= x[k];
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const double dv = tx < bs ? sqrt(piv[tx]) : 1.0, di = 1.0 / dv;
-#pragma unroll
-    for (int i = 0; i < NB / 4; ++i) {
-        const int r = ty + 4 * i;
-        v[i] = r < tx ? v[i] * di : (r == tx ? dv : 0.0);                  // a non-positive pivot leaves 1 on the diagonal
-        VT[tx][ty][i] = v[i];
-    }
-    if (ty == 0) dinvs[tx] = di;
-    __syncthreads();
-    // W = V^-1 (upper), V W = I solved for all columns at once from the last row up: row r of W is final once the
-    // contributions of the rows below it have been taken from the right-hand side, and is then taken from the rows above
-    double w[NB / 4];
-#pragma unroll
-    for (int i = 0; i < NB / 4; ++i) w[i] = (ty + 4 * i == tx && tx < bs) ? 1.0 : 0.0;
-#pragma unroll
-    for (int i = NB / 4 - 1; i >= 0; --i)
-        for (int q = 3; q >= 0; --q) {
-            const int r = 4 * i + q;
-            if (r >= bs) continue;                                          // uniform
-            if (ty == q) { w[i] *= dinvs[r]; row[r & 1][tx] = w[i]; }
-            __syncthreads();
-            const double wr = row[r & 1][tx];
-#pragma unroll
-            for (int k = 0; k <= i; ++k)
-                if (k < i || ty < q) w[k] = __builtin_fma(-VT[r][ty][k], wr, w[k]);
-        }
     double* D = dinv + ((long long)b * nblk + blk) * NB * NB;
-#pragma unroll
-    for (int i = 0; i < NB / 4; ++i) {
-        const int r = ty + 4 * i;
-        D[r * NB + tx] = (r < bs && tx < bs) ? w[i] : 0.0;
-        if (r < bs && tx < bs) Hb[(long long)(j0 + r) * n + j0 + tx] = v[i];      // lower part of the block becomes zero
+    for (int i = t; i < NB * NB; i += 256) {
+        const int r = i >> 6, c = i & 63;
+        const bool in = r < bs && c < bs;
+        D[i] = in ? W[r][c] : 0.0;
+        if (in) Hb[(long long)(j0 + r) * n + j0 + c] = r <= c ? S[r][c] : 0.0;      // lower part of the block becomes zero
     }
 }
 
