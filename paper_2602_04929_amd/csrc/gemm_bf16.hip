@@ -27,10 +27,15 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// one 32 x 32 x 16 matrix-core step on 16-bit operands held as 8 x 16 bits per lane; F16: the bits are IEEE half, else bf16
-template <bool F16>
+// one matrix-core step on operands held as 16 bytes per lane: 32 x 32 x 16 of IEEE half (KIND 1) or bf16 (KIND 0), or 32 x 32 x 32 of signed bytes (KIND 2), whose
+// accumulators are the bits of 32-bit integers
+template <int KIND>
 __device__ __forceinline__ f32x16 mma16(bf16x8 a, bf16x8 b, f32x16 c) {
-    if constexpr (F16) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
+    if constexpr (KIND == 2) {
+        typedef int i32x4 __attribute__((ext_vector_type(4)));
+        typedef int i32x16 __attribute__((ext_vector_type(16)));
+        return __builtin_bit_cast(f32x16, __builtin_amdgcn_mfma_i32_32x32x32_i8(__builtin_bit_cast(i32x4, a), __builtin_bit_cast(i32x4, b), __builtin_bit_cast(i32x16, c), 0, 0, 0));
+    } else if constexpr (KIND == 1) return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
 
@@ -252,6 +257,31 @@ __device__ __forceinline__ void store_acc_gate_up(const Args& g, const f32x16 (&
         }
 }
 
+// results as they are (the bits of integers)
+template <int TI, int TJ>
+__device__ __forceinline__ void store_acc_bits(const Args& g, const f32x16 (&acc)[TI][TJ], int row0, int col0, long long coff) {
+    const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
+    const bool whole = g.vec_c && col0 + 32 * TJ <= g.N;
+    float* C = (float*)g.C + coff;
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int row = row0 + 32 * i + 8 * b + 4 * lh + (l32 & 3);
+            if (row >= g.M) continue;
+#pragma unroll
+            for (int j = 0; j < TJ; ++j) {
+                const int col = col0 + 32 * j + 4 * (l32 >> 2);
+                float* p = C + (long long)row * g.ldc + col;
+                const f32x4 r = {acc[i][j][4 * b], acc[i][j][4 * b + 1], acc[i][j][4 * b + 2], acc[i][j][4 * b + 3]};
+                if (whole) *(f32x4*)p = r;
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) if (col + e < g.N) p[e] = r[e];
+            }
+        }
+}
+
 template <int TJ>
 __device__ __forceinline__ void store_acc(const Args& g, const f32x16 (&acc)[4][TJ], int row0, int col0, long long coff) {
     if (g.flags & TBOA_GEMM_C_TILED) {
@@ -440,7 +470,7 @@ template <int N>
 __device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
 // NS: stages in the LDS ring (NS - 1 of them in flight while one is multiplied)
-template <int WAVES, int NS, bool F16>
+template <int WAVES, int NS, int KIND>
 __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     constexpr int TJ = (WAVES == 8) ? 2 : 4;         // 32-wide MFMA tile columns per wavefront
     constexpr int LPW = 16 / WAVES;                  // 1 KB blocks of the A tile (and of the B tile) per wavefront and stage
@@ -460,7 +490,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     int nseg = g.kseg > 0 ? g.K / g.kseg : 1;
     if (g.segs) nseg = min(nseg, __builtin_amdgcn_readfirstlane(g.segs[z]));
     int kend = seg_len;
-    if (causal) kend = min(kend, n0 + BN);
+    if (causal) kend = min(kend, KIND == 2 ? (n0 + BN) / 2 : n0 + BN);      // (bytes: two contraction indices an element)
     const int kbeg = (g.flags & TBOA_GEMM_KLO) ? min(kend, max(m0, n0)) : 0;      // a multiple of the tile size
     const int nk_seg = (kend - kbeg) / FK;         // kend is a multiple of 32 on this path
     const int nk = nk_seg * nseg;
@@ -535,7 +565,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
 #define TB_MMA(SET)                                                                                         \
     _Pragma("unroll") for (int i = 0; i < 4; ++i)                                                           \
         _Pragma("unroll") for (int jj = 0; jj < TJ; ++jj)                                                   \
-            acc[i][jj] = mma16<F16>(fa[SET][i], fb[SET][jj], acc[i][jj]);
+            acc[i][jj] = mma16<KIND>(fa[SET][i], fb[SET][jj], acc[i][jj]);
 #define TB_INTERLEAVE_DS                                                                                    \
     __builtin_amdgcn_sched_group_barrier(0x100, 4 + TJ, 0);                                                 \
     __builtin_amdgcn_sched_group_barrier(0x008, 4 * TJ, 0);
@@ -560,8 +590,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
         {                                                                                                   \
             _Pragma("unroll") for (int i = 0; i < 4; ++i) {                                                 \
                 _Pragma("unroll") for (int jj = 0; jj < TJ; jj += 2) {                                      \
-                    acc[i][jj] = mma16<F16>(fa[1][i], fb[1][jj], acc[i][jj]); \
-                    acc[i][jj + 1] = mma16<F16>(fa[1][i], fb[1][jj + 1], acc[i][jj + 1]); \
+                    acc[i][jj] = mma16<KIND>(fa[1][i], fb[1][jj], acc[i][jj]); \
+                    acc[i][jj + 1] = mma16<KIND>(fa[1][i], fb[1][jj + 1], acc[i][jj + 1]); \
                     const int q_ = (i * TJ + jj) / 2;              /* 0 .. 2 LPW - 1 */                       \
                     const unsigned blk_ = (unsigned)(wave_s * LPW + q_ / 2) * 1024u;                        \
                     __builtin_amdgcn_sched_barrier(0);                                                      \
@@ -594,14 +624,19 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
         __syncthreads();
         TB_LOAD_FRAGS(0, 0, 0)
         int kt = 0;
-        const int kscale = (g.last_scale != 1.f && nseg > 1) ? nk - nk_seg : -1;      // the stage at which the last term begins
+        // the stage at which the last term begins; bytes: at which the next one does
+        int kscale = nseg > 1 && (KIND == 2 || g.last_scale != 1.f) ? (KIND == 2 ? nk_seg : nk - nk_seg) : -1;
         auto rescale = [&]() {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
 #pragma unroll
                 for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[i][j][v] *= g.last_scale;
+                    for (int v = 0; v < 16; ++v) {
+                        if constexpr (KIND == 2) acc[i][j][v] = __int_as_float(__float_as_int(acc[i][j][v]) << 8);      // (the digits of B, the highest first)
+                        else acc[i][j][v] *= g.last_scale;
+                    }
+            if (KIND == 2) kscale += nk_seg;
         };
         // steady state, unrolled over the ring so that slot numbers are constants: the loads of stages kt+2 and kt+3 may
         // stay in flight while stage kt+1 is awaited
@@ -623,7 +658,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
 
     transpose_acc(acc);
     const int r0 = m0 + __builtin_amdgcn_readfirstlane(wm), c0 = n0 + __builtin_amdgcn_readfirstlane(wn);
-    if (g.half_n) store_acc_gate_up(g, acc, r0, c0);
+    if constexpr (KIND == 2) store_acc_bits(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
+    else if (g.half_n) store_acc_gate_up(g, acc, r0, c0);
     else if (g.col_scale || g.residual) store_acc_linear<TJ>(g, acc, r0, c0);
     else store_acc<TJ>(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
 }
@@ -1082,8 +1118,9 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     if (!attr_set) {
         TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-        TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_fast_kernel<8, 4, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
-        TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_fast_kernel<8, 4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
+        TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_fast_kernel<8, 4, 0>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
+        TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_fast_kernel<8, 4, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
+        TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_fast_kernel<8, 4, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
         TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_stream_kernel<4, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
         TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_bf16_nt_stream_kernel<4, true>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_fast));
         attr_set = true;
@@ -1095,6 +1132,9 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
         return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: a scaled result is the single bf16 result of one product of the dispatched LDS-direct kernel");
     if (q.gate_up && (q.N % 64 || q.ldc % 4 || ((uintptr_t)q.C & 7) || 2LL * q.N * q.ldb >= (1LL << 32)))
         return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: the gated product needs whole 32s of columns and its weights below 4 GiB");
+    if ((q.flags & TBOA_GEMM_I8) && (!fast || q.c_dtype != TBOA_F32 || q.accumulate || q.alpha != 1.f || q.kseg || q.last_scale != 1.f ||
+                                     (q.flags & (TBOA_GEMM_PERSISTENT | TBOA_GEMM_KLO | TBOA_GEMM_F16)) || (q.nterms > 1 && q.K % (FK * 4))))
+        return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: products of bytes leave 32-bit integers, by the dispatched LDS-direct kernel");
     if ((q.flags & (TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) && !fast) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: blocked operands are read by the LDS-direct kernel only");
     Args a{};
     a.sched = nullptr; a.rounds = 0;
@@ -1119,7 +1159,7 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on && q.tag >= 0) {
         const int nseg = q.kseg > 0 ? q.K / q.kseg : 1;
-        const double ks = q.kseg > 0 ? q.kseg : q.K;
+        const double ks = (q.kseg > 0 ? q.kseg : q.K) * ((q.flags & TBOA_GEMM_I8) ? 2.0 : 1.0);
         double mnk = (double)q.M * q.N * ks;
         if ((q.flags & TBOA_GEMM_KLO) && q.M == q.N) {      // sum over (i, j) of (ks - max(i, j)); the symmetric product: i >= j only
             const double n = q.M;
@@ -1160,8 +1200,9 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
         if (f16) hipLaunchKernelGGL((gemm_bf16_nt_stream_kernel<4, true>), dim3(wgs), dim3(512), smem_fast, ctx->stream, a);
         else hipLaunchKernelGGL((gemm_bf16_nt_stream_kernel<4, false>), dim3(wgs), dim3(512), smem_fast, ctx->stream, a);
     } else if (fast) {
-        if (f16) hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<8, 4, true>), dim3(nwg), dim3(512), smem_fast, ctx->stream, a);
-        else hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<8, 4, false>), dim3(nwg), dim3(512), smem_fast, ctx->stream, a);
+        if (q.flags & TBOA_GEMM_I8) hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<8, 4, 2>), dim3(nwg), dim3(512), smem_fast, ctx->stream, a);
+        else if (f16) hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<8, 4, 1>), dim3(nwg), dim3(512), smem_fast, ctx->stream, a);
+        else hipLaunchKernelGGL((gemm_bf16_nt_fast_kernel<8, 4, 0>), dim3(nwg), dim3(512), smem_fast, ctx->stream, a);
     } else if (f16) hipLaunchKernelGGL(gemm_bf16_nt_kernel<true>, dim3(nwg), dim3(256), smem, ctx->stream, a);
     else hipLaunchKernelGGL(gemm_bf16_nt_kernel<false>, dim3(nwg), dim3(256), smem, ctx->stream, a);
     TB_KERNEL_CHECK(ctx);

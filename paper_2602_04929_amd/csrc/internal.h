@@ -144,6 +144,9 @@ struct GemmBf16 {
 // internal flag: a 16-bit result leaves as an exact-to-16-bit pair of bf16 values (hi into C, lo into C2), whatever the operands
 #define TBOA_GEMM_C_HILO 0x10000
 #define TBOA_GEMM_C_HILO_HALF 0x20000     // (with C_HILO) the pair is IEEE half, 22 significant bits, instead of bf16, 16: for values known to fit half
+// internal flag: A and B hold signed bytes, two in every 16-bit element (K, lda, ldb and strides count elements; 16 x 32 blocks hold 64 bytes of a row), C receives
+// 32-bit integers.  Several terms are digits of B to the base 256, the highest first: C = sum_t 256^(terms - 1 - t) A termB[t]^T, modulo 2^32.
+#define TBOA_GEMM_I8 0x40000
 int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& g);
 // C = scale * sum_t termA[t] termB[t]^T as one fp32 matrix whose sums round as those of `chunk` (a multiple of 128) contraction indices do (gemm_gram_kernel); nterms pairs of K / nterms
 // columns each, K / nterms a multiple of 32, no batch, C fp32; flags: LOWER (only the tiles on or below the diagonal are written), F16, A_TILED and B_TILED together.

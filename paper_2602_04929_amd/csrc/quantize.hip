@@ -120,33 +120,46 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
 // ---- two-phase search: approximate costs of all candidates on the 16-bit matrix cores, exact fp64 costs of the few
 // candidates within GRID_TAU of the approximate minimum.
 //
-// delta_k = s_k qbar_k - w with qbar = code - zero, small integers that IEEE half holds exactly, so that
-//     delta_k H delta_k^T = 2 sum_c delta_c (s_k G_k[c] - G_w[c]),   G_k = qbar_k T^T,  G_w = w T^T,
-// T = the lower triangle of H with half its diagonal (H is symmetric; the GEMM then needs, for output column r, only the
-// contraction indices c <= r: its causal limit).  The left operand is exact and w enters as 22 bits in two extra rows per weight
-// row, so that only T has to be split, into one or two half terms, where (hi, lo) pairs of delta and of H took three products.
-// With one term what is left is the rounding of H, at most 2^-11 of an entry and the same for every candidate (the diagonal is exempt: its
-// rounding is known and added back).  Its effect on a cost goes by rho = |H off the diagonal|_F / tr H: measured 2.9e-4 rho (root mean square over the
-// near-minimal candidates) and up to 1.4e-3 rho below rho = 0.01, at every width and number of bits, and more of it above (up to 8e-3 rho at 0.4).  The three products of bf16 pairs were off
-// by 1.4e-6 - 2.3e-6 with 2 bits, 1e-6 - 2e-6 with 3 and 4, 0.6e-6 - 2.3e-6 with 8 (root mean square, widths 1024 - 8192, 16 - 131 thousand tokens): one
-// term is taken where it is off by no more than that, which is where channels are uncorrelated and the tokens many (grid_one_term), and two (22 bits)
-// elsewhere: 1e-7 - 3e-7.  The device decides per matrix (grid_terms_kernel).
-// The channels are equilibrated by powers of two, T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, and
-// qbar'_c = qbar_c 2^(e_c - e_max) (exact), so that the entries of T' are at most 2^12 whatever the spread of the channels.
-// Measured on the 70B-shaped W_O (8192 x 8192, 80 candidates): the products take 44 ms with one term and 82 with two, where three took 120.  As a guard, every
-// exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of GRID_TAU is
-// repeated: with two terms if a matrix had one, else with exact costs for every candidate (counted by tboa_counter).
-// Largest deviations seen: 7e-6 with one term; with two 2e-6 on uncorrelated channels, 4e-5 on strongly correlated ones (one term there: 6e-3) and
-// 1.2e-4 on the Hessian of a down projection; the three products of bf16 pairs had 1.5e-5, 8e-5 and 1.4e-4.
+// With T the part of H below its diagonal, delta H delta^T = sum_c delta_c (2 (delta T^T)[c] + H_cc delta_c) (H is symmetric; the product then needs, for
+// output column r, only the contraction indices c < r: its causal limit).  Two forms of the product:
+//
+// Integers (coarse grids, see grid_delta): delta_k = s_k qbar_k - w with qbar = code - zero, at most maxq in magnitude, so that
+//     delta_k T^T = s_k G_k - G_w,   G_k = qbar_k T^T,  G_w = w T^T,
+// and every row r of T is taken as integers times a step v_r, two or three digits to the base 256: the product runs on signed bytes at twice the rate of 16-bit
+// operands, its sums are exact, and v_r is large enough that maxq sum |T'_r| stays below 2^31.  G_w comes from the 31-bit integer form of the weight rows, one product
+// for every pair of digits, added in 64-bit integers.  So a cost is that of T' = v times the integers, the same T' for all candidates, and the one error is
+// the rounding of T: expected relative error E = 2 sqrt(sum_r r v_r^2 / 12) / tr H, which the device forms per matrix; two digits where E <= 6e-7, three
+// elsewhere (1e-9 - 8e-7, the latter on channels correlated by common factors).
+// (hi, lo) half terms of T with the codes as halves before: one term up to 1.4e-6, two 1e-7 - 3e-7 and, where G_k and G_w cancel in their fp32 sums, up to
+// 2.1e-5 (root mean square).  70B-shaped W_O (8192 x 8192, 80 candidates, three digits against two half terms): products 86 -> 63 ms.
+//
+// Pairs of delta (fine grids): delta itself as a (hi, lo) pair of halves against one or two half terms of T with half of H's diagonal, the channels
+// equilibrated by powers of two: T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, delta'_c = delta_c 2^(e_c - e_max), so that the entries of T' are at
+// most 2^12 whatever the spread of the channels.  With one term what is left is the rounding of H, at most 2^-11 of an entry and the same for every
+// candidate (the diagonal is exempt: its rounding is known and added back).  Its effect on a cost goes by rho = |H off the diagonal|_F / tr H: measured 2.9e-4 rho
+// (root mean square over the near-minimal candidates) and up to 1.4e-3 rho below rho = 0.01, at every width and number of bits, and more of it above (up to 8e-3 rho
+// at 0.4).  Three products of bf16 pairs were off by 1e-6 - 2e-6 with 3 and 4 bits, 0.6e-6 - 2.3e-6 with 8 (root mean square, widths 1024 - 8192, 16 - 131
+// thousand tokens): one term is taken where it is off by no more than that, which is where channels are uncorrelated and the tokens many
+// (grid_one_term), and two (22 bits) elsewhere: 1e-7 - 3e-7, on strongly correlated channels 1.5e-6 - 5.8e-6.  The device decides per matrix (grid_terms_kernel).
+//
+// As a guard, every exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of the margin of the
+// survivors is repeated: with the longer form of T if a matrix had the shorter one, else with exact costs for every candidate (counted by tboa_counter).
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
-constexpr double GRID_TAU = 2e-3;   // survivors: approximate cost <= (1 + tau) * approximate minimum
-constexpr bool grid_delta(int bits, int n) { return bits > 3 || (bits == 3 && n > 2048); }      // the left operand is delta as a pair, else the integer codes (see grid_codes_kernel)
+// survivors: approximate cost <= (1 + tau) * approximate minimum.  The integer form is closer (largest deviations seen 1e-7 - 5e-7 on uncorrelated channels, 5e-5 on
+// channels correlated by common factors, where half terms had 2e-6 and 1.2e-4), and its margin is half as wide: fewer exact costs.
+constexpr double GRID_TAU = 2e-3, GRID_TAU_INT = 1e-3;
+constexpr double GRID_TWO_DIGITS = 6e-7;      // expected relative error of a cost up to which two digits of T do
+// the left operand is delta as a pair of halves, else the integer codes: 3 levels of qbar over any width, 7 over 2048 columns.  The step of T grows with maxq times
+// the width; beyond that the pairs are closer on correlated channels (4 bits, 8192 columns: 1.5e-6 - 5.8e-6 against 2e-5 expected of integers)
+constexpr bool grid_delta(int bits, int n) { return bits > 3 || (bits == 3 && n > 2048); }
 constexpr double grid_one_term(int bits) { return bits == 2 ? 0.005 : bits <= 4 ? 0.003 : 0.0; }      // one half term of T is enough for |H off the diagonal|_F up to this times tr H
 constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
-inline int grid_width(int n) { return (n + 31) / 32 * 32; }      // columns of the operands: zeros beyond n
-inline long long grid_mat_rows(long long rows, int ncand) { return (rows * (ncand + 2) + 15) / 16 * 16; }
+// columns of the operands: zeros beyond n (integers: whole output tiles, whose contraction then is whole turns of the LDS ring)
+inline int grid_width(int n, bool delta) { return delta ? (n + 31) / 32 * 32 : (n + 255) / 256 * 256; }
+inline long long grid_pitch(int np, bool delta) { return (delta ? np : np / 2) + GRID_PAD; }      // of an operand, in 16-bit elements
+inline long long rows16(long long rows) { return (rows + 15) / 16 * 16; }
 
 // What a matrix's equilibration leaves behind, [n_hin][np] each: up[c] = 2^(e_c - e_max) (0 beyond n), down[c] = 2^-e_c, dcorr[c] = H'_cc less
 // twice what the half terms hold of T'_cc, off2[c] = sum of the squares of row c left of the diagonal; per matrix scale = 2^(2 e_max) and
@@ -235,15 +248,94 @@ __global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restric
     }
 }
 
-// Rows of a pass, in one array of matrices (the rows that share one H): matrix row of (weight row rl of the matrix, candidate k) is
-// rl ncand + k; the high and low parts of the weights follow at per ncand + rl and per ncand + per + rl.
-struct GridRows { int per, ncand; long long mat_rows; int np; };
+// Integer form of T.  Per row r and matrix, [n_hin][np]: v = step of the row, hd = H_rr (both 0 beyond n); v2, v3: the steps with two and three digits, e2: the row's part
+// of E with two; terms: digits taken.
+struct GridInt { double *v, *hd, *v2, *v3, *e2; int* terms; };
+constexpr double GRID_DIGITS2 = 32600.0, GRID_DIGITS3 = 8.3e6;      // largest magnitudes of two and three digits in [-128, 127]
 
-// per weight row (one wavefront): range, candidates (s_k, z_k) and 1 / s_k in fp32 (0 where that is no normal number), the row in fp32, and the
-// row's two operand rows: w up 2^t as a (hi, lo) pair of halves, 2^t bringing the row's largest magnitude into [2^13, 2^14)
+__global__ __launch_bounds__(256) void grid_int_steps_kernel(const double* __restrict__ H, int n, int np, double maxq, GridInt g) {
+    __shared__ double red[2][4];
+    const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const long long o = (long long)blockIdx.y * np;
+    const double* h = H + (long long)blockIdx.y * n * n + (long long)r * n;
+    double sum = 0.0, big = 0.0;
+    if (r < n)
+        for (int c = threadIdx.x; c < r; c += 256) { const double a = fabs(h[c]); sum += a; big = fmax(big, a); }
+    sum = wave_sum(sum);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) big = fmax(big, __shfl_xor(big, w, 64));
+    if (lane == 0) { red[0][wave] = sum; red[1][wave] = big; }
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    sum = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
+    big = fmax(fmax(red[1][0], red[1][1]), fmax(red[1][2], red[1][3]));
+    // maxq sum |T'| <= maxq (sum / v + n / 2) < 2^31
+    const double least = maxq * sum / (2147483000.0 - 0.5 * maxq * n), v2 = fmax(big / GRID_DIGITS2, least), v3 = fmax(big / GRID_DIGITS3, least);
+    g.v2[o + r] = v2; g.v3[o + r] = sum == sum ? v3 : sum;      // (a sum that is undefined makes every cost undefined)
+    g.e2[o + r] = (double)r * v2 * v2;
+    g.hd[o + r] = r < n ? h[r] : 0.0;
+}
+
+__global__ __launch_bounds__(256) void grid_int_terms_kernel(int n, int np, GridInt g, int longer, int* __restrict__ gstat) {
+    __shared__ double red[2][256];
+    const long long o = (long long)blockIdx.x * np;
+    double tr = 0.0, e = 0.0;
+    for (int c = threadIdx.x; c < n; c += 256) { tr += g.hd[o + c]; e += g.e2[o + c]; }
+    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = e;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) { red[0][threadIdx.x] += red[0][threadIdx.x + w]; red[1][threadIdx.x] += red[1][threadIdx.x + w]; }
+        __syncthreads();
+    }
+    const double lim = GRID_TWO_DIGITS * red[0][0];
+    const int terms = (!longer && red[1][0] / 3.0 <= lim * lim) ? 2 : 3;      // E = 2 sqrt(e / 12) / tr
+    if (threadIdx.x == 0) { g.terms[blockIdx.x] = terms; if (terms == 2) atomicOr(gstat, 1); }
+    for (int c = threadIdx.x; c < np; c += 256) g.v[o + c] = c < n ? (terms == 2 ? g.v2[o + c] : g.v3[o + c]) : 0.0;
+}
+
+// signed bytes d0, d1, d2 with t = d0 + 256 d1 + 65536 d2
+__device__ __forceinline__ void digits(int t, signed char& d0, signed char& d1, signed char& d2) {
+    d0 = (signed char)(t & 255); t = (t - d0) >> 8;
+    d1 = (signed char)(t & 255); d2 = (signed char)((t - d1) >> 8);
+}
+__device__ __forceinline__ int clamped_int(double x, double lim) { return (int)fmin(fmax(rint(x), -lim), lim); }      // (an undefined value becomes -lim)
+
+// the digits of T', the highest first, in the GEMM's blocks, one [np, pitch] matrix per H and digit (all highest digits, then ..); only what the causal limit reads
+// is written.  One workgroup per row, sixteen consecutive columns per thread.
+__global__ __launch_bounds__(256) void grid_int_factor_kernel(const double* __restrict__ H, int n, int np, long long pitch, GridInt g, signed char* __restrict__ out, long long term_bytes) {
+    const int r = blockIdx.x;
+    const long long o = (long long)blockIdx.y * np;
+    const double* h = H + (long long)blockIdx.y * n * n + (long long)r * n;
+    signed char* dst = out + 2LL * blockIdx.y * np * pitch;
+    const double v = g.v[o + r], inv = v > 0.0 ? 1.0 / v : 0.0;
+    const bool two = g.terms[blockIdx.y] == 2;
+    const int cend = min(np, (r / 256 + 1) * 256);
+    for (int c = 16 * threadIdx.x; c < cend; c += 4096) {
+        union { signed char b[16]; uint4 u; } d[3];
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int t = (r < n && c + j < r) ? clamped_int(h[c + j] * inv, two ? 32639.0 : 8355711.0) : 0;
+            if (two) { digits(t, d[1].b[j], d[0].b[j], d[2].b[j]); d[2].b[j] = 0; }
+            else digits(t, d[2].b[j], d[1].b[j], d[0].b[j]);
+        }
+        const long long a = 2 * tboa_blocked_offset(r, c / 2, pitch >> 5);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) *(uint4*)(dst + k * term_bytes + a) = d[k].u;
+    }
+}
+
+// Rows of a pass, in one array of matrices (the rows that share one H): matrix row of (weight row rl of the matrix, candidate k) is rl ncand + k.
+struct GridRows { int per, ncand; long long mat_rows, pitch; int np; };
+// integers: the four digits of the weight rows, digit i (the highest first) of row rl at i per + rl of [w_rows, pitch]; wu = step of a weight row
+constexpr int GRID_WD = 4;
+struct GridWeights { signed char* A; long long w_rows; double* wu; };
+
+// per weight row (one wavefront): range, candidates (s_k, z_k) and 1 / s_k in fp32 (0 where that is no normal number), the row in fp32, and
+// DELTA: wdown = 2^-t, 2^t bringing the row's largest magnitude into [2^13, 2^14); else the row's digits
+template <bool DELTA>
 __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict__ Wk, long long ldw, int n, int rows, int grid_points, double maxq,
-                                                        GridRows m, GridScale g, double* __restrict__ cand_s, double* __restrict__ cand_z,
-                                                        float* __restrict__ cand_r, float* __restrict__ Wf, float* __restrict__ wdown, __half* __restrict__ Acat) {
+                                                        GridRows m, GridWeights gw, double* __restrict__ cand_s, double* __restrict__ cand_z,
+                                                        float* __restrict__ cand_r, float* __restrict__ Wf, float* __restrict__ wdown) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const double* w = Wk + (long long)row * ldw;
@@ -252,7 +344,7 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o, 64)); hi = fmax(hi, __shfl_xor(hi, o, 64)); }
     const double big = fmax(-lo, hi);
-    const int t = (big > 0.0 && big < 1e300) ? 13 - ilogb(big) : 0;
+    const int e = (big > 0.0 && big < 1e300) ? ilogb(big) : 0;
     if (lo == hi) { lo = -1.0; hi = 1.0; }
     for (int k = lane; k < m.ncand; k += 64) {
         const double p = 1.0 - (double)k / (double)grid_points;
@@ -262,33 +354,69 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict
         const double r = 1.0 / s;
         cand_r[(long long)row * m.ncand + k] = (r >= 1.17549435e-38 && r <= 3.4e38) ? (float)r : 0.f;
     }
-    if (lane == 0) wdown[row] = ldexpf(1.f, -t);
-    const int mat = row / m.per, rl = row % m.per;
-    const long long pitch = m.np + GRID_PAD, R = (long long)m.per * m.ncand + rl;
-    const float* up = g.up + (long long)mat * m.np;
-    _Float16* A = (_Float16*)Acat + (long long)mat * m.mat_rows * pitch;
-    for (int c = lane; c < m.np; c += 64) {
-        const double v = c < n ? w[c] : 0.0;
-        Wf[(long long)row * m.np + c] = (float)v;
-        const double x = ldexp(v, t) * (double)up[c];
-        const _Float16 h = (_Float16)(float)x;
-        A[tboa_blocked_offset(R, c, pitch >> 5)] = h;
-        A[tboa_blocked_offset(R + m.per, c, pitch >> 5)] = (_Float16)(float)(x - (double)h);
+    for (int c = lane; c < m.np; c += 64) Wf[(long long)row * m.np + c] = c < n ? (float)w[c] : 0.f;
+    if constexpr (DELTA) {
+        if (lane == 0) wdown[row] = ldexpf(1.f, e - 13);
+    } else {
+        const int mat = row / m.per, rl = row % m.per;
+        signed char* A = gw.A + 2LL * mat * gw.w_rows * m.pitch;
+        if (lane == 0) gw.wu[row] = ldexp(1.0, e - 29);
+        for (int c = 16 * lane; c < m.np; c += 1024) {
+            union { signed char b[16]; uint4 u; } d[GRID_WD];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+                const int t = c + j < n ? clamped_int(ldexp(w[c + j], 29 - e), 1073741824.0) : 0;
+                d[3].b[j] = (signed char)(t & 255);
+                digits((t - d[3].b[j]) >> 8, d[2].b[j], d[1].b[j], d[0].b[j]);
+            }
+#pragma unroll
+            for (int k = 0; k < GRID_WD; ++k) *(uint4*)(A + 2 * tboa_blocked_offset((long long)k * m.per + rl, c / 2, m.pitch >> 5)) = d[k].u;
+        }
     }
 }
 
-// qbar'[(row, k), c] = (clamp(round(w_c / s_k) + z_k) - z_k) up[c].  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so
-// wherever it is further than 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
-// A wavefront makes whole 16 x 32 blocks: lane = (row of the block lane / 4, eight columns of lane % 4).
-// DELTA (grid_delta): the operand is delta itself, delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off
-// elements further on.  The finer the grid, the closer s qbar and w, whose products with T, formed in fp32, the integer form subtracts: it loses bits by
-// the number of levels, the width and the correlation of H.  Deviations (largest, root mean square) on the Hessian of a 7B down projection (d_in 11008, rows of
-// silu(gate) up over 131072 fake-quantized tokens): integer form 4.0e-4, 8.1e-5 with 16 levels, 2.4e-4, 4.2e-5 with 8, 1.2e-4, 2.1e-5 with 4; three products
-// of bf16 pairs of delta and H 1.4e-4, 2.7e-5 and this form 2.9e-5, 5.8e-6 for any of them.  On channels correlated by eight common factors (8192 wide): integer
-// form 9.9e-6 with 8 levels and 5.9e-6 with 4 (root mean square), bf16 pairs 9e-6, this form 1.5e-6.  The integer form, which saves a product, is kept where it is
-// at least as close as the bf16 pairs were on every H tried: 4 levels at any width, 8 levels up to 3072 columns (at 4096 2.0e-5 against 1.7e-5 on a down projection).
-template <bool DELTA>
-__global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, int rows, float maxq,
+// clamp(round(w / s) + z) - z of one weight.  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so wherever it is further than
+// 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
+__device__ __forceinline__ float grid_code(float wf, float inv, float z, float maxq, const double* w, bool exists, double s) {
+    const float t = wf * inv;
+    float r = rintf(t);
+    const bool safe = inv != 0.f && fabsf(t - r) < 0.5f - (fabsf(t) * 9.5367431640625e-7f + 9.5367431640625e-7f);
+    if (!safe && exists) r = (float)fmin(fmax(rint(*w / s), -1024.0), 1024.0);
+    return fminf(fmaxf(r + z, 0.f), maxq) - z;
+}
+
+// qbar of every (row, candidate) as bytes; a wavefront makes whole blocks of 16 rows x 64: lane = (row of the block lane / 4, sixteen columns of lane % 4)
+__global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, float maxq, GridRows m,
+                                                         const double* __restrict__ cand_s, const double* __restrict__ cand_z, const float* __restrict__ cand_r,
+                                                         signed char* __restrict__ Acat) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, mat = blockIdx.z;
+    const long long R = 16LL * (blockIdx.y * 4 + (threadIdx.x >> 6)) + (lane >> 2);
+    if (R >= (long long)m.per * m.ncand) return;
+    const int rl = (int)(R / m.ncand), k = (int)(R % m.ncand), row = mat * m.per + rl;
+    const double s = cand_s[(long long)row * m.ncand + k];
+    const float inv = cand_r[(long long)row * m.ncand + k], z = (float)cand_z[(long long)row * m.ncand + k];
+    const float* wf = Wf + (long long)row * m.np; const double* w = Wk + (long long)row * ldw;
+    signed char* A = Acat + 2LL * mat * m.mat_rows * m.pitch;
+    const int nblk = m.np / 64, per = (nblk + gridDim.x - 1) / gridDim.x, b1 = min(nblk, ((int)blockIdx.x + 1) * per);
+    for (int cb = blockIdx.x * per; cb < b1; ++cb) {
+        const int c = 64 * cb + 16 * (lane & 3);
+        union { signed char b[16]; uint4 u; } o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const f4 wv = *(const f4*)(wf + c + 4 * q);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) o.b[4 * q + j] = (signed char)(int)grid_code(wv[j], inv, z, maxq, w + c + 4 * q + j, c + 4 * q + j < n, s);
+        }
+        *(uint4*)(A + 2 * tboa_blocked_offset(R, c / 2, m.pitch >> 5)) = o.u;
+    }
+}
+
+// delta up 2^t (2^t as for the weights) as a (hi, lo) pair of halves, the low parts lo_off elements further on, in blocks of 16 rows x 32.
+// The finer the grid, the closer s qbar and w, whose products the integer form subtracts; deviations (largest, root mean square) on the Hessian of a 7B down
+// projection (d_in 11008, rows of silu(gate) up over 131072 fake-quantized tokens): three products of bf16 pairs of delta and H 1.4e-4, 2.7e-5 and
+// this form 2.9e-5, 5.8e-6 for any number of levels.
+__global__ __launch_bounds__(256) void grid_delta_pair_kernel(const double* __restrict__ Wk, long long ldw, const float* __restrict__ Wf, int n, float maxq,
                                                          GridRows m, GridScale g, const double* __restrict__ cand_s, const double* __restrict__ cand_z,
                                                          const float* __restrict__ cand_r, const float* __restrict__ wdown, __half* __restrict__ Acat, long long lo_off) {
     const int lane = threadIdx.x & 63;
@@ -296,11 +424,10 @@ __global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restric
     const long long R = 16LL * (blockIdx.y * 4 + (threadIdx.x >> 6)) + (lane >> 2);
     if (R >= (long long)m.per * m.ncand) return;
     const int rl = (int)(R / m.ncand), k = (int)(R % m.ncand), row = mat * m.per + rl;
-    const double s = cand_s[(long long)row * m.ncand + k], zd = cand_z[(long long)row * m.ncand + k], up2 = DELTA ? 1.0 / (double)wdown[row] : 0.0;
-    const float inv = cand_r[(long long)row * m.ncand + k], z = (float)zd;
-    const float* wf = Wf + (long long)row * m.np; const float* up = g.up + (long long)mat * m.np;
-    const long long pitch = m.np + GRID_PAD;
-    _Float16* A = (_Float16*)Acat + (long long)mat * m.mat_rows * pitch;
+    const double s = cand_s[(long long)row * m.ncand + k], up2 = 1.0 / (double)wdown[row];
+    const float inv = cand_r[(long long)row * m.ncand + k], z = (float)cand_z[(long long)row * m.ncand + k];
+    const float* wf = Wf + (long long)row * m.np; const float* up = g.up + (long long)mat * m.np; const double* w = Wk + (long long)row * ldw;
+    _Float16* A = (_Float16*)Acat + (long long)mat * m.mat_rows * m.pitch;
     const int nblk = m.np / 32, per = (nblk + gridDim.x - 1) / gridDim.x, b1 = min(nblk, ((int)blockIdx.x + 1) * per);
     typedef float f4 __attribute__((ext_vector_type(4)));
     for (int cb = blockIdx.x * per; cb < b1; ++cb) {
@@ -309,76 +436,120 @@ __global__ __launch_bounds__(256) void grid_codes_kernel(const double* __restric
         union { _Float16 b[8]; uint4 u; } o, l;
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float t = wv[j >> 2][j & 3] * inv, uj = uv[j >> 2][j & 3];
-            float r = rintf(t);
-            const bool safe = inv != 0.f && fabsf(t - r) < 0.5f - (fabsf(t) * 9.5367431640625e-7f + 9.5367431640625e-7f);
-            if (!safe && c + j < n) r = (float)fmin(fmax(rint(Wk[(long long)row * ldw + c + j] / s), -1024.0), 1024.0);
-            const float q = fminf(fmaxf(r + z, 0.f), maxq);
-            if constexpr (DELTA) {
-                const double w = c + j < n ? Wk[(long long)row * ldw + c + j] : 0.0;
-                const double d = (s * ((double)q - zd) - w) * (double)uj * up2;
-                o.b[j] = (_Float16)(float)d; l.b[j] = (_Float16)(float)(d - (double)o.b[j]);
-            } else o.b[j] = (_Float16)((q - z) * uj);
+            const bool in = c + j < n;
+            const double q = (double)grid_code(wv[j >> 2][j & 3], inv, z, maxq, w + c + j, in, s);
+            const double d = (s * q - (in ? w[c + j] : 0.0)) * (double)uv[j >> 2][j & 3] * up2;
+            o.b[j] = (_Float16)(float)d; l.b[j] = (_Float16)(float)(d - (double)o.b[j]);
         }
-        const long long a = tboa_blocked_offset(R, c, pitch >> 5);
+        const long long a = tboa_blocked_offset(R, c, m.pitch >> 5);
         *(uint4*)(A + a) = o.u;
-        if constexpr (DELTA) *(uint4*)(A + lo_off + a) = l.u;
+        *(uint4*)(A + lo_off + a) = l.u;
     }
 }
 
-// cost[(row, k)] = 2^(2 e_max) sum_c delta'_c (2 (s G[c] - Gw[c]) 2^-10 + dcorr_c delta'_c), delta' = s qbar' - w'; one wavefront per (row, k).
-// DELTA: delta' = the pair, G its product.
-template <bool DELTA>
-__global__ __launch_bounds__(256) void grid_cost_kernel(const float* __restrict__ G, const __half* __restrict__ Acat, int rows, GridRows m, GridScale g,
-                                                        const double* __restrict__ cand_s, const float* __restrict__ wdown, double* __restrict__ out, long long lo_off) {
+// cost[(row, k)] = 2^(2 e_max) sum_c delta'_c (2 G[c] 2^-10 + dcorr_c delta'_c), delta' the pair, G its product; one wavefront per (row, k)
+__global__ __launch_bounds__(256) void grid_pair_cost_kernel(const float* __restrict__ G, const __half* __restrict__ Acat, int rows, GridRows m, GridScale g,
+                                                        const float* __restrict__ wdown, double* __restrict__ out, long long lo_off) {
     typedef float f4 __attribute__((ext_vector_type(4)));
     typedef _Float16 h4 __attribute__((ext_vector_type(4)));
     const int lane = threadIdx.x & 63;
     const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (i >= (long long)rows * m.ncand) return;
     const int row = (int)(i / m.ncand), k = (int)(i % m.ncand), mat = row / m.per, rl = row % m.per;
-    const long long pitch = m.np + GRID_PAD, kb = pitch >> 5, R = (long long)rl * m.ncand + k, Rw = (long long)m.per * m.ncand + rl;
-    const _Float16* A = (const _Float16*)Acat + (long long)mat * m.mat_rows * pitch;
-    const float* Gm = G + (long long)mat * m.mat_rows * m.np;
-    const float *g0 = Gm + R * m.np, *g1 = Gm + Rw * m.np, *g2 = Gm + (Rw + m.per) * m.np, *dc = g.dcorr + (long long)mat * m.np;
-    const double s = cand_s[i], wd = wdown[row];
+    const long long kb = m.pitch >> 5, R = (long long)rl * m.ncand + k;
+    const _Float16* A = (const _Float16*)Acat + (long long)mat * m.mat_rows * m.pitch;
+    const float *g0 = G + ((long long)mat * m.mat_rows + R) * m.np, *dc = g.dcorr + (long long)mat * m.np;
+    const double wd = wdown[row];
     double acc = 0.0;
     for (int c = 4 * lane; c < m.np; c += 256) {
         const f4 a = __builtin_nontemporal_load((const f4*)(g0 + c)), d = *(const f4*)(dc + c);
-        const h4 q = *(const h4*)(A + tboa_blocked_offset(R, c, kb));
-        if constexpr (DELTA) {
-            const h4 ql = *(const h4*)(A + lo_off + tboa_blocked_offset(R, c, kb));
+        const h4 q = *(const h4*)(A + tboa_blocked_offset(R, c, kb)), ql = *(const h4*)(A + lo_off + tboa_blocked_offset(R, c, kb));
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double delta = wd * ((double)(float)q[j] + (double)(float)ql[j]);
-                acc += delta * ((2.0 / 1024.0) * wd * (double)a[j] + (double)d[j] * delta);
-            }
-        } else {
-            const f4 wh = *(const f4*)(g1 + c), wl = *(const f4*)(g2 + c);
-            const h4 vh = *(const h4*)(A + tboa_blocked_offset(Rw, c, kb)), vl = *(const h4*)(A + tboa_blocked_offset(Rw + m.per, c, kb));
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const double delta = s * (double)(float)q[j] - wd * ((double)(float)vh[j] + (double)(float)vl[j]);
-                const double gd = s * (double)a[j] - wd * ((double)wh[j] + (double)wl[j]);
-                acc += delta * ((2.0 / 1024.0) * gd + (double)d[j] * delta);
-            }
+        for (int j = 0; j < 4; ++j) {
+            const double delta = wd * ((double)(float)q[j] + (double)(float)ql[j]);
+            acc += delta * ((2.0 / 1024.0) * wd * (double)a[j] + (double)d[j] * delta);
         }
     }
     acc = wave_sum(acc);
     if (lane == 0) out[i] = g.scale[mat] * acc;
 }
 
+// Gw[row, c] = (w T'^T)[c] / v_c from the products of the digits, P[mat][digit of T][digit of w * per + row, c]
+__global__ __launch_bounds__(256) void grid_weight_products_kernel(const int* __restrict__ P, GridRows m, GridWeights gw, GridInt g, double* __restrict__ Gw) {
+    const int row = blockIdx.y, mat = row / m.per, rl = row % m.per, c = blockIdx.x * 256 + threadIdx.x;
+    if (c >= m.np) return;
+    const int terms = g.terms[mat];
+    const int* p = P + 3LL * mat * gw.w_rows * m.np + (long long)rl * m.np + c;
+    long long sum = 0;
+#pragma unroll
+    for (int i = 0; i < GRID_WD; ++i) {
+        long long t = 0;
+        for (int k = 0; k < terms; ++k) t = t * 256 + p[((long long)k * gw.w_rows + (long long)i * m.per) * m.np];
+        sum = sum * 256 + t;
+    }
+    Gw[(long long)row * m.np + c] = gw.wu[row] * (double)sum;
+}
+
+// cost[(row, k)] = sum_c delta_c (2 v_c (s G[c] - Gw[c]) + H_cc delta_c), delta = s qbar - w.  One wavefront per row and GRID_KC candidates: bound by reading G, 4 bytes an
+// entry, once; what belongs to the row and the columns is read once for them all (one candidate a wavefront read as much again from L2).
+// least[row] = 2^-40 sum_c H_cc w_c^2: a candidate that costs less meets the weights up to the rounding of 24-bit numbers, which their 31 bits do not resolve well
+// enough to tell costs apart (see grid_count_kernel).
+constexpr int GRID_KC = 8;
+__global__ __launch_bounds__(256) void grid_cost_kernel(const int* __restrict__ G, const signed char* __restrict__ Acat, int rows, GridRows m, GridInt g,
+                                                        const double* __restrict__ cand_s, const double* __restrict__ Wk, long long ldw, int n, const double* __restrict__ Gw,
+                                                        double* __restrict__ out, double* __restrict__ least) {
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, parts = (m.ncand + GRID_KC - 1) / GRID_KC;
+    const long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= (long long)rows * parts) return;
+    const int row = (int)(i / parts), k0 = (int)(i % parts) * GRID_KC, mat = row / m.per, rl = row % m.per;
+    const long long kb = m.pitch >> 5, R0 = (long long)rl * m.ncand;
+    const signed char* A = Acat + 2LL * mat * m.mat_rows * m.pitch;
+    const int* Gm = G + ((long long)mat * m.mat_rows + R0) * m.np;
+    double s[GRID_KC], acc[GRID_KC];
+#pragma unroll
+    for (int k = 0; k < GRID_KC; ++k) { s[k] = cand_s[(long long)row * m.ncand + min(k0 + k, m.ncand - 1)]; acc[k] = 0.0; }
+    double norm = 0.0;
+    for (int c = 4 * lane; c < m.np; c += 256) {
+        double w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[j] = c + j < n ? Wk[(long long)row * ldw + c + j] : 0.0;
+        const d4 gw = *(const d4*)(Gw + (long long)row * m.np + c), v = *(const d4*)(g.v + (long long)mat * m.np + c), hd = *(const d4*)(g.hd + (long long)mat * m.np + c);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) norm += hd[j] * w[j] * w[j];
+#pragma unroll
+        for (int k = 0; k < GRID_KC; ++k) {
+            const int kk = min(k0 + k, m.ncand - 1);
+            const i4 a = __builtin_nontemporal_load((const i4*)(Gm + (long long)kk * m.np + c));
+            const int q = *(const int*)(A + 2 * tboa_blocked_offset(R0 + kk, (c / 16) * 8, kb) + (c & 15));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double delta = s[k] * (double)(signed char)(q >> (8 * j)) - w[j];
+                acc[k] += delta * (2.0 * v[j] * (s[k] * (double)a[j] - gw[j]) + hd[j] * delta);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < GRID_KC; ++k) {
+        const double t = wave_sum(acc[k]);
+        if (lane == 0 && k0 + k < m.ncand) out[(long long)row * m.ncand + k0 + k] = t;
+    }
+    norm = wave_sum(norm);
+    if (lane == 0 && k0 == 0) least[row] = 9.094947017729282e-13 * norm;
+}
+
 // Device-side bookkeeping of the two-phase search, accumulated over every pass of a quantize_layer call and read once at
 // its end: [0] set when a pass could not be trusted as it stands (non-finite approximate cost, more near-minimal
 // candidates in a group of rows than the exact re-evaluation has room for), [1] near-minimal candidates evaluated exactly,
-// [2] the largest |approximate - exact| / |exact| seen, as the bits of a non-negative float, [3] set when a matrix of the call has one half
-// term (see grid_terms_kernel).
-enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_ONE_TERM = 3, GS_WORDS = 4 };
+// [2] the largest |approximate - exact| / |exact| seen, as the bits of a non-negative float, [3] set when a matrix of the call has the shorter
+// form of T (one half term, two digits).
+enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_WORDS = 4 };
 
 // per row (one wavefront): the candidates whose approximate cost makes them survivors (in increasing k, list[row][0 ..]), and the number that
 // the exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
 // exact cost is what the deviation guard of the pass measures.
-__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, int* __restrict__ list,
+__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, const double* __restrict__ least, int* __restrict__ list,
                                   int* __restrict__ cnt_out, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
@@ -398,7 +569,7 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restric
     }
     if (lane != 0) return;
     if (cnt == 0) out[0] = 0;
-    if (bad || cnt == 0) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
+    if (bad || cnt == 0 || (least && m < least[row])) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
     const int ev = (cnt > 1 || row % 8 == 0) ? cnt : 0;
     cnt_out[row] = ev;
     if (ev) atomicAdd(gstat + GS_SURVIVORS, ev);
@@ -774,6 +945,7 @@ struct Layer {
     double *cand_s, *cand_z, *Delta, *G, *cost, *DeltaS, *GS, *costS;
     __half* Hcat; int *sel, *list; int fast_grid, grid_terms;          // two-phase search: T' of every H_in, survivor bookkeeping
     GridScale gscale; float *cand_r, *Wf, *wdown;
+    GridInt gint; GridWeights gwt; int* gwp; double *gwv, *gleast;      // integer form: T', digits of the weight rows, their products, w T'^T, costs that void a pass
     double *Wbar, *Abar, *Z, *WR, *Cm, *Fm, *dvec, *lossbuf;
     double *Cg, *Fg, *cdnum;    // group-wise refinement: Gram blocks per (group, group) pair
     int grid_chunk, fast_chunk;     // block rows (shared H_in) or heads (per-head H_in) per grid-search pass: exact, two-phase
@@ -799,47 +971,65 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
         const int r0 = u0 * rows_per_unit, rows = nu * rows_per_unit;
         const double* Wc = Wrows + (long long)r0 * ldw;
         if (fast) {
-            const int n = L.n, np = grid_width(n);
-            __half* Acat = (__half*)L.Delta; float* G32 = (float*)L.G;
-            const int mats = ph ? nu : 1;
-            const GridRows m{ph ? rows_per_head : rows, ncand, grid_mat_rows(ph ? rows_per_head : rows, ncand), np};
-            GridScale gs = L.gscale;      // of the first matrix of this pass
-            if (ph) { gs.up += (long long)u0 * np; gs.down += (long long)u0 * np; gs.dcorr += (long long)u0 * np; gs.scale += u0; gs.terms += u0; }
-            hipLaunchKernelGGL(grid_rows_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, n, rows, L.d->grid_points, L.maxq, m, gs,
-                               L.cand_s, L.cand_z, L.cand_r, L.Wf, L.wdown, Acat);
+            const bool delta = grid_delta(L.d->bits, L.n);
+            const int n = L.n, np = grid_width(n, delta);
+            const int mats = ph ? nu : 1, per_mat = ph ? rows_per_head : rows;
+            const long long pitch = grid_pitch(np, delta), mo = ph ? (long long)u0 * np : 0;
+            const GridRows m{per_mat, ncand, rows16((long long)per_mat * ncand), pitch, np};
+            GridWeights gw = L.gwt;
+            gw.w_rows = rows16((long long)GRID_WD * per_mat);
+            if (delta) hipLaunchKernelGGL(grid_rows_kernel<true>, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, n, rows, L.d->grid_points, L.maxq, m, gw,
+                                          L.cand_s, L.cand_z, L.cand_r, L.Wf, L.wdown);
+            else hipLaunchKernelGGL(grid_rows_kernel<false>, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, Wc, ldw, n, rows, L.d->grid_points, L.maxq, m, gw,
+                                    L.cand_s, L.cand_z, L.cand_r, L.Wf, L.wdown);
             const unsigned rb = (unsigned)(((long long)m.per * ncand + 63) / 64);
             // (columns in up to 8 parts where there are few rows)
             const unsigned cparts = (long long)rb * mats >= 2048 ? 1u : (unsigned)std::min<long long>(8, 2048 / ((long long)rb * mats) + 1);
-            const bool delta = grid_delta(L.d->bits, n);
-            const long long lo_off = (long long)mats * m.mat_rows * (np + GRID_PAD);
-            if (delta)
-                hipLaunchKernelGGL(grid_codes_kernel<true>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
-                                   L.cand_s, L.cand_z, L.cand_r, L.wdown, Acat, lo_off);
-            else
-                hipLaunchKernelGGL(grid_codes_kernel<false>, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, rows, (float)L.maxq, m, gs,
-                                   L.cand_s, L.cand_z, L.cand_r, L.wdown, Acat, lo_off);
-            TB_KERNEL_CHECK(ctx);
             GemmBf16 a{};
-            a.M = (int)m.mat_rows; a.N = np; a.K = np; a.alpha = 1.f; a.lda = np + GRID_PAD; a.ldb = a.lda; a.C = G32; a.ldc = np;
-            a.A = (const __hip_bfloat16*)Acat; a.B = (const __hip_bfloat16*)L.Hcat + (ph ? (long long)u0 * np * a.ldb : 0);
-            a.batch = mats; a.strideA = m.mat_rows * a.lda; a.strideB = (long long)np * a.ldb; a.strideC = m.mat_rows * np;
+            a.M = (int)m.mat_rows; a.N = np; a.alpha = 1.f; a.lda = a.ldb = pitch; a.C = L.G; a.ldc = np;
+            a.A = (const __hip_bfloat16*)L.Delta; a.B = (const __hip_bfloat16*)L.Hcat + (ph ? (long long)u0 * np * pitch : 0);
+            a.batch = mats; a.strideA = m.mat_rows * pitch; a.strideB = (long long)np * pitch; a.strideC = m.mat_rows * np;
             a.c_dtype = TBOA_F32; a.accumulate = 0; a.tag = TBOA_PROF_GRID;
-            a.segs = gs.terms; a.nterms = 2; a.termA[0] = a.termA[1] = a.A; a.termB[0] = a.B; a.termB[1] = a.B + (long long)L.nhin * np * a.ldb;
-            a.flags = TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED | TBOA_GEMM_CAUSAL_K;     // T' is lower triangular
-            TB_TRY(gemm_bf16_nt(ctx, a));
-            if (delta) {      // the low parts of delta against the first term of T'
-                a.A += lo_off; a.segs = nullptr; a.nterms = 1; a.accumulate = 1;
-                TB_TRY(gemm_bf16_nt(ctx, a));
-            }
+            const long long term = (long long)L.nhin * np * pitch;
+            a.nterms = delta ? 2 : 3;
+            for (int t = 0; t < a.nterms; ++t) { a.termA[t] = a.A; a.termB[t] = a.B + t * term; }
+            a.flags = TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED | TBOA_GEMM_CAUSAL_K;     // T' is lower triangular
             const long long crow = (long long)rows * ncand;
-            if (delta)
-                hipLaunchKernelGGL(grid_cost_kernel<true>, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, G32, Acat, rows, m, gs, L.cand_s, L.wdown, L.cost, lo_off);
-            else
-                hipLaunchKernelGGL(grid_cost_kernel<false>, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, G32, Acat, rows, m, gs, L.cand_s, L.wdown, L.cost, lo_off);
+            if (delta) {
+                GridScale gs = L.gscale;      // of the first matrix of this pass
+                gs.up += mo; gs.down += mo; gs.dcorr += mo; if (ph) { gs.scale += u0; gs.terms += u0; }
+                __half* Acat = (__half*)L.Delta;
+                const long long lo_off = (long long)mats * m.mat_rows * pitch;
+                hipLaunchKernelGGL(grid_delta_pair_kernel, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, (float)L.maxq, m, gs,
+                                   L.cand_s, L.cand_z, L.cand_r, L.wdown, Acat, lo_off);
+                TB_KERNEL_CHECK(ctx);
+                a.K = np; a.segs = gs.terms; a.flags |= TBOA_GEMM_F16;
+                TB_TRY(gemm_bf16_nt(ctx, a));
+                a.A += lo_off; a.segs = nullptr; a.nterms = 1; a.accumulate = 1;      // the low parts of delta against the first term of T'
+                TB_TRY(gemm_bf16_nt(ctx, a));
+                hipLaunchKernelGGL(grid_pair_cost_kernel, dim3((unsigned)((crow + 3) / 4)), dim3(256), 0, ctx->stream, (const float*)L.G, Acat, rows, m, gs, L.wdown, L.cost, lo_off);
+            } else {
+                GridInt gi2 = L.gint;
+                gi2.v += mo; gi2.hd += mo; if (ph) gi2.terms += u0;
+                signed char* Acat = (signed char*)L.Delta;
+                hipLaunchKernelGGL(grid_codes_kernel, dim3(cparts, rb, mats), dim3(256), 0, ctx->stream, Wc, ldw, L.Wf, n, (float)L.maxq, m, L.cand_s, L.cand_z, L.cand_r, Acat);
+                TB_KERNEL_CHECK(ctx);
+                a.K = np / 2; a.segs = gi2.terms; a.flags |= TBOA_GEMM_I8;
+                TB_TRY(gemm_bf16_nt(ctx, a));
+                // the digits of the weight rows against every digit of T', one result each (a third digit that is not taken is zero)
+                GemmBf16 w = a;
+                w.M = (int)gw.w_rows; w.A = (const __hip_bfloat16*)gw.A; w.C = L.gwp; w.segs = nullptr; w.nterms = 1; w.tag = -1;
+                w.batch = 3 * mats; w.batch_inner = 3; w.strideA = gw.w_rows * pitch; w.strideA2 = 0; w.strideB2 = term; w.strideC = 3 * gw.w_rows * np; w.strideC2 = gw.w_rows * np;
+                TB_TRY(gemm_bf16_nt(ctx, w));
+                hipLaunchKernelGGL(grid_weight_products_kernel, dim3((unsigned)((np + 255) / 256), rows), dim3(256), 0, ctx->stream, L.gwp, m, gw, gi2, L.gwv);
+                const long long parts = (ncand + GRID_KC - 1) / GRID_KC;
+                hipLaunchKernelGGL(grid_cost_kernel, dim3((unsigned)((rows * parts + 3) / 4)), dim3(256), 0, ctx->stream, (const int*)L.G, Acat, rows, m, gi2, L.cand_s, Wc, ldw, n, L.gwv, L.cost, L.gleast);
+            }
+            TB_KERNEL_CHECK(ctx);
             const int per = ph ? rows_per_head : rows, ngrp = rows / per;    // rows that share one H_in
             const int cap = per * GRID_KS;                                    // exact re-evaluations a group has room for
             int* cntv = L.sel; int* offv = cntv + rows; int* totv = offv + rows;
-            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, GRID_TAU, L.list, cntv, L.gstat);
+            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, delta ? GRID_TAU : GRID_TAU_INT, delta ? nullptr : L.gleast, L.list, cntv, L.gstat);
             hipLaunchKernelGGL(grid_scan_kernel, dim3(ngrp), dim3(256), 0, ctx->stream, cntv, per, cap, offv, totv, L.gstat);
             hipLaunchKernelGGL(grid_delta_sel_kernel, dim3((n + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
                                L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
@@ -935,10 +1125,18 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     TB_TRY(launch_symmetric_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hi));
     TB_TRY(launch_f32_to_f64_damp(ctx, n, nhin, H_in, d->damp, L.Hfac));
     if (L.fast_grid) {
-        const int np = grid_width(n);
-        hipLaunchKernelGGL(grid_scale_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale);
-        hipLaunchKernelGGL(grid_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.Hcat, (long long)nhin * np * (np + GRID_PAD));
-        hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, grid_one_term(d->bits), L.gstat + GS_ONE_TERM);
+        const bool delta = grid_delta(d->bits, n);
+        const int np = grid_width(n, delta);
+        const long long pitch = grid_pitch(np, delta), term = (long long)nhin * np * pitch;
+        if (delta) {
+            hipLaunchKernelGGL(grid_scale_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale);
+            hipLaunchKernelGGL(grid_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.Hcat, term);
+            hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, grid_one_term(d->bits), L.gstat + GS_SHORT);
+        } else {
+            hipLaunchKernelGGL(grid_int_steps_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.maxq, L.gint);
+            hipLaunchKernelGGL(grid_int_terms_kernel, dim3(nhin), dim3(256), 0, st, n, np, L.gint, L.grid_terms >= 2, L.gstat + GS_SHORT);
+            hipLaunchKernelGGL(grid_int_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, pitch, L.gint, (signed char*)L.Hcat, 2 * term);
+        }
         TB_KERNEL_CHECK(ctx);
     }
     // U_in, P and U_out are first needed by the first in-channel sweep; the grid search before it needs only W and H_in.
@@ -1228,8 +1426,12 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         const double guard = d->grid_guard > 0.0 ? d->grid_guard : 0.25;
         if (gs[GS_TRIPPED]) { free(host); return RUN_AGAIN_EXACT; }
         // a cost that its approximation misses by as much as itself (weights that lie on the candidate's grid but for the last bits) is no
-        // matter of the bits of H
-        if (dev > guard * GRID_TAU) { free(host); return gs[GS_ONE_TERM] && dev < 1.f ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT; }
+        // matter of the bits of H; nor is, with integers, one that it misses by a thousand times what two digits leave out
+        const bool delta = grid_delta(d->bits, n);
+        if (dev > (delta ? guard * GRID_TAU : std::min(guard * GRID_TAU, 0.25 * GRID_TAU_INT))) {
+            free(host);
+            return gs[GS_SHORT] && dev < (delta ? 1.f : 1e-3f) ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT;
+        }
     }
     if (want_loss) {
         double q = 0.0, c = 0.0;
@@ -1252,10 +1454,12 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     const size_t wn = (size_t)d->d_out * n, brows = (size_t)nh * blk;
     const int unit_rows = L.nhin > 1 ? (d->adaptive_grid ? blk : dh) : 1;
     const size_t grows = (size_t)(L.fast_grid ? L.fast_chunk : L.grid_chunk) * unit_rows;
+    const bool delta = grid_delta(d->bits, n);
+    const size_t np = grid_width(n, delta), mats = L.nhin > 1 ? L.fast_chunk : 1, mat_rows = L.nhin > 1 ? unit_rows : grows;      // of a pass of the two-phase search
     size_t delta_bytes = (size_t)L.grid_chunk * unit_rows * L.ncand * L.gsz * sizeof(double), g_bytes = delta_bytes;
     if (L.fast_grid) {
-        const size_t np = grid_width(n), mrows = (L.nhin > 1 ? (size_t)L.fast_chunk : 1) * grid_mat_rows(L.nhin > 1 ? unit_rows : (long long)grows, L.ncand);
-        delta_bytes = std::max(delta_bytes, (grid_delta(d->bits, n) ? 2 : 1) * mrows * (np + GRID_PAD) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
+        const size_t mrows = mats * rows16((long long)mat_rows * L.ncand);
+        delta_bytes = std::max(delta_bytes, (delta ? 2 : 1) * mrows * (size_t)grid_pitch((int)np, delta) * sizeof(__half)); g_bytes = std::max(g_bytes, mrows * np * sizeof(float));
     }
     const int fmax = n > dh ? n : dh;
     const int fb = (L.nhin > nh) ? L.nhin : nh;
@@ -1283,11 +1487,20 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     if (L.fast_grid) {
         L.DeltaS = ar.get<double>(grows * GRID_KS * n); L.GS = ar.get<double>(grows * GRID_KS * n);
         L.costS = ar.get<double>(grows * GRID_KS); L.sel = ar.get<int>(grows * 3); L.list = ar.get<int>(grows * L.ncand);
-        const size_t np = grid_width(n);
-        L.Hcat = ar.get<__half>((size_t)2 * L.nhin * np * (np + GRID_PAD));
-        L.gscale.up = ar.get<float>(L.nhin * np); L.gscale.down = ar.get<double>(L.nhin * np); L.gscale.dcorr = ar.get<float>(L.nhin * np);
-        L.gscale.off2 = ar.get<double>(L.nhin * np); L.gscale.scale = ar.get<double>(L.nhin); L.gscale.terms = ar.get<int>(L.nhin);
-        L.cand_r = ar.get<float>(grows * L.ncand); L.Wf = ar.get<float>(grows * np); L.wdown = ar.get<float>(grows);
+        const size_t cols = L.nhin * np;
+        L.Hcat = ar.get<__half>((delta ? 2 : 3) * cols * grid_pitch((int)np, delta));
+        L.cand_r = ar.get<float>(grows * L.ncand); L.Wf = ar.get<float>(grows * np);
+        if (delta) {
+            L.gscale.up = ar.get<float>(cols); L.gscale.down = ar.get<double>(cols); L.gscale.dcorr = ar.get<float>(cols);
+            L.gscale.off2 = ar.get<double>(cols); L.gscale.scale = ar.get<double>(L.nhin); L.gscale.terms = ar.get<int>(L.nhin);
+            L.wdown = ar.get<float>(grows);
+        } else {
+            L.gint.v = ar.get<double>(cols); L.gint.hd = ar.get<double>(cols); L.gint.v2 = ar.get<double>(cols); L.gint.v3 = ar.get<double>(cols);
+            L.gint.e2 = ar.get<double>(cols); L.gint.terms = ar.get<int>(L.nhin);
+            const size_t w_rows = mats * rows16(GRID_WD * (long long)mat_rows);
+            L.gwt.A = (signed char*)ar.get<__half>(w_rows * grid_pitch((int)np, delta)); L.gwt.wu = ar.get<double>(grows);
+            L.gwp = ar.get<int>(3 * w_rows * np); L.gwv = ar.get<double>(grows * np); L.gleast = ar.get<double>(grows);
+        }
     }
     L.Wbar = ar.get<double>(wn); L.Abar = ar.get<double>(wn); L.Z = ar.get<double>(wn);
     L.WR = R ? ar.get<double>(wn) : nullptr;
@@ -1337,8 +1550,10 @@ void init_layer(Layer& L, tboa_ctx* ctx, const tboa_layer_desc* d) {
     // the two-phase search holds 2 + 4 bytes per entry where the exact one holds 8 + 8: twice the rows in the same buffers
     L.fast_chunk = c < 0.5 ? 1 : (2.0 * c > units ? units : (int)(2.0 * c));
     // per-row grids of wide layers: two-phase search (a negative grid_guard asks for exact costs throughout).  Narrow layers
-    // (d_in < 256) keep the exact search: one launch over all candidates, nothing to re-evaluate
-    L.fast_grid = (!d->group && L.n >= 256 && !(d->grid_guard < 0.0)) ? 1 : 0;
+    // (d_in < 256) keep the exact search: one launch over all candidates, nothing to re-evaluate.  So do steps of few rows whose fp64 products are a few
+    // microseconds: a search is 5 launches then and not 12 (block of 256 columns, 4 rows a head and step: 5.3 instead of 6.3 ms)
+    const bool few = d->adaptive_grid && blk < 16 && (double)L.nh * blk * L.ncand * (double)L.nn <= 1e9;
+    L.fast_grid = (!d->group && L.n >= 256 && !few && !(d->grid_guard < 0.0)) ? 1 : 0;
     L.gstat = ctx ? ctx->d_status + TB_GSTAT_WORD : nullptr;
 }
 

@@ -1,0 +1,46 @@
+"""The integer form of the grid search's products (2 bits, 3 bits up to 2048 columns): products of bytes by digits against 64-bit sums, at the edges of its
+256-column padding and of its two and three digits, through layers whose results must be those of exact costs (GPU)."""
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def layer(n, rows, seed, kind):
+    g = torch.Generator(device="cuda"); g.manual_seed(seed)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float64)
+    x = rnd(2 * n, n)
+    if kind == "factors":          # a few common factors: costs far below the trace
+        x = x + 3.0 * rnd(2 * n, 4) @ rnd(4, n)
+    elif kind == "one channel":    # one channel holds nearly all of the variance
+        x[:, n // 3] *= 3e3
+    elif kind == "signs":          # entries of T of one sign and one size: the sums that the step of a row has to bound
+        x = 1.0 + 1e-2 * x
+    return (rnd(rows, n) * 0.02).float(), (x.T @ x).float()
+
+
+@pytest.mark.parametrize("kind", ["independent", "factors", "one channel", "signs"])
+@pytest.mark.parametrize("bits,n,rows", [(2, 256, 16), (2, 511, 33), (2, 513, 130), (3, 768, 40), (3, 2048, 20), (2, 3000, 24)])
+def test_equals_exact(lib, bits, n, rows, kind):
+    W, H = layer(n, rows, n + bits, kind)
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, None, None, 1, bits, rows)
+    assert ctx.counter(0) > 0 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    exact = ctx.quantize_layer(W, H, None, None, 1, bits, rows, grid_guard=-1.0)
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(fast[k], exact[k]), k
+    ctx.close()
+
+
+@pytest.mark.parametrize("block", [4, 15, 16])
+def test_few_rows_a_step(lib, block):
+    """Steps of fewer than 16 rows take exact costs at once; the results are those of either."""
+    W, H = layer(320, 32, 3, "independent")
+    ctx = lib.Context()
+    Ho = torch.eye(32, device="cuda")[None] * 2 + 0.1
+    fast = ctx.quantize_layer(W, H, Ho, None, 1, 2, block)
+    assert (ctx.counter(0) > 0) == (block >= 16)
+    exact = ctx.quantize_layer(W, H, Ho, None, 1, 2, block, grid_guard=-1.0)
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(fast[k], exact[k]), k
+    ctx.close()
