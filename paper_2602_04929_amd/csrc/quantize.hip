@@ -117,6 +117,116 @@ __global__ __launch_bounds__(256) void grid_argmin_kernel(const double* __restri
     z_out[lr * ng + gi] = cand_z[(long long)row * ncand + best];
 }
 
+// clamp(round(w / s) + z) - z of one weight.  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so wherever it is further than
+// 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
+__device__ __forceinline__ float grid_code(float wf, float inv, float z, float maxq, const double* w, bool exists, double s) {
+    const float t = wf * inv;
+    float r = rintf(t);
+    const bool safe = inv != 0.f && fabsf(t - r) < 0.5f - (fabsf(t) * 9.5367431640625e-7f + 9.5367431640625e-7f);
+    if (!safe && exists) r = (float)fmin(fmax(rint(*w / s), -1024.0), 1024.0);
+    return fminf(fmaxf(r + z, 0.f), maxq) - z;
+}
+
+// The whole search over 32, 64 or 128 columns with exact costs (a grid per group of columns, narrow layers): candidates, their errors, the products with H_in and
+// the minimum of a row in one workgroup, nothing of it in memory.  H_in's block stays in registers for all rows of a workgroup, in the lanes of the fp64 MFMA's right operand: wavefront
+// w owns the tiles w and NT - 1 - w of 16 columns (NT = 4, 2: tile w), and of the symmetric block each column tile only takes the rows up to its own (doubled
+// above it: delta H delta^T = delta T delta^T).  Sixteen candidates at a time: every thread forms delta for its column, LDS hands it to the wavefronts as left operand
+// and, after the products, to be multiplied with them.  The MFMAs are 36 of 64 tiles, 24 us of those 82; forming delta and handing it over are the rest.
+// Separate launches (candidates, delta, product, row sums, minimum) wrote and read delta and the products, 105 MB each for 1280 rows x 80 candidates x 128 columns:
+// 144 us, now 82 us.
+template <int NT>
+__global__ __launch_bounds__(256) void grid_group_kernel(const double* __restrict__ Wk, long long ldw, int c0, const double* __restrict__ H, long long h_stride, int n, int rows_per_mat,
+                                                         int rows_wg, int ncand, int grid_points, double maxq, BlockMap m, double* __restrict__ s_out, double* __restrict__ z_out,
+                                                         int ng, int gi) {
+    typedef double v4d __attribute__((ext_vector_type(4)));
+    constexpr int NC = 16 * NT, P = NC + 4, PER = 256 / NC, MAXC = 256;      // (pitch: 16 rows fall into different banks)
+    constexpr bool PAIR = NT == 8;
+    __shared__ double D[2][16][P], cs[MAXC], cz[MAXC], part[4][MAXC], ws[NC];
+    __shared__ float cr[MAXC];
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6), l16 = lane & 15, lk = lane >> 4;
+    const int mat = blockIdx.y, r_lo = blockIdx.x * rows_wg, r_hi = min(rows_per_mat, r_lo + rows_wg), tiles = (ncand + 15) / 16;
+    const int j2 = PAIR ? NT - 1 - wave : wave, j1 = wave;      // column tiles of this wavefront (j1: NT = 8)
+    const double* Hm = H + mat * h_stride + (long long)c0 * n + c0;
+    double b2[4 * NT], b1[PAIR ? 2 * NT : 1];
+#pragma unroll
+    for (int i = 0; i < 4 * NT; ++i) b2[i] = (j2 < NT && i / 4 <= j2) ? (i / 4 < j2 ? 2.0 : 1.0) * Hm[(long long)(4 * i + lk) * n + 16 * j2 + l16] : 0.0;
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int i = 0; i < 2 * NT; ++i) b1[i] = i / 4 <= j1 ? (i / 4 < j1 ? 2.0 : 1.0) * Hm[(long long)(4 * i + lk) * n + 16 * j1 + l16] : 0.0;
+    }
+    for (int r = r_lo; r < r_hi; ++r) {
+        const int row = mat * rows_per_mat + r;
+        const double* w = Wk + (long long)row * ldw + c0;
+        double lo = 0.0, hi = 0.0;
+        for (int c = lane; c < NC; c += 64) { const double v = w[c]; lo = fmin(lo, v); hi = fmax(hi, v); }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { lo = fmin(lo, __shfl_xor(lo, o, 64)); hi = fmax(hi, __shfl_xor(hi, o, 64)); }
+        if (lo == hi) { lo = -1.0; hi = 1.0; }
+        __syncthreads();      // the last row's costs have been read
+        if (t < NC) ws[t] = w[t];
+        for (int k = t; k < ncand; k += 256) {
+            const double p = 1.0 - (double)k / (double)grid_points;
+            const double s = (p * hi - p * lo) / maxq, i = 1.0 / s;
+            cs[k] = s; cz[k] = rint(-(p * lo) / s);
+            cr[k] = (i >= 1.17549435e-38 && i <= 3.4e38) ? (float)i : 0.f;
+        }
+        __syncthreads();
+        const int c = t % NC;
+        const double wv = ws[c];
+        const float wf = (float)wv;
+        for (int ct = 0; ct < tiles; ++ct) {
+            double (&Db)[16][P] = D[ct & 1];
+#pragma unroll
+            for (int i = 0; i < 16 / PER; ++i) {
+                const int q = i * PER + t / NC, k = min(16 * ct + q, ncand - 1);
+                Db[q][c] = cs[k] * (double)grid_code(wf, cr[k], (float)cz[k], (float)maxq, &wv, true, cs[k]) - wv;
+            }
+            __syncthreads();      // (the other buffer is written after every wavefront has passed here, done with it)
+            double cost[4] = {0.0, 0.0, 0.0, 0.0};
+            if (j2 < NT) {
+                v4d x2 = {0.0, 0.0, 0.0, 0.0}, x1 = x2;
+#pragma unroll
+                for (int kt = 0; kt < NT; ++kt) {
+                    if (kt > j2) break;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const double a = Db[l16][16 * kt + 4 * u + lk];
+                        x2 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b2[4 * kt + u], x2, 0, 0, 0);
+                        if constexpr (PAIR) { if (kt < NT / 2 && kt <= j1) x1 = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b1[(4 * kt + u) % (2 * NT)], x1, 0, 0, 0); }
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    cost[v] = x2[v] * Db[lk + 4 * v][16 * j2 + l16];
+                    if constexpr (PAIR) cost[v] += x1[v] * Db[lk + 4 * v][16 * j1 + l16];
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+#pragma unroll
+                for (int o = 8; o > 0; o >>= 1) cost[v] += __shfl_xor(cost[v], o, 64);
+                if (l16 == 0 && 16 * ct + lk + 4 * v < ncand) part[wave][16 * ct + lk + 4 * v] = cost[v];
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {      // as grid_argmin_kernel
+            double bc = 0.0; int best = 0x7fffffff;
+            bool first = true;
+            for (int k = lane; k < ncand; k += 64) {
+                const double v = (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
+                if (k == 0) first = v == v;
+                if (v == v && (best == 0x7fffffff || v < bc)) { bc = v; best = k; }
+            }
+            wave_argmin(bc, best);
+            if (lane == 0) {
+                if (best == 0x7fffffff || !first) best = 0;
+                const long long lr = layer_row(m, row);
+                s_out[lr * ng + gi] = cs[best]; z_out[lr * ng + gi] = cz[best];
+            }
+        }
+    }
+}
+
 // ---- two-phase search: approximate costs of all candidates on the 16-bit matrix cores, exact fp64 costs of the few
 // candidates within GRID_TAU of the approximate minimum.
 //
@@ -373,16 +483,6 @@ __global__ __launch_bounds__(256) void grid_rows_kernel(const double* __restrict
             for (int k = 0; k < GRID_WD; ++k) *(uint4*)(A + 2 * tboa_blocked_offset((long long)k * m.per + rl, c / 2, m.pitch >> 5)) = d[k].u;
         }
     }
-}
-
-// clamp(round(w / s) + z) - z of one weight.  The quotient is that of fp64: fl32(w) fl32(1 / s) is within 2^-22 (relative) of it, so wherever it is further than
-// 2^-20 |t| from a half-integer both round to the same integer; only the others take the fp64 division.
-__device__ __forceinline__ float grid_code(float wf, float inv, float z, float maxq, const double* w, bool exists, double s) {
-    const float t = wf * inv;
-    float r = rintf(t);
-    const bool safe = inv != 0.f && fabsf(t - r) < 0.5f - (fabsf(t) * 9.5367431640625e-7f + 9.5367431640625e-7f);
-    if (!safe && exists) r = (float)fmin(fmax(rint(*w / s), -1024.0), 1024.0);
-    return fminf(fmaxf(r + z, 0.f), maxq) - z;
 }
 
 // qbar of every (row, candidate) as bytes; a wavefront makes whole blocks of 16 rows x 64: lane = (row of the block lane / 4, sixteen columns of lane % 4)
@@ -988,6 +1088,20 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
     const int units = ph ? nh : total_rows;                 // chunk unit: a head or a row
     const int rows_per_unit = ph ? rows_per_head : 1;
     const bool fast = L.fast_grid && c0 == 0 && ncols == L.n;
+    if (!fast && ncand <= 256 && (ncols == 32 || ncols == 64 || ncols == 128)) {
+        const int mats = ph ? nh : 1, per = ph ? rows_per_head : total_rows, rows_wg = std::max(1, (total_rows + 511) / 512);      // two workgroups of 128 columns fit a CU
+        const dim3 grid((unsigned)((per + rows_wg - 1) / rows_wg), (unsigned)mats);
+        ProfRec rec{}; bool timed = false;
+        if (ctx->prof_on) TB_TRY(prof_begin(ctx, TBOA_PROF_F64_GRID, (double)total_rows * ncand * ncols * (ncols + 16.0), rec, timed));
+#define TB_GROUP(NT) hipLaunchKernelGGL(grid_group_kernel<NT>, grid, dim3(256), 0, ctx->stream, Wrows, ldw, c0, L.Hi, ph ? L.nn : 0LL, L.n, per, rows_wg, ncand, \
+                                        L.d->grid_points, L.maxq, map, L.s64, L.z64, L.ng, gi)
+        if (ncols == 128) TB_GROUP(8);
+        else if (ncols == 64) TB_GROUP(4);
+        else TB_GROUP(2);
+#undef TB_GROUP
+        TB_KERNEL_CHECK(ctx);
+        return prof_end(ctx, rec, timed);
+    }
     const int chunk = fast ? L.fast_chunk : L.grid_chunk;
     for (int u0 = 0; u0 < units; u0 += chunk) {
         const int nu = (units - u0 < chunk) ? units - u0 : chunk;
