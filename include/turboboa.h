@@ -58,12 +58,12 @@ void tboa_destroy(tboa_ctx* ctx);
 const char* tboa_last_error(const tboa_ctx* ctx);
 /* Event counters of this context since its creation (host values).
  * TBOA_CTR_GRID_PASSES: grid-search passes that used the two-phase search (approximate costs of all candidates on the
- * 16-bit matrix cores, exact fp64 costs of the near-minimal ones); TBOA_CTR_GRID_FALLBACKS: tboa_quantize_layer calls whose
+ * matrix cores, exact fp64 costs of the near-minimal ones); TBOA_CTR_GRID_FALLBACKS: tboa_quantize_layer calls whose
  * two-phase search did not trust itself (see tboa_layer_desc.grid_guard) and that were therefore run again with every
  * candidate of every row evaluated in fp64; TBOA_CTR_GRID_EXACT_ROWS: unused, always 0;
  * TBOA_CTR_GRID_SURVIVORS: near-minimal candidates that were evaluated exactly (rows with a single near-minimal
- * candidate need none); TBOA_CTR_GRID_TWO_TERM_RUNS: tboa_quantize_layer calls that were run again with H_in as two half terms in the
- * approximate costs where one had been taken.
+ * candidate need none); TBOA_CTR_GRID_TWO_TERM_RUNS: tboa_quantize_layer calls that were run again with the longer form of H_in in
+ * the approximate costs (two half terms, three digits) where the shorter one (one term, two digits) had been taken.
  * TBOA_CTR_WEIGHTS_INT_FORM / TBOA_CTR_WEIGHTS_HILO: dequantized fp32 weight matrices handed to
  * tboa_build_hessian_out_proj or tboa_swiglu_forward that were found to be integer multiples of one step per row (one
  * bf16 GEMM with exact operands per product) / that were not and were split into bf16 terms (two or three). */
@@ -213,10 +213,11 @@ typedef struct {
     double max_shrink;  /* candidates k = 0 .. ceil(max_shrink*grid_points)-1, range scaled by 1-k/grid_points */
     double damp;        /* every Hessian gets damp * mean(diag) added to its diagonal at entry        */
     double grid_guard;  /* the grid search of wide per-row layers (d_in >= 256, group = 0) finds its candidates' costs
-                           approximately on the 16-bit matrix cores and re-evaluates the near-minimal ones (within tau = 2e-3
-                           of the minimum) in fp64; every re-evaluation is compared with its approximation, and a call in
-                           which one differs by more than grid_guard * tau (relative) is run again with fp64 costs for every
-                           candidate (where H_in went in as one half term: with two terms first).  0: the default, 0.25.  Negative: fp64 costs for every candidate from the start. */
+                           approximately on the matrix cores and re-evaluates the near-minimal ones (within 2e-3, coarse grids
+                           1e-3, of the minimum) in fp64; every re-evaluation is compared with its approximation, and a call in
+                           which one differs by more than grid_guard * 2e-3 (relative; coarse grids: at most 2.5e-4) is run again with
+                           fp64 costs for every candidate (where the shorter form of H_in was taken: with the longer one first).  0: the
+                           default, 0.25.  Negative: fp64 costs for every candidate from the start. */
 } tboa_layer_desc;
 
 /* Workspace that tboa_quantize_layer needs for this descriptor, called with (with_H_out != 0) or without H_out and with

@@ -177,13 +177,13 @@ __device__ __forceinline__ void store_acc_interior(const Args& g, const f32x16 (
 
 // C in 16 x 32 blocks (TBOA_GEMM_C_TILED; bf16, whole tiles): the 8 bytes of a lane go to row (8 b + 4 (l / 32) + l % 4) % 16
 // of block (row / 16, column / 32), piece ((l % 32) / 8) ^ ((row % 16) / 4) of that row, first or second half of the piece
-template <int TJ, bool SCALE>
-__device__ __forceinline__ void store_acc_tiled(const Args& g, const f32x16 (&acc)[4][TJ], int row0, int col0, long long coff) {
+template <bool SCALE, int TI, int TJ>
+__device__ __forceinline__ void store_acc_tiled(const Args& g, const f32x16 (&acc)[TI][TJ], int row0, int col0, long long coff) {
     const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5, q = l32 & 3, c = l32 >> 2;
     const long long kb = g.ldc >> 5;
     __hip_bfloat16* base = (__hip_bfloat16*)g.C + coff + ((long long)(row0 >> 4) * kb + (col0 >> 5)) * 512;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int ri = 8 * (b & 1) + 4 * lh + q, cs = (c >> 1) ^ ((2 * (b & 1) + lh) & 3);
@@ -282,21 +282,21 @@ __device__ __forceinline__ void store_acc_bits(const Args& g, const f32x16 (&acc
         }
 }
 
-template <int TJ>
-__device__ __forceinline__ void store_acc(const Args& g, const f32x16 (&acc)[4][TJ], int row0, int col0, long long coff) {
+template <int TI, int TJ>
+__device__ __forceinline__ void store_acc(const Args& g, const f32x16 (&acc)[TI][TJ], int row0, int col0, long long coff) {
     if (g.flags & TBOA_GEMM_C_TILED) {
-        if (g.alpha == 1.0f) store_acc_tiled<TJ, false>(g, acc, row0, col0, coff);
-        else store_acc_tiled<TJ, true>(g, acc, row0, col0, coff);
+        if (g.alpha == 1.0f) store_acc_tiled<false>(g, acc, row0, col0, coff);
+        else store_acc_tiled<true>(g, acc, row0, col0, coff);
         return;
     }
-    if (g.vec_c && row0 + 128 <= g.M && col0 + 32 * TJ <= g.N) {
+    if (g.vec_c && row0 + 32 * TI <= g.M && col0 + 32 * TJ <= g.N) {
         if (g.alpha == 1.0f) store_acc_interior<false>(g, acc, row0, col0, coff);
         else store_acc_interior<true>(g, acc, row0, col0, coff);
         return;
     }
     const int lane = threadIdx.x & 63, l32 = lane & 31, lh = lane >> 5;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int row = row0 + 32 * i + 8 * b + 4 * lh + (l32 & 3);
@@ -424,7 +424,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_nt_kernel(Args g) {
     }
 
     transpose_acc(acc);
-    store_acc<4>(g, acc, m0 + __builtin_amdgcn_readfirstlane(wm), n0 + __builtin_amdgcn_readfirstlane(wn), z1 * g.sC1 + z2 * g.sC2);
+    store_acc(g, acc, m0 + __builtin_amdgcn_readfirstlane(wm), n0 + __builtin_amdgcn_readfirstlane(wn), z1 * g.sC1 + z2 * g.sC2);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -661,7 +661,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_bf16_nt_fast_kernel(Args g) {
     if constexpr (KIND == 2) store_acc_bits(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
     else if (g.half_n) store_acc_gate_up(g, acc, r0, c0);
     else if (g.col_scale || g.residual) store_acc_linear<TJ>(g, acc, r0, c0);
-    else store_acc<TJ>(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
+    else store_acc(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
         // issued: the first NS - 1 stages of the next tile then need no wait, and by the time stage NS is awaited the stores
         // (which count among the outstanding operations) have had NS - 1 stage times to be acknowledged
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        store_acc<TJ>(g, acc, cur.m0 + __builtin_amdgcn_readfirstlane(wm), cur.n0 + __builtin_amdgcn_readfirstlane(wn), cur.coff);
+        store_acc(g, acc, cur.m0 + __builtin_amdgcn_readfirstlane(wm), cur.n0 + __builtin_amdgcn_readfirstlane(wn), cur.coff);
         if (!nxt.valid) break;
         cur = nxt;                       // the stream entered this tile at least one stage ago
         nxt = decode(raw2); nxt_taken = false;
@@ -847,30 +847,31 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 // wavefront has 64 x 64 results instead of 128 x 64.  LDS then binds (eight wavefronts read 32 KB and write 12 KB per 256 cycles of MFMAs): 1.0 PFLOP/s at
 // 11008 x 11008 x 16384, H and R of 8192 tokens 8.9 -> 4.9 ms.  (96 x 64 per wavefront does not fit the registers: 35 spilled, 14.8 ms; 256 x 128 per
 // workgroup: 5.05.)
-template <int TI, int TJ, int WM, int WN, int NS, bool F16>
+template <int TI, int TJ, int WM, int WN, int NS, bool F16, bool FOLD>
 __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, double scale) {
     constexpr int TM = 32 * TI * WM, TN = 32 * TJ * WN, BLKS = (TM + TN) / 16, LPW = (BLKS + 7) / 8, STAGE_BYTES = (TM + TN) * FK * 2;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     int z, tm, tn;
     if (!work_item(g, z, tm, tn)) return;
     const int m0 = tm * TM, n0 = tn * TN;
-    const int nk_seg = g.kseg / FK, nk = g.K / FK;
+    const int z1 = z / g.batch_inner, z2 = z % g.batch_inner;
+    const int kend = (g.flags & TBOA_GEMM_CAUSAL_K) ? min(g.kseg, n0 + TN) : g.kseg, nk = kend / FK * (g.K / g.kseg);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = (wave / WN) * (32 * TI), wn = (wave % WN) * (32 * TJ);
     const int l32 = lane & 31, lh = lane >> 5;
-    f32x16 acc[TI][TJ], sum[TI][TJ];
+    f32x16 acc[TI][TJ], sum[FOLD ? TI : 1][FOLD ? TJ : 1];
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
         for (int j = 0; j < TJ; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.0f; sum[i][j][v] = 0.0f; }
+            for (int v = 0; v < 16; ++v) { acc[i][j][v] = 0.0f; if constexpr (FOLD) sum[i][j][v] = 0.0f; }
 
     // this wavefront's LPW blocks (16 rows x 32) of a stage, the A tile's first; where 8 LPW exceeds their number the last one is copied more than once
-    const bool tiled = g.flags & TBOA_GEMM_A_TILED;
-    const int sh = tiled ? 4 : 0, wave_s = __builtin_amdgcn_readfirstlane(wave);
-    const char* Abase = (const char*)(g.A + (long long)m0 * g.lda);
-    const char* Bbase = (const char*)(g.B + (long long)n0 * g.ldb);
+    const bool tiledA = g.flags & TBOA_GEMM_A_TILED, tiledB = g.flags & TBOA_GEMM_B_TILED;
+    const int shA = tiledA ? 4 : 0, shB = tiledB ? 4 : 0, wave_s = __builtin_amdgcn_readfirstlane(wave);
+    const char* Abase = (const char*)(g.A + z1 * g.sA1 + z2 * g.sA2 + (long long)m0 * g.lda);
+    const char* Bbase = (const char*)(g.B + z1 * g.sB1 + z2 * g.sB2 + (long long)n0 * g.ldb);
     unsigned off[LPW];
 #pragma unroll
     for (int i = 0; i < LPW; ++i) {
@@ -878,12 +879,12 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
         const long long ld = inB ? g.ldb : g.lda;
         const int last = (inB ? g.N - n0 : g.M - m0) - 1;                 // last row of the operand, from the tile's first
         const int row = 16 * b + (lane >> 2), lc = (lane & 3) ^ ((row >> 2) & 3);
-        off[i] = tiled ? (unsigned)((long long)min(b, last >> 4) * (ld >> 5) * 1024 + lane * 16) : (unsigned)(((long long)min(row, last) * ld + lc * 8) * 2);
+        off[i] = (inB ? tiledB : tiledA) ? (unsigned)((long long)min(b, last >> 4) * (ld >> 5) * 1024 + lane * 16) : (unsigned)(((long long)min(row, last) * ld + lc * 8) * 2);
     }
     int kin = 0, term = 0; long long koff = 0;
     auto advance = [&]() {
         kin += FK; koff += 2 * FK;
-        if (kin == g.kseg) { kin = 0; koff = 0; Abase += g.term_dA[term]; Bbase += g.term_dB[term]; if (term < 2) ++term; }
+        if (kin == kend) { kin = 0; koff = 0; Abase += g.term_dA[term]; Bbase += g.term_dB[term]; if (term < 2) ++term; }
     };
     const unsigned ring_lds = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)smem);
     auto issue_one = [&](int i, const char* pa, const char* pb, unsigned st) {
@@ -891,7 +892,7 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
         lds_direct_16(off[i], blk >= TM / 16 ? pb : pa, st + (unsigned)blk * 1024u);
     };
     auto issue = [&](int slot) {
-        const char* pa = Abase + (koff << sh); const char* pb = Bbase + (koff << sh);
+        const char* pa = Abase + (koff << shA); const char* pb = Bbase + (koff << shB);
         advance();
 #pragma unroll
         for (int i = 0; i < LPW; ++i) issue_one(i, pa, pb, ring_lds + (unsigned)(slot * STAGE_BYTES));
@@ -912,6 +913,7 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
             for (int j = 0; j < TJ; ++j) acc[i][j] = mma16<F16>(fa[set][i], fb[set][j], acc[i][j]);
     };
     auto fold = [&]() {
+        if constexpr (FOLD)
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -927,13 +929,13 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
     if (nk < NS) wait_loads_but<0>(); else wait_loads_but<(NS - 1) * LPW>();
     __syncthreads();
     frags(0, 0, 0);
-    int kt = 0, next = flush;
+    int kt = 0, next = FOLD ? flush : nk;
     for (; kt + 2 * NS - 1 < nk; kt += NS) {
         if (kt >= next) { fold(); next += flush; }
 #pragma unroll
         for (int u = 0; u < NS; ++u) {
             __builtin_amdgcn_sched_barrier(0);
-            const char* pa = Abase + (koff << sh); const char* pb = Bbase + (koff << sh);
+            const char* pa = Abase + (koff << shA); const char* pb = Bbase + (koff << shB);
             const unsigned st = ring_lds + (unsigned)(u * STAGE_BYTES);
             advance();
             frags(1, u, 1);
@@ -968,6 +970,7 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
         }
         mma(1);
     }
+    if constexpr (FOLD)
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -976,6 +979,7 @@ __global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, doubl
             for (int v = 0; v < 16; ++v) acc[i][j][v] = (float)(scale * ((double)sum[i][j][v] + (double)acc[i][j][v]));
     transpose_acc(acc);
     const int r0 = m0 + __builtin_amdgcn_readfirstlane(wm), c0 = n0 + __builtin_amdgcn_readfirstlane(wn);
+    if constexpr (!FOLD) { store_acc(g, acc, r0, c0, z1 * g.sC1 + z2 * g.sC2); return; }
     if (g.vec_c && r0 + 32 * TI <= g.M && c0 + 32 * TJ <= g.N) { store_acc_interior<false>(g, acc, r0, c0, 0); return; }
 #pragma unroll
     for (int i = 0; i < TI; ++i)
@@ -1082,6 +1086,11 @@ int tile_schedule(tboa_ctx* ctx, const GemmBf16& q, int tiles_m, int tiles_n, co
     return 0;
 }
 
+}  // namespace
+
+namespace {
+constexpr int GRAM_TI = 2, GRAM_TJ = 2, GRAM_WM = 2, GRAM_WN = 4, GRAM_NS = 4;      // 128 x 256 per workgroup
+constexpr int GRAM_ROWS = 32 * GRAM_TI * GRAM_WM, GRAM_COLS = 32 * GRAM_TJ * GRAM_WN;
 }  // namespace
 
 int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
@@ -1193,6 +1202,32 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
             a.term_dB[t] = ((const char*)q.termB[t + 1] - (const char*)q.termB[t]) - bytesB;
         }
     } else if (q.segs || q.last_scale != 1.f) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: terms to choose from or to scale need several operand pairs");
+    // Results of at most 128 rows (P V: the head dimension) take tiles of 128 x 256: a tile of 256 x 256 copies and multiplies as many rows that do not exist.  32 heads of 128 x 2048
+    // from pairs of probabilities, three terms with a causal limit: 162 -> 155 us (reading the probabilities then binds); a whole forward pass of 4 x 512 tokens 2 - 4 % less.
+    const int segs_all = q.nterms > 1 ? q.nterms : q.kseg > 0 ? q.K / q.kseg : 1;
+    if (fast && (q.flags & TBOA_GEMM_PERSISTENT) && q.M <= GRAM_ROWS && q.N >= GRAM_COLS && segs_all <= 4 && !q.accumulate && !q.col_scale && !q.residual && !q.gate_up && (q.nterms <= 1 || q.kseg == 0 || q.kseg * q.nterms == q.K) &&
+        !(q.flags & (TBOA_GEMM_LOWER | TBOA_GEMM_KLO | TBOA_GEMM_C_TILED | TBOA_GEMM_I8))) {
+        const long long seg = q.K / segs_all;
+        a.kseg = (int)seg; a.K = q.K;
+        for (int t = 0; t + 1 < segs_all; ++t) {
+            a.term_dA[t] = q.nterms > 1 ? (const char*)q.termA[t + 1] - (const char*)q.termA[t] : (seg * 2) << ((q.flags & TBOA_GEMM_A_TILED) ? 4 : 0);
+            a.term_dB[t] = q.nterms > 1 ? (const char*)q.termB[t + 1] - (const char*)q.termB[t] : (seg * 2) << ((q.flags & TBOA_GEMM_B_TILED) ? 4 : 0);
+        }
+        TB_TRY(tile_order(ctx, 1, (int)cdiv64(q.N, GRAM_COLS), q.flags & TBOA_GEMM_CAUSAL_K, &a.tile_order, &a.ntiles, GRAM_ROWS, GRAM_COLS));
+        a.nitems = (long long)a.ntiles * q.batch; a.chunk = q.batch >= 8 ? 32 : 0;
+        a.per = a.chunk ? ((a.nitems + a.chunk - 1) / a.chunk + 7) / 8 * a.chunk : (a.nitems + 7) / 8;
+        constexpr int smem_narrow = GRAM_NS * (GRAM_ROWS + GRAM_COLS) * FK * 2;
+        const dim3 wgs((unsigned)(8 * a.per));
+        if (f16) {
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
+            hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
+        } else {
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
+            hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
+        }
+        TB_KERNEL_CHECK(ctx);
+        return prof_end(ctx, rec, timed);
+    }
     const bool persistent = fast && (q.kseg > 0 ? q.kseg : q.K) % (FK * 4) == 0 && (q.flags & TBOA_GEMM_PERSISTENT) != 0;
     if (persistent) {
         int wgs = 0;
@@ -1210,10 +1245,6 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     return 0;
 }
 
-namespace {
-constexpr int GRAM_TI = 2, GRAM_TJ = 2, GRAM_WM = 2, GRAM_WN = 4, GRAM_NS = 4;      // 128 x 256 per workgroup
-constexpr int GRAM_ROWS = 32 * GRAM_TI * GRAM_WM, GRAM_COLS = 32 * GRAM_TJ * GRAM_WN;
-}  // namespace
 
 long long gemm_gram_tiles(int M, int N, int lower) {
     const long long tm = cdiv64(M, GRAM_ROWS), tn = cdiv64(N, GRAM_COLS);
@@ -1247,13 +1278,13 @@ int gemm_gram(tboa_ctx* ctx, const GemmBf16& q, double scale, int chunk) {
     constexpr int smem = GRAM_NS * (GRAM_ROWS + GRAM_COLS) * FK * 2;
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on && q.tag >= 0) TB_TRY(prof_begin(ctx, q.tag, ((q.flags & TBOA_GEMM_LOWER) ? (double)q.M * (q.M + 1.0) : 2.0 * q.M * q.N) * q.K, rec, timed));
-    const void* kern = (q.flags & TBOA_GEMM_F16) ? (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true>
-                                                 : (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false>;
+    const void* kern = (q.flags & TBOA_GEMM_F16) ? (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, true>
+                                                 : (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, true>;
     TB_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     if (q.flags & TBOA_GEMM_F16)
-        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
     else
-        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
     TB_KERNEL_CHECK(ctx);
     return prof_end(ctx, rec, timed);
 }

@@ -2,9 +2,9 @@
 //
 // Heads are independent and run side by side: the N rows of the current step of every head form one
 // "block" of n_heads*N rows (block row R = h*nbr + r  <->  layer row h*d_h + i0 + r).  Per step:
-//   grid search   (Alg. 1 line 9)  candidates -> approximate costs of all of them on the 16-bit matrix cores (integer codes against
-//                                  H_in as one or two half terms) -> exact fp64 costs of the near-minimal ones -> argmin
-//                                  (narrow layers and group-wise grids: every candidate exactly, one fp64 GEMM)
+//   grid search   (Alg. 1 line 9)  candidates -> approximate costs of all of them on the matrix cores (integer codes against
+//                                  digits of H_in, or pairs of errors against half terms) -> exact fp64 costs of the near-minimal ones -> argmin
+//                                  (narrow layers and group-wise grids: every candidate exactly, one kernel or one fp64 GEMM)
 //   in-channel sweep (Algorithm 3) groups of 512 columns (sweep.hip); the columns right of a group get one rank-512 GEMM update per term
 //   compensation  (Prop. 3.1/3.2)  T = [U_out^T]_{i1:,B} [U_out^T]_{B,B}^-1 per head, then W~[i1:] -= T E as a
 //                                  batched GEMM, E = (W_B - Q_B) - ((W_B R) U_in^T) U_in
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void grid_group_kernel(const double* __restric
     }
 }
 
-// ---- two-phase search: approximate costs of all candidates on the 16-bit matrix cores, exact fp64 costs of the few
+// ---- two-phase search: approximate costs of all candidates on the matrix cores, exact fp64 costs of the few
 // candidates within GRID_TAU of the approximate minimum.
 //
 // With T the part of H below its diagonal, delta H delta^T = sum_c delta_c (2 (delta T^T)[c] + H_cc delta_c) (H is symmetric; the product then needs, for
