@@ -1203,9 +1203,10 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
         }
     } else if (q.segs || q.last_scale != 1.f) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: terms to choose from or to scale need several operand pairs");
     // Results of at most 128 rows (P V: the head dimension) take tiles of 128 x 256: a tile of 256 x 256 copies and multiplies as many rows that do not exist.  32 heads of 128 x 2048
-    // from pairs of probabilities, three terms with a causal limit: 162 -> 155 us (reading the probabilities then binds); a whole forward pass of 4 x 512 tokens 2 - 4 % less.
+    // from pairs of probabilities, three terms with a causal limit: 162 -> 155 us (reading the probabilities then binds); small
+    // forward passes 2 - 4 % less.  Only where one round of workgroups takes all tiles: with 64 heads the resident workgroups, which fetch across tiles, take 236 us and these 288.
     const int segs_all = q.nterms > 1 ? q.nterms : q.kseg > 0 ? q.K / q.kseg : 1;
-    if (fast && (q.flags & TBOA_GEMM_PERSISTENT) && q.M <= GRAM_ROWS && q.N >= GRAM_COLS && segs_all <= 4 && !q.accumulate && !q.col_scale && !q.residual && !q.gate_up && (q.nterms <= 1 || q.kseg == 0 || q.kseg * q.nterms == q.K) &&
+    if (fast && (q.flags & TBOA_GEMM_PERSISTENT) && q.M <= GRAM_ROWS && q.N >= GRAM_COLS && cdiv64(q.N, GRAM_COLS) * q.batch <= 256 && segs_all <= 4 && !q.accumulate && !q.col_scale && !q.residual && !q.gate_up && (q.nterms <= 1 || q.kseg == 0 || q.kseg * q.nterms == q.K) &&
         !(q.flags & (TBOA_GEMM_LOWER | TBOA_GEMM_KLO | TBOA_GEMM_C_TILED | TBOA_GEMM_I8))) {
         const long long seg = q.K / segs_all;
         a.kseg = (int)seg; a.K = q.K;
