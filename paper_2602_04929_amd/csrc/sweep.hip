@@ -76,7 +76,8 @@ __device__ __forceinline__ void walk(Walk& k, const Pieces& pc, int l, double uj
     walk_step<MODE, 12>(k, y, ujj, lo, hi);
 }
 
-// The same walk not divided by the row's step s, with the quotient w / s where that decides a code
+// The same walk not divided by the row's step s, with the quotient w / s where that decides a code.  Columns up to j are left alone by a condition and not
+// by zero pieces: an undefined or infinite column (which always comes here) touches later ones only
 template <int MODE>
 __device__ __forceinline__ void walk_dividing(Walk& k, const Pieces& pc, int l, double s, double lo, double hi) {
 #pragma unroll 1
@@ -84,9 +85,10 @@ __device__ __forceinline__ void walk_dividing(Walk& k, const Pieces& pc, int l, 
         const int from = (threadIdx.x & 48) + j;
         const double x = __shfl(k.w, from), y = MODE == 2 ? __shfl(k.v, from) : 0.0, wj = MODE == 2 ? __builtin_fma(y, pc.ud[j], x) : x;
         const double d = x - s * fmin(fmax(rint(wj / s), lo), hi);
-        if (MODE == 1) { k.a = __builtin_fma(wj, pc.p1[j][l], k.a); k.w = __builtin_fma(wj, pc.p0[j][l], k.w); }
-        if (MODE == 2) { k.b = __builtin_fma(wj, pc.p1[j][l], k.b); k.v = __builtin_fma(wj, pc.p0[j][l], k.v); }
-        k.w = __builtin_fma(d, pc.u0[j][l], k.w); k.a = __builtin_fma(d, pc.u1[j][l], k.a);
+        const bool later = l > j;
+        if (MODE == 1) { k.a = __builtin_fma(wj, pc.p1[j][l], k.a); k.w = later ? __builtin_fma(wj, pc.p0[j][l], k.w) : k.w; }
+        if (MODE == 2) { k.b = __builtin_fma(wj, pc.p1[j][l], k.b); k.v = later ? __builtin_fma(wj, pc.p0[j][l], k.v) : k.v; }
+        k.w = later ? __builtin_fma(d, pc.u0[j][l], k.w) : k.w; k.a = __builtin_fma(d, pc.u1[j][l], k.a);
     }
 }
 

@@ -1,5 +1,7 @@
 """The column sweep at the edges of its sub-panels (16 columns), tiles (16 rows) and groups (512 columns), with and without the deviation term, shared and
 per-head Hessians, grid groups narrower than, equal to and wider than a sub-panel; and columns that lie on the border between two codes."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -49,3 +51,31 @@ def test_columns_on_the_border_between_codes(lib):
     W = (step[:, None] * k).astype(np.float32)
     H = np.diag(rng.uniform(1, 4, n)).astype(np.float32)
     run(lib, W, H, None, None, 1, 3, rows, damp=0.0)
+
+
+@pytest.mark.parametrize("n,rows,dev,kw", [(40, 20, 0, {}), (40, 20, 1, {}), (1100, 8, 1, {}), (528, 6, 0, {}), (96, 6, 1, dict(group=32, adaptive_grid=False))])
+@pytest.mark.parametrize("where", ["first", "in a sub-panel", "end of a sub-panel", "last"])
+def test_an_undefined_weight_touches_later_columns_only(lib, n, rows, dev, kw, where):
+    """An undefined weight leaves the columns before it, and the other rows, as they are without it (the grids have one candidate each, whose range it
+    does not enter).  Asked for no loss, the call reports nothing."""
+    col = {"first": 0, "in a sub-panel": 23, "end of a sub-panel": 31, "last": n - 1}[where]
+    g = torch.Generator(device="cuda"); g.manual_seed(n + col)
+    X = torch.randn(2 * n, n, generator=g, device="cuda", dtype=torch.float64)
+    H = (X.T @ X).float()
+    R = (0.05 * X.T @ torch.randn(2 * n, n, generator=g, device="cuda", dtype=torch.float64)).float() if dev else None
+    W = 0.02 * torch.randn(rows, n, generator=g, device="cuda")
+    ctx = lib.Context()
+    ng = n // kw["group"] if kw else 1
+
+    def codes(bad):
+        w = W.clone(); w[2, col] = bad
+        d = ctx.layer_desc(w, H, 1, 4, rows, grid_points=100, max_shrink=0.01, cd_iters=0, **kw)
+        out = [torch.empty(rows, n, dtype=torch.uint8, device="cuda"), torch.empty(rows, ng, device="cuda"), torch.empty(rows, ng, device="cuda"), torch.empty(rows, n, device="cuda")]
+        p = lib.binding._ptr
+        ctx._check(lib.binding._lib.tboa_quantize_layer(ctx._h, C.byref(d), p(w), p(H), None, p(R), *[p(t) for t in out], None, None))
+        return out
+    got, want = codes(float("nan")), codes(0.0)
+    for a, b in zip((got[0], got[3]), (want[0], want[3])):
+        assert torch.equal(a[2, :col], b[2, :col])
+        assert torch.equal(a[[i for i in range(rows) if i != 2]], b[[i for i in range(rows) if i != 2]])
+    ctx.close()
