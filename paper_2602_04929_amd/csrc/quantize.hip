@@ -593,7 +593,7 @@ __global__ __launch_bounds__(256) void grid_weight_products_kernel(const int* __
 // cost[(row, k)] = sum_c delta_c (2 v_c (s G[c] - Gw[c]) + H_cc delta_c), delta = s qbar - w.  One wavefront per row and GRID_KC candidates: bound by reading G, 4 bytes an
 // entry, once; what belongs to the row and the columns is read once for them all (one candidate a wavefront read as much again from L2).
 // least[row] = 2^-40 sum_c H_cc w_c^2: a candidate that costs less meets the weights up to the rounding of 24-bit numbers, which their 31 bits do not resolve well
-// enough to tell costs apart (see grid_count_kernel).
+// enough to tell costs apart (grid_count_kernel sends those of such a row to exact costs).
 constexpr int GRID_KC = 8;
 __global__ __launch_bounds__(256) void grid_cost_kernel(const int* __restrict__ G, const signed char* __restrict__ Acat, int rows, GridRows m, GridInt g,
                                                         const double* __restrict__ cand_s, const double* __restrict__ Wk, long long ldw, int n, const double* __restrict__ Gw,
@@ -643,13 +643,16 @@ __global__ __launch_bounds__(256) void grid_cost_kernel(const int* __restrict__ 
 // its end: [0] set when a pass could not be trusted as it stands (non-finite approximate cost, more near-minimal
 // candidates in a group of rows than the exact re-evaluation has room for), [1] near-minimal candidates evaluated exactly,
 // [2] the largest |approximate - exact| / |exact| seen, as the bits of a non-negative float, [3] set when a matrix of the call has the shorter
-// form of T (one half term, two digits).
-enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_WORDS = 4 };
+// form of T (one half term, two digits), [4] rows of which some candidate costs less than approximate costs resolve.
+enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_LOW = 4, GS_WORDS = 5 };
 
 // per row (one wavefront): the candidates whose approximate cost makes them survivors (in increasing k, list[row][0 ..]), and the number that
 // the exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
 // exact cost is what the deviation guard of the pass measures.
-__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, const double* __restrict__ least, int* __restrict__ list,
+// least (integer form; null: none): where the minimum lies below it (a row that one candidate meets, a constant row, a row of one weight) approximate costs
+// do not tell which candidate it is: every candidate up to twice least[row] survives, all are evaluated, and the row stays out of the guard's
+// deviation (least[row] becomes -1 for grid_argmin_sel_kernel).  From there on costs are resolved, so nothing cheaper lies beyond twice least[row].
+__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, double* __restrict__ least, int* __restrict__ list,
                                   int* __restrict__ cnt_out, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
@@ -658,7 +661,9 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restric
     for (int k = lane; k < ncand; k += 64) { const double v = c[k]; m = fmin(m, v); bad |= !(v == v); }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { m = fmin(m, __shfl_xor(m, o, 64)); bad |= __shfl_xor(bad, o, 64); }
-    const double lim = m + tau * fabs(m);
+    const double lowest = least ? least[row] : 0.0;
+    const bool low = least && m < lowest && 2.0 * lowest < INFINITY;
+    const double lim = low ? fmax(m + tau * fabs(m), 2.0 * lowest) : m + tau * fabs(m);
     int cnt = 0;
     for (int k0 = 0; k0 < ncand; k0 += 64) {
         const int k = k0 + lane;
@@ -669,8 +674,9 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restric
     }
     if (lane != 0) return;
     if (cnt == 0) out[0] = 0;
-    if (bad || cnt == 0 || (least && m < least[row])) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
-    const int ev = (cnt > 1 || row % 8 == 0) ? cnt : 0;
+    if (bad || cnt == 0 || (least && m < lowest && !low)) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
+    if (low) { least[row] = -1.0; atomicAdd(gstat + GS_LOW, 1); }
+    const int ev = (cnt > 1 || low || row % 8 == 0) ? cnt : 0;
     cnt_out[row] = ev;
     if (ev) atomicAdd(gstat + GS_SURVIVORS, ev);
 }
@@ -734,12 +740,12 @@ __global__ __launch_bounds__(256) void rowdot_limited_kernel(const double* __res
 
 // lowest exact cost among the survivors of a row (lowest k among equals); a row whose survivors were not evaluated takes its
 // first one (it has a single one, or the pass is void anyway).  Every exact re-evaluation is compared with its approximation for
-// the guard.  One wavefront per row, one survivor per lane.
+// the guard (rows with least[row] < 0 aside).  One wavefront per row, one survivor per lane.
 __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __restrict__ costS, const double* __restrict__ cost, const int* __restrict__ list,
                                        const int* __restrict__ cnt, const int* __restrict__ off, int per, int cap,
                                        const double* __restrict__ cand_s, const double* __restrict__ cand_z, int rows, int ncand,
                                        BlockMap m, int r_off, double* __restrict__ s_out, double* __restrict__ z_out, int ng, int gi,
-                                       int* __restrict__ gstat) {
+                                       const double* __restrict__ least, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const double* cr = cost + (long long)row * ncand; const int* l = list + (long long)row * ncand;
@@ -756,7 +762,7 @@ __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __re
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dev = fmax(dev, __shfl_xor(dev, o, 64));
     if (lane != 0) return;
-    if (nc > 0) atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
+    if (nc > 0 && !(least && least[row] < 0.0)) atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
     if (best == 0x7fffffff) best = l[0];
     const long long lr = layer_row(m, r_off + row);
     s_out[lr * ng + gi] = cand_s[(long long)row * ncand + best];
@@ -1181,7 +1187,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             hipLaunchKernelGGL(rowdot_limited_kernel, dim3((unsigned)((srow + 3) / 4)), dim3(256), 0, ctx->stream, L.GS, L.DeltaS, n, cap,
                                srow, totv, L.costS);
             hipLaunchKernelGGL(grid_argmin_sel_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.costS, L.cost, L.list, cntv, offv, per, cap,
-                               L.cand_s, L.cand_z, rows, ncand, map, r0, L.s64, L.z64, L.ng, gi, L.gstat);
+                               L.cand_s, L.cand_z, rows, ncand, map, r0, L.s64, L.z64, L.ng, gi, delta ? nullptr : L.gleast, L.gstat);
             TB_KERNEL_CHECK(ctx);
             ++ctx->counters[TBOA_CTR_GRID_PASSES];
             continue;
@@ -1568,7 +1574,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         float dev; memcpy(&dev, &gs[GS_MAXDEV], sizeof(float));
         ctx->counters[TBOA_CTR_GRID_SURVIVORS] += gs[GS_SURVIVORS];
         const double guard = d->grid_guard > 0.0 ? d->grid_guard : 0.25;
-        if (gs[GS_TRIPPED]) { free(host); return RUN_AGAIN_EXACT; }
+        // (the guard measures one row in eight at least: where more than that are out of its reach, the approximation is not relied on)
+        if (gs[GS_TRIPPED] || 8LL * gs[GS_LOW] > d->d_out) { free(host); return RUN_AGAIN_EXACT; }
         // a cost that its approximation misses by as much as itself (weights that lie on the candidate's grid but for the last bits) is no
         // matter of the bits of H; nor is, with integers, one that it misses by a thousand times what two digits leave out
         const bool delta = grid_delta(d->bits, n);

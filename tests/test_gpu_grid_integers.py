@@ -44,3 +44,22 @@ def test_few_rows_a_step(lib, block):
     for k in ("codes", "scales", "zeros", "W_deq"):
         assert torch.equal(fast[k], exact[k]), k
     ctx.close()
+
+
+@pytest.mark.parametrize("bits,n", [(2, 320), (3, 768)])
+def test_rows_that_lie_on_a_candidate_s_grid(lib, bits, n):
+    """A row on a grid, a constant row and a row of a single weight, sampled by the guard (every eighth row) and not, among ordinary rows: the least cost of such a row is
+    rounding, which its approximation does not resolve.  Its candidates get exact costs; the layer is not run again."""
+    W, H = layer(n, 64, n, "independent")
+    q = torch.randint(0, 2 ** bits, (2, n), device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)); q[:, 0] = 0; q[:, 1] = 2 ** bits - 1
+    W[[8, 13]] = (q - 1).float() * 0.0123
+    W[16] = 0.0457
+    W[24] = 0; W[24, n // 2] = -0.031
+    W[37] = 0; W[37, 5] = 0.77
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, None, None, 1, bits, 64)
+    assert ctx.counter(0) == 1 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    exact = ctx.quantize_layer(W, H, None, None, 1, bits, 64, grid_guard=-1.0)
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(fast[k], exact[k]), k
+    ctx.close()
