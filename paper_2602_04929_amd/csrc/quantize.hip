@@ -256,9 +256,10 @@ __global__ __launch_bounds__(256) void grid_group_kernel(const double* __restric
 // survivors is repeated: with the longer form of T if a matrix had the shorter one, else with exact costs for every candidate (counted by tboa_counter).
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
-// survivors: approximate cost <= (1 + tau) * approximate minimum.  The integer form is closer (largest deviations seen 1e-7 - 5e-7 on uncorrelated channels, 5e-5 on
-// channels correlated by common factors, where half terms had 2e-6 and 1.2e-4), and its margin is half as wide: fewer exact costs.
-constexpr double GRID_TAU = 2e-3, GRID_TAU_INT = 1e-3;
+// survivors: approximate cost <= (1 + tau) * approximate minimum.  Half of that with integers where the expected error E of a cost is 5000 times below what the default
+// guard lets pass in half a margin (2.5e-4): uncorrelated channels over many tokens, where the largest deviations seen are 8e-8, and fewer candidates need exact costs (70B-shaped W_O:
+// the call 168.5 -> 165 ms).  A caller's guard above the default keeps the whole margin.
+constexpr double GRID_TAU = 2e-3, GRID_TAU_NARROW = 1e-3, GRID_NARROW_ERROR = 5e-8;
 constexpr double GRID_TWO_DIGITS = 6e-7;      // expected relative error of a cost up to which two digits of T do
 // the left operand is delta as a pair of halves, else the integer codes: 3 levels of qbar over any width, 7 over 2048 columns.  The step of T grows with maxq times
 // the width; beyond that the pairs are closer on correlated channels (4 bits, 8192 columns: 1.5e-6 - 5.8e-6 against 2e-5 expected of integers)
@@ -359,8 +360,8 @@ __global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restric
 }
 
 // Integer form of T.  Per row r and matrix, [n_hin][np]: v = step of the row, hd = H_rr (both 0 beyond n); v2, v3: the steps with two and three digits, e2: the row's part
-// of E with two; terms: digits taken.
-struct GridInt { double *v, *hd, *v2, *v3, *e2; int* terms; };
+// of E with two; terms: digits taken; tau: margin of the survivors.
+struct GridInt { double *v, *hd, *v2, *v3, *e2, *tau; int* terms; };
 constexpr double GRID_DIGITS2 = 32600.0, GRID_DIGITS3 = 8.3e6;      // largest magnitudes of two and three digits in [-128, 127]
 
 __global__ __launch_bounds__(256) void grid_int_steps_kernel(const double* __restrict__ H, int n, int np, double maxq, GridInt g) {
@@ -386,20 +387,25 @@ __global__ __launch_bounds__(256) void grid_int_steps_kernel(const double* __res
     g.hd[o + r] = r < n ? h[r] : 0.0;
 }
 
-__global__ __launch_bounds__(256) void grid_int_terms_kernel(int n, int np, GridInt g, int longer, int* __restrict__ gstat) {
-    __shared__ double red[2][256];
+__global__ __launch_bounds__(256) void grid_int_terms_kernel(int n, int np, GridInt g, int longer, int whole_margin, int* __restrict__ gstat) {
+    __shared__ double red[3][256];
     const long long o = (long long)blockIdx.x * np;
-    double tr = 0.0, e = 0.0;
-    for (int c = threadIdx.x; c < n; c += 256) { tr += g.hd[o + c]; e += g.e2[o + c]; }
-    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = e;
+    double tr = 0.0, e = 0.0, e3 = 0.0;
+    for (int c = threadIdx.x; c < n; c += 256) { tr += g.hd[o + c]; e += g.e2[o + c]; e3 += (double)c * g.v3[o + c] * g.v3[o + c]; }
+    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = e; red[2][threadIdx.x] = e3;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) { red[0][threadIdx.x] += red[0][threadIdx.x + w]; red[1][threadIdx.x] += red[1][threadIdx.x + w]; }
+        if ((int)threadIdx.x < w)
+            for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
         __syncthreads();
     }
-    const double lim = GRID_TWO_DIGITS * red[0][0];
-    const int terms = (!longer && red[1][0] / 3.0 <= lim * lim) ? 2 : 3;      // E = 2 sqrt(e / 12) / tr
-    if (threadIdx.x == 0) { g.terms[blockIdx.x] = terms; if (terms == 2) atomicOr(gstat, 1); }
+    auto within = [&](double ee, double lim) { lim *= red[0][0]; return ee / 3.0 <= lim * lim; };      // E = 2 sqrt(e / 12) / tr
+    const int terms = (!longer && within(red[1][0], GRID_TWO_DIGITS)) ? 2 : 3;
+    if (threadIdx.x == 0) {
+        g.terms[blockIdx.x] = terms;
+        g.tau[blockIdx.x] = !whole_margin && within(red[terms == 2 ? 1 : 2][0], GRID_NARROW_ERROR) ? GRID_TAU_NARROW : GRID_TAU;
+        if (terms == 2) atomicOr(gstat, 1);
+    }
     for (int c = threadIdx.x; c < np; c += 256) g.v[o + c] = c < n ? (terms == 2 ? g.v2[o + c] : g.v3[o + c]) : 0.0;
 }
 
@@ -649,10 +655,11 @@ enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_LOW = 4
 // per row (one wavefront): the candidates whose approximate cost makes them survivors (in increasing k, list[row][0 ..]), and the number that
 // the exact pass evaluates.  A row with a single survivor needs none (that candidate wins), except every eighth row, whose
 // exact cost is what the deviation guard of the pass measures.
+// taus (integer form; null: GRID_TAU): the margin of each group of `per` rows.
 // least (integer form; null: none): where the minimum lies below it (a row that one candidate meets, a constant row, a row of one weight) approximate costs
 // do not tell which candidate it is: every candidate up to twice least[row] survives, all are evaluated, and the row stays out of the guard's
 // deviation (least[row] becomes -1 for grid_argmin_sel_kernel).  From there on costs are resolved, so nothing cheaper lies beyond twice least[row].
-__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, double tau, double* __restrict__ least, int* __restrict__ list,
+__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, const double* __restrict__ taus, int per, double* __restrict__ least, int* __restrict__ list,
                                   int* __restrict__ cnt_out, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
@@ -661,6 +668,7 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restric
     for (int k = lane; k < ncand; k += 64) { const double v = c[k]; m = fmin(m, v); bad |= !(v == v); }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { m = fmin(m, __shfl_xor(m, o, 64)); bad |= __shfl_xor(bad, o, 64); }
+    const double tau = taus ? taus[row / per] : GRID_TAU;
     const double lowest = least ? least[row] : 0.0;
     const bool low = least && m < lowest && 2.0 * lowest < INFINITY;
     const double lim = low ? fmax(m + tau * fabs(m), 2.0 * lowest) : m + tau * fabs(m);
@@ -1172,7 +1180,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             const int per = ph ? rows_per_head : rows, ngrp = rows / per;    // rows that share one H_in
             const int cap = per * GRID_KS;                                    // exact re-evaluations a group has room for
             int* cntv = L.sel; int* offv = cntv + rows; int* totv = offv + rows;
-            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, delta ? GRID_TAU : GRID_TAU_INT, delta ? nullptr : L.gleast, L.list, cntv, L.gstat);
+            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, delta ? nullptr : L.gint.tau + (ph ? u0 : 0), per, delta ? nullptr : L.gleast, L.list, cntv, L.gstat);
             hipLaunchKernelGGL(grid_scan_kernel, dim3(ngrp), dim3(256), 0, ctx->stream, cntv, per, cap, offv, totv, L.gstat);
             hipLaunchKernelGGL(grid_delta_sel_kernel, dim3((n + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
                                L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
@@ -1277,7 +1285,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, grid_one_term(d->bits), L.gstat + GS_SHORT);
         } else {
             hipLaunchKernelGGL(grid_int_steps_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.maxq, L.gint);
-            hipLaunchKernelGGL(grid_int_terms_kernel, dim3(nhin), dim3(256), 0, st, n, np, L.gint, L.grid_terms >= 2, L.gstat + GS_SHORT);
+            hipLaunchKernelGGL(grid_int_terms_kernel, dim3(nhin), dim3(256), 0, st, n, np, L.gint, L.grid_terms >= 2, d->grid_guard > 0.25, L.gstat + GS_SHORT);
             hipLaunchKernelGGL(grid_int_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, pitch, L.gint, (signed char*)L.Hcat, 2 * term);
         }
         TB_KERNEL_CHECK(ctx);
@@ -1579,7 +1587,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         // a cost that its approximation misses by as much as itself (weights that lie on the candidate's grid but for the last bits) is no
         // matter of the bits of H; nor is, with integers, one that it misses by a thousand times what two digits leave out
         const bool delta = grid_delta(d->bits, n);
-        if (dev > (delta ? guard * GRID_TAU : std::min(guard * GRID_TAU, 0.25 * GRID_TAU_INT))) {
+        if (dev > guard * GRID_TAU) {
             free(host);
             return gs[GS_SHORT] && dev < (delta ? 1.f : 1e-3f) ? RUN_AGAIN_TWO_TERMS : RUN_AGAIN_EXACT;
         }
@@ -1647,7 +1655,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
             L.wdown = ar.get<float>(grows);
         } else {
             L.gint.v = ar.get<double>(cols); L.gint.hd = ar.get<double>(cols); L.gint.v2 = ar.get<double>(cols); L.gint.v3 = ar.get<double>(cols);
-            L.gint.e2 = ar.get<double>(cols); L.gint.terms = ar.get<int>(L.nhin);
+            L.gint.e2 = ar.get<double>(cols); L.gint.tau = ar.get<double>(L.nhin); L.gint.terms = ar.get<int>(L.nhin);
             const size_t w_rows = mats * rows16(GRID_WD * (long long)mat_rows);
             L.gwt.A = (signed char*)ar.get<__half>(w_rows * grid_pitch((int)np, delta)); L.gwt.wu = ar.get<double>(grows);
             L.gwp = ar.get<int>(3 * w_rows * np); L.gwv = ar.get<double>(grows * np); L.gleast = ar.get<double>(grows);

@@ -63,3 +63,20 @@ def test_rows_that_lie_on_a_candidate_s_grid(lib, bits, n):
     for k in ("codes", "scales", "zeros", "W_deq"):
         assert torch.equal(fast[k], exact[k]), k
     ctx.close()
+
+
+@pytest.mark.parametrize("guard,again", [(0.0, 0), (0.25, 0), (0.5, 0), (0.125, 1)])
+def test_the_guard_is_the_caller_s(lib, guard, again):
+    """One direction holds nearly all of the variance and little damping hides it: the largest deviation of this layer's approximate costs lies between 2.5e-4 and
+    5e-4, which a guard of 0.25 (the default) or more lets pass and one of 0.125 does not.  The results are those of exact costs."""
+    g = torch.Generator(device="cuda"); g.manual_seed(1)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda", dtype=torch.float64)
+    x = 1.0 + 1e-2 * rnd(1024, 512)
+    W, H = (rnd(64, 512) * 0.02).float(), (x.T @ x).float()
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, None, None, 1, 2, 64, damp=1e-6, grid_guard=guard)
+    assert ctx.counter(0) > 0 and ctx.counter(1) + ctx.counter(6) == again
+    exact = ctx.quantize_layer(W, H, None, None, 1, 2, 64, damp=1e-6, grid_guard=-1.0)
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(fast[k], exact[k]), k
+    ctx.close()
