@@ -841,8 +841,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 
 // ------------------------------------------------------------------------------------------------
 // Gram products over long contractions: C = scale * sum over the operand pairs of A B^T as ONE fp32 matrix.  After every `flush` stages what the accumulators
-// hold is added to running sums without loss: t = s + a, and what t has rounded away goes back into the accumulators, where the next stages are added to
-// it.  So a sum rounds as those of 32 `flush` terms do.  That took 16 partial sums in memory before (n x n each, 7.8 GB at n = 11008) and a pass that added
+// hold is added to running sums: t = s + a, and r = a - (t - s), what t has rounded away, goes back into the accumulators, where the next stages are added to
+// it.  r is exact where |s| >= |a|; where a chunk exceeds the running sum, which sums without a common sign do now and then, t - s may round once, and up to 2^-24 |a| is
+// lost: one rounding of the chunk beside those of its own 32 `flush` terms.  (The two-sum of six operations loses nothing; the vector units bind while a fold
+// lasts, and H and R of 11008 columns take 5.14 instead of 4.92 ms with it, for an R that is off by 5.36e-8 instead of 5.48e-8 at 8192 x 4096.)
+// So a sum rounds as those of 32 `flush` terms do.  That took 16 partial sums in memory before (n x n each, 7.8 GB at n = 11008) and a pass that added
 // them in fp64, a third of the time.  The pipeline is that of gemm_bf16_nt_fast_kernel; the running sums take as many registers as the accumulators, so that a
 // wavefront has 64 x 64 results instead of 128 x 64.  LDS then binds (eight wavefronts read 32 KB and write 12 KB per 256 cycles of MFMAs): 1.0 PFLOP/s at
 // 11008 x 11008 x 16384, H and R of 8192 tokens 8.9 -> 4.9 ms.  (96 x 64 per wavefront does not fit the registers: 35 spilled, 14.8 ms; 256 x 128 per
