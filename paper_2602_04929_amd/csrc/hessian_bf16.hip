@@ -865,6 +865,13 @@ bool one_pass_gram(int n, int splits, int npairs, int Kc, int lower, int blocked
     return one < split;
 }
 
+// partial sums in memory (fp32 elements) that gram_splitk needs for H (npairs_h operand pairs) and, npairs_r > 0, R over K contraction indices
+size_t gram_part_elems(int n, int splits, long long K, int npairs_h, int npairs_r, int blocked) {
+    const int Kc = (int)(K / splits);
+    const bool none = one_pass_gram(n, splits, npairs_h, Kc, 1, blocked) && (npairs_r == 0 || one_pass_gram(n, splits, npairs_r, Kc, 0, blocked));
+    return none ? 0 : (size_t)splits * n * n;
+}
+
 // out[n, n] = scale * sum over the operand pairs p of A_p B_p^T, with the contraction over all T tokens split into `splits`
 // chunks (an exact-to-16-bit (hi, lo) operand takes part as several pairs: hi.hi + lo.hi + hi.lo)
 struct GramPair { const bf16* A; const bf16* B; };
@@ -1045,6 +1052,7 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     const int nsg = rv ? 2 : 1, nsx = (grouped ? 2 : 1) * (rv ? 3 : 1), splits = pick_splits(D.S);
     const int Lp = padded_len(L);       // (the summed form has whole 256-tiles: Lp = L there)
     const long long Tp = padded_tokens(T, splits);
+    const int blocked_x = dm % 16 == 0;      // X^T and dX^T of the Gram products in 16 x 32 blocks
     const long long dd = (long long)dm * dm, hh = (long long)dh * dh, TP = Tp + PADE;
     // summed form: pitches of the transposed probabilities, of [B1_hi | B1_lo | B2^T_hi | B2^T_lo], of the chunk buffers
     const long long ldpt = (long long)rep * L + PADE, ldbc = (rv ? 4LL : 2LL) * L + PADE, ldg = (long long)G * L + PADE;
@@ -1062,7 +1070,7 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
         Arena ar(pass ? ctx->ws : nullptr);
         XT = ar.get<bf16>((size_t)dm * TP);
         dXh = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr; dXl = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr;
-        part = ar.get<float>((size_t)splits * dd);
+        part = ar.get<float>(Hin_qk ? gram_part_elems(dm, splits, Tp, 1, fp && R_qk ? 2 : 0, blocked_x) : 0);
         Qf = ar.get<float>((size_t)G * L * dq); Kf = ar.get<float>((size_t)G * L * dkv);
         Qh = ar.get<bf16>((size_t)G * L * dq * 3); Kh = ar.get<bf16>((size_t)G * L * dkv * 3);
         Qhf = rv ? ar.get<bf16>((size_t)G * L * dq * 3) : nullptr; Khf = rv ? ar.get<bf16>((size_t)G * L * dkv * 3) : nullptr;
@@ -1092,10 +1100,9 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     if (Hin_qk) {
     if (Tp != T)
         for (bf16* p : {XT, dXh, dXl}) if (p) TB_TRY(clear16(ctx, p, dm * TP));
-    const int blocked = dm % 16 == 0;
-    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, dm, T, dm, XT, fp ? dXh : nullptr, dXl, TP, blocked));
-    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk, blocked));
-    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk, blocked));
+    TB_TRY(transpose(D, X, fp ? X_fp : nullptr, dm, T, dm, XT, fp ? dXh : nullptr, dXl, TP, blocked_x));
+    TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk, blocked_x));
+    if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk, blocked_x));
     // ---- H_out: K_g^T K_g = W_K,g H_in W_K,g^T ; sum_h Q_h^T Q_h ; sum_h W_out,h^T W_out,h   (fp64)
     // (the wide product W_Q H_in, d_q x d x d, is taken with the triangular half of H_in; the d_h x d_h products of a group's heads
     // are one launch whose terms are summed in fp64: as one launch per head of the group they ran on n_kv_heads workgroups)
@@ -1387,7 +1394,7 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
         VTc = ar.get<bf16>((size_t)dkv * (G * nsg * Lp + PADE));
         OT = ar.get<bf16>((size_t)dq * TP); OTl = ar.get<bf16>((size_t)dq * TP);
         dOT = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr; dOTl = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr;
-        part = ar.get<float>((size_t)splits * dq * dq);
+        part = ar.get<float>(Hin_o ? gram_part_elems(dq, splits, Tp, 3, fp ? 3 : 0, 0) : 0);
         steps = ar.get<float>((size_t)dq + 2 * dkv);
         amx = ar.get<int>((size_t)4 * G);
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
@@ -1526,8 +1533,7 @@ int build_hessian_linear_bf16(tboa_ctx* ctx, long long T, int n, double alpha, c
         Arena ar(pass ? ctx->ws : nullptr);
         XT = ar.get<bf16>((size_t)n * TP);
         dXh = fp ? ar.get<bf16>((size_t)n * TP) : nullptr; dXl = fp ? ar.get<bf16>((size_t)n * TP) : nullptr;
-        const int Kc = (int)(Tp / splits);
-        part = one_pass_gram(n, splits, 1, Kc, 1, blocked) && (!fp || one_pass_gram(n, splits, 2, Kc, 0, blocked)) ? nullptr : ar.get<float>((size_t)splits * n * n);
+        part = ar.get<float>(gram_part_elems(n, splits, Tp, 1, fp ? 2 : 0, blocked));
         if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
     }
     Dims D{}; D.ctx = ctx;

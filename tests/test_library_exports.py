@@ -96,3 +96,12 @@ def test_workspace_queries_are_host_arithmetic():
         qk = C.quantize_workspace_bytes(desc(cfg.d_q + cfg.d_kv, cfg.d_model, cfg.n_q_heads + cfg.n_kv_heads, 0, cfg.block))
         assert 0 < o < 64 * 2 ** 30 and 0 < v < 64 * 2 ** 30 and 0 < qk < 64 * 2 ** 30, (name, o, v, qk)
     print("workspace: 7B Hessians %.1f GiB, 70B Hessians %.1f GiB, 7B W_Q %.1f GiB, 7B W_V %.1f GiB" % (big / 2 ** 30, gqa / 2 ** 30, a / 2 ** 30, b / 2 ** 30))
+
+
+def test_hessian_workspace_holds_no_partial_sums_that_are_not_written():
+    """16 sequences split the contraction of the Gram products 16 ways and 17 do not; at 8192 columns neither leaves partial sums in memory (16 would be 4.3 GB), so
+    the fewer sequences need no more workspace."""
+    import paper_2602_04929_amd as tb
+    import torch
+    fewer, more = (tb.Context.hessian_workspace_bytes(8192, 64, 8, 128, s, 2048, torch.bfloat16) for s in (16, 17))
+    assert 0 < fewer <= more
