@@ -840,7 +840,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// Gram products over long contractions: C = scale * sum over the operand pairs of A B^T as ONE fp32 matrix.  After every `flush` stages what the accumulators
+// Tiles of 128 x 256.  FOLD: Gram products over long contractions (gemm_gram).  Without: products with at most 128 result rows (narrow_product), as
+// gemm_bf16_nt_fast_kernel but for the height of the tile.
+// Gram products: C = scale * sum over the operand pairs of A B^T as ONE fp32 matrix.  After every `flush` stages what the accumulators
 // hold is added to running sums: t = s + a, and r = a - (t - s), what t has rounded away, goes back into the accumulators, where the next stages are added to
 // it.  r is exact where |s| >= |a|; where a chunk exceeds the running sum, which sums without a common sign do now and then, t - s may round once, and up to 2^-24 |a| is
 // lost: one rounding of the chunk beside those of its own 32 `flush` terms.  (The two-sum of six operations loses nothing; the vector units bind while a fold
@@ -851,7 +853,7 @@ __global__ __launch_bounds__(512) void gemm_bf16_nt_stream_kernel(Args g) {
 // 11008 x 11008 x 16384, H and R of 8192 tokens 8.9 -> 4.9 ms.  (96 x 64 per wavefront does not fit the registers: 35 spilled, 14.8 ms; 256 x 128 per
 // workgroup: 5.05.)
 template <int TI, int TJ, int WM, int WN, int NS, bool F16, bool FOLD>
-__global__ __launch_bounds__(512) void gemm_gram_kernel(Args g, int flush, double scale) {
+__global__ __launch_bounds__(512) void gemm_128x256_kernel(Args g, int flush, double scale) {
     constexpr int TM = 32 * TI * WM, TN = 32 * TJ * WN, BLKS = (TM + TN) / 16, LPW = (BLKS + 7) / 8, STAGE_BYTES = (TM + TN) * FK * 2;
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     int z, tm, tn;
@@ -1092,8 +1094,20 @@ int tile_schedule(tboa_ctx* ctx, const GemmBf16& q, int tiles_m, int tiles_n, co
 }  // namespace
 
 namespace {
-constexpr int GRAM_TI = 2, GRAM_TJ = 2, GRAM_WM = 2, GRAM_WN = 4, GRAM_NS = 4;      // 128 x 256 per workgroup
-constexpr int GRAM_ROWS = 32 * GRAM_TI * GRAM_WM, GRAM_COLS = 32 * GRAM_TJ * GRAM_WN;
+constexpr int T128_TI = 2, T128_TJ = 2, T128_WM = 2, T128_WN = 4, T128_NS = 4;      // 128 x 256 per workgroup
+constexpr int T128_ROWS = 32 * T128_TI * T128_WM, T128_COLS = 32 * T128_TJ * T128_WN;
+
+// Whether a product over `segs` operand pairs or segments takes tiles of 128 x 256: results of at most 128 rows (P V: the head dimension), where a tile of
+// 256 x 256 copies and multiplies as many rows that do not exist.  Only where one round of workgroups takes all tiles: beyond it the resident workgroups, which fetch
+// across tiles, are the faster ones (64 heads of 128 x 2048: 236 us and 288 here).  P V with pairs of probabilities and a causal limit, tiles of 256 x 256 and these:
+//     heads x rows x length   32 x 128 x 2048   40 x 128 x 1536   16 x 128 x 2048   12 x 128 x 1000   24 x 64 x 1000   32 x 64 x 1024   8 x 128 x 512   16 x 96 x 256
+//     us                        171 -> 162        134 -> 124        129 -> 118         80 -> 67          70 -> 67         64 -> 47         39 -> 30        31 -> 23
+bool narrow_product(const GemmBf16& q, int segs) {
+    if (!(q.flags & TBOA_GEMM_PERSISTENT) || q.M > T128_ROWS || q.N < T128_COLS || cdiv64(q.N, T128_COLS) * q.batch > 256) return false;
+    // what the kernel's operand walk does: up to four pairs, or one pair in up to four segments; and its epilogue: no accumulation, factors or blocked result
+    if (segs > 4 || (q.nterms > 1 && q.kseg > 0 && q.kseg * q.nterms != q.K)) return false;
+    return !q.accumulate && !q.col_scale && !q.residual && !q.gate_up && !(q.flags & (TBOA_GEMM_LOWER | TBOA_GEMM_KLO | TBOA_GEMM_C_TILED | TBOA_GEMM_I8));
+}
 }  // namespace
 
 int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
@@ -1205,29 +1219,25 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
             a.term_dB[t] = ((const char*)q.termB[t + 1] - (const char*)q.termB[t]) - bytesB;
         }
     } else if (q.segs || q.last_scale != 1.f) return tboa_fail(ctx, TBOA_EINVAL, "gemm_bf16: terms to choose from or to scale need several operand pairs");
-    // Results of at most 128 rows (P V: the head dimension) take tiles of 128 x 256: a tile of 256 x 256 copies and multiplies as many rows that do not exist.  32 heads of 128 x 2048
-    // from pairs of probabilities, three terms with a causal limit: 162 -> 155 us (reading the probabilities then binds); small
-    // forward passes 2 - 4 % less.  Only where one round of workgroups takes all tiles: with 64 heads the resident workgroups, which fetch across tiles, take 236 us and these 288.
     const int segs_all = q.nterms > 1 ? q.nterms : q.kseg > 0 ? q.K / q.kseg : 1;
-    if (fast && (q.flags & TBOA_GEMM_PERSISTENT) && q.M <= GRAM_ROWS && q.N >= GRAM_COLS && cdiv64(q.N, GRAM_COLS) * q.batch <= 256 && segs_all <= 4 && !q.accumulate && !q.col_scale && !q.residual && !q.gate_up && (q.nterms <= 1 || q.kseg == 0 || q.kseg * q.nterms == q.K) &&
-        !(q.flags & (TBOA_GEMM_LOWER | TBOA_GEMM_KLO | TBOA_GEMM_C_TILED | TBOA_GEMM_I8))) {
+    if (fast && narrow_product(q, segs_all)) {
         const long long seg = q.K / segs_all;
         a.kseg = (int)seg; a.K = q.K;
         for (int t = 0; t + 1 < segs_all; ++t) {
             a.term_dA[t] = q.nterms > 1 ? (const char*)q.termA[t + 1] - (const char*)q.termA[t] : (seg * 2) << ((q.flags & TBOA_GEMM_A_TILED) ? 4 : 0);
             a.term_dB[t] = q.nterms > 1 ? (const char*)q.termB[t + 1] - (const char*)q.termB[t] : (seg * 2) << ((q.flags & TBOA_GEMM_B_TILED) ? 4 : 0);
         }
-        TB_TRY(tile_order(ctx, 1, (int)cdiv64(q.N, GRAM_COLS), q.flags & TBOA_GEMM_CAUSAL_K, &a.tile_order, &a.ntiles, GRAM_ROWS, GRAM_COLS));
+        TB_TRY(tile_order(ctx, 1, (int)cdiv64(q.N, T128_COLS), q.flags & TBOA_GEMM_CAUSAL_K, &a.tile_order, &a.ntiles, T128_ROWS, T128_COLS));
         a.nitems = (long long)a.ntiles * q.batch; a.chunk = q.batch >= 8 ? 32 : 0;
         a.per = a.chunk ? ((a.nitems + a.chunk - 1) / a.chunk + 7) / 8 * a.chunk : (a.nitems + 7) / 8;
-        constexpr int smem_narrow = GRAM_NS * (GRAM_ROWS + GRAM_COLS) * FK * 2;
+        constexpr int smem_narrow = T128_NS * (T128_ROWS + T128_COLS) * FK * 2;
         const dim3 wgs((unsigned)(8 * a.per));
         if (f16) {
-            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
-            hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, true, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
+            hipLaunchKernelGGL((gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, true, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
         } else {
-            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
-            hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, false, false>, hipFuncAttributeMaxDynamicSharedMemorySize, smem_narrow));
+            hipLaunchKernelGGL((gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, false, false>), wgs, dim3(512), smem_narrow, ctx->stream, a, 0, 1.0);
         }
         TB_KERNEL_CHECK(ctx);
         return prof_end(ctx, rec, timed);
@@ -1249,12 +1259,11 @@ int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& q) {
     return 0;
 }
 
-
 long long gemm_gram_tiles(int M, int N, int lower) {
-    const long long tm = cdiv64(M, GRAM_ROWS), tn = cdiv64(N, GRAM_COLS);
+    const long long tm = cdiv64(M, T128_ROWS), tn = cdiv64(N, T128_COLS);
     if (!lower) return tm * tn;
     long long t = 0;
-    for (long long i = 0; i < tm; ++i) t += std::min<long long>(tn, cdiv64((i + 1) * GRAM_ROWS, GRAM_COLS));
+    for (long long i = 0; i < tm; ++i) t += std::min<long long>(tn, cdiv64((i + 1) * T128_ROWS, T128_COLS));
     return t;
 }
 
@@ -1262,7 +1271,7 @@ int gemm_gram(tboa_ctx* ctx, const GemmBf16& q, double scale, int chunk) {
     if (q.M <= 0 || q.N <= 0) return 0;
     const bool tiled = (q.flags & TBOA_GEMM_A_TILED) != 0;
     const int term = q.nterms > 0 ? q.K / q.nterms : 0;
-    if (!q.A || !q.B || !q.C || q.batch != 1 || q.c_dtype != TBOA_F32 || q.accumulate || q.nterms < 1 || q.nterms > 4 || chunk < FK * GRAM_NS || chunk % (FK * GRAM_NS) || q.K % q.nterms || term % FK || term <= 0 ||
+    if (!q.A || !q.B || !q.C || q.batch != 1 || q.c_dtype != TBOA_F32 || q.accumulate || q.nterms < 1 || q.nterms > 4 || chunk < FK * T128_NS || chunk % (FK * T128_NS) || q.K % q.nterms || term % FK || term <= 0 ||
         (q.flags & ~(TBOA_GEMM_LOWER | TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) || tiled != ((q.flags & TBOA_GEMM_B_TILED) != 0) ||
         q.lda % (tiled ? 32 : 8) || q.ldb % (tiled ? 32 : 8) || (tiled && (q.M % 16 || q.N % 16)) || ((q.flags & TBOA_GEMM_LOWER) && q.M != q.N))
         return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: unsupported product");
@@ -1275,20 +1284,20 @@ int gemm_gram(tboa_ctx* ctx, const GemmBf16& q, double scale, int chunk) {
         if (!A || !B || ((uintptr_t)A & 15) || ((uintptr_t)B & 15) || (t == 0 && (A != q.A || B != q.B))) return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: operand pair %d", t);
         if (t + 1 < q.nterms) { a.term_dA[t] = (const char*)q.termA[t + 1] - (const char*)A; a.term_dB[t] = (const char*)q.termB[t + 1] - (const char*)B; }
     }
-    const int tiles_m = (int)cdiv64(q.M, GRAM_ROWS), tiles_n = (int)cdiv64(q.N, GRAM_COLS);
+    const int tiles_m = (int)cdiv64(q.M, T128_ROWS), tiles_n = (int)cdiv64(q.N, T128_COLS);
     if (tiles_m > 32767 || tiles_n > 32767) return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: more than 32767 tiles along one axis");
-    TB_TRY(tile_order(ctx, tiles_m, tiles_n, q.flags & TBOA_GEMM_LOWER, &a.tile_order, &a.ntiles, GRAM_ROWS, GRAM_COLS));
+    TB_TRY(tile_order(ctx, tiles_m, tiles_n, q.flags & TBOA_GEMM_LOWER, &a.tile_order, &a.ntiles, T128_ROWS, T128_COLS));
     a.nitems = a.ntiles; a.per = (a.nitems + 7) / 8;
-    constexpr int smem = GRAM_NS * (GRAM_ROWS + GRAM_COLS) * FK * 2;
+    constexpr int smem = T128_NS * (T128_ROWS + T128_COLS) * FK * 2;
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on && q.tag >= 0) TB_TRY(prof_begin(ctx, q.tag, ((q.flags & TBOA_GEMM_LOWER) ? (double)q.M * (q.M + 1.0) : 2.0 * q.M * q.N) * q.K, rec, timed));
-    const void* kern = (q.flags & TBOA_GEMM_F16) ? (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, true>
-                                                 : (const void*)gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, true>;
+    const void* kern = (q.flags & TBOA_GEMM_F16) ? (const void*)gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, true, true>
+                                                 : (const void*)gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, false, true>;
     TB_HIP(ctx, hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
     if (q.flags & TBOA_GEMM_F16)
-        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, true, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+        hipLaunchKernelGGL((gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, true, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
     else
-        hipLaunchKernelGGL((gemm_gram_kernel<GRAM_TI, GRAM_TJ, GRAM_WM, GRAM_WN, GRAM_NS, false, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
+        hipLaunchKernelGGL((gemm_128x256_kernel<T128_TI, T128_TJ, T128_WM, T128_WN, T128_NS, false, true>), dim3((unsigned)(8 * a.per)), dim3(512), smem, ctx->stream, a, chunk / FK, scale);
     TB_KERNEL_CHECK(ctx);
     return prof_end(ctx, rec, timed);
 }

@@ -148,7 +148,7 @@ struct GemmBf16 {
 // 32-bit integers.  Several terms are digits of B to the base 256, the highest first: C = sum_t 256^(terms - 1 - t) A termB[t]^T, modulo 2^32.
 #define TBOA_GEMM_I8 0x40000
 int gemm_bf16_nt(tboa_ctx* ctx, const GemmBf16& g);
-// C = scale * sum_t termA[t] termB[t]^T as one fp32 matrix whose sums round as those of `chunk` (a multiple of 128) contraction indices do (gemm_gram_kernel); nterms pairs of K / nterms
+// C = scale * sum_t termA[t] termB[t]^T as one fp32 matrix whose sums round as those of `chunk` (a multiple of 128) contraction indices do (gemm_128x256_kernel); nterms pairs of K / nterms
 // columns each, K / nterms a multiple of 32, no batch, C fp32; flags: LOWER (only the tiles on or below the diagonal are written), F16, A_TILED and B_TILED together.
 // gemm_gram_tiles: how many workgroups such a launch has.
 int gemm_gram(tboa_ctx* ctx, const GemmBf16& g, double scale, int chunk);

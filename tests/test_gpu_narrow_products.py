@@ -27,3 +27,48 @@ def test_against_64_bits(lib, batch, M, N, K, causal, half):
     got16 = ctx.gemm_bf16_nt(A.view(torch.bfloat16), B.view(torch.bfloat16), out_dtype=torch.bfloat16, flags=flags).view(dt)
     assert bool(((got16.double() - want).abs() <= (K + 2) * 2.0 ** -24 * size + (2.0 ** -11 if half else 2.0 ** -8) * want.abs() + 2.0 ** -24).all())
     ctx.close()
+
+
+def attention(X, Wq, Wk, Wv, hq, hkv, dh, cut=lambda name, t: t):
+    """Concatenated attention outputs [S L, hq dh] in 64 bits; cut("v" or "a", t): what is done to values and probabilities."""
+    S, L, d = X.shape
+    mask = torch.ones(L, L, dtype=torch.bool, device=X.device).triu(1)
+    out = torch.empty(S, L, hq * dh, dtype=torch.float64, device=X.device)
+    for s in range(S):
+        for h in range(hq):
+            g = h * hkv // hq
+            q, k, v = X[s] @ Wq[h * dh:(h + 1) * dh].T, X[s] @ Wk[g * dh:(g + 1) * dh].T, X[s] @ Wv[g * dh:(g + 1) * dh].T
+            a = torch.softmax((q @ k.T / dh ** 0.5).masked_fill(mask, float("-inf")), 1)
+            out[s, :, h * dh:(h + 1) * dh] = cut("a", a) @ cut("v", v)
+    return out.reshape(S * L, hq * dh)
+
+
+@pytest.mark.parametrize("L,hq,hkv,dh", [(256, 4, 2, 64), (512, 3, 1, 128), (256, 2, 1, 96), (264, 2, 1, 128), (288, 2, 2, 104), (328, 4, 4, 64)])
+def test_values_times_probabilities_by_segments(lib, L, hq, hkv, dh):
+    """The form in which attention outputs are taken: three segments or pairs of (hi, lo) operands with a causal limit each, a two-level batch, a (hi, lo) result; from the
+    fused probabilities (whole 256s) and from stored ones.  Values have a common part and probabilities are nearly equal, so that what a missing or a
+    wrong segment leaves out (2^-12 of an operand) does not average out: the oracle without the low part of either operand fails the bound."""
+    S, d = 2, 64
+    g = torch.Generator(device="cuda"); g.manual_seed(L + dh)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    xf = r(S, L, d); xf[..., 0] = 1.0
+    X, Xf = (xf + 0.02 * r(S, L, d)).bfloat16(), xf.bfloat16()
+    X[..., 0] = 1.0
+    W = [0.002 * r(hq * dh, d), 0.002 * r(hkv * dh, d), 0.002 * r(hkv * dh, d)]
+    W[2][:, 0] = 0.3 + 0.7 * torch.rand(hkv * dh, generator=g, device="cuda")
+    Wb = [w.bfloat16() for w in W]
+    ctx = lib.Context()
+    H, R = ctx.build_hessian_out_proj(X, Xf, *W, *Wb, hq, hkv, dh, alpha=0.25)
+    ctx.close()
+    W64, Wb64 = [w.double() for w in W], [w.double() for w in Wb]
+    O, Of = attention(X.double(), *W64, hq, hkv, dh), attention(Xf.double(), *Wb64, hq, hkv, dh)
+    size = O.norm(dim=0)[:, None] * O.norm(dim=0)[None, :]
+    # a query's probabilities are divided by their sum in fp32: L nearly equal numbers, each addition off by 2^-24 of the sum so far at most, together L / 2 of the whole
+    # sum's; twice that in H, that of either path in R; they do not all round the same way in every binade: a quarter of it
+    bound = L * 2.0 ** -26
+    assert float(((H.double() - O.T @ O).abs() / size).max()) <= bound
+    assert float(((R.double() - 0.25 * (O - Of).T @ O).abs() / size).max()) <= 0.25 * bound
+    for x, w, n in ((X, W64, "v"), (X, W64, "a"), (Xf, Wb64, "v")):
+        cut = attention(x.double(), *w, hq, hkv, dh, lambda m, t: t.half().double() if m == n else t)
+        wrong = cut.T @ cut - O.T @ O if x is X else (Of - cut).T @ O
+        assert float((wrong.abs() / size).max()) > bound
