@@ -238,10 +238,15 @@ __global__ __launch_bounds__(256) void grid_group_kernel(const double* __restric
 // and every row r of T is taken as integers times a step v_r, two or three digits to the base 256: the product runs on signed bytes at twice the rate of 16-bit
 // operands, its sums are exact, and v_r is large enough that maxq sum |T'_r| stays below 2^31.  G_w comes from the 31-bit integer form of the weight rows, one product
 // for every pair of digits, added in 64-bit integers.  So a cost is that of T' = v times the integers, the same T' for all candidates, and the one error is
-// the rounding of T: expected relative error E = 2 sqrt(sum_r r v_r^2 / 12) / tr H, which the device forms per matrix; two digits where E <= 6e-7, three
-// elsewhere (1e-9 - 8e-7, the latter on channels correlated by common factors).
-// (hi, lo) half terms of T with the codes as halves before: one term up to 1.4e-6, two 1e-7 - 3e-7 and, where G_k and G_w cancel in their fp32 sums, up to
-// 2.1e-5 (root mean square).  70B-shaped W_O (8192 x 8192, 80 candidates, three digits against two half terms): products 86 -> 63 ms.
+// the rounding of T: expected relative error E = 2 sqrt(sum_r r v_r^2 / 12) / tr H, which the device forms per matrix.  Two digits where E <= 6e-7 and |H off the
+// diagonal|_F is small enough for one half term (grid_one_term), three elsewhere (E 1e-9 - 8e-7, the latter on channels correlated by common factors).
+// T itself is coarser than as halves, a fixed step per row where those have 11 or 22 bits of every entry: median relative error of an entry (2048 columns, 4096 tokens)
+// 2.6e-6 with three digits against 2.2e-8 with two half terms, 6.5e-4 with two digits against 1.7e-4 with one.  The exact sums and the weights' 31 bits more than make up for it,
+// because half terms lost more where G_k and G_w cancel in their fp32 sums.  Largest deviations of a cost, half terms -> digits, widths 320 - 8192:
+//     independent channels   one term -> two digits 3e-6 -> 3e-7 - 1e-6,   two terms -> three digits 1e-7 - 5e-7 -> 5e-9 - 4e-8   (two digits there: 5e-7 - 1.3e-6)
+//     outlier channels 5e-7 - 2.5e-6 -> 8e-9 - 6e-8,   common factors 1.3e-6 - 2.3e-5 -> 5e-7 - 5e-6,   a rank-4 map of the channels 7e-6 - 1.2e-4 -> 3e-6 - 4e-5
+//     one direction with nearly all of the variance 9e-5 - 1.3e-3 -> 3e-5 - 5e-4 (equal on average at 4096 columns)
+// 70B-shaped W_O (8192 x 8192, 80 candidates, three digits against two half terms): products 86 -> 63 ms.
 //
 // Pairs of delta (fine grids): delta itself as a (hi, lo) pair of halves against one or two half terms of T with half of H's diagonal, the channels
 // equilibrated by powers of two: T'_rc = T_rc 2^(10 - e_r - e_c) with e_c half the exponent of H_cc, delta'_c = delta_c 2^(e_c - e_max), so that the entries of T' are at
@@ -252,19 +257,19 @@ __global__ __launch_bounds__(256) void grid_group_kernel(const double* __restric
 // thousand tokens): one term is taken where it is off by no more than that, which is where channels are uncorrelated and the tokens many
 // (grid_one_term), and two (22 bits) elsewhere: 1e-7 - 3e-7, on strongly correlated channels 1.5e-6 - 5.8e-6.  The device decides per matrix (grid_terms_kernel).
 //
-// As a guard, every exact re-evaluation is compared with its approximation, and a pass whose largest deviation exceeds a quarter of the margin of the
-// survivors is repeated: with the longer form of T if a matrix had the shorter one, else with exact costs for every candidate (counted by tboa_counter).
+// As a guard, every exact re-evaluation is compared with its approximation, and a call whose largest deviation exceeds grid_guard GRID_TAU (a quarter of it by
+// default) is repeated: with the longer form of T if a matrix had the shorter one, else with exact costs for every candidate (counted by tboa_counter).
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
 // survivors: approximate cost <= (1 + tau) * approximate minimum.  Half of that with integers where the expected error E of a cost is 5000 times below what the default
 // guard lets pass in half a margin (2.5e-4): uncorrelated channels over many tokens, where the largest deviations seen are 8e-8, and fewer candidates need exact costs (70B-shaped W_O:
 // the call 168.5 -> 165 ms).  A caller's guard above the default keeps the whole margin.
 constexpr double GRID_TAU = 2e-3, GRID_TAU_NARROW = 1e-3, GRID_NARROW_ERROR = 5e-8;
-constexpr double GRID_TWO_DIGITS = 6e-7;      // expected relative error of a cost up to which two digits of T do
+constexpr double GRID_TWO_DIGITS = 6e-7;      // expected relative error of a cost up to which two digits of T do, |H off the diagonal|_F permitting (grid_one_term)
 // the left operand is delta as a pair of halves, else the integer codes: 3 levels of qbar over any width, 7 over 2048 columns.  The step of T grows with maxq times
 // the width; beyond that the pairs are closer on correlated channels (4 bits, 8192 columns: 1.5e-6 - 5.8e-6 against 2e-5 expected of integers)
 constexpr bool grid_delta(int bits, int n) { return bits > 3 || (bits == 3 && n > 2048); }
-constexpr double grid_one_term(int bits) { return bits == 2 ? 0.005 : bits <= 4 ? 0.003 : 0.0; }      // one half term of T is enough for |H off the diagonal|_F up to this times tr H
+constexpr double grid_one_term(int bits) { return bits == 2 ? 0.005 : bits <= 4 ? 0.003 : 0.0; }      // one half term of T (or two digits) is enough for |H off the diagonal|_F up to this times tr H
 constexpr int GRID_SPREAD = 14;     // channels whose variance is below 2^-28 of the largest share an exponent (no subnormal half values)
 
 // columns of the operands: zeros beyond n (integers: whole output tiles, whose contraction then is whole turns of the LDS ring)
@@ -360,22 +365,22 @@ __global__ __launch_bounds__(256) void grid_terms_kernel(const double* __restric
 }
 
 // Integer form of T.  Per row r and matrix, [n_hin][np]: v = step of the row, hd = H_rr (both 0 beyond n); v2, v3: the steps with two and three digits, e2: the row's part
-// of E with two; terms: digits taken; tau: margin of the survivors.
-struct GridInt { double *v, *hd, *v2, *v3, *e2, *tau; int* terms; };
+// of E with two; off2: sum of the squares of row r left of the diagonal; terms: digits taken; tau: margin of the survivors.
+struct GridInt { double *v, *hd, *v2, *v3, *e2, *off2, *tau; int* terms; };
 constexpr double GRID_DIGITS2 = 32600.0, GRID_DIGITS3 = 8.3e6;      // largest magnitudes of two and three digits in [-128, 127]
 
 __global__ __launch_bounds__(256) void grid_int_steps_kernel(const double* __restrict__ H, int n, int np, double maxq, GridInt g) {
-    __shared__ double red[2][4];
+    __shared__ double red[3][4];
     const int r = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long o = (long long)blockIdx.y * np;
     const double* h = H + (long long)blockIdx.y * n * n + (long long)r * n;
-    double sum = 0.0, big = 0.0;
+    double sum = 0.0, big = 0.0, sq = 0.0;
     if (r < n)
-        for (int c = threadIdx.x; c < r; c += 256) { const double a = fabs(h[c]); sum += a; big = fmax(big, a); }
-    sum = wave_sum(sum);
+        for (int c = threadIdx.x; c < r; c += 256) { const double a = fabs(h[c]); sum += a; big = fmax(big, a); sq += a * a; }
+    sum = wave_sum(sum); sq = wave_sum(sq);
 #pragma unroll
     for (int w = 32; w > 0; w >>= 1) big = fmax(big, __shfl_xor(big, w, 64));
-    if (lane == 0) { red[0][wave] = sum; red[1][wave] = big; }
+    if (lane == 0) { red[0][wave] = sum; red[1][wave] = big; red[2][wave] = sq; }
     __syncthreads();
     if (threadIdx.x != 0) return;
     sum = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
@@ -384,23 +389,25 @@ __global__ __launch_bounds__(256) void grid_int_steps_kernel(const double* __res
     const double least = maxq * sum / (2147483000.0 - 0.5 * maxq * n), v2 = fmax(big / GRID_DIGITS2, least), v3 = fmax(big / GRID_DIGITS3, least);
     g.v2[o + r] = v2; g.v3[o + r] = sum == sum ? v3 : sum;      // (a sum that is undefined makes every cost undefined)
     g.e2[o + r] = (double)r * v2 * v2;
+    g.off2[o + r] = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
     g.hd[o + r] = r < n ? h[r] : 0.0;
 }
 
-__global__ __launch_bounds__(256) void grid_int_terms_kernel(int n, int np, GridInt g, int longer, int whole_margin, int* __restrict__ gstat) {
-    __shared__ double red[3][256];
+__global__ __launch_bounds__(256) void grid_int_terms_kernel(int n, int np, GridInt g, int longer, double shorter_off, int whole_margin, int* __restrict__ gstat) {
+    __shared__ double red[4][256];
     const long long o = (long long)blockIdx.x * np;
-    double tr = 0.0, e = 0.0, e3 = 0.0;
-    for (int c = threadIdx.x; c < n; c += 256) { tr += g.hd[o + c]; e += g.e2[o + c]; e3 += (double)c * g.v3[o + c] * g.v3[o + c]; }
-    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = e; red[2][threadIdx.x] = e3;
+    double tr = 0.0, e = 0.0, e3 = 0.0, off = 0.0;
+    for (int c = threadIdx.x; c < n; c += 256) { tr += g.hd[o + c]; e += g.e2[o + c]; off += g.off2[o + c]; e3 += (double)c * g.v3[o + c] * g.v3[o + c]; }
+    red[0][threadIdx.x] = tr; red[1][threadIdx.x] = e; red[2][threadIdx.x] = e3; red[3][threadIdx.x] = off;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
         if ((int)threadIdx.x < w)
-            for (int k = 0; k < 3; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
+            for (int k = 0; k < 4; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + w];
         __syncthreads();
     }
     auto within = [&](double ee, double lim) { lim *= red[0][0]; return ee / 3.0 <= lim * lim; };      // E = 2 sqrt(e / 12) / tr
-    const int terms = (!longer && within(red[1][0], GRID_TWO_DIGITS)) ? 2 : 3;
+    const double off_lim = shorter_off * red[0][0];
+    const int terms = (!longer && within(red[1][0], GRID_TWO_DIGITS) && 2.0 * red[3][0] <= off_lim * off_lim) ? 2 : 3;
     if (threadIdx.x == 0) {
         g.terms[blockIdx.x] = terms;
         g.tau[blockIdx.x] = !whole_margin && within(red[terms == 2 ? 1 : 2][0], GRID_NARROW_ERROR) ? GRID_TAU_NARROW : GRID_TAU;
@@ -1285,7 +1292,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             hipLaunchKernelGGL(grid_terms_kernel, dim3(nhin), dim3(256), 0, st, L.Hi, n, np, L.gscale, L.grid_terms, grid_one_term(d->bits), L.gstat + GS_SHORT);
         } else {
             hipLaunchKernelGGL(grid_int_steps_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, L.maxq, L.gint);
-            hipLaunchKernelGGL(grid_int_terms_kernel, dim3(nhin), dim3(256), 0, st, n, np, L.gint, L.grid_terms >= 2, d->grid_guard > 0.25, L.gstat + GS_SHORT);
+            hipLaunchKernelGGL(grid_int_terms_kernel, dim3(nhin), dim3(256), 0, st, n, np, L.gint, L.grid_terms >= 2, grid_one_term(d->bits), d->grid_guard > 0.25, L.gstat + GS_SHORT);
             hipLaunchKernelGGL(grid_int_factor_kernel, dim3(np, nhin), dim3(256), 0, st, L.Hi, n, np, pitch, L.gint, (signed char*)L.Hcat, 2 * term);
         }
         TB_KERNEL_CHECK(ctx);
@@ -1655,7 +1662,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
             L.wdown = ar.get<float>(grows);
         } else {
             L.gint.v = ar.get<double>(cols); L.gint.hd = ar.get<double>(cols); L.gint.v2 = ar.get<double>(cols); L.gint.v3 = ar.get<double>(cols);
-            L.gint.e2 = ar.get<double>(cols); L.gint.tau = ar.get<double>(L.nhin); L.gint.terms = ar.get<int>(L.nhin);
+            L.gint.e2 = ar.get<double>(cols); L.gint.off2 = ar.get<double>(cols); L.gint.tau = ar.get<double>(L.nhin); L.gint.terms = ar.get<int>(L.nhin);
             const size_t w_rows = mats * rows16(GRID_WD * (long long)mat_rows);
             L.gwt.A = (signed char*)ar.get<__half>(w_rows * grid_pitch((int)np, delta)); L.gwt.wu = ar.get<double>(grows);
             L.gwp = ar.get<int>(3 * w_rows * np); L.gwv = ar.get<double>(grows * np); L.gleast = ar.get<double>(grows);

@@ -80,3 +80,16 @@ def test_the_guard_is_the_caller_s(lib, guard, again):
     for k in ("codes", "scales", "zeros", "W_deq"):
         assert torch.equal(fast[k], exact[k]), k
     ctx.close()
+
+
+@pytest.mark.parametrize("bits,tokens", [(2, 16384), (3, 65536)])
+def test_two_digits_only_where_one_half_term_did(lib, bits, tokens):
+    """Independent channels over so many tokens that two digits would be off by no more than 6e-7 by expectation, but too few for one half term of H_in: costs from pairs of
+    half terms are within 2.4e-7 of the exact ones, from two digits 5e-7 - 1e-6, from three, which are taken, 2e-8."""
+    g = torch.Generator(device="cuda"); g.manual_seed(1024 + bits)
+    x = torch.randn(tokens, 1024, generator=g, device="cuda", dtype=torch.float64)
+    W, H = (torch.randn(64, 1024, generator=g, device="cuda") * 0.02), (x.T @ x).float()
+    ctx = lib.Context()
+    ctx.quantize_layer(W, H, None, None, 1, bits, 64, grid_guard=2.4e-7 / 2e-3)
+    assert ctx.counter(0) == 1 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    ctx.close()
