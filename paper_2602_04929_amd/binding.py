@@ -136,7 +136,7 @@ class Context:
     def counter(self, which):
         """tboa_counter_id: 0 two-phase grid-search passes, 1 quantize_layer calls run again with exact grid-search costs,
         2 unused, 3 near-minimal candidates evaluated exactly, 4 / 5 dequantized weight matrices taken in integer form / split,
-        6 quantize_layer calls run again with H_in as two half terms where one had been taken."""
+        6 quantize_layer calls run again with the longer form of H_in (two half terms, three digits) where the shorter one had been taken."""
         return int(_lib.tboa_counter(self._h, which))
 
     def workspace_bytes(self):

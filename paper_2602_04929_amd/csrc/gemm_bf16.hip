@@ -1271,7 +1271,8 @@ int gemm_gram(tboa_ctx* ctx, const GemmBf16& q, double scale, int chunk) {
     if (q.M <= 0 || q.N <= 0) return 0;
     const bool tiled = (q.flags & TBOA_GEMM_A_TILED) != 0;
     const int term = q.nterms > 0 ? q.K / q.nterms : 0;
-    if (!q.A || !q.B || !q.C || q.batch != 1 || q.c_dtype != TBOA_F32 || q.accumulate || q.nterms < 1 || q.nterms > 4 || chunk < FK * T128_NS || chunk % (FK * T128_NS) || q.K % q.nterms || term % FK || term <= 0 ||
+    if (!q.A || !q.B || !q.C || q.batch != 1 || q.c_dtype != TBOA_F32 || q.accumulate || q.nterms < 1 || q.nterms > 4 ||
+        chunk < FK * T128_NS || chunk % (FK * T128_NS) || q.K % q.nterms || term % FK || term <= 0 ||
         (q.flags & ~(TBOA_GEMM_LOWER | TBOA_GEMM_F16 | TBOA_GEMM_A_TILED | TBOA_GEMM_B_TILED)) || tiled != ((q.flags & TBOA_GEMM_B_TILED) != 0) ||
         q.lda % (tiled ? 32 : 8) || q.ldb % (tiled ? 32 : 8) || (tiled && (q.M % 16 || q.N % 16)) || ((q.flags & TBOA_GEMM_LOWER) && q.M != q.N))
         return tboa_fail(ctx, TBOA_EINVAL, "gemm_gram: unsupported product");

@@ -666,8 +666,8 @@ enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_LOW = 4
 // least (integer form; null: none): where the minimum lies below it (a row that one candidate meets, a constant row, a row of one weight) approximate costs
 // do not tell which candidate it is: every candidate up to twice least[row] survives, all are evaluated, and the row stays out of the guard's
 // deviation (least[row] becomes -1 for grid_argmin_sel_kernel).  From there on costs are resolved, so nothing cheaper lies beyond twice least[row].
-__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, const double* __restrict__ taus, int per, double* __restrict__ least, int* __restrict__ list,
-                                  int* __restrict__ cnt_out, int* __restrict__ gstat) {
+__global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, const double* __restrict__ taus, int per,
+                                                         double* __restrict__ least, int* __restrict__ list, int* __restrict__ cnt_out, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= rows) return;
     const double* c = cost + (long long)row * ncand; int* out = list + (long long)row * ncand;
@@ -1181,13 +1181,15 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
                 TB_TRY(gemm_bf16_nt(ctx, w));
                 hipLaunchKernelGGL(grid_weight_products_kernel, dim3((unsigned)((np + 255) / 256), rows), dim3(256), 0, ctx->stream, L.gwp, m, gw, gi2, L.gwv);
                 const long long parts = (ncand + GRID_KC - 1) / GRID_KC;
-                hipLaunchKernelGGL(grid_cost_kernel, dim3((unsigned)((rows * parts + 3) / 4)), dim3(256), 0, ctx->stream, (const int*)L.G, Acat, rows, m, gi2, L.cand_s, Wc, ldw, n, L.gwv, L.cost, L.gleast);
+                hipLaunchKernelGGL(grid_cost_kernel, dim3((unsigned)((rows * parts + 3) / 4)), dim3(256), 0, ctx->stream, (const int*)L.G, Acat, rows, m, gi2, L.cand_s,
+                                   Wc, ldw, n, L.gwv, L.cost, L.gleast);
             }
             TB_KERNEL_CHECK(ctx);
             const int per = ph ? rows_per_head : rows, ngrp = rows / per;    // rows that share one H_in
             const int cap = per * GRID_KS;                                    // exact re-evaluations a group has room for
             int* cntv = L.sel; int* offv = cntv + rows; int* totv = offv + rows;
-            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand, delta ? nullptr : L.gint.tau + (ph ? u0 : 0), per, delta ? nullptr : L.gleast, L.list, cntv, L.gstat);
+            hipLaunchKernelGGL(grid_count_kernel, dim3((rows + 3) / 4), dim3(256), 0, ctx->stream, L.cost, rows, ncand,
+                               delta ? nullptr : L.gint.tau + (ph ? u0 : 0), per, delta ? nullptr : L.gleast, L.list, cntv, L.gstat);
             hipLaunchKernelGGL(grid_scan_kernel, dim3(ngrp), dim3(256), 0, ctx->stream, cntv, per, cap, offv, totv, L.gstat);
             hipLaunchKernelGGL(grid_delta_sel_kernel, dim3((n + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
                                L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
@@ -1263,7 +1265,7 @@ int pair_gemm(Layer& L, int nbr, int N, int K, int ecol, long long boff, const d
 }
 
 // return values of run_layer: the approximate costs of the two-phase grid search could not be trusted somewhere in this
-// run (see grid_search): the caller runs the layer again with exact costs for every candidate, or (one half term of H was not enough) with two
+// run (see grid_search): the caller runs the layer again with exact costs for every candidate, or (the shorter form of H was not enough) with the longer one
 constexpr int RUN_AGAIN_EXACT = 1, RUN_AGAIN_TWO_TERMS = 2;
 
 int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, const float* R, uint8_t* codes, float* scales,
@@ -1713,11 +1715,14 @@ void init_layer(Layer& L, tboa_ctx* ctx, const tboa_layer_desc* d) {
     const int units = L.nhin > 1 ? L.nh : L.nh * max_rows_block;
     const double c = cap / (L.nhin > 1 ? per_row * max_rows_block : per_row);
     L.grid_chunk = c < 1.0 ? 1 : (c > units ? units : (int)c);
-    // the two-phase search holds 2 + 4 bytes per entry where the exact one holds 8 + 8: twice the rows in the same buffers
+    // the two-phase search holds 1 + 4 bytes per entry (codes and products; 4 + 4 with pairs of delta) where the exact one holds 8 + 8: twice the rows in the same buffers
     L.fast_chunk = c < 0.5 ? 1 : (2.0 * c > units ? units : (int)(2.0 * c));
     // per-row grids of wide layers: two-phase search (a negative grid_guard asks for exact costs throughout).  Narrow layers
-    // (d_in < 256) keep the exact search: one launch over all candidates, nothing to re-evaluate.  So do steps of few rows whose fp64 products are a few
-    // microseconds: a search is 5 launches then and not 12 (block of 256 columns, 4 rows a head and step: 5.3 instead of 6.3 ms)
+    // (d_in < 256) keep the exact search: one launch over all candidates, nothing to re-evaluate.  So do steps whose fp64 products take a few
+    // microseconds, where a search is 5 launches and not 12.  The line in rows x candidates x d_in^2, a whole step in us, two phases -> exact costs:
+    //     2e7 148 -> 111, 8e7 154 -> 121, 3e8 228 -> 198, 7e8 237 -> 221, 1.0e9 252 -> 234, 1.3e9 262 -> 286 (d_in 512), 410 -> 411 (1024), 2.7e9 257 -> 321
+    // whatever the rows per head.  Taken below 16 rows a head only, though exact costs would save 10 - 35 us a step up to 1e9 there too (256 columns, 16 rows: 179 -> 146): from 16 rows
+    // on the search keeps to two phases at every size, with the counters and the guard that callers of such blocks read and set.
     const bool few = d->adaptive_grid && blk < 16 && (double)L.nh * blk * L.ncand * (double)L.nn <= 1e9;
     L.fast_grid = (!d->group && L.n >= 256 && !few && !(d->grid_guard < 0.0)) ? 1 : 0;
     L.gstat = ctx ? ctx->d_status + TB_GSTAT_WORD : nullptr;

@@ -44,6 +44,6 @@ def test_names_the_pivot(lib, n, col):
     H = torch.eye(n, device="cuda")[None].repeat(2, 1, 1)
     H[1, col, col] = -1.0
     H[1, 0, 0] = -2.0
-    with pytest.raises(Exception, match=r"1 of the batch is not positive definite: pivot %d " % max(col, 0)):
+    with pytest.raises(Exception, match=r"1 of the batch is not positive definite: pivot %d " % col):
         ctx.chol_inv_upper(H)
     ctx.close()
