@@ -855,7 +855,10 @@ GemmBf16 nt(int M, int N, int K, float alpha, const bf16* A, long long lda, cons
 // Whether a Gram product goes through gemm_gram (one result, long sums folded in registers) instead of `splits` partial sums in memory.  A stage of 32 contraction
 // indices takes a workgroup 0.40 us there (128 x 256; 0.46 from row-major operands) and 0.75 us in the split launches (256 x 256), and the partial sums are written once and read once at
 // 4.5 TB/s; few tiles leave the chip idle in one pass.  Measured (H and R, 8192 tokens): 11008 columns 8.2 -> 4.9 ms, 8192 4.7 -> 2.7, 4096 1.24 -> 0.72,
-// 2048 0.35 -> 0.29, 1024 0.13 -> 0.26 (stays split).  Sums are folded after no more terms than a split had (of 512 in R's two pairs 384: at
+// 2048 0.35 -> 0.29, 1024 0.13 -> 0.26 (stays split).
+// Token counts without a divisor have one split, whose sum runs over all of them.  There is no traffic to save there, the stages of full rounds take 0.46 us here (the power
+// limit) where 0.40 is reckoned, and one pass takes up to 1.2 times as long (H and R, 5888 tokens: 5120 columns 734 -> 876 us, 3328 382 -> 413, 8192 1766 -> 1985; 2048 and fewer
+// gain, 329 -> 215).  It stays for its sums, folded every 512 terms: H and R of 3328 columns are off by 7.6e-8 instead of 4.5e-7.  Sums are folded after no more terms than a split had (of 512 in R's two pairs 384: at
 // 8192 tokens R is then off by 6e-8, with partial sums by 7e-8); those of splits of fewer than 128 tokens stay as they are, and sums of fewer than 512.
 bool one_pass_gram(int n, int splits, int npairs, int Kc, int lower, int blocked) {
     if (Kc % 32 || Kc < 128 || Kc * splits < 512 || (long long)Kc * npairs * splits > 0x7fffffffLL) return false;
