@@ -664,8 +664,9 @@ enum { GS_TRIPPED = 0, GS_SURVIVORS = 1, GS_MAXDEV = 2, GS_SHORT = 3, GS_LOW = 4
 // exact cost is what the deviation guard of the pass measures.
 // taus (integer form; null: GRID_TAU): the margin of each group of `per` rows.
 // least (integer form; null: none): where the minimum lies below it (a row that one candidate meets, a constant row, a row of one weight) approximate costs
-// do not tell which candidate it is: every candidate up to twice least[row] survives, all are evaluated, and the row stays out of the guard's
-// deviation (least[row] becomes -1 for grid_argmin_sel_kernel).  From there on costs are resolved, so nothing cheaper lies beyond twice least[row].
+// do not tell which candidate it is: every candidate up to twice least[row] survives, all are evaluated, and the row stays out of the guard's relative
+// deviation (its least changes sign for grid_argmin_sel_kernel).  Approximations of the survivors within half of least[row] leave nothing cheaper beyond twice least[row]; one
+// that is further off (a cost below its own approximation's error) voids the pass.
 __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restrict__ cost, int rows, int ncand, const double* __restrict__ taus, int per,
                                                          double* __restrict__ least, int* __restrict__ list, int* __restrict__ cnt_out, int* __restrict__ gstat) {
     const int lane = threadIdx.x & 63, row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -690,7 +691,7 @@ __global__ __launch_bounds__(256) void grid_count_kernel(const double* __restric
     if (lane != 0) return;
     if (cnt == 0) out[0] = 0;
     if (bad || cnt == 0 || (least && m < lowest && !low)) { atomicOr(gstat + GS_TRIPPED, 1); cnt = 0; }
-    if (low) { least[row] = -1.0; atomicAdd(gstat + GS_LOW, 1); }
+    if (low) { least[row] = -lowest; atomicAdd(gstat + GS_LOW, 1); }
     const int ev = (cnt > 1 || low || row % 8 == 0) ? cnt : 0;
     cnt_out[row] = ev;
     if (ev) atomicAdd(gstat + GS_SURVIVORS, ev);
@@ -755,7 +756,7 @@ __global__ __launch_bounds__(256) void rowdot_limited_kernel(const double* __res
 
 // lowest exact cost among the survivors of a row (lowest k among equals); a row whose survivors were not evaluated takes its
 // first one (it has a single one, or the pass is void anyway).  Every exact re-evaluation is compared with its approximation for
-// the guard (rows with least[row] < 0 aside).  One wavefront per row, one survivor per lane.
+// the guard, in rows with least[row] < 0 by the distance and not in relation to the cost.  One wavefront per row, one survivor per lane.
 __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __restrict__ costS, const double* __restrict__ cost, const int* __restrict__ list,
                                        const int* __restrict__ cnt, const int* __restrict__ off, int per, int cap,
                                        const double* __restrict__ cand_s, const double* __restrict__ cand_z, int rows, int ncand,
@@ -766,18 +767,20 @@ __global__ __launch_bounds__(256) void grid_argmin_sel_kernel(const double* __re
     const double* cr = cost + (long long)row * ncand; const int* l = list + (long long)row * ncand;
     const double* ce = costS + (long long)(row / per) * cap;
     const int nc = cnt[row], slot0 = off[row];
+    const double half = least && least[row] < 0.0 ? -0.5 * least[row] : 0.0;
     double bc = 0.0, dev = 0.0; int best = 0x7fffffff;
     for (int j = lane; j < nc && slot0 + j < cap; j += 64) {
         const int k = l[j];
         const double e = ce[slot0 + j], d = cr[k] == e ? 0.0 : fabs(cr[k] - e) / fabs(e);      // (equal: a row of zeros costs 0 both ways)
         if (best == 0x7fffffff || e < bc) { bc = e; best = k; }
-        dev = fmax(dev, (d == d) ? d : 1.0);
+        dev = fmax(dev, half > 0.0 ? (fabs(cr[k] - e) <= half ? 0.0 : 1.0) : (d == d) ? d : 1.0);
     }
     wave_argmin(bc, best);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) dev = fmax(dev, __shfl_xor(dev, o, 64));
     if (lane != 0) return;
-    if (nc > 0 && !(least && least[row] < 0.0)) atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
+    if (nc > 0 && half == 0.0) atomicMax(gstat + GS_MAXDEV, __float_as_int((float)fmin(dev, 1.0)));
+    if (half > 0.0 && dev > 0.0) atomicOr(gstat + GS_TRIPPED, 1);
     if (best == 0x7fffffff) best = l[0];
     const long long lr = layer_row(m, r_off + row);
     s_out[lr * ng + gi] = cand_s[(long long)row * ncand + best];

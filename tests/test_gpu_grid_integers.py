@@ -1,5 +1,6 @@
 """The integer form of the grid search's products (2 bits, 3 bits up to 2048 columns): products of bytes by digits against 64-bit sums, at the edges of its
 256-column padding and of its two and three digits, through layers whose results must be those of exact costs (GPU)."""
+import numpy as np
 import pytest
 import torch
 
@@ -92,4 +93,55 @@ def test_two_digits_only_where_one_half_term_did(lib, bits, tokens):
     ctx = lib.Context()
     ctx.quantize_layer(W, H, None, None, 1, bits, 64, grid_guard=2.4e-7 / 2e-3)
     assert ctx.counter(0) == 1 and ctx.counter(1) == 0 and ctx.counter(6) == 0
+    ctx.close()
+
+
+def test_a_row_whose_costs_the_integers_do_not_resolve(lib):
+    """H = 1 1^T + 2^-23 I, whose rows of T' are all off by the same factor: a row is made (on the CPU, with the costs of T') of which two candidates cost next to nothing,
+    the dearer of them less than nothing by its approximation.  What is so far off is no row on a candidate's grid: the call goes to exact costs."""
+    n, rng = 4096, np.random.default_rng(0)
+    v = np.maximum(3.0 * np.arange(n) / (2147483000.0 - 1.5 * n), 1.0 / 8.3e6)
+    T = np.rint(1.0 / v) * v
+
+    def costs(w):      # of T', of H, and the sums of delta
+        lo, hi, p = min(w.min(), 0.0), max(w.max(), 0.0), 1.0 - np.arange(80) / 100.0
+        s = (p * hi - p * lo) / 3.0
+        z = np.rint(-(p * lo) / s)
+        d = s[:, None] * (np.clip(np.rint(w / s[:, None]) + z[:, None], 0, 3) - z[:, None]) - w
+        before, sq = np.cumsum(d, 1) - d, (1.0 + 2.0 ** -23) * d * d
+        return (2 * d * T * before + sq).sum(1), (2 * d * before + sq).sum(1), d.sum(1)
+
+    def draw():
+        return (0.02 * rng.standard_normal(n)).astype(np.float32).astype(np.float64)
+
+    def misled():
+        while True:
+            w = draw()
+            sums = costs(w)[2]
+            order = np.argsort(sums)
+            for g in np.argsort(np.diff(sums[order]))[:6]:
+                if abs(sums[order[g]]) > 0.08: continue
+                for f in (0.0, 0.25, 0.5, 0.75, 1.0):
+                    u, c = w.copy(), np.argsort(np.abs(w))[n // 4: 3 * n // 4]
+                    for _ in range(3):      # every sum falls by the same as long as no code changes
+                        sums_u = costs(u)[2]
+                        u[c] += (sums_u[order[g]] * f + sums_u[order[g + 1]] * (1 - f)) / len(c)
+                        u = u.astype(np.float32).astype(np.float64)
+                    a, e, _ = costs(u)
+                    if a.min() < 0 and a.argmin() != e.argmin() and a[e.argmin()] > 0: return u
+    rows = []
+    while len(rows) < 15:      # rows that the integers resolve
+        w = draw()
+        if np.sort(costs(w)[1])[0] > 2e-3: rows.append(w)
+    rows.insert(3, misled())
+    W = torch.from_numpy(np.stack(rows).astype(np.float32)).cuda()
+    H = torch.ones(n, n, device="cuda")
+    H.diagonal().add_(2.0 ** -23)
+    ctx = lib.Context()
+    fast = ctx.quantize_layer(W, H, None, None, 1, 2, 16, damp=0.0)
+    assert ctx.counter(0) > 0
+    exact = ctx.quantize_layer(W, H, None, None, 1, 2, 16, damp=0.0, grid_guard=-1.0)
+    for k in ("codes", "scales", "zeros", "W_deq"):
+        assert torch.equal(fast[k], exact[k]), k
+    assert ctx.counter(1) == 1
     ctx.close()
