@@ -214,7 +214,7 @@ typedef struct {
     double damp;        /* every Hessian gets damp * mean(diag) added to its diagonal at entry        */
     double grid_guard;  /* the grid search of wide per-row layers (d_in >= 256, group = 0) finds its candidates' costs
                            approximately on the matrix cores (adaptive grids by steps of fewer than 16 rows a head with at most 1e9 products
-                           rows x candidates x d_in^2: exactly) and re-evaluates the near-minimal ones (within 2e-3 of the minimum, 1e-3 where
+                           rows x candidates x d_in^2: exactly) and re-evaluates the near-minimal ones (within 2e-3 of the minimum, 1.05e-3 where
                            costs are expected to be off by less than 5e-8 and grid_guard <= 0.25) in fp64; every re-evaluation is compared with its
                            approximation, and a call in which one differs by more than grid_guard * 2e-3 (relative) is run again with
                            fp64 costs for every candidate (where the shorter form of H_in was taken: with the longer one first).  0: the

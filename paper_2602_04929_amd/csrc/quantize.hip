@@ -261,10 +261,11 @@ __global__ __launch_bounds__(256) void grid_group_kernel(const double* __restric
 // default) is repeated: with the longer form of T if a matrix had the shorter one, else with exact costs for every candidate (counted by tboa_counter).
 constexpr int GRID_PAD = 256;        // extra elements per row of the operands (memory-channel spread)
 constexpr int GRID_KS = 6;          // exact re-evaluations per row
-// survivors: approximate cost <= (1 + tau) * approximate minimum.  Half of that with integers where the expected error E of a cost is 5000 times below what the default
-// guard lets pass in half a margin (2.5e-4): uncorrelated channels over many tokens, where the largest deviations seen are 8e-8, and fewer candidates need exact costs (70B-shaped W_O:
-// the call 168.5 -> 165 ms).  A caller's guard above the default keeps the whole margin.
-constexpr double GRID_TAU = 2e-3, GRID_TAU_NARROW = 1e-3, GRID_NARROW_ERROR = 5e-8;
+// survivors: approximate cost <= (1 + tau) * approximate minimum.  The cheapest candidate is among them where no cost is off by more than g with (1 + g) / (1 - g) <= 1 + tau.
+// A narrower margin, which covers the g = 5e-4 that the default guard lets pass, with integers where the expected error E of a cost is 10000 times below that:
+// uncorrelated channels over many tokens, where the largest deviations seen are 8e-8, and fewer candidates need exact costs (70B-shaped W_O: the call 168.7 -> 163.6 ms).
+// A caller's guard above the default keeps the whole margin.
+constexpr double GRID_TAU = 2e-3, GRID_TAU_NARROW = 1.05e-3, GRID_NARROW_ERROR = 5e-8;
 constexpr double GRID_TWO_DIGITS = 6e-7;      // expected relative error of a cost up to which two digits of T do, |H off the diagonal|_F permitting (grid_one_term)
 // the left operand is delta as a pair of halves, else the integer codes: 3 levels of qbar over any width, 7 over 2048 columns.  The step of T grows with maxq times
 // the width; beyond that the pairs are closer on correlated channels (4 bits, 8192 columns: 1.5e-6 - 5.8e-6 against 2e-5 expected of integers)
