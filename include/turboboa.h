@@ -290,6 +290,13 @@ int tboa_gemm_f64(tboa_ctx* ctx, int M, int N, int K, double alpha,
                   double beta, double* C, int64_t ldc,
                   int batch, int64_t strideA, int64_t strideB, int64_t strideC);
 
+/* C = alpha A B + beta C in fp64 on the integer matrix cores: A (row-major, lda) and B (element (k, n) at B[k*sbk + n*sbn], one of the strides 1) are taken as integers of 57
+ * and 58 bits below the 2-norm of each row of A and column of B, and the product modulo 15 numbers of 8 bits.  A result is off by at most 2^-56 |a_m| |b_n| plus its own
+ * rounding (an fp64 product rounds every partial sum: about 2^-54.7 |a_m| |b_n| over terms of random sign).  A row or column that holds an infinity or NaN gives NaN.
+ * K <= 32768.  Operands in residues and residues of C take context workspace: 15 bytes per element, rows and columns rounded up to 256 for C. */
+int tboa_gemm_f64_residues(tboa_ctx* ctx, int M, int N, int K, double alpha, const double* A, int64_t lda,
+                           const double* B, int64_t sbk, int64_t sbn, double beta, double* C, int64_t ldc);
+
 /* C[b] = alpha * A[b] B[b]^T (+ C[b] if accumulate) with bf16 operands, fp32 accumulation on the bf16
  * matrix cores.  A [M, K] row-major lda, B [N, K] row-major ldb (both K-contiguous; lda, ldb multiples of 8,
  * pointers 16-byte aligned).  C [M, N] ldc, fp32 (c_dtype = TBOA_F32) or bf16 (TBOA_BF16, accumulate must be 0).

@@ -53,6 +53,7 @@ def _load():
         "tboa_reserve_workspace": ([vp, C.c_size_t], i32),
         "tboa_quantize_workspace_bytes": ([C.POINTER(LayerDesc), C.c_int, C.c_int], C.c_size_t),
         "tboa_gemm_f64": ([vp, i32, i32, i32, f64, vp, i64, i64, vp, i64, i64, f64, vp, i64, i32, i64, i64, i64], i32),
+        "tboa_gemm_f64_residues": ([vp, i32, i32, i32, f64, vp, i64, vp, i64, i64, f64, vp, i64], i32),
         "tboa_gemm_bf16_nt": ([vp, i32, i32, i32, f32, vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i64, i64, i64], i32),
         "tboa_chol_inv_upper": ([vp, i32, i32, vp, f64, vp], i32),
         "tboa_chol_inv_upper_static": ([vp, i32, i32, vp, f64, vp], i32),
@@ -176,6 +177,16 @@ class Context:
         return dict(ms=ms.value, launches=n.value, flops=fl.value)
 
     # ---- building blocks
+    def gemm_f64_residues(self, A, B, C_out=None, alpha=1.0, beta=0.0, transB=False):
+        """alpha A op(B) + beta C_out for one pair of fp64 matrices, on the integer matrix cores."""
+        _dev(A, torch.float64); _dev(B, torch.float64)
+        M, K = A.shape
+        N = B.shape[0] if transB else B.shape[1]
+        out = torch.zeros(M, N, dtype=torch.float64, device=A.device) if C_out is None else C_out
+        sbk, sbn = (1, K) if transB else (N, 1)
+        self._check(_lib.tboa_gemm_f64_residues(self._h, M, N, K, alpha, _ptr(A), K, _ptr(B), sbk, sbn, beta, _ptr(out), N))
+        return out
+
     def gemm_f64(self, A, B, C_out=None, alpha=1.0, beta=0.0, transA=False, transB=False):
         """C = alpha op(A) op(B) + beta C for 2-D or batched 3-D fp64 tensors."""
         batched = A.dim() == 3

@@ -287,7 +287,7 @@ constexpr double STEP_US[4] = {2.1, 0.78, 0.32, 0.8};
 // second kernel and the traffic of the parts when there is a split.
 // own_rows: C takes A's place, row for row: a workgroup reads all of the rows that it writes and no others, with one column of tiles.
 // always_parts: the result goes through the parts whatever the split.
-Choice choose(const GemmF64& q, bool akc, size_t part_elems, bool always_parts, bool own_rows) {
+Choice choose(const GemmF64& q, bool akc, size_t part_elems, bool always_parts, bool own_rows, double* modelled = nullptr) {
     const double k16 = std::max(1.0, q.K / 16.0 * (q.A2 ? 2.0 : q.sym ? 0.5 : 1.0));
     const bool no_split = q.skip_lower || q.skip_upper || q.m_limit || q.sym || own_rows;
     Choice best{S128, 1}; double best_us = 1e30;
@@ -305,6 +305,7 @@ Choice choose(const GemmF64& q, bool akc, size_t part_elems, bool always_parts, 
             if (us < best_us) { best_us = us; best = Choice{(Shape)s, sp}; }
         }
     }
+    if (modelled) *modelled = best_us;
     return best;
 }
 
@@ -326,6 +327,14 @@ void launch(tboa_ctx* ctx, dim3 grid, bool akc, bool bkc, const Args& a, bool ve
 }
 
 }  // namespace
+
+double gemm_f64_model_us(int M, int N, int K) {
+    GemmF64 q{};
+    q.M = M; q.N = N; q.K = K; q.batch = 1;
+    double us = 0.0;
+    choose(q, true, TB_SPLITK_ELEMS, false, false, &us);
+    return us;
+}
 
 int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
     if (q.M <= 0 || q.N <= 0 || q.batch <= 0) return 0;

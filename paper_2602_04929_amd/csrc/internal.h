@@ -107,9 +107,52 @@ struct GemmF64 {
     int tag = -1;   // tboa_prof_tag of this launch (timed with HIP events when profiling is on)
 };
 int gemm_f64(tboa_ctx* ctx, const GemmF64& g);
+double gemm_f64_model_us(int M, int N, int K);      // what a product without restrictions takes, as gemm_f64's choice of tiles models it
 // brackets a tagged launch with HIP events on the context's current stream when profiling is on
 int prof_begin(tboa_ctx* ctx, int tag, double flops, ProfRec& rec, bool& timed);
 int prof_end(tboa_ctx* ctx, const ProfRec& rec, bool timed);
+
+// ---------------------------------------------------------------- gemm_rns.hip
+// fp64 products as products of residues (signed bytes).  An operand is prepared once (norms -> exponents -> residues) and may serve many products.
+#define TB_RNS_MODULI 15
+constexpr int RNS_BITS_A = 57, RNS_BITS_B = 58;      // bits of the rows' 2-norms: together with the sign and half a bit of room, what 15 moduli hold
+constexpr int RNS_CHUNKS = 64;                       // partial sums of rns_norms over a row-contiguous source: RNS_CHUNKS * rns_squares_elems(rows) doubles
+struct RnsSource {
+    const double* a; long long ld, stride;      // element (r, k): a[r ld + k] (kc), else a[k ld + r]; stride: batch entries
+    int kc, rows, k;
+    int half;                                    // symmetric source: twice what is before the diagonal, the diagonal once (as GemmF64::sym)
+    const int* kexp; int ksign;                  // column k times 2^(ksign kexp[k])
+    const int* exp_shift;                        // everything times 2^(ksign exp_shift[0])
+    const int* row_limit;                        // device word: rows from there on are not needed
+};
+struct RnsOperand { signed char* p; size_t plane; long long stride; int kpad; int* e; long long e_stride; };      // p: [batch][planes]; e null: integers, taken as they are
+struct RnsGemm {
+    const RnsOperand *A, *B; const RnsOperand* B2 = nullptr;      // C = alpha (A B^T [+ A' B2^T, A' = the K columns of A after the first K]) + beta C
+    int a_row = 0, b_row = 0, a_k = 0, b_k = 0;                    // first row (multiple of 16) and first contraction index (multiple of 64)
+    int M, N, K, batch = 1, nm;
+    int row0 = 0;      // of C within the matrix that the limits below speak of (multiple of 256)
+    int klo_m = 0, klo_n = 0, khi_n = 0;      // as in GemmF64, with tiles of 256
+    int upper = 0;     // C is only wanted above its diagonal: zero on and below it
+    const int* m_limit = nullptr;
+    double alpha, beta; double* C; long long ldc, strideC = 0;
+    unsigned char* residues;      // rns_residue_bytes
+    int tag = -1;
+};
+int rns_moduli(double bits);      // how many moduli hold products of |a|_2 |b|_2 <= 2^bits (0: too many bits)
+int rns_pad(int k);
+size_t rns_plane(int rows, int k);
+size_t rns_squares_elems(int rows);
+size_t rns_residue_bytes(int M, int N, int batch, int nm);
+// operand whose rows are contiguous (second: a second source right after the first along k): exponents, bits below the norm each (bits < 0: small integers as they are), and residues
+int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm);
+// operand whose rows are strided: sums of squares, exponents, residues
+int rns_norms(tboa_ctx* ctx, const RnsSource& s, int batch, double* sq, long long sq_stride, double* part);
+int rns_exps(tboa_ctx* ctx, int rows, int batch, const double* sq, long long sq_stride, int bits, int* e, long long e_stride);
+int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm);
+int rns_balance(tboa_ctx* ctx, int rows, double* sq1, const double* sq2, int* f);
+int rns_gemm(tboa_ctx* ctx, const RnsGemm& q);
+double rns_model_us(int M, int N, int K, bool triangular, bool beta, int nm);
+double rns_prepare_us(int rows, int k);
 
 // ---------------------------------------------------------------- gemm_bf16.hip
 struct GemmBf16 {

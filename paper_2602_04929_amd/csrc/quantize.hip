@@ -16,6 +16,7 @@
 #include <string.h>
 #include <stdlib.h>
 #include <math.h>
+#include <initializer_list>
 
 namespace {
 
@@ -1083,6 +1084,9 @@ __global__ __launch_bounds__(256) void head_sum_kernel(const double* __restrict_
 inline unsigned gx(long long n) { long long g = (n + 255) / 256; return (unsigned)(g < 1 ? 1 : (g > 64 ? 64 : g)); }
 
 // ------------------------------------------------------------------------------------------------ host side
+// products with d_in x d_in matrices: refinement and loss, exact grid costs, P, compensation, updates of the sweep
+enum { RNS_REFINE = 1, RNS_EXACT = 2, RNS_P = 4, RNS_COMP = 8, RNS_SWEEP = 16 };
+
 struct Layer {
     tboa_ctx* ctx; const tboa_layer_desc* d;
     int n, nh, dh, ng, gsz, nhin, ncand; double maxq;
@@ -1101,7 +1105,69 @@ struct Layer {
     double *nr, *nv;
     int* gstat;         // device words of the two-phase search (GS_*), cleared at the start of a run
     long long nn;
+    // Products with the d_in x d_in matrices on the integer matrix cores (gemm_rns.hip): the matrices as right operands, prepared once a call, and per stream of the call
+    // (0: main, 1: aux) the left operand of a product, residues of its result and sums of squares
+    int rns, rns_rows_max;      // rns: which products (RNS_*); rns_rows_max: rows of a product at a time
+    RnsOperand hT, uR, uC, pC, rC, left[2];      // H_in (its half T; group-wise: whole), rows of U, columns of U, columns of P, columns of R
+    unsigned char* rres[2]; double *rsq, *rsq2, *rpart; int *kexp, *pshift;
 };
+
+RnsSource rows_of(const double* a, long long ld, int rows, int k) {
+    RnsSource s{};
+    s.a = a; s.ld = ld; s.kc = 1; s.rows = rows; s.k = k;
+    return s;
+}
+RnsSource columns_of(const double* a, long long ld, int columns, int k) {
+    RnsSource s = rows_of(a, ld, columns, k);
+    s.kc = 0;
+    return s;
+}
+
+// kexp[k]: half the exponent of H_kk, the size of channel k: what is contracted over channels grows with it on one side and falls on the other
+__global__ void channel_exponents_kernel(const double* __restrict__ H, int n, int* __restrict__ kexp) {
+    const int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= n) return;
+    const double v = H[(long long)k * n + k];
+    kexp[k] = v > 0.0 && v < 1.7976931348623157e308 ? ilogb(v) >> 1 : 0;
+}
+
+// Columns of U as right operand, with_P: and those of P beside them (the sweep's two terms), after U and P
+int rns_u_columns(Layer& L, bool with_P) {
+    tboa_ctx* ctx = L.ctx;
+    RnsSource u = columns_of(L.Uin, L.n, L.n, L.n), p = columns_of(L.P, L.n, L.n, L.n);
+    p.exp_shift = L.pshift; p.ksign = 1;
+    TB_TRY(rns_norms(ctx, u, 1, L.rsq, 0, L.rpart));
+    if (with_P) {
+        RnsSource plain = p;
+        plain.exp_shift = nullptr;
+        TB_TRY(rns_norms(ctx, plain, 1, L.rsq2, 0, L.rpart));
+        TB_TRY(rns_balance(ctx, L.n, L.rsq, L.rsq2, L.pshift));
+    }
+    TB_TRY(rns_exps(ctx, L.n, 1, L.rsq, 0, RNS_BITS_B, L.uC.e, 0));
+    TB_TRY(rns_columns(ctx, u, 1, L.uC, 0, TB_RNS_MODULI));
+    return with_P ? rns_columns(ctx, p, 1, L.pC, 0, TB_RNS_MODULI) : 0;
+}
+
+// Products of `rows` rows (contiguous, pitch lda) with prepared right operands, N = columns each: C = A B + beta C, at most rns_rows_max rows at a time.
+// bits < 0: rows of integers up to 2^int_bits in 2-norm.
+struct RnsProduct { const RnsOperand* B; double* C; int klo_m, klo_n, khi_n, upper, nm; };
+int rns_products(Layer& L, int which, const RnsSource& A, int bits, int nm_rows, std::initializer_list<RnsProduct> products, int tag) {
+    tboa_ctx* ctx = L.ctx;
+    for (int r0 = 0; r0 < A.rows; r0 += L.rns_rows_max) {
+        RnsSource a = A;
+        a.a += (long long)r0 * A.ld; a.rows = std::min(L.rns_rows_max, A.rows - r0);
+        RnsOperand left = L.left[which];
+        if (bits < 0) left.e = nullptr;
+        TB_TRY(rns_rows(ctx, a, nullptr, 1, bits, left, nm_rows));
+        for (const RnsProduct& p : products) {
+            RnsGemm g{};
+            g.A = &left; g.B = p.B; g.M = a.rows; g.N = L.n; g.K = A.k; g.nm = p.nm; g.klo_m = p.klo_m; g.klo_n = p.klo_n; g.khi_n = p.khi_n; g.upper = p.upper; g.row0 = r0;
+            g.alpha = 1.0; g.beta = 0.0; g.C = p.C + (long long)r0 * L.n; g.ldc = L.n; g.residues = L.rres[which]; g.tag = tag; g.m_limit = A.row_limit;
+            TB_TRY(rns_gemm(ctx, g));
+        }
+    }
+    return 0;
+}
 
 // Algorithm 1 line 9 for the rows Wrows (block rows of every head, or whole heads for the fixed grid), columns [c0, c0 + ncols).
 // Everything is enqueued; nothing is read back here.
@@ -1198,12 +1264,18 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             hipLaunchKernelGGL(grid_delta_sel_kernel, dim3((n + 255) / 256, rows), dim3(256), 0, ctx->stream, Wc, ldw, n, ncand, L.maxq,
                                L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
             TB_KERNEL_CHECK(ctx);
+            if (L.rns & RNS_EXACT) {
+                RnsSource a = rows_of(L.DeltaS, n, cap, n);
+                a.row_limit = totv;
+                TB_TRY(rns_products(L, 0, a, RNS_BITS_A, TB_RNS_MODULI, {{&L.hT, L.GS, 0, 0, 1, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_GRID));
+            } else {
             GemmF64 g{};
             g.M = cap; g.N = n; g.K = n; g.alpha = 1.0; g.beta = 0.0; g.A = L.DeltaS; g.sam = n; g.sak = 1; g.sbk = n; g.sbn = 1;
             g.C = L.GS; g.ldc = n; g.batch = ngrp; g.strideA = (long long)g.M * n; g.strideC = g.strideA; g.m_limit = totv;
             g.B = L.Hi + (ph ? (long long)u0 * L.nn : 0); g.strideB = ph ? L.nn : 0;
             g.tag = TBOA_PROF_F64_GRID; g.sym = 1;      // delta H delta^T: half of H is enough
             TB_TRY(gemm_f64(ctx, g));
+            }
             const long long srow = (long long)ngrp * cap;
             hipLaunchKernelGGL(rowdot_limited_kernel, dim3((unsigned)((srow + 3) / 4)), dim3(256), 0, ctx->stream, L.GS, L.DeltaS, n, cap,
                                srow, totv, L.costS);
@@ -1268,6 +1340,21 @@ int pair_gemm(Layer& L, int nbr, int N, int K, int ecol, long long boff, const d
     return gemm_f64(L.ctx, g);
 }
 
+// Wk[:, s1 ..] -= Epan U[s0 .. s1, s1 ..] + Wsnap P[s0 .. s1, s1 ..], both terms in one product of residues
+int rns_sweep_update(Layer& L, int rows, int s0, int s1, bool with_P) {
+    for (int r0 = 0; r0 < rows; r0 += L.rns_rows_max) {
+        const int m = std::min(L.rns_rows_max, rows - r0);
+        RnsSource e = rows_of(L.Epan + (long long)r0 * SWEEP_SP, SWEEP_SP, m, SWEEP_SP), w = rows_of(L.Wsnap + (long long)r0 * SWEEP_SP, SWEEP_SP, m, SWEEP_SP);
+        w.exp_shift = L.pshift; w.ksign = -1;
+        TB_TRY(rns_rows(L.ctx, e, with_P ? &w : nullptr, 1, RNS_BITS_A, L.left[0], TB_RNS_MODULI));
+        RnsGemm g{};
+        g.A = &L.left[0]; g.B = &L.uC; g.B2 = with_P ? &L.pC : nullptr; g.b_row = s1; g.b_k = s0; g.M = m; g.N = L.n - s1; g.K = SWEEP_SP; g.nm = TB_RNS_MODULI;
+        g.alpha = -1.0; g.beta = 1.0; g.C = L.Wk + (long long)r0 * L.n + s1; g.ldc = L.n; g.residues = L.rres[0]; g.tag = TBOA_PROF_F64_SWEEP;
+        TB_TRY(rns_gemm(L.ctx, g));
+    }
+    return 0;
+}
+
 // return values of run_layer: the approximate costs of the two-phase grid search could not be trusted somewhere in this
 // run (see grid_search): the caller runs the layer again with exact costs for every candidate, or (the shorter form of H was not enough) with the longer one
 constexpr int RUN_AGAIN_EXACT = 1, RUN_AGAIN_TWO_TERMS = 2;
@@ -1303,6 +1390,13 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         }
         TB_KERNEL_CHECK(ctx);
     }
+    if (L.rns) {
+        RnsSource h = rows_of(L.Hi, n, n, n);
+        h.half = !d->group;
+        if (L.hT.p) TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, L.hT, TB_RNS_MODULI));
+        hipLaunchKernelGGL(channel_exponents_kernel, dim3((n + 255) / 256), dim3(256), 0, st, L.Hi, n, L.kexp);
+        TB_KERNEL_CHECK(ctx);
+    }
     // U_in, P and U_out are first needed by the first in-channel sweep; the grid search before it needs only W and H_in.
     // The factorisations and the two P products (for one matrix: chains of small kernels that leave most of the GPU idle)
     // therefore run on the context's second stream, beside that grid search; setup_join() below is where they meet.
@@ -1330,6 +1424,15 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     // SWEEP_SP d^2 for the blocks: taken when that is less than the products it saves (rows < d / 2 - SWEEP_SP per H_in).
     if (R) {
         TB_TRY(launch_cvt_f32_to_f64(ctx, R, L.Rd, nhin * nn));
+        if (L.rC.p) {
+            RnsSource r = columns_of(L.Rd, n, n, n);
+            TB_TRY(rns_norms(ctx, r, 1, L.rsq, 0, L.rpart)); TB_TRY(rns_exps(ctx, n, 1, L.rsq, 0, RNS_BITS_B, L.rC.e, 0)); TB_TRY(rns_columns(ctx, r, 1, L.rC, 0, TB_RNS_MODULI));
+        }
+        if (L.uR.p) {
+            RnsSource u = rows_of(L.Uin, n, n, n);
+            u.kexp = L.kexp; u.ksign = 1;
+            TB_TRY(rns_rows(ctx, u, nullptr, 1, RNS_BITS_B, L.uR, TB_RNS_MODULI));
+        }
         if (L.lazy) {
             // only the blocks of SWEEP_SP columns on the diagonal of S = R U^T, into L.P
             for (int s0 = 0; s0 < n; s0 += SWEEP_SP) {
@@ -1340,6 +1443,12 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                 a.C = L.P + o; a.ldc = n; a.batch = nhin; a.strideA = nn; a.strideB = nn; a.strideC = nn; a.tag = TBOA_PROF_F64_FACTOR;
                 TB_TRY(gemm_f64(ctx, a));
             }
+        } else if (L.rns & RNS_P) {
+            RnsSource r = rows_of(L.Rd, n, n, n);
+            r.kexp = L.kexp; r.ksign = -1;
+            TB_TRY(rns_products(L, 1, r, RNS_BITS_A, TB_RNS_MODULI, {{&L.uR, L.Hfac, 0, 1, 0, 1, TB_RNS_MODULI}}, TBOA_PROF_F64_FACTOR));      // U[c, k] = 0 for k < c; only above the diagonal
+            TB_TRY(rns_u_columns(L, false));
+            TB_TRY(rns_products(L, 1, rows_of(L.Hfac, n, n, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.uC, L.P, 1, 0, 1, 1, TB_RNS_MODULI}}, TBOA_PROF_F64_FACTOR));
         } else {
             GemmF64 a{};
             a.M = n; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0;
@@ -1359,6 +1468,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             TB_TRY(gemm_f64(ctx, b));
         }
     }
+    if (L.pC.p || (L.uC.p && !(R && (L.rns & RNS_P)))) TB_TRY(rns_u_columns(L, L.pC.p != nullptr));
     if (H_out) {
         TB_TRY(launch_f32_to_f64_damp(ctx, dh, nh, H_out, d->damp, L.Ho));
         TB_HIP(ctx, hipMemcpyAsync(L.Hofac, L.Ho, (size_t)nh * dh * dh * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
@@ -1418,6 +1528,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                     TB_TRY(pair_gemm(L, nbr, n - s1, s1 - s0, 0, (long long)s0 * n + s1, L.Rd, s1, L.nr));
                     continue;
                 }
+                if ((L.rns & RNS_SWEEP) && s1 - s0 == SWEEP_SP) { TB_TRY(rns_sweep_update(L, rows, s0, s1, Pp != nullptr)); continue; }
                 GemmF64 two{};
                 if (Pp) { two.A2 = L.Wsnap; two.B2 = L.P + (long long)s0 * n + s1; }
                 TB_TRY(block_gemm(L, nbr, n - s1, s1 - s0, -1.0, L.Epan, SWEEP_SP, L.Uin, (long long)s0 * n + s1, n, 1, 1.0, L.Wk + s1, n,
@@ -1426,7 +1537,14 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         }
         if (H_out && i1 < dh) {
             const double* S3 = nullptr;
-            if (R) {   // W_B R H_in^-1 = ((W_B R) U^T) U
+            if (R && (L.rns & RNS_COMP)) {   // W_B R H_in^-1 = ((W_B R) U^T) U
+                RnsSource s1 = rows_of(L.S1, n, rows, n);
+                s1.kexp = L.kexp; s1.ksign = -1;
+                TB_TRY(rns_products(L, 0, rows_of(L.Wb, n, rows, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.rC, L.S1, 0, 0, 0, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, s1, RNS_BITS_A, TB_RNS_MODULI, {{&L.uR, L.S2, 0, 1, 0, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, rows_of(L.S2, n, rows, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.uC, L.S1, 0, 0, 1, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
+                S3 = L.S1;
+            } else if (R) {
                 GemmF64 f1{}; f1.klo_n = 1;
                 GemmF64 f2{}; f2.khi_n = 1;
                 TB_TRY(block_gemm(L, nbr, n, n, 1.0, L.Wb, n, L.Rd, 0, n, 1, 0.0, L.S1, n, TBOA_PROF_F64_COMP));
@@ -1456,12 +1574,21 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     GemmF64 half{}; half.sym = 1;
     hipLaunchKernelGGL(wbar_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, codes, L.z64, ng, L.gsz, n, L.Wbar);
     TB_KERNEL_CHECK(ctx);
-    if (R) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Rd, 0, n, 1, 0.0, L.WR, n, TBOA_PROF_F64_CD));
+    // with products of residues W R and W H_in share the left operand; without groups H_in enters as its half T in either form (see below)
+    const int half_range = d->group ? 0 : 1, nm_int = rns_moduli(log2(L.maxq * sqrt((double)n)) + RNS_BITS_B);
+    const bool rns = L.rns & RNS_REFINE;
+    if (rns) {
+        const RnsProduct wr{&L.rC, L.WR, 0, 0, 0, 0, TB_RNS_MODULI}, wh{&L.hT, L.Z, 0, 0, half_range, 0, TB_RNS_MODULI};
+        const RnsSource w = rows_of(L.W64, n, rows_all, n);
+        if (R && d->cd_iters > 0) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wr, wh}, TBOA_PROF_F64_CD));
+        else if (R) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wr}, TBOA_PROF_F64_CD));
+        else if (d->cd_iters > 0) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wh}, TBOA_PROF_F64_CD));
+    } else if (R) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Rd, 0, n, 1, 0.0, L.WR, n, TBOA_PROF_F64_CD));
     if (d->cd_iters > 0 && d->group) {
         // Z = W (H_in - R); per group g: AH = Wbar[:, G] H_in[G, :] (into Abar), then the Gram blocks against every group
         const int gsz = L.gsz;
         const long long rr = (long long)dh * dh;
-        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD));
+        if (!rns) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD));
         if (R) TB_TRY(launch_sub_f64(ctx, L.Z, L.WR, L.Z, wn));
         if (H_out) {
             GemmF64 f{};   // Fg[h][g] = Wbar_h[:, G] Z_h[:, G]^T
@@ -1514,8 +1641,11 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         TB_KERNEL_CHECK(ctx);
     } else if (d->cd_iters > 0) {
         // H_in is symmetric and its products only go into symmetric forms: half products A = Wbar T and Z = W T, T + T^T = 2 H_in
-        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
-        TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD, &half));
+        if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), -1, nm_int, {{&L.hT, L.Abar, 0, 0, 1, 0, nm_int}}, TBOA_PROF_F64_CD));
+        else {
+            TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
+            TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD, &half));
+        }
         if (H_out) {
             GemmF64 c{};
             c.M = dh; c.N = dh; c.K = n; c.alpha = 1.0; c.beta = 0.0;
@@ -1545,7 +1675,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         if (d->cd_iters > 0 && !d->group) {   // Abar = Wbar T and Z = W T are still those of the scale refinement
             hipLaunchKernelGGL(dh_from_products_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, L.Abar, L.s64, L.Z, n);
             TB_KERNEL_CHECK(ctx);
-        } else TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
+        } else if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.hT, L.Abar, 0, 0, half_range, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_CD));
+        else TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
         double* lq = L.lossbuf; double* lc = L.lossbuf + nh;
         TB_TRY(launch_fill_f64(ctx, L.lossbuf, 2 * nh, 0.0));
         if (H_out) {
@@ -1618,6 +1749,53 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     return 0;
 }
 
+// right operands that a choice of products needs
+struct RnsNeeds { bool hT, rC, uR, uC, pC; };
+RnsNeeds rns_needs(int products, bool R) {
+    return {(products & (RNS_REFINE | RNS_EXACT)) != 0, R && (products & (RNS_REFINE | RNS_COMP)), R && (products & (RNS_P | RNS_COMP)),
+            (products & RNS_SWEEP) || (R && (products & (RNS_P | RNS_COMP))), R && (products & RNS_SWEEP)};
+}
+
+// Which products go to the integer matrix cores: the choice of least modelled time over both forms of every kind and the right operands that it needs (gemm_f64_model_us,
+// rns_model_us).  Per-head Hessians keep fp64: their products have the rows of one head, which the preparation of d_in x d_in operands does not repay.
+int rns_choice(const Layer& L, bool H_out, bool R) {
+    const tboa_layer_desc* d = L.d;
+    const int n = L.n, rows = d->d_out;
+    if (L.nhin > 1 || n < SWEEP_SP || n > 32768) return 0;
+    const int blk = d->block < L.dh ? d->block : L.dh, steps = (L.dh + blk - 1) / blk, step_rows = L.nh * blk;
+    const double half = d->group ? 1.0 : 0.5;      // of a product with H_in
+    const int nm_int = rns_moduli(log2(L.maxq * sqrt((double)n)) + RNS_BITS_B), all = TB_RNS_MODULI;
+    auto fp64 = [](int M, int N, int K) { return 1.15 * gemm_f64_model_us(M, N, K); };      // (one launch among others: 332 us for 2048^3, where the steps alone are 269)
+    auto rns = [&](int M, int N, int K, bool tri, bool beta = false, int nm = TB_RNS_MODULI) {
+        double us = 0.0;
+        for (int r = 0; r < M; r += 8192) us += rns_model_us(std::min(8192, M - r), N, K, tri, beta, nm);
+        return us;
+    };
+    double gain[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (R) gain[0] += fp64(rows, n, n) - rns(rows, n, n, false);
+    if (d->cd_iters > 0) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, !d->group) + rns_prepare_us(rows, n) * (R ? 1.0 : 0.0);
+    if (d->cd_iters > 0 && !d->group) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, true, false, nm_int);
+    if (d->cd_iters == 0 || d->group) gain[0] += 0.5 * fp64(rows, n, n) - rns(rows, n, n, !d->group);
+    if (L.fast_grid) {      // about one and a half exact costs a row
+        const int at_once = std::min(step_rows, L.fast_chunk), m = std::max(1, at_once * 3 / 2);
+        gain[1] = (double)steps * step_rows / at_once * (0.5 * fp64(m, n, n) - rns_model_us(m, n, n, true, false, all));
+    }
+    if (R && !L.lazy) gain[2] = fp64(n, n, n) - 2.0 * rns(n, n, n, true);
+    if (R && H_out) gain[3] = (steps - 1) * (2.0 * fp64(step_rows, n, n) - rns(step_rows, n, n, false) - 2.0 * rns(step_rows, n, n, true));
+    const bool whole_groups = !d->group || SWEEP_SP % L.gsz == 0 || L.gsz % SWEEP_SP == 0;
+    if (!L.lazy && whole_groups)
+        for (int s1 = SWEEP_SP; s1 < n; s1 += SWEEP_SP) gain[4] += steps * (fp64(step_rows, n - s1, (R ? 2 : 1) * SWEEP_SP) - rns(step_rows, n - s1, (R ? 2 : 1) * SWEEP_SP, false, true));
+    int best = 0; double most = 150.0;      // us: what the model does not tell apart
+    for (int c = 1; c < 32; ++c) {
+        if (((c & RNS_P) && (!R || L.lazy)) || ((c & RNS_COMP) && !(R && H_out)) || ((c & RNS_EXACT) && !L.fast_grid) || ((c & RNS_SWEEP) && (L.lazy || !whole_groups))) continue;
+        const RnsNeeds need = rns_needs(c, R);
+        double g = -(need.hT + need.rC + need.uR + need.uC + need.pC + ((c & RNS_P) && need.pC ? 1 : 0)) * (rns_prepare_us(n, n) + 8.0);
+        for (int k = 0; k < 5; ++k) if (c >> k & 1) g += gain[k];
+        if (g > most) { most = g; best = c; }
+    }
+    return best;
+}
+
 // The workspace of a quantize_layer call, carved from `ar` (base == nullptr: only counted).
 void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     const tboa_layer_desc* d = L.d;
@@ -1678,6 +1856,29 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.WR = R ? ar.get<double>(wn) : nullptr;
     L.Cm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr; L.Fm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr;
     L.dvec = ar.get<double>(2 * (size_t)d->d_out); L.lossbuf = ar.get<double>(2 * (size_t)nh);
+    L.rns = rns_choice(L, H_out, R);
+    if (L.rns) {
+        const size_t cap = L.fast_grid ? (size_t)L.fast_chunk * GRID_KS : 0;
+        auto operand = [&](int rows, int k, bool exps) {
+            RnsOperand o{};
+            o.kpad = rns_pad(k); o.plane = rns_plane(rows, k); o.p = ar.get<signed char>(TB_RNS_MODULI * o.plane); o.e = exps ? ar.get<int>(rows) : nullptr;
+            return o;
+        };
+        const RnsNeeds need = rns_needs(L.rns, R);
+        const bool aux = R && (L.rns & RNS_P);
+        L.rns_rows_max = (int)std::max<size_t>((std::min(d->d_out, 8192) + 255) / 256 * 256, (L.rns & RNS_EXACT) ? (cap + 255) / 256 * 256 : 0);
+        const int aux_rows = std::min((n + 255) / 256 * 256, L.rns_rows_max);
+        if (need.hT) L.hT = operand(n, n, true);
+        if (need.rC) L.rC = operand(n, n, true);
+        if (need.uR) L.uR = operand(n, n, true);
+        if (need.uC) L.uC = operand(n, n, true);
+        if (need.pC) { L.pC = operand(n, n, false); L.pC.e = L.uC.e; }
+        L.left[0] = operand(L.rns_rows_max, std::max(n, 2 * SWEEP_SP), true);
+        L.rres[0] = ar.get<unsigned char>(rns_residue_bytes(L.rns_rows_max, n, 1, TB_RNS_MODULI));
+        if (aux) { L.left[1] = operand(aux_rows, n, true); L.rres[1] = ar.get<unsigned char>(rns_residue_bytes(aux_rows, n, 1, TB_RNS_MODULI)); }
+        L.rsq = ar.get<double>(rns_squares_elems(n)); L.rsq2 = ar.get<double>(rns_squares_elems(n)); L.rpart = ar.get<double>(RNS_CHUNKS * rns_squares_elems(n));
+        L.kexp = ar.get<int>(n); L.pshift = ar.get<int>(1);
+    }
     L.Cg = L.Fg = L.cdnum = nullptr;
     if (d->group && d->cd_iters > 0) {
         const size_t ng = (size_t)L.ng;
