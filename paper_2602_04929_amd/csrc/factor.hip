@@ -6,6 +6,7 @@
 // fp64: diagonal blocks are factored and inverted inside LDS by one workgroup per matrix, the panel and trailing
 // updates are fp64-MFMA GEMMs batched over the matrices (the per-head Hessians of W_V factor in lockstep).
 #include "internal.h"
+#include <algorithm>
 
 namespace {
 
@@ -216,41 +217,157 @@ int chol_status_f64(tboa_ctx* ctx, int status_slot) {
     return 0;
 }
 
-int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H, double* U, double* tmp, double* dinv, int status_slot, bool defer_status) {
+// Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores
+static bool chol_rns_pays(int n, int batch) { return n >= 2048 && (long long)n * n * batch >= 3072LL * 3072; }
+
+void chol_rns_plan(int n, int batch, Arena& ar, CholRns& w) {
+    w = CholRns{};
+    if (!chol_rns_pays(n, batch)) return;
+    auto operand = [&]() {
+        RnsOperand o{};
+        o.kpad = rns_pad(n); o.plane = rns_plane(n, n); o.stride = (long long)(TB_RNS_MODULI * o.plane); o.p = ar.get<signed char>(TB_RNS_MODULI * o.plane * batch);
+        o.e = ar.get<int>((size_t)n * batch); o.e_stride = n;
+        return o;
+    };
+    w.V = operand(); w.U = operand();
+    w.res = ar.get<unsigned char>(rns_residue_bytes(n, TB_FACT_OB, batch, TB_RNS_MODULI));
+    w.sq = ar.get<double>(rns_squares_elems(n) * batch); w.panel = ar.get<double>(rns_squares_elems(n) * batch);
+    w.part = ar.get<double>(RNS_CHUNKS * rns_squares_elems(n) * batch); w.grown = ar.get<int>((size_t)n * batch);
+    if (!ar.base) w.V.p = nullptr;
+}
+
+// The columns J0 .. J1 of V: diagonal blocks of NB columns, the panels above them, and their updates of the other columns of the same outer block
+static int factor_columns(tboa_ctx* ctx, int n, int batch, double* H, double* dinv, int J0, int J1, int* status) {
+    const int nblk = (n + NB - 1) / NB;
+    const long long nn = (long long)n * n, dstride = (long long)nblk * NB * NB;
+    for (int blk = (J1 + NB - 1) / NB - 1; blk >= J0 / NB; --blk) {
+        const int j0 = blk * NB, bs = (n - j0 < NB) ? n - j0 : NB;
+        hipLaunchKernelGGL(diag_factor_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, n, j0, bs, dinv, blk, nblk, status);
+        TB_KERNEL_CHECK(ctx);
+        if (j0 == 0) break;
+        // panel: V[0:j0, blk] = H[0:j0, blk] Vinv_jj^T   (in place: one column tile, each workgroup owns its rows)
+        GemmF64 p{};
+        p.M = j0; p.N = bs; p.K = bs; p.alpha = 1.0; p.beta = 0.0;
+        p.A = H + j0; p.sam = n; p.sak = 1;
+        p.B = dinv + (long long)blk * NB * NB; p.sbk = 1; p.sbn = NB;
+        p.C = H + j0; p.ldc = n;
+        p.batch = batch; p.strideA = nn; p.strideB = dstride; p.strideC = nn;
+        TB_TRY(gemm_f64(ctx, p));
+        if (j0 > J0) {   // inside the outer block: H[0:j0, J0:j0] -= V[0:j0, blk] V[J0:j0, blk]^T  (upper part)
+            GemmF64 s{};
+            s.M = j0; s.N = j0 - J0; s.K = bs; s.alpha = -1.0; s.beta = 1.0;
+            s.A = H + j0; s.sam = n; s.sak = 1;
+            s.B = H + (long long)J0 * n + j0; s.sbk = 1; s.sbn = n;
+            s.C = H + J0; s.ldc = n; s.skip_lower = 1; s.skip_col0 = J0;
+            s.batch = batch; s.strideA = nn; s.strideB = nn; s.strideC = nn;
+            TB_TRY(gemm_f64(ctx, s));
+        }
+    }
+    return 0;
+}
+
+// The inverses of the diagonal blocks of V of OB columns, U[J0:J1, J0:J1], from those of their NB columns (placed in U): blocks [ob, ob + count) of full width side by side
+static int invert_diagonal_blocks(tboa_ctx* ctx, int n, int batch, const double* H, double* U, double* tmp, const double* dinv, int ob, int count) {
+    constexpr int OB = TB_FACT_OB;
+    const int nblk = (n + NB - 1) / NB, J0 = ob * OB, J1 = std::min(n, J0 + OB), TL = chol_tmp_pitch(n);
+    const long long nn = (long long)n * n, dstride = (long long)nblk * NB * NB, step = (long long)OB * (n + 1);
+    for (int blk = J0 / NB + 1; blk <= (J1 + NB - 1) / NB - 1; ++blk) {   // U[J0:j0, blk]
+        const int j0 = blk * NB, bs = (n - j0 < NB) ? n - j0 : NB, m = j0 - J0;
+        GemmF64 a{};   // tmp = U[J0:j0, J0:j0] V[J0:j0, blk]
+        a.M = m; a.N = bs; a.K = m; a.alpha = 1.0; a.beta = 0.0;
+        a.A = U + (long long)J0 * (n + 1); a.sam = n; a.sak = 1; a.klo_m = 1;
+        a.B = H + (long long)J0 * n + j0; a.sbk = n; a.sbn = 1;
+        a.C = tmp + (long long)J0 * TL; a.ldc = TL;
+        a.batch = batch * count; a.batch_inner = count; a.strideA = nn; a.strideB = nn; a.strideC = (long long)n * TL;
+        a.strideA2 = step; a.strideB2 = step; a.strideC2 = (long long)OB * TL;
+        TB_TRY(gemm_f64(ctx, a));
+        GemmF64 c{};   // U[J0:j0, blk] = -tmp Vinv_jj
+        c.M = m; c.N = bs; c.K = bs; c.alpha = -1.0; c.beta = 0.0;
+        c.A = tmp + (long long)J0 * TL; c.sam = TL; c.sak = 1;
+        c.B = dinv + (long long)blk * NB * NB; c.sbk = NB; c.sbn = 1;
+        c.C = U + (long long)J0 * n + j0; c.ldc = n;
+        c.batch = batch * count; c.batch_inner = count; c.strideA = (long long)n * TL; c.strideB = dstride; c.strideC = nn;
+        c.strideA2 = (long long)OB * TL; c.strideB2 = (long long)(OB / NB) * NB * NB; c.strideC2 = step;
+        TB_TRY(gemm_f64(ctx, c));
+    }
+    return 0;
+}
+
+// With products of residues (CholRns).  They take contractions of any length at 100 - 140 TFLOP/s but write and read 15 bytes per result, so that every block of 512 columns gets ONE
+// update over all columns behind it (right-looking updates of 512 terms each run no faster than in fp64: 1.15 ms for 8192 x 8192 x 512 either way):
+//     V: H[0:J1, J0:J1] -= V[0:J1, J1:n] V[J0:J1, J1:n]^T, the rows of V in residues once, their norms known from H's diagonal
+//     U: U[ob, J1:n] = -U[ob, ob] (V[ob, J1:n] U[J1:n, J1:n]), from the last rows up; the columns of U in residues as they grow
+static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, double* tmp, double* dinv, int* status, const CholRns& w) {
+    constexpr int OB = TB_FACT_OB;
+    const int nblk = (n + NB - 1) / NB, nob = (n + OB - 1) / OB, TL = chol_tmp_pitch(n);
+    const long long nn = (long long)n * n;
+    TB_TRY(rns_diagonal_exps(ctx, n, batch, H, RNS_BITS_A, w.V.e));
+    RnsGemm g{};
+    g.batch = batch; g.nm = TB_RNS_MODULI; g.residues = w.res;
+    for (int ob = nob - 1; ob >= 0; --ob) {
+        const int J0 = ob * OB, J1 = std::min(n, J0 + OB);
+        if (J1 < n) {
+            g.A = &w.V; g.B = &w.V; g.a_row = 0; g.b_row = J0; g.a_k = g.b_k = J1; g.M = J1; g.N = J1 - J0; g.K = n - J1;
+            g.alpha = -1.0; g.beta = 1.0; g.C = H + J0; g.ldc = n; g.strideC = nn;
+            TB_TRY(rns_gemm(ctx, g));
+        }
+        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status));
+        if (J0 > 0) {
+            RnsSource v{};
+            v.a = H + J0; v.ld = n; v.stride = nn; v.kc = 1; v.rows = J0; v.k = J1 - J0;
+            TB_TRY(rns_rows(ctx, v, nullptr, batch, RNS_GIVEN, w.V, TB_RNS_MODULI, J0));
+        }
+    }
+    TB_TRY(launch_fill_f64(ctx, U, (int64_t)batch * nn, 0.0));
+    hipLaunchKernelGGL(place_diag_inverse_kernel, dim3(nblk, batch), dim3(256), 0, ctx->stream, U, n, dinv, nblk);
+    TB_KERNEL_CHECK(ctx);
+    const int whole = n / OB;
+    TB_TRY(invert_diagonal_blocks(ctx, n, batch, H, U, tmp, dinv, 0, whole));
+    if (whole < nob) TB_TRY(invert_diagonal_blocks(ctx, n, batch, H, U, tmp, dinv, whole, 1));
+    for (int ob = nob - 1; ob >= 0; --ob) {
+        const int J0 = ob * OB, J1 = std::min(n, J0 + OB), width = J1 - J0;
+        if (J1 < n) {
+            // tmp = V[ob, J1:n] U[J1:n, J1:n]; transposed room: width x (n - J1) of tmp's n x TL
+            g.A = &w.V; g.B = &w.U; g.a_row = J0; g.b_row = J1; g.a_k = g.b_k = J1; g.M = width; g.N = n - J1; g.K = n - J1; g.khi_n = 1;
+            g.alpha = 1.0; g.beta = 0.0; g.C = tmp; g.ldc = n - J1; g.strideC = (long long)n * TL;
+            TB_TRY(rns_gemm(ctx, g));
+            GemmF64 c{};   // U[ob, J1:n] = -U[ob, ob] tmp   (U[ob, ob] upper: k >= row)
+            c.M = width; c.N = n - J1; c.K = width; c.alpha = -1.0; c.beta = 0.0; c.klo_m = 1;
+            c.A = U + (long long)J0 * (n + 1); c.sam = n; c.sak = 1;
+            c.B = tmp; c.sbk = n - J1; c.sbn = 1;
+            c.C = U + (long long)J0 * n + J1; c.ldc = n;
+            c.batch = batch; c.strideA = nn; c.strideB = (long long)n * TL; c.strideC = nn;
+            TB_TRY(gemm_f64(ctx, c));
+        }
+        if (J0 == 0) break;
+        RnsSource p{};      // the new rows, of the columns J0 ..
+        p.a = U + (long long)J0 * (n + 1); p.ld = n; p.stride = nn; p.rows = n - J0; p.k = width;
+        TB_TRY(rns_norms(ctx, p, batch, w.panel, 3LL * n, w.part));
+        TB_TRY(rns_grow(ctx, n - J0, batch, w.panel, 3LL * n, w.sq + J0, n, 3LL * n, width, RNS_BITS_B, w.U.e + J0, n, w.grown + J0));
+        RnsOperand u = w.U;
+        u.p += (long long)(J0 >> 4) * u.kpad * 16; u.e += J0;
+        p.k = n - J0;
+        TB_TRY(rns_columns(ctx, p, batch, u, J0, TB_RNS_MODULI, w.grown + J0, width));
+    }
+    return 0;
+}
+
+int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H, double* U, double* tmp, double* dinv, int status_slot, bool defer_status, const CholRns* rns) {
     int* status = ctx->d_status + status_slot;
-    constexpr int OB = TB_FACT_OB, IPB = OB / NB;
+    constexpr int OB = TB_FACT_OB;
     const int nblk = (n + NB - 1) / NB, nob = (n + OB - 1) / OB;
     const int TL = chol_tmp_pitch(n);     // row pitch of tmp: a matrix of one outer block only ever holds NB columns there
-    const long long nn = (long long)n * n, dstride = (long long)nblk * NB * NB;
+    const long long nn = (long long)n * n;
     hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, ctx->stream, status);
     TB_KERNEL_CHECK(ctx);
+    if (rns && rns->V.p) {
+        TB_TRY(chol_inv_rns(ctx, n, batch, H, U, tmp, dinv, status, *rns));
+        return defer_status ? 0 : chol_status_f64(ctx, status_slot);
+    }
     // ---- H = V V^T from the last column to the first
     for (int ob = nob - 1; ob >= 0; --ob) {
         const int J0 = ob * OB, J1 = (J0 + OB < n) ? J0 + OB : n;
-        const int blk_hi = (J1 + NB - 1) / NB - 1, blk_lo = ob * IPB;
-        for (int blk = blk_hi; blk >= blk_lo; --blk) {
-            const int j0 = blk * NB, bs = (n - j0 < NB) ? n - j0 : NB;
-            hipLaunchKernelGGL(diag_factor_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, n, j0, bs, dinv, blk, nblk, status);
-            TB_KERNEL_CHECK(ctx);
-            if (j0 == 0) break;
-            // panel: V[0:j0, blk] = H[0:j0, blk] Vinv_jj^T   (in place: one column tile, each workgroup owns its rows)
-            GemmF64 p{};
-            p.M = j0; p.N = bs; p.K = bs; p.alpha = 1.0; p.beta = 0.0;
-            p.A = H + j0; p.sam = n; p.sak = 1;
-            p.B = dinv + (long long)blk * NB * NB; p.sbk = 1; p.sbn = NB;
-            p.C = H + j0; p.ldc = n;
-            p.batch = batch; p.strideA = nn; p.strideB = dstride; p.strideC = nn;
-            TB_TRY(gemm_f64(ctx, p));
-            if (j0 > J0) {   // inside the outer block: H[0:j0, J0:j0] -= V[0:j0, blk] V[J0:j0, blk]^T  (upper part)
-                GemmF64 s{};
-                s.M = j0; s.N = j0 - J0; s.K = bs; s.alpha = -1.0; s.beta = 1.0;
-                s.A = H + j0; s.sam = n; s.sak = 1;
-                s.B = H + (long long)J0 * n + j0; s.sbk = 1; s.sbn = n;
-                s.C = H + J0; s.ldc = n; s.skip_lower = 1; s.skip_col0 = J0;
-                s.batch = batch; s.strideA = nn; s.strideB = nn; s.strideC = nn;
-                TB_TRY(gemm_f64(ctx, s));
-            }
-        }
+        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status));
         if (J0 > 0) {   // H[0:J0, 0:J0] -= V[0:J0, ob] V[0:J0, ob]^T  (upper part)
             GemmF64 s{};
             s.M = J0; s.N = J0; s.K = J1 - J0; s.alpha = -1.0; s.beta = 1.0;
@@ -265,43 +382,25 @@ int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H, double* U, do
     TB_TRY(launch_fill_f64(ctx, U, (int64_t)batch * nn, 0.0));
     hipLaunchKernelGGL(place_diag_inverse_kernel, dim3(nblk, batch), dim3(256), 0, ctx->stream, U, n, dinv, nblk);
     TB_KERNEL_CHECK(ctx);
-    for (int ob = 0; ob < nob; ++ob) {
-        const int J0 = ob * OB, J1 = (J0 + OB < n) ? J0 + OB : n;
-        const int blk_hi = (J1 + NB - 1) / NB - 1, blk_lo = ob * IPB;
-        for (int blk = blk_lo + 1; blk <= blk_hi; ++blk) {   // the diagonal block of the outer block: U[J0:j0, blk]
-            const int j0 = blk * NB, bs = (n - j0 < NB) ? n - j0 : NB, m = j0 - J0;
-            GemmF64 a{};   // tmp = U[J0:j0, J0:j0] V[J0:j0, blk]
-            a.M = m; a.N = bs; a.K = m; a.alpha = 1.0; a.beta = 0.0;
-            a.A = U + (long long)J0 * n + J0; a.sam = n; a.sak = 1; a.klo_m = 1;
-            a.B = H + (long long)J0 * n + j0; a.sbk = n; a.sbn = 1;
-            a.C = tmp; a.ldc = TL;
-            a.batch = batch; a.strideA = nn; a.strideB = nn; a.strideC = (long long)n * TL;
-            TB_TRY(gemm_f64(ctx, a));
-            GemmF64 c{};   // U[J0:j0, blk] = -tmp Vinv_jj
-            c.M = m; c.N = bs; c.K = bs; c.alpha = -1.0; c.beta = 0.0;
-            c.A = tmp; c.sam = TL; c.sak = 1;
-            c.B = dinv + (long long)blk * NB * NB; c.sbk = NB; c.sbn = 1;
-            c.C = U + (long long)J0 * n + j0; c.ldc = n;
-            c.batch = batch; c.strideA = (long long)n * TL; c.strideB = dstride; c.strideC = nn;
-            TB_TRY(gemm_f64(ctx, c));
-        }
-        if (J0 > 0) {
-            const int w = J1 - J0;
-            GemmF64 a{};   // tmp = U[0:J0, 0:J0] V[0:J0, ob]
-            a.M = J0; a.N = w; a.K = J0; a.alpha = 1.0; a.beta = 0.0;
-            a.A = U; a.sam = n; a.sak = 1; a.klo_m = 1;
-            a.B = H + J0; a.sbk = n; a.sbn = 1;
-            a.C = tmp; a.ldc = TL;
-            a.batch = batch; a.strideA = nn; a.strideB = nn; a.strideC = (long long)n * TL;
-            TB_TRY(gemm_f64(ctx, a));
-            GemmF64 c{};   // U[0:J0, ob] = -tmp U[ob, ob]   (U[ob, ob] upper: k <= column)
-            c.M = J0; c.N = w; c.K = w; c.alpha = -1.0; c.beta = 0.0;
-            c.A = tmp; c.sam = TL; c.sak = 1;
-            c.B = U + (long long)J0 * n + J0; c.sbk = n; c.sbn = 1; c.khi_n = 1;
-            c.C = U + J0; c.ldc = n;
-            c.batch = batch; c.strideA = (long long)n * TL; c.strideB = nn; c.strideC = nn;
-            TB_TRY(gemm_f64(ctx, c));
-        }
+    const int whole = n / OB;
+    if (whole > 0) TB_TRY(invert_diagonal_blocks(ctx, n, batch, H, U, tmp, dinv, 0, whole));
+    if (whole < nob) TB_TRY(invert_diagonal_blocks(ctx, n, batch, H, U, tmp, dinv, whole, 1));
+    for (int ob = 1; ob < nob; ++ob) {
+        const int J0 = ob * OB, J1 = (J0 + OB < n) ? J0 + OB : n, w = J1 - J0;
+        GemmF64 a{};   // tmp = U[0:J0, 0:J0] V[0:J0, ob]
+        a.M = J0; a.N = w; a.K = J0; a.alpha = 1.0; a.beta = 0.0;
+        a.A = U; a.sam = n; a.sak = 1; a.klo_m = 1;
+        a.B = H + J0; a.sbk = n; a.sbn = 1;
+        a.C = tmp; a.ldc = TL;
+        a.batch = batch; a.strideA = nn; a.strideB = nn; a.strideC = (long long)n * TL;
+        TB_TRY(gemm_f64(ctx, a));
+        GemmF64 c{};   // U[0:J0, ob] = -tmp U[ob, ob]   (U[ob, ob] upper: k <= column)
+        c.M = J0; c.N = w; c.K = w; c.alpha = -1.0; c.beta = 0.0;
+        c.A = tmp; c.sam = TL; c.sak = 1;
+        c.B = U + (long long)J0 * n + J0; c.sbk = n; c.sbn = 1; c.khi_n = 1;
+        c.C = U + J0; c.ldc = n;
+        c.batch = batch; c.strideA = (long long)n * TL; c.strideB = nn; c.strideC = nn;
+        TB_TRY(gemm_f64(ctx, c));
     }
     return defer_status ? 0 : chol_status_f64(ctx, status_slot);
 }
@@ -316,9 +415,11 @@ extern "C" int tboa_chol_inv_upper(tboa_ctx* ctx, int n, int batch, const float*
         double* H64 = ar.get<double>((size_t)batch * n * n);
         double* tmp = ar.get<double>((size_t)batch * n * chol_tmp_pitch(n));
         double* dinv = ar.get<double>((size_t)batch * nblk * NB * NB);
+        CholRns rns;
+        chol_rns_plan(n, batch, ar, rns);
         if (!pass) { TB_TRY(tboa_ws_reserve(ctx, ar.off)); continue; }
         TB_TRY(launch_f32_to_f64_damp(ctx, n, batch, H, damp, H64));
-        TB_TRY(chol_inv_upper_f64(ctx, n, batch, H64, U, tmp, dinv));
+        TB_TRY(chol_inv_upper_f64(ctx, n, batch, H64, U, tmp, dinv, 0, false, &rns));
     }
     return 0;
 }

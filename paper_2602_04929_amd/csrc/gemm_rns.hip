@@ -121,6 +121,30 @@ __global__ __launch_bounds__(1024) void rns_balance_kernel(int rows, double* __r
     }
 }
 
+// Columns that are completed panel by panel: sq += the panel's squares; a column that has outgrown its power of two gets one with room for twice its norm, and is marked
+__global__ __launch_bounds__(256) void rns_grow_kernel(int rows, const double* __restrict__ panel, long long panel_stride, double* __restrict__ sq, int sq_rows, long long sq_stride, int fresh_below,
+                                                       int bits, int* __restrict__ e, long long e_stride, int* __restrict__ grown) {
+    const int r = blockIdx.x * 256 + threadIdx.x;
+    if (r >= rows) return;
+    const double* p = panel + blockIdx.z * panel_stride + r;
+    double* q = sq + blockIdx.z * sq_stride + r;
+    const bool fresh = r < fresh_below;      // the panel's own columns begin here
+    double v[3];
+    for (int c = 0; c < 3; ++c) { v[c] = p[(long long)c * rows] + (fresh ? 0.0 : q[(long long)c * sq_rows]); q[(long long)c * sq_rows] = v[c]; }
+    int* ep = e + blockIdx.z * e_stride + r;
+    const int now = row_exponent(v[0], v[1], v[2], bits), had = *ep;
+    const bool more = fresh || now > had;      // (UNDEFINED is the largest)
+    if (more) *ep = fresh || now == UNDEFINED ? now : now + 1;
+    grown[blockIdx.z * e_stride + r] = more && !fresh;
+}
+// powers of two of the rows of V, H = V V^T: a row's norm is the root of H's diagonal entry
+__global__ __launch_bounds__(256) void rns_diagonal_exps_kernel(int n, const double* __restrict__ H, long long stride, int bits, int* __restrict__ e, long long e_stride) {
+    const int r = blockIdx.x * 256 + threadIdx.x;
+    if (r >= n) return;
+    const double v = H[blockIdx.z * stride + (long long)r * (n + 1)];
+    e[blockIdx.z * e_stride + r] = v > 0.0 ? row_exponent(v, 0.0, 0.0, bits) : v == v ? 0 : UNDEFINED;
+}
+
 struct Moduli { float inv[NMAX]; int m[NMAX]; };
 struct Residue { double inv[NMAX], c[NMAX]; int m[NMAX], ci[NMAX]; };      // c = 2^29 mod m, centred
 
@@ -155,9 +179,10 @@ __device__ __forceinline__ void store_residues(const double (&x)[16], int nm, co
 // Row-contiguous source, exponents given: a wavefront makes one block of 16 rows x 64 contraction indices of every plane.  Bound by memory: 8 bytes read and 15 written per
 // element, 8192 x 8192 in 0.35 ms.
 __global__ __launch_bounds__(256) void rns_columns_kernel(RnsSource s, const int* __restrict__ exps, long long e_stride, int nm, Residue q, signed char* __restrict__ out,
-                                                          long long plane, long long out_stride, int kpad, int koff, int kblocks) {
+                                                          long long plane, long long out_stride, int kpad, int koff, int kblocks, const int* __restrict__ grown, int kpanel) {
     const int lane = threadIdx.x & 63, kb = blockIdx.x * 4 + (threadIdx.x >> 6), r0 = blockIdx.y * 16;
     if (kb >= kblocks) return;
+    if (grown && kb >= kpanel && !__any(r0 + (lane & 15) < s.rows && grown[blockIdx.z * e_stride + r0 + (lane & 15)])) return;      // beyond the panel only rows of a new power of two
     const int ri = lane & 15, piece = lane >> 4, r = r0 + ri, k0 = kb * SK + 16 * piece, shift = shift_of(s);
     const double* a = s.a + blockIdx.z * s.stride + r;
     const int e = r < s.rows ? exps[blockIdx.z * e_stride + r] : UNDEFINED;
@@ -197,7 +222,7 @@ __global__ __launch_bounds__(256) void rns_row_exps_kernel(RnsSource s0, RnsSour
 // wavefront's own part) to 16 consecutive elements a lane; read that way from memory each lane would walk a line of its own.  exps null: small integers as they are.
 constexpr int ROW_PITCH = 66;
 __global__ __launch_bounds__(256) void rns_rows_kernel(RnsSource s0, RnsSource s1, const int* __restrict__ exps, long long e_stride, int nm, Residue q, signed char* __restrict__ out,
-                                                       long long plane, long long out_stride, int kpad, int kblocks0, int kblocks1) {
+                                                       long long plane, long long out_stride, int kpad, int koff, int kblocks0, int kblocks1) {
     __shared__ __attribute__((aligned(16))) double lds[4][16 * ROW_PITCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r0 = blockIdx.y * 16, kb = blockIdx.x * 4 + wave;
     if (kb >= kblocks0 + kblocks1 || (s0.row_limit && r0 >= s0.row_limit[0])) return;
@@ -226,7 +251,7 @@ __global__ __launch_bounds__(256) void rns_rows_kernel(RnsSource s0, RnsSource s
     double x[16];
 #pragma unroll
     for (int i = 0; i < 8; ++i) { const double2 v = *(const double2*)(mine + ri * ROW_PITCH + 16 * piece + 2 * i); x[2 * i] = v.x; x[2 * i + 1] = v.y; }
-    store_residues(x, nm, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
+    store_residues(x, nm, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + (koff >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
 }
 
 // ---------------------------------------------------------------------------------------------- the product
@@ -505,6 +530,18 @@ int rns_norms(tboa_ctx* ctx, const RnsSource& s, int batch, double* sq, long lon
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
+int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long panel_stride, double* sq, int sq_rows, long long sq_stride, int fresh_below, int bits, int* e, long long e_stride,
+             int* grown) {
+    hipLaunchKernelGGL(rns_grow_kernel, dim3((unsigned)cdiv64(rows, 256), 1, batch), dim3(256), 0, ctx->stream, rows, panel, panel_stride, sq, sq_rows, sq_stride, fresh_below, bits, e, e_stride,
+                       grown);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
+int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e) {
+    hipLaunchKernelGGL(rns_diagonal_exps_kernel, dim3((unsigned)cdiv64(n, 256), 1, batch), dim3(256), 0, ctx->stream, n, H, (long long)n * n, bits, e, (long long)n);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
 int rns_balance(tboa_ctx* ctx, int rows, double* sq1, const double* sq2, int* f) {
     hipLaunchKernelGGL(rns_balance_kernel, dim3(1), dim3(1024), 0, ctx->stream, rows, sq1, sq2, f);
     TB_KERNEL_CHECK(ctx);
@@ -524,24 +561,24 @@ static Residue residue_constants() {
     }
     return q;
 }
-int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm) {
+int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm, const int* grown, int panel) {
     const int kblocks = (int)(std::min<int64_t>(rns_pad(s.k), o.kpad - koff) / SK);
     const unsigned rb = (unsigned)cdiv64(s.rows, 16);
     if (s.kc || !o.e || koff % SK || kblocks * SK < s.k || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane) return tboa_fail(ctx, TBOA_EINVAL, "rns_columns: source does not fit the operand");
     hipLaunchKernelGGL(rns_columns_kernel, dim3((unsigned)cdiv64(kblocks, 4), rb, batch), dim3(256), 0, ctx->stream, s, o.e, o.e_stride, nm, residue_constants(), o.p, (long long)o.plane,
-                       o.stride, o.kpad, koff, kblocks);
+                       o.stride, o.kpad, koff, kblocks, grown, (panel + SK - 1) / SK);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
-int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm) {
+int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm, int koff) {
     const int kb0 = rns_pad(s.k) / SK, kb1 = second ? rns_pad(second->k) / SK : 0;
     const unsigned rb = (unsigned)cdiv64(s.rows, 16);
-    if (!s.kc || (second && (!second->kc || second->rows != s.rows || s.k % KPAD)) || (bits >= 0) != (o.e != nullptr) || (kb0 + kb1) * SK > o.kpad || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane)
+    if (!s.kc || (second && (!second->kc || second->rows != s.rows || s.k % KPAD)) || (bits >= 0 && !o.e) || (bits == RNS_INTEGERS && o.e) || koff % SK || koff + (kb0 + kb1) * SK > o.kpad || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane)
         return tboa_fail(ctx, TBOA_EINVAL, "rns_rows: source does not fit the operand");
     const RnsSource& s1 = second ? *second : s;
     if (bits >= 0) hipLaunchKernelGGL(rns_row_exps_kernel, dim3((unsigned)cdiv64(s.rows, 4), 1, batch), dim3(256), 0, ctx->stream, s, s1, second ? 1 : 0, bits, o.e, o.e_stride);
     hipLaunchKernelGGL(rns_rows_kernel, dim3((unsigned)cdiv64(kb0 + kb1, 4), rb, batch), dim3(256), 0, ctx->stream, s, s1, o.e, o.e_stride, nm, residue_constants(), o.p, (long long)o.plane,
-                       o.stride, o.kpad, kb0, kb1);
+                       o.stride, o.kpad, koff, kb0, kb1);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }

@@ -143,12 +143,19 @@ int rns_pad(int k);
 size_t rns_plane(int rows, int k);
 size_t rns_squares_elems(int rows);
 size_t rns_residue_bytes(int M, int N, int batch, int nm);
-// operand whose rows are contiguous (second: a second source right after the first along k): exponents, bits below the norm each (bits < 0: small integers as they are), and residues
-int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm);
+// operand whose rows are contiguous (second: a second source right after the first along k): exponents, `bits` below the norm each, and residues; bits RNS_INTEGERS: small
+// integers, taken as they are (no exponents); RNS_GIVEN: the operand's exponents stand already
+constexpr int RNS_INTEGERS = -1, RNS_GIVEN = -2;
+int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm, int koff = 0);
 // operand whose rows are strided: sums of squares, exponents, residues
 int rns_norms(tboa_ctx* ctx, const RnsSource& s, int batch, double* sq, long long sq_stride, double* part);
 int rns_exps(tboa_ctx* ctx, int rows, int batch, const double* sq, long long sq_stride, int bits, int* e, long long e_stride);
-int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm);
+int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm, const int* grown = nullptr, int panel = 0);
+// columns that grow by panels (of `rows` columns whose squares are `panel`; the first fresh_below of them begin with it): sq, exponents, and which have a new one; rns_columns
+// then makes the first `panel` indices of every row, the others of the rows that have grown
+int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long panel_stride, double* sq, int sq_rows, long long sq_stride, int fresh_below, int bits, int* e, long long e_stride,
+             int* grown);
+int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e);      // of the rows of V, H = V V^T
 int rns_balance(tboa_ctx* ctx, int rows, double* sq1, const double* sq2, int* f);
 int rns_gemm(tboa_ctx* ctx, const RnsGemm& q);
 double rns_model_us(int M, int N, int K, bool triangular, bool beta, int nm);
@@ -241,8 +248,11 @@ __device__ __forceinline__ long long tboa_blocked_offset(long long r, long long 
 static inline int chol_tmp_pitch(int n) { return n <= TB_FACT_OB ? TB_FACT_NB : TB_FACT_OB; }
 // status_slot: which pair of device status words records a breakdown (0 or 2); defer_status: do not wait for them here,
 // the caller checks with chol_status_f64 once the work has been joined.
+// rns: workspace of the form that takes the large updates to the integer matrix cores (chol_rns_plan; its V.p null: fp64 throughout).
+struct CholRns { RnsOperand V, U; unsigned char* res; double *sq, *panel, *part; int* grown; };
+void chol_rns_plan(int n, int batch, Arena& ar, CholRns& w);
 int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H64, double* U, double* tmp, double* dinv, int status_slot = 0,
-                       bool defer_status = false);
+                       bool defer_status = false, const CholRns* rns = nullptr);
 int chol_status_f64(tboa_ctx* ctx, int status_slot);
 int chol_static_init(int device);   // looks up the device address of the static scratch of tboa_chol_inv_upper_static (device current)
 int launch_f32_to_f64_damp(tboa_ctx* ctx, int n, int batch, const float* H, double damp, double* out);

@@ -1109,7 +1109,7 @@ struct Layer {
     // (0: main, 1: aux) the left operand of a product, residues of its result and sums of squares
     int rns, rns_rows_max;      // rns: which products (RNS_*); rns_rows_max: rows of a product at a time
     RnsOperand hT, uR, uC, pC, rC, left[2];      // H_in (its half T; group-wise: whole), rows of U, columns of U, columns of P, columns of R
-    unsigned char* rres[2]; double *rsq, *rsq2, *rpart; int *kexp, *pshift;
+    unsigned char* rres[2]; CholRns frns; double *rsq, *rsq2, *rpart; int *kexp, *pshift;
 };
 
 RnsSource rows_of(const double* a, long long ld, int rows, int k) {
@@ -1149,7 +1149,6 @@ int rns_u_columns(Layer& L, bool with_P) {
 }
 
 // Products of `rows` rows (contiguous, pitch lda) with prepared right operands, N = columns each: C = A B + beta C, at most rns_rows_max rows at a time.
-// bits < 0: rows of integers up to 2^int_bits in 2-norm.
 struct RnsProduct { const RnsOperand* B; double* C; int klo_m, klo_n, khi_n, upper, nm; };
 int rns_products(Layer& L, int which, const RnsSource& A, int bits, int nm_rows, std::initializer_list<RnsProduct> products, int tag) {
     tboa_ctx* ctx = L.ctx;
@@ -1157,7 +1156,7 @@ int rns_products(Layer& L, int which, const RnsSource& A, int bits, int nm_rows,
         RnsSource a = A;
         a.a += (long long)r0 * A.ld; a.rows = std::min(L.rns_rows_max, A.rows - r0);
         RnsOperand left = L.left[which];
-        if (bits < 0) left.e = nullptr;
+        if (bits == RNS_INTEGERS) left.e = nullptr;
         TB_TRY(rns_rows(ctx, a, nullptr, 1, bits, left, nm_rows));
         for (const RnsProduct& p : products) {
             RnsGemm g{};
@@ -1415,7 +1414,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     {
     StreamSwap swap(ctx);
     TB_HIP(ctx, hipStreamWaitEvent(ctx->aux, ctx->ev_fork, 0));
-    TB_TRY(chol_inv_upper_f64(ctx, n, nhin, L.Hfac, L.Uin, L.ftmp, L.fdinv, 0, true));
+    TB_TRY(chol_inv_upper_f64(ctx, n, nhin, L.Hfac, L.Uin, L.ftmp, L.fdinv, 0, true, &L.frns));
     // Algorithm 3 line 2: P = ((R U^T) * M_U) U.  Two products of d^3 / 3 flops each per H_in, which few rows do not repay (W_V of a grouped-query
     // block: 128 rows per 8192 x 8192 Hessian, 54 of its 176 ms).  L.lazy: the term that P carries from the columns j to a column k is
     //     sum_{j < k} w_j P[j, k] = sum_{m <= k} v_m U[m, k],    v_m = sum_{j < m} w_j S[j, m] = sum_{k >= m} U[m, k] sum_{j < m} w_j R[j, k],  S = R U^T
@@ -1641,7 +1640,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         TB_KERNEL_CHECK(ctx);
     } else if (d->cd_iters > 0) {
         // H_in is symmetric and its products only go into symmetric forms: half products A = Wbar T and Z = W T, T + T^T = 2 H_in
-        if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), -1, nm_int, {{&L.hT, L.Abar, 0, 0, 1, 0, nm_int}}, TBOA_PROF_F64_CD));
+        if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), RNS_INTEGERS, nm_int, {{&L.hT, L.Abar, 0, 0, 1, 0, nm_int}}, TBOA_PROF_F64_CD));
         else {
             TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
             TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD, &half));
@@ -1823,6 +1822,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     // the two factorisations (H_in: nhin matrices of order n; H_out: nh of order dh) share their temporaries
     const size_t t_in = (size_t)L.nhin * n * chol_tmp_pitch(n), t_out = H_out ? (size_t)nh * dh * chol_tmp_pitch(dh) : 0;
     L.ftmp = ar.get<double>(t_in > t_out ? t_in : t_out); L.fdinv = ar.get<double>((size_t)fb * nblk_f * TB_FACT_NB * TB_FACT_NB);
+    chol_rns_plan(n, L.nhin, ar, L.frns);
     L.Wb = ar.get<double>(brows * n); L.Wk = ar.get<double>(brows * n);
     L.Epan = ar.get<double>(brows * SWEEP_SP); L.Wsnap = ar.get<double>(brows * SWEEP_SP);
     L.E = H_out ? ar.get<double>(brows * n) : nullptr;
