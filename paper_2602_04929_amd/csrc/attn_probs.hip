@@ -16,7 +16,7 @@
 // both paths (segments k_hi, k_lo: 64 x d_h each) is copied global -> LDS block by block (a 16 x 32 block is 1 KB contiguous
 // in memory and lands as it is: its XOR-swizzled 16-byte pieces are what conflict-free fragment reads need), the copy of
 // the next tile running under the element-wise work on the current one.
-// With one score matrix only (attention forward, Hessians without the full-precision path; TWO false) the second path's buffers take the next 64
+// With one score matrix only (Hessians without the full-precision path; TWO false) the second path's buffers take the next 64
 // keys of the same matrix, a tile is 128 keys then, and the wavefronts of both paths share its queries: each walks the two halves of the tile one
 // after the other for 32 queries instead of one half for 64, so that a query's maximum and sum go through the same keys in the same order, and
 // come out the same to the bit, as with two matrices.  (Left idle the second path's were half of the wavefronts.)
@@ -46,13 +46,11 @@ __device__ __forceinline__ float dec16(bf16 b, int f16) {
 }
 
 constexpr int BT = 128;        // queries per workgroup
-// floats per row of the exchange buffer.  Transposed result: the two lane halves of a wavefront write rows 4 apart (4 x 136 = 32 banks
-// apart) and the store phase reads 16-byte pieces of a row; row-major result: the store phase reads columns, eight lanes taking rows 8
-// apart (8 x 137 = 8 banks apart), the other lanes consecutive queries
-template <bool ROWS> constexpr int exch_pitch() { return ROWS ? BT + 9 : BT + 8; }
+// floats per row of the exchange buffer: the two lane halves of a wavefront write rows 4 apart (4 x 136 = 32 banks apart) and the store phase reads 16-byte pieces of a row
+constexpr int EXP = BT + 8;
 
 template <int DH>
-constexpr int attn_lds_bytes() { return 4 * 64 * 2 * DH + 2 * 64 * (BT + 9) * 4 + 2 * 2 * 2 * BT * 4 + 2 * 2 * BT * 4; }
+constexpr int attn_lds_bytes() { return 4 * 64 * 2 * DH + 2 * 64 * EXP * 4 + 2 * 2 * 2 * BT * 4 + 2 * 2 * BT * 4; }
 
 // one 1 KB block global -> LDS: lane l moves the 16 bytes at base + voff (voff = 16 l) to lds_addr + 16 l
 __device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
@@ -62,7 +60,7 @@ __device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, u
 // 2^x on the transcendental unit
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-template <int DH, bool ROWS, bool TWO>
+template <int DH, bool TWO>
 __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restrict__ Qa, const bf16* __restrict__ Ka, const bf16* __restrict__ Qb,
                                                            const bf16* __restrict__ Kb, int L, int nheads, int rep, int xcd_runs, float scale2,
                                                            PtOut out, long long ldp, long long group_stride, int f16, QkScale qs) {
@@ -71,7 +69,6 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
     constexpr int SEGB = 64 * 2 * DH;            // bytes of one (path, segment) image: [NCB][64 keys][32 elements], pieces swizzled
     constexpr int KB = 3 * DH / 32;              // 16 x 32 blocks per block row of Q^ / K^
     constexpr int NBLK = 2 * 2 * NCB * 4;        // 1 KB blocks of a tile, both paths
-    constexpr int EXP = exch_pitch<ROWS>();
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     unsigned char* kt = smem;                                // [path][k_hi, k_lo][NCB][64 keys][64 bytes]
     float* ex = (float*)(smem + 4 * SEGB);                   // [path][64 keys][EXP]: probabilities of the tile
@@ -256,82 +253,59 @@ __global__ __launch_bounds__(512) void attn_probs_t_kernel(const bf16* __restric
             __syncthreads();                               // the tile has been read, its probabilities are in LDS
             if (it + 1 < live) issue(step * (it + 1));
         }
-        if constexpr (ROWS) {
-            // per-head result P[h][t][.] = [A_hi | A_lo | A~_hi | A~_lo] (segments of L columns), queries as rows: eight consecutive
-            // lanes take the 64 keys of one query, 8 each; two queries per thread
+        // transposed blocked result: sixteen consecutive lanes take the 128 queries of one key row, 8 each (one 16-byte piece per
+        // output), so that a wavefront store covers four key rows of four blocks, 256 contiguous bytes in each; two rows per thread
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int slot = threadIdx.x + 512 * half, i8 = slot & 7, tq2 = slot >> 3;
-                union { bf16 b[8]; uint4 u; } hi, lo, h2, l2;
+        for (int half = 0; half < 2; ++half) {
+            const int slot = threadIdx.x + 512 * half, t8 = slot & 15, ri = slot >> 4;
+            union { bf16 b[8]; uint4 u; } hi, lo, dh, dl;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const float a = (it < live) ? ex[(8 * i8 + e) * EXP + tq2] * osc : 0.f;
-                    const float a2 = (it < live) ? ex[(64 + 8 * i8 + e) * EXP + tq2] * osc : 0.f;
-                    hi.b[e] = enc16(a, f16); lo.b[e] = enc16(a - dec16(hi.b[e], f16), f16);
-                    h2.b[e] = enc16(a2, f16); l2.b[e] = enc16(a2 - dec16(h2.b[e], f16), f16);
+            for (int q = 0; q < 2; ++q) {
+                f4 v = {0.f, 0.f, 0.f, 0.f}, w = {0.f, 0.f, 0.f, 0.f};
+                if (it < live) {
+                    v = *(const f4*)(ex + ri * EXP + 8 * t8 + 4 * q);
+                    w = *(const f4*)(ex + (64 + ri) * EXP + 8 * t8 + 4 * q);
                 }
-                // (the head's [L, ldp] matrix in 16 x 32 blocks: the eight queries of a wavefront store are 512 contiguous bytes per block)
-                bf16* ph = out.hi + h * group_stride;
-                const long long kb = ldp >> 5, tq3 = t0 + tq2, col = i0 + 8 * i8;
-                *(uint4*)(ph + tboa_blocked_offset(tq3, col, kb)) = hi.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + col, kb)) = lo.u;
-                const long long c2 = TWO ? 2LL * L + col : col + 64;      // the other path's segments, or the next 64 keys
-                *(uint4*)(ph + tboa_blocked_offset(tq3, c2, kb)) = h2.u; *(uint4*)(ph + tboa_blocked_offset(tq3, L + c2, kb)) = l2.u;
-            }
-        } else {
-            // transposed blocked result: sixteen consecutive lanes take the 128 queries of one key row, 8 each (one 16-byte piece per
-            // output), so that a wavefront store covers four key rows of four blocks, 256 contiguous bytes in each; two rows per thread
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int slot = threadIdx.x + 512 * half, t8 = slot & 15, ri = slot >> 4;
-                union { bf16 b[8]; uint4 u; } hi, lo, dh, dl;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    f4 v = {0.f, 0.f, 0.f, 0.f}, w = {0.f, 0.f, 0.f, 0.f};
-                    if (it < live) {
-                        v = *(const f4*)(ex + ri * EXP + 8 * t8 + 4 * q);
-                        w = *(const f4*)(ex + (64 + ri) * EXP + 8 * t8 + 4 * q);
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float a = v[e] * osc, d = (TWO ? v[e] - w[e] : w[e]) * osc;
-                        hi.b[4 * q + e] = enc16(a, f16); lo.b[4 * q + e] = enc16(a - dec16(hi.b[4 * q + e], f16), f16);
-                        dh.b[4 * q + e] = enc16(d, f16); dl.b[4 * q + e] = enc16(d - dec16(dh.b[4 * q + e], f16), f16);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const float a = v[e] * osc, d = (TWO ? v[e] - w[e] : w[e]) * osc;
+                    hi.b[4 * q + e] = enc16(a, f16); lo.b[4 * q + e] = enc16(a - dec16(hi.b[4 * q + e], f16), f16);
+                    dh.b[4 * q + e] = enc16(d, f16); dl.b[4 * q + e] = enc16(d - dec16(dh.b[4 * q + e], f16), f16);
                 }
-                const long long o = tboa_blocked_offset(i0 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
-                *(uint4*)(dst[0] + o) = hi.u; *(uint4*)(dst[1] + o) = lo.u;
-                const long long o2 = TWO ? o : tboa_blocked_offset(i0 + 64 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
-                *(uint4*)(dst[2] + o2) = dh.u; *(uint4*)(dst[3] + o2) = dl.u;
             }
+            const long long o = tboa_blocked_offset(i0 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
+            *(uint4*)(dst[0] + o) = hi.u; *(uint4*)(dst[1] + o) = lo.u;
+            const long long o2 = TWO ? o : tboa_blocked_offset(i0 + 64 + ri, (long long)r * L + t0 + 8 * t8, ldp >> 5);
+            *(uint4*)(dst[2] + o2) = dh.u; *(uint4*)(dst[3] + o2) = dl.u;
         }
         if (it < live) landed();                           // next tile in LDS; the exchange buffer is free again
     }
 }
 
-template <int DH, bool ROWS, bool TWO>
+template <int DH, bool TWO>
 int launch(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, PtOut out, long long ldp,
            long long group_stride, int f16, QkScale qs) {
     static bool attr_set = false;
     constexpr int smem = attn_lds_bytes<DH>();
     if (!attr_set) {
-        TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_probs_t_kernel<DH, ROWS, TWO>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+        TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_probs_t_kernel<DH, TWO>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
         attr_set = true;
     }
     const int total = Hq * (L / BT), xcd_runs = ((Hq / rep) % 8 == 0 && total % 8 == 0) ? 1 : 0;
-    hipLaunchKernelGGL((attn_probs_t_kernel<DH, ROWS, TWO>), dim3(total), dim3(512), smem, ctx->stream, Qa, Ka, Qb, Kb, L, Hq, rep, xcd_runs,
+    hipLaunchKernelGGL((attn_probs_t_kernel<DH, TWO>), dim3(total), dim3(512), smem, ctx->stream, Qa, Ka, Qb, Kb, L, Hq, rep, xcd_runs,
                        (float)(1.4426950408889634 / sqrt((double)DH)), out, ldp, group_stride, f16, qs);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
 
-template <bool ROWS, bool TWO>
+template <bool TWO>
 int dispatch(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, int dh, PtOut out,
              long long ldp, long long group_stride, int f16, QkScale qs) {
     switch (dh) {
-        case 32: return launch<32, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        case 64: return launch<64, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        case 96: return launch<96, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
-        default: return launch<128, ROWS, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 32: return launch<32, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 64: return launch<64, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        case 96: return launch<96, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
+        default: return launch<128, TWO>(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, out, ldp, group_stride, f16, qs);
     }
 }
 
@@ -345,13 +319,5 @@ int attn_probs_t(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, 
                  long long ldp, long long group_stride, int f16, QkScale qs) {
     if (!attn_probs_t_supported(L, dh) || Hq % rep || !Qa || !Ka || (Qb && !Kb) || !out.hi || !out.lo || (Qb && (!out.dhi || !out.dlo)) || ldp % 32)
         return tboa_fail(ctx, TBOA_EINVAL, "attn_probs_t: unsupported shape or missing buffer");
-    return (Qb ? dispatch<false, true> : dispatch<false, false>)(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, group_stride, f16, qs);
-}
-
-int attn_probs_rows(tboa_ctx* ctx, const bf16* Qa, const bf16* Ka, const bf16* Qb, const bf16* Kb, int L, int Hq, int rep, int dh, bf16* P,
-                    long long ldp, int f16, QkScale qs) {
-    if (!attn_probs_t_supported(L, dh) || Hq % rep || !Qa || !Ka || (Qb && !Kb) || !P || ldp % 32 || ldp < (Qb ? 4LL : 2LL) * L || ((uintptr_t)P & 15))
-        return tboa_fail(ctx, TBOA_EINVAL, "attn_probs_rows: unsupported shape or missing buffer");
-    PtOut out{P, nullptr, nullptr, nullptr};
-    return (Qb ? dispatch<true, true> : dispatch<true, false>)(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, (long long)L * ldp, f16, qs);
+    return (Qb ? dispatch<true> : dispatch<false>)(ctx, Qa, Ka, Qb, Kb, L, Hq, rep, dh, out, ldp, group_stride, f16, qs);
 }

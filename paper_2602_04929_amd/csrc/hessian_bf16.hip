@@ -1374,12 +1374,13 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
     const int T = D.T, dm = D.dm, Hq = D.Hq, dh = D.dh, L = D.L, dq = D.dq, dkv = D.dkv, rep = D.rep;
     const bool fp = X_fp && R_o;
     int G = d->seq_chunk > 0 ? d->seq_chunk : 8; if (G > D.S) G = D.S;
-    const bool fused = d->causal && qk_blocked(D) && attn_probs_t_supported(D.L, D.dh);     // no score matrices in memory
-    // segments of V^T ((hi, hi, lo) per path) and of P (the same, or (hi, lo) per path from the fused kernel: its products name
-    // their three operand pairs instead of reading a repeated segment)
-    const int nsg = fp ? 6 : 3, nsp = fused ? (fp ? 4 : 2) : (fp ? 6 : 3), splits = pick_splits(D.S);
-    const int Lp = padded_len(L);       // (the fused kernel takes whole 256-tiles: Lp = L there)
-    const long long Tp = padded_tokens(T, splits), TP = Tp + PADE, ldp = (long long)nsp * Lp + PADE;
+    const bool fused = attn_output_supported(L, dh);      // neither scores nor probabilities in memory
+    // half pairs of Q and K (see QkScale) where build_hessians has them too: what it leaves in fp_cache then is what is computed here without
+    const bool words = fused && d->causal && qk_blocked(D) && attn_probs_t_supported(L, dh);
+    // segments of V^T and of P where these are stored: (hi, hi, lo) per path
+    const int nsg = fp ? 6 : 3, splits = pick_splits(D.S);
+    const int Lp = padded_len(L);
+    const long long Tp = padded_tokens(T, splits), TP = Tp + PADE, ldp = (long long)nsg * Lp + PADE;
     bf16 *Wqh, *Wql, *Wkh, *Wkl, *Wvh, *Wvl, *Wq3, *Wk3, *Wv3, *Qh, *Kh, *Qhf, *Khf, *P, *VTc, *OT, *OTl, *dOT, *dOTl;
     float *Qf, *Kf, *VT32, *VT32f, *Sc, *Scf, *part, *steps;
     int* amx;      // [q | k | q~ | k~] x G (see QkScale)
@@ -1393,9 +1394,10 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
         VT32f = fp ? ar.get<float>((size_t)dkv * G * L) : nullptr; Scf = (fp && !fused) ? ar.get<float>((size_t)Hq * L * L) : nullptr;
         Qh = ar.get<bf16>((size_t)G * L * dq * 3); Kh = ar.get<bf16>((size_t)G * L * dkv * 3);
         Qhf = fp ? ar.get<bf16>((size_t)G * L * dq * 3) : nullptr; Khf = fp ? ar.get<bf16>((size_t)G * L * dkv * 3) : nullptr;
-        Sc = fused ? nullptr : ar.get<float>((size_t)Hq * L * L); P = ar.get<bf16>((size_t)Hq * Lp * ldp);
-        VTc = ar.get<bf16>((size_t)dkv * (G * nsg * Lp + PADE));
-        OT = ar.get<bf16>((size_t)dq * TP); OTl = ar.get<bf16>((size_t)dq * TP);
+        Sc = fused ? nullptr : ar.get<float>((size_t)Hq * L * L); P = fused ? nullptr : ar.get<bf16>((size_t)Hq * Lp * ldp);
+        VTc = ar.get<bf16>(fused ? attn_output_v_elems(dkv, G, L, fp ? 2 : 1) : (size_t)dkv * (G * nsg * Lp + PADE));
+        const bool pairs = !(fused && O_rows && !Hin_o && ((uintptr_t)O_rows & 15) == 0);      // O^T as pairs; the forward pass alone takes rows (16-byte stores) from the fused kernel
+        OT = pairs ? ar.get<bf16>((size_t)dq * TP) : nullptr; OTl = pairs ? ar.get<bf16>((size_t)dq * TP) : nullptr;
         dOT = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr; dOTl = fp ? ar.get<bf16>((size_t)dq * TP) : nullptr;
         part = ar.get<float>(Hin_o ? gram_part_elems(dq, splits, Tp, 3, fp ? 3 : 0, 0) : 0);
         steps = ar.get<float>((size_t)dq + 2 * dkv);
@@ -1430,59 +1432,52 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
             int first = 1;
             for (const bf16* w : tv) if (w) { TB_TRY(gemm_bf16_nt(ctx, nt(dkv, Gc * L, dm, 1.f, w, dm, Xc, dm, VT32, (long long)Gc * L, TBOA_F32, first ? 0 : 1, 0))); first = 0; }
         }
-        int *aq = fused ? amx : nullptr, *ak = fused ? amx + G : nullptr;
-        const int *aqf = fused ? amx + 2 * G : nullptr, *akf = fused ? amx + 3 * G : nullptr;
+        int *aq = words ? amx : nullptr, *ak = words ? amx + G : nullptr;
+        const int *aqf = words ? amx + 2 * G : nullptr, *akf = words ? amx + 3 * G : nullptr;
         TB_TRY(project_qk(D, Xc, Gc * L, Wqh, Wql_u, Wkh, Wkl_u, Qf, Kf, Qh, Kh, sq, sk, aq, ak, Wq3_u, Wk3_u));
         if (fp) {
             TB_TRY(gemm_bf16_nt(ctx, nt(dkv, Gc * L, dm, 1.f, Wv, dm, X_fp + t0 * dm, dm, VT32f, (long long)Gc * L, TBOA_F32, 0, 0)));
             if (fp_cache) {     // projections of X_fp by W_Q, W_K as tboa_build_hessians left them, with the words that say how
                 Qhf = (bf16*)fp_cache + t0 * dq * 3; Khf = (bf16*)fp_cache + (long long)T * dq * 3 + t0 * dkv * 3;
-                const int* words = (const int*)(fp_cache + (long long)T * (dq + dkv) * 3);
-                aqf = words + s0; akf = words + D.S + s0;
+                const int* enc = (const int*)(fp_cache + (long long)T * (dq + dkv) * 3);
+                aqf = enc + s0; akf = enc + D.S + s0;
             } else TB_TRY(project_qk(D, X_fp + t0 * dm, Gc * L, Wq, nullptr, Wk, nullptr, Qf, Kf, Qhf, Khf, nullptr, nullptr,
-                                     fused ? amx + 2 * G : nullptr, fused ? amx + 3 * G : nullptr));
+                                     words ? amx + 2 * G : nullptr, words ? amx + 3 * G : nullptr));
+        }
+        if (fused) {
+            AttnOutput o{};
+            o.S = Gc; o.L = L; o.Hq = Hq; o.rep = rep; o.dh = dh; o.paths = fp ? 2 : 1; o.blocked = qk_blocked(D); o.causal = d->causal; o.f16 = D.f16;
+            o.path[0] = {Qh, Kh, aq, ak}; o.path[1] = {Qhf, Khf, aqf, akf};
+            o.VT32[0] = VT32; o.VT32[1] = VT32f; o.v_scale[0] = sv; o.V = VTc;
+            if (OT) { o.OT[0] = OT + t0; o.OTl[0] = OTl + t0; o.OT[1] = fp ? dOT + t0 : nullptr; o.OTl[1] = fp ? dOTl + t0 : nullptr; o.ldo = TP; }      // (dOT: O~^T for now)
+            else { o.rows = O_rows + t0 * dq; o.ldr = dq; }
+            TB_TRY(attn_output(ctx, o));
+            continue;
         }
         if (Lp != L) TB_TRY(clear16(ctx, VTc, dkv * ldv));
         hipLaunchKernelGGL(vt_segments_kernel, dim3(g1((long long)dkv * Gc * L)), dim3(256), 0, st, VT32, sv, fp ? VT32f : nullptr, VTc, dkv, Gc, L, Lp,
                            nsg, ldv, D.f16);
         TB_KERNEL_CHECK(ctx);
         for (int sl = 0; sl < Gc; ++sl) {
-            // V^T segments [V'hi | V'hi | V'lo | V~hi | V~hi | V~lo], P = [A'hi | A'lo | A'hi | A~hi | A~lo | A~hi] ([A'hi | A'lo | A~hi | A~lo] fused):
+            // V^T segments [V'hi | V'hi | V'lo | V~hi | V~hi | V~lo], P = [A'hi | A'lo | A'hi | A~hi | A~lo | A~hi]:
             // O^T_h = [V'hi | V'hi | V'lo] [A'hi | A'lo | A'hi]^T and O~^T_h likewise from the second halves, both left as (hi, lo)
             // pairs; the deviation O - O~ is taken from the two pairs afterwards (its 22 bits then hold 1e-5 of a difference that
             // is a few percent of either: products of single half values of V' - V~, V~ and A' - A~ left 1e-4)
-            if (fused) {      // scores and softmax in one kernel, nothing of the scores stored
-                const long long qo = (long long)sl * Hq * L * 3 * dh, ko = (long long)sl * D.Hkv * L * 3 * dh;
-                const QkScale qs{aq + sl, ak + sl, fp ? aqf + sl : nullptr, fp ? akf + sl : nullptr};
-                TB_TRY(attn_probs_rows(ctx, Qh + qo, Kh + ko, fp ? Qhf + qo : nullptr, fp ? Khf + ko : nullptr, L, Hq, rep, dh, P, ldp, D.f16, qs));
-            } else {
-                if (fp) TB_TRY(scores_pair(D, Qh, Kh, Qhf, Khf, sl, Sc, Scf));
-                else TB_TRY(scores(D, Qh, Kh, sl, Sc));
-                TB_TRY(softmax(D, Sc, fp ? Scf : nullptr, P, Lp, ldp, 2 * Lp, Lp, 3 * Lp, 0, 1));
-            }
+            if (fp) TB_TRY(scores_pair(D, Qh, Kh, Qhf, Khf, sl, Sc, Scf));
+            else TB_TRY(scores(D, Qh, Kh, sl, Sc));
+            TB_TRY(softmax(D, Sc, fp ? Scf : nullptr, P, Lp, ldp, 2 * Lp, Lp, 3 * Lp, 0, 1));
             const long long co = t0 + (long long)sl * L;
-            const float pa = (fused && D.f16) ? 1.f / ATTN_PROBS_HALF_SCALE : 1.f;       // half probabilities from the fused kernel are scaled
             // (an attention output is a convex combination of values: it fits half where they do, and then leaves as a pair of halves)
-            GemmBf16 o = nt(dh, L, 3 * Lp, pa, VTc + (long long)sl * nsg * Lp, ldv, P, ldp, OT + co, TP, TBOA_BF16, 0,
+            GemmBf16 o = nt(dh, L, 3 * Lp, 1.f, VTc + (long long)sl * nsg * Lp, ldv, P, ldp, OT + co, TP, TBOA_BF16, 0,
                             cflag | TBOA_GEMM_C_HILO | (D.f16 ? TBOA_GEMM_C_HILO_HALF : 0));
             o.C2 = OTl + co;
             o.kseg = Lp; o.batch = Hq; o.batch_inner = rep; o.tag = TBOA_PROF_PV;
             o.strideA = (long long)dh * ldv; o.strideA2 = 0;
             o.strideB = (long long)rep * Lp * ldp; o.strideB2 = (long long)Lp * ldp;
             o.strideC = (long long)rep * dh * TP; o.strideC2 = (long long)dh * TP;
-            if (fused) {       // (the fused kernel leaves P in 16 x 32 blocks: a column offset c is the pointer offset 16 c)
-                o.flags |= TBOA_GEMM_B_TILED;
-                o.nterms = 3;
-                o.termA[0] = o.A; o.termA[1] = o.A; o.termA[2] = o.A + 2 * L;
-                o.termB[0] = P; o.termB[1] = P + 16LL * L; o.termB[2] = P;
-            }
             TB_TRY(gemm_bf16_nt(ctx, o));
             if (fp) {       // O~^T for now
-                o.A = VTc + ((long long)sl * nsg + 3) * Lp; o.B = P + (fused ? 16LL * 2 : 3) * Lp; o.C = dOT + co; o.C2 = dOTl + co;
-                if (fused) {
-                    o.termA[0] = o.A; o.termA[1] = o.A; o.termA[2] = o.A + 2 * L;
-                    o.termB[0] = o.B; o.termB[1] = o.B + 16LL * L; o.termB[2] = o.B;
-                }
+                o.A = VTc + ((long long)sl * nsg + 3) * Lp; o.B = P + 3LL * Lp; o.C = dOT + co; o.C2 = dOTl + co;
                 TB_TRY(gemm_bf16_nt(ctx, o));
             }
         }
@@ -1492,6 +1487,7 @@ int build_hessian_out_proj_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf
         TB_KERNEL_CHECK(ctx);
     }
     if (O_rows) {
+        if (!OT) return 0;
         hipLaunchKernelGGL(ot_rows_kernel, dim3((unsigned)((T + 63) / 64), (dq + 63) / 64), dim3(256), 0, st, OT, OTl, TP, dq, (long long)T, O_rows, D.f16);
         TB_KERNEL_CHECK(ctx);
         if (!Hin_o) return 0;

@@ -209,7 +209,7 @@ long long gemm_gram_tiles(int M, int N, int lower);
 // rows i up to the end of the 256-tile that holds t written (zeros beyond the diagonal).  dhi, dlo: A - A~ of a second
 // score matrix (nullptr without one).
 struct PtOut { __hip_bfloat16 *hi, *lo, *dhi, *dlo; };
-// factor on the probabilities attn_probs_t / attn_probs_rows write as IEEE half (f16 set); bf16 results are unscaled
+// factor on the probabilities attn_probs_t writes as IEEE half (f16 set), and that attn_output holds as such; bf16 ones are unscaled
 #define ATTN_PROBS_HALF_SCALE 16384.f
 // How the (hi, lo) pairs of Q^ and K^ are encoded, per score matrix: a device word per operand that holds the bits of the
 // largest magnitude of that operand's fp32 values, in which case the pairs are IEEE half values of the operand times
@@ -224,13 +224,26 @@ __host__ __device__ __forceinline__ int tboa_half_exp(int amax_bits) {
 // straight from the blocked 3-term operands Q^ [Hq][L, 3 dh], K^ [Hkv][L, 3 dh] of the score product (second pair Qb, Kb or
 // nullptr); attn_probs_t_supported tells which shapes the kernel takes
 bool attn_probs_t_supported(int L, int dh);
-// the same probabilities with the queries as rows, P[h][t][.] = [A_hi | A_lo | A~_hi | A~_lo] (segments of L columns, pitch ldp, a
-// multiple of 32: every head's [L, ldp] matrix in 16 x 32 blocks; the last two segments only with a second pair: the
-// probabilities of the second score matrix), rows written up to the end of the 256-tile of t
-int attn_probs_rows(tboa_ctx* ctx, const __hip_bfloat16* Qa, const __hip_bfloat16* Ka, const __hip_bfloat16* Qb, const __hip_bfloat16* Kb, int L,
-                    int Hq, int rep, int dh, __hip_bfloat16* P, long long ldp, int f16, QkScale qs);
 int attn_probs_t(tboa_ctx* ctx, const __hip_bfloat16* Qa, const __hip_bfloat16* Ka, const __hip_bfloat16* Qb, const __hip_bfloat16* Kb, int L,
                  int Hq, int rep, int dh, PtOut out, long long ldp, long long group_stride, int f16, QkScale qs);
+
+// ---------------------------------------------------------------- attn_output.hip
+// Attention outputs of S whole sequences of L tokens, one or two paths (operands of their own, the same shapes).  Q, K: the 3-term operands of the score product of all
+// sequences (blocked: one [L, 3 dh] matrix in 16 x 32 blocks per sequence and head, else rows [S L][heads][3 dh]); qa, ka: words of their encoding (QkScale), one per sequence,
+// or null; VT32: V^T [Hkv dh][S L] in fp32, v_scale: a factor per row or null; V: room for attn_output_v_elems 16-bit elements.
+// Results: rows (one path): token-major bf16 [S L][ldr]; else O^T [Hq dh][ldo] per path as (hi, lo) pairs in OT, OTl (half when f16, else bf16).
+struct AttnPath { const __hip_bfloat16 *Q, *K; const int *qa, *ka; };
+struct AttnOutput {
+    int S, L, Hq, rep, dh, paths, blocked, causal, f16;
+    AttnPath path[2];
+    const float *VT32[2], *v_scale[2];
+    __hip_bfloat16* V;
+    __hip_bfloat16 *OT[2], *OTl[2]; long long ldo;
+    __hip_bfloat16* rows; long long ldr;
+};
+bool attn_output_supported(int L, int dh);
+size_t attn_output_v_elems(int dkv, int S, int L, int paths);
+int attn_output(tboa_ctx* ctx, const AttnOutput& q);
 
 // element offset of (r, c) in a matrix kept in the 16 x 32 blocks the bf16 GEMM can read and write (TBOA_GEMM_*_TILED);
 // kb = leading dimension / 32
