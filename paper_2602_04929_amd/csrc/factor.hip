@@ -301,7 +301,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
     constexpr int OB = TB_FACT_OB;
     const int nblk = (n + NB - 1) / NB, nob = (n + OB - 1) / OB, TL = chol_tmp_pitch(n);
     const long long nn = (long long)n * n;
-    TB_TRY(rns_diagonal_exps(ctx, n, batch, H, RNS_BITS_A, w.V.e));
+    TB_TRY(rns_diagonal_exps(ctx, n, batch, H, RNS_BITS_A, w.V.e, w.sq, 3LL * n));
     RnsGemm g{};
     g.batch = batch; g.nm = TB_RNS_MODULI; g.residues = w.res;
     for (int ob = nob - 1; ob >= 0; --ob) {
@@ -315,6 +315,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
         if (J0 > 0) {
             RnsSource v{};
             v.a = H + J0; v.ld = n; v.stride = nn; v.kc = 1; v.rows = J0; v.k = J1 - J0;
+            TB_TRY(rns_row_guard(ctx, v, batch, RNS_BITS_A, w.V, w.sq, 3LL * n));
             TB_TRY(rns_rows(ctx, v, nullptr, batch, RNS_GIVEN, w.V, TB_RNS_MODULI, J0));
         }
     }

@@ -137,12 +137,33 @@ __global__ __launch_bounds__(256) void rns_grow_kernel(int rows, const double* _
     if (more) *ep = fresh || now == UNDEFINED ? now : now + 1;
     grown[blockIdx.z * e_stride + r] = more && !fresh;
 }
-// powers of two of the rows of V, H = V V^T: a row's norm is the root of H's diagonal entry
-__global__ __launch_bounds__(256) void rns_diagonal_exps_kernel(int n, const double* __restrict__ H, long long stride, int bits, int* __restrict__ e, long long e_stride) {
+// powers of two of the rows of V, H = V V^T: a row's norm is the root of H's diagonal entry.  None for an entry that is not positive; sum: nothing so far
+__global__ __launch_bounds__(256) void rns_diagonal_exps_kernel(int n, const double* __restrict__ H, long long stride, int bits, int* __restrict__ e, double* __restrict__ sum, long long sum_stride) {
     const int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= n) return;
     const double v = H[blockIdx.z * stride + (long long)r * (n + 1)];
-    e[blockIdx.z * e_stride + r] = v > 0.0 ? row_exponent(v, 0.0, 0.0, bits) : v == v ? 0 : UNDEFINED;
+    e[blockIdx.z * (long long)n + r] = v > 0.0 ? row_exponent(v, 0.0, 0.0, bits) : UNDEFINED;
+    sum[blockIdx.z * sum_stride + r] = 0.0;
+}
+// The norms above are those of a positive definite H only.  A row whose squares so far (a wavefront sums those of the panel, in units of its power of two) are more than twice as many
+// as H's diagonal entry allows, or undefined, no longer fits its residues: it is marked undefined, so that its own pivot is, as the negative one would be that fp64 products leave.
+// Rows up to twice too long are held exactly (|a| |b| <= 2^115) and their pivots come out negative.
+__global__ __launch_bounds__(256) void rns_row_guard_kernel(RnsSource s, int bits, int* __restrict__ e, long long e_stride, double* __restrict__ sum, long long sum_stride) {
+    const int lane = threadIdx.x & 63, r = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (r >= s.rows) return;
+    int* er = e + blockIdx.z * e_stride + r;
+    if (*er == UNDEFINED) return;
+    const double* a = s.a + blockIdx.z * s.stride + (long long)r * s.ld;
+    const int down = -*er - bits;
+    double q = 0.0;
+    for (int k = lane; k < s.k; k += 64) { const double v = ldexp(a[k], down); q = __builtin_fma(v, v, q); }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o, 64);
+    if (lane == 0) {
+        double* sr = sum + blockIdx.z * sum_stride + r;
+        q += *sr; *sr = q;
+        if (!(q <= 2.0)) *er = UNDEFINED;
+    }
 }
 
 struct Moduli { float inv[NMAX]; int m[NMAX]; };
@@ -537,8 +558,14 @@ int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long 
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
-int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e) {
-    hipLaunchKernelGGL(rns_diagonal_exps_kernel, dim3((unsigned)cdiv64(n, 256), 1, batch), dim3(256), 0, ctx->stream, n, H, (long long)n * n, bits, e, (long long)n);
+int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e, double* sum, long long sum_stride) {
+    hipLaunchKernelGGL(rns_diagonal_exps_kernel, dim3((unsigned)cdiv64(n, 256), 1, batch), dim3(256), 0, ctx->stream, n, H, (long long)n * n, bits, e, sum, sum_stride);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
+int rns_row_guard(tboa_ctx* ctx, const RnsSource& s, int batch, int bits, const RnsOperand& o, double* sum, long long sum_stride) {
+    if (!s.kc || !o.e || s.kexp || s.exp_shift || s.half) return tboa_fail(ctx, TBOA_EINVAL, "rns_row_guard: source must be plain rows");
+    hipLaunchKernelGGL(rns_row_guard_kernel, dim3((unsigned)cdiv64(s.rows, 4), 1, batch), dim3(256), 0, ctx->stream, s, bits, o.e, o.e_stride, sum, sum_stride);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }

@@ -155,7 +155,9 @@ int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& 
 // then makes the first `panel` indices of every row, the others of the rows that have grown
 int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long panel_stride, double* sq, int sq_rows, long long sq_stride, int fresh_below, int bits, int* e, long long e_stride,
              int* grown);
-int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e);      // of the rows of V, H = V V^T
+// exponents of the rows of V, H = V V^T, from H's diagonal; before rns_rows with them: which rows are longer than H's diagonal says (sum: their squares over all panels)
+int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e, double* sum, long long sum_stride);
+int rns_row_guard(tboa_ctx* ctx, const RnsSource& s, int batch, int bits, const RnsOperand& o, double* sum, long long sum_stride);
 int rns_balance(tboa_ctx* ctx, int rows, double* sq1, const double* sq2, int* f);
 int rns_gemm(tboa_ctx* ctx, const RnsGemm& q);
 double rns_model_us(int M, int N, int K, bool triangular, bool beta, int nm);

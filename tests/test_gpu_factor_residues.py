@@ -47,3 +47,29 @@ def test_breakdown_is_reported(lib):
     with pytest.raises(lib.TurboBoAError, match="pivot 700 is not positive"):
         ctx.chol_inv_upper(H)
     ctx.close()
+
+
+@pytest.mark.parametrize("value", [1.5, 10.0, 12345.0, 3e6, 1e12, float("nan"), float("inf")])
+@pytest.mark.parametrize("r,k", [(700, 2900), (3, 3099), (1500, 1530)])
+def test_rows_longer_than_the_diagonal_says(lib, r, k, value):
+    """A pivot that an entry beyond the diagonal's reach makes negative (or undefined), in a later block of 512 columns or the same one: refused, and named, whatever the residues hold."""
+    n = 3100
+    H = torch.eye(n, device="cuda")
+    H[r, k] = H[k, r] = value
+    H[r - 2, k - 1] = H[k - 1, r - 2] = 0.5
+    ctx = lib.Context()
+    with pytest.raises(lib.TurboBoAError, match="pivot %d is not positive" % r):
+        ctx.chol_inv_upper(H)
+    ctx.close()
+
+
+@pytest.mark.parametrize("value", [0.0, -1e30])
+def test_diagonal_entries_that_are_not_positive(lib, value):
+    n = 3100
+    H = torch.eye(n, device="cuda")
+    H[40, 40] = value
+    H[40, 2500] = H[2500, 40] = 1e12
+    ctx = lib.Context()
+    with pytest.raises(lib.TurboBoAError, match="pivot 40 is not positive"):
+        ctx.chol_inv_upper(H)
+    ctx.close()
