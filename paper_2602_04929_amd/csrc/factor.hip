@@ -410,15 +410,21 @@ extern "C" int tboa_chol_inv_upper(tboa_ctx* ctx, int n, int batch, const float*
     if (!ctx) return TBOA_EINVAL;
     if (n <= 0 || batch <= 0 || !H || !U) return tboa_fail(ctx, TBOA_EINVAL, "chol_inv_upper: bad arguments");
     const int nblk = (n + NB - 1) / NB;
-    Arena plan(nullptr);
+    bool residues = true;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         double* H64 = ar.get<double>((size_t)batch * n * n);
         double* tmp = ar.get<double>((size_t)batch * n * chol_tmp_pitch(n));
         double* dinv = ar.get<double>((size_t)batch * nblk * NB * NB);
-        CholRns rns;
-        chol_rns_plan(n, batch, ar, rns);
-        if (!pass) { TB_TRY(tboa_ws_reserve(ctx, ar.off)); continue; }
+        const size_t plain = ar.off;
+        CholRns rns{};
+        if (residues) chol_rns_plan(n, batch, ar, rns);
+        if (!pass) {
+            int rc = tboa_ws_reserve(ctx, ar.off);
+            if (rc == TBOA_ENOMEM && ar.off > plain) { residues = false; rc = tboa_ws_reserve(ctx, plain); }      // what fits without residues still runs
+            TB_TRY(rc);
+            continue;
+        }
         TB_TRY(launch_f32_to_f64_damp(ctx, n, batch, H, damp, H64));
         TB_TRY(chol_inv_upper_f64(ctx, n, batch, H64, U, tmp, dinv, 0, false, &rns));
     }

@@ -1107,6 +1107,7 @@ struct Layer {
     long long nn;
     // Products with the d_in x d_in matrices on the integer matrix cores (gemm_rns.hip): the matrices as right operands, prepared once a call, and per stream of the call
     // (0: main, 1: aux) the left operand of a product, residues of its result and sums of squares
+    int no_rns;                 // no room for residues: everything in fp64, the factorisation too
     int rns, rns_rows_max;      // rns: which products (RNS_*); rns_rows_max: rows of a product at a time
     RnsOperand hT, uR, uC, pC, rC, left[2];      // H_in (its half T; group-wise: whole), rows of U, columns of U, columns of P, columns of R
     unsigned char* rres[2]; CholRns frns; double *rsq, *rsq2, *rpart; int *kexp, *pshift;
@@ -1822,7 +1823,8 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     // the two factorisations (H_in: nhin matrices of order n; H_out: nh of order dh) share their temporaries
     const size_t t_in = (size_t)L.nhin * n * chol_tmp_pitch(n), t_out = H_out ? (size_t)nh * dh * chol_tmp_pitch(dh) : 0;
     L.ftmp = ar.get<double>(t_in > t_out ? t_in : t_out); L.fdinv = ar.get<double>((size_t)fb * nblk_f * TB_FACT_NB * TB_FACT_NB);
-    chol_rns_plan(n, L.nhin, ar, L.frns);
+    if (!L.no_rns) chol_rns_plan(n, L.nhin, ar, L.frns);
+    else L.frns = CholRns{};
     L.Wb = ar.get<double>(brows * n); L.Wk = ar.get<double>(brows * n);
     L.Epan = ar.get<double>(brows * SWEEP_SP); L.Wsnap = ar.get<double>(brows * SWEEP_SP);
     L.E = H_out ? ar.get<double>(brows * n) : nullptr;
@@ -1856,7 +1858,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
     L.WR = R ? ar.get<double>(wn) : nullptr;
     L.Cm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr; L.Fm = H_out ? ar.get<double>((size_t)nh * dh * dh) : nullptr;
     L.dvec = ar.get<double>(2 * (size_t)d->d_out); L.lossbuf = ar.get<double>(2 * (size_t)nh);
-    L.rns = rns_choice(L, H_out, R);
+    L.rns = L.no_rns ? 0 : rns_choice(L, H_out, R);
     if (L.rns) {
         const size_t cap = L.fast_grid ? (size_t)L.fast_chunk * GRID_KS : 0;
         auto operand = [&](int rows, int k, bool exps) {
@@ -1957,7 +1959,15 @@ extern "C" int tboa_quantize_layer(tboa_ctx* ctx, const tboa_layer_desc* d, cons
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         plan_layer(L, H_out != nullptr, R != nullptr, ar);
-        if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
+        if (pass) break;
+        int rc = tboa_ws_reserve(ctx, ar.off);
+        if (rc == TBOA_ENOMEM) {      // residues take as much memory again as the fp64 matrices: what fits without them still runs
+            Arena plain(nullptr);
+            L.no_rns = 1;
+            plan_layer(L, H_out != nullptr, R != nullptr, plain);
+            rc = tboa_ws_reserve(ctx, plain.off);
+        }
+        TB_TRY(rc);
     }
     int rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
     if (rc == RUN_AGAIN_TWO_TERMS) {

@@ -73,3 +73,32 @@ def test_diagonal_entries_that_are_not_positive(lib, value):
     with pytest.raises(lib.TurboBoAError, match="pivot 40 is not positive"):
         ctx.chol_inv_upper(H)
     ctx.close()
+
+
+def test_room_for_fp64_only(lib):
+    """Residues take 30 bytes an element, more than the device has left: the factorisation and a layer run in fp64, as they would have without them."""
+    n, batch = 2048, 96
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(2 * n, n, generator=g, device="cuda")
+    H = (x.T @ x)[None].repeat(batch, 1, 1)
+    y = torch.randn(10000, 8192, generator=g, device="cuda")
+    H1, W = y.T @ y, 0.02 * torch.randn(8192, 8192, generator=g, device="cuda")
+    del y
+    out = torch.empty(batch, n, n, dtype=torch.float64, device="cuda")
+    for call in (lambda c: c.chol_inv_upper(H, out=out), lambda c: c.quantize_layer(W, H1, None, None, 1, bits=2, block=8192)["codes"]):
+        ctx = lib.Context()
+        want, need = call(ctx).clone(), ctx.workspace_bytes()
+        ctx.close()
+        torch.cuda.synchronize()
+        torch.cuda.empty_cache()
+        ballast = torch.empty(torch.cuda.mem_get_info()[0] - need + (4 << 30), dtype=torch.uint8, device="cuda")
+        ctx = lib.Context()
+        got = call(ctx)
+        assert 0 < ctx.workspace_bytes() < need - (4 << 30)
+        ctx.close()
+        del ballast
+        torch.cuda.empty_cache()
+        if want.dtype == torch.float64:
+            assert torch.linalg.norm(got - want) <= 1e-12 * torch.linalg.norm(want)
+        else:
+            assert torch.equal(got, want)
