@@ -1026,6 +1026,48 @@ int check_bf16_dims(const Dims& D) {
     return 0;
 }
 
+// The wide product of the W_Q and W_K Hessians, C = W T with T + T^T = H_in (T triangular), in fp64 or as a product of residues.
+struct WideResidues { RnsOperand h, w; unsigned char* res; };      // h.p null: fp64
+// In the room from `from` on, which is in use at another time (a few short sequences need less than the residues: the workspace grows then).  The line, on whole builds over 512
+// tokens, fp64 -> residues with the preparation of both operands: rows x n^2 = 0.6e9 (1024 x 768) 0.83 -> 0.85 ms, 2.1e9 (2048 x 1024) 0.868 -> 0.864, 4.5e9 (1920 x 1536)
+// 1.12 -> 1.03, 17e9 (4096 x 2048) 1.96 -> 1.77, 137e9 (8192 x 4096) 8.6 -> 7.1, 618e9 (9216 x 8192) 18.3 -> 13.4; few rows do not repay the preparation of H_in (n^2 elements).
+WideResidues plan_wide_residues(int rows, int n, Arena& ar, size_t from) {
+    WideResidues r{};
+    if (n > 32768 || rows < n / 4 || (double)rows * n * n < 3e9) return r;
+    Arena a(ar.base);
+    a.off = from;
+    auto operand = [&](int m) {
+        RnsOperand o{};
+        o.kpad = rns_pad(n); o.plane = rns_plane(m, n); o.p = a.get<signed char>(TB_RNS_MODULI * o.plane); o.e = a.get<int>(m);
+        return o;
+    };
+    r.h = operand(n); r.w = operand(rows);
+    r.res = a.get<unsigned char>(rns_residue_bytes(rows, n, 1, TB_RNS_MODULI));
+    ar.off = std::max(ar.off, a.off);
+    return ar.base ? r : WideResidues{};
+}
+int wide_half_product(tboa_ctx* ctx, int rows, int n, const double* W, const float* H, double* T, double* C, const WideResidues& r) {
+    const long long nn = (long long)n * n;
+    if (r.h.p) {
+        // T: twice what is before the diagonal (alpha takes the factor out) and the diagonal once
+        TB_TRY(launch_cvt_f32_to_f64(ctx, H, T, nn));
+        RnsSource h{}, w{};
+        h.a = T; h.ld = n; h.kc = 1; h.rows = n; h.k = n; h.half = 1;
+        w.a = W; w.ld = n; w.kc = 1; w.rows = rows; w.k = n;
+        TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, r.h, TB_RNS_MODULI));
+        TB_TRY(rns_rows(ctx, w, nullptr, 1, RNS_BITS_A, r.w, TB_RNS_MODULI));
+        RnsGemm g{};
+        g.A = &r.w; g.B = &r.h; g.M = rows; g.N = n; g.K = n; g.nm = TB_RNS_MODULI; g.khi_n = 1; g.alpha = 0.5; g.beta = 0.0; g.C = C; g.ldc = n; g.residues = r.res;
+        return rns_gemm(ctx, g);
+    }
+    hipLaunchKernelGGL(lower_half_f64_kernel, dim3(g1(nn)), dim3(256), 0, ctx->stream, H, T, n);
+    TB_KERNEL_CHECK(ctx);
+    GemmF64 a{};
+    a.M = rows; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0; a.A = W; a.sam = n; a.sak = 1; a.B = T; a.sbk = n; a.sbn = 1;
+    a.C = C; a.ldc = n; a.batch = 1; a.klo_n = 1; a.diag_order = 1;
+    return gemm_f64(ctx, a);
+}
+
 // H_in and R of W_V for bf16 inputs (Table 1: X A_h^T A_h X^T, summed over the sequences and the query heads of the KV group).
 //
 // Summed form (summed_form: every named configuration):  sum_{h in g} (A_h X_s)^T (A_h X_s) = X_s^T (sum_h A_h^T A_h) X_s, so
@@ -1069,11 +1111,14 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     float *part, *Qf, *Kf, *Sc, *Scf, *B1f = nullptr, *B2f = nullptr;
     int* amx;      // [q | k | q~ | k~] x G: largest magnitudes of the chunk's projections, per sequence (see QkScale)
     double *Hin64, *Wq64, *Wk64, *Wo64, *Tq, *Tk, *Ho;
+    WideResidues res{};
+    bool residues = true;
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);
         XT = ar.get<bf16>((size_t)dm * TP);
         dXh = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr; dXl = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr;
         part = ar.get<float>(Hin_qk ? gram_part_elems(dm, splits, Tp, 1, fp && R_qk ? 2 : 0, blocked_x) : 0);
+        const size_t wv0 = ar.off;      // from here on: buffers of the W_V Hessian, which is built last
         Qf = ar.get<float>((size_t)G * L * dq); Kf = ar.get<float>((size_t)G * L * dkv);
         Qh = ar.get<bf16>((size_t)G * L * dq * 3); Kh = ar.get<bf16>((size_t)G * L * dkv * 3);
         Qhf = rv ? ar.get<bf16>((size_t)G * L * dq * 3) : nullptr; Khf = rv ? ar.get<bf16>((size_t)G * L * dkv * 3) : nullptr;
@@ -1093,10 +1138,14 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             P = ar.get<bf16>((size_t)Hq * Lp * (nsg * Lp + PADE));
             YT = ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)); dYT = rv ? ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)) : nullptr;
         }
-        Hin64 = ar.get<double>((size_t)dd); Wq64 = ar.get<double>((size_t)dq * dm); Wk64 = ar.get<double>((size_t)dkv * dm);
-        Wo64 = ar.get<double>((size_t)dm * dq); Tq = ar.get<double>((size_t)dq * dm); Tk = ar.get<double>((size_t)dkv * dm);
+        if (residues) res = plan_wide_residues(dq + dkv, dm, ar, wv0);
+        Hin64 = ar.get<double>((size_t)dd); Wq64 = ar.get<double>((size_t)(dq + dkv) * dm); Wk64 = Wq64 + (size_t)dq * dm;
+        Wo64 = ar.get<double>((size_t)dm * dq); Tq = ar.get<double>((size_t)(dq + dkv) * dm); Tk = Tq + (size_t)dq * dm;
         Ho = ar.get<double>((size_t)Hkv * hh);
-        if (!pass) TB_TRY(tboa_ws_reserve(ctx, ar.off));
+        if (pass) break;
+        const int rc = tboa_ws_reserve(ctx, ar.off);
+        if (rc == TBOA_ENOMEM && residues) { residues = false; pass = -1; continue; }      // what fits without residues still runs
+        TB_TRY(rc);
     }
     hipStream_t st = ctx->stream;
     // ---- H_in and R for W_Q / W_K
@@ -1107,19 +1156,12 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     TB_TRY(gram_splitk(ctx, splits, dm, XT, nullptr, XT, TP, (int)Tp, 1.0, 1, part, Hin_qk, blocked_x));
     if (fp && R_qk) TB_TRY(gram_splitk(ctx, splits, dm, dXh, dXl, XT, TP, (int)Tp, d->alpha, 0, part, R_qk, blocked_x));
     // ---- H_out: K_g^T K_g = W_K,g H_in W_K,g^T ; sum_h Q_h^T Q_h ; sum_h W_out,h^T W_out,h   (fp64)
-    // (the wide product W_Q H_in, d_q x d x d, is taken with the triangular half of H_in; the d_h x d_h products of a group's heads
+    // (the wide product [W_Q; W_K] H_in, (d_q + d_kv) x d x d, is taken with a triangular half of H_in; the d_h x d_h products of a group's heads
     // are one launch whose terms are summed in fp64: as one launch per head of the group they ran on n_kv_heads workgroups)
-    hipLaunchKernelGGL(lower_half_f64_kernel, dim3(g1(dd)), dim3(256), 0, st, Hin_qk, Hin64, dm);
-    TB_KERNEL_CHECK(ctx);
     TB_TRY(launch_cvt_to_f64(ctx, Wq, TBOA_BF16, Wq64, (int64_t)dq * dm));
     TB_TRY(launch_cvt_to_f64(ctx, Wk, TBOA_BF16, Wk64, (int64_t)dkv * dm));
     {
-        GemmF64 a{};
-        a.M = dq; a.N = dm; a.K = dm; a.alpha = 1.0; a.beta = 0.0; a.A = Wq64; a.sam = dm; a.sak = 1; a.B = Hin64; a.sbk = dm; a.sbn = 1;
-        a.C = Tq; a.ldc = dm; a.batch = 1; a.klo_n = 1; a.diag_order = 1;
-        TB_TRY(gemm_f64(ctx, a));
-        a.M = dkv; a.A = Wk64; a.C = Tk;
-        TB_TRY(gemm_f64(ctx, a));
+        TB_TRY(wide_half_product(ctx, dq + dkv, dm, Wq64, Hin_qk, Hin64, Tq, res));
         GemmF64 b{};   // per KV head: Tk_g Wk_g^T
         b.M = dh; b.N = dh; b.K = dm; b.alpha = 1.0; b.beta = 0.0; b.A = Tk; b.sam = dm; b.sak = 1; b.B = Wk64; b.sbk = 1; b.sbn = dm;
         b.C = Ho; b.ldc = dh; b.batch = Hkv; b.strideA = (long long)dh * dm; b.strideB = b.strideA; b.strideC = hh;
