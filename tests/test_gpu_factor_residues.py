@@ -102,3 +102,21 @@ def test_room_for_fp64_only(lib):
             assert torch.linalg.norm(got - want) <= 1e-12 * torch.linalg.norm(want)
         else:
             assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("n,batch", [(127, 33), (128, 32), (129, 31), (192, 22), (513, 9), (577, 8), (1000, 5), (1023, 4), (1100, 4), (1100, 3)])
+def test_updates_inside_outer_blocks(lib, n, batch):
+    """fp64 throughout: one update per diagonal block (rows x matrices from 4096 on) or one per finished block, in outer blocks of whole and ragged width."""
+    g = torch.Generator(device="cuda").manual_seed(n * 7 + batch)
+    x = torch.randn(batch, 2 * n, n, generator=g, device="cuda", dtype=torch.float64)
+    H = torch.stack([(m.T @ m) for m in x]).float()
+    ctx = lib.Context()
+    U = ctx.chol_inv_upper(H)
+    ctx.close()
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    for b in range(batch):
+        h = H[b].double()
+        h = h.triu() + h.triu(1).T
+        assert (U[b].tril(-1) == 0).all()
+        # condition numbers of 2n samples: below 40
+        assert ((U[b] @ h) @ U[b].T - eye).abs().max() <= 64 * 2.0 ** -53 * 40 * n ** 0.5
