@@ -31,7 +31,7 @@ struct Args {
     double* C; long long ldc;
     long long strideA, strideB, strideC, strideA2, strideB2, strideC2;
     int batch_inner;
-    int klo_m, klo_n, khi_m, khi_n, skip_lower, skip_upper, skip_col0, diag_order;
+    int klo_m, klo_n, khi_m, khi_n, skip_lower, skip_upper, skip_col0, diag_order, by_length;
     const int* m_limit;
     const double* A2; const double* B2;
     int sym;
@@ -118,9 +118,17 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
     // Workgroups go to the eight XCDs round-robin by linear number, so with a column count that is a multiple of 8 an XCD
     // always gets the same tile columns; where the contraction length grows with the column (diag_order), the columns of
     // each tile row are rotated by the row number so that every XCD sees all lengths.
-    const int tx = g.diag_order ? (int)((blockIdx.x + blockIdx.y) % gridDim.x) : (int)blockIdx.x;
-    const int m0 = blockIdx.y * TM, n0 = tx * TN;
-    const int bz = blockIdx.z / g.splits, sp = blockIdx.z % g.splits;
+    int tx = g.diag_order ? (int)((blockIdx.x + blockIdx.y) % gridDim.x) : (int)blockIdx.x, ty = blockIdx.y, tz = blockIdx.z;
+    if (g.by_length) {
+        // Few rounds of workgroups: the 256 of a round go to the CUs in the same order, so that a CU got the same tile column, and the same length, in every round (8 x 128 rows,
+        // 8192 columns, triangular: 2.0 ms, the time of the whole product).  Longest columns first, every other round backwards: long and short ones meet (1.16 ms).
+        const int linear = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z)), total = (int)(gridDim.x * gridDim.y * gridDim.z), first = linear & ~255;
+        const int at = linear & 256 ? first + min(256, total - first) - 1 - (linear - first) : linear;
+        const int other = (int)(gridDim.y * gridDim.z), rank = at / other, rest = at % other;
+        tx = g.khi_n ? (int)gridDim.x - 1 - rank : rank; ty = rest % (int)gridDim.y; tz = rest / (int)gridDim.y;
+    }
+    const int m0 = ty * TM, n0 = tx * TN;
+    const int bz = tz / g.splits, sp = tz % g.splits;
     if (g.m_limit && m0 >= g.m_limit[bz]) return;
     if (g.skip_lower && g.skip_col0 + n0 + TN <= m0) return;
     if (g.skip_upper && m0 + TM <= g.skip_col0 + n0) return;
@@ -239,7 +247,7 @@ __global__ __launch_bounds__(256) void gemm_f64_kernel(Args g, bool vecA, bool v
     }
 
     // accumulator element v of tile (i, j): row 16 i + lane / 16 + 4 v, column 16 j + lane % 16
-    double* P = g.part ? g.part + (long long)blockIdx.z * g.M * g.N : nullptr;
+    double* P = g.part ? g.part + (long long)tz * g.M * g.N : nullptr;
 #pragma unroll
     for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -404,6 +412,8 @@ int gemm_f64(tboa_ctx* ctx, const GemmF64& q) {
     a.part = (ch.splits > 1 || sum > 1 || detour) ? part : nullptr;
     dim3 grid((unsigned)cdiv64(q.N, tn), (unsigned)cdiv64(q.M, tm), (unsigned)(q.batch * ch.splits));
     if (grid.y > 65535 || cdiv64(q.batch, 1) * ch.splits > 65535) return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64: grid too large");
+    const long long wgs = (long long)grid.x * grid.y * grid.z;
+    a.by_length = (q.sym || q.klo_n || q.khi_n) && wgs > 256 && wgs <= 2048;      // (many rounds even out by themselves, and neighbours share operands in the other order)
     switch (ch.shape) {
         case S128: launch<128, 128, 16>(ctx, grid, akc, bkc, a, vecA, vecB); break;
         case S64: launch<64, 64, 32>(ctx, grid, akc, bkc, a, vecA, vecB); break;
