@@ -35,7 +35,7 @@ __device__ __forceinline__ double lane_value(double v, int lane) {      // of a 
 // they found from the tiles left of and above it.
 // 55 -> 28 us per 64 x 64 block (the kernel alone on the GPU) against a step with one barrier for every column of the factorisation and of the inverse.
 __global__ __launch_bounds__(256) void diag_factor_kernel(double* __restrict__ H, int n, int j0, int bs,
-                                                          double* __restrict__ dinv, int blk, int nblk, int* status) {
+                                                          double* __restrict__ dinv, int blk, int nblk, int* status, int b0) {
     typedef double v4d __attribute__((ext_vector_type(4)));
     constexpr int TP = NB + 1;                                             // odd pitch: 16 rows fall into different banks
     __shared__ double S[NB][TP], W[NB][TP];                                // the block, then V; the right-hand side I, then W = V^-1
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(256) void diag_factor_kernel(double* __restrict__ H
                 for (int r = 0; r < 16; ++r)
                     if (r < c) v[r] = __builtin_fma(-lane_value(v[r], c), f, v[r]);
             }
-            if (bad >= 0 && t == 0) { if (atomicCAS(&status[0], 0, 1 + j0 + 16 * q + bad) == 0) status[1] = b; }
+            if (bad >= 0 && t == 0) { if (atomicCAS(&status[0], 0, 1 + j0 + 16 * q + bad) == 0) status[1] = b0 + b; }
             const double dv = sqrt(piv), di = 1.0 / dv;
             if (lk == 0) {
                 dq[l16] = di;
@@ -220,9 +220,16 @@ int chol_status_f64(tboa_ctx* ctx, int status_slot) {
 // Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores
 static bool chol_rns_pays(int n, int batch) { return n >= 2048 && (long long)n * n * batch >= 3072LL * 3072; }
 
+// Matrices at a time: 30 bytes of residues per element, 8 GB or 8 matrices (40 of 5120 at once would take another 31 GB beside the 55 of a layer's fp64 matrices)
+static int chol_rns_batch(int n, int batch) {
+    const int64_t most = std::max<int64_t>(8, (1LL << 28) / ((long long)n * n));
+    return (int)cdiv64(batch, cdiv64(batch, most));
+}
+
 void chol_rns_plan(int n, int batch, Arena& ar, CholRns& w) {
     w = CholRns{};
     if (!chol_rns_pays(n, batch)) return;
+    batch = chol_rns_batch(n, batch);
     auto operand = [&]() {
         RnsOperand o{};
         o.kpad = rns_pad(n); o.plane = rns_plane(n, n); o.stride = (long long)(TB_RNS_MODULI * o.plane); o.p = ar.get<signed char>(TB_RNS_MODULI * o.plane * batch);
@@ -243,7 +250,7 @@ void chol_rns_plan(int n, int batch, Arena& ar, CholRns& w) {
 static bool factor_left(int J1, int batch) { return (long long)J1 * batch >= 4096; }
 
 // The columns J0 .. J1 of V: diagonal blocks of NB columns, the panels above them, and their updates of the other columns of the same outer block
-static int factor_columns(tboa_ctx* ctx, int n, int batch, double* H, double* dinv, int J0, int J1, int* status) {
+static int factor_columns(tboa_ctx* ctx, int n, int batch, double* H, double* dinv, int J0, int J1, int* status, int b0) {
     const int nblk = (n + NB - 1) / NB;
     const long long nn = (long long)n * n, dstride = (long long)nblk * NB * NB;
     const bool left = factor_left(J1, batch);
@@ -258,7 +265,7 @@ static int factor_columns(tboa_ctx* ctx, int n, int batch, double* H, double* di
             u.batch = batch; u.strideA = nn; u.strideB = nn; u.strideC = nn;
             TB_TRY(gemm_f64(ctx, u));
         }
-        hipLaunchKernelGGL(diag_factor_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, n, j0, bs, dinv, blk, nblk, status);
+        hipLaunchKernelGGL(diag_factor_kernel, dim3(batch), dim3(256), 0, ctx->stream, H, n, j0, bs, dinv, blk, nblk, status, b0);
         TB_KERNEL_CHECK(ctx);
         if (j0 == 0) break;
         // panel: V[0:j0, blk] = H[0:j0, blk] Vinv_jj^T   (in place: one column tile, each workgroup owns its rows)
@@ -313,7 +320,7 @@ static int invert_diagonal_blocks(tboa_ctx* ctx, int n, int batch, const double*
 // update over all columns behind it (right-looking updates of 512 terms each run no faster than in fp64: 1.15 ms for 8192 x 8192 x 512 either way):
 //     V: H[0:J1, J0:J1] -= V[0:J1, J1:n] V[J0:J1, J1:n]^T, the rows of V in residues once, their norms known from H's diagonal
 //     U: U[ob, J1:n] = -U[ob, ob] (V[ob, J1:n] U[J1:n, J1:n]), from the last rows up; the columns of U in residues as they grow
-static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, double* tmp, double* dinv, int* status, const CholRns& w) {
+static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, double* tmp, double* dinv, int* status, int b0, const CholRns& w) {
     constexpr int OB = TB_FACT_OB;
     const int nblk = (n + NB - 1) / NB, nob = (n + OB - 1) / OB, TL = chol_tmp_pitch(n);
     const long long nn = (long long)n * n;
@@ -327,7 +334,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
             g.alpha = -1.0; g.beta = 1.0; g.C = H + J0; g.ldc = n; g.strideC = nn;
             TB_TRY(rns_gemm(ctx, g));
         }
-        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status));
+        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status, b0));
         if (J0 > 0) {
             RnsSource v{};
             v.a = H + J0; v.ld = n; v.stride = nn; v.kc = 1; v.rows = J0; v.k = J1 - J0;
@@ -378,13 +385,14 @@ int chol_inv_upper_f64(tboa_ctx* ctx, int n, int batch, double* H, double* U, do
     hipLaunchKernelGGL(clear_status_kernel, dim3(1), dim3(64), 0, ctx->stream, status);
     TB_KERNEL_CHECK(ctx);
     if (rns && rns->V.p) {
-        TB_TRY(chol_inv_rns(ctx, n, batch, H, U, tmp, dinv, status, *rns));
+        for (int b0 = 0, per = chol_rns_batch(n, batch); b0 < batch; b0 += per)
+            TB_TRY(chol_inv_rns(ctx, n, std::min(per, batch - b0), H + b0 * nn, U + b0 * nn, tmp + (long long)b0 * n * TL, dinv + (long long)b0 * nblk * NB * NB, status, b0, *rns));
         return defer_status ? 0 : chol_status_f64(ctx, status_slot);
     }
     // ---- H = V V^T from the last column to the first
     for (int ob = nob - 1; ob >= 0; --ob) {
         const int J0 = ob * OB, J1 = (J0 + OB < n) ? J0 + OB : n;
-        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status));
+        TB_TRY(factor_columns(ctx, n, batch, H, dinv, J0, J1, status, 0));
         if (J0 > 0) {   // H[0:J0, 0:J0] -= V[0:J0, ob] V[0:J0, ob]^T  (upper part)
             GemmF64 s{};
             s.M = J0; s.N = J0; s.K = J1 - J0; s.alpha = -1.0; s.beta = 1.0;

@@ -120,3 +120,20 @@ def test_updates_inside_outer_blocks(lib, n, batch):
         assert (U[b].tril(-1) == 0).all()
         # condition numbers of 2n samples: below 40
         assert ((U[b] @ h) @ U[b].T - eye).abs().max() <= 64 * 2.0 ** -53 * 40 * n ** 0.5
+
+
+def test_more_matrices_than_residues_hold(lib):
+    """Residues of 64 matrices of order 2048 at a time: 65 go in two runs, and a breakdown names its matrix."""
+    n = 2048
+    g = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn(2 * n, n, generator=g, device="cuda")
+    H = (x.T @ x)[None] * torch.arange(1, 66, device="cuda", dtype=torch.float32)[:, None, None].sqrt()
+    ctx = lib.Context()
+    U = ctx.chol_inv_upper(H)
+    eye = torch.eye(n, dtype=torch.float64, device="cuda")
+    for b in (0, 31, 32, 33, 64):
+        assert ((U[b] @ H[b].double()) @ U[b].T - eye).abs().max() <= 64 * 2.0 ** -53 * 40 * n ** 0.5
+    H[50, 900, 900] = -1.0
+    with pytest.raises(lib.TurboBoAError, match="Hessian 50 .* pivot 900 is not positive"):
+        ctx.chol_inv_upper(H)
+    ctx.close()
