@@ -869,72 +869,116 @@ __global__ __launch_bounds__(256) void cd_head_kernel(const double* __restrict__
 // g = 0 .. ng-1, and Q = sum over (k, g') of s[k, g'] Wbar[k, G'] (rows masked to one group).  With
 //   Cg[g][g'][j][k] = Wbar[j, G] H_in[G, G'] Wbar[k, G']^T      Fg[g][j][k] = Wbar[j, G] (W (H_in - R))[k, G]^T
 // the step is  s[j, g] += sum_k Ho[k, j] (Fg[g][j][k] - sum_g' s[k, g'] Cg[g][g'][j][k]) / (Cg[g][g][j][j] Ho[j, j]).
-// While the groups of row j are visited only the scales of row j itself change, so the numerators of all its groups are summed at
-// once with the scales as they stand when the row begins, and a short recurrence over the groups then takes out what the steps before
-// have changed: num[g] -= Ho[j, j] Cg[g][g'][j][j] (change of s[j, g']), g' < g.  d_h long sums instead of d_h n_groups dependent
-// ones: bound by reading Cg once (n_groups^2 d_h^2 doubles per head) at the rate of one CU per head.  40 heads of 128 rows and 40
-// groups: 54 ms with one sum per (row, group), 6.7 ms this way.
-// One workgroup of 16 wavefronts per head; the scales of the head (by group) live in LDS, and where they leave room the numerators and column j
-// of H_out (lds & 1; else num_mem and H_out itself) and the diagonals Cg[g][g'][j][j] (lds & 2; else read from memory).
-__global__ __launch_bounds__(1024) void cd_group_head_kernel(const double* __restrict__ Fg, const double* __restrict__ Cg,
-                                                             const double* __restrict__ Ho, int dh, int ng, int iters, int lds,
-                                                             double* __restrict__ num_mem, double* __restrict__ s_all) {
-    extern __shared__ double sh[];
-    const bool cd_lds = lds & 2, hoj_lds = lds & 1;
-    double* s = sh; double* hoj = s + (size_t)dh * ng; double* cd = hoj + dh + ng;     // s[g dh + k]
-    double* num = hoj_lds ? hoj + dh : num_mem + (long long)blockIdx.x * ng;
-    const int h = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6;
+// While the groups of row j are visited only the scales of row j itself change, so the numerators of all its groups are summed at once with the scales as they stand when the row
+// begins, and a short recurrence over the groups then takes out what the steps before have changed: num[g] -= Ho[j, j] Cg[g][g'][j][j] (change of s[j, g']), g' < g.  The same goes for
+// blocks of up to 16 rows: cd_group_sums_kernel sums the numerators of a block's rows over the whole chip with the scales as they stand when the block begins (it reads all of Cg, 8.4 GB
+// for 40 heads of 128 rows and 40 groups), and in cd_group_chain_kernel, one workgroup per head, a row takes out what the rows of the block before it have changed, which needs 16
+// columns of Cg at most.  (All sums in one kernel of a workgroup per head, at the rate of one CU each: 6.7 ms for these sizes; 1.8 + 1.5 this way.)
+constexpr int CD_ROWS = 16;
+
+// num0[h][j - j0][g] = sum_k Ho[k, j] (Fg[g][j][k] - sum_g' s[k, g'] Cg[g][g'][j][k]): a workgroup per (group, head) and share of the rows, a wavefront per row; the head's scales in LDS
+__global__ __launch_bounds__(256) void cd_group_sums_kernel(const double* __restrict__ Fg, const double* __restrict__ Cg, const double* __restrict__ Ho, int dh, int ng, int j0, int nj,
+                                                            int pitch, const double* __restrict__ s_all, double* __restrict__ num0) {
+    extern __shared__ double s[];      // s[g pitch + k]
+    const int g = blockIdx.x, h = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const long long rr = (long long)dh * dh;
-    const double* Fh = Fg + (long long)h * ng * rr; const double* Ch = Cg + (long long)h * ng * ng * rr;
     const double* Hh = Ho + (long long)h * rr;
-    double* sg = s_all + (long long)h * dh * ng;
-    for (int i = t; i < dh * ng; i += 1024) s[(i % ng) * dh + i / ng] = sg[i];
-    for (int it = 0; it < iters; ++it)
-        for (int j = 0; j < dh; ++j) {
-            __syncthreads();
-            if (hoj_lds) for (int k = t; k < dh; k += 1024) hoj[k] = Hh[(long long)k * dh + j];
-            __syncthreads();
-            for (int g = wave; g < ng; g += 16) {
-                const double* F = Fh + ((long long)g * dh + j) * dh; const double* C = Ch + ((long long)g * ng * dh + j) * dh;
-                double acc = 0.0;
-                for (int k = lane; k < dh; k += 64) {
-                    double a = F[k];
-                    int g2 = 0;
-                    for (; g2 + 8 <= ng; g2 += 8) {
-                        double c[8];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) c[u] = C[(g2 + u) * rr + k];
-#pragma unroll
-                        for (int u = 0; u < 8; ++u) {
-                            a -= s[(g2 + u) * dh + k] * c[u];
-                            if (cd_lds && k == j) cd[g * ng + g2 + u] = c[u];
-                        }
-                    }
-                    for (; g2 < ng; ++g2) {
-                        const double c = C[g2 * rr + k];
-                        a -= s[g2 * dh + k] * c;
-                        if (cd_lds && k == j) cd[g * ng + g2] = c;
-                    }
-                    acc += a * (hoj_lds ? hoj[k] : Hh[(long long)k * dh + j]);
-                }
-                acc = wave_sum(acc);
-                if (lane == 0) num[g] = acc;
-            }
-            __syncthreads();
-            if (wave == 0) {       // the recurrence over the groups of row j
-                const double hjj = Hh[(long long)j * dh + j];
-                for (int g = 0; g < ng; ++g) {
-                    const double den = (cd_lds ? cd[g * ng + g] : Ch[((long long)(g * ng + g) * dh + j) * dh + j]) * hjj;
-                    const double step = den > 0.0 ? num[g] / den : 0.0;
-                    for (int g2 = g + 1 + lane; g2 < ng; g2 += 64)
-                        num[g2] -= hjj * (cd_lds ? cd[g2 * ng + g] : Ch[((long long)(g2 * ng + g) * dh + j) * dh + j]) * step;
-                    if (lane == 0) s[g * dh + j] += step;
-                    __builtin_amdgcn_wave_barrier();
-                }
-            }
-        }
+    const double* sg = s_all + (long long)h * dh * ng;
+    for (int i = threadIdx.x; i < dh * ng; i += 256) s[(i % ng) * pitch + i / ng] = sg[i];
     __syncthreads();
-    for (int i = t; i < dh * ng; i += 1024) sg[i] = s[(i % ng) * dh + i / ng];
+    for (int jj = blockIdx.z * 4 + wave; jj < nj; jj += 4 * gridDim.z) {
+        const int j = j0 + jj;
+        const double* F = Fg + (((long long)h * ng + g) * dh + j) * dh; const double* C = Cg + (((long long)h * ng + g) * ng * dh + j) * dh;
+        double acc = 0.0;
+        for (int k = lane; k < dh; k += 64) {
+            double a = F[k];
+            int g2 = 0;
+            for (; g2 + 8 <= ng; g2 += 8) {
+                double c[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) c[u] = C[(g2 + u) * rr + k];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a -= s[(g2 + u) * pitch + k] * c[u];
+            }
+            for (; g2 < ng; ++g2) a -= s[g2 * pitch + k] * C[g2 * rr + k];
+            acc += a * Hh[(long long)k * dh + j];
+        }
+        acc = wave_sum(acc);
+        if (lane == 0) num0[((long long)h * CD_ROWS + jj) * ng + g] = acc;
+    }
+}
+
+__device__ __forceinline__ double lane_of(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// The rows j0 .. j0 + nj of a head one after the other.  LDS: ds[g nj + row of the block], the changes of the block's scales so far; where they fit beside it the numerators
+// (lds & 1; else num_mem) and the diagonals Cg[g][g'][j][j] (lds & 2; else read from memory)
+__global__ __launch_bounds__(1024) void cd_group_chain_kernel(const double* __restrict__ Cg, const double* __restrict__ Ho, int dh, int ng, int j0, int nj, int lds,
+                                                              const double* __restrict__ num0, double* __restrict__ num_mem, double* __restrict__ s_all) {
+    extern __shared__ double sh[];
+    const int h = blockIdx.x, t = threadIdx.x, lane = t & 63, wave = t >> 6, kk = lane & 15;
+    const bool cd_lds = lds & 2;
+    double* ds = sh; double* num = lds & 1 ? ds + (size_t)nj * ng : num_mem + (long long)h * ng; double* cd = ds + (size_t)(nj + 1) * ng;
+    const long long rr = (long long)dh * dh;
+    const double* Ch = Cg + (long long)h * ng * ng * rr; const double* Hh = Ho + (long long)h * rr;
+    double* sg = s_all + (long long)h * dh * ng;
+    for (int jj = 0; jj < nj; ++jj) {
+        const int j = j0 + jj;
+        const double hkj = kk < jj ? Hh[(long long)(j0 + kk) * dh + j] : 0.0, hjj = Hh[(long long)j * dh + j];
+        for (int g = wave; g < ng; g += 16) {
+            // lanes: 16 rows of the block, 4 groups
+            const double* C = Ch + ((long long)g * ng * dh + j) * dh + j0 + kk;
+            const double start = num0[((long long)h * CD_ROWS + jj) * ng + g];
+            double acc = 0.0;
+            if (kk < jj || (cd_lds && kk == jj)) {
+                int g2 = lane >> 4;
+                for (; g2 + 28 < ng; g2 += 32) {
+                    double c[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) c[u] = C[(g2 + 4 * u) * rr];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        if (kk < jj) acc += ds[(g2 + 4 * u) * nj + kk] * c[u];
+                        else cd[g * ng + g2 + 4 * u] = c[u];
+                    }
+                }
+                for (; g2 < ng; g2 += 4) {
+                    const double c = C[g2 * rr];
+                    if (kk < jj) acc += ds[g2 * nj + kk] * c;
+                    else cd[g * ng + g2] = c;
+                }
+            }
+            acc = wave_sum(acc * hkj);
+            if (lane == 0) num[g] = start - acc;
+        }
+        __syncthreads();
+        // the recurrence over the groups of row j.  A numerator per lane where they and the diagonals allow: every lane divides its own (a reciprocal, and the quotient's remainder
+        // once more), the group whose turn it is passes its step on
+        if (wave == 0 && cd_lds && ng <= 64) {
+            const int own = min(lane, ng - 1);
+            const double den = cd[own * ng + own] * hjj, inv = den > 0.0 ? 1.0 / den : 0.0;
+            double x = lane < ng ? num[lane] : 0.0, mine = 0.0;
+            for (int g = 0; g < ng; ++g) {
+                const double c = hjj * cd[g * ng + own];      // (the diagonals of Cg[g][g'] and Cg[g'][g] are the same)
+                const double q = x * inv, step = lane_of(den > 0.0 ? __builtin_fma(__builtin_fma(-q, den, x), inv, q) : 0.0, g);
+                if (lane == g) mine = step;
+                if (lane > g) x = __builtin_fma(-c, step, x);
+            }
+            if (lane < ng) { ds[lane * nj + jj] = mine; sg[(long long)j * ng + lane] += mine; }
+        } else if (wave == 0) {
+            for (int g = 0; g < ng; ++g) {
+                const double den = (cd_lds ? cd[g * ng + g] : Ch[((long long)(g * ng + g) * dh + j) * dh + j]) * hjj;
+                const double step = den > 0.0 ? num[g] / den : 0.0;
+                for (int g2 = g + 1 + lane; g2 < ng; g2 += 64)
+                    num[g2] -= hjj * (cd_lds ? cd[g2 * ng + g] : Ch[((long long)(g2 * ng + g) * dh + j) * dh + j]) * step;
+                if (lane == 0) ds[g * nj + jj] = step;
+                __builtin_amdgcn_wave_barrier();
+            }
+            for (int g = lane; g < ng; g += 64) sg[(long long)j * ng + g] += ds[g * nj + jj];
+        }
+        __syncthreads();
+    }
 }
 
 // Cg[h][g'][g] = Cg[h][g][g']^T for g' < g, 64 x 64 pieces through LDS; grid.x runs over (pair, piece), grid.z over the heads.  Bound by memory: 40 heads, 40 groups,
@@ -1627,12 +1671,24 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                 hipLaunchKernelGGL(cd_group_mirror_kernel, dim3((unsigned)(tiles * ng * (ng - 1) / 2), 1, nh), dim3(256), 0, st, L.Cg, dh, ng);
                 TB_KERNEL_CHECK(ctx);
             }
-            const size_t room = 160 * 1024 / sizeof(double), scales = (size_t)dh * ng, small = (size_t)dh + ng, diag = (size_t)ng * ng;
+            const size_t room = 160 * 1024 / sizeof(double), scales = (size_t)dh * ng;
             if (scales + dh + 8 > room) return tboa_fail(ctx, TBOA_EINVAL, "quantize_layer: %d scales per head exceed the LDS of the group-wise refinement", dh * ng);
-            const int lds = scales + small + diag <= room ? 3 : scales + small <= room ? 1 : 0;
-            const size_t smem = (scales + (lds & 1 ? small : 0) + (lds & 2 ? diag : 0)) * sizeof(double);
-            TB_HIP(ctx, hipFuncSetAttribute((const void*)cd_group_head_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
-            hipLaunchKernelGGL(cd_group_head_kernel, dim3(nh), dim3(1024), smem, st, L.Fg, L.Cg, L.Ho, dh, ng, d->cd_iters, lds, L.cdnum, L.s64);
+            const int pitch = scales + ng <= room ? dh + 1 : dh;      // (an odd pitch: lanes store consecutive groups)
+            const int B = (int)std::max<size_t>(1, std::min<size_t>(std::min(CD_ROWS, dh), room / ng - 1));
+            const size_t ds = (size_t)B * ng, smem_sums = (size_t)pitch * ng * sizeof(double);
+            const int lds = ds + ng + (size_t)ng * ng <= room ? 3 : ds + ng <= room ? 1 : 0;
+            const size_t smem = (ds + (lds & 1 ? ng : 0) + (lds & 2 ? (size_t)ng * ng : 0)) * sizeof(double);
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)cd_group_sums_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_sums));
+            TB_HIP(ctx, hipFuncSetAttribute((const void*)cd_group_chain_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
+            double* num0 = L.cdnum + (size_t)nh * ng;
+            const int shares = (long long)nh * ng < 512 ? 4 : 1;
+            for (int it = 0; it < d->cd_iters; ++it)
+                for (int j0 = 0; j0 < dh; j0 += B) {
+                    const int nj = std::min(B, dh - j0);
+                    hipLaunchKernelGGL(cd_group_sums_kernel, dim3(ng, nh, shares), dim3(256), smem_sums, st, L.Fg, L.Cg, L.Ho, dh, ng, j0, nj, pitch, L.s64, num0);
+                    hipLaunchKernelGGL(cd_group_chain_kernel, dim3(nh), dim3(1024), smem, st, L.Cg, L.Ho, dh, ng, j0, nj, lds, num0, L.cdnum, L.s64);
+                    TB_KERNEL_CHECK(ctx);
+                }
         } else {
             const size_t smem = (size_t)4 * ng * sizeof(double);
             hipLaunchKernelGGL(cd_group_diag_kernel, dim3((rows_all + 3) / 4), dim3(256), smem, st, L.Fg, L.Cg, (long long)rows_all, ng,
@@ -1886,7 +1942,7 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
         const size_t ng = (size_t)L.ng;
         L.Cg = ar.get<double>(H_out ? (size_t)nh * ng * ng * dh * dh : (size_t)d->d_out * ng * ng);
         L.Fg = ar.get<double>(H_out ? (size_t)nh * ng * dh * dh : (size_t)d->d_out * ng);
-        L.cdnum = H_out ? ar.get<double>((size_t)nh * ng) : nullptr;
+        L.cdnum = H_out ? ar.get<double>((size_t)nh * ng * (CD_ROWS + 1)) : nullptr;
     }
 }
 
