@@ -217,8 +217,8 @@ int chol_status_f64(tboa_ctx* ctx, int status_slot) {
     return 0;
 }
 
-// Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores
-static bool chol_rns_pays(int n, int batch) { return n >= 2048 && (long long)n * n * batch >= 3072LL * 3072; }
+// Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores; the longest of them contract over n - 512 columns
+static bool chol_rns_pays(int n, int batch) { return n >= 2048 && (long long)n * n * batch >= 3072LL * 3072 && rns_takes(n, TB_FACT_OB, n - TB_FACT_OB); }
 
 // Matrices at a time: 30 bytes of residues per element, 8 GB or 8 matrices (40 of 5120 at once would take another 31 GB beside the 55 of a layer's fp64 matrices)
 static int chol_rns_batch(int n, int batch) {

@@ -536,6 +536,7 @@ int rns_moduli(double bits) {
     for (int p = 0; p < NMAX; ++p) { have += log2((double)MODULI[p]); if (have >= bits + 1.5) return p + 1; }
     return 0;
 }
+bool rns_takes(int M, int N, int K) { return K <= 32768 && cdiv64(M, BM) * cdiv64(N, BN) <= 65535; }
 int rns_pad(int k) { return (k + KPAD - 1) / KPAD * KPAD; }
 size_t rns_plane(int rows, int k) { return (size_t)((rows + 15) / 16 * 16) * rns_pad(k); }
 size_t rns_squares_elems(int rows) { return (size_t)3 * rows; }
@@ -633,7 +634,7 @@ double rns_prepare_us(int rows, int k) { return 12.0 + (double)rows * k * (16.0 
 int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     if (q.M <= 0 || q.N <= 0) return 0;
     const int K = rns_pad(q.K);
-    if (!q.A || !q.B || !q.C || !q.residues || q.K <= 0 || K > 32768 || q.nm < 1 || q.nm > NMAX || q.a_row % 16 || q.b_row % 16 || q.a_k % SK || q.b_k % SK ||
+    if (!q.A || !q.B || !q.C || !q.residues || q.K <= 0 || !rns_takes(q.M, q.N, K) || q.nm < 1 || q.nm > NMAX || q.a_row % 16 || q.b_row % 16 || q.a_k % SK || q.b_k % SK ||
         q.a_k + (q.B2 ? 2 : 1) * K > q.A->kpad || q.b_k + K > q.B->kpad || (size_t)(q.a_row + cdiv64(q.M, 16) * 16) * q.A->kpad > q.A->plane ||
         (size_t)(q.b_row + cdiv64(q.N, 16) * 16) * q.B->kpad > q.B->plane || (q.B2 && (q.K % KPAD || q.B2->kpad != q.B->kpad || q.B2->plane != q.B->plane || q.B2->stride != q.B->stride)))
         return tboa_fail(ctx, TBOA_EINVAL, "rns_gemm: unsupported product");
@@ -651,7 +652,7 @@ int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     const long long items = tiles * a.splits;
     a.chunk = (int)std::max<long long>(1, std::min<long long>(32, cdiv64(items, 8)));
     const long long wgs = cdiv64(items, 8LL * a.chunk) * 8 * a.chunk;
-    if (wgs > 0x7fffffffLL || (long long)a.tiles_m * a.tiles_n > 65535 || q.batch > 65535) return tboa_fail(ctx, TBOA_EINVAL, "rns_gemm: grid too large");
+    if (wgs > 0x7fffffffLL || q.batch > 65535) return tboa_fail(ctx, TBOA_EINVAL, "rns_gemm: grid too large");
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on && q.tag >= 0) {
         double macs = 0.0;
@@ -682,8 +683,7 @@ int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
 extern "C" int tboa_gemm_f64_residues(tboa_ctx* ctx, int M, int N, int K, double alpha, const double* A, int64_t lda, const double* B, int64_t sbk, int64_t sbn, double beta, double* C,
                                       int64_t ldc) {
     if (!ctx) return TBOA_EINVAL;
-    if (M <= 0 || N <= 0 || K <= 0 || K > 32768 || !A || !B || !C || lda < K || ldc < N || !((sbk == 1 && sbn >= K) || (sbn == 1 && sbk >= N)) ||
-        cdiv64(M, 256) * cdiv64(N, 256) > 65535)
+    if (M <= 0 || N <= 0 || K <= 0 || !rns_takes(M, N, K) || !A || !B || !C || lda < K || ldc < N || !((sbk == 1 && sbn >= K) || (sbn == 1 && sbk >= N)))
         return tboa_fail(ctx, TBOA_EINVAL, "gemm_f64_residues: bad arguments");
     for (int pass = 0; pass < 2; ++pass) {
         Arena ar(pass ? ctx->ws : nullptr);

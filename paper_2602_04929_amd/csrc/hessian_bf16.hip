@@ -1033,7 +1033,7 @@ struct WideResidues { RnsOperand h, w; unsigned char* res; };      // h.p null: 
 // 1.12 -> 1.03, 17e9 (4096 x 2048) 1.96 -> 1.77, 137e9 (8192 x 4096) 8.6 -> 7.1, 618e9 (9216 x 8192) 18.3 -> 13.4; few rows do not repay the preparation of H_in (n^2 elements).
 WideResidues plan_wide_residues(int rows, int n, Arena& ar, size_t from) {
     WideResidues r{};
-    if (n > 32768 || rows < n / 4 || (double)rows * n * n < 3e9) return r;
+    if (!rns_takes(rows, n, n) || rows < n / 4 || (double)rows * n * n < 3e9) return r;
     Arena a(ar.base);
     a.off = from;
     auto operand = [&](int m) {

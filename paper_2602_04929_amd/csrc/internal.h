@@ -143,6 +143,7 @@ int rns_pad(int k);
 size_t rns_plane(int rows, int k);
 size_t rns_squares_elems(int rows);
 size_t rns_residue_bytes(int M, int N, int batch, int nm);
+bool rns_takes(int M, int N, int K);      // what rns_gemm can do: sums of K terms (two operands' worth of them) within 32 bits and the quotients' 22, tiles within a grid
 // operand whose rows are contiguous (second: a second source right after the first along k): exponents, `bits` below the norm each, and residues; bits RNS_INTEGERS: small
 // integers, taken as they are (no exponents); RNS_GIVEN: the operand's exponents stand already
 constexpr int RNS_INTEGERS = -1, RNS_GIVEN = -2;

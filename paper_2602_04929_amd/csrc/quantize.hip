@@ -1817,7 +1817,7 @@ RnsNeeds rns_needs(int products, bool R) {
 int rns_choice(const Layer& L, bool H_out, bool R) {
     const tboa_layer_desc* d = L.d;
     const int n = L.n, rows = d->d_out;
-    if (L.nhin > 1 || n < SWEEP_SP || n > 32768) return 0;
+    if (L.nhin > 1 || n < SWEEP_SP || !rns_takes(8192, n, n)) return 0;
     const int blk = d->block < L.dh ? d->block : L.dh, steps = (L.dh + blk - 1) / blk, step_rows = L.nh * blk;
     const double half = d->group ? 1.0 : 0.5;      // of a product with H_in
     const int nm_int = rns_moduli(log2(L.maxq * sqrt((double)n)) + RNS_BITS_B), all = TB_RNS_MODULI;
