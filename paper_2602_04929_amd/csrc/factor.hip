@@ -237,7 +237,7 @@ void chol_rns_plan(int n, int batch, Arena& ar, CholRns& w) {
         return o;
     };
     w.V = operand(); w.U = operand();
-    w.res = ar.get<unsigned char>(rns_residue_bytes(n, TB_FACT_OB, batch, TB_RNS_MODULI));
+    w.res = ar.get<unsigned char>(rns_residue_bytes(n, TB_FACT_OB, batch));
     w.sq = ar.get<double>(rns_squares_elems(n) * batch); w.panel = ar.get<double>(rns_squares_elems(n) * batch);
     w.part = ar.get<double>(RNS_CHUNKS * rns_squares_elems(n) * batch); w.grown = ar.get<int>((size_t)n * batch);
     if (!ar.base) w.V.p = nullptr;
@@ -326,7 +326,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
     const long long nn = (long long)n * n;
     TB_TRY(rns_diagonal_exps(ctx, n, batch, H, RNS_BITS_A, w.V.e, w.sq, 3LL * n));
     RnsGemm g{};
-    g.batch = batch; g.nm = TB_RNS_MODULI; g.residues = w.res;
+    g.batch = batch; g.residues = w.res;
     for (int ob = nob - 1; ob >= 0; --ob) {
         const int J0 = ob * OB, J1 = std::min(n, J0 + OB);
         if (J1 < n) {
@@ -339,7 +339,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
             RnsSource v{};
             v.a = H + J0; v.ld = n; v.stride = nn; v.kc = 1; v.rows = J0; v.k = J1 - J0;
             TB_TRY(rns_row_guard(ctx, v, batch, RNS_BITS_A, w.V, w.sq, 3LL * n));
-            TB_TRY(rns_rows(ctx, v, nullptr, batch, RNS_GIVEN, w.V, TB_RNS_MODULI, J0));
+            TB_TRY(rns_rows(ctx, v, nullptr, batch, RNS_GIVEN, w.V, J0));
         }
     }
     TB_TRY(launch_fill_f64(ctx, U, (int64_t)batch * nn, 0.0));
@@ -371,7 +371,7 @@ static int chol_inv_rns(tboa_ctx* ctx, int n, int batch, double* H, double* U, d
         RnsOperand u = w.U;
         u.p += (long long)(J0 >> 4) * u.kpad * 16; u.e += J0;
         p.k = n - J0;
-        TB_TRY(rns_columns(ctx, p, batch, u, J0, TB_RNS_MODULI, w.grown + J0, width));
+        TB_TRY(rns_columns(ctx, p, batch, u, J0, w.grown + J0, width));
     }
     return 0;
 }

@@ -7,7 +7,9 @@
 //
 // Error.  The sums are exact, what is rounded is the operands: 0.29 units an entry (root mean square), so that C is off by 0.41 x 2^-57 |a| |b| at most at the
 // unfavourable ends of the powers of two, plus the rounding of the result.  An fp64 product rounds every partial sum: 0.3 x 2^-53 |a| |b| over terms of random sign whatever
-// their number, more where they have one sign.  An operand of small integers (|a|_2 up to 2^int_bits) enters as it is, and fewer moduli hold the product.
+// their number, more where they have one sign.
+// What the error is measured against are norms, not sum |a_k b_k|: contractions over channels of very different size take the sizes out by powers of two per channel, half of
+// them on either side (rns_channel_exps), and what no product reads does not count in a norm (RnsSource::before).
 //
 //   rns_rows, rns_columns  powers of two of the rows, residues: one plane of signed bytes per modulus in the blocks of 16 rows x 64 bytes that the product copies into LDS
 //   rns_gemm_kernel        one output tile through all (or some) moduli per workgroup
@@ -38,11 +40,16 @@ __device__ __forceinline__ void add_square(Squares& s, double v) {
     s.mid += b || t ? 0.0 : q; s.big += b ? q : 0.0; s.tiny += t ? q : 0.0;      // (an undefined entry is none of the two)
 }
 
-// what an element that is stored as v counts
-__device__ __forceinline__ double scaled(const RnsSource& s, double v, int r, int k, int shift) {
+// what an element that is stored as v counts, and its power of two
+__device__ __forceinline__ double counted(const RnsSource& s, double v, int r, int k) {
     if (s.half) v = k > r ? 0.0 : k < r ? v + v : v;
-    if (s.kexp) shift += s.ksign * s.kexp[k];
-    return (s.kexp || s.exp_shift) ? ldexp(v, shift) : v;
+    if (s.before && k >= r - r % s.before) v = 0.0;
+    return v;
+}
+__device__ __forceinline__ int power(const RnsSource& s, int k, int shift) { return s.kexp ? shift + s.ksign * s.kexp[k] : shift; }
+__device__ __forceinline__ double scaled(const RnsSource& s, double v, int r, int k, int shift) {
+    v = counted(s, v, r, k);
+    return (s.kexp || s.exp_shift) ? ldexp(v, power(s, k, shift)) : v;
 }
 __device__ __forceinline__ int shift_of(const RnsSource& s) { return s.exp_shift ? s.ksign * s.exp_shift[0] : 0; }
 
@@ -80,6 +87,50 @@ __global__ __launch_bounds__(256) void rns_exps_kernel(int rows, const double* _
     if (r >= rows) return;
     const double* p = sq + blockIdx.z * sq_stride + r;
     e[blockIdx.z * e_stride + r] = row_exponent(p[0], p[rows], p[2 * rows], bits);
+}
+
+// size[k]: half the exponent of H_kk, the size of channel k
+__global__ __launch_bounds__(256) void rns_channel_sizes_kernel(const double* __restrict__ H, int n, int* __restrict__ size) {
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= n) return;
+    const double v = H[(long long)k * n + k];
+    size[k] = v > 0.0 && v < INFINITY ? ilogb(v) >> 1 : 0;
+}
+// Powers of two for a contraction over channels k between a weight's columns (sq: their squares in the three ranges) and rows of size 2^right[k]: the right operand times 2^x[k] and the
+// left one times 2^-x[k] are of one size in every channel, where |a| |b| is least and next to sum |a_k b_k|.  Later rows and columns of a layer also carry what compensation for the
+// others has added, which goes with 1 / 2^size[k], the channel's size: a column counts as no less than 2^-6 of the root mean square of column x size, over its own size.
+// (Weights falling from 1e2 to 1e-2 as the channels grow from 1e-2 to 1e2: 2^-55 of sum |w h| instead of 2^-48, from 1e4 and 1e-4: 2^-55 instead of 2^-36; fp64 products 2^-51 - 2^-54.)
+// One workgroup: n words in, n words out.
+__global__ __launch_bounds__(1024) void rns_channel_exps_kernel(int n, const double* __restrict__ sq, const int* __restrict__ size, const int* right, int* x) {      // (right may be x)
+    __shared__ double red[16];
+    __shared__ int top_s;
+    constexpr int NONE = -(1 << 28);      // nothing in the column, or something undefined
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto left_of = [&](int k) {
+        const double m = sq[k], b = sq[n + k], t = sq[2LL * n + k];
+        const int e = row_exponent(m, b, t, 0);
+        return m + b + t > 0.0 && e != UNDEFINED ? e : NONE;
+    };
+    if (threadIdx.x == 0) top_s = NONE;
+    __syncthreads();
+    int top = NONE;
+    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NONE) top = max(top, l + size[k]); }
+    atomicMax(&top_s, top);
+    __syncthreads();
+    top = top_s;
+    double sum = 0.0;
+    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NONE) sum += ldexp(1.0, 2 * (l + size[k] - top)); }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    if (lane == 0) red[wave] = sum;
+    __syncthreads();
+    sum = 0.0;
+    for (int w = 0; w < 16; ++w) sum += red[w];
+    const int least = top == NONE ? NONE : top + (ilogb(sum / n) >> 1) - 6;
+    for (int k = threadIdx.x; k < n; k += 1024) {
+        const int r = right[k], l = least == NONE ? NONE : max(left_of(k), least - size[k]);
+        x[k] = l == NONE || r == UNDEFINED ? 0 : min(max((l - r) >> 1, -900), 900);
+    }
 }
 
 // Two pairs of operands of one product, A1 B1 + A2 B2, share the powers of two of their rows: B2 times 2^f (A2 times 2^-f), which brings its Frobenius norm to that of B1, so
@@ -171,7 +222,7 @@ struct Residue { double inv[NMAX], c[NMAX]; int m[NMAX], ci[NMAX]; };      // c 
 
 // Residues of 16 consecutive elements of a row, scaled and rounded: one 16-byte piece of every plane.  The integers have up to 58 bits: x = h 2^29 + l, and x mod m from
 // y = h (2^29 mod m) + l, 37 bits, so that the quotient is off by nothing that matters.  Of y - quotient m only the low byte is wanted: 32-bit integers do.
-__device__ __forceinline__ void store_residues(const double (&x)[16], int nm, const Residue& q, signed char* __restrict__ o, long long plane) {
+__device__ __forceinline__ void store_residues(const double (&x)[16], const Residue& q, signed char* __restrict__ o, long long plane) {
     constexpr double MAGIC = 0x1.8p52;
     double h[16], l[16];
     int hi[16], li[16];
@@ -179,7 +230,6 @@ __device__ __forceinline__ void store_residues(const double (&x)[16], int nm, co
     for (int i = 0; i < 16; ++i) { h[i] = rint(x[i] * 0x1p-29); l[i] = __builtin_fma(h[i], -0x1p29, x[i]); hi[i] = (int)h[i]; li[i] = (int)l[i]; }
 #pragma unroll
     for (int p = 0; p < NMAX; ++p) {
-        if (p >= nm) continue;
         unsigned w[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -199,7 +249,7 @@ __device__ __forceinline__ void store_residues(const double (&x)[16], int nm, co
 
 // Row-contiguous source, exponents given: a wavefront makes one block of 16 rows x 64 contraction indices of every plane.  Bound by memory: 8 bytes read and 15 written per
 // element, 8192 x 8192 in 0.35 ms.
-__global__ __launch_bounds__(256) void rns_columns_kernel(RnsSource s, const int* __restrict__ exps, long long e_stride, int nm, Residue q, signed char* __restrict__ out,
+__global__ __launch_bounds__(256) void rns_columns_kernel(RnsSource s, const int* __restrict__ exps, long long e_stride, Residue q, signed char* __restrict__ out,
                                                           long long plane, long long out_stride, int kpad, int koff, int kblocks, const int* __restrict__ grown, int kpanel) {
     const int lane = threadIdx.x & 63, kb = blockIdx.x * 4 + (threadIdx.x >> 6), r0 = blockIdx.y * 16;
     if (kb >= kblocks) return;
@@ -211,8 +261,8 @@ __global__ __launch_bounds__(256) void rns_columns_kernel(RnsSource s, const int
 #pragma unroll
     for (int i = 0; i < 16; ++i) x[i] = e != UNDEFINED && k0 + i < s.k ? a[(long long)(k0 + i) * s.ld] : 0.0;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) x[i] = e != UNDEFINED && k0 + i < s.k ? rint(ldexp(scaled(s, x[i], r, k0 + i, shift), -e)) : 0.0;
-    store_residues(x, nm, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + (koff >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
+    for (int i = 0; i < 16; ++i) x[i] = e != UNDEFINED && k0 + i < s.k ? rint(ldexp(counted(s, x[i], r, k0 + i), power(s, k0 + i, shift - e))) : 0.0;
+    store_residues(x, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + (koff >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
 }
 
 // Exponents of rows whose elements are contiguous, over one or two sources: a wavefront per row
@@ -226,11 +276,11 @@ __global__ __launch_bounds__(256) void rns_row_exps_kernel(RnsSource s0, RnsSour
         const int shift = shift_of(s), kend = s.half ? min(s.k, r + 1) : s.k;
         int k = lane;
         for (; k + 7 * 64 < kend; k += 512) {      // eight loads in flight
-            double v[8];
+            double v[8]; int p[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = a[k + 64 * i];
+            for (int i = 0; i < 8; ++i) { v[i] = a[k + 64 * i]; p[i] = power(s, k + 64 * i, shift); }
 #pragma unroll
-            for (int i = 0; i < 8; ++i) add_square(t, scaled(s, v[i], r, k + 64 * i, shift));
+            for (int i = 0; i < 8; ++i) add_square(t, ldexp(counted(s, v[i], r, k + 64 * i), p[i]));
         }
         for (; k < kend; k += 64) add_square(t, scaled(s, a[k], r, k, shift));
     }
@@ -240,9 +290,9 @@ __global__ __launch_bounds__(256) void rns_row_exps_kernel(RnsSource s0, RnsSour
 }
 
 // Residues of rows whose elements are contiguous, one or two sources one after the other along the contraction.  A block of 16 rows x 64 indices passes through LDS (a
-// wavefront's own part) to 16 consecutive elements a lane; read that way from memory each lane would walk a line of its own.  exps null: small integers as they are.
+// wavefront's own part) to 16 consecutive elements a lane; read that way from memory each lane would walk a line of its own.
 constexpr int ROW_PITCH = 66;
-__global__ __launch_bounds__(256) void rns_rows_kernel(RnsSource s0, RnsSource s1, const int* __restrict__ exps, long long e_stride, int nm, Residue q, signed char* __restrict__ out,
+__global__ __launch_bounds__(256) void rns_rows_kernel(RnsSource s0, RnsSource s1, const int* __restrict__ exps, long long e_stride, Residue q, signed char* __restrict__ out,
                                                        long long plane, long long out_stride, int kpad, int koff, int kblocks0, int kblocks1) {
     __shared__ __attribute__((aligned(16))) double lds[4][16 * ROW_PITCH];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, r0 = blockIdx.y * 16, kb = blockIdx.x * 4 + wave;
@@ -255,24 +305,24 @@ __global__ __launch_bounds__(256) void rns_rows_kernel(RnsSource s0, RnsSource s
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int r = r0 + 2 * j + (lane >> 5);
-        e[j] = r >= s.rows ? UNDEFINED : exps ? exps[blockIdx.z * e_stride + r] : 0;
+        e[j] = r >= s.rows ? UNDEFINED : exps[blockIdx.z * e_stride + r];
         const bool live = r < s.rows && !(s.half && k > r);
         v0[j] = live && k < s.k ? a[(long long)r * s.ld] : 0.0; v1[j] = live && k + 1 < s.k ? a[(long long)r * s.ld + 1] : 0.0;
     }
     double* mine = lds[wave];
+    const int p0 = k < s.k ? power(s, k, shift) : 0, p1 = k + 1 < s.k ? power(s, k + 1, shift) : 0;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int ri = 2 * j + (lane >> 5), r = r0 + ri;
-        if (k < s.k) v0[j] = scaled(s, v0[j], r, k, shift);
-        if (k + 1 < s.k) v1[j] = scaled(s, v1[j], r, k + 1, shift);
-        *(double2*)(mine + ri * ROW_PITCH + kk) = e[j] == UNDEFINED ? make_double2(0.0, 0.0) : make_double2(rint(ldexp(v0[j], -e[j])), rint(ldexp(v1[j], -e[j])));
+        *(double2*)(mine + ri * ROW_PITCH + kk) = e[j] == UNDEFINED ? make_double2(0.0, 0.0)
+                                                                    : make_double2(rint(ldexp(counted(s, v0[j], r, k), p0 - e[j])), rint(ldexp(counted(s, v1[j], r, k + 1), p1 - e[j])));
     }
     __builtin_amdgcn_wave_barrier();
     const int ri = lane >> 2, piece = lane & 3;
     double x[16];
 #pragma unroll
     for (int i = 0; i < 8; ++i) { const double2 v = *(const double2*)(mine + ri * ROW_PITCH + 16 * piece + 2 * i); x[2 * i] = v.x; x[2 * i + 1] = v.y; }
-    store_residues(x, nm, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + (koff >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
+    store_residues(x, q, out + blockIdx.z * out_stride + ((long long)(r0 >> 4) * (kpad >> 6) + (koff >> 6) + kb) * 1024 + ri * 64 + ((piece ^ (ri >> 2)) << 4), plane);
 }
 
 // ---------------------------------------------------------------------------------------------- the product
@@ -284,7 +334,7 @@ struct Args {
     int row0, klo_m, klo_n, khi_n, upper, wide;
     const int* m_limit;
     unsigned char* C;
-    int tiles_m, tiles_n, batch, nm, splits, per, chunk;      // per: moduli a workgroup takes
+    int tiles_m, tiles_n, batch, splits, per, chunk;      // per: moduli a workgroup takes
     Moduli q;
 };
 
@@ -328,7 +378,7 @@ __global__ __launch_bounds__(512) void rns_gemm_kernel(Args g) {
     if (g.upper && n0 + BN <= g.row0 + m0) return;
     const Range kr = k_range(g.K, g.klo_m, g.klo_n, g.khi_n, g.row0 + m0, n0);
     if (kr.hi <= kr.lo) return;
-    const int p0 = sp * g.per, p1 = min(g.nm, p0 + g.per);
+    const int p0 = sp * g.per, p1 = min(NMAX, p0 + g.per);
     if (p0 >= p1) return;
     const int nk = (kr.hi - kr.lo) / SK * g.terms;      // stages of a plane: a multiple of NS
 
@@ -459,7 +509,7 @@ struct ResultArgs {
     const unsigned char* R;
     const int *ea, *eb; long long strideEa, strideEb;
     double *C; long long ldc, strideC; double alpha, beta;
-    int M, N, K, row0, klo_m, klo_n, khi_n, upper, tiles_m, tiles_n, batch, nm;
+    int M, N, K, row0, klo_m, klo_n, khi_n, upper, tiles_m, tiles_n, batch;
     const int* m_limit;
     Crt c;
 };
@@ -478,10 +528,9 @@ __global__ __launch_bounds__(256) void rns_result_kernel(ResultArgs g) {
         const long long step = (long long)g.batch * g.tiles_m * g.tiles_n * (BM * BN);
         uint4 x[NMAX];
 #pragma unroll
-        for (int p = 0; p < NMAX; ++p) x[p] = p < g.nm ? *(const uint4*)(src + p * step) : make_uint4(0, 0, 0, 0);
+        for (int p = 0; p < NMAX; ++p) x[p] = *(const uint4*)(src + p * step);
 #pragma unroll
         for (int p = 0; p < NMAX; ++p) {
-            if (p >= g.nm) continue;
             const unsigned q[4] = {x[p].x, x[p].y, x[p].z, x[p].w};
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -491,13 +540,13 @@ __global__ __launch_bounds__(256) void rns_result_kernel(ResultArgs g) {
         }
     }
     if (col >= g.N) return;
-    const int eb = g.eb ? g.eb[z * g.strideEb + col] : 0;
+    const int eb = g.eb[z * g.strideEb + col];
     double* C = g.C + z * g.strideC + col;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int row = rl + 8 * (v >> 2) + (v & 3);
         if (row >= g.M) continue;
-        const int ea = g.ea ? g.ea[z * g.strideEa + row] : 0;
+        const int ea = g.ea[z * g.strideEa + row];
         double x = ldexp(((hi[v] - rint(hi[v])) + lo[v]) * g.c.M, ea + eb);
         if (ea == UNDEFINED || eb == UNDEFINED) x = NAN;
         if (g.upper && col <= g.row0 + row) x = 0.0;
@@ -508,18 +557,18 @@ __global__ __launch_bounds__(256) void rns_result_kernel(ResultArgs g) {
     }
 }
 
-int mulmod_all_but(int l, int nm) {      // the product of the other moduli modulo the l-th
+int mulmod_all_but(int l) {      // the product of the other moduli modulo the l-th
     int r = 1;
-    for (int p = 0; p < nm; ++p) if (p != l) r = r * (MODULI[p] % MODULI[l]) % MODULI[l];
+    for (int p = 0; p < NMAX; ++p) if (p != l) r = r * (MODULI[p] % MODULI[l]) % MODULI[l];
     return r;
 }
-Crt crt_of(int nm) {
+Crt crt_constants() {
     Crt c{};
     unsigned __int128 M = 1;
-    for (int p = 0; p < nm; ++p) M *= (unsigned)MODULI[p];
+    for (int p = 0; p < NMAX; ++p) M *= (unsigned)MODULI[p];
     c.M = (double)M;
-    for (int p = 0; p < nm; ++p) {
-        const int m = MODULI[p], o = mulmod_all_but(p, nm);
+    for (int p = 0; p < NMAX; ++p) {
+        const int m = MODULI[p], o = mulmod_all_but(p);
         long long inv = 1;
         while (inv * o % m != 1) ++inv;
         const long long h = ((inv << 40) + m / 2) / m;
@@ -531,17 +580,12 @@ Crt crt_of(int nm) {
 
 }  // namespace
 
-int rns_moduli(double bits) {
-    double have = 0.0;
-    for (int p = 0; p < NMAX; ++p) { have += log2((double)MODULI[p]); if (have >= bits + 1.5) return p + 1; }
-    return 0;
-}
 bool rns_takes(int M, int N, int K) { return K <= 32768 && cdiv64(M, BM) * cdiv64(N, BN) <= 65535; }
 int rns_pad(int k) { return (k + KPAD - 1) / KPAD * KPAD; }
 size_t rns_plane(int rows, int k) { return (size_t)((rows + 15) / 16 * 16) * rns_pad(k); }
 size_t rns_squares_elems(int rows) { return (size_t)3 * rows; }
 static int col_chunks(int rows, int k) { return (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(RNS_CHUNKS, cdiv64(k, 32)), cdiv64(2048, cdiv64(rows, 256)))); }
-size_t rns_residue_bytes(int M, int N, int batch, int nm) { return (size_t)cdiv64(M, BM) * cdiv64(N, BN) * batch * nm * BM * BN; }
+size_t rns_residue_bytes(int M, int N, int batch) { return (size_t)cdiv64(M, BM) * cdiv64(N, BN) * batch * NMAX * BM * BN; }
 
 int rns_norms(tboa_ctx* ctx, const RnsSource& s, int batch, double* sq, long long sq_stride, double* part) {
     if (s.kc) return tboa_fail(ctx, TBOA_EINVAL, "rns_norms: rows that are contiguous have theirs from rns_rows");
@@ -580,6 +624,22 @@ int rns_exps(tboa_ctx* ctx, int rows, int batch, const double* sq, long long sq_
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
+int rns_channel_sizes(tboa_ctx* ctx, int n, const double* H, int* size) {
+    hipLaunchKernelGGL(rns_channel_sizes_kernel, dim3((unsigned)cdiv64(n, 256)), dim3(256), 0, ctx->stream, H, n, size);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
+int rns_channel_exps(tboa_ctx* ctx, int n, const double* sq, const int* size, const int* right, int* x) {
+    hipLaunchKernelGGL(rns_channel_exps_kernel, dim3(1), dim3(1024), 0, ctx->stream, n, sq, size, right, x);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
+int rns_row_exps(tboa_ctx* ctx, const RnsSource& s, int bits, int* e) {
+    if (!s.kc) return tboa_fail(ctx, TBOA_EINVAL, "rns_row_exps: rows must be contiguous");
+    hipLaunchKernelGGL(rns_row_exps_kernel, dim3((unsigned)cdiv64(s.rows, 4), 1, 1), dim3(256), 0, ctx->stream, s, s, 0, bits, e, 0LL);
+    TB_KERNEL_CHECK(ctx);
+    return 0;
+}
 static Residue residue_constants() {
     Residue q;
     for (int p = 0; p < NMAX; ++p) {
@@ -589,23 +649,23 @@ static Residue residue_constants() {
     }
     return q;
 }
-int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm, const int* grown, int panel) {
+int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, const int* grown, int panel) {
     const int kblocks = (int)(std::min<int64_t>(rns_pad(s.k), o.kpad - koff) / SK);
     const unsigned rb = (unsigned)cdiv64(s.rows, 16);
     if (s.kc || !o.e || koff % SK || kblocks * SK < s.k || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane) return tboa_fail(ctx, TBOA_EINVAL, "rns_columns: source does not fit the operand");
-    hipLaunchKernelGGL(rns_columns_kernel, dim3((unsigned)cdiv64(kblocks, 4), rb, batch), dim3(256), 0, ctx->stream, s, o.e, o.e_stride, nm, residue_constants(), o.p, (long long)o.plane,
+    hipLaunchKernelGGL(rns_columns_kernel, dim3((unsigned)cdiv64(kblocks, 4), rb, batch), dim3(256), 0, ctx->stream, s, o.e, o.e_stride, residue_constants(), o.p, (long long)o.plane,
                        o.stride, o.kpad, koff, kblocks, grown, (panel + SK - 1) / SK);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
-int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm, int koff) {
+int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int koff) {
     const int kb0 = rns_pad(s.k) / SK, kb1 = second ? rns_pad(second->k) / SK : 0;
     const unsigned rb = (unsigned)cdiv64(s.rows, 16);
-    if (!s.kc || (second && (!second->kc || second->rows != s.rows || s.k % KPAD)) || (bits >= 0 && !o.e) || (bits == RNS_INTEGERS && o.e) || koff % SK || koff + (kb0 + kb1) * SK > o.kpad || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane)
+    if (!s.kc || (second && (!second->kc || second->rows != s.rows || s.k % KPAD)) || !o.e || koff % SK || koff + (kb0 + kb1) * SK > o.kpad || rb > 65535 || (size_t)rb * 16 * o.kpad > o.plane)
         return tboa_fail(ctx, TBOA_EINVAL, "rns_rows: source does not fit the operand");
     const RnsSource& s1 = second ? *second : s;
     if (bits >= 0) hipLaunchKernelGGL(rns_row_exps_kernel, dim3((unsigned)cdiv64(s.rows, 4), 1, batch), dim3(256), 0, ctx->stream, s, s1, second ? 1 : 0, bits, o.e, o.e_stride);
-    hipLaunchKernelGGL(rns_rows_kernel, dim3((unsigned)cdiv64(kb0 + kb1, 4), rb, batch), dim3(256), 0, ctx->stream, s, s1, o.e, o.e_stride, nm, residue_constants(), o.p, (long long)o.plane,
+    hipLaunchKernelGGL(rns_rows_kernel, dim3((unsigned)cdiv64(kb0 + kb1, 4), rb, batch), dim3(256), 0, ctx->stream, s, s1, o.e, o.e_stride, residue_constants(), o.p, (long long)o.plane,
                        o.stride, o.kpad, koff, kb0, kb1);
     TB_KERNEL_CHECK(ctx);
     return 0;
@@ -614,27 +674,27 @@ int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int bat
 // Microseconds of a launch and its best number of runs of moduli.  A plane of a tile takes 11.6 us for 1024 contraction indices and 6 for its residues, a workgroup 8 to fill and
 // drain its ring (measured at 256 - 8192); tiles of unequal length (triangular operands, half of it on average) go longest first, so that what counts is the sum of the
 // work and, at the end, half of the longest workgroup.
-static double gemm_us(long long tiles, int K, bool triangular, int nm, int* splits) {
+static double gemm_us(long long tiles, int K, bool triangular, int* splits) {
     auto plane = [](double k) { return k / 1024.0 * 11.6 + 6.0; };
     double best = 1e300;
-    for (int s = 1; s <= nm; ++s) {
-        const int per = (nm + s - 1) / s;
-        if ((nm + per - 1) / per != s) continue;
+    for (int s = 1; s <= NMAX; ++s) {
+        const int per = (NMAX + s - 1) / s;
+        if ((NMAX + per - 1) / per != s) continue;
         const double us = triangular ? (double)tiles * s / 256.0 * (per * plane(0.5 * K) + 8.0) + 0.5 * (per * plane(K) + 8.0) : (double)cdiv64(tiles * s, 256) * (per * plane(K) + 8.0);
         if (us < best) { best = us; if (splits) *splits = s; }
     }
     return best;
 }
 // Microseconds of a product with its left operand's preparation; of the preparation of an operand (4.5 TB/s, launches of 5 us)
-double rns_model_us(int M, int N, int K, bool triangular, bool beta, int nm) {
-    return rns_prepare_us(M, K) + gemm_us(cdiv64(M, BM) * cdiv64(N, BN), rns_pad(K), triangular, nm, nullptr) + 10.0 + (double)M * N * (nm + (beta ? 16.0 : 8.0)) / 4.5e6;
+double rns_model_us(int M, int N, int K, bool triangular, bool beta) {
+    return rns_prepare_us(M, K) + gemm_us(cdiv64(M, BM) * cdiv64(N, BN), rns_pad(K), triangular, nullptr) + 10.0 + (double)M * N * (NMAX + (beta ? 16.0 : 8.0)) / 4.5e6;
 }
 double rns_prepare_us(int rows, int k) { return 12.0 + (double)rows * k * (16.0 + TB_RNS_MODULI) / 4.5e6; }
 
 int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     if (q.M <= 0 || q.N <= 0) return 0;
     const int K = rns_pad(q.K);
-    if (!q.A || !q.B || !q.C || !q.residues || q.K <= 0 || !rns_takes(q.M, q.N, K) || q.nm < 1 || q.nm > NMAX || q.a_row % 16 || q.b_row % 16 || q.a_k % SK || q.b_k % SK ||
+    if (!q.A || !q.B || !q.C || !q.residues || q.K <= 0 || !rns_takes(q.M, q.N, K) || !q.A->e || !q.B->e || q.a_row % 16 || q.b_row % 16 || q.a_k % SK || q.b_k % SK ||
         q.a_k + (q.B2 ? 2 : 1) * K > q.A->kpad || q.b_k + K > q.B->kpad || (size_t)(q.a_row + cdiv64(q.M, 16) * 16) * q.A->kpad > q.A->plane ||
         (size_t)(q.b_row + cdiv64(q.N, 16) * 16) * q.B->kpad > q.B->plane || (q.B2 && (q.K % KPAD || q.B2->kpad != q.B->kpad || q.B2->plane != q.B->plane || q.B2->stride != q.B->stride)))
         return tboa_fail(ctx, TBOA_EINVAL, "rns_gemm: unsupported product");
@@ -645,10 +705,10 @@ int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     a.planeA = (long long)q.A->plane; a.planeB = (long long)q.B->plane; a.strideA = q.A->stride; a.strideB = q.B->stride;
     a.M = q.M; a.N = q.N; a.K = K; a.terms = q.B2 ? 2 : 1; a.termB = q.B2 ? (long long)(q.B2->p - q.B->p) : 0;
     a.klo_m = q.klo_m; a.klo_n = q.klo_n; a.khi_n = q.khi_n; a.upper = q.upper; a.row0 = q.row0; a.wide = K * a.terms > 4096; a.m_limit = q.m_limit;
-    a.C = q.residues; a.tiles_m = (int)cdiv64(q.M, BM); a.tiles_n = (int)cdiv64(q.N, BN); a.batch = q.batch; a.nm = q.nm;
+    a.C = q.residues; a.tiles_m = (int)cdiv64(q.M, BM); a.tiles_n = (int)cdiv64(q.N, BN); a.batch = q.batch;
     for (int p = 0; p < NMAX; ++p) { a.q.m[p] = MODULI[p]; a.q.inv[p] = 1.0f / (float)MODULI[p]; }
     const long long tiles = (long long)a.tiles_m * a.tiles_n * q.batch;
-    gemm_us(tiles, K * a.terms, q.klo_m || q.klo_n || q.khi_n || q.upper, q.nm, &a.splits); a.per = (q.nm + a.splits - 1) / a.splits;
+    gemm_us(tiles, K * a.terms, q.klo_m || q.klo_n || q.khi_n || q.upper, &a.splits); a.per = (NMAX + a.splits - 1) / a.splits;
     const long long items = tiles * a.splits;
     a.chunk = (int)std::max<long long>(1, std::min<long long>(32, cdiv64(items, 8)));
     const long long wgs = cdiv64(items, 8LL * a.chunk) * 8 * a.chunk;
@@ -670,10 +730,10 @@ int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     hipLaunchKernelGGL(rns_gemm_kernel, dim3((unsigned)wgs), dim3(512), smem, ctx->stream, a);
     TB_KERNEL_CHECK(ctx);
     ResultArgs r{};
-    r.R = q.residues; r.ea = q.A->e ? q.A->e + q.a_row : nullptr; r.eb = q.B->e ? q.B->e + q.b_row : nullptr; r.strideEa = q.A->e_stride; r.strideEb = q.B->e_stride;
+    r.R = q.residues; r.ea = q.A->e + q.a_row; r.eb = q.B->e + q.b_row; r.strideEa = q.A->e_stride; r.strideEb = q.B->e_stride;
     r.C = q.C; r.ldc = q.ldc; r.strideC = q.strideC; r.alpha = q.alpha; r.beta = q.beta; r.M = q.M; r.N = q.N; r.K = K; r.klo_m = q.klo_m; r.klo_n = q.klo_n; r.khi_n = q.khi_n;
-    r.row0 = q.row0; r.upper = q.upper; r.tiles_m = a.tiles_m; r.tiles_n = a.tiles_n; r.batch = q.batch; r.nm = q.nm; r.m_limit = q.m_limit;
-    r.c = crt_of(q.nm);
+    r.row0 = q.row0; r.upper = q.upper; r.tiles_m = a.tiles_m; r.tiles_n = a.tiles_n; r.batch = q.batch; r.m_limit = q.m_limit;
+    r.c = crt_constants();
     hipLaunchKernelGGL(rns_result_kernel, dim3(16, (unsigned)(a.tiles_m * a.tiles_n), q.batch), dim3(256), 0, ctx->stream, r);
     TB_KERNEL_CHECK(ctx);
     return prof_end(ctx, rec, timed);
@@ -693,16 +753,16 @@ extern "C" int tboa_gemm_f64_residues(tboa_ctx* ctx, int M, int N, int K, double
         a.e = ar.get<int>(M); b.e = ar.get<int>(N);
         double* sq = ar.get<double>(rns_squares_elems(N));
         double* part = ar.get<double>(RNS_CHUNKS * rns_squares_elems(N));
-        unsigned char* res = ar.get<unsigned char>(rns_residue_bytes(M, N, 1, NMAX));
+        unsigned char* res = ar.get<unsigned char>(rns_residue_bytes(M, N, 1));
         if (!pass) { TB_TRY(tboa_ws_reserve(ctx, ar.off)); continue; }
         RnsSource sa{}, sb{};
         sa.a = A; sa.ld = lda; sa.kc = 1; sa.rows = M; sa.k = K;
         sb.a = B; sb.kc = sbk == 1; sb.ld = sb.kc ? sbn : sbk; sb.rows = N; sb.k = K;
-        TB_TRY(rns_rows(ctx, sa, nullptr, 1, RNS_BITS_A, a, NMAX));
-        if (sb.kc) TB_TRY(rns_rows(ctx, sb, nullptr, 1, RNS_BITS_B, b, NMAX));
-        else { TB_TRY(rns_norms(ctx, sb, 1, sq, 0, part)); TB_TRY(rns_exps(ctx, N, 1, sq, 0, RNS_BITS_B, b.e, 0)); TB_TRY(rns_columns(ctx, sb, 1, b, 0, NMAX)); }
+        TB_TRY(rns_rows(ctx, sa, nullptr, 1, RNS_BITS_A, a));
+        if (sb.kc) TB_TRY(rns_rows(ctx, sb, nullptr, 1, RNS_BITS_B, b));
+        else { TB_TRY(rns_norms(ctx, sb, 1, sq, 0, part)); TB_TRY(rns_exps(ctx, N, 1, sq, 0, RNS_BITS_B, b.e, 0)); TB_TRY(rns_columns(ctx, sb, 1, b, 0)); }
         RnsGemm g{};
-        g.A = &a; g.B = &b; g.M = M; g.N = N; g.K = K; g.batch = 1; g.nm = NMAX; g.alpha = alpha; g.beta = beta; g.C = C; g.ldc = ldc; g.residues = res;
+        g.A = &a; g.B = &b; g.M = M; g.N = N; g.K = K; g.batch = 1; g.alpha = alpha; g.beta = beta; g.C = C; g.ldc = ldc; g.residues = res;
         TB_TRY(rns_gemm(ctx, g));
     }
     return 0;

@@ -1027,7 +1027,7 @@ int check_bf16_dims(const Dims& D) {
 }
 
 // The wide product of the W_Q and W_K Hessians, C = W T with T + T^T = H_in (T triangular), in fp64 or as a product of residues.
-struct WideResidues { RnsOperand h, w; unsigned char* res; };      // h.p null: fp64
+struct WideResidues { RnsOperand h, w; unsigned char* res; double *sq, *part; int *size, *x; };      // h.p null: fp64
 // In the room from `from` on, which is in use at another time (a few short sequences need less than the residues: the workspace grows then).  The line, on whole builds over 512
 // tokens, fp64 -> residues with the preparation of both operands: rows x n^2 = 0.6e9 (1024 x 768) 0.83 -> 0.85 ms, 2.1e9 (2048 x 1024) 0.868 -> 0.864, 4.5e9 (1920 x 1536)
 // 1.12 -> 1.03, 17e9 (4096 x 2048) 1.96 -> 1.77, 137e9 (8192 x 4096) 8.6 -> 7.1, 618e9 (9216 x 8192) 18.3 -> 13.4; few rows do not repay the preparation of H_in (n^2 elements).
@@ -1042,7 +1042,8 @@ WideResidues plan_wide_residues(int rows, int n, Arena& ar, size_t from) {
         return o;
     };
     r.h = operand(n); r.w = operand(rows);
-    r.res = a.get<unsigned char>(rns_residue_bytes(rows, n, 1, TB_RNS_MODULI));
+    r.res = a.get<unsigned char>(rns_residue_bytes(rows, n, 1));
+    r.sq = a.get<double>(rns_squares_elems(n)); r.part = a.get<double>(RNS_CHUNKS * rns_squares_elems(n)); r.size = a.get<int>(n); r.x = a.get<int>(n);
     ar.off = std::max(ar.off, a.off);
     return ar.base ? r : WideResidues{};
 }
@@ -1052,12 +1053,16 @@ int wide_half_product(tboa_ctx* ctx, int rows, int n, const double* W, const flo
         // T: twice what is before the diagonal (alpha takes the factor out) and the diagonal once
         TB_TRY(launch_cvt_f32_to_f64(ctx, H, T, nn));
         RnsSource h{}, w{};
-        h.a = T; h.ld = n; h.kc = 1; h.rows = n; h.k = n; h.half = 1;
-        w.a = W; w.ld = n; w.kc = 1; w.rows = rows; w.k = n;
-        TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, r.h, TB_RNS_MODULI));
-        TB_TRY(rns_rows(ctx, w, nullptr, 1, RNS_BITS_A, r.w, TB_RNS_MODULI));
+        w.a = W; w.ld = n; w.rows = n; w.k = rows;      // (its columns)
+        TB_TRY(rns_norms(ctx, w, 1, r.sq, 0, r.part));
+        TB_TRY(rns_channel_sizes(ctx, n, T, r.size));
+        TB_TRY(rns_channel_exps(ctx, n, r.sq, r.size, r.size, r.x));
+        h.a = T; h.ld = n; h.kc = 1; h.rows = n; h.k = n; h.half = 1; h.kexp = r.x; h.ksign = 1;
+        w.kc = 1; w.rows = rows; w.k = n; w.kexp = r.x; w.ksign = -1;
+        TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, r.h));
+        TB_TRY(rns_rows(ctx, w, nullptr, 1, RNS_BITS_A, r.w));
         RnsGemm g{};
-        g.A = &r.w; g.B = &r.h; g.M = rows; g.N = n; g.K = n; g.nm = TB_RNS_MODULI; g.khi_n = 1; g.alpha = 0.5; g.beta = 0.0; g.C = C; g.ldc = n; g.residues = r.res;
+        g.A = &r.w; g.B = &r.h; g.M = rows; g.N = n; g.K = n; g.khi_n = 1; g.alpha = 0.5; g.beta = 0.0; g.C = C; g.ldc = n; g.residues = r.res;
         return rns_gemm(ctx, g);
     }
     hipLaunchKernelGGL(lower_half_f64_kernel, dim3(g1(nn)), dim3(256), 0, ctx->stream, H, T, n);

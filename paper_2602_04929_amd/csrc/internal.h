@@ -121,15 +121,16 @@ struct RnsSource {
     const double* a; long long ld, stride;      // element (r, k): a[r ld + k] (kc), else a[k ld + r]; stride: batch entries
     int kc, rows, k;
     int half;                                    // symmetric source: twice what is before the diagonal, the diagonal once (as GemmF64::sym)
+    int before;                                  // > 0: only what lies before the row's own block of that many indices (k < r - r % before) counts, the rest is zero
     const int* kexp; int ksign;                  // column k times 2^(ksign kexp[k])
     const int* exp_shift;                        // everything times 2^(ksign exp_shift[0])
     const int* row_limit;                        // device word: rows from there on are not needed
 };
-struct RnsOperand { signed char* p; size_t plane; long long stride; int kpad; int* e; long long e_stride; };      // p: [batch][planes]; e null: integers, taken as they are
+struct RnsOperand { signed char* p; size_t plane; long long stride; int kpad; int* e; long long e_stride; };      // p: [batch][planes]
 struct RnsGemm {
     const RnsOperand *A, *B; const RnsOperand* B2 = nullptr;      // C = alpha (A B^T [+ A' B2^T, A' = the K columns of A after the first K]) + beta C
     int a_row = 0, b_row = 0, a_k = 0, b_k = 0;                    // first row (multiple of 16) and first contraction index (multiple of 64)
-    int M, N, K, batch = 1, nm;
+    int M, N, K, batch = 1;
     int row0 = 0;      // of C within the matrix that the limits below speak of (multiple of 256)
     int klo_m = 0, klo_n = 0, khi_n = 0;      // as in GemmF64, with tiles of 256
     int upper = 0;     // C is only wanted above its diagonal: zero on and below it
@@ -138,20 +139,19 @@ struct RnsGemm {
     unsigned char* residues;      // rns_residue_bytes
     int tag = -1;
 };
-int rns_moduli(double bits);      // how many moduli hold products of |a|_2 |b|_2 <= 2^bits (0: too many bits)
 int rns_pad(int k);
 size_t rns_plane(int rows, int k);
 size_t rns_squares_elems(int rows);
-size_t rns_residue_bytes(int M, int N, int batch, int nm);
+size_t rns_residue_bytes(int M, int N, int batch);
 bool rns_takes(int M, int N, int K);      // what rns_gemm can do: sums of K terms (two operands' worth of them) within 32 bits and the quotients' 22, tiles within a grid
-// operand whose rows are contiguous (second: a second source right after the first along k): exponents, `bits` below the norm each, and residues; bits RNS_INTEGERS: small
-// integers, taken as they are (no exponents); RNS_GIVEN: the operand's exponents stand already
-constexpr int RNS_INTEGERS = -1, RNS_GIVEN = -2;
-int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int nm, int koff = 0);
+// operand whose rows are contiguous (second: a second source right after the first along k): exponents, `bits` below the norm each, and residues; bits RNS_GIVEN:
+// the operand's exponents stand already
+constexpr int RNS_GIVEN = -1;
+int rns_rows(tboa_ctx* ctx, const RnsSource& s, const RnsSource* second, int batch, int bits, const RnsOperand& o, int koff = 0);
 // operand whose rows are strided: sums of squares, exponents, residues
 int rns_norms(tboa_ctx* ctx, const RnsSource& s, int batch, double* sq, long long sq_stride, double* part);
 int rns_exps(tboa_ctx* ctx, int rows, int batch, const double* sq, long long sq_stride, int bits, int* e, long long e_stride);
-int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, int nm, const int* grown = nullptr, int panel = 0);
+int rns_columns(tboa_ctx* ctx, const RnsSource& s, int batch, const RnsOperand& o, int koff, const int* grown = nullptr, int panel = 0);
 // columns that grow by panels (of `rows` columns whose squares are `panel`; the first fresh_below of them begin with it): sq, exponents, and which have a new one; rns_columns
 // then makes the first `panel` indices of every row, the others of the rows that have grown
 int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long panel_stride, double* sq, int sq_rows, long long sq_stride, int fresh_below, int bits, int* e, long long e_stride,
@@ -159,9 +159,14 @@ int rns_grow(tboa_ctx* ctx, int rows, int batch, const double* panel, long long 
 // exponents of the rows of V, H = V V^T, from H's diagonal; before rns_rows with them: which rows are longer than H's diagonal says (sum: their squares over all panels)
 int rns_diagonal_exps(tboa_ctx* ctx, int n, int batch, const double* H, int bits, int* e, double* sum, long long sum_stride);
 int rns_row_guard(tboa_ctx* ctx, const RnsSource& s, int batch, int bits, const RnsOperand& o, double* sum, long long sum_stride);
+// exponents of rows that are contiguous (norm < 2^(e + bits)); powers of two per channel for a contraction between columns of a weight (sq: their squares, of rns_norms) and rows of size
+// 2^right[k] (size: exponents of the channels' sizes, half those of H's diagonal; x may be right).  The right operand takes x as kexp with ksign 1, the left one with -1
+int rns_channel_sizes(tboa_ctx* ctx, int n, const double* H, int* size);
+int rns_row_exps(tboa_ctx* ctx, const RnsSource& s, int bits, int* e);
+int rns_channel_exps(tboa_ctx* ctx, int n, const double* sq, const int* size, const int* right, int* x);
 int rns_balance(tboa_ctx* ctx, int rows, double* sq1, const double* sq2, int* f);
 int rns_gemm(tboa_ctx* ctx, const RnsGemm& q);
-double rns_model_us(int M, int N, int K, bool triangular, bool beta, int nm);
+double rns_model_us(int M, int N, int K, bool triangular, bool beta);
 double rns_prepare_us(int rows, int k);
 
 // ---------------------------------------------------------------- gemm_bf16.hip

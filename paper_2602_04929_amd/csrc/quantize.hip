@@ -16,7 +16,6 @@
 #include <string.h>
 #include <stdlib.h>
 #include <math.h>
-#include <initializer_list>
 
 namespace {
 
@@ -1153,8 +1152,8 @@ struct Layer {
     // (0: main, 1: aux) the left operand of a product, residues of its result and sums of squares
     int no_rns;                 // no room for residues: everything in fp64, the factorisation too
     int rns, rns_rows_max;      // rns: which products (RNS_*); rns_rows_max: rows of a product at a time
-    RnsOperand hT, uR, uC, pC, rC, left[2];      // H_in (its half T; group-wise: whole), rows of U, columns of U, columns of P, columns of R
-    unsigned char* rres[2]; CholRns frns; double *rsq, *rsq2, *rpart; int *kexp, *pshift;
+    RnsOperand hT, uR, uC, uS, pS, rC, left[2];      // H_in (its half T; group-wise: whole), rows of U, columns of U, columns of U and P for the sweep, columns of R
+    unsigned char* rres[2]; CholRns frns; double *rsq, *rsq2, *rpart, *wsq; int *kexp, *hexp, *rexp, *pshift;      // kexp .. rexp: powers of two per channel (see run_layer)
 };
 
 RnsSource rows_of(const double* a, long long ld, int rows, int k) {
@@ -1168,18 +1167,26 @@ RnsSource columns_of(const double* a, long long ld, int columns, int k) {
     return s;
 }
 
-// kexp[k]: half the exponent of H_kk, the size of channel k: what is contracted over channels grows with it on one side and falls on the other
-__global__ void channel_exponents_kernel(const double* __restrict__ H, int n, int* __restrict__ kexp) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const double v = H[(long long)k * n + k];
-    kexp[k] = v > 0.0 && v < 1.7976931348623157e308 ? ilogb(v) >> 1 : 0;
+// rows that are contracted over channels, with the powers of two that the right operand has the other way round
+RnsSource left_of_channels(const double* a, long long ld, int rows, int k, const int* kexp) {
+    RnsSource s = rows_of(a, ld, rows, k);
+    s.kexp = kexp; s.ksign = -1;
+    return s;
 }
 
-// Columns of U as right operand, with_P: and those of P beside them (the sweep's two terms), after U and P
-int rns_u_columns(Layer& L, bool with_P) {
+int rns_right_columns(Layer& L, const RnsSource& s, const RnsOperand& o) {
+    TB_TRY(rns_norms(L.ctx, s, 1, L.rsq, 0, L.rpart));
+    TB_TRY(rns_exps(L.ctx, L.n, 1, L.rsq, 0, RNS_BITS_B, o.e, 0));
+    return rns_columns(L.ctx, s, 1, o, 0);
+}
+
+// Columns of U as right operand of the sweep's updates, with_P: and those of P beside them (its two terms), after U and P.  A column's updates come from the blocks of SWEEP_SP columns
+// before its own: the entries within that block, the diagonal among them, are no part of its norm.  (With them, where the damping makes channels that are hardly in use as large as
+// 1e-2 of the mean, their columns of U are little else than diagonal, and an update is rounded in units that it does not reach: 2^-38 - 2^-50 of sum |e u| instead of 2^-55.)
+int rns_sweep_columns(Layer& L, bool with_P) {
     tboa_ctx* ctx = L.ctx;
     RnsSource u = columns_of(L.Uin, L.n, L.n, L.n), p = columns_of(L.P, L.n, L.n, L.n);
+    u.before = p.before = SWEEP_SP;
     p.exp_shift = L.pshift; p.ksign = 1;
     TB_TRY(rns_norms(ctx, u, 1, L.rsq, 0, L.rpart));
     if (with_P) {
@@ -1188,27 +1195,23 @@ int rns_u_columns(Layer& L, bool with_P) {
         TB_TRY(rns_norms(ctx, plain, 1, L.rsq2, 0, L.rpart));
         TB_TRY(rns_balance(ctx, L.n, L.rsq, L.rsq2, L.pshift));
     }
-    TB_TRY(rns_exps(ctx, L.n, 1, L.rsq, 0, RNS_BITS_B, L.uC.e, 0));
-    TB_TRY(rns_columns(ctx, u, 1, L.uC, 0, TB_RNS_MODULI));
-    return with_P ? rns_columns(ctx, p, 1, L.pC, 0, TB_RNS_MODULI) : 0;
+    TB_TRY(rns_exps(ctx, L.n, 1, L.rsq, 0, RNS_BITS_B, L.uS.e, 0));
+    TB_TRY(rns_columns(ctx, u, 1, L.uS, 0));
+    return with_P ? rns_columns(ctx, p, 1, L.pS, 0) : 0;
 }
 
-// Products of `rows` rows (contiguous, pitch lda) with prepared right operands, N = columns each: C = A B + beta C, at most rns_rows_max rows at a time.
-struct RnsProduct { const RnsOperand* B; double* C; int klo_m, klo_n, khi_n, upper, nm; };
-int rns_products(Layer& L, int which, const RnsSource& A, int bits, int nm_rows, std::initializer_list<RnsProduct> products, int tag) {
+// C = A B, B a prepared right operand of n columns, at most rns_rows_max rows of A (contiguous) at a time
+struct RnsProduct { const RnsOperand* B; double* C; int klo_m, klo_n, khi_n, upper; };
+int rns_products(Layer& L, int which, const RnsSource& A, const RnsProduct& p, int tag) {
     tboa_ctx* ctx = L.ctx;
     for (int r0 = 0; r0 < A.rows; r0 += L.rns_rows_max) {
         RnsSource a = A;
         a.a += (long long)r0 * A.ld; a.rows = std::min(L.rns_rows_max, A.rows - r0);
-        RnsOperand left = L.left[which];
-        if (bits == RNS_INTEGERS) left.e = nullptr;
-        TB_TRY(rns_rows(ctx, a, nullptr, 1, bits, left, nm_rows));
-        for (const RnsProduct& p : products) {
-            RnsGemm g{};
-            g.A = &left; g.B = p.B; g.M = a.rows; g.N = L.n; g.K = A.k; g.nm = p.nm; g.klo_m = p.klo_m; g.klo_n = p.klo_n; g.khi_n = p.khi_n; g.upper = p.upper; g.row0 = r0;
-            g.alpha = 1.0; g.beta = 0.0; g.C = p.C + (long long)r0 * L.n; g.ldc = L.n; g.residues = L.rres[which]; g.tag = tag; g.m_limit = A.row_limit;
-            TB_TRY(rns_gemm(ctx, g));
-        }
+        TB_TRY(rns_rows(ctx, a, nullptr, 1, RNS_BITS_A, L.left[which]));
+        RnsGemm g{};
+        g.A = &L.left[which]; g.B = p.B; g.M = a.rows; g.N = L.n; g.K = A.k; g.klo_m = p.klo_m; g.klo_n = p.klo_n; g.khi_n = p.khi_n; g.upper = p.upper; g.row0 = r0;
+        g.alpha = 1.0; g.beta = 0.0; g.C = p.C + (long long)r0 * L.n; g.ldc = L.n; g.residues = L.rres[which]; g.tag = tag; g.m_limit = A.row_limit;
+        TB_TRY(rns_gemm(ctx, g));
     }
     return 0;
 }
@@ -1309,9 +1312,9 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
                                L.cand_s, L.cand_z, L.list, cntv, offv, per, cap, L.DeltaS);
             TB_KERNEL_CHECK(ctx);
             if (L.rns & RNS_EXACT) {
-                RnsSource a = rows_of(L.DeltaS, n, cap, n);
+                RnsSource a = left_of_channels(L.DeltaS, n, cap, n, L.hexp);
                 a.row_limit = totv;
-                TB_TRY(rns_products(L, 0, a, RNS_BITS_A, TB_RNS_MODULI, {{&L.hT, L.GS, 0, 0, 1, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_GRID));
+                TB_TRY(rns_products(L, 0, a, {&L.hT, L.GS, 0, 0, 1, 0}, TBOA_PROF_F64_GRID));
             } else {
             GemmF64 g{};
             g.M = cap; g.N = n; g.K = n; g.alpha = 1.0; g.beta = 0.0; g.A = L.DeltaS; g.sam = n; g.sak = 1; g.sbk = n; g.sbn = 1;
@@ -1390,9 +1393,9 @@ int rns_sweep_update(Layer& L, int rows, int s0, int s1, bool with_P) {
         const int m = std::min(L.rns_rows_max, rows - r0);
         RnsSource e = rows_of(L.Epan + (long long)r0 * SWEEP_SP, SWEEP_SP, m, SWEEP_SP), w = rows_of(L.Wsnap + (long long)r0 * SWEEP_SP, SWEEP_SP, m, SWEEP_SP);
         w.exp_shift = L.pshift; w.ksign = -1;
-        TB_TRY(rns_rows(L.ctx, e, with_P ? &w : nullptr, 1, RNS_BITS_A, L.left[0], TB_RNS_MODULI));
+        TB_TRY(rns_rows(L.ctx, e, with_P ? &w : nullptr, 1, RNS_BITS_A, L.left[0]));
         RnsGemm g{};
-        g.A = &L.left[0]; g.B = &L.uC; g.B2 = with_P ? &L.pC : nullptr; g.b_row = s1; g.b_k = s0; g.M = m; g.N = L.n - s1; g.K = SWEEP_SP; g.nm = TB_RNS_MODULI;
+        g.A = &L.left[0]; g.B = &L.uS; g.B2 = with_P ? &L.pS : nullptr; g.b_row = s1; g.b_k = s0; g.M = m; g.N = L.n - s1; g.K = SWEEP_SP;
         g.alpha = -1.0; g.beta = 1.0; g.C = L.Wk + (long long)r0 * L.n + s1; g.ldc = L.n; g.residues = L.rres[0]; g.tag = TBOA_PROF_F64_SWEEP;
         TB_TRY(rns_gemm(L.ctx, g));
     }
@@ -1435,11 +1438,16 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         TB_KERNEL_CHECK(ctx);
     }
     if (L.rns) {
-        RnsSource h = rows_of(L.Hi, n, n, n);
-        h.half = !d->group;
-        if (L.hT.p) TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, L.hT, TB_RNS_MODULI));
-        hipLaunchKernelGGL(channel_exponents_kernel, dim3((n + 255) / 256), dim3(256), 0, st, L.Hi, n, L.kexp);
-        TB_KERNEL_CHECK(ctx);
+        // (R U^T and (W R) U^T: rows of R grow with a channel's size, U's entries fall)
+        TB_TRY(rns_channel_sizes(ctx, n, L.Hi, L.kexp));
+        // products of W (and what has its size: delta, codes less zeros, the rows of a step) with H_in and R: sizes of W's columns against those of H_in's and of R's rows
+        if (L.hT.p || L.rC.p) TB_TRY(rns_norms(ctx, columns_of(L.W64, n, n, d->d_out), 1, L.wsq, 0, L.rpart));
+        if (L.hT.p) {
+            TB_TRY(rns_channel_exps(ctx, n, L.wsq, L.kexp, L.kexp, L.hexp));
+            RnsSource h = rows_of(L.Hi, n, n, n);
+            h.half = !d->group; h.kexp = L.hexp; h.ksign = 1;
+            TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, L.hT));
+        }
     }
     // U_in, P and U_out are first needed by the first in-channel sweep; the grid search before it needs only W and H_in.
     // The factorisations and the two P products (for one matrix: chains of small kernels that leave most of the GPU idle)
@@ -1469,13 +1477,17 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     if (R) {
         TB_TRY(launch_cvt_f32_to_f64(ctx, R, L.Rd, nhin * nn));
         if (L.rC.p) {
+            TB_TRY(rns_row_exps(ctx, rows_of(L.Rd, n, n, n), 0, L.rexp));
+            TB_TRY(rns_channel_exps(ctx, n, L.wsq, L.kexp, L.rexp, L.rexp));
             RnsSource r = columns_of(L.Rd, n, n, n);
-            TB_TRY(rns_norms(ctx, r, 1, L.rsq, 0, L.rpart)); TB_TRY(rns_exps(ctx, n, 1, L.rsq, 0, RNS_BITS_B, L.rC.e, 0)); TB_TRY(rns_columns(ctx, r, 1, L.rC, 0, TB_RNS_MODULI));
+            r.kexp = L.rexp; r.ksign = 1;
+            TB_TRY(rns_right_columns(L, r, L.rC));
         }
+        if (L.uC.p) TB_TRY(rns_right_columns(L, columns_of(L.Uin, n, n, n), L.uC));
         if (L.uR.p) {
             RnsSource u = rows_of(L.Uin, n, n, n);
             u.kexp = L.kexp; u.ksign = 1;
-            TB_TRY(rns_rows(ctx, u, nullptr, 1, RNS_BITS_B, L.uR, TB_RNS_MODULI));
+            TB_TRY(rns_rows(ctx, u, nullptr, 1, RNS_BITS_B, L.uR));
         }
         if (L.lazy) {
             // only the blocks of SWEEP_SP columns on the diagonal of S = R U^T, into L.P
@@ -1488,11 +1500,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                 TB_TRY(gemm_f64(ctx, a));
             }
         } else if (L.rns & RNS_P) {
-            RnsSource r = rows_of(L.Rd, n, n, n);
-            r.kexp = L.kexp; r.ksign = -1;
-            TB_TRY(rns_products(L, 1, r, RNS_BITS_A, TB_RNS_MODULI, {{&L.uR, L.Hfac, 0, 1, 0, 1, TB_RNS_MODULI}}, TBOA_PROF_F64_FACTOR));      // U[c, k] = 0 for k < c; only above the diagonal
-            TB_TRY(rns_u_columns(L, false));
-            TB_TRY(rns_products(L, 1, rows_of(L.Hfac, n, n, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.uC, L.P, 1, 0, 1, 1, TB_RNS_MODULI}}, TBOA_PROF_F64_FACTOR));
+            TB_TRY(rns_products(L, 1, left_of_channels(L.Rd, n, n, n, L.kexp), {&L.uR, L.Hfac, 0, 1, 0, 1}, TBOA_PROF_F64_FACTOR));      // U[c, k] = 0 for k < c; only above the diagonal
+            TB_TRY(rns_products(L, 1, rows_of(L.Hfac, n, n, n), {&L.uC, L.P, 1, 0, 1, 1}, TBOA_PROF_F64_FACTOR));
         } else {
             GemmF64 a{};
             a.M = n; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0;
@@ -1512,7 +1521,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
             TB_TRY(gemm_f64(ctx, b));
         }
     }
-    if (L.pC.p || (L.uC.p && !(R && (L.rns & RNS_P)))) TB_TRY(rns_u_columns(L, L.pC.p != nullptr));
+    if (L.uS.p) TB_TRY(rns_sweep_columns(L, L.pS.p != nullptr));
     if (H_out) {
         TB_TRY(launch_f32_to_f64_damp(ctx, dh, nh, H_out, d->damp, L.Ho));
         TB_HIP(ctx, hipMemcpyAsync(L.Hofac, L.Ho, (size_t)nh * dh * dh * sizeof(double), hipMemcpyDeviceToDevice, ctx->stream));
@@ -1582,11 +1591,9 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         if (H_out && i1 < dh) {
             const double* S3 = nullptr;
             if (R && (L.rns & RNS_COMP)) {   // W_B R H_in^-1 = ((W_B R) U^T) U
-                RnsSource s1 = rows_of(L.S1, n, rows, n);
-                s1.kexp = L.kexp; s1.ksign = -1;
-                TB_TRY(rns_products(L, 0, rows_of(L.Wb, n, rows, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.rC, L.S1, 0, 0, 0, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
-                TB_TRY(rns_products(L, 0, s1, RNS_BITS_A, TB_RNS_MODULI, {{&L.uR, L.S2, 0, 1, 0, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
-                TB_TRY(rns_products(L, 0, rows_of(L.S2, n, rows, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.uC, L.S1, 0, 0, 1, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, left_of_channels(L.Wb, n, rows, n, L.rexp), {&L.rC, L.S1, 0, 0, 0, 0}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, left_of_channels(L.S1, n, rows, n, L.kexp), {&L.uR, L.S2, 0, 1, 0, 0}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, rows_of(L.S2, n, rows, n), {&L.uC, L.S1, 0, 0, 1, 0}, TBOA_PROF_F64_COMP));
                 S3 = L.S1;
             } else if (R) {
                 GemmF64 f1{}; f1.klo_n = 1;
@@ -1618,15 +1625,12 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     GemmF64 half{}; half.sym = 1;
     hipLaunchKernelGGL(wbar_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, codes, L.z64, ng, L.gsz, n, L.Wbar);
     TB_KERNEL_CHECK(ctx);
-    // with products of residues W R and W H_in share the left operand; without groups H_in enters as its half T in either form (see below)
-    const int half_range = d->group ? 0 : 1, nm_int = rns_moduli(log2(L.maxq * sqrt((double)n)) + RNS_BITS_B);
+    // products with H_in (without groups its half T in either form, see below)
     const bool rns = L.rns & RNS_REFINE;
+    auto rns_with_h = [&](const double* rows, double* to) { return rns_products(L, 0, left_of_channels(rows, n, rows_all, n, L.hexp), {&L.hT, to, 0, 0, d->group ? 0 : 1, 0}, TBOA_PROF_F64_CD); };
     if (rns) {
-        const RnsProduct wr{&L.rC, L.WR, 0, 0, 0, 0, TB_RNS_MODULI}, wh{&L.hT, L.Z, 0, 0, half_range, 0, TB_RNS_MODULI};
-        const RnsSource w = rows_of(L.W64, n, rows_all, n);
-        if (R && d->cd_iters > 0) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wr, wh}, TBOA_PROF_F64_CD));
-        else if (R) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wr}, TBOA_PROF_F64_CD));
-        else if (d->cd_iters > 0) TB_TRY(rns_products(L, 0, w, RNS_BITS_A, TB_RNS_MODULI, {wh}, TBOA_PROF_F64_CD));
+        if (R) TB_TRY(rns_products(L, 0, left_of_channels(L.W64, n, rows_all, n, L.rexp), {&L.rC, L.WR, 0, 0, 0, 0}, TBOA_PROF_F64_CD));
+        if (d->cd_iters > 0) TB_TRY(rns_with_h(L.W64, L.Z));
     } else if (R) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Rd, 0, n, 1, 0.0, L.WR, n, TBOA_PROF_F64_CD));
     if (d->cd_iters > 0 && d->group) {
         // Z = W (H_in - R); per group g: AH = Wbar[:, G] H_in[G, :] (into Abar), then the Gram blocks against every group
@@ -1697,7 +1701,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         TB_KERNEL_CHECK(ctx);
     } else if (d->cd_iters > 0) {
         // H_in is symmetric and its products only go into symmetric forms: half products A = Wbar T and Z = W T, T + T^T = 2 H_in
-        if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), RNS_INTEGERS, nm_int, {{&L.hT, L.Abar, 0, 0, 1, 0, nm_int}}, TBOA_PROF_F64_CD));
+        if (rns) TB_TRY(rns_with_h(L.Wbar, L.Abar));
         else {
             TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
             TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Hi, 0, n, 1, 0.0, L.Z, n, TBOA_PROF_F64_CD, &half));
@@ -1731,7 +1735,7 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         if (d->cd_iters > 0 && !d->group) {   // Abar = Wbar T and Z = W T are still those of the scale refinement
             hipLaunchKernelGGL(dh_from_products_kernel, dim3(gx(n), rows_all), dim3(256), 0, st, L.Abar, L.s64, L.Z, n);
             TB_KERNEL_CHECK(ctx);
-        } else if (rns) TB_TRY(rns_products(L, 0, rows_of(L.Wbar, n, rows_all, n), RNS_BITS_A, TB_RNS_MODULI, {{&L.hT, L.Abar, 0, 0, half_range, 0, TB_RNS_MODULI}}, TBOA_PROF_F64_CD));
+        } else if (rns) TB_TRY(rns_with_h(L.Wbar, L.Abar));
         else TB_TRY(block_gemm(L, dh, n, n, 1.0, L.Wbar, n, L.Hi, 0, n, 1, 0.0, L.Abar, n, TBOA_PROF_F64_CD, &half));
         double* lq = L.lossbuf; double* lc = L.lossbuf + nh;
         TB_TRY(launch_fill_f64(ctx, L.lossbuf, 2 * nh, 0.0));
@@ -1806,10 +1810,10 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
 }
 
 // right operands that a choice of products needs
-struct RnsNeeds { bool hT, rC, uR, uC, pC; };
+struct RnsNeeds { bool hT, rC, uR, uC, uS, pS; };
 RnsNeeds rns_needs(int products, bool R) {
-    return {(products & (RNS_REFINE | RNS_EXACT)) != 0, R && (products & (RNS_REFINE | RNS_COMP)), R && (products & (RNS_P | RNS_COMP)),
-            (products & RNS_SWEEP) || (R && (products & (RNS_P | RNS_COMP))), R && (products & RNS_SWEEP)};
+    const bool u = R && (products & (RNS_P | RNS_COMP));
+    return {(products & (RNS_REFINE | RNS_EXACT)) != 0, R && (products & (RNS_REFINE | RNS_COMP)), u, u, (products & RNS_SWEEP) != 0, R && (products & RNS_SWEEP)};
 }
 
 // Which products go to the integer matrix cores: the choice of least modelled time over both forms of every kind and the right operands that it needs (gemm_f64_model_us,
@@ -1820,21 +1824,20 @@ int rns_choice(const Layer& L, bool H_out, bool R) {
     if (L.nhin > 1 || n < SWEEP_SP || !rns_takes(8192, n, n)) return 0;
     const int blk = d->block < L.dh ? d->block : L.dh, steps = (L.dh + blk - 1) / blk, step_rows = L.nh * blk;
     const double half = d->group ? 1.0 : 0.5;      // of a product with H_in
-    const int nm_int = rns_moduli(log2(L.maxq * sqrt((double)n)) + RNS_BITS_B), all = TB_RNS_MODULI;
     auto fp64 = [](int M, int N, int K) { return 1.15 * gemm_f64_model_us(M, N, K); };      // (one launch among others: 332 us for 2048^3, where the steps alone are 269)
-    auto rns = [&](int M, int N, int K, bool tri, bool beta = false, int nm = TB_RNS_MODULI) {
+    auto rns = [&](int M, int N, int K, bool tri, bool beta = false) {
         double us = 0.0;
-        for (int r = 0; r < M; r += 8192) us += rns_model_us(std::min(8192, M - r), N, K, tri, beta, nm);
+        for (int r = 0; r < M; r += 8192) us += rns_model_us(std::min(8192, M - r), N, K, tri, beta);
         return us;
     };
     double gain[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (R) gain[0] += fp64(rows, n, n) - rns(rows, n, n, false);
-    if (d->cd_iters > 0) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, !d->group) + rns_prepare_us(rows, n) * (R ? 1.0 : 0.0);
-    if (d->cd_iters > 0 && !d->group) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, true, false, nm_int);
+    if (d->cd_iters > 0) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, !d->group);
+    if (d->cd_iters > 0 && !d->group) gain[0] += half * fp64(rows, n, n) - rns(rows, n, n, true);
     if (d->cd_iters == 0 || d->group) gain[0] += 0.5 * fp64(rows, n, n) - rns(rows, n, n, !d->group);
     if (L.fast_grid) {      // about one and a half exact costs a row
         const int at_once = std::min(step_rows, L.fast_chunk), m = std::max(1, at_once * 3 / 2);
-        gain[1] = (double)steps * step_rows / at_once * (0.5 * fp64(m, n, n) - rns_model_us(m, n, n, true, false, all));
+        gain[1] = (double)steps * step_rows / at_once * (0.5 * fp64(m, n, n) - rns_model_us(m, n, n, true, false));
     }
     if (R && !L.lazy) gain[2] = fp64(n, n, n) - 2.0 * rns(n, n, n, true);
     if (R && H_out) gain[3] = (steps - 1) * (2.0 * fp64(step_rows, n, n) - rns(step_rows, n, n, false) - 2.0 * rns(step_rows, n, n, true));
@@ -1845,7 +1848,7 @@ int rns_choice(const Layer& L, bool H_out, bool R) {
     for (int c = 1; c < 32; ++c) {
         if (((c & RNS_P) && (!R || L.lazy)) || ((c & RNS_COMP) && !(R && H_out)) || ((c & RNS_EXACT) && !L.fast_grid) || ((c & RNS_SWEEP) && (L.lazy || !whole_groups))) continue;
         const RnsNeeds need = rns_needs(c, R);
-        double g = -(need.hT + need.rC + need.uR + need.uC + need.pC + ((c & RNS_P) && need.pC ? 1 : 0)) * (rns_prepare_us(n, n) + 8.0);
+        double g = -(need.hT + need.rC + need.uR + need.uC + need.uS + need.pS) * (rns_prepare_us(n, n) + 8.0);
         for (int k = 0; k < 5; ++k) if (c >> k & 1) g += gain[k];
         if (g > most) { most = g; best = c; }
     }
@@ -1930,12 +1933,14 @@ void plan_layer(Layer& L, bool H_out, bool R, Arena& ar) {
         if (need.rC) L.rC = operand(n, n, true);
         if (need.uR) L.uR = operand(n, n, true);
         if (need.uC) L.uC = operand(n, n, true);
-        if (need.pC) { L.pC = operand(n, n, false); L.pC.e = L.uC.e; }
+        if (need.uS) L.uS = operand(n, n, true);
+        if (need.pS) { L.pS = operand(n, n, false); L.pS.e = L.uS.e; }
         L.left[0] = operand(L.rns_rows_max, std::max(n, 2 * SWEEP_SP), true);
-        L.rres[0] = ar.get<unsigned char>(rns_residue_bytes(L.rns_rows_max, n, 1, TB_RNS_MODULI));
-        if (aux) { L.left[1] = operand(aux_rows, n, true); L.rres[1] = ar.get<unsigned char>(rns_residue_bytes(aux_rows, n, 1, TB_RNS_MODULI)); }
+        L.rres[0] = ar.get<unsigned char>(rns_residue_bytes(L.rns_rows_max, n, 1));
+        if (aux) { L.left[1] = operand(aux_rows, n, true); L.rres[1] = ar.get<unsigned char>(rns_residue_bytes(aux_rows, n, 1)); }
         L.rsq = ar.get<double>(rns_squares_elems(n)); L.rsq2 = ar.get<double>(rns_squares_elems(n)); L.rpart = ar.get<double>(RNS_CHUNKS * rns_squares_elems(n));
-        L.kexp = ar.get<int>(n); L.pshift = ar.get<int>(1);
+        L.wsq = ar.get<double>(rns_squares_elems(n));
+        L.kexp = ar.get<int>(n); L.hexp = ar.get<int>(n); L.rexp = ar.get<int>(n); L.pshift = ar.get<int>(1);
     }
     L.Cg = L.Fg = L.cdnum = nullptr;
     if (d->group && d->cd_iters > 0) {
