@@ -73,7 +73,13 @@ int64_t tboa_counter(const tboa_ctx* ctx, int which);
 /* Bytes of context-owned workspace currently allocated (host value). */
 size_t tboa_workspace_bytes(const tboa_ctx* ctx);
 /* Makes the context's workspace at least `bytes` large (no-op when it already is).  Synchronises the stream when it has to
- * reallocate.  TBOA_ENOMEM when the device cannot provide it (the context then has no workspace at all). */
+ * reallocate.  TBOA_ENOMEM when the device cannot provide it (the context then keeps the workspace that it had, unless something else has
+ * taken that memory meanwhile).
+ * Calls that can run part of their fp64 products as products of residues (tboa_gemm_f64_residues) need more memory for them: the
+ * tboa_*_workspace_bytes queries state the size with residues, tboa_*_workspace_min_bytes the size without.  A call takes the larger form where the
+ * device has room for it and the smaller one, with the same results up to rounding, where it has not.  A context remembers what size the device has
+ * refused, and no call asks for as much again: where tboa_reserve_workspace of the larger size fails, one of the smaller size is what the calls then
+ * keep to, without allocating.  (A later tboa_reserve_workspace that succeeds with a refused size takes that back.) */
 int tboa_reserve_workspace(tboa_ctx* ctx, size_t bytes);
 
 /* ------------------------------------------------------------------------------------------------
@@ -116,6 +122,7 @@ size_t tboa_fp_cache_bytes(const tboa_attn_desc* desc);
 /* Workspace that tboa_build_hessians and tboa_build_hessian_out_proj need for this block (the larger of the two, with X_fp
  * and every output requested); 0 for an invalid descriptor. */
 size_t tboa_hessian_workspace_bytes(const tboa_attn_desc* desc);
+size_t tboa_hessian_workspace_min_bytes(const tboa_attn_desc* desc);      /* without residues: see tboa_reserve_workspace */
 int tboa_build_hessians(tboa_ctx* ctx, const tboa_attn_desc* desc,
                         const void* X, const void* X_fp,
                         const void* Wq, const void* Wk, const void* Wv, const void* Wo,
@@ -225,6 +232,7 @@ typedef struct {
  * (with_R != 0) or without R; 0 for an invalid descriptor.  (Without H_out the rows are independent, and the group-wise
  * scale refinement then keeps one Gram entry per row and pair of groups instead of one d_h x d_h block per head.) */
 size_t tboa_quantize_workspace_bytes(const tboa_layer_desc* desc, int with_H_out, int with_R);
+size_t tboa_quantize_workspace_min_bytes(const tboa_layer_desc* desc, int with_H_out, int with_R);      /* without residues: see tboa_reserve_workspace */
 
 /*   W      [d_out, d_in]            (w_dtype)
  *   H_in   fp32, shape per hin_per_head; symmetric.  Where it is so up to rounding only, the factorisation reads the upper

@@ -52,6 +52,7 @@ def _load():
         "tboa_workspace_bytes": ([vp], C.c_size_t),
         "tboa_reserve_workspace": ([vp, C.c_size_t], i32),
         "tboa_quantize_workspace_bytes": ([C.POINTER(LayerDesc), C.c_int, C.c_int], C.c_size_t),
+        "tboa_quantize_workspace_min_bytes": ([C.POINTER(LayerDesc), C.c_int, C.c_int], C.c_size_t),
         "tboa_gemm_f64": ([vp, i32, i32, i32, f64, vp, i64, i64, vp, i64, i64, f64, vp, i64, i32, i64, i64, i64], i32),
         "tboa_gemm_f64_residues": ([vp, i32, i32, i32, f64, vp, i64, vp, i64, i64, f64, vp, i64], i32),
         "tboa_gemm_bf16_nt": ([vp, i32, i32, i32, f32, vp, i64, vp, i64, vp, i64, i32, i32, i32, i32, i64, i64, i64], i32),
@@ -62,6 +63,7 @@ def _load():
         "tboa_build_hessian_out_proj": ([vp, C.POINTER(AttnDesc)] + [vp] * 11, i32),
         "tboa_fp_cache_bytes": ([C.POINTER(AttnDesc)], C.c_size_t),
         "tboa_hessian_workspace_bytes": ([C.POINTER(AttnDesc)], C.c_size_t),
+        "tboa_hessian_workspace_min_bytes": ([C.POINTER(AttnDesc)], C.c_size_t),
         "tboa_act_fakequant": ([vp, i64, i32, i32, i32, vp, vp], i32),
         "tboa_hadamard_rotate": ([vp, i64, i32, i32, vp, vp, vp], i32),
         "tboa_build_hessian_linear": ([vp, i64, i32, i32, f64, vp, vp, vp, vp], i32),
@@ -154,14 +156,16 @@ class Context:
                          int(adaptive_grid), grid_points, max_shrink, damp, grid_guard)
 
     @staticmethod
-    def hessian_workspace_bytes(d_model, n_q_heads, n_kv_heads, head_dim, n_seqs, seq_len, dtype, causal=True, seq_chunk=0):
+    def hessian_workspace_bytes(d_model, n_q_heads, n_kv_heads, head_dim, n_seqs, seq_len, dtype, causal=True, seq_chunk=0, least=False):
+        """least: the size without room for residues (see tboa_reserve_workspace)."""
         desc = AttnDesc(d_model, n_q_heads, n_kv_heads, head_dim, n_seqs, seq_len, {torch.float32: F32, torch.bfloat16: BF16}[dtype],
                         int(causal), 0.0, seq_chunk)
-        return int(_lib.tboa_hessian_workspace_bytes(C.byref(desc)))
+        return int((_lib.tboa_hessian_workspace_min_bytes if least else _lib.tboa_hessian_workspace_bytes)(C.byref(desc)))
 
     @staticmethod
-    def quantize_workspace_bytes(desc, with_H_out=True, with_R=True):
-        return int(_lib.tboa_quantize_workspace_bytes(C.byref(desc), int(with_H_out), int(with_R)))
+    def quantize_workspace_bytes(desc, with_H_out=True, with_R=True, least=False):
+        """least: the size without room for residues (see tboa_reserve_workspace)."""
+        return int((_lib.tboa_quantize_workspace_min_bytes if least else _lib.tboa_quantize_workspace_bytes)(C.byref(desc), int(with_H_out), int(with_R)))
 
     # ---- live kernel timing
     PROF_TAGS = {"hv_syrk": 0, "ax": 1, "rv": 2, "gram": 3, "proj": 4, "grid": 5,

@@ -12,18 +12,34 @@ int tboa_fail(tboa_ctx* ctx, int code, const char* fmt, ...) {
 }
 
 int tboa_ws_reserve(tboa_ctx* ctx, size_t bytes) {
-    if (ctx->plan_only) { if (bytes > ctx->plan_bytes) ctx->plan_bytes = bytes; return TB_PLAN_STOP; }
+    if (ctx->plan_only) { if (bytes > ctx->plan_bytes) ctx->plan_bytes = bytes; if (bytes > ctx->plan_plain) ctx->plan_plain = bytes; return TB_PLAN_STOP; }
     if (bytes <= ctx->ws_bytes) return 0;
     TB_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    const size_t had = ctx->ws_bytes;
     if (ctx->ws) { TB_HIP(ctx, hipFree(ctx->ws)); ctx->ws = nullptr; ctx->ws_bytes = 0; }
     hipError_t e = hipMalloc(&ctx->ws, bytes);
     if (e != hipSuccess) {
-        ctx->ws = nullptr;
         (void)hipGetLastError();
+        if (bytes < ctx->no_room) ctx->no_room = bytes;
+        if (had && hipMalloc(&ctx->ws, had) == hipSuccess) ctx->ws_bytes = had;      // what it had, where nobody else has taken it meanwhile
+        else { ctx->ws = nullptr; (void)hipGetLastError(); }
         return tboa_fail(ctx, TBOA_ENOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     }
     ctx->ws_bytes = bytes;
+    if (bytes >= ctx->no_room) ctx->no_room = (size_t)-1;
     return 0;
+}
+
+int tboa_ws_reserve_either(tboa_ctx* ctx, size_t full, size_t plain, bool& take_full) {
+    take_full = true;
+    if (ctx->plan_only) { if (plain > ctx->plan_plain) ctx->plan_plain = plain; if (full > ctx->plan_bytes) ctx->plan_bytes = full; return TB_PLAN_STOP; }
+    if (full <= ctx->ws_bytes) return 0;
+    if (full < ctx->no_room || full <= plain) {
+        const int rc = tboa_ws_reserve(ctx, full);
+        if (rc != TBOA_ENOMEM || full <= plain) return rc;
+    }
+    take_full = false;
+    return tboa_ws_reserve(ctx, plain);
 }
 
 extern "C" int tboa_create(tboa_ctx** out, int hip_device, void* hip_stream) {
@@ -66,7 +82,9 @@ extern "C" int tboa_create(tboa_ctx** out, int hip_device, void* hip_stream) {
 
 extern "C" int tboa_reserve_workspace(tboa_ctx* ctx, size_t bytes) {
     if (!ctx) return TBOA_EINVAL;
-    return tboa_ws_reserve(ctx, bytes);
+    TB_TRY(tboa_ws_reserve(ctx, bytes));
+    if (ctx->no_room != (size_t)-1) ctx->no_room = ctx->ws_bytes + 1;      // refused more before: this is what the caller has settled for
+    return 0;
 }
 
 int prof_begin(tboa_ctx* ctx, int tag, double flops, ProfRec& rec, bool& timed) {

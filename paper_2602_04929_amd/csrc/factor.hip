@@ -443,12 +443,7 @@ extern "C" int tboa_chol_inv_upper(tboa_ctx* ctx, int n, int batch, const float*
         const size_t plain = ar.off;
         CholRns rns{};
         if (residues) chol_rns_plan(n, batch, ar, rns);
-        if (!pass) {
-            int rc = tboa_ws_reserve(ctx, ar.off);
-            if (rc == TBOA_ENOMEM && ar.off > plain) { residues = false; rc = tboa_ws_reserve(ctx, plain); }      // what fits without residues still runs
-            TB_TRY(rc);
-            continue;
-        }
+        if (!pass) { TB_TRY(tboa_ws_reserve_either(ctx, ar.off, plain, residues)); continue; }      // what fits without residues still runs
         TB_TRY(launch_f32_to_f64_damp(ctx, n, batch, H, damp, H64));
         TB_TRY(chol_inv_upper_f64(ctx, n, batch, H64, U, tmp, dinv, 0, false, &rns));
     }

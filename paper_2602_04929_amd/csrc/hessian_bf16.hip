@@ -1117,9 +1117,10 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
     int* amx;      // [q | k | q~ | k~] x G: largest magnitudes of the chunk's projections, per sequence (see QkScale)
     double *Hin64, *Wq64, *Wk64, *Wo64, *Tq, *Tk, *Ho;
     WideResidues res{};
-    bool residues = true;
-    for (int pass = 0; pass < 2; ++pass) {
-        Arena ar(pass ? ctx->ws : nullptr);
+    bool residues = Hin_qk != nullptr;
+    size_t full = 0;
+    for (int pass = 0; pass < 3; ++pass) {      // counted with residues, counted without (what fits so still runs), carved
+        Arena ar(pass == 2 ? ctx->ws : nullptr);
         XT = ar.get<bf16>((size_t)dm * TP);
         dXh = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr; dXl = fp ? ar.get<bf16>((size_t)dm * TP) : nullptr;
         part = ar.get<float>(Hin_qk ? gram_part_elems(dm, splits, Tp, 1, fp && R_qk ? 2 : 0, blocked_x) : 0);
@@ -1143,14 +1144,12 @@ int build_hessians_bf16(tboa_ctx* ctx, const tboa_attn_desc* d, const bf16* X, c
             P = ar.get<bf16>((size_t)Hq * Lp * (nsg * Lp + PADE));
             YT = ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)); dYT = rv ? ar.get<bf16>((size_t)Hkv * dm * (rep * G * Lp + PADE)) : nullptr;
         }
-        if (residues) res = plan_wide_residues(dq + dkv, dm, ar, wv0);
+        res = residues && pass != 1 ? plan_wide_residues(dq + dkv, dm, ar, wv0) : WideResidues{};
         Hin64 = ar.get<double>((size_t)dd); Wq64 = ar.get<double>((size_t)(dq + dkv) * dm); Wk64 = Wq64 + (size_t)dq * dm;
         Wo64 = ar.get<double>((size_t)dm * dq); Tq = ar.get<double>((size_t)(dq + dkv) * dm); Tk = Tq + (size_t)dq * dm;
         Ho = ar.get<double>((size_t)Hkv * hh);
-        if (pass) break;
-        const int rc = tboa_ws_reserve(ctx, ar.off);
-        if (rc == TBOA_ENOMEM && residues) { residues = false; pass = -1; continue; }      // what fits without residues still runs
-        TB_TRY(rc);
+        if (pass == 0) full = ar.off;
+        else if (pass == 1) TB_TRY(tboa_ws_reserve_either(ctx, full, ar.off, residues));
     }
     hipStream_t st = ctx->stream;
     // ---- H_in and R for W_Q / W_K
@@ -1814,7 +1813,7 @@ extern "C" int tboa_build_hessian_out_proj(tboa_ctx* ctx, const tboa_attn_desc* 
 
 // The workspace the two Hessian builds of an attention block need: their own planning code, run on a host-only context that
 // stops at the point where a real call would reserve the workspace (no pointer is read before that).
-extern "C" size_t tboa_hessian_workspace_bytes(const tboa_attn_desc* d) {
+static size_t hessian_workspace(const tboa_attn_desc* d, bool least) {
     tboa_ctx plan{};
     plan.plan_only = 1;
     if (check_attn_desc(&plan, d) != 0) return 0;
@@ -1823,8 +1822,10 @@ extern "C" size_t tboa_hessian_workspace_bytes(const tboa_attn_desc* d) {
     if (rc != TB_PLAN_STOP) return 0;
     rc = tboa_build_hessian_out_proj(&plan, d, in, in, out, out, out, in, in, in, out, out, nullptr);
     if (rc != TB_PLAN_STOP) return 0;
-    return plan.plan_bytes;
+    return least ? plan.plan_plain : plan.plan_bytes;
 }
+extern "C" size_t tboa_hessian_workspace_bytes(const tboa_attn_desc* d) { return hessian_workspace(d, false); }
+extern "C" size_t tboa_hessian_workspace_min_bytes(const tboa_attn_desc* d) { return hessian_workspace(d, true); }
 
 extern "C" int tboa_build_hout(tboa_ctx* ctx, int d_in, int n_heads, int rep, int head_dim, const float* H_in, int w_dtype, const void* W,
                                float* H_out) {

@@ -31,7 +31,8 @@ struct tboa_ctx {
     std::vector<ProfRec> prof;
     long long counters[8];   // tboa_counter_id
     int plan_only = 0;       // a host-only context of the workspace queries: tboa_ws_reserve records the request and stops the call
-    size_t plan_bytes = 0;
+    size_t plan_bytes = 0, plan_plain = 0;
+    size_t no_room = (size_t)-1;   // a workspace from this size on is not asked for again: the device has refused one (tboa_reserve_workspace)
     std::vector<TileOrder> tile_orders;   // device tables owned by the context
     std::vector<TileSchedule> tile_schedules;
 };
@@ -73,6 +74,8 @@ struct Arena {
 // returns TB_PLAN_STOP (not an error) on a plan-only context, after recording `bytes`
 #define TB_PLAN_STOP 1000
 int tboa_ws_reserve(tboa_ctx* ctx, size_t bytes);
+// for a call that has a form with residues (`full` bytes) and one without (`plain`): the first unless it is known or found not to fit
+int tboa_ws_reserve_either(tboa_ctx* ctx, size_t full, size_t plain, bool& take_full);
 
 static inline int64_t cdiv64(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

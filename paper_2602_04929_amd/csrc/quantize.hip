@@ -1996,15 +1996,22 @@ void init_layer(Layer& L, tboa_ctx* ctx, const tboa_layer_desc* d) {
     L.gstat = ctx ? ctx->d_status + TB_GSTAT_WORD : nullptr;
 }
 
+size_t layer_bytes(const tboa_layer_desc* d, bool H_out, bool R, bool no_rns) {
+    Layer L{};
+    init_layer(L, nullptr, d);
+    L.no_rns = no_rns;
+    Arena ar(nullptr);
+    plan_layer(L, H_out, R, ar);
+    return ar.off;
+}
+
 }  // namespace
 
 extern "C" size_t tboa_quantize_workspace_bytes(const tboa_layer_desc* d, int with_H_out, int with_R) {
-    if (check_layer_desc(nullptr, d) != 0) return 0;
-    Layer L{};
-    init_layer(L, nullptr, d);
-    Arena ar(nullptr);
-    plan_layer(L, with_H_out != 0, with_R != 0, ar);
-    return ar.off;
+    return check_layer_desc(nullptr, d) != 0 ? 0 : layer_bytes(d, with_H_out != 0, with_R != 0, false);
+}
+extern "C" size_t tboa_quantize_workspace_min_bytes(const tboa_layer_desc* d, int with_H_out, int with_R) {
+    return check_layer_desc(nullptr, d) != 0 ? 0 : layer_bytes(d, with_H_out != 0, with_R != 0, true);
 }
 
 extern "C" int tboa_quantize_layer(tboa_ctx* ctx, const tboa_layer_desc* d, const void* W, const float* H_in, const float* H_out,
@@ -2017,19 +2024,12 @@ extern "C" int tboa_quantize_layer(tboa_ctx* ctx, const tboa_layer_desc* d, cons
 
     Layer L{};
     init_layer(L, ctx, d);
-    for (int pass = 0; pass < 2; ++pass) {
-        Arena ar(pass ? ctx->ws : nullptr);
-        plan_layer(L, H_out != nullptr, R != nullptr, ar);
-        if (pass) break;
-        int rc = tboa_ws_reserve(ctx, ar.off);
-        if (rc == TBOA_ENOMEM) {      // residues take as much memory again as the fp64 matrices: what fits without them still runs
-            Arena plain(nullptr);
-            L.no_rns = 1;
-            plan_layer(L, H_out != nullptr, R != nullptr, plain);
-            rc = tboa_ws_reserve(ctx, plain.off);
-        }
-        TB_TRY(rc);
-    }
+    // residues take as much memory again as the fp64 matrices: what fits without them still runs
+    bool residues = true;
+    TB_TRY(tboa_ws_reserve_either(ctx, layer_bytes(d, H_out != nullptr, R != nullptr, false), layer_bytes(d, H_out != nullptr, R != nullptr, true), residues));
+    L.no_rns = !residues;
+    Arena ar(ctx->ws);
+    plan_layer(L, H_out != nullptr, R != nullptr, ar);
     int rc = run_layer(L, W, H_in, H_out, R, codes, scales, zeros, W_deq, loss, loss_per_head);
     if (rc == RUN_AGAIN_TWO_TERMS) {
         ++ctx->counters[TBOA_CTR_GRID_TWO_TERM_RUNS];

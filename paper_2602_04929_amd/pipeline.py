@@ -16,27 +16,36 @@ def make_side_contexts(n=2):
 def reserve_workspaces(ctx, cfg, side_contexts=None, stack_qk=True, cd_iters=1, adaptive_grid=True, seq_chunk=0):
     """Sizes every context's workspace for one attention block of `cfg` ahead of the calls (tboa_hessian_workspace_bytes,
     tboa_quantize_workspace_bytes, tboa_reserve_workspace), so that no call of quantize_attention_block allocates.  Returns
-    the bytes reserved per context."""
+    the bytes reserved per context.  A context for which the device has no room for residues gets the workspace that the same calls need without."""
     import paper_2602_04929_amd as tb
     dt = {"fp32": torch.float32, "bf16": torch.bfloat16}[cfg.dtype]
     wd = tb.F32 if cfg.dtype == "fp32" else tb.BF16
     Hq, Hkv, dh, d = cfg.n_q_heads, cfg.n_kv_heads, cfg.head_dim, cfg.d_model
 
-    def layer(d_out, d_in, n_heads, per_head, block, with_H_out=True):
-        return ctx.quantize_workspace_bytes(tb.LayerDesc(d_out, d_in, n_heads, int(per_head), cfg.bits, block, cfg.group, wd, cd_iters,
-                                                         int(adaptive_grid), 100, 0.8, 0.01, 0.0), with_H_out, True)
-    hess = ctx.hessian_workspace_bytes(d, Hq, Hkv, dh, cfg.n_seqs, cfg.seq_len, dt, seq_chunk=seq_chunk)
-    o = layer(d, Hq * dh, 1, False, d, with_H_out=False)
-    v = layer(Hkv * dh, d, Hkv, True, cfg.block)
-    first = [layer((Hq + Hkv) * dh, d, Hq + Hkv, False, cfg.block)] if stack_qk else [layer(Hq * dh, d, Hq, False, cfg.block), layer(Hkv * dh, d, Hkv, False, cfg.block)]
-    jobs = first + [v]
-    ctxs = [ctx] + list(side_contexts or [])[:len(jobs) - 1]
-    need = [0] * len(ctxs)
-    for i, b in enumerate(jobs):          # job i runs on context i when there are side contexts, else all on the main one
-        need[i if i < len(ctxs) else 0] = max(need[i if i < len(ctxs) else 0], b)
-    need[0] = max(need[0], hess, o, *(jobs if len(ctxs) == 1 else []))
-    for c, n in zip(ctxs, need):
-        c.reserve_workspace(n)
+    def sizes(least):
+        def layer(d_out, d_in, n_heads, per_head, block, with_H_out=True):
+            return ctx.quantize_workspace_bytes(tb.LayerDesc(d_out, d_in, n_heads, int(per_head), cfg.bits, block, cfg.group, wd, cd_iters,
+                                                             int(adaptive_grid), 100, 0.8, 0.01, 0.0), with_H_out, True, least=least)
+        hess = ctx.hessian_workspace_bytes(d, Hq, Hkv, dh, cfg.n_seqs, cfg.seq_len, dt, seq_chunk=seq_chunk, least=least)
+        o = layer(d, Hq * dh, 1, False, d, with_H_out=False)
+        v = layer(Hkv * dh, d, Hkv, True, cfg.block)
+        first = [layer((Hq + Hkv) * dh, d, Hq + Hkv, False, cfg.block)] if stack_qk else [layer(Hq * dh, d, Hq, False, cfg.block), layer(Hkv * dh, d, Hkv, False, cfg.block)]
+        jobs = first + [v]
+        need = [0] * min(1 + len(side_contexts or []), len(jobs))
+        for i, b in enumerate(jobs):          # job i runs on context i when there are side contexts, else all on the main one
+            need[i if i < len(need) else 0] = max(need[i if i < len(need) else 0], b)
+        need[0] = max(need[0], hess, o, *(jobs if len(need) == 1 else []))
+        return need
+    need = []
+    for c, n, least in zip([ctx] + list(side_contexts or []), sizes(False), sizes(True)):
+        try:
+            c.reserve_workspace(n)
+        except tb.TurboBoAError as e:
+            if e.code != -3:
+                raise
+            n = least
+            c.reserve_workspace(n)
+        need.append(n)
     return need
 
 
