@@ -17,12 +17,14 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 / fp16 MFMA, published
 PEAK_F64_TFLOPS = 78.6         # MI355X fp64 MFMA, published
+PEAK_I8_TOPS = 5000.0          # MI355X dense signed bytes, published
+RESIDUE_MODULI = 15            # byte products per fp64 product
 BF16_TAGS = ("hv_syrk", "rv", "ax", "ata", "gram", "proj", "scores", "pv", "grid")
 F64_TAGS = ("f64_factor", "f64_sweep", "f64_comp", "f64_cd", "f64_grid")
 KERNEL_OF = {"hv_syrk": "gemm_bf16_nt_fast_kernel (H_in^V += T1^T X, lower tiles)", "rv": "gemm_bf16_nt_fast_kernel (R_v += alpha Z^T X)",
              "ax": "gemm_bf16_nt_stream_kernel (T1 = B1 X, Z = B1 dX + B2^T X~; per-head form: A X)", "ata": "gemm_bf16_nt_stream_kernel (sum_h A_h^T A_h)",
              "gram": "gemm_bf16_nt_fast_kernel (X^T X, dX^T X, O^T O)", "proj": "gemm_bf16_nt_stream_kernel (projections X W^T)", "scores": "gemm_bf16_nt_stream_kernel (Q K^T, fp32 out)",
-             "pv": "gemm_bf16_nt_stream_kernel (O^T = V^T A^T)",
+             "pv": "attn_output_kernel (O^T = V^T A^T with its scores and probabilities)",
              "grid": "gemm_bf16_nt_fast_kernel (approximate grid-search costs)"}
 
 
@@ -256,7 +258,8 @@ def main():
                 "ms_per_step": prof[dom]["ms"] / args.steps,
                 "traffic": measured_traffic(cfg.name if not args.n_seqs else "", dom),
                 "traffic_unit": "bytes per launch (FETCH_SIZE + WRITE_SIZE, scaled by a 1 GiB copy)"}
-    # the fp64 matrix-core GEMMs of quantize_layer (compensation, sweep updates, P, scale refinement): the largest tag with counted flops
+    # the fp64 matrix-core GEMMs of quantize_layer (those of compensation, sweep updates, P and scale refinement that stay in fp64): the largest tag with counted flops; and the
+    # fp64 products that run as products of residues, priced in byte operations
     f64_counted = [k for k in F64_TAGS if prof[k]["flops"] > 0]
     dom64 = max(f64_counted, key=lambda k: prof[k]["ms"]) if f64_counted else None
     roofline_f64 = None
@@ -266,6 +269,12 @@ def main():
                         "unit": "TFLOP/s", "frac": rate(prof[dom64]) / PEAK_F64_TFLOPS, "ms_per_step": prof[dom64]["ms"] / args.steps,
                         "all_counted_tags": {"ms_per_step": tot_ms / args.steps, "achieved": tot_fl / (tot_ms * 1e-3) / 1e12 if tot_ms > 0 else 0.0},
                         "note": "tagged launches run beside other layers' kernels on other streams: rates are lower bounds"}
+    roofline_residues = None
+    if prof["residues"]["flops"] > 0:
+        tops = RESIDUE_MODULI * rate(prof["residues"])
+        roofline_residues = {"bound": "mfma", "kernel": "rns_gemm_kernel, with rns_result_kernel in its time", "achieved": tops, "peak": PEAK_I8_TOPS, "unit": "TOP/s", "frac": tops / PEAK_I8_TOPS,
+                             "as_fp64_tflops": rate(prof["residues"]), "ms_per_step": prof["residues"]["ms"] / args.steps,
+                             "note": "preparation of operands not timed; launches run beside other layers' kernels on other streams: rates are lower bounds"}
     kernels = {k: {"ms_per_step": v["ms"] / args.steps, "launches_per_step": v["launches"] // args.steps, "tflops": rate(v)} for k, v in prof.items()}
     bf_ms = sum(prof[k]["ms"] for k in BF16_TAGS); bf_fl = sum(prof[k]["flops"] for k in BF16_TAGS)
     util_all = (bf_fl / (bf_ms * 1e-3) / 1e12) / PEAK_BF16_TFLOPS if bf_ms > 0 else 0.0
@@ -284,6 +293,7 @@ def main():
         "stage_seconds": {k: v / args.steps for k, v in stages.items()},
         "bf16_gemm_seconds_per_step": bf_ms * 1e-3 / args.steps,
         "f64_gemm_seconds_per_step": sum(prof[k]["ms"] for k in F64_TAGS) * 1e-3 / args.steps,
+        "residue_gemm_seconds_per_step": prof["residues"]["ms"] * 1e-3 / args.steps,
         "kernels": kernels,
         "losses": {k: out[k]["loss"] for k in ("q", "k", "v", "o")},
         "workspace_gib": sum(c.workspace_bytes() for c in ctxs) / 2 ** 30,
@@ -292,6 +302,7 @@ def main():
                         "layers_rerun_two_terms": sum(c.counter(6) for c in ctxs)},
         "roofline": roofline,
         "roofline_f64": roofline_f64,
+        "roofline_residues": roofline_residues,
     }
     if args.with_mlp:
         from paper_2602_04929_amd.pipeline import quantize_mlp

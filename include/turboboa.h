@@ -360,7 +360,9 @@ enum tboa_prof_tag {
     TBOA_PROF_ATA = 11,        /* sum over a KV group's heads of A_h^T A_h and A_h^T (A_h - A~_h) (grouped-query form of the W_V Hessian) */
     TBOA_PROF_SCORES = 12,     /* scores Q_h K_g^T of a sequence (short contraction: 3 d_h with the (hi, lo) parts), fp32 out */
     TBOA_PROF_PV = 13,         /* attention outputs O_h^T = V^T A_h^T and their differences, for the W_O Hessian */
-    TBOA_PROF_NTAGS = 14
+    TBOA_PROF_RESIDUES = 14,   /* fp64 products as products of residues, whatever they are for (flops: of the fp64 product); preparation of operands not timed.  The F64 tags are
+                                  launches of fp64 products, and under F64_GRID also those exact costs that run as residues */
+    TBOA_PROF_NTAGS = 15
 };
 int tboa_profile_enable(tboa_ctx* ctx, int on);
 int tboa_profile_reset(tboa_ctx* ctx);

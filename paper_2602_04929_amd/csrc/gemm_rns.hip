@@ -714,16 +714,16 @@ int rns_gemm(tboa_ctx* ctx, const RnsGemm& q) {
     const long long wgs = cdiv64(items, 8LL * a.chunk) * 8 * a.chunk;
     if (wgs > 0x7fffffffLL || q.batch > 65535) return tboa_fail(ctx, TBOA_EINVAL, "rns_gemm: grid too large");
     ProfRec rec{}; bool timed = false;
-    if (ctx->prof_on && q.tag >= 0) {
+    if (ctx->prof_on) {
         double macs = 0.0;
-        if (!q.m_limit)
+        if (!q.m_limit)      // (how many rows there are only the device knows)
             for (int m0 = 0; m0 < q.M; m0 += BM)
                 for (int n0 = 0; n0 < q.N; n0 += BN) {
                     if (q.upper && n0 + BN <= q.row0 + m0) continue;
                     const int lo = std::max(q.klo_m ? q.row0 + m0 : 0, q.klo_n ? n0 : 0), hi = q.khi_n ? std::min(q.K, n0 + BN) : q.K;
                     if (hi > lo) macs += (double)std::min(BM, q.M - m0) * std::min(BN, q.N - n0) * (hi - lo) * a.terms;
                 }
-        TB_TRY(prof_begin(ctx, q.tag, 2.0 * macs * q.batch, rec, timed));
+        TB_TRY(prof_begin(ctx, q.m_limit ? TBOA_PROF_F64_GRID : TBOA_PROF_RESIDUES, 2.0 * macs * q.batch, rec, timed));
     }
     constexpr int smem = NS * STAGE_BYTES;
     TB_HIP(ctx, hipFuncSetAttribute((const void*)rns_gemm_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, smem));

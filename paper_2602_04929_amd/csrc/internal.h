@@ -140,7 +140,6 @@ struct RnsGemm {
     const int* m_limit = nullptr;
     double alpha, beta; double* C; long long ldc, strideC = 0;
     unsigned char* residues;      // rns_residue_bytes
-    int tag = -1;
 };
 int rns_pad(int k);
 size_t rns_plane(int rows, int k);

@@ -1202,7 +1202,7 @@ int rns_sweep_columns(Layer& L, bool with_P) {
 
 // C = A B, B a prepared right operand of n columns, at most rns_rows_max rows of A (contiguous) at a time
 struct RnsProduct { const RnsOperand* B; double* C; int klo_m, klo_n, khi_n, upper; };
-int rns_products(Layer& L, int which, const RnsSource& A, const RnsProduct& p, int tag) {
+int rns_products(Layer& L, int which, const RnsSource& A, const RnsProduct& p) {
     tboa_ctx* ctx = L.ctx;
     for (int r0 = 0; r0 < A.rows; r0 += L.rns_rows_max) {
         RnsSource a = A;
@@ -1210,7 +1210,7 @@ int rns_products(Layer& L, int which, const RnsSource& A, const RnsProduct& p, i
         TB_TRY(rns_rows(ctx, a, nullptr, 1, RNS_BITS_A, L.left[which]));
         RnsGemm g{};
         g.A = &L.left[which]; g.B = p.B; g.M = a.rows; g.N = L.n; g.K = A.k; g.klo_m = p.klo_m; g.klo_n = p.klo_n; g.khi_n = p.khi_n; g.upper = p.upper; g.row0 = r0;
-        g.alpha = 1.0; g.beta = 0.0; g.C = p.C + (long long)r0 * L.n; g.ldc = L.n; g.residues = L.rres[which]; g.tag = tag; g.m_limit = A.row_limit;
+        g.alpha = 1.0; g.beta = 0.0; g.C = p.C + (long long)r0 * L.n; g.ldc = L.n; g.residues = L.rres[which]; g.m_limit = A.row_limit;
         TB_TRY(rns_gemm(ctx, g));
     }
     return 0;
@@ -1314,7 +1314,7 @@ int grid_search(Layer& L, const double* Wrows, long long ldw, int rows_per_head,
             if (L.rns & RNS_EXACT) {
                 RnsSource a = left_of_channels(L.DeltaS, n, cap, n, L.hexp);
                 a.row_limit = totv;
-                TB_TRY(rns_products(L, 0, a, {&L.hT, L.GS, 0, 0, 1, 0}, TBOA_PROF_F64_GRID));
+                TB_TRY(rns_products(L, 0, a, {&L.hT, L.GS, 0, 0, 1, 0}));
             } else {
             GemmF64 g{};
             g.M = cap; g.N = n; g.K = n; g.alpha = 1.0; g.beta = 0.0; g.A = L.DeltaS; g.sam = n; g.sak = 1; g.sbk = n; g.sbn = 1;
@@ -1396,7 +1396,7 @@ int rns_sweep_update(Layer& L, int rows, int s0, int s1, bool with_P) {
         TB_TRY(rns_rows(L.ctx, e, with_P ? &w : nullptr, 1, RNS_BITS_A, L.left[0]));
         RnsGemm g{};
         g.A = &L.left[0]; g.B = &L.uS; g.B2 = with_P ? &L.pS : nullptr; g.b_row = s1; g.b_k = s0; g.M = m; g.N = L.n - s1; g.K = SWEEP_SP;
-        g.alpha = -1.0; g.beta = 1.0; g.C = L.Wk + (long long)r0 * L.n + s1; g.ldc = L.n; g.residues = L.rres[0]; g.tag = TBOA_PROF_F64_SWEEP;
+        g.alpha = -1.0; g.beta = 1.0; g.C = L.Wk + (long long)r0 * L.n + s1; g.ldc = L.n; g.residues = L.rres[0];
         TB_TRY(rns_gemm(L.ctx, g));
     }
     return 0;
@@ -1500,8 +1500,8 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
                 TB_TRY(gemm_f64(ctx, a));
             }
         } else if (L.rns & RNS_P) {
-            TB_TRY(rns_products(L, 1, left_of_channels(L.Rd, n, n, n, L.kexp), {&L.uR, L.Hfac, 0, 1, 0, 1}, TBOA_PROF_F64_FACTOR));      // U[c, k] = 0 for k < c; only above the diagonal
-            TB_TRY(rns_products(L, 1, rows_of(L.Hfac, n, n, n), {&L.uC, L.P, 1, 0, 1, 1}, TBOA_PROF_F64_FACTOR));
+            TB_TRY(rns_products(L, 1, left_of_channels(L.Rd, n, n, n, L.kexp), {&L.uR, L.Hfac, 0, 1, 0, 1}));      // U[c, k] = 0 for k < c; only above the diagonal
+            TB_TRY(rns_products(L, 1, rows_of(L.Hfac, n, n, n), {&L.uC, L.P, 1, 0, 1, 1}));
         } else {
             GemmF64 a{};
             a.M = n; a.N = n; a.K = n; a.alpha = 1.0; a.beta = 0.0;
@@ -1591,9 +1591,9 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
         if (H_out && i1 < dh) {
             const double* S3 = nullptr;
             if (R && (L.rns & RNS_COMP)) {   // W_B R H_in^-1 = ((W_B R) U^T) U
-                TB_TRY(rns_products(L, 0, left_of_channels(L.Wb, n, rows, n, L.rexp), {&L.rC, L.S1, 0, 0, 0, 0}, TBOA_PROF_F64_COMP));
-                TB_TRY(rns_products(L, 0, left_of_channels(L.S1, n, rows, n, L.kexp), {&L.uR, L.S2, 0, 1, 0, 0}, TBOA_PROF_F64_COMP));
-                TB_TRY(rns_products(L, 0, rows_of(L.S2, n, rows, n), {&L.uC, L.S1, 0, 0, 1, 0}, TBOA_PROF_F64_COMP));
+                TB_TRY(rns_products(L, 0, left_of_channels(L.Wb, n, rows, n, L.rexp), {&L.rC, L.S1, 0, 0, 0, 0}));
+                TB_TRY(rns_products(L, 0, left_of_channels(L.S1, n, rows, n, L.kexp), {&L.uR, L.S2, 0, 1, 0, 0}));
+                TB_TRY(rns_products(L, 0, rows_of(L.S2, n, rows, n), {&L.uC, L.S1, 0, 0, 1, 0}));
                 S3 = L.S1;
             } else if (R) {
                 GemmF64 f1{}; f1.klo_n = 1;
@@ -1627,9 +1627,9 @@ int run_layer(Layer& L, const void* W, const float* H_in, const float* H_out, co
     TB_KERNEL_CHECK(ctx);
     // products with H_in (without groups its half T in either form, see below)
     const bool rns = L.rns & RNS_REFINE;
-    auto rns_with_h = [&](const double* rows, double* to) { return rns_products(L, 0, left_of_channels(rows, n, rows_all, n, L.hexp), {&L.hT, to, 0, 0, d->group ? 0 : 1, 0}, TBOA_PROF_F64_CD); };
+    auto rns_with_h = [&](const double* rows, double* to) { return rns_products(L, 0, left_of_channels(rows, n, rows_all, n, L.hexp), {&L.hT, to, 0, 0, d->group ? 0 : 1, 0}); };
     if (rns) {
-        if (R) TB_TRY(rns_products(L, 0, left_of_channels(L.W64, n, rows_all, n, L.rexp), {&L.rC, L.WR, 0, 0, 0, 0}, TBOA_PROF_F64_CD));
+        if (R) TB_TRY(rns_products(L, 0, left_of_channels(L.W64, n, rows_all, n, L.rexp), {&L.rC, L.WR, 0, 0, 0, 0}));
         if (d->cd_iters > 0) TB_TRY(rns_with_h(L.W64, L.Z));
     } else if (R) TB_TRY(block_gemm(L, dh, n, n, 1.0, L.W64, n, L.Rd, 0, n, 1, 0.0, L.WR, n, TBOA_PROF_F64_CD));
     if (d->cd_iters > 0 && d->group) {

@@ -55,3 +55,17 @@ def test_rows_that_are_not_finite(lib):
     bad[[3, 17]] = True; bad[:, 49] = True
     assert np.isnan(got[bad]).all() and (got[~bad] == 64.0).all()
     ctx.close()
+
+
+def test_time_and_operations_have_a_tag_of_their_own(lib):
+    """Launches are timed as products of residues, with the operations of the fp64 product, and not among the fp64 kernels'."""
+    M, N, K = 300, 520, 1000
+    ctx = lib.Context()
+    a, b = (torch.randn(*s, device="cuda", dtype=torch.float64) for s in ((M, K), (K, N)))
+    ctx.profile(True)
+    ctx.gemm_f64_residues(a, b)
+    got = {k: ctx.profile_read(k) for k in ctx.PROF_TAGS}
+    ctx.profile(False)
+    ctx.close()
+    assert got["residues"]["launches"] == 1 and got["residues"]["ms"] > 0 and got["residues"]["flops"] == 2.0 * M * N * K
+    assert all(v["launches"] == 0 for k, v in got.items() if k != "residues")
