@@ -184,9 +184,10 @@ class Context:
     def gemm_f64_residues(self, A, B, C_out=None, alpha=1.0, beta=0.0, transB=False):
         """alpha A op(B) + beta C_out for one pair of fp64 matrices, on the integer matrix cores."""
         _dev(A, torch.float64); _dev(B, torch.float64)
-        M, K = A.shape
-        N = B.shape[0] if transB else B.shape[1]
-        out = torch.zeros(M, N, dtype=torch.float64, device=A.device) if C_out is None else C_out
+        (M, K), (N, Kb) = A.shape, B.shape if transB else B.shape[::-1]
+        assert K == Kb, "A has %d columns, op(B) %d rows" % (K, Kb)
+        out = torch.zeros(M, N, dtype=torch.float64, device=A.device) if C_out is None else _dev(C_out, torch.float64)
+        assert tuple(out.shape) == (M, N), "C_out is %s, the product %d x %d" % (tuple(out.shape), M, N)
         sbk, sbn = (1, K) if transB else (N, 1)
         self._check(_lib.tboa_gemm_f64_residues(self._h, M, N, K, alpha, _ptr(A), K, _ptr(B), sbk, sbn, beta, _ptr(out), N))
         return out
