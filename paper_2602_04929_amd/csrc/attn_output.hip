@@ -2,7 +2,7 @@
 // in the registers of one wavefront.  (Probabilities by attn_probs_t_kernel, which forms the scores twice and writes 8 bytes per probability and path, and a product that
 // reads them again took 4.4 + 2.5 ms of the 7B-shaped W_O Hessian over 8 x 2048 tokens, both paths.)
 //
-// One workgroup per (path, sequence, head, 32 W queries); each of its W wavefronts keeps the Q^ fragments of 32 queries (as attn_probs_t_kernel does) and all
+// One workgroup per (path, sequence, head, 256 queries); each of its eight wavefronts keeps the Q^ fragments of 32 queries (as attn_probs_t_kernel does) and all
 // d_h outputs of them.  Blocks of 32 keys of K^ (segments k_hi, k_lo) and V^T (hi, lo) are copied global -> LDS into a ring of four.  For each:
 //     S^T = K^ Q^T              a lane holds one query and 16 of the keys, 8 b + 4 (lane / 32) + j for b, j < 4
 //     r = running maximum of the query less 14 (0 for bf16), p = 2^(S - r) as (hi, lo) pair: half values below 2^14, whose low parts are normal numbers down to 2^-17 of the largest;
@@ -11,7 +11,9 @@
 //                               V^T is stored with its keys in that order (vt_blocks_kernel), so that nothing is exchanged between lanes
 // The scores of block i + 1 and the product of block i are one run of MFMAs, the exponentials one run of vector instructions, with a barrier after each; of the two wavefronts of a
 // SIMD one is a run behind, so that one multiplies while the other exponentiates.  (Both paths of 8 sequences x 32 heads x 2048 x 128: 2.2 ms, with all in step 2.44; the MFMAs
-// take 0.75 of it, the rest is the exponentials' and the pairs' vector instructions, which the two wavefronts of a SIMD share.  A ring of five blocks or priorities: no gain.)
+// take 0.75 of it, the rest is the exponentials' and the pairs' vector instructions, which the two wavefronts of a SIMD share.  A ring of five blocks or priorities: no gain.
+// Four wavefronts and 128 queries are not better for short sequences either, though half of the eight have nothing to do up to 128 tokens: 16 sequences x 32 heads x 128, forward pass, 4 -> 8
+// wavefronts, 72 tokens 0.237 -> 0.221 ms, 128 0.248 -> 0.242, 136 0.287 -> 0.259, 256 0.489 -> 0.451; 2 x 4 heads of 128 tokens 0.099 -> 0.098.)
 // Operands as for the stored probabilities: scores q_hi k_hi + q_lo k_hi + q_hi k_lo of half pairs (22 bits) or bf16 pairs, probabilities and values as pairs of 16-bit values in
 // three products, fp32 sums.
 #include "internal.h"
@@ -59,6 +61,7 @@ struct Args {
 };
 
 constexpr int NS = 4;      // blocks of 32 keys in the LDS ring
+constexpr int W = 8;       // wavefronts
 template <int DH> constexpr int ring_slot() { return 4 * 32 * 2 * DH; }
 
 template <int N>
@@ -69,10 +72,11 @@ __device__ __forceinline__ void phase_end() {      // nothing is moved across
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int DH, int W, bool F16>
+template <int DH, bool F16>
 __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
     constexpr int NKS = DH / 16, NCB = DH / 32, KB = 3 * DH / 32, BQ = 32 * W;
-    constexpr int KSEG = 32 * 2 * DH, KBYTES = 2 * KSEG, VPART = 32 * 2 * DH, SLOT = ring_slot<DH>(), NBLK = SLOT / 1024, LPW = (NBLK + W - 1) / W;
+    constexpr int KSEG = 32 * 2 * DH, KBYTES = 2 * KSEG, VPART = 32 * 2 * DH, SLOT = ring_slot<DH>(), NBLK = SLOT / 1024, LPW = NBLK / W;
+    static_assert(NBLK % W == 0, "every wavefront copies as many blocks");
     extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
     // an XCD takes consecutive items: the blocks of a head, longest first, walk the same keys side by side, and so do the heads of a group
     int item = blockIdx.x;
@@ -110,12 +114,12 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
 
     const unsigned lds0 = (unsigned)(unsigned long long)((__attribute__((address_space(3))) void*)smem);
     // block of 32 keys into its slot of the ring.  K: 1 KB blocks ((seg NCB + cb) 2 + rb), 16 keys x 64 bytes, pieces swizzled; V: (part DH / 16 + rb).  Keys
-    // beyond the sequence are read from earlier rows (their probabilities are zero); V^T is there, zeros, up to whole 64s.  This wavefront's LPW of them (a number of blocks that W
-    // does not divide: the last twice): address of the next block, bytes to the one after it, the last there is.
+    // beyond the sequence are read from earlier rows (their probabilities are zero); V^T is there, zeros, up to whole 64s.  This wavefront's LPW of them:
+    // address of the next block, bytes to the one after it, the last there is.
     const char* src[LPW]; unsigned step[LPW], voff[LPW]; int last[LPW];
 #pragma unroll
     for (int j = 0; j < LPW; ++j) {
-        const int b = min(wave_s + W * j, NBLK - 1);
+        const int b = wave_s + W * j;
         voff[j] = (unsigned)lane * 16u;
         if (b < KBYTES / 1024) {
             const int rb = b & 1, sc = b >> 1, cb = sc % NCB, seg = sc / NCB;
@@ -136,7 +140,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
         const bool ragged = !blocked && 32 * i + 32 > L;
 #pragma unroll
         for (int j = 0; j < LPW; ++j) {
-            const int b = min(wave_s + W * j, NBLK - 1);
+            const int b = wave_s + W * j;
             unsigned vo = voff[j];
             if (ragged && b < KBYTES / 1024) {
                 const int row = 16 * (b & 1) + (lane >> 2), piece = (lane & 3) ^ ((row >> 2) & 3);
@@ -211,7 +215,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
             for (int ks = 0; ks < NKS; ++ks) scores_step(smem, ks, hs);
             exponentials(0);
         }
-        const bool behind = W == 8 && wave_s >= 4;
+        const bool behind = wave_s >= 4;
         if (behind) phase_end();
         auto multiply_end = [&](int i) __attribute__((always_inline)) {
             if (i + NS - 1 < nblk) wait_loads_but<LPW>();      // all but the newest block's
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
             multiply_end(i);
             phase_end();
         }
-        if (W == 8 && !behind) phase_end();
+        if (!behind) phase_end();
     };
     if (half_ops) walk(std::true_type{});
     else walk(std::false_type{});
@@ -323,21 +327,20 @@ __global__ __launch_bounds__(256) void vt_blocks_kernel(const float* __restrict_
     }
 }
 
-template <int DH, int W, bool F16>
+template <int DH, bool F16>
 int launch(tboa_ctx* ctx, const Args& a) {
     constexpr int buf = NS * ring_slot<DH>(), rows = 32 * W * (DH + 8) * 2, cols = DH * (32 * W + 8) * 2, smem = buf > rows ? (buf > cols ? buf : cols) : rows > cols ? rows : cols;
-    TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_output_kernel<DH, W, F16>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
-    hipLaunchKernelGGL((attn_output_kernel<DH, W, F16>), dim3((unsigned)a.total), dim3(64 * W), smem, ctx->stream, a);
+    TB_HIP(ctx, hipFuncSetAttribute((const void*)attn_output_kernel<DH, F16>, hipFuncAttributeMaxDynamicSharedMemorySize, smem));
+    hipLaunchKernelGGL((attn_output_kernel<DH, F16>), dim3((unsigned)a.total), dim3(64 * W), smem, ctx->stream, a);
     TB_KERNEL_CHECK(ctx);
     return 0;
 }
-template <int W>
 int dispatch(tboa_ctx* ctx, int dh, const Args& a) {
     switch (dh) {
-        case 32: return a.f16 ? launch<32, W, true>(ctx, a) : launch<32, W, false>(ctx, a);
-        case 64: return a.f16 ? launch<64, W, true>(ctx, a) : launch<64, W, false>(ctx, a);
-        case 96: return a.f16 ? launch<96, W, true>(ctx, a) : launch<96, W, false>(ctx, a);
-        default: return a.f16 ? launch<128, W, true>(ctx, a) : launch<128, W, false>(ctx, a);
+        case 32: return a.f16 ? launch<32, true>(ctx, a) : launch<32, false>(ctx, a);
+        case 64: return a.f16 ? launch<64, true>(ctx, a) : launch<64, false>(ctx, a);
+        case 96: return a.f16 ? launch<96, true>(ctx, a) : launch<96, false>(ctx, a);
+        default: return a.f16 ? launch<128, true>(ctx, a) : launch<128, false>(ctx, a);
     }
 }
 
@@ -370,12 +373,11 @@ int attn_output(tboa_ctx* ctx, const AttnOutput& q) {
         TB_KERNEL_CHECK(ctx);
     }
     const long long heads = (long long)q.paths * q.S * q.Hq;
-    const bool wide = q.L > 128;      // eight wavefronts of 32 queries, or four
-    a.nqb = (int)cdiv64(q.L, wide ? 256 : 128);
+    a.nqb = (int)cdiv64(q.L, 32 * W);
     a.total = heads * a.nqb; a.runs = a.total % 8 == 0;
     if (a.total > 0x7fffffffLL) return tboa_fail(ctx, TBOA_EINVAL, "attn_output: grid too large");
     ProfRec rec{}; bool timed = false;
     if (ctx->prof_on) TB_TRY(prof_begin(ctx, TBOA_PROF_PV, 2.0 * 6.0 * heads * q.dh * (q.causal ? 0.5 * q.L * (q.L + 1.0) : (double)q.L * q.L), rec, timed));
-    TB_TRY(wide ? dispatch<8>(ctx, q.dh, a) : dispatch<4>(ctx, q.dh, a));
+    TB_TRY(dispatch(ctx, q.dh, a));
     return prof_end(ctx, rec, timed);
 }

@@ -217,7 +217,9 @@ int chol_status_f64(tboa_ctx* ctx, int status_slot) {
     return 0;
 }
 
-// Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores; the longest of them contract over n - 512 columns
+// Order from which (and number of matrices with which) the updates of 512 columns go to the integer matrix cores; the longest of them contract over n - 512 columns.
+// Whole factorisations, fp64 -> residues: 2 of 2048 1.99 -> 2.08 ms, 3 2.45 -> 2.37, 8 3.31 -> 3.30; one of 2048 1.81 -> 1.88, 2560 2.45 -> 2.46, 3008 3.20 -> 3.10, 3072 3.21 -> 3.10,
+// 3584 4.03 -> 3.81, 4096 4.85 -> 4.44, 8192 19.0 -> 12.4; below 2048 nothing is gained (4 of 1536 1.59 -> 1.67, 16 2.80 -> 2.92; 8 of 2047 3.67 -> 3.57).
 static bool chol_rns_pays(int n, int batch) { return n >= 2048 && (long long)n * n * batch >= 3072LL * 3072 && rns_takes(n, TB_FACT_OB, n - TB_FACT_OB); }
 
 // Matrices at a time: 30 bytes of residues per element, 8 GB or 8 matrices (40 of 5120 at once would take another 31 GB beside the 55 of a layer's fp64 matrices)
