@@ -299,8 +299,9 @@ int tboa_gemm_f64(tboa_ctx* ctx, int M, int N, int K, double alpha,
                   int batch, int64_t strideA, int64_t strideB, int64_t strideC);
 
 /* C = alpha A B + beta C in fp64 on the integer matrix cores: A (row-major, lda) and B (element (k, n) at B[k*sbk + n*sbn], one of the strides 1) are taken as integers of 57
- * and 58 bits below the 2-norm of each row of A and column of B, and the product modulo 15 numbers of 8 bits.  A result is off by at most 2^-56 |a_m| |b_n| plus its own
- * rounding (an fp64 product rounds every partial sum: about 2^-54.7 |a_m| |b_n| over terms of random sign).  A row or column that holds an infinity or NaN gives NaN.
+ * and 58 bits below the 2-norm of each row of A and column of B, and the product modulo 15 numbers of 8 bits.  A result is off by at most 0.75 sqrt(K) 2^-56 |a_m| |b_n|,
+ * 2^-57.6 |a_m| |b_n| or less as root mean square, plus its own rounding (an fp64 product rounds every partial sum: about 2^-54.7 |a_m| |b_n| over terms of random sign).  The bound is one of norms: where the
+ * columns of A differ much in size and the rows of B make up for it, as channels of a layer may, take the sizes out by powers of two first.  A row or column that holds an infinity or NaN gives NaN.
  * K <= 32768.  Operands in residues and residues of C take context workspace: 15 bytes per element, rows and columns rounded up to 256 for C. */
 int tboa_gemm_f64_residues(tboa_ctx* ctx, int M, int N, int K, double alpha, const double* A, int64_t lda,
                            const double* B, int64_t sbk, int64_t sbn, double beta, double* C, int64_t ldc);

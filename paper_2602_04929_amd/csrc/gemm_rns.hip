@@ -5,8 +5,8 @@
 // modulo 15 coprime numbers of 8 bits whose product is 2^116.8 (the Chinese remainder theorem; the scheme is that of Ozaki, Uchino and Imamura, "Ozaki Scheme II: A
 // GEMM-oriented emulation of floating-point matrix multiplication using an integer modular technique", 2025).  Each residue of C is one exact product of bytes.
 //
-// Error.  The sums are exact, what is rounded is the operands: 0.29 units an entry (root mean square), so that C is off by 0.41 x 2^-57 |a| |b| at most at the
-// unfavourable ends of the powers of two, plus the rounding of the result.  An fp64 product rounds every partial sum: 0.3 x 2^-53 |a| |b| over terms of random sign whatever
+// Error.  The sums are exact, what is rounded is the operands: half a unit an entry at most, 0.29 as root mean square, with norms of 2^56 and 2^57 units at least.  C is off by
+// 0.32 - 0.65 x 2^-57 |a| |b| (root mean square, by where the norms lie within their powers of two) and 0.75 sqrt(K) 2^-56 |a| |b| at most, plus the rounding of the result.  An fp64 product rounds every partial sum: 0.3 x 2^-53 |a| |b| over terms of random sign whatever
 // their number, more where they have one sign.
 // What the error is measured against are norms, not sum |a_k b_k|: contractions over channels of very different size take the sizes out by powers of two per channel, half of
 // them on either side (rns_channel_exps), and what no product reads does not count in a norm (RnsSource::before).
