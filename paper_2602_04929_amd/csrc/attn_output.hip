@@ -27,9 +27,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 namespace {
 
-__device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(voff), "s"(lds_addr), "s"(base) : "memory", "m0");
-}
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <bool F16>
@@ -64,8 +61,6 @@ constexpr int NS = 4;      // blocks of 32 keys in the LDS ring
 constexpr int W = 8;       // wavefronts
 template <int DH> constexpr int ring_slot() { return 4 * 32 * 2 * DH; }
 
-template <int N>
-__device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void phase_end() {      // nothing is moved across
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_barrier" ::: "memory");

@@ -52,11 +52,6 @@ constexpr int EXP = BT + 8;
 template <int DH>
 constexpr int attn_lds_bytes() { return 4 * 64 * 2 * DH + 2 * 64 * EXP * 4 + 2 * 2 * 2 * BT * 4 + 2 * 2 * BT * 4; }
 
-// one 1 KB block global -> LDS: lane l moves the 16 bytes at base + voff (voff = 16 l) to lds_addr + 16 l
-__device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(voff), "s"(lds_addr), "s"(base) : "memory", "m0");
-}
-
 // 2^x on the transcendental unit
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 

@@ -21,11 +21,6 @@ __device__ __forceinline__ double over_pivot(double v, double p) {
     return ldexp(v, -__builtin_amdgcn_frexp_exp(p)) * (p < INFINITY ? r : 0.0);
 }
 
-__device__ __forceinline__ double lane_value(double v, int lane) {      // of a lane that is the same for the wavefront
-    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane), hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
-    return __hiloint2double(hi, lo);
-}
-
 // status[0] = 1 + column of the first non-positive pivot (0 = fine), status[1] = batch index
 //
 // Latency-bound (one workgroup per matrix, between the updates of the factorisation): 64 columns that wait for each other.  The block is taken as 4 x 4 tiles of

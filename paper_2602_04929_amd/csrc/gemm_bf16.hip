@@ -440,12 +440,7 @@ constexpr int STAGE_ELEMS = (BM + BN) * FK;     // bf16 elements per stage: A ti
 
 // One stage = 8 LDS-direct loads per wavefront (4 blocks of the A tile, 4 of the B tile).  The per-lane byte offsets
 // are loop-invariant; the tile's k position lives in the uniform base pointers; M0 carries the LDS address of the
-// 1 KB block.  Written as inline assembly so that the compiler does not pair every later LDS read with a wait for
-// ALL outstanding loads (it cannot tell that the ring slot being filled is not the one being read); the explicit
-// s_waitcnt vmcnt(N) + barrier in the main loop is the synchronisation.
-__device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(voff), "s"(lds_addr), "s"(base) : "memory", "m0");
-}
+// 1 KB block.
 
 __device__ __forceinline__ bf16x8 read_frag32(const __hip_bfloat16* __restrict__ t, int row, int chunk) {
     return *(const bf16x8*)(t + row * FK + ((chunk ^ ((row >> 2) & 3)) * 8));
@@ -466,8 +461,6 @@ __device__ __forceinline__ void gate_up_rows(const Args& g, int wave, int lane, 
 // WAVES = 8: 512 threads, two wavefronts per SIMD, each owning 128 x 64 of the tile (128 accumulators, at most 256
 // registers).  With one wavefront per SIMD every cycle it spends issuing an LDS read or an LDS-direct load is a cycle
 // in which no MFMA is issued; with two, one wavefront's issue stalls fall into the shadow of the other's MFMAs.
-template <int N>
-__device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 
 // NS: stages in the LDS ring (NS - 1 of them in flight while one is multiplied)
 template <int WAVES, int NS, int KIND>

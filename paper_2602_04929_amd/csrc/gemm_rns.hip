@@ -347,11 +347,6 @@ __device__ __forceinline__ Range k_range(int K, int klo_m, int klo_n, int khi_n,
     return r;
 }
 
-__device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(voff), "s"(lds_addr), "s"(base) : "memory", "m0");
-}
-template <int N>
-__device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ i32x4 read_frag(const signed char* __restrict__ t, int row, int chunk) {
     return *(const i32x4*)(t + row * SK + ((chunk ^ ((row >> 2) & 3)) << 4));
 }

@@ -255,6 +255,20 @@ bool attn_output_supported(int L, int dh);
 size_t attn_output_v_elems(int dkv, int S, int L, int paths);
 int attn_output(tboa_ctx* ctx, const AttnOutput& q);
 
+// ---------------------------------------------------------------- device code that several files use
+// One 1 KB block global -> LDS: lane l moves the 16 bytes at base + voff to lds_addr + 16 l.  Written as inline assembly so that the compiler does not pair every later LDS read with a wait for
+// ALL outstanding loads (it cannot tell that the ring slot being filled is not the one being read); the explicit wait_loads_but + barrier of the main loops is the
+// synchronisation.
+__device__ __forceinline__ void lds_direct_16(unsigned voff, const char* base, unsigned lds_addr) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %2" ::"v"(voff), "s"(lds_addr), "s"(base) : "memory", "m0");
+}
+// waits until no more than the N newest loads are in flight, and for all LDS reads
+template <int N>
+__device__ __forceinline__ void wait_loads_but() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory"); }
+__device__ __forceinline__ double lane_value(double v, int lane) {      // of a lane that is the same for the wavefront
+    const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane), hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+    return __hiloint2double(hi, lo);
+}
 // element offset of (r, c) in a matrix kept in the 16 x 32 blocks the bf16 GEMM can read and write (TBOA_GEMM_*_TILED);
 // kb = leading dimension / 32
 __device__ __forceinline__ long long tboa_blocked_offset(long long r, long long c, long long kb) {

@@ -907,10 +907,6 @@ __global__ __launch_bounds__(256) void cd_group_sums_kernel(const double* __rest
     }
 }
 
-__device__ __forceinline__ double lane_of(double v, int l) {
-    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l), __builtin_amdgcn_readlane(__double2loint(v), l));
-}
-
 // The rows j0 .. j0 + nj of a head one after the other.  LDS: ds[g nj + row of the block], the changes of the block's scales so far; where they fit beside it the numerators
 // (lds & 1; else num_mem) and the diagonals Cg[g][g'][j][j] (lds & 2; else read from memory)
 __global__ __launch_bounds__(1024) void cd_group_chain_kernel(const double* __restrict__ Cg, const double* __restrict__ Ho, int dh, int ng, int j0, int nj, int lds,
@@ -960,7 +956,7 @@ __global__ __launch_bounds__(1024) void cd_group_chain_kernel(const double* __re
             double x = lane < ng ? num[lane] : 0.0, mine = 0.0;
             for (int g = 0; g < ng; ++g) {
                 const double c = hjj * cd[g * ng + own];      // (the diagonals of Cg[g][g'] and Cg[g'][g] are the same)
-                const double q = x * inv, step = lane_of(den > 0.0 ? __builtin_fma(__builtin_fma(-q, den, x), inv, q) : 0.0, g);
+                const double q = x * inv, step = lane_value(den > 0.0 ? __builtin_fma(__builtin_fma(-q, den, x), inv, q) : 0.0, g);
                 if (lane == g) mine = step;
                 if (lane > g) x = __builtin_fma(-c, step, x);
             }
