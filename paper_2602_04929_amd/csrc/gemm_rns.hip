@@ -29,6 +29,7 @@ constexpr int BM = 256, BN = 256, SK = 64, NS = 4;      // output tile; bytes of
 constexpr int STAGE_BYTES = (BM + BN) * SK;
 constexpr int KPAD = SK * NS;                           // contraction lengths and limits are whole turns of the ring
 constexpr int UNDEFINED = 0x7fffffff;                   // exponent of a row that holds an infinity or NaN
+constexpr int NOTHING = -(1 << 28);                     // and of one that is zero: smaller than any other
 
 // Sums of squares in three ranges, so that squares neither overflow nor vanish: entries beyond 2^400, below 2^-400, and the others
 struct Squares { double mid = 0.0, big = 0.0, tiny = 0.0; };
@@ -80,7 +81,7 @@ __device__ __forceinline__ int row_exponent(double mid, double big, double tiny,
     double v = mid + tiny * DOWN * DOWN; int e = 0;
     if (big > 0.0) { v = big + mid * DOWN * DOWN; e = 600; }
     else if (mid == 0.0) { v = tiny; e = -600; }
-    return v > 0.0 ? (ilogb(v) >> 1) + 1 + e - bits : 0;
+    return v > 0.0 ? (ilogb(v) >> 1) + 1 + e - bits : NOTHING;
 }
 __global__ __launch_bounds__(256) void rns_exps_kernel(int rows, const double* __restrict__ sq, long long sq_stride, int bits, int* __restrict__ e, long long e_stride) {
     const int r = blockIdx.x * 256 + threadIdx.x;
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(256) void rns_channel_sizes_kernel(const double* __
     const int k = blockIdx.x * 256 + threadIdx.x;
     if (k >= n) return;
     const double v = H[(long long)k * n + k];
-    size[k] = v > 0.0 && v < INFINITY ? ilogb(v) >> 1 : 0;
+    size[k] = v > 0.0 && v < INFINITY ? ilogb(v) >> 1 : v == 0.0 ? NOTHING : 0;
 }
 // Powers of two for a contraction over channels k between a weight's columns (sq: their squares in the three ranges) and rows of size 2^right[k]: the right operand times 2^x[k] and the
 // left one times 2^-x[k] are of one size in every channel, where |a| |b| is least and next to sum |a_k b_k|.  Later rows and columns of a layer also carry what compensation for the
@@ -104,32 +105,32 @@ __global__ __launch_bounds__(256) void rns_channel_sizes_kernel(const double* __
 __global__ __launch_bounds__(1024) void rns_channel_exps_kernel(int n, const double* __restrict__ sq, const int* __restrict__ size, const int* right, int* x) {      // (right may be x)
     __shared__ double red[16];
     __shared__ int top_s;
-    constexpr int NONE = -(1 << 28);      // nothing in the column, or something undefined
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     auto left_of = [&](int k) {
         const double m = sq[k], b = sq[n + k], t = sq[2LL * n + k];
         const int e = row_exponent(m, b, t, 0);
-        return m + b + t > 0.0 && e != UNDEFINED ? e : NONE;
+        return e != UNDEFINED ? e : NOTHING;
     };
-    if (threadIdx.x == 0) top_s = NONE;
+    if (threadIdx.x == 0) top_s = NOTHING;
     __syncthreads();
-    int top = NONE;
-    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NONE) top = max(top, l + size[k]); }
+    int top = NOTHING;
+    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NOTHING && size[k] != NOTHING) top = max(top, l + size[k]); }
     atomicMax(&top_s, top);
     __syncthreads();
     top = top_s;
     double sum = 0.0;
-    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NONE) sum += ldexp(1.0, 2 * (l + size[k] - top)); }
+    for (int k = threadIdx.x; k < n; k += 1024) { const int l = left_of(k); if (l != NOTHING && size[k] != NOTHING) sum += ldexp(1.0, 2 * (l + size[k] - top)); }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
     if (lane == 0) red[wave] = sum;
     __syncthreads();
     sum = 0.0;
     for (int w = 0; w < 16; ++w) sum += red[w];
-    const int least = top == NONE ? NONE : top + (ilogb(sum / n) >> 1) - 6;
+    const int least = top == NOTHING ? NOTHING : top + (ilogb(sum / n) >> 1) - 6;
     for (int k = threadIdx.x; k < n; k += 1024) {
-        const int r = right[k], l = least == NONE ? NONE : max(left_of(k), least - size[k]);
-        x[k] = l == NONE || r == UNDEFINED ? 0 : min(max((l - r) >> 1, -900), 900);
+        const int r = right[k], l = top == NOTHING || size[k] == NOTHING ? left_of(k) : max(left_of(k), least - size[k]);
+        // (a channel that is zero on the right must not count on the left, whatever its size there)
+        x[k] = r == NOTHING ? 900 : l == NOTHING || r == UNDEFINED ? 0 : min(max((l - r) >> 1, -900), 900);
     }
 }
 

@@ -91,3 +91,25 @@ def test_updates_of_channels_that_the_damping_holds(lib, rows, n):
     part = ctx.quantize_layer(W[:40].contiguous(), Hin, None, R, 1, bits=4, block=40, group=128)
     ctx.close()
     assert torch.equal(whole["codes"][:40], part["codes"])
+
+
+@pytest.mark.parametrize("rows,n,heads,kw", [(4096, 2950, 64, dict(bits=2, block=16)), (2112, 2948, 33, dict(bits=8, block=64))])
+def test_channels_without_deviation(lib, rows, n, heads, kw):
+    """Rows of R that are zero, beside others of 1e-13: what the weights are in those channels does not count in the products with R."""
+    g = torch.Generator(device="cuda").manual_seed(rows * 3 + n)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    dh, T = rows // heads, 4096
+    X = 1e-8 * (rnd(T, n) + 0.5 * rnd(T, 1)).double()
+    dev = 1e-8 * rnd(T, n).double()
+    dev[:, ::31] = 0.0
+    Hin, R = (X.T @ X).float(), (0.0125 * (dev.T @ X)).float().contiguous()
+    W = 0.02 * rnd(rows, n)
+    G = rnd(heads, 512, dh)
+    Hout = torch.matmul(G.transpose(1, 2).contiguous(), G).contiguous()
+    ctx = lib.Context()
+    whole = ctx.quantize_layer(W, Hin, Hout, R, heads, **kw)
+    part = ctx.quantize_layer(W[:dh].contiguous(), Hin, Hout[:1].contiguous(), R, 1, **kw)
+    ctx.close()
+    assert torch.equal(whole["codes"][:dh], part["codes"])
+    (a, ac), (b, bc) = whole["loss_per_head_terms"][0], part["loss_per_head_terms"][0]
+    assert abs(a - b) <= 2.0 ** -40 * b and abs(ac - bc) <= 2.0 ** -38 * abs(bc)
