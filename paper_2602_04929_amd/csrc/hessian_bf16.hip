@@ -1056,8 +1056,11 @@ int wide_half_product(tboa_ctx* ctx, int rows, int n, const double* W, const flo
         w.a = W; w.ld = n; w.rows = n; w.k = rows;      // (its columns)
         TB_TRY(rns_norms(ctx, w, 1, r.sq, 0, r.part));
         TB_TRY(rns_channel_sizes(ctx, n, T, r.size));
-        TB_TRY(rns_channel_exps(ctx, n, r.sq, r.size, r.size, r.x));
-        h.a = T; h.ld = n; h.kc = 1; h.rows = n; h.k = n; h.half = 1; h.kexp = r.x; h.ksign = 1;
+        // (the right side's sizes are those of its rows: a channel below 1e-22 has a diagonal entry that vanishes in fp32 and others that do not)
+        h.a = T; h.ld = n; h.kc = 1; h.rows = n; h.k = n;
+        TB_TRY(rns_row_exps(ctx, h, 0, r.x));
+        TB_TRY(rns_channel_exps(ctx, n, r.sq, r.size, r.x, r.x));
+        h.half = 1; h.kexp = r.x; h.ksign = 1;
         w.kc = 1; w.rows = rows; w.k = n; w.kexp = r.x; w.ksign = -1;
         TB_TRY(rns_rows(ctx, h, nullptr, 1, RNS_BITS_B, r.h));
         TB_TRY(rns_rows(ctx, w, nullptr, 1, RNS_BITS_A, r.w));
