@@ -6,7 +6,8 @@
 // d_h outputs of them.  Blocks of 32 keys of K^ (segments k_hi, k_lo) and V^T (hi, lo) are copied global -> LDS into a ring of four.  For each:
 //     S^T = K^ Q^T              a lane holds one query and 16 of the keys, 8 b + 4 (lane / 32) + j for b, j < 4
 //     r = running maximum of the query less 14 (0 for bf16), p = 2^(S - r) as (hi, lo) pair: half values below 2^14, whose low parts are normal numbers down to 2^-17 of the largest;
-//                               O^T and the sum are rescaled where a maximum has grown
+//                               O^T and the sum are rescaled where a maximum has grown.  Beyond |r| = 2^20 the difference to the maximum is taken before the
+//                               scale: r is rounded, and p would be 2^14 times up to half a unit of r, infinite as half from r = 2^25 on (both ways: the same time there)
 //     O^T += V^T P^T            the lane's 16 probabilities ARE the right operand of two 16-deep steps, if step s contracts over the keys 16 s + 4 (lane / 32) + {0 .. 3, 8 .. 11}:
 //                               V^T is stored with its keys in that order (vt_blocks_kernel), so that nothing is exchanged between lanes
 // The scores of block i + 1 and the product of block i are one run of MFMAs, the exponentials one run of vector instructions, with a barrier after each; of the two wavefronts of a
@@ -150,9 +151,11 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
 #pragma unroll
     for (int c = 0; c < NCB; ++c) O[c] = zero16;
     union { unsigned short h[8]; bf16x8 x; } ph[2], pl[2];
-    constexpr float UP = F16 ? 14.f : 0.f;
+    constexpr float UP = F16 ? 14.f : 0.f, LARGE = 0x1p20f;
     static_assert(ATTN_PROBS_HALF_SCALE == 16384.f, "2^14");
-    float r = -INFINITY, s[4] = {0.f, 0.f, 0.f, 0.f};      // (four sums: one over all keys is off by as much as the rest together)
+    // m: the maximum; r: what the exponents are taken from, m times the scale less UP; large: of this wavefront's r some are, and p = 2^((S - m) scale + UP)
+    float m = -INFINITY, r = -INFINITY, s[4] = {0.f, 0.f, 0.f, 0.f};      // (four sums: one over all keys is off by as much as the rest together)
+    bool large = false;
 
     const int kend = g.causal ? min(L, t0 + BQ) : L, nblk = __builtin_amdgcn_readfirstlane((kend + 31) / 32);
     const int mine = __builtin_amdgcn_readfirstlane(tq >= L ? 0 : g.causal ? min(nblk, tq / 32 + 1) : nblk);      // this wavefront's blocks
@@ -180,18 +183,28 @@ __global__ __launch_bounds__(64 * W, 2) void attn_output_kernel(Args g) {
         float vm = acc[0];
 #pragma unroll
         for (int e = 1; e < 16; ++e) vm = fmaxf(vm, acc[e]);
-        vm = fmaxf(vm, __shfl_xor(vm, 32, 64)) * sc2 - UP;
-        if (__any(vm > r)) {
-            const float rn = fmaxf(r, vm), f = r == -INFINITY ? 0.f : ex2(r - rn);
+        vm = fmaxf(vm, __shfl_xor(vm, 32, 64));
+        if (__any(vm > m)) {
+            const float mn = fmaxf(m, vm), rn = mn * sc2 - UP;
+            const bool was = large;
+            large = was || __any(fabsf(rn) > LARGE);
+            const float f = m == -INFINITY ? 0.f : ex2(was ? (m - mn) * sc2 : large ? __builtin_fmaf(-mn, sc2, r) + UP : r - rn);
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] *= f;
 #pragma unroll
             for (int c = 0; c < NCB; ++c)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) O[c][e] *= f;
-            r = rn;
+            m = mn; r = rn;
         }
-        const float ref = r == -INFINITY ? 0.f : -r;
+        float ref = m == -INFINITY ? 0.f : -r;
+        if (large) {
+            asm volatile("s_nop 0");
+            const float from = m == -INFINITY ? 0.f : m;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) acc[e] -= from;
+            ref = UP;
+        }
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const float a = ex2(__builtin_fmaf(acc[e], sc2, ref));

@@ -85,3 +85,28 @@ def test_hessian_of_the_output_projection(lib, dh, hq, hkv, S, L):
     bar = 2e-3 if L % 256 else 2e-6
     assert torch.linalg.norm(H - want) <= bar * torch.linalg.norm(want)
     assert torch.linalg.norm(R - dev) <= 10 * bar * torch.linalg.norm(dev)
+
+
+@pytest.mark.parametrize("up", [6, 10, 14])
+@pytest.mark.parametrize("dh,hq,hkv,S,L,causal", [(128, 4, 2, 2, 72, 1), (64, 4, 4, 2, 264, 0), (128, 2, 2, 2, 256, 1), (96, 2, 2, 2, 512, 1)])
+def test_large_scores(lib, dh, hq, hkv, S, L, causal, up):
+    """Scores of 1e7, 1e9 and 1e12, of which fp32 leaves units of 1, 64 and 65536 (correlated channels with heavy-tailed tokens reach 1e8): a softmax that picks one key.  Where the two largest scores
+    of a query are further apart than what the operands' 16 bits and fp32 sums leave of them, the output is the value of the larger; no output is undefined or larger than the values."""
+    print("attention_forward", dh, hq, hkv, S, L, causal, up, flush=True)
+    b = block(dh, hq, hkv, S, L)
+    wq, wk = b["Wq"] * 2.0 ** up, b["Wk"] * 2.0 ** up
+    ctx = lib.Context()
+    got = ctx.attention_forward(b["X"], wq, wk, b["Wv"], hq, hkv, dh, causal=bool(causal)).double().view(S, L, hq, dh)
+    ctx.close()
+    X, rep = b["X"].double(), hq // hkv
+    q, k, v = ((X @ w.double().T).view(S, L, -1, dh).transpose(1, 2) for w in (wq, wk, b["Wv"]))
+    k, v = k.repeat_interleave(rep, 1), v.repeat_interleave(rep, 1)
+    sc = torch.matmul(q, k.transpose(2, 3).contiguous()) / math.sqrt(dh)
+    if causal:
+        sc = sc.masked_fill(torch.ones(L, L, dtype=torch.bool, device="cuda").triu(1), -math.inf)
+    two, at = sc.topk(2, -1)
+    want = torch.gather(v, 2, at[..., :1].expand(-1, -1, -1, dh)).transpose(1, 2)
+    decided = (two[..., 0] - two[..., 1] > 2.0 ** -13 * q.norm(dim=-1) * k.norm(dim=-1).amax(-1, keepdim=True) / math.sqrt(dh) + 40.0).transpose(1, 2)
+    assert decided.double().mean() > 0.25
+    assert got.abs().amax() <= 1.01 * v.abs().amax()      # (no NaN either)
+    assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-4 * want.abs().max())[decided].all()
