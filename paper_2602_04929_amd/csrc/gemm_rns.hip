@@ -189,12 +189,13 @@ __global__ __launch_bounds__(256) void rns_grow_kernel(int rows, const double* _
     if (more) *ep = fresh || now == UNDEFINED ? now : now + 1;
     grown[blockIdx.z * e_stride + r] = more && !fresh;
 }
-// powers of two of the rows of V, H = V V^T: a row's norm is the root of H's diagonal entry.  None for an entry that is not positive; sum: nothing so far
+// powers of two of the rows of V, H = V V^T: a row's norm is the root of H's diagonal entry.  None for an entry that is not positive; sum: nothing so far.
+// (An infinite entry makes the damping and with it the whole diagonal infinite: V then has nothing beside its diagonal, as in fp64)
 __global__ __launch_bounds__(256) void rns_diagonal_exps_kernel(int n, const double* __restrict__ H, long long stride, int bits, int* __restrict__ e, double* __restrict__ sum, long long sum_stride) {
     const int r = blockIdx.x * 256 + threadIdx.x;
     if (r >= n) return;
     const double v = H[blockIdx.z * stride + (long long)r * (n + 1)];
-    e[blockIdx.z * (long long)n + r] = v > 0.0 ? row_exponent(v, 0.0, 0.0, bits) : UNDEFINED;
+    e[blockIdx.z * (long long)n + r] = !(v > 0.0) ? UNDEFINED : v < INFINITY ? row_exponent(v, 0.0, 0.0, bits) : 0;
     sum[blockIdx.z * sum_stride + r] = 0.0;
 }
 // The norms above are those of a positive definite H only.  A row whose squares so far (a wavefront sums those of the panel, in units of its power of two) are more than twice as many

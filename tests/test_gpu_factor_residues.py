@@ -3,6 +3,8 @@ whose columns of U outgrow their first power of two.
 
 Tolerance: the factors of order n of a matrix with condition number c leave U H U^T - I within a few n 2^-53 c of zero (c ~ 1e3 .. 1e7 here after scaling of the channels; the
 fp64 form leaves the same); compared with torch's factorisation in fp64 on the same matrices, which may be off by as much."""
+import math
+
 import pytest
 import torch
 
@@ -72,6 +74,23 @@ def test_diagonal_entries_that_are_not_positive(lib, value):
     ctx = lib.Context()
     with pytest.raises(lib.TurboBoAError, match="pivot 40 is not positive"):
         ctx.chol_inv_upper(H)
+    ctx.close()
+
+
+@pytest.mark.parametrize("n,batch", [(1000, 1), (2048, 3), (3100, 2)])
+def test_infinite_diagonal(lib, n, batch):
+    """The damping, a share of the diagonal's mean, is infinite where an entry is: H + inf I is its diagonal alone and U is zero, in fp64 (orders below 2048) and with residues."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn(n + 100, n, generator=g, device="cuda")
+    H = (x.T @ x)[None].repeat(batch, 1, 1)
+    want = H.clone()
+    H[-1, n // 2, n // 2] = math.inf
+    ctx = lib.Context()
+    U, rest = ctx.chol_inv_upper(H, damp=0.01), ctx.chol_inv_upper(want, damp=0.01)
+    assert (U[-1] == 0.0).all() and torch.equal(U[:-1], rest[:-1])
+    with pytest.raises(lib.TurboBoAError) as e:
+        ctx.quantize_layer(0.02 * x[:64].contiguous(), H[-1].contiguous(), None, None, 1, bits=2, block=64)
+    assert e.value.code == -5
     ctx.close()
 
 
