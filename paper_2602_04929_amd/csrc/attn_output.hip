@@ -7,7 +7,7 @@
 //     S^T = K^ Q^T              a lane holds one query and 16 of the keys, 8 b + 4 (lane / 32) + j for b, j < 4
 //     r = running maximum of the query less 14 (0 for bf16), p = 2^(S - r) as (hi, lo) pair: half values below 2^14, whose low parts are normal numbers down to 2^-17 of the largest;
 //                               O^T and the sum are rescaled where a maximum has grown.  Beyond |r| = 2^20 the difference to the maximum is taken before the
-//                               scale: r is rounded, and p would be 2^14 times up to half a unit of r, infinite as half from r = 2^25 on (both ways: the same time there)
+//                               scale: r is rounded, and p would be 2^14 times up to half a unit of r, infinite as half from r = 2^25 on
 //     O^T += V^T P^T            the lane's 16 probabilities ARE the right operand of two 16-deep steps, if step s contracts over the keys 16 s + 4 (lane / 32) + {0 .. 3, 8 .. 11}:
 //                               V^T is stored with its keys in that order (vt_blocks_kernel), so that nothing is exchanged between lanes
 // The scores of block i + 1 and the product of block i are one run of MFMAs, the exponentials one run of vector instructions, with a barrier after each; of the two wavefronts of a
